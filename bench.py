@@ -444,7 +444,7 @@ def main():
             }
         else:
             result["roofline"] = {
-                "bound": "alu", "kernel": "attn_generic", "achieved": tf, "peak": FP32_VALU_PEAK_TFLOPS,
+                "bound": "alu", "kernel": "attn_f32", "achieved": tf, "peak": FP32_VALU_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": tf / FP32_VALU_PEAK_TFLOPS, "traffic": None,
             }
         stages = {}

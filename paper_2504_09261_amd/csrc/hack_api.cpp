@@ -296,6 +296,12 @@ bool use_split_attention(const hack_ctx* ctx, int n_units, int N_k) {
   return (int64_t)n_units * ((N_k + tile - 1) / tile) <= ctx->split_max_items;
 }
 
+// Queries per attention work item of a launch.
+int attn_tile_rows(const hack_ctx* ctx, int n_units, int N_k) {
+  if (ctx->cfg.dtype == HACK_F32) return attn_f32_q_tile_rows(n_units, N_k);
+  return use_split_attention(ctx, n_units, N_k) ? attn_split_q_tile_rows() : kAttnTileRows;
+}
+
 // The 128-query bf16 kernel in its streamed form: the work items of the launch are cut into one run of
 // key blocks per resident work-group (plan_attn_stream), so that every work-group holds the same number of
 // blocks whatever the number and the lengths of the work items are; work items that a cut falls into are
@@ -328,8 +334,7 @@ constexpr int kStreamMinBlocks = 4;        // shortest segment a work item is cu
 bool use_stream_attention(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, int N_k, bool shared, AttnStreamPlan* plan) {
   if (ctx->cfg.dtype != HACK_BF16 || ctx->attn_kernel == 0 || ctx->attn_stream == 0 || ctx->attn_slots <= 0 || shared) return false;
   if (descs.empty()) return false;
-  const int tile = attn_q_tile_rows(ctx->cfg.dtype, ctx->cfg.head_dim, (int)descs.size(), N_k);
-  if (tile != 128) return false;
+  const int tile = kAttnTileRows;
   std::vector<int32_t> n_keys(descs.size());
   for (size_t i = 0; i < descs.size(); ++i) n_keys[i] = descs[i].n_out;
   if (ctx->attn_stream == 2) {
@@ -879,7 +884,7 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
     descs[u] = d;
   }
   const bool split = use_split_attention(ctx, U, N_k);
-  const int tile = split ? attn_split_q_tile_rows() : attn_q_tile_rows(ctx->cfg.dtype, ctx->cfg.head_dim, U, N_k);
+  const int tile = attn_tile_rows(ctx, U, N_k);
   std::vector<AttnItem> items;
   AttnStreamPlan plan;
   const bool streamed = !split && use_stream_attention(ctx, descs, N_k, false, &plan);
@@ -900,9 +905,12 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
     launch_attn_split(s, ctx->cfg.head_dim, (const UnitDesc*)(dev + o_desc), (const AttnItem*)(dev + o_items),
                       (int)items.size(), q, kv->k, kv->v, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale,
                       out);
+  else if (ctx->cfg.dtype == HACK_F32)
+    launch_attn_f32(s, ctx->cfg.head_dim, (const AttnItem*)(dev + o_items), (int)items.size(), tile, q, kv->k, kv->v, nullptr,
+                    nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale, out);
   else
-    launch_attn(s, ctx->cfg.dtype, ctx->cfg.head_dim, (const UnitDesc*)(dev + o_desc), (const AttnItem*)(dev + o_items),
-                (int)items.size(), tile, q, kv->k, kv->v, N_k, scale, out, ctx->attn_kernel);
+    launch_attn(s, ctx->cfg.head_dim, (const UnitDesc*)(dev + o_desc), (const AttnItem*)(dev + o_items), (int)items.size(), q,
+                kv->k, kv->v, N_k, scale, out, ctx->attn_kernel);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
 }
@@ -1098,9 +1106,12 @@ void launch_group_attention(hack_ctx* ctx, const StepGroup& g, const StepArgs& a
   else if (a.split)
     launch_attn_split(s, ctx->cfg.head_dim, g.ddev(), items, (int)g.items.size(), a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k,
                       a.cp.v, a.cp.pos, a.pos_new, a.fuse_append ? 1 : 0, a.N_k, a.scale, a.out);
+  else if (ctx->cfg.dtype == HACK_F32)
+    launch_attn_f32(s, ctx->cfg.head_dim, items, (int)g.items.size(), a.tile, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k,
+                    a.cp.v, a.cp.pos, a.pos_new, a.fuse_append ? 1 : 0, a.N_k, a.scale, a.out);
   else
-    launch_attn(s, ctx->cfg.dtype, ctx->cfg.head_dim, g.ddev(), items, (int)g.items.size(), a.tile, a.q, a.cp.k, a.cp.v, a.N_k,
-                a.scale, a.out, ctx->attn_kernel);
+    launch_attn(s, ctx->cfg.head_dim, g.ddev(), items, (int)g.items.size(), a.q, a.cp.k, a.cp.v, a.N_k, a.scale, a.out,
+                ctx->attn_kernel);
 }
 
 }  // namespace
@@ -1168,8 +1179,9 @@ static hack_status step_impl(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int3
   int32_t rows[kMaxObs];
   fill_q_rows(nullptr, a.n_obs, N_k, rows);
   a.split = use_split_attention(ctx, U, N_k);
-  a.fuse_append = a.split && n_comp == 0;   // no unit compresses: the attention launch appends as well
-  a.tile = a.split ? attn_split_q_tile_rows() : attn_q_tile_rows(ctx->cfg.dtype, ctx->cfg.head_dim, U, N_k);
+  // no unit compresses: the key-split bf16 kernel and the float32 kernel append as well
+  a.fuse_append = (a.split || ctx->cfg.dtype == HACK_F32) && n_comp == 0;
+  a.tile = attn_tile_rows(ctx, U, N_k);
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out; a.scale = scale;
   a.cp = CachePtrs{cache->k, cache->v, cache->pos};
   a.pos_new = (int32_t)cache->tokens_seen;

@@ -139,13 +139,20 @@ void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, in
                    int64_t idx_stride);
 size_t select_lds_bytes(int max_t_in);
 
-// Attention of N_k queries per unit over rows [out_off, out_off + n_out).
-// bf16_kernel: which bf16 kernel serves the 128-query work items, 1 = the deeper
+// bf16 attention of N_k queries per unit over rows [out_off, out_off + n_out), work items of 128 queries.
+// bf16_kernel: which kernel serves the 128-query work items, 1 = the deeper
 // software pipeline (default), 0 = the plain one-block pipeline (kept for A/B timing
 // and as a second implementation the tests run over the same shapes).
-void launch_attn(hipStream_t s, int dtype, int head_dim, const UnitDesc* descs, const AttnItem* items,
-                 int n_items, int q_tile_rows, const void* q, const void* k_cache,
-                 const void* v_cache, int N_k, float scale, void* out, int bf16_kernel);
+constexpr int kAttnTileRows = 128;
+void launch_attn(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, const void* q,
+                 const void* k_cache, const void* v_cache, int N_k, float scale, void* out, int bf16_kernel);
+// float32 attention; work items of q_tile_rows = attn_f32_q_tile_rows(units, N_k) queries (16 or 32); fuse and the
+// append arguments as in launch_attn_split.
+constexpr int kAttnF32SmallItems = 384;   // launches with at most this many 16-query items take those
+int attn_f32_q_tile_rows(int n_units, int N_k);
+void launch_attn_f32(hipStream_t s, int head_dim, const AttnItem* items, int n_items, int q_tile_rows, const void* q,
+                     const void* k_cache, const void* v_cache, const void* k_new, const void* v_new, void* k_app, void* v_app,
+                     int32_t* pos_app, int pos_new, int fuse, int N_k, float scale, void* out);
 // Streamed form of the 128-query bf16 kernel: work-group i serves segs[seg_begin[i] .. seg_begin[i+1]).
 // part_o: n_slots * 128 * head_dim floats, part_ml: n_slots * 256 floats, part_count: one zeroed
 // counter per cut work item (left zero).  Launches that share these arrays must not overlap.
@@ -180,7 +187,4 @@ void launch_merge(hipStream_t s, int head_dim, const UnitDesc* descs, const int3
                   int max_out, const void* k_in, const void* v_in, const void* k_new, const void* v_new, int N_k,
                   const int32_t* kept_idx, int64_t idx_stride, void* k_out, void* v_out, int32_t* nearest, float* weight,
                   float* inv_norm, int64_t ws_stride);
-// Query rows per attention work item for this dtype/head_dim and launch size.
-int attn_q_tile_rows(int dtype, int head_dim, int n_units, int N_k);
-
 }  // namespace hack

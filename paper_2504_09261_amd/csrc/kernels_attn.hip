@@ -19,8 +19,6 @@
 //     ring of four slots per tensor, one barrier per block; an XOR swizzle of
 //     16-byte chunks keeps the b128 K reads and the transposing V reads
 //     bank-conflict free.
-// fp32 path: one query per lane, fp32 FMA, K/V rows broadcast from LDS; exact
-// enough for the 1e-4 bar and only used for the small fp32 configuration.
 #include <type_traits>
 
 #include "device_util.h"
@@ -31,68 +29,6 @@ namespace hack {
 namespace {
 
 using namespace dev;
-
-// ---------------------------------------------------------------------------
-// fp32 / generic path
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ float ld_f(const float* p) { return *p; }
-__device__ __forceinline__ float ld_f(const __bf16* p) { return (float)(*p); }
-__device__ __forceinline__ void st_f(float* p, float v) { *p = v; }
-__device__ __forceinline__ void st_f(__bf16* p, float v) { *p = (__bf16)v; }
-
-constexpr int kGenQ = 64;   // queries per work-group (one per lane)
-constexpr int kGenKT = 32;  // keys per LDS tile
-
-template <typename T, int D>
-__global__ __launch_bounds__(kGenQ) void attn_generic(
-    const UnitDesc* __restrict__ descs, const AttnItem* __restrict__ items, const T* __restrict__ q,
-    const T* __restrict__ k_cache, const T* __restrict__ v_cache, int N_k, float scale,
-    T* __restrict__ out) {
-  const AttnItem it = items[blockIdx.x];
-  if (it.desc < 0) return;
-  const AttnItem& d = it;   // the item carries the descriptor fields read here
-  const int len = d.n_out;
-  const int qi = it.q_tile * kGenQ + threadIdx.x;
-  const bool qvalid = qi < N_k;
-  const int64_t qrow = (int64_t)d.unit * N_k + (qvalid ? qi : N_k - 1);
-
-  __shared__ float ks[kGenKT][D];
-  __shared__ float vs[kGenKT][D];
-
-  float qr[D], o[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    qr[c] = ld_f(q + qrow * D + c) * scale;
-    o[c] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  for (int t0 = 0; t0 < len; t0 += kGenKT) {
-    const int nk = min(kGenKT, len - t0);
-    __syncthreads();
-    for (int e = threadIdx.x; e < nk * D; e += kGenQ) {
-      const int r = e / D, c = e % D;
-      ks[r][c] = ld_f(k_cache + (d.out_off + t0 + r) * D + c);
-      vs[r][c] = ld_f(v_cache + (d.out_off + t0 + r) * D + c);
-    }
-    __syncthreads();
-    for (int r = 0; r < nk; ++r) {
-      float s = 0.f;
-#pragma unroll
-      for (int c = 0; c < D; ++c) s = fmaf(qr[c], ks[r][c], s);
-      const float mn = fmaxf(m, s);
-      const float a = __expf(m - mn), p = __expf(s - mn);
-      l = l * a + p;
-#pragma unroll
-      for (int c = 0; c < D; ++c) o[c] = fmaf(o[c], a, p * vs[r][c]);
-      m = mn;
-    }
-  }
-  if (qvalid) {
-    const float inv = 1.f / l;
-#pragma unroll
-    for (int c = 0; c < D; ++c) st_f(out + qrow * D + c, o[c] * inv);
-  }
-}
 
 // ---------------------------------------------------------------------------
 // bf16 MFMA path
@@ -803,12 +739,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_pipe(
 }  // namespace
 
 
-// Queries per work item.
-int attn_q_tile_rows(int dtype, int head_dim, int n_units, int N_k) {
-  (void)head_dim; (void)n_units; (void)N_k;
-  return dtype == 1 ? kGenQ : 128;
-}
-
 template <int D, int NW>
 static void launch_mfma_t(hipStream_t s, const UnitDesc* descs, const AttnItem* items, int n_items,
                           const void* q, const void* k_cache, const void* v_cache, int N_k,
@@ -822,22 +752,9 @@ static void launch_mfma_t(hipStream_t s, const UnitDesc* descs, const AttnItem* 
                        (const T*)q, (const T*)k_cache, (const T*)v_cache, N_k, scale, (T*)out);
 }
 
-void launch_attn(hipStream_t s, int dtype, int head_dim, const UnitDesc* descs, const AttnItem* items,
-                 int n_items, int q_tile_rows, const void* q, const void* k_cache,
-                 const void* v_cache, int N_k, float scale, void* out, int bf16_kernel) {
+void launch_attn(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, const void* q,
+                 const void* k_cache, const void* v_cache, int N_k, float scale, void* out, int bf16_kernel) {
   if (n_items <= 0) return;
-  (void)q_tile_rows;
-  if (dtype == 1) {
-    if (head_dim == 64)
-      hipLaunchKernelGGL((attn_generic<float, 64>), dim3(n_items), dim3(kGenQ), 0, s, descs, items,
-                         (const float*)q, (const float*)k_cache, (const float*)v_cache, N_k, scale,
-                         (float*)out);
-    else
-      hipLaunchKernelGGL((attn_generic<float, 128>), dim3(n_items), dim3(kGenQ), 0, s, descs, items,
-                         (const float*)q, (const float*)k_cache, (const float*)v_cache, N_k, scale,
-                         (float*)out);
-    return;
-  }
   if (head_dim == 64) launch_mfma_t<64, 4>(s, descs, items, n_items, q, k_cache, v_cache, N_k, scale, out, bf16_kernel);
   else launch_mfma_t<128, 4>(s, descs, items, n_items, q, k_cache, v_cache, N_k, scale, out, bf16_kernel);
 }

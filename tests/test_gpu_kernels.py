@@ -373,6 +373,62 @@ def test_attention_matches_oracle(dtype, d, Nk, lens, tol, kernel):
     hk.close()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Nk,lens", [
+    (5, 1, [1, 2, 16, 17, 127]),            # one query; block edges; fewer blocks than waves
+    (5, 17, [15, 31, 128, 129, 300]),       # ragged query tile; wave-split edges
+    (3, 48, [257, 33, 640]),
+    (26, 250, [1 + 13 * i for i in range(26)]),   # more than 384 tiles of 16 queries: the 32-query form, ragged tiles
+])
+def test_f32_attention_tile_edges(d, H, Nk, lens):
+    """Float32 sums of at most 640 terms and one exponential each: within 2e-5 of the fp64 result (outputs are
+    averages of values of unit variance; the observed worst is 4e-6)."""
+    u = _u()
+    rng = np.random.default_rng(5 * d + Nk)
+    hk = u.make_hack(heads=H, head_dim=d, dtype="f32", max_units=H, max_cache_len=640, max_queries=Nk)
+    q = u.rand_values(rng, (1, H, Nk, d), "f32")
+    rows = [(u.rand_values(rng, (n, d), "f32"), u.rand_values(rng, (n, d), "f32")) for n in lens]
+    cache, _ = u.build_cache(rows, d, "f32", pad_rows=3, fill=np.nan)   # rows of nobody must not be read into a result
+    out = torch.full((1, H, Nk, d), float("nan"), device=u.DEV)
+    scale = float(np.float32(1.0 / np.sqrt(d)))
+    hk.attn(u.to_dev(q, "f32"), cache, scale, out)
+    torch.cuda.synchronize()
+    got = u.from_dev(out)[0]
+    for h in range(H):
+        K, V = (x.astype(np.float64) for x in rows[h])
+        s = q[0, h].astype(np.float64) @ K.T * scale
+        p = np.exp(s - s.max(1, keepdims=True))
+        assert np.abs(got[h] - (p / p.sum(1, keepdims=True)) @ V).max() < 2e-5
+    hk.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_step_appends_in_the_attention_launch(d):
+    """Steps that do not compress: cached rows and position ids are exactly the concatenation, outputs those of hack_attn."""
+    u = _u()
+    rng = np.random.default_rng(d)
+    H = 3
+    hk = u.make_hack(heads=H, head_dim=d, dtype="f32", max_units=H, max_cache_len=512, max_queries=196)
+    mc = hk.managed_cache([300] * H)
+    want_k, want_v = [], []
+    for n in (1, 4, 37, 196):
+        q, k, v = (torch.from_numpy(u.rand_values(rng, (1, H, n, d), "f32")).to(u.DEV) for _ in range(3))
+        out, ref = torch.empty_like(q), torch.empty_like(q)
+        hk.step(mc, q, k, v, np.zeros(H, np.uint8), [1 << 30] * H, 5, 0.1, out)
+        hk.attn(q, mc.as_cache(), 0.1, ref)
+        want_k.append(k[0])
+        want_v.append(v[0])
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+    off, ln = mc.view()
+    K, V = torch.cat(want_k, 1), torch.cat(want_v, 1)
+    for h in range(H):
+        assert torch.equal(mc.k[off[h]:off[h] + ln[h]], K[h]) and torch.equal(mc.v[off[h]:off[h] + ln[h]], V[h])
+        assert torch.equal(mc.pos[off[h]:off[h] + ln[h]].cpu(), torch.arange(238, dtype=torch.int32))
+    mc.close()
+    hk.close()
+
+
 def test_cut_and_streamed_attention_launches_agree_with_whole_work_items():
     """Random unit counts, cache lengths and query counts: the 128-query kernel with every cut the pair
     model likes, and in its streamed form (equal runs of key blocks), against the same kernel on whole
