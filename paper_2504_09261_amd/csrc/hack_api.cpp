@@ -453,8 +453,8 @@ void run_score(hack_ctx* ctx, hipStream_t s, bool two_pass, unsigned long long* 
                const int32_t* rows_dev, int n_obs, int N_k, float scale, const void* k_cache, const void* k_new,
                float* importance, int64_t imp_stride) {
   if (ctx->cfg.dtype == HACK_F32) {
-    launch_score_generic(s, ctx->cfg.head_dim, ddev, list_dev, n_list, max_t, q, rows_dev, n_obs, N_k, scale, k_cache,
-                         k_new, ctx->stats, importance, imp_stride);
+    launch_score_f32(s, ctx->cfg.head_dim, ddev, list_dev, n_list, max_t, q, rows_dev, n_obs, N_k, scale, k_cache, k_new,
+                     ctx->stats, importance, imp_stride);
     return;
   }
   for (size_t g = 0; g + 1 < group_begin.size(); ++g)
@@ -517,7 +517,7 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   ctx->cfg = *cfg;
   ctx->elem_bytes = cfg->dtype == HACK_F32 ? 4 : 2;
   ctx->ws_stride = round_up(cfg->max_cache_len, 64);
-  ctx->max_chunks = (cfg->max_cache_len + kScoreChunk - 1) / kScoreChunk;
+  ctx->max_chunks = (cfg->max_cache_len + kScoreF32Chunk - 1) / kScoreF32Chunk;
   ctx->split_max_items = split_max_items_default(cfg->head_dim);
   ctx->spin_limit = kScoreSpinLimit;
   // test hook: a tiny limit makes the score kernel's bounded wait give up (every work-group still exits normally)
@@ -534,7 +534,8 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   const size_t n_ws = (size_t)cfg->max_units * ctx->ws_stride;
   if (e == hipSuccess) e = hipMalloc((void**)&ctx->importance, n_ws * sizeof(float));
   if (e == hipSuccess) e = hipMalloc((void**)&ctx->kept, n_ws * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&ctx->stats, (size_t)cfg->max_units * ctx->max_chunks * kMaxObs * 2 * sizeof(double));
+  if (e == hipSuccess && cfg->dtype == HACK_F32)
+    e = hipMalloc((void**)&ctx->stats, (size_t)cfg->max_units * ctx->max_chunks * kMaxObs * 2 * sizeof(double));
   ctx->score_groups = score_max_groups();   // exchange slots per unit: enough for every item size
   const size_t n_slots = (size_t)cfg->max_units * ctx->score_groups * kMaxObs;
   ctx->n_slots = n_slots;

@@ -59,7 +59,7 @@ struct CachePtrs {
   int32_t* pos;
 };
 
-constexpr int kScoreChunk = 256;   // keys per score work-group (fp32 path)
+constexpr int kScoreF32Chunk = 64; // keys per score work-group, the smallest of the fp32 path (sizes its workspace)
 constexpr int kMaxObs = 32;        // observation queries (one MFMA column block)
 
 // ---- kernel launchers (each validates nothing: the API layer has done so) ----
@@ -93,7 +93,6 @@ struct alignas(16) ScoreItem {
   int32_t n_groups;  // work-groups (sets of 4 items) of the unit
 };
 static_assert(sizeof(ScoreItem) == 32, "ScoreItem must stay 32 bytes");
-int score_item_keys(int dtype);
 int score_max_groups();   // work-groups per unit the fused kernel's exchange supports
 int score_fused_capacity(int head_dim, int item_keys);
 // two_pass: two launches (row sums, then importance) that read K twice but never wait inside
@@ -126,12 +125,12 @@ hipError_t score_static_setup(int device);   // once per device: finds the devic
 hipError_t launch_score_static(hipStream_t s, int device, int head_dim, const StaticScorePlan& plan, const void* q, int n_obs,
                                int N_k, float scale, const void* k_cache, const void* k_new, float* importance,
                                int64_t imp_stride, int* fault);
-// fp32: two passes over (chunk of 256 keys, listed unit); list[n_list] indexes
-// descs; stats is a workspace of n_list * ceil(max_t_in / 256) * 64 doubles.
-void launch_score_generic(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,
-                          int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
-                          const void* k_cache, const void* k_new, double* stats, float* importance,
-                          int64_t imp_stride);
+// fp32: two passes over (chunk of keys, listed unit); list[n_list] indexes
+// descs; stats is a workspace of n_list * ceil(max_t_in / kScoreF32Chunk) * 64 doubles.
+void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,
+                      int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
+                      const void* k_cache, const void* k_new, double* stats, float* importance,
+                      int64_t imp_stride);
 
 // Budgeted selection; one work-group per listed unit.
 void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list,

@@ -13,8 +13,8 @@
 // the logits in registers, publishes its work-group's row sums in a per-unit
 // exchange area, collects (bounded wait) those of the unit's other work-groups
 // and then writes importance_j = sum_i 2^t_ij / l_i from the parked logits.
-// fp32 (score_generic): two streaming passes over (unit, chunk of 256 keys),
-// plain fp64 FMA dot products, one key per lane:
+// fp32 (score_f32): two streaming passes over (unit, chunk of keys), fp64 dot
+// products on the matrix cores:
 //   pass 1  per chunk and observation row: max logit and sum of exp(logit - max)
 //   pass 2  combine the chunk partials of the unit, recompute the logits and
 //           write importance[j] = sum_i exp(s_ij - m_i) / l_i.
@@ -34,6 +34,7 @@ namespace {
 using namespace dev;
 
 constexpr int kThreads = 256;
+constexpr int kF32SmallGroups = 640;   // float32: launches of up to this many work-groups of 64 keys take them
 constexpr double kLog2e = 1.4426950408889634074;
 
 // 2^t for a double t with ~1 ulp float32 accuracy: the range reduction is done
@@ -46,16 +47,11 @@ __device__ __forceinline__ float exp2_split(double t) {
 }
 __device__ __forceinline__ double exp_neg(double x) { return (double)exp2_split(x * kLog2e); }
 
-__device__ __forceinline__ float to_float(float v) { return v; }
-__device__ __forceinline__ float to_float(__bf16 v) { return (float)v; }
-
-// Combine the per-chunk (reference, sum) partials of one unit into sm[i]
-// (reference) and sinv[i] (1 / normaliser) for the rows i < n_obs.  All 256
+// Combine the per-chunk (maximum, sum) partials of one unit into sm[i] (maximum) and
+// sinv[i] (1 / normaliser) for the rows i < n_obs.  All 256
 // threads take part: thread (g, i) = (tid / 32, tid % 32) folds the chunks
 // g, g + 8, ... of row i, then the eight groups are merged through LDS.
-// LOG2: the partials are in log2 units (MFMA path) instead of natural units.
 // Ends with a barrier: sm / sinv are ready for every thread on return.
-template <bool LOG2>
 __device__ __forceinline__ void combine_stats(const double* __restrict__ st, int n_chunks, int n_obs,
                                               double* sm, double* sinv, double (*red)[kMaxObs]) {
   const int i = threadIdx.x & 31, g = threadIdx.x >> 5;
@@ -70,7 +66,7 @@ __device__ __forceinline__ void combine_stats(const double* __restrict__ st, int
   double l = 0.0;
   for (int c = g; c < n_chunks; c += 8) {
     const double mc = st[(c * kMaxObs + i) * 2], lc = st[(c * kMaxObs + i) * 2 + 1];
-    l += lc * (LOG2 ? (double)exp2_split(mc - m) : exp_neg(mc - m));
+    l += lc * exp_neg(mc - m);
   }
   red[g][i] = l;
   __syncthreads();
@@ -78,83 +74,150 @@ __device__ __forceinline__ void combine_stats(const double* __restrict__ st, int
     l = red[0][i];
 #pragma unroll
     for (int k = 1; k < 8; ++k) l += red[k][i];
-    sm[i] = (i < n_obs) ? m : 0.0;  // unused rows: finite shift, zero weight
+    sm[i] = m;                          // unused rows repeat row 0: exponents stay <= 0, weight zero
     sinv[i] = (i < n_obs) ? 1.0 / l : 0.0;
   }
   __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
-// generic path (fp32 inputs; also usable for bf16): one key per lane, fp64 dots
+// float32 inputs: float64 dot products on the matrix cores
 // ---------------------------------------------------------------------------
-template <typename T, int D, int PASS>
-__global__ __launch_bounds__(kThreads) void score_generic(
+// A wave forms the logits of 32 observation rows against tiles of 16 keys with
+// v_mfma_f64_16x16x4_f64 (products and sums in float64, as exact as a chain of fp64
+// fused multiply-adds).  Lane (i, g) = (l % 16, l / 16) feeds step 4 c + e with element
+// 16 c + 4 g + e of its Q~ / K rows (any order of the contraction will do as long as
+// both operands agree), so operands come from global memory in 16-byte loads without
+// LDS; C register r of lane (i, g) is observation row 4 r + g, key i.  A work-group
+// takes a chunk of 64 TPW keys, its four waves TPW tiles each.
+// Latency bounds these launches (a 680-token schedule holds 44 Mflop of them), so the
+// chunk is 64 keys (TPW = 1) while that gives at most 640 work-groups; beyond that 256 keys
+// (TPW = 4), whose fewer partials are combined faster in pass 2.  Measured, us for both
+// passes, TPW 1 / 4: head_dim 64, 16 units x 680 keys 11.3 / 19.2, 32 x 680 (352
+// work-groups of 64 keys) 16.0 / 19.6, 64 x 1000 (1024) 27.0 / 22.2, 128 x 2000 79 / 59;
+// head_dim 128: 15.4 / 29.6, 24.1 / 29.8, 40.1 / 33.7, 132 / 98.  One key per lane with a
+// work-group reduction per observation row, the form this replaces, took 69 us at 16 x 680.
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double doublex4;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+
+// all-reduce over the 16 lanes of a row
+template <typename Op>
+__device__ __forceinline__ double row16_reduce(double v, Op op) {
+  v = op(v, dpp_mov_f64<0xB1>(v));
+  v = op(v, dpp_mov_f64<0x4E>(v));
+  v = op(v, dpp_mov_f64<0x141>(v));
+  return op(v, dpp_mov_f64<0x140>(v));
+}
+
+template <int D, int TPW, int PASS>
+__global__ __launch_bounds__(kThreads) void score_f32(
     const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, int max_chunks,
-    const T* __restrict__ q, const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale,
-    const T* __restrict__ k_cache, const T* __restrict__ k_new, double* __restrict__ stats,
+    const float* __restrict__ q, const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale,
+    const float* __restrict__ k_cache, const float* __restrict__ k_new, double* __restrict__ stats,
     float* __restrict__ importance, int64_t imp_stride) {
+  constexpr int C = D / 16;             // 16-byte pieces of a row per lane
+  constexpr int kChunk = 64 * TPW;      // keys per work-group
   const UnitDesc d = descs[list[blockIdx.y]];
   const int T_in = d.len_in + d.n_new;
-  const int key0 = blockIdx.x * kScoreChunk;
-  if (key0 >= T_in) return;
-  const int n_chunks = (T_in + kScoreChunk - 1) / kScoreChunk;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if ((int)blockIdx.x * kChunk >= T_in) return;
+  const int n_chunks = (T_in + kChunk - 1) / kChunk;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = lane & 15, g = lane >> 4;
+  const int key0 = blockIdx.x * kChunk + w * 16 * TPW;
 
-  __shared__ float qs[kMaxObs][D];
   __shared__ double red[8][kMaxObs];
+  __shared__ double red_m[4][kMaxObs];
   __shared__ double sm[kMaxObs], sinv[kMaxObs];
 
-  for (int e = tid; e < n_obs * D; e += kThreads) {
-    const int i = e / D, c = e % D;
-    qs[i][c] = to_float(q[((int64_t)d.unit * N_k + q_rows[i]) * D + c]);
-  }
-  double* st_unit = stats + (int64_t)blockIdx.y * max_chunks * kMaxObs * 2;
-  if (PASS == 2) combine_stats<false>(st_unit, n_chunks, n_obs, sm, sinv, red);
-  __syncthreads();
-
-  const int j = key0 + tid;
-  const bool valid = j < T_in;
-  const int jc = valid ? j : T_in - 1;
-  const T* krow = (jc < d.len_in) ? k_cache + (d.in_off + jc) * D
-                                  : k_new + ((int64_t)d.unit * N_k + (jc - d.len_in)) * D;
-  float kr[D];
+  // Q~ rows i and 16 + i (a row past n_obs repeats row 0; it gets weight zero)
+  floatx4 qf[2][C], kf[C];
 #pragma unroll
-  for (int c = 0; c < D; ++c) kr[c] = to_float(krow[c]);
+  for (int h = 0; h < 2; ++h) {
+    const int row = 16 * h + i;
+    const float* p = q + ((int64_t)d.unit * N_k + q_rows[row < n_obs ? row : 0]) * D + 4 * g;
+#pragma unroll
+    for (int c = 0; c < C; ++c) qf[h][c] = *reinterpret_cast<const floatx4*>(p + 16 * c);
+  }
+  auto load_k = [&](int t) {
+    const int j = min(key0 + 16 * t + i, T_in - 1);
+    const float* p = (j < d.len_in ? k_cache + (d.in_off + j) * D : k_new + ((int64_t)d.unit * N_k + (j - d.len_in)) * D) + 4 * g;
+#pragma unroll
+    for (int c = 0; c < C; ++c) kf[c] = *reinterpret_cast<const floatx4*>(p + 16 * c);
+  };
+  load_k(0);
+  double* st_unit = stats + (int64_t)blockIdx.y * max_chunks * kMaxObs * 2;
+  if (PASS == 2) combine_stats(st_unit, n_chunks, n_obs, sm, sinv, red);
+
+  double s[TPW][2][4];   // logits of tile t: observation row 16 h + 4 r + g, key i
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    doublex4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double kd = (double)kf[c][e];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qf[h][c][e], kd, acc[h], 0, 0, 0);
+      }
+    if (t + 1 < TPW) load_k(t + 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[t][h][r] = acc[h][r] * (double)scale;
+  }
 
   if (PASS == 1) {
-    for (int i = 0; i < n_obs; ++i) {
-      double acc = 0.0;
+    // this wave's maximum and sum per row, then the work-group's
 #pragma unroll
-      for (int c = 0; c < D; ++c) acc = fma((double)qs[i][c], (double)kr[c], acc);
-      const double s = acc * (double)scale;
-      double m = valid ? s : -INFINITY;
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) m = fmax(m, shfl_xor_f64(m, o));
-      if (lane == 0) red[w][i] = m;
-      __syncthreads();
-      m = fmax(fmax(red[0][i], red[1][i]), fmax(red[2][i], red[3][i]));
-      __syncthreads();
-      double l = valid ? exp_neg(s - m) : 0.0;
+      for (int r = 0; r < 4; ++r) {
+        double m = -INFINITY;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) l += shfl_xor_f64(l, o);
-      if (lane == 0) red[w][i] = l;
-      __syncthreads();
-      if (tid == 0) {
-        double* o2 = st_unit + ((int64_t)blockIdx.x * kMaxObs + i) * 2;
-        o2[0] = m;
-        o2[1] = red[0][i] + red[1][i] + red[2][i] + red[3][i];
+        for (int t = 0; t < TPW; ++t)
+          if (key0 + 16 * t + i < T_in) m = fmax(m, s[t][h][r]);
+        m = row16_reduce(m, [](double a, double b) { return fmax(a, b); });
+        double l = 0.0;
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+          if (key0 + 16 * t + i < T_in) l += exp_neg(s[t][h][r] - m);
+        l = row16_reduce(l, [](double a, double b) { return a + b; });
+        if (i == 0) {
+          red_m[w][16 * h + 4 * r + g] = m;
+          red[w][16 * h + 4 * r + g] = l;
+        }
       }
-      __syncthreads();
+    __syncthreads();
+    if (threadIdx.x < kMaxObs) {
+      const int row = threadIdx.x;
+      double m = red_m[0][row];     // finite: the chunk's first key exists, and wave 0 holds it
+#pragma unroll
+      for (int k = 1; k < 4; ++k) m = fmax(m, red_m[k][row]);
+      double l = 0.0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (red_m[k][row] > -INFINITY) l += red[k][row] * exp_neg(red_m[k][row] - m);
+      double* o2 = st_unit + ((int64_t)blockIdx.x * kMaxObs + row) * 2;
+      o2[0] = m;
+      o2[1] = l;
     }
   } else {
-    double imp = 0.0;
-    for (int i = 0; i < n_obs; ++i) {
-      double acc = 0.0;
 #pragma unroll
-      for (int c = 0; c < D; ++c) acc = fma((double)qs[i][c], (double)kr[c], acc);
-      imp += exp_neg(acc * (double)scale - sm[i]) * sinv[i];
+    for (int t = 0; t < TPW; ++t) {
+      double imp = 0.0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * h + 4 * r + g;
+          imp += exp_neg(s[t][h][r] - sm[row]) * sinv[row];
+        }
+      imp += shfl_xor_f64(imp, 16);
+      imp += shfl_xor_f64(imp, 32);
+      const int j = key0 + 16 * t + i;
+      if (g == 0 && j < T_in) importance[(int64_t)d.unit * imp_stride + j] = (float)imp;
     }
-    if (valid) importance[(int64_t)d.unit * imp_stride + j] = (float)imp;
   }
 }
 
@@ -173,7 +236,6 @@ __global__ __launch_bounds__(kThreads) void score_generic(
 // wait on their own copies (hand-placed s_waitcnt vmcnt), so they drift freely and
 // keep HBM busy.  Reading K fragments straight from HBM in operand layout would touch
 // 32 rows x 32 bytes per instruction and re-fetch every cache line several times.
-constexpr int kItemKeys = 128;                 // keys per wave item that the workspace sizes of the fp32 path refer to
 
 // Logits are parked in registers between the two halves of the fused kernel as
 // 32-bit fixed point, log2 units with 22 fractional bits: the quantisation moves
@@ -491,22 +553,20 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
   }
 }
 
-template <typename T, int D>
-void launch_generic(hipStream_t s, dim3 grid, const UnitDesc* descs, const int32_t* list,
-                    int max_chunks, const void* q, const int32_t* q_rows, int n_obs, int N_k,
-                    float scale, const void* k_cache, const void* k_new, double* stats,
-                    float* importance, int64_t imp_stride) {
-  hipLaunchKernelGGL((score_generic<T, D, 1>), grid, dim3(kThreads), 0, s, descs, list, max_chunks,
-                     (const T*)q, q_rows, n_obs, N_k, scale, (const T*)k_cache, (const T*)k_new,
-                     stats, importance, imp_stride);
-  hipLaunchKernelGGL((score_generic<T, D, 2>), grid, dim3(kThreads), 0, s, descs, list, max_chunks,
-                     (const T*)q, q_rows, n_obs, N_k, scale, (const T*)k_cache, (const T*)k_new,
-                     stats, importance, imp_stride);
+template <int D, int TPW>
+void launch_f32(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in, const float* q,
+                const int32_t* q_rows, int n_obs, int N_k, float scale, const float* k_cache, const float* k_new, double* stats,
+                float* importance, int64_t imp_stride) {
+  const int max_chunks = (max_t_in + 64 * TPW - 1) / (64 * TPW);
+  const dim3 grid(max_chunks, n_list);
+  hipLaunchKernelGGL((score_f32<D, TPW, 1>), grid, dim3(kThreads), 0, s, descs, list, max_chunks, q, q_rows, n_obs, N_k, scale,
+                     k_cache, k_new, stats, importance, imp_stride);
+  hipLaunchKernelGGL((score_f32<D, TPW, 2>), grid, dim3(kThreads), 0, s, descs, list, max_chunks, q, q_rows, n_obs, N_k, scale,
+                     k_cache, k_new, stats, importance, imp_stride);
 }
 
 }  // namespace
 
-int score_item_keys(int dtype) { return dtype == 1 ? kScoreChunk : kItemKeys; }
 int score_max_groups() { return kMaxGroups; }
 
 // Items (= waves) of one fused launch the device keeps resident at once, for items of item_keys keys.
@@ -668,16 +728,22 @@ hipError_t launch_score_static(hipStream_t s, int device, int head_dim, const St
   return hipGetLastError();
 }
 
-void launch_score_generic(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,
-                          int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
-                          const void* k_cache, const void* k_new, double* stats, float* importance,
-                          int64_t imp_stride) {
+void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,
+                      int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
+                      const void* k_cache, const void* k_new, double* stats, float* importance,
+                      int64_t imp_stride) {
   if (n_list <= 0 || max_t_in <= 0) return;
-  const int max_chunks = (max_t_in + kScoreChunk - 1) / kScoreChunk;
-  dim3 grid(max_chunks, n_list);
-#define HACK_ARGS s, grid, descs, list, max_chunks, q, q_rows, n_obs, N_k, scale, k_cache, k_new, stats, importance, imp_stride
-  if (head_dim == 64) launch_generic<float, 64>(HACK_ARGS);
-  else launch_generic<float, 128>(HACK_ARGS);
+  const bool small = (int64_t)n_list * ((max_t_in + kScoreF32Chunk - 1) / kScoreF32Chunk) <= kF32SmallGroups;
+  typedef float T;
+#define HACK_ARGS s, descs, list, n_list, max_t_in, (const T*)q, q_rows, n_obs, N_k, scale, (const T*)k_cache, (const T*)k_new, \
+                  stats, importance, imp_stride
+  if (head_dim == 64) {
+    if (small) launch_f32<64, 1>(HACK_ARGS);
+    else launch_f32<64, 4>(HACK_ARGS);
+  } else {
+    if (small) launch_f32<128, 1>(HACK_ARGS);
+    else launch_f32<128, 4>(HACK_ARGS);
+  }
 #undef HACK_ARGS
 }
 

@@ -208,6 +208,36 @@ def test_score_matches_oracle(dtype, d, Nk, lens):
     hk.close()
 
 
+@pytest.mark.parametrize("d,H,Nk,lens,n_obs,gain", [
+    (64, 4, 32, [0, 31, 32, 33], 32, 1.0),                  # exactly one chunk of 64 keys, one less, one more
+    (128, 4, 16, [0, 1, 47, 240], 16, 1.0),                 # one tile of 16 keys; half of the observation rows unused
+    (64, 2, 9, [3, 1000], 5, 60.0),                         # logits of thousands: only the maximum of a row is left
+    (64, 44, 40, [900 + i for i in range(44)], 32, 1.0),    # more than 640 chunks of 64 keys: chunks of 256
+    (128, 44, 40, [730 + i for i in range(44)], 7, 1.0),    # ... the last chunk of 256 begins at 768
+])
+def test_f32_score_chunk_edges(d, H, Nk, lens, n_obs, gain):
+    """Logits are fp64 dot products (error ~1e-16 of their terms); 2^x of the reduced argument carries about one float32
+    ulp (1.2e-7) per term, the stored importance half another one: 2e-7 relative, plus 1e-13 of a logit in absolute terms."""
+    u = _u()
+    rng = np.random.default_rng(d + H + Nk)
+    hk = u.make_hack(heads=H, head_dim=d, dtype="f32", max_units=H, max_cache_len=1100, max_queries=Nk)
+    scale = float(np.float32(gain / np.sqrt(d)))
+    rows = [(u.rand_values(rng, (n, d), "f32"),) * 2 for n in lens]
+    cin, _ = u.build_cache(rows, d, "f32", pad_rows=2, fill=np.nan)
+    q, k_new = u.rand_values(rng, (1, H, Nk, d), "f32"), u.rand_values(rng, (1, H, Nk, d), "f32")
+    imp = torch.full((H, 1100), -1.0, device=u.DEV)
+    hk.score(u.to_dev(q, "f32"), cin, scale, imp, k_new=u.to_dev(k_new, "f32"), n_obs=n_obs)
+    torch.cuda.synchronize()
+    got = imp.cpu().numpy().astype(np.float64)
+    obs = [(i * Nk) // n_obs for i in range(n_obs)]
+    for h in range(H):
+        K = np.concatenate([rows[h][0], k_new[0, h]]).astype(np.float64)
+        want = ho.importance(q[0, h][obs].astype(np.float64), K, scale)
+        assert np.all(np.abs(got[h, :len(K)] - want) <= 2e-7 * want + 1e-30 + (gain > 1) * 1e-10 * want)
+        assert np.all(got[h, len(K):] == -1.0)
+    hk.close()
+
+
 def test_score_many_units_split_into_launch_groups_and_repeated_calls():
     """More score work items than the device holds at once: the library must cut
     the launch into groups of whole units.  Calling twice on the same context
