@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <unordered_map>
@@ -100,14 +101,53 @@ struct hack_ctx {
   std::string err;
 };
 
+// What launching one group of a step's units needs once the launch tables are on the device (sizes, offsets into
+// the uploaded table, launch shapes); built by upload_group.
+struct StepGroup {
+  int n_desc = 0, n_comp = 0, n_merge = 0, n_items = 0, n_stream = 0;   // units, compressing / merging ones, attention work items, streamed work-groups
+  int max_t = 0, max_rows = 0, merge_t = 0, merge_out = 0;
+  bool streamed = false;                  // attention in the streamed form (then n_items is 0)
+  int item_keys = 0;
+  bool two_pass = false;
+  std::vector<int> launches;              // score launch groups
+  unsigned long long* slots = nullptr;    // row-sum exchange area of the group's score launches
+  const uint8_t* dev = nullptr;
+  size_t o_desc = 0, o_comp = 0, o_merge = 0, o_rows = 0, o_items = 0, o_sit = 0, o_segs = 0, o_segb = 0;
+  const UnitDesc* ddev() const { return reinterpret_cast<const UnitDesc*>(dev + o_desc); }
+};
+
+// A state of a managed cache (lengths, rows) together with the step that led to it and its launch plan.  The states
+// form a tree below the empty cache: a schedule that is repeated (every image, every replay of the same budgets)
+// walks the same path again, and a step whose arguments equal those of a child of the current state needs no planning:
+// comparing budgets and head classes is all that is left.  (Building descriptors and work lists and hashing the table
+// for every step took 230 us at 960 units, against 39 us of kernels.)
+struct StepNode {
+  // the step: plan inputs besides the parent's state
+  int32_t N_k = 0, n_init = 0;
+  bool final_merge = false, two_pass = false;
+  std::vector<uint8_t> head_type;   // [H]
+  std::vector<int32_t> budget;      // [units]
+  // its plan
+  int n_obs = 0, tile = 0, max_budget = 0;   // max_budget: rows the longest kept-index list needs
+  bool split = false, fuse_append = false, two_groups = false;
+  StepGroup g[2];
+  // the state after it
+  std::vector<uint8_t> cur;         // which slab holds the unit's rows
+  std::vector<int64_t> off;
+  std::vector<int32_t> len;
+  std::vector<std::unique_ptr<StepNode>> next;
+};
+constexpr int kMaxStepNodes = 512;   // per managed cache; beyond that the tree is dropped and grown again
+
 struct hack_kvcache {
   hack_ctx* ctx;
   int32_t n_units;
   std::vector<int32_t> cap;
   std::vector<int64_t> slab[2];
-  std::vector<uint8_t> cur;
-  std::vector<int64_t> off;
-  std::vector<int32_t> len;
+  StepNode root;                    // the empty cache
+  std::unique_ptr<StepNode> base;   // current state carried over when the tree was dropped
+  const StepNode* at = nullptr;     // current state
+  int n_nodes = 0;
   void* k;
   void* v;
   int32_t* pos;
@@ -984,12 +1024,13 @@ extern "C" hack_status hack_kvcache_create(hack_ctx* ctx, int32_t n_units, const
   c->ctx = ctx; c->n_units = n_units; c->k = k_mem; c->v = v_mem; c->pos = pos_mem; c->rows = mem_rows; c->tokens_seen = 0;
   c->cap.assign(cap, cap + n_units);
   c->slab[0].resize(n_units); c->slab[1].resize(n_units);
-  c->cur.assign(n_units, 0); c->len.assign(n_units, 0); c->off.resize(n_units);
+  c->root.cur.assign(n_units, 0); c->root.len.assign(n_units, 0); c->root.off.resize(n_units);
+  c->at = &c->root;
   int64_t r = 0;
   for (int u = 0; u < n_units; ++u) {
     c->slab[0][u] = r; r += round_up(cap[u], 8);
     c->slab[1][u] = r; r += round_up(cap[u], 8);
-    c->off[u] = c->slab[0][u];
+    c->root.off[u] = c->slab[0][u];
   }
   *out = c;
   return HACK_OK;
@@ -999,9 +1040,7 @@ extern "C" void hack_kvcache_destroy(hack_kvcache* c) { delete c; }
 
 extern "C" hack_status hack_kvcache_reset(hack_kvcache* c) {
   if (!c) return HACK_EINVAL;
-  for (int u = 0; u < c->n_units; ++u) {
-    c->len[u] = 0; c->cur[u] = 0; c->off[u] = c->slab[0][u];
-  }
+  c->at = &c->root;
   c->tokens_seen = 0;
   return HACK_OK;
 }
@@ -1009,33 +1048,19 @@ extern "C" hack_status hack_kvcache_reset(hack_kvcache* c) {
 extern "C" hack_status hack_kvcache_view(const hack_kvcache* c, hack_cache* view) {
   if (!c || !view) return HACK_EINVAL;
   view->k = c->k; view->v = c->v; view->pos = c->pos; view->rows = c->rows;
-  view->off = c->off.data(); view->len = c->len.data();
+  view->off = c->at->off.data(); view->len = c->at->len.data();
   return HACK_OK;
 }
 
 namespace {
 
-// The units of a step that are launched together on one stream, with their launch tables.
-struct StepGroup {
+// The units of a step that are launched together on one stream, before their tables are uploaded.
+struct GroupUnits {
   std::vector<UnitDesc> descs;            // copies of the group's unit descriptors
   std::vector<int32_t> comp, merging;     // indices into descs: units that compress / that also merge
-  int max_t = 0, max_rows = 0, merge_t = 0, merge_out = 0;
-  std::vector<AttnItem> items;
-  AttnStreamPlan plan;                    // attention in the streamed form (then `items` stays empty)
-  bool streamed = false;
-  std::vector<ScoreItem> sitems;
-  std::vector<int> launches;
-  int item_keys = 0;
-  bool two_pass = false;
-  unsigned long long* slots = nullptr;    // row-sum exchange area of the group's score launches
-  const uint8_t* dev = nullptr;
-  size_t o_desc = 0, o_comp = 0, o_merge = 0, o_rows = 0, o_items = 0, o_sit = 0, o_segs = 0, o_segb = 0;
-  const UnitDesc* ddev() const { return reinterpret_cast<const UnitDesc*>(dev + o_desc); }
 };
 
 struct StepArgs {
-  int N_k, n_obs, tile;
-  bool split, fuse_append, shared;   // shared: two groups of the step may attend at the same time
   const void *q, *k_new, *v_new;
   void* out;
   float scale;
@@ -1045,15 +1070,15 @@ struct StepArgs {
   int32_t pos_new;
 };
 
-void add_unit(StepGroup* g, const UnitDesc& d, bool merges, int N_k) {
-  const int idx = (int)g->descs.size();
-  g->descs.push_back(d);
+void add_unit(GroupUnits* u, StepGroup* g, const UnitDesc& d, bool merges, int N_k) {
+  const int idx = (int)u->descs.size();
+  u->descs.push_back(d);
   if (d.mode == MOVE_GATHER) {
-    g->comp.push_back(idx);
+    u->comp.push_back(idx);
     g->max_t = std::max(g->max_t, d.len_in + d.n_new);
     g->max_rows = std::max(g->max_rows, d.n_out);
     if (merges) {
-      g->merging.push_back(idx);
+      u->merging.push_back(idx);
       g->merge_t = std::max(g->merge_t, d.len_in + d.n_new);
       g->merge_out = std::max(g->merge_out, d.n_out);
     }
@@ -1062,57 +1087,161 @@ void add_unit(StepGroup* g, const UnitDesc& d, bool merges, int N_k) {
   }
 }
 
-hack_status upload_group(hack_ctx* ctx, StepGroup* g, const StepArgs& a, const int32_t* rows, hipStream_t s) {
-  g->streamed = !a.split && use_stream_attention(ctx, g->descs, a.N_k, a.shared, &g->plan);
-  if (!g->streamed) build_attn_items(g->descs, a.N_k, a.tile, &g->items);
-  if (ctx->cfg.dtype == HACK_BF16 && !g->comp.empty())
-    g->item_keys = plan_score_items(ctx, g->descs, g->comp, g->two_pass, &g->sitems, &g->launches);
+// shared: another group of the step may attend at the same time
+hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, bool shared, const int32_t* rows, hipStream_t s,
+                         StepGroup* g) {
+  AttnStreamPlan plan;
+  std::vector<AttnItem> items;
+  std::vector<ScoreItem> sitems;
+  g->streamed = !n.split && use_stream_attention(ctx, u.descs, n.N_k, shared, &plan);
+  if (!g->streamed) build_attn_items(u.descs, n.N_k, n.tile, &items);
+  if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty())
+    g->item_keys = plan_score_items(ctx, u.descs, u.comp, g->two_pass, &sitems, &g->launches);
+  g->n_desc = (int)u.descs.size();
+  g->n_comp = (int)u.comp.size();
+  g->n_merge = (int)u.merging.size();
+  g->n_items = (int)items.size();
+  g->n_stream = plan.n_groups;
   Table t;
-  g->o_desc = t.add(g->descs.data(), g->descs.size());
-  g->o_comp = t.add(g->comp.data(), g->comp.size());
-  g->o_merge = t.add(g->merging.data(), g->merging.size());
+  g->o_desc = t.add(u.descs.data(), u.descs.size());
+  g->o_comp = t.add(u.comp.data(), u.comp.size());
+  g->o_merge = t.add(u.merging.data(), u.merging.size());
   g->o_rows = t.add(rows, kMaxObs);
-  g->o_items = t.add(g->items.data(), g->items.size());
-  g->o_sit = t.add(g->sitems.data(), g->sitems.size());
-  g->o_segs = t.add(g->plan.segs.data(), g->plan.segs.size());
-  g->o_segb = t.add(g->plan.seg_begin.data(), g->plan.seg_begin.size());
+  g->o_items = t.add(items.data(), items.size());
+  g->o_sit = t.add(sitems.data(), sitems.size());
+  g->o_segs = t.add(plan.segs.data(), plan.segs.size());
+  g->o_segb = t.add(plan.seg_begin.data(), plan.seg_begin.size());
   return table_device(ctx, t, s, &g->dev);
 }
 
 // score -> select -> append / gather (-> merge) of a group's units
-void launch_chain(hack_ctx* ctx, const StepGroup& g, const StepArgs& a, hipStream_t s) {
+void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
   const int32_t* comp_dev = reinterpret_cast<const int32_t*>(g.dev + g.o_comp);
-  if (!g.comp.empty()) {
-    run_score(ctx, s, g.two_pass, g.slots, g.ddev(), comp_dev, (int)g.comp.size(), g.max_t,
+  if (g.n_comp > 0) {
+    run_score(ctx, s, g.two_pass, g.slots, g.ddev(), comp_dev, g.n_comp, g.max_t,
               reinterpret_cast<const ScoreItem*>(g.dev + g.o_sit), g.item_keys, g.launches, a.q,
-              reinterpret_cast<const int32_t*>(g.dev + g.o_rows), a.n_obs, a.N_k, a.scale, a.cp.k, a.k_new, ctx->importance,
+              reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->importance,
               ctx->ws_stride);
-    launch_select(s, g.ddev(), comp_dev, (int)g.comp.size(), g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride);
+    launch_select(s, g.ddev(), comp_dev, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride);
   }
-  if (!a.fuse_append)
-    launch_move(s, ctx->elem_bytes, ctx->cfg.head_dim, g.ddev(), (int)g.descs.size(), g.max_rows, a.cp, a.cp, a.k_new, a.v_new,
-                a.N_k, a.pos_new, a.kept, a.kstride);
-  if (!g.merging.empty())   // compression, the merge included, precedes the attention of the step
-    launch_merge(s, ctx->cfg.head_dim, g.ddev(), reinterpret_cast<const int32_t*>(g.dev + g.o_merge), (int)g.merging.size(),
-                 g.merge_t, g.merge_out, a.cp.k, a.cp.v, a.k_new, a.v_new, a.N_k, a.kept, a.kstride, a.cp.k, a.cp.v,
-                 ctx->merge_nn, ctx->merge_w, ctx->merge_inv, ctx->ws_stride);
+  if (!n.fuse_append)
+    launch_move(s, ctx->elem_bytes, ctx->cfg.head_dim, g.ddev(), g.n_desc, g.max_rows, a.cp, a.cp, a.k_new, a.v_new, n.N_k,
+                a.pos_new, a.kept, a.kstride);
+  if (g.n_merge > 0)   // compression, the merge included, precedes the attention of the step
+    launch_merge(s, ctx->cfg.head_dim, g.ddev(), reinterpret_cast<const int32_t*>(g.dev + g.o_merge), g.n_merge, g.merge_t,
+                 g.merge_out, a.cp.k, a.cp.v, a.k_new, a.v_new, n.N_k, a.kept, a.kstride, a.cp.k, a.cp.v, ctx->merge_nn,
+                 ctx->merge_w, ctx->merge_inv, ctx->ws_stride);
 }
 
-void launch_group_attention(hack_ctx* ctx, const StepGroup& g, const StepArgs& a, hipStream_t s) {
+void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
   const AttnItem* items = reinterpret_cast<const AttnItem*>(g.dev + g.o_items);
   if (g.streamed)
     launch_attn_stream(s, ctx->cfg.head_dim, g.ddev(), reinterpret_cast<const AttnSeg*>(g.dev + g.o_segs),
-                       reinterpret_cast<const int32_t*>(g.dev + g.o_segb), g.plan.n_groups, a.q, a.cp.k, a.cp.v, a.N_k, a.scale,
-                       a.out, ctx->part_o, ctx->part_ml, ctx->part_count);
-  else if (a.split)
-    launch_attn_split(s, ctx->cfg.head_dim, g.ddev(), items, (int)g.items.size(), a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k,
-                      a.cp.v, a.cp.pos, a.pos_new, a.fuse_append ? 1 : 0, a.N_k, a.scale, a.out);
+                       reinterpret_cast<const int32_t*>(g.dev + g.o_segb), g.n_stream, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out,
+                       ctx->part_o, ctx->part_ml, ctx->part_count);
+  else if (n.split)
+    launch_attn_split(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v,
+                      a.cp.pos, a.pos_new, n.fuse_append ? 1 : 0, n.N_k, a.scale, a.out);
   else if (ctx->cfg.dtype == HACK_F32)
-    launch_attn_f32(s, ctx->cfg.head_dim, items, (int)g.items.size(), a.tile, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k,
-                    a.cp.v, a.cp.pos, a.pos_new, a.fuse_append ? 1 : 0, a.N_k, a.scale, a.out);
+    launch_attn_f32(s, ctx->cfg.head_dim, items, g.n_items, n.tile, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v, a.cp.pos,
+                    a.pos_new, n.fuse_append ? 1 : 0, n.N_k, a.scale, a.out);
   else
-    launch_attn(s, ctx->cfg.head_dim, g.ddev(), items, (int)g.items.size(), a.q, a.cp.k, a.cp.v, a.N_k, a.scale, a.out,
-                ctx->attn_kernel);
+    launch_attn(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out, ctx->attn_kernel);
+}
+
+// The child of the cache's current state that these arguments lead to, if it is known.
+const StepNode* find_step(const hack_kvcache* c, int32_t N_k, const uint8_t* head_type, int H, const int32_t* budget, int U,
+                          int32_t n_init, bool final_merge, bool two_pass) {
+  for (const auto& p : c->at->next)
+    if (p->N_k == N_k && p->n_init == n_init && p->final_merge == final_merge && p->two_pass == two_pass &&
+        memcmp(p->head_type.data(), head_type, H) == 0 && memcmp(p->budget.data(), budget, (size_t)U * sizeof(int32_t)) == 0)
+      return p.get();
+  return nullptr;
+}
+
+// Validates and plans a step from the cache's current state, uploads its tables and adds it to the tree.
+hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k, const uint8_t* head_type, const int32_t* budget,
+                      int32_t n_init, bool final_merge, hipStream_t s, const StepNode** out) {
+  const int U = B * ctx->cfg.heads, H = ctx->cfg.heads;
+  for (int h = 0; h < H; ++h)
+    if (head_type[h] > 1) return fail(ctx, HACK_EINVAL, "head_type[%d] = %d is not a head class", h, head_type[h]);
+  std::unique_ptr<StepNode> n(new (std::nothrow) StepNode());
+  if (!n) return fail(ctx, HACK_EHIP, "out of host memory");
+  const StepNode& from = *cache->at;
+  std::vector<UnitDesc> descs(U);
+  int n_comp = 0, n_side = 0;
+  n->cur = from.cur;
+  n->off = from.off;
+  n->len.resize(U);
+  for (int u = 0; u < U; ++u) {
+    const int L = from.len[u];
+    const int64_t T = (int64_t)L + N_k;
+    if (budget[u] < 1) return fail(ctx, HACK_EINVAL, "budget[%d] = %d", u, budget[u]);
+    UnitDesc d{};
+    d.unit = u; d.in_off = from.off[u]; d.len_in = L; d.n_new = N_k;
+    if (budget[u] < T) {
+      if (T > ctx->cfg.max_cache_len) return fail(ctx, HACK_ECAPACITY, "unit %d: T_in = %lld exceeds max_cache_len %d", u, (long long)T, ctx->cfg.max_cache_len);
+      if (budget[u] > cache->cap[u]) return fail(ctx, HACK_ECAPACITY, "unit %d: budget %d exceeds its slab of %d rows", u, budget[u], cache->cap[u]);
+      n->cur[u] ^= 1;
+      n->off[u] = cache->slab[n->cur[u]][u];
+      n->max_budget = std::max(n->max_budget, budget[u]);
+      d.mode = MOVE_GATHER; d.n_out = budget[u];
+      plan_select(head_type[u % H], (int)T, budget[u], n_init, N_k, &d);
+      ++n_comp;
+      if (head_type[u % H] == HACK_CONTEXTUAL) ++n_side;
+    } else {
+      if (T > cache->cap[u]) return fail(ctx, HACK_ECAPACITY, "unit %d: %lld rows do not fit its slab of %d", u, (long long)T, cache->cap[u]);
+      d.mode = MOVE_APPEND; d.n_out = (int)T;
+    }
+    d.out_off = n->off[u];
+    n->len[u] = d.n_out;
+    descs[u] = d;
+  }
+  n->N_k = N_k;
+  n->n_init = n_init;
+  n->final_merge = final_merge;
+  n->two_pass = ctx->score_mode == HACK_SCORE_TWO_PASS;
+  n->head_type.assign(head_type, head_type + H);
+  n->budget.assign(budget, budget + U);
+  n->n_obs = std::min(ctx->cfg.n_obs, N_k);
+  n->split = use_split_attention(ctx, U, N_k);
+  // no unit compresses: the key-split bf16 kernel and the float32 kernel append as well
+  n->fuse_append = (n->split || ctx->cfg.dtype == HACK_F32) && n_comp == 0;
+  n->tile = attn_tile_rows(ctx, U, N_k);
+  int32_t rows[kMaxObs];
+  fill_q_rows(nullptr, n->n_obs, N_k, rows);
+
+  // group 0: the caller's stream; group 1 (optional): the compressing contextual units, beside group 0's attention
+  n->two_groups = ctx->step_overlap && ctx->cfg.dtype == HACK_BF16 && n_side > 0 && n_side < U;
+  GroupUnits units[2];
+  n->g[0].two_pass = n->two_pass;
+  n->g[0].slots = ctx->rowstat;
+  n->g[1].two_pass = true;          // leaves its sums in the slots, hence an exchange area of its own
+  n->g[1].slots = ctx->rowstat_side;
+  for (int u = 0; u < U; ++u) {
+    const bool ctxl = head_type[u % H] == HACK_CONTEXTUAL, compresses = descs[u].mode == MOVE_GATHER;
+    const int i = n->two_groups && ctxl && compresses ? 1 : 0;
+    add_unit(&units[i], &n->g[i], descs[u], final_merge && ctxl && compresses, N_k);
+  }
+  for (int i = 0; i < (n->two_groups ? 2 : 1); ++i) {
+    const hack_status st = upload_group(ctx, units[i], *n, n->two_groups, rows, s, &n->g[i]);
+    if (st != HACK_OK) return st;
+  }
+  if (cache->n_nodes >= kMaxStepNodes) {
+    // the tree is full (arguments that keep changing): keep the current state alone and start over
+    std::unique_ptr<StepNode> base(new (std::nothrow) StepNode());
+    if (!base) return fail(ctx, HACK_EHIP, "out of host memory");
+    base->cur = from.cur; base->off = from.off; base->len = from.len;
+    const bool at_root = cache->at == &cache->root;
+    cache->root.next.clear();
+    cache->base = std::move(base);   // drops the earlier one and what grew below it
+    cache->at = at_root ? &cache->root : cache->base.get();
+    cache->n_nodes = 0;
+  }
+  *out = n.get();
+  const_cast<StepNode*>(cache->at)->next.push_back(std::move(n));
+  ++cache->n_nodes;
+  return HACK_OK;
 }
 
 }  // namespace
@@ -1146,84 +1275,35 @@ static hack_status step_impl(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int3
   if (!aligned16(q) || !aligned16(k_new) || !aligned16(v_new) || !aligned16(out)) return fail(ctx, HACK_EINVAL, "q/k_new/v_new/out must be 16-byte aligned");
   if (!scale_ok(scale)) return fail(ctx, HACK_EINVAL, "scale must be finite and > 0");
   if (n_init < 0) return fail(ctx, HACK_EINVAL, "n_init must be >= 0");
-  for (int h = 0; h < H; ++h)
-    if (head_type[h] > 1) return fail(ctx, HACK_EINVAL, "head_type[%d] = %d is not a head class", h, head_type[h]);
   if (cache->tokens_seen + N_k > INT32_MAX) return fail(ctx, HACK_ECAPACITY, "token ids overflow int32");
 
   StepArgs a{};
   a.kept = kept_idx_opt ? kept_idx_opt : ctx->kept;
   a.kstride = kept_idx_opt ? idx_stride : ctx->ws_stride;
-  std::vector<UnitDesc> descs(U);
-  int n_comp = 0, n_side = 0;
-  for (int u = 0; u < U; ++u) {
-    const int L = cache->len[u];
-    const int64_t T = (int64_t)L + N_k;
-    if (budget[u] < 1) return fail(ctx, HACK_EINVAL, "budget[%d] = %d", u, budget[u]);
-    UnitDesc d{};
-    d.unit = u; d.in_off = cache->off[u]; d.len_in = L; d.n_new = N_k;
-    if (budget[u] < T) {
-      if (T > ctx->cfg.max_cache_len) return fail(ctx, HACK_ECAPACITY, "unit %d: T_in = %lld exceeds max_cache_len %d", u, (long long)T, ctx->cfg.max_cache_len);
-      if (budget[u] > cache->cap[u]) return fail(ctx, HACK_ECAPACITY, "unit %d: budget %d exceeds its slab of %d rows", u, budget[u], cache->cap[u]);
-      if (budget[u] > a.kstride) return fail(ctx, HACK_ECAPACITY, "idx_stride %lld < budget[%d] = %d", (long long)a.kstride, u, budget[u]);
-      d.mode = MOVE_GATHER; d.n_out = budget[u]; d.out_off = cache->slab[cache->cur[u] ^ 1][u];
-      plan_select(head_type[u % H], (int)T, budget[u], n_init, N_k, &d);
-      ++n_comp;
-      if (head_type[u % H] == HACK_CONTEXTUAL) ++n_side;
-    } else {
-      if (T > cache->cap[u]) return fail(ctx, HACK_ECAPACITY, "unit %d: %lld rows do not fit its slab of %d", u, (long long)T, cache->cap[u]);
-      d.mode = MOVE_APPEND; d.n_out = (int)T; d.out_off = cache->off[u];
-    }
-    descs[u] = d;
-  }
-  a.N_k = N_k;
-  a.n_obs = std::min(ctx->cfg.n_obs, N_k);
-  int32_t rows[kMaxObs];
-  fill_q_rows(nullptr, a.n_obs, N_k, rows);
-  a.split = use_split_attention(ctx, U, N_k);
-  // no unit compresses: the key-split bf16 kernel and the float32 kernel append as well
-  a.fuse_append = (a.split || ctx->cfg.dtype == HACK_F32) && n_comp == 0;
-  a.tile = attn_tile_rows(ctx, U, N_k);
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out; a.scale = scale;
   a.cp = CachePtrs{cache->k, cache->v, cache->pos};
   a.pos_new = (int32_t)cache->tokens_seen;
 
-  // group 0: the caller's stream; group 1 (optional): the compressing contextual units, beside group 0's attention
-  const bool two_groups = ctx->step_overlap && ctx->cfg.dtype == HACK_BF16 && n_side > 0 && n_side < U;
-  a.shared = two_groups;
-  StepGroup g[2];
-  g[0].two_pass = ctx->score_mode == HACK_SCORE_TWO_PASS;
-  g[0].slots = ctx->rowstat;
-  g[1].two_pass = true;          // leaves its sums in the slots, hence an exchange area of its own
-  g[1].slots = ctx->rowstat_side;
-  for (int u = 0; u < U; ++u) {
-    const bool ctxl = head_type[u % H] == HACK_CONTEXTUAL, compresses = descs[u].mode == MOVE_GATHER;
-    add_unit(&g[two_groups && ctxl && compresses ? 1 : 0], descs[u], final_merge && ctxl && compresses, N_k);
-  }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if ((st = upload_group(ctx, &g[0], a, rows, s)) != HACK_OK) return st;
-  if (two_groups && (st = upload_group(ctx, &g[1], a, rows, s)) != HACK_OK) return st;
+  const StepNode* n = find_step(cache, N_k, head_type, H, budget, U, n_init, final_merge, ctx->score_mode == HACK_SCORE_TWO_PASS);
+  if (!n && (st = plan_step(ctx, cache, B, N_k, head_type, budget, n_init, final_merge, s, &n)) != HACK_OK) return st;
+  if (n->max_budget > a.kstride)
+    return fail(ctx, HACK_ECAPACITY, "idx_stride %lld < largest budget %d of a compressing unit", (long long)a.kstride, n->max_budget);
 
-  launch_chain(ctx, g[0], a, s);
-  if (two_groups) {
+  launch_chain(ctx, *n, n->g[0], a, s);
+  if (n->two_groups) {
     HIP_TRY(ctx, hipEventRecord(ctx->ev_fork, s));
     HIP_TRY(ctx, hipStreamWaitEvent(ctx->aux_stream, ctx->ev_fork, 0));
   }
-  launch_group_attention(ctx, g[0], a, s);
-  if (two_groups) {
-    launch_chain(ctx, g[1], a, ctx->aux_stream);
-    launch_group_attention(ctx, g[1], a, ctx->aux_stream);
+  launch_group_attention(ctx, *n, n->g[0], a, s);
+  if (n->two_groups) {
+    launch_chain(ctx, *n, n->g[1], a, ctx->aux_stream);
+    launch_group_attention(ctx, *n, n->g[1], a, ctx->aux_stream);
     HIP_TRY(ctx, hipEventRecord(ctx->ev_join, ctx->aux_stream));
     HIP_TRY(ctx, hipStreamWaitEvent(s, ctx->ev_join, 0));
   }
   HIP_TRY(ctx, hipGetLastError());
-
-  for (int u = 0; u < U; ++u) {
-    if (descs[u].mode == MOVE_GATHER) {
-      cache->cur[u] ^= 1;
-      cache->off[u] = cache->slab[cache->cur[u]][u];
-    }
-    cache->len[u] = descs[u].n_out;
-  }
+  cache->at = n;
   cache->tokens_seen += N_k;
   return HACK_OK;
 }

@@ -41,7 +41,7 @@ class TableCache {
 
   // Device address of a table with exactly these bytes.
   TableStatus get(const uint8_t* bytes, size_t n, void* stream, const uint8_t** dev) {
-    const uint64_t h = fnv1a(bytes, n);
+    const uint64_t h = hash(bytes, n);
     auto range = index_.equal_range(h);
     for (auto it = range.first; it != range.second; ++it) {
       const Entry& e = it->second;
@@ -92,13 +92,29 @@ class TableCache {
   struct Entry {
     size_t chunk, offset, bytes;
   };
-  static uint64_t fnv1a(const uint8_t* p, size_t n) {
-    uint64_t h = 1469598103934665603ull;
-    for (size_t i = 0; i < n; ++i) {
-      h ^= p[i];
-      h *= 1099511628211ull;
+  // Four independent 8-byte lanes (multiply, fold the high half down), so that the multiplies overlap: a table of a
+  // few hundred kilobytes is hashed at memory speed instead of one multiply latency per byte (960 units: 25 us of
+  // 210 for the table of a step).  Equal hashes are told apart by comparing the contents.
+  static uint64_t hash(const uint8_t* p, size_t n) {
+    constexpr uint64_t kMul = 0x9E3779B97F4A7C15ull;
+    uint64_t h[4] = {n, n ^ kMul, n + kMul, ~n};
+    auto mix = [](uint64_t a, uint64_t v) {
+      a = (a ^ v) * kMul;
+      return a ^ (a >> 29);
+    };
+    size_t i = 0;
+    for (; i + 32 <= n; i += 32)
+      for (int k = 0; k < 4; ++k) {
+        uint64_t v;
+        memcpy(&v, p + i + 8 * k, 8);
+        h[k] = mix(h[k], v);
+      }
+    for (; i < n; i += 8) {
+      uint64_t v = 0;
+      memcpy(&v, p + i, n - i < 8 ? n - i : 8);
+      h[0] = mix(h[0], v);
     }
-    return h;
+    return mix(mix(mix(h[0], h[1]), h[2]), h[3]);
   }
 
   Backend be_;

@@ -348,6 +348,48 @@ def test_teacher_forced_steps_through_individual_calls():
     hk.close()
 
 
+def test_step_plans_are_kept_per_state_and_dropped_when_there_are_too_many():
+    """A managed cache remembers the plans of the steps it has seen: more different budgets than it keeps (the drop falls
+    between two steps of a schedule), budgets and classes seen before, and a fresh cache all give the same rows."""
+    u = _u()
+    H, d = 2, 64
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=64, max_queries=40)
+    rng = np.random.default_rng(3)
+    mc = hk.managed_cache([49] * H)
+    ten = [[u.to_dev(u.rand_values(rng, (1, H, n, d), "bf16"), "bf16") for _ in range(3)] for n in (40, 9)]
+    outs = [torch.empty_like(t[0]) for t in ten]
+
+    def walk(cache, budget, types):
+        cache.reset()
+        for (q, k, v), b, o in zip(ten, ([1 << 30] * H, budget), outs):
+            hk.step(cache, q, k, v, types, b, 5, 0.125, o)
+        torch.cuda.synchronize()
+        off, ln = cache.view()
+        assert list(ln) == list(budget)
+        return [cache.pos[o:o + n].clone() for o, n in zip(off, ln)] + [outs[1].clone()]
+
+    for i in list(range(600)) + [0, 599, 510, 511, 512]:
+        budget = [15 + i // 25, 15 + i % 25]
+        types = np.array([i % 2, 1], np.uint8)
+        got = walk(mc, budget, types)
+        if i in (0, 1, 509, 510, 511, 512, 513, 599):
+            fresh = hk.managed_cache([49] * H)
+            assert all(torch.equal(a, b) for a, b in zip(got, walk(fresh, budget, types))), i
+            fresh.close()
+    # the stride of a caller's index buffer is checked for remembered steps too
+    kept = torch.zeros((H, 16), dtype=torch.int32, device=u.DEV)
+    mc.reset()
+    q, k, v = ten[0]
+    hk.step(mc, q, k, v, np.ones(H, np.uint8), [1 << 30] * H, 5, 0.125, outs[0])
+    for _ in range(2):
+        with pytest.raises(HackError) as e:
+            hk.step(mc, *ten[1], np.ones(H, np.uint8), [20, 20], 5, 0.125, outs[1], kept_idx=kept)
+        assert e.value.status == -2
+    assert list(mc.view()[1]) == [40, 40]
+    mc.close()
+    hk.close()
+
+
 def test_step_capacity_and_argument_errors():
     u = _u()
     from paper_2504_09261_amd.binding import HackError
