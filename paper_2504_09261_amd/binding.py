@@ -41,7 +41,7 @@ class hack_config(C.Structure):
 
 class hack_cache(C.Structure):
     _fields_ = [("k", C.c_void_p), ("v", C.c_void_p), ("pos", C.c_void_p), ("rows", C.c_int64),
-                ("off", C.POINTER(C.c_int64)), ("len", C.POINTER(C.c_int32))]
+                ("off", C.c_void_p), ("len", C.c_void_p)]   # int64 / int32 host arrays
 
 
 _lib = None
@@ -60,7 +60,7 @@ def load_library() -> C.CDLL:
             "(there is no fallback path)")
     lib = C.CDLL(LIB_PATH)
     vp, i32, i64, f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
-    pi32, pi64, pu8 = C.POINTER(C.c_int32), C.POINTER(C.c_int64), C.POINTER(C.c_uint8)
+    pi32 = pi64 = pu8 = vp   # host arrays: an address, byref() or a ctypes array
     pcache = C.POINTER(hack_cache)
     lib.hack_create.argtypes = [C.POINTER(vp), C.POINTER(hack_config)]
     lib.hack_destroy.argtypes = [vp]
@@ -110,8 +110,23 @@ def _u8(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.uint8)
 
 
-def _p(a: Optional[np.ndarray], ctype):
-    return None if a is None else a.ctypes.data_as(C.POINTER(ctype))
+def _h(a: Optional[np.ndarray]):
+    """A host array as a pointer argument.  (ndarray.ctypes.data_as costs 5 us an array, more than a kernel launch;
+    this 0.4.)  The object keeps the array alive; for read-only or empty arrays the caller does."""
+    if a is None:
+        return None
+    try:
+        return C.byref(C.c_char.from_buffer(a))
+    except (TypeError, ValueError):
+        return a.__array_interface__["data"][0]
+
+
+def _addr(a: np.ndarray) -> int:
+    """Address of a host array for a structure member (the caller keeps the array alive)."""
+    try:
+        return C.addressof(C.c_char.from_buffer(a))
+    except (TypeError, ValueError):
+        return a.__array_interface__["data"][0]
 
 
 def _dev(t) -> Optional[int]:
@@ -121,9 +136,17 @@ def _dev(t) -> Optional[int]:
     return t.data_ptr()
 
 
+_raw_stream = None
+
+
 def _stream() -> int:
+    """hipStream_t of the current device's current stream."""
+    global _raw_stream
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        # the raw handle without building a torch.cuda.Stream object for every call
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", lambda _: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 class Cache:
@@ -137,7 +160,7 @@ class Cache:
 
     def struct(self) -> hack_cache:
         return hack_cache(_dev(self.k), _dev(self.v), _dev(self.pos), self.rows,
-                          _p(self.off, C.c_int64), _p(self.len, C.c_int32))
+                          _addr(self.off), _addr(self.len))
 
 
 class ManagedCache:
@@ -149,14 +172,14 @@ class ManagedCache:
         self.cap = _i32(cap)
         lib = hack.lib
         rows = C.c_int64()
-        hack._check(lib.hack_kvcache_rows_required(len(self.cap), _p(self.cap, C.c_int32), C.byref(rows)))
+        hack._check(lib.hack_kvcache_rows_required(len(self.cap), _h(self.cap), C.byref(rows)))
         self.rows = rows.value
         dev = torch.device("cuda", hack.device)
         self.k = torch.empty((self.rows, hack.head_dim), dtype=hack.torch_dtype, device=dev)
         self.v = torch.empty((self.rows, hack.head_dim), dtype=hack.torch_dtype, device=dev)
         self.pos = torch.empty((self.rows,), dtype=torch.int32, device=dev) if with_pos else None
         h = C.c_void_p()
-        hack._check(lib.hack_kvcache_create(hack.ctx, len(self.cap), _p(self.cap, C.c_int32), _dev(self.k),
+        hack._check(lib.hack_kvcache_create(hack.ctx, len(self.cap), _h(self.cap), _dev(self.k),
                                             _dev(self.v), _dev(self.pos), self.rows, C.byref(h)))
         self.handle = h
 
@@ -168,7 +191,8 @@ class ManagedCache:
         s = hack_cache()
         self.hack._check(self.hack.lib.hack_kvcache_view(self.handle, C.byref(s)))
         n = len(self.cap)
-        return np.ctypeslib.as_array(s.off, (n,)).copy(), np.ctypeslib.as_array(s.len, (n,)).copy()
+        return (np.frombuffer((C.c_int64 * n).from_address(s.off), np.int64).copy(),
+                np.frombuffer((C.c_int32 * n).from_address(s.len), np.int32).copy())
 
     def as_cache(self) -> Cache:
         off, ln = self.view()
@@ -238,8 +262,8 @@ class Hack:
         qi = None if q_idx is None else _i32(q_idx)
         act = None if active is None else _u8(active)
         cs = cache.struct()
-        self._check(self.lib.hack_score(self.ctx, B, Nk, _dev(q), _p(qi, C.c_int32), n_obs, scale, C.byref(cs),
-                                        _dev(k_new), _p(act, C.c_uint8), _dev(importance),
+        self._check(self.lib.hack_score(self.ctx, B, Nk, _dev(q), _h(qi), n_obs, scale, C.byref(cs),
+                                        _dev(k_new), _h(act), _dev(importance),
                                         importance.stride(0), _stream()))
 
     def score_static(self, q, cache: Cache, scale: float, importance, k_new=None, q_idx=None,
@@ -250,17 +274,17 @@ class Hack:
         qi = None if q_idx is None else _i32(q_idx)
         act = None if active is None else _u8(active)
         cs = cache.struct()
-        self._check(self.lib.hack_score_static(self.ctx, B, Nk, _dev(q), _p(qi, C.c_int32), n_obs, scale, C.byref(cs),
-                                               _dev(k_new), _p(act, C.c_uint8), _dev(importance),
+        self._check(self.lib.hack_score_static(self.ctx, B, Nk, _dev(q), _h(qi), n_obs, scale, C.byref(cs),
+                                               _dev(k_new), _h(act), _dev(importance),
                                                importance.stride(0), _stream()))
 
     # ---- a2 ----
     def select(self, B: int, importance, t_in, head_type, budget, n_init: int, n_recent: int, kept_idx) -> np.ndarray:
         t_in, budget, ht = _i32(t_in), _i32(budget), _u8(head_type)
         len_out = np.zeros(len(t_in), np.int32)
-        self._check(self.lib.hack_select(self.ctx, B, _dev(importance), importance.stride(0), _p(t_in, C.c_int32),
-                                         _p(ht, C.c_uint8), _p(budget, C.c_int32), n_init, n_recent,
-                                         _dev(kept_idx), kept_idx.stride(0), _p(len_out, C.c_int32), _stream()))
+        self._check(self.lib.hack_select(self.ctx, B, _dev(importance), importance.stride(0), _h(t_in),
+                                         _h(ht), _h(budget), n_init, n_recent,
+                                         _dev(kept_idx), kept_idx.stride(0), _h(len_out), _stream()))
         return len_out
 
     # ---- a3 ----
@@ -275,7 +299,7 @@ class Hack:
         ci, co = cache_in.struct(), cache_out.struct()
         act = None if active is None else _u8(active)
         self._check(self.lib.hack_merge(self.ctx, B, Nk, C.byref(ci), _dev(k_new), _dev(v_new), _dev(kept_idx),
-                                        kept_idx.stride(0), _p(act, C.c_uint8), C.byref(co), _stream()))
+                                        kept_idx.stride(0), _h(act), C.byref(co), _stream()))
 
     # ---- a4 ----
     def attn(self, q, cache: Cache, scale: float, out):
@@ -308,5 +332,5 @@ class Hack:
         ht, bud = _u8(head_type), _i32(budget)
         fn = self.lib.hack_step_final if final else self.lib.hack_step
         self._check(fn(self.ctx, cache.handle, B, Nk, _dev(q), _dev(k_new), _dev(v_new),
-                                       _p(ht, C.c_uint8), _p(bud, C.c_int32), n_init, scale, _dev(out),
+                                       _h(ht), _h(bud), n_init, scale, _dev(out),
                                        _dev(kept_idx), 0 if kept_idx is None else kept_idx.stride(0), _stream()))
