@@ -136,7 +136,6 @@ void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const 
 void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list,
                    int max_t_in, const float* importance, int64_t imp_stride, int32_t* kept_idx,
                    int64_t idx_stride);
-size_t select_lds_bytes(int max_t_in);
 
 // bf16 attention of N_k queries per unit over rows [out_off, out_off + n_out), work items of 128 queries.
 // bf16_kernel: which kernel serves the 128-query work items, 1 = the deeper

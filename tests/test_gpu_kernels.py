@@ -150,6 +150,36 @@ def test_select_ties_and_degenerate_segments():
     hk.close()
 
 
+@pytest.mark.parametrize("T", [1, 255, 1024, 1025, 2048, 2049, 4096, 4097, 8191, 8192, 8193, 16384, 16385, 32768])
+def test_select_every_size_class_and_digit(T):
+    """Both sides of every launch form, with importance whose threshold is settled by the first, second or last digit of
+    the keys, in ties of equal keys, and with rows that are not 16-byte aligned: exact."""
+    u = _u()
+    rng = np.random.default_rng(T)
+    pad = 1 if T % 2 else 4           # odd strides take the unaligned loads
+    stride = T + pad
+    spread = rng.lognormal(-6, 2, T)                                     # fifty octave pieces
+    close = (1.0 + rng.integers(0, 1 << 9, T) * 2.0 ** -23)              # equal but for the last nine bits
+    few = rng.integers(0, 3, T).astype(np.float64)                       # three values, zero among them
+    second = (1.0 + rng.permutation(T) * 2.0 ** -18)                     # inside one first-digit bin up to T = 2^15
+    imp_h = np.zeros((4, stride), np.float32)
+    for i, x in enumerate((spread, close, few, second)):
+        imp_h[i, :T] = x
+    hk = u.make_hack(heads=4, head_dim=64, dtype="bf16", max_units=4, max_cache_len=32768, max_queries=16)
+    imp = torch.from_numpy(imp_h).to(u.DEV)
+    for budget, n_init, n_recent, types in (((T + 1) // 2, 0, 0, [0, 0, 0, 0]), (max(1, T // 3), min(5, T // 4), T // 5, [1, 1, 0, 1]),
+                                            (1, 0, 0, [0, 0, 0, 0]), (max(1, T - 1), 0, min(3, T), [0, 1, 1, 0])):
+        kept = torch.full((4, stride), -1, dtype=torch.int32, device=u.DEV)
+        ln = hk.select(1, imp, [T] * 4, types, [budget] * 4, n_init, n_recent, kept)
+        torch.cuda.synchronize()
+        for h in range(4):
+            want = ho.select(imp_h[h, :T], types[h], budget, n_init, n_recent)
+            got = kept[h, :ln[h]].cpu().numpy()
+            assert np.array_equal(got, want), (T, h, budget)
+            assert torch.all(kept[h, ln[h]:] == -1)
+    hk.close()
+
+
 def test_select_rejects_bad_arguments():
     u = _u()
     hk = u.make_hack(heads=1, head_dim=64, dtype="bf16", max_units=1, max_cache_len=128, max_queries=16)

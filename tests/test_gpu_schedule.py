@@ -7,7 +7,7 @@ import torch
 
 from oracle import hack_oracle as ho
 from paper_2504_09261_amd import workload as wl
-from paper_2504_09261_amd.binding import Cache
+from paper_2504_09261_amd.binding import Cache, HackError
 
 pytestmark = pytest.mark.gpu
 
