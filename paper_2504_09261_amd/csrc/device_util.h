@@ -148,10 +148,11 @@ struct BlockStream {
       src[i] = (unsigned)(r * D + ((c ^ swz_k<D>(r)) & (CPR - 1)) * 8) * 2u;
     }
   }
-  __device__ __forceinline__ void issue(int b, int slot) const {
+  // full: the caller knows that all 32 rows of the block exist
+  __device__ __forceinline__ void issue(int b, int slot, bool full = false) const {
     const int r0 = b * 32;
     const __bf16* blk = base + (int64_t)r0 * D;
-    if (r0 + 32 <= n_rows) {
+    if (full || r0 + 32 <= n_rows) {
 #pragma unroll
       for (int i = 0; i < IPW; ++i)
         load_to_lds(blk, src[i], lds0 + (unsigned)((slot * BLK + (w + i * WAVES) * 512) * 2));

@@ -77,6 +77,30 @@ def test_head_variance_ragged_shapes_and_degenerate_cases():
         hk.close()
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("Nk,lens", [(96, [1, 96, 224]), (225, [225, 256, 257]), (257, [320, 353, 640])])
+def test_head_variance_pipeline_lengths_and_rising_logits(head_dim, Nk, lens):
+    """Lengths around the pipeline's fill, steady loop and drain on both sides, with keys that grow along the cache so
+    that pass 1 has to move its reference again and again.  Largest logit about 18 nats: a chained float32 dot product
+    is off by at most D 2^-24 times the sum of its |products|, here below 6e-6 nats, which moves a probability by
+    as much and sigma by twice that."""
+    u = _u()
+    rng = np.random.default_rng(100 * Nk + head_dim)
+    hk = u.make_hack(heads=3, head_dim=head_dim, dtype="bf16", max_units=3, max_cache_len=640, max_queries=Nk)
+    rows = [wl.bf16_to_f32(wl.bf16_round(u.rand_values(rng, (n, head_dim), "bf16") * np.linspace(0.1, 4.0, n, dtype=np.float32)[:, None]))
+            for n in lens]
+    cache, _ = u.build_cache([(k, k) for k in rows], head_dim, "bf16", pad_rows=3, fill=50.0)
+    Q = wl.bf16_to_f32(wl.bf16_round(u.rand_values(rng, (1, 3, Nk, head_dim), "bf16")))
+    scale = float(np.float32(head_dim ** -0.5))
+    sigma = torch.full((3,), -1.0, dtype=torch.float64, device=u.DEV)
+    hk.head_variance(u.to_dev(Q, "bf16"), cache, scale, sigma)
+    torch.cuda.synchronize()
+    for h in range(3):
+        want = ho.head_variance(Q[0, h].astype(np.float64), rows[h].astype(np.float64), scale)
+        assert abs(float(sigma[h]) - want) <= REL * max(want, 1e-3) + ABS, (h, float(sigma[h]), want)
+    hk.close()
+
+
 def test_head_variance_full_size_sampled_units_and_errors():
     """The 1024^2 benchmark shape (4096 queries x 10521 keys per unit) on the device;
     two units through the oracle."""
