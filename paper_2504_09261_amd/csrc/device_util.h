@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "hack_internal.h"
+
 namespace hack {
 namespace dev {
 
@@ -15,6 +17,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
+typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned uintx4;
 
 constexpr float kLog2eF = 1.4426950408889634f;
 
@@ -117,6 +120,47 @@ __device__ __forceinline__ double half_sum_f64(double v) {
   const int lo = __builtin_amdgcn_ds_swizzle(__double2loint(v), 0x401F);
   const int hi = __builtin_amdgcn_ds_swizzle(__double2hiint(v), 0x401F);
   return v + __hiloint2double(hi, lo);
+}
+
+// ---- cache update beside another kernel's work --------------------------------
+// A work-group takes one item: kMoveItemRows rows of a unit go to where the next step expects them.  All loads of a
+// thread (up to 8 pieces of K and of V, their positions) are in flight before its first store.
+template <int D, int THREADS>
+__device__ __forceinline__ void move_rows(const UnitDesc* __restrict__ descs, const GatherArgs& g, int item, int N_k) {
+  constexpr int LPR = D / 8, RPP = THREADS / LPR, PASSES = kMoveItemRows / RPP;   // 16-byte pieces per row, rows per pass
+  const int lane = threadIdx.x % LPR;
+  const MoveItem it = g.moves[item];
+  const UnitDesc d = descs[it.desc];
+  const bool gather = d.mode == MOVE_GATHER;
+  const int n_rows = gather ? d.n_out : d.n_new;
+  const int r0 = it.row0 + (int)threadIdx.x / LPR;
+  int s[PASSES];
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    const int i = min(r0 + p * RPP, n_rows - 1);
+    s[p] = gather ? g.kept[(int64_t)d.unit * g.kept_stride + i] : d.len_in + i;
+  }
+  uintx4 kr[PASSES], vr[PASSES];
+  int pos[PASSES];
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    const bool cached = s[p] < d.len_in;
+    const int64_t row = cached ? d.in_off + s[p] : (int64_t)d.unit * N_k + (s[p] - d.len_in);
+    kr[p] = (static_cast<const uintx4*>(cached ? g.cache.k : g.k_new))[row * LPR + lane];
+    vr[p] = (static_cast<const uintx4*>(cached ? g.cache.v : g.v_new))[row * LPR + lane];
+    pos[p] = g.pos_new + (s[p] - d.len_in);
+    if (cached && g.cache.pos != nullptr) pos[p] = g.cache.pos[row];
+  }
+  const int64_t dst0 = gather ? d.out_off : d.in_off + d.len_in;
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    const int i = r0 + p * RPP;
+    if (i < n_rows) {
+      static_cast<uintx4*>(g.cache.k)[(dst0 + i) * LPR + lane] = kr[p];
+      static_cast<uintx4*>(g.cache.v)[(dst0 + i) * LPR + lane] = vr[p];
+      if (g.cache.pos != nullptr && lane == 0) g.cache.pos[dst0 + i] = pos[p];
+    }
+  }
 }
 
 // ---- accumulator layout -----------------------------------------------------

@@ -28,6 +28,7 @@ namespace {
 
 constexpr size_t kTableChunkBytes = 32u << 20;   // launch tables: one chunk (device memory + pinned mirror)
 constexpr size_t kTableLimitBytes = 1u << 30;    // ... and all chunks of a context together
+constexpr int kIotaRows = 32768;                 // rows a unit that keeps everything may have where its list is read
 // Polls (each an atomic round trip plus a short sleep, ~1 us) a score wave spends waiting for the
 // other items of its unit before it gives up; real waits last a few microseconds.
 constexpr int kScoreSpinLimit = 1 << 18;
@@ -64,6 +65,8 @@ struct hack_ctx {
   // workspace
   float* importance = nullptr;   // [max_units, ws_stride]
   int32_t* kept = nullptr;       // [max_units, ws_stride]
+  int32_t* seam = nullptr;       // bf16 path: [max_units] kept rows of the step's selection that come from the cache
+  int32_t* iota = nullptr;       // bf16 path: [kIotaRows] 0, 1, 2, ...
   double* stats = nullptr;       // fp32 path: [max_units, max_chunks, 32, 2] softmax partials
   unsigned long long* rowstat = nullptr;  // bf16 path: [max_units, score_groups, 32] row-sum exchange slots, all-ones between launches
   unsigned long long* rowstat_side = nullptr;  // the same for the side branch of hack_step (two-pass form: its slots are not re-armed)
@@ -107,12 +110,14 @@ struct StepGroup {
   int n_desc = 0, n_comp = 0, n_merge = 0, n_items = 0, n_stream = 0;   // units, compressing / merging ones, attention work items, streamed work-groups
   int max_t = 0, max_rows = 0, merge_t = 0, merge_out = 0;
   bool streamed = false;                  // attention in the streamed form (then n_items is 0)
+  bool gathered = false;                  // attention reads the kept rows in place and updates the cache beside it (n_moves work-groups)
+  int n_moves = 0;
   int item_keys = 0;
   bool two_pass = false;
   std::vector<int> launches;              // score launch groups
   unsigned long long* slots = nullptr;    // row-sum exchange area of the group's score launches
   const uint8_t* dev = nullptr;
-  size_t o_desc = 0, o_comp = 0, o_merge = 0, o_rows = 0, o_items = 0, o_sit = 0, o_segs = 0, o_segb = 0;
+  size_t o_desc = 0, o_comp = 0, o_merge = 0, o_rows = 0, o_items = 0, o_sit = 0, o_segs = 0, o_segb = 0, o_moves = 0;
   const UnitDesc* ddev() const { return reinterpret_cast<const UnitDesc*>(dev + o_desc); }
 };
 
@@ -574,6 +579,13 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   const size_t n_ws = (size_t)cfg->max_units * ctx->ws_stride;
   if (e == hipSuccess) e = hipMalloc((void**)&ctx->importance, n_ws * sizeof(float));
   if (e == hipSuccess) e = hipMalloc((void**)&ctx->kept, n_ws * sizeof(int32_t));
+  if (e == hipSuccess && cfg->dtype == HACK_BF16) e = hipMalloc((void**)&ctx->seam, (size_t)cfg->max_units * sizeof(int32_t));
+  if (e == hipSuccess && cfg->dtype == HACK_BF16) e = hipMalloc((void**)&ctx->iota, kIotaRows * sizeof(int32_t));
+  if (e == hipSuccess && cfg->dtype == HACK_BF16) {
+    std::unique_ptr<int32_t[]> rows(new (std::nothrow) int32_t[kIotaRows]);
+    for (int i = 0; rows && i < kIotaRows; ++i) rows[i] = i;
+    e = rows ? hipMemcpy(ctx->iota, rows.get(), kIotaRows * sizeof(int32_t), hipMemcpyHostToDevice) : hipErrorOutOfMemory;
+  }
   if (e == hipSuccess && cfg->dtype == HACK_F32)
     e = hipMalloc((void**)&ctx->stats, (size_t)cfg->max_units * ctx->max_chunks * kMaxObs * 2 * sizeof(double));
   ctx->score_groups = score_max_groups();   // exchange slots per unit: enough for every item size
@@ -630,6 +642,8 @@ extern "C" void hack_destroy(hack_ctx* ctx) {
   if (!ctx) return;
   if (ctx->importance) (void)hipFree(ctx->importance);
   if (ctx->kept) (void)hipFree(ctx->kept);
+  if (ctx->seam) (void)hipFree(ctx->seam);
+  if (ctx->iota) (void)hipFree(ctx->iota);
   if (ctx->stats) (void)hipFree(ctx->stats);
   if (ctx->rowstat) (void)hipFree(ctx->rowstat);
   if (ctx->rowstat_side) (void)hipFree(ctx->rowstat_side);
@@ -792,7 +806,7 @@ extern "C" hack_status hack_select(hack_ctx* ctx, int32_t B, const float* import
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = table_device(ctx, t, s, &dev)) != HACK_OK) return st;
   launch_select(s, (const UnitDesc*)(dev + o_desc), (const int32_t*)(dev + o_list), U, max_t, importance, imp_stride,
-                kept_idx, idx_stride);
+                kept_idx, idx_stride, nullptr);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
 }
@@ -1097,6 +1111,16 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   if (!g->streamed) build_attn_items(u.descs, n.N_k, n.tile, &items);
   if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty())
     g->item_keys = plan_score_items(ctx, u.descs, u.comp, g->two_pass, &sitems, &g->launches);
+  // The key-split kernel reads the rows in place unless they change on the way (merge) or a unit's cache is longer than
+  // the list of a unit that keeps everything.
+  std::vector<MoveItem> moves;
+  g->gathered = n.split && !n.fuse_append && u.merging.empty();
+  for (const UnitDesc& d : u.descs) g->gathered = g->gathered && (d.mode == MOVE_GATHER || d.n_out <= kIotaRows);
+  if (g->gathered)
+    for (size_t i = 0; i < u.descs.size(); ++i)
+      for (int r = 0; r < (u.descs[i].mode == MOVE_GATHER ? u.descs[i].n_out : u.descs[i].n_new); r += kMoveItemRows)
+        moves.push_back(MoveItem{(int32_t)i, r});
+  g->n_moves = (int)moves.size();
   g->n_desc = (int)u.descs.size();
   g->n_comp = (int)u.comp.size();
   g->n_merge = (int)u.merging.size();
@@ -1111,6 +1135,7 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->o_sit = t.add(sitems.data(), sitems.size());
   g->o_segs = t.add(plan.segs.data(), plan.segs.size());
   g->o_segb = t.add(plan.seg_begin.data(), plan.seg_begin.size());
+  g->o_moves = t.add(moves.data(), moves.size());
   return table_device(ctx, t, s, &g->dev);
 }
 
@@ -1122,9 +1147,9 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
               reinterpret_cast<const ScoreItem*>(g.dev + g.o_sit), g.item_keys, g.launches, a.q,
               reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->importance,
               ctx->ws_stride);
-    launch_select(s, g.ddev(), comp_dev, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride);
+    launch_select(s, g.ddev(), comp_dev, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
   }
-  if (!n.fuse_append)
+  if (!n.fuse_append && !g.gathered)
     launch_move(s, ctx->elem_bytes, ctx->cfg.head_dim, g.ddev(), g.n_desc, g.max_rows, a.cp, a.cp, a.k_new, a.v_new, n.N_k,
                 a.pos_new, a.kept, a.kstride);
   if (g.n_merge > 0)   // compression, the merge included, precedes the attention of the step
@@ -1135,6 +1160,12 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
 
 void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
   const AttnItem* items = reinterpret_cast<const AttnItem*>(g.dev + g.o_items);
+  if (g.gathered) {
+    const GatherArgs ga{a.kept, a.kstride, ctx->seam, ctx->iota, reinterpret_cast<const MoveItem*>(g.dev + g.o_moves), g.n_moves,
+                        a.pos_new, a.k_new, a.v_new, a.cp};
+    launch_attn_split_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
+    return;
+  }
   if (g.streamed)
     launch_attn_stream(s, ctx->cfg.head_dim, g.ddev(), reinterpret_cast<const AttnSeg*>(g.dev + g.o_segs),
                        reinterpret_cast<const int32_t*>(g.dev + g.o_segb), g.n_stream, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out,

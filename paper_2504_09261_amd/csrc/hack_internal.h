@@ -42,13 +42,14 @@ struct alignas(16) AttnItem {
   int64_t out_off;  // UnitDesc::out_off
   int64_t in_off;   // UnitDesc::in_off
   int32_t len_in;   // UnitDesc::len_in
-  int32_t pad[3];
+  int32_t mode;     // UnitDesc::mode
+  int32_t pad[2];
 };
 static_assert(sizeof(AttnItem) == 48, "AttnItem must stay 48 bytes");
 inline AttnItem make_attn_item(const UnitDesc& d, int desc, int q_tile) {
   AttnItem it{};
   it.desc = desc; it.q_tile = q_tile; it.unit = d.unit; it.n_out = d.n_out; it.out_off = d.out_off; it.in_off = d.in_off;
-  it.len_in = d.len_in;
+  it.len_in = d.len_in; it.mode = d.mode;
   return it;
 }
 inline AttnItem attn_item_padding() { AttnItem it{}; it.desc = -1; return it; }
@@ -57,6 +58,28 @@ struct CachePtrs {
   void* k;
   void* v;
   int32_t* pos;
+};
+
+// Attention that performs the step's cache update itself: keys and values are read in place, row by row through the
+// unit's list of kept rows, while further work-groups of the same launch move those rows to where the next step
+// expects them.  An entry of a list is a row of the virtual concatenation [cached rows | rows of the current scale];
+// lists ascend, so all but one 32-row block of a unit come from one of the two homes.
+constexpr int kMoveItemRows = 128;   // rows per moving work-group
+struct alignas(8) MoveItem {
+  int32_t desc;   // index into the UnitDesc table
+  int32_t row0;   // first of the rows it moves
+};
+struct GatherArgs {
+  const int32_t* kept;     // [unit id, kept_stride] lists of the compressing units
+  int64_t kept_stride;
+  const int32_t* seam;     // [unit id] how many entries of that list are cached rows
+  const int32_t* iota;     // 0, 1, 2, ...: the list of a unit that keeps everything
+  const MoveItem* moves;
+  int32_t n_moves;         // moving work-groups, the last ones of the launch
+  int32_t pos_new;         // position of the current scale's first row
+  const void* k_new;
+  const void* v_new;
+  CachePtrs cache;         // written by the moving work-groups
 };
 
 constexpr int kScoreF32Chunk = 64; // keys per score work-group, the smallest of the fp32 path (sizes its workspace)
@@ -132,10 +155,11 @@ void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const 
                       const void* k_cache, const void* k_new, double* stats, float* importance,
                       int64_t imp_stride);
 
-// Budgeted selection; one work-group per listed unit.
+// Budgeted selection; one work-group per listed unit.  seam[unit id] (or NULL) gets the number of
+// kept rows below len_in; every unit must then have new rows.
 void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list,
                    int max_t_in, const float* importance, int64_t imp_stride, int32_t* kept_idx,
-                   int64_t idx_stride);
+                   int64_t idx_stride, int32_t* seam);
 
 // bf16 attention of N_k queries per unit over rows [out_off, out_off + n_out), work items of 128 queries.
 // bf16_kernel: which kernel serves the 128-query work items, 1 = the deeper
@@ -165,7 +189,12 @@ void launch_attn_stream(hipStream_t s, int head_dim, const UnitDesc* descs, cons
 // of k_new / v_new] (n_out = len_in + N_k) and also writes those rows (and their
 // positions pos_new + row, if pos_app != nullptr) behind the cached ones in
 // k_app / v_app / pos_app, i.e. it performs the append of the step as well.
+// launch_attn_split_gather: over the rows the units keep (n_out of each), read in place through g; g.n_moves further
+// work-groups update the cache.
 int attn_split_q_tile_rows();
+void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
+                              const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
+                              float scale, void* out);
 void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
                        void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale,

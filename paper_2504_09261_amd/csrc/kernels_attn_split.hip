@@ -18,7 +18,17 @@
 // equation of the Preliminaries): keys are then read from the virtual
 // concatenation [cached rows | rows of the current scale] and work item t
 // copies rows [32t, 32t+32) of the current scale behind the unit's cached rows,
-// so a step that does not compress needs a single launch.
+// so a step that does not compress needs a single launch.  A step that compresses
+// (GATHER) reads keys and values in place through the units' lists of kept rows,
+// and further work-groups of the launch move those rows: one launch less, and the
+// move beside the attention (one 256^2 image, seven compressing steps of 60 units,
+// 120 -> 111 us; odd sides 128 -> 121 us).  A wave copies the list entries of its next-but-one
+// block into an LDS ring of its own; all but one block of a unit lie wholly in the
+// cached or wholly in the new rows, so their rows are a wave-uniform base plus 32 bits.
+// The 128-query kernel gains nothing from the same: each of its work items pays 4 us for
+// the way through the list, and beside matrix work that already draws all the power the
+// chip may take, the moving work-groups cost what they cost alone (1024^2 schedules
+// 784 / 1267 / 3326 us as separate launches, 763 / 1254 / 3355 fused).
 #include "device_util.h"
 #include "hack_internal.h"
 
@@ -37,11 +47,11 @@ constexpr int kQTile = 32;     // queries per work item
 // ones (k_app / v_app / pos_app are the cache arrays, which k_cache / v_cache then
 // alias: reads stay below row len_in, writes at or above it).
 // fuse == 0: keys are rows [out_off, out_off + n_out) of the cache.
-template <int D>
+template <int D, bool GATHER>
 __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
     const UnitDesc* __restrict__ descs, const AttnItem* __restrict__ items, const __bf16* __restrict__ q,
     const __bf16* k_cache, const __bf16* v_cache, const __bf16* k_new, const __bf16* v_new, __bf16* k_app,
-    __bf16* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale, __bf16* __restrict__ out) {
+    __bf16* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale, __bf16* __restrict__ out, GatherArgs ga) {
   constexpr int KK = D / 16;        // MFMA steps over head_dim for S^T
   constexpr int MB = D / 32;        // 32-row blocks of O^T
   constexpr int CPR = D / 8;        // 16-byte chunks per row
@@ -49,6 +59,16 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
   constexpr int IPB = kKB / RPI;    // copy instructions per V block
   constexpr int BLK = kKB * D;      // elements per block
 
+  constexpr int XI = GATHER ? 1 : 0;   // list copies per block
+  // list entries of this wave's blocks w, w + 4, ...: block b in slot (b / 4) % 4 (a copy also fills the 32 words behind it)
+  __shared__ __attribute__((aligned(256))) int idx_ring[GATHER ? kWaves : 1][GATHER ? 4 * 2 * kKB : 1];
+  if constexpr (GATHER) {
+    const int mover = (int)blockIdx.x - ((int)gridDim.x - ga.n_moves);
+    if (mover >= 0) {
+      move_rows<D, 64 * kWaves>(descs, ga, mover, N_k);
+      return;
+    }
+  }
   const AttnItem it = items[blockIdx.x];
   if (it.desc < 0) return;
   const AttnItem& d = it;   // the item carries the descriptor fields read here
@@ -117,11 +137,60 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
       }
     }
   };
-  auto issue_k = [&](int b) { issue(b, k_cache, k_new, k_src, k_lds, true); };
-  auto issue_v = [&](int b) { issue(b, v_cache, v_new, v_src, v_lds, false); };
-
   const int n_blocks = (total + kKB - 1) / kKB;
+  const int32_t* list = nullptr;
+  int seam = 0;
+  const char *kc = nullptr, *vc = nullptr, *kn = nullptr, *vn = nullptr;   // row 0 of the list's numbering in the two homes
+  if constexpr (GATHER) {
+    const bool gather = d.mode == MOVE_GATHER;
+    list = gather ? ga.kept + (int64_t)d.unit * ga.kept_stride : ga.iota;
+    seam = gather ? ga.seam[d.unit] : d.len_in;
+    const int64_t rc = d.in_off * (D * 2), rn = (new_row0 - d.len_in) * (D * 2);
+    kc = reinterpret_cast<const char*>(k_cache) + rc;
+    vc = reinterpret_cast<const char*>(v_cache) + rc;
+    kn = static_cast<const char*>(ga.k_new) + rn;
+    vn = static_cast<const char*>(ga.v_new) + rn;
+  }
+  int* const ring = &idx_ring[GATHER ? w : 0][0];
+  const unsigned ring_lds = lds_addr_of(ring);
+  auto issue_x = [&](int b) {   // b = w + 4 i; past the end: entries of the last block
+    const int b0 = min(b, n_blocks - 1);
+    load_to_lds_dword(list + b0 * kKB, (unsigned)(min(lane, total - 1 - b0 * kKB) * 4), ring_lds + (unsigned)(((b >> 2) & 3) * 2 * kKB * 4));
+  };
+  auto issue_rows = [&](int b, const char* cached, const char* fresh, const unsigned (&src)[IPB], unsigned lds) {
+    const int j0 = b * kKB;
+    const int* x = ring + ((b >> 2) & 3) * 2 * kKB + lane / CPR;
+    if (j0 + kKB <= seam || j0 >= seam) {
+      const char* base = j0 >= seam ? fresh : cached;
+#pragma unroll
+      for (int i = 0; i < IPB; ++i) load_to_lds(base, (unsigned)x[i * RPI] * (unsigned)(D * 2) + (src[i] & (D * 2 - 1)), lds + (unsigned)(i * 1024));
+    } else {
+#pragma unroll
+      for (int i = 0; i < IPB; ++i) {
+        const int j = x[i * RPI];
+        load_to_lds((j < d.len_in ? cached : fresh) + (int64_t)j * (D * 2) + (src[i] & (D * 2 - 1)), lds + (unsigned)(i * 1024));
+      }
+    }
+  };
+  auto issue_k = [&](int b) {
+    if constexpr (GATHER) {
+      issue_x(b + 2 * kWaves);
+      issue_rows(b, kc, kn, k_src, k_lds);
+    } else {
+      issue(b, k_cache, k_new, k_src, k_lds, true);
+    }
+  };
+  auto issue_v = [&](int b) {
+    if constexpr (GATHER) issue_rows(b, vc, vn, v_src, v_lds);
+    else issue(b, v_cache, v_new, v_src, v_lds, false);
+  };
+
   if (w < n_blocks) {
+    if constexpr (GATHER) {
+      issue_x(w);
+      issue_x(w + kWaves);
+      dma_wait_but<0>();
+    }
     issue_k(w);
     issue_v(w);
   }
@@ -212,7 +281,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
       psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, psum, false);
     }
     l_run += psum;
-    if (more) dma_wait_but<IPB>();       // V(b) has landed (K(next) may still be in flight)
+    if (more) dma_wait_but<IPB + XI>();  // V(b) has landed (K(next) and list entries may still be in flight)
     else dma_wait_but<0>();
 #pragma unroll
     for (int sg = 0; sg < 2; ++sg) {
@@ -294,13 +363,29 @@ void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const
   if (n_items <= 0) return;
   typedef __bf16 T;
   if (head_dim == 64)
-    hipLaunchKernelGGL(attn_split<64>, dim3(n_items), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
+    hipLaunchKernelGGL((attn_split<64, false>), dim3(n_items), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
                        (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
-                       pos_app, pos_new, fuse, N_k, scale, (T*)out);
+                       pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
   else
-    hipLaunchKernelGGL(attn_split<128>, dim3(n_items), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
+    hipLaunchKernelGGL((attn_split<128, false>), dim3(n_items), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
                        (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
-                       pos_app, pos_new, fuse, N_k, scale, (T*)out);
+                       pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
+}
+
+void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
+                              const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
+                              float scale, void* out) {
+  const int n = n_items + g.n_moves;
+  if (n <= 0) return;
+  typedef __bf16 T;
+  if (head_dim == 64)
+    hipLaunchKernelGGL((attn_split<64, true>), dim3(n), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
+                       (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale,
+                       (T*)out, g);
+  else
+    hipLaunchKernelGGL((attn_split<128, true>), dim3(n), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
+                       (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale,
+                       (T*)out, g);
 }
 
 }  // namespace hack

@@ -70,7 +70,7 @@ template <int NT, int PER, int B0, int B1>
 __global__ __launch_bounds__(NT) void select_kernel(
     const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list,
     const float* __restrict__ importance, int64_t imp_stride, int32_t* __restrict__ kept_idx,
-    int64_t idx_stride) {
+    int64_t idx_stride, int32_t* __restrict__ seam) {
   constexpr int kWaves = NT / 64;
   constexpr int B2 = 32 - B0 - B1;
   constexpr int kHist = (1 << B0) + (1 << B1) + (1 << B2);
@@ -194,6 +194,8 @@ __global__ __launch_bounds__(NT) void select_kernel(
       }
   }
   int pos = block_exclusive_scan<kWaves>(__popc(keep), wave_tot[4]);
+  // how many kept rows precede row len_in, the first new one
+  if (seam != nullptr && d.len_in >= j0 && d.len_in < j0 + PER) seam[d.unit] = pos + __popc(keep & ((1u << (d.len_in - j0)) - 1u));
 #pragma unroll
   for (int e = 0; e < PER; ++e)
     if ((keep >> e) & 1u) out[pos++] = j0 + e;
@@ -203,11 +205,11 @@ __global__ __launch_bounds__(NT) void select_kernel(
 
 void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list,
                    int max_t_in, const float* importance, int64_t imp_stride, int32_t* kept_idx,
-                   int64_t idx_stride) {
+                   int64_t idx_stride, int32_t* seam) {
   if (n_list <= 0) return;
 #define HACK_SELECT(NT_, PER_, B0_, B1_)                                                                                      \
   hipLaunchKernelGGL((select_kernel<NT_, PER_, B0_, B1_>), dim3(n_list), dim3(NT_), 0, s, descs, list, importance, imp_stride, \
-                     kept_idx, idx_stride)
+                     kept_idx, idx_stride, seam)
   if (max_t_in <= 1024) HACK_SELECT(512, 2, 11, 11);
   else if (max_t_in <= 2048) HACK_SELECT(1024, 2, 12, 10);
   else if (max_t_in <= 4096) HACK_SELECT(1024, 4, 12, 10);

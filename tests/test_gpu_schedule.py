@@ -390,6 +390,62 @@ def test_step_plans_are_kept_per_state_and_dropped_when_there_are_too_many():
     hk.close()
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("with_pos", [True, False])
+def test_steps_that_read_kept_rows_in_place(head_dim, with_pos):
+    """The key-split kernel attends over the kept rows where they lie and moves them in the same launch.  The outputs
+    must be the bits that the same kernel gives over the moved rows, and the moved rows copies of the listed ones:
+    lists whose seam between cached and new rows falls inside a block, between blocks, before the first and behind the
+    last row; lengths around block and mover sizes; units that keep everything beside units that compress."""
+    from tests import gpu_util as u
+    B, H = 2, 4
+    sides_n = [7, 90, 64, 131, 33, 200, 1, 95]
+    hk = u.make_hack(heads=H, head_dim=head_dim, dtype="bf16", max_units=B * H, max_cache_len=sum(sides_n), max_queries=max(sides_n),
+                     attention="split")
+    types = np.array([0, 0, 1, 1], np.uint8)
+    budget = np.array([40, 64, 230, 10**6, 129, 31, 161, 10**6], np.int32)
+    mc = hk.managed_cache(np.minimum(np.maximum(budget, 100), sum(sides_n)), with_pos=with_pos)
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(head_dim)
+    stride = int(budget[budget < 10**6].max())
+    scale, ids = float(np.float32(head_dim ** -0.5)), 0
+    mask_seen = set()
+    for step, n in enumerate(sides_n):
+        q, kn, vn = (torch.randn((B, H, n, head_dim), generator=gen, device=u.DEV) for _ in range(3))
+        # heads 0: queries along e_0, keys of odd steps towards them and of even steps away from them
+        q[:, 0, :, 0] += 4
+        kn[:, 0, :, 0] += 6 if step % 2 else -6
+        q, kn, vn = (x.to(torch.bfloat16).contiguous() for x in (q, kn, vn))
+        off0, len0 = mc.view()
+        k0, v0 = mc.k.clone(), mc.v.clone()
+        p0 = mc.pos.clone() if with_pos else None
+        kept = torch.full((B * H, stride), -1, dtype=torch.int32, device=u.DEV)
+        out, want = torch.zeros_like(q), torch.zeros_like(q)
+        now = np.full_like(budget, 10**6) if step == 0 else budget
+        hk.step(mc, q, kn, vn, types, now, 5, scale, out, kept_idx=kept)
+        hk.attn(q, mc.as_cache(), scale, want)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), (step, n)
+        off, ln = mc.view()
+        for x in range(B * H):
+            b, h = divmod(x, H)
+            o0, l0, t = int(off0[x]), int(len0[x]), int(len0[x]) + n
+            rows = kept[x, :ln[x]].long() if now[x] < t else torch.arange(t, device=u.DEV)
+            assert ln[x] == min(int(now[x]), t) and bool((rows[1:] > rows[:-1]).all()) and 0 <= int(rows[0]) and int(rows[-1]) < t
+            if now[x] < t:
+                mask_seen.add("new" if int(rows[0]) >= l0 else "cached" if int(rows[-1]) < l0 else "both")
+            for got, old, new in ((mc.k, k0, kn), (mc.v, v0, vn)):
+                assert torch.equal(got[off[x]:off[x] + ln[x]], torch.cat([old[o0:o0 + l0], new[b, h]])[rows]), (step, x)
+            if with_pos:
+                src = torch.cat([p0[o0:o0 + l0], torch.arange(ids, ids + n, dtype=torch.int32, device=u.DEV)])
+                assert torch.equal(mc.pos[off[x]:off[x] + ln[x]], src[rows]), (step, x)
+        ids += n
+    assert mask_seen == {"new", "cached", "both"}
+    hk.check()
+    mc.close()
+    hk.close()
+
+
 def test_step_capacity_and_argument_errors():
     u = _u()
     from paper_2504_09261_amd.binding import HackError
