@@ -251,10 +251,31 @@ __device__ __forceinline__ int fix_from(double t_scaled) {  // t_scaled = t * 2^
   // what clamping the double first would (one three-operand median instead of two fp64 min / max)
   return min(max(__double2int_rn(t_scaled), -kFixLimit), kFixLimit);
 }
+// The same for a dot product well inside the clamp: adding 1.5 * 2^52 leaves the rounded integer in the low word.
+__device__ __forceinline__ int fix_from_small(double dot, double c2) { return __double2loint(fma(dot, c2, 6755399441055744.0)); }
 __device__ __forceinline__ double exp2_fix(int qv) {
-  const int n = qv >> 22;
   const float f = (float)(qv & 0x3FFFFF) * (float)(1.0 / kFixOne);  // [0, 1), exact
-  return ldexp((double)__builtin_amdgcn_exp2f(f), n);
+  const double m = (double)__builtin_amdgcn_exp2f(f);               // [1, 2]; the integer part goes to the exponent field
+  return __hiloint2double(__double2hiint(m) + ((qv >> 22) << 20), __double2loint(m));
+}
+// Row sums of a wave, through 8 KiB of LDS: put_row leaves the value of register r (observation row c_row(r, half), column
+// col) of every lane, take_rows returns the sum of row lane / 2 over the 32 columns.  256 bytes a row, the 16-byte chunk at
+// position c holds columns 2 (c ^ row % 16) and the next: 16 writes and 8 reads without bank conflicts and
+// 16 additions, where a shuffle tree for each of the 16 registers takes 240 vector instructions.
+__device__ __forceinline__ void put_row(char* buf, int r, int col, int half, double v) {
+  const int row = c_row(r, half);
+  *reinterpret_cast<double*>(buf + row * 256 + (((col >> 1) ^ (row & 15)) << 4) + (col & 1) * 8) = v;
+}
+__device__ __forceinline__ double take_rows(const char* buf, int lane) {
+  const int row = lane >> 1;
+  double s = 0.0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const double2 x = *reinterpret_cast<const double2*>(buf + row * 256 + ((((lane & 1) * 8 + j) ^ (row & 15)) << 4));
+    s += x.x;
+    s += x.y;
+  }
+  return s + dpp_mov_f64<0xB1>(s);
 }
 // One launch, K read once.  Every wave
 //   A. forms the logits t_ij (log2 units) of its item, 32 observation rows x up
@@ -289,6 +310,13 @@ __device__ __forceinline__ double exp2_fix(int qv) {
 //   kScoreWrite   A again, then C with the sums pass 1 left (no waiting: pass 1 has
 //                 completed), pass 2 of 2.  The two-pass form reads K twice but does
 //                 not depend on the launch being resident as a whole.
+// What bounds a launch is the latency of its stages (first tile, exchange) and then the vector unit, 30 to 47 %
+// busy with some 500 instructions per 32 keys of a wave.  Rounding by one fused multiply-add instead of
+// multiply, round, convert and clamp (fix_from_small), the integer part added to the exponent field and the row
+// sums through LDS took 200 to 300 of 800 (one tile per wave) or 570 (four) away: 12.8 / 17.2 / 21.2 / 22.2 -> 11.6 /
+// 16.1 / 19.7 / 21.0 us at 32 units of 2500 / 4000 / 6000 / 8000 keys, D = 128 (kernel trace).  Tried and slower: copies two tiles
+// ahead (23 registers more; eight-tile items spill), single-tile items with one buffer and five work-groups a compute unit
+// (18.2 against 16.1 us at 4000 keys: four times the slots to exchange).
 // skip_publish: test hook, index of a work-group of the launch that does not publish its
 // sums (-1: none); with a small spin_limit this makes the give-up path run
 // deterministically while every work-group still exits normally.
@@ -397,7 +425,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
   int tq[kParkP ? 1 : kItemTiles][16];
   double pq[kParkP ? kItemTiles : 1][16];
   auto p_of = [&](int t, int r) -> double { return kParkP ? pq[t][r] : exp2_fix(tq[t][r]); };
-  int q_hi = 0, q_lo = 0;              // extremes of the fixed-point logits, for the clamp report
+  bool clamped = false;                // a logit hit the clamp of the parked format
+  const double dot_safe = (double)(kFixLimit - 1) / c2;   // a dot product below this stays clear of it
 #pragma unroll
   for (int t = 0; t < kItemTiles; ++t) {
     if (t < n_tiles) {                 // wave-uniform
@@ -420,13 +449,23 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
 #pragma unroll
         for (int r = 0; r < 16; ++r) sd[r] = (kk == 0) ? (double)c[r] : sd[r] + (double)c[r];   // 0.0 + x == x: same bits
       }
+      double top = 0.0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) top = fmax(top, fabs(sd[r]));
+      int qv[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) qv[r] = fix_from_small(sd[r], c2);
+      if (__any(!(top < dot_safe))) {  // rare
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          qv[r] = fix_from(sd[r] * c2);
+          clamped |= qv[r] >= kFixLimit || qv[r] <= -kFixLimit;
+        }
+      }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int qv = fix_from(sd[r] * c2);
-        q_hi = max(q_hi, qv);
-        q_lo = min(q_lo, qv);
-        if (kParkP) pq[t][r] = exp2_fix(qv);
-        else tq[t][r] = qv;
+        if (kParkP) pq[t][r] = exp2_fix(qv[r]);
+        else tq[t][r] = qv[r];
       }
     } else {
 #pragma unroll
@@ -439,24 +478,42 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
 
   // A logit that hit the clamp of the parked format makes the result differ from
   // the definition: tell the host (second flag word; the launch still completes).
-  if (__any(q_hi >= kFixLimit || q_lo <= -kFixLimit)) {
+  if (__any(clamped)) {
     if (lane == 0) __hip_atomic_store(fault + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 
   // ---- B: row sums of the work-group -> its slot ------------------------------
-  // Each wave's tile buffers are free by now, so they carry the exchange inside
-  // the work-group: every wave leaves its 32 row sums there, wave 0 adds the four
+  // Each wave's tile buffers are free by now, so they carry the reduction inside the wave and the
+  // exchange inside the work-group: every wave leaves its 32 row sums there, wave 0 adds the four
   // and publishes one value per row.
   double* red = reinterpret_cast<double*>(&tiles[w][0][0]);
-  if (MODE != kScoreWrite)
+  if (MODE != kScoreWrite) {
+    char* buf = reinterpret_cast<char*>(red);
+    if (kParkP) {
+      double lsum[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    double lsum = 0.0;
+      for (int r = 0; r < 16; ++r) lsum[r] = 0.0;
 #pragma unroll
-    for (int t = 0; t < kItemTiles; ++t)
-      if (t < n_tiles && key0 + t * 32 + col < T_in) lsum += p_of(t, r);
-    const double l = half_sum_f64(lsum);
-    if (col == 0) red[c_row(r, half)] = l;
+      for (int t = 0; t < kItemTiles; ++t)
+        if (t < n_tiles && key0 + t * 32 + col < T_in) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) lsum[r] += p_of(t, r);
+        }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) put_row(buf, r, col, half, lsum[r]);
+    } else {
+      // row by row: there are no registers for 16 sums beside the parked logits
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        double lsum = 0.0;
+#pragma unroll
+        for (int t = 0; t < kItemTiles; ++t)
+          if (t < n_tiles && key0 + t * 32 + col < T_in) lsum += p_of(t, r);
+        put_row(buf, r, col, half, lsum);
+      }
+    }
+    const double l = take_rows(buf, lane);
+    if ((lane & 1) == 0) red[lane >> 1] = l;
   }
   __syncthreads();
   if (MODE != kScoreWrite && w == 0 && lane < kMaxObs && (MODE != kScoreFused || (int)blockIdx.x != skip_publish)) {
