@@ -114,6 +114,7 @@ struct StepGroup {
   int n_moves = 0;
   int item_keys = 0;
   bool two_pass = false;
+  bool small = false;                     // score and selection in one launch
   std::vector<int> launches;              // score launch groups
   unsigned long long* slots = nullptr;    // row-sum exchange area of the group's score launches
   const uint8_t* dev = nullptr;
@@ -1109,7 +1110,8 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   std::vector<ScoreItem> sitems;
   g->streamed = !n.split && use_stream_attention(ctx, u.descs, n.N_k, shared, &plan);
   if (!g->streamed) build_attn_items(u.descs, n.N_k, n.tile, &items);
-  if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty())
+  g->small = ctx->cfg.dtype == HACK_BF16 && use_score_select(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t);
+  if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty() && !g->small)
     g->item_keys = plan_score_items(ctx, u.descs, u.comp, g->two_pass, &sitems, &g->launches);
   // The key-split kernel reads the rows in place unless they change on the way (merge) or a unit's cache is longer than
   // the list of a unit that keeps everything.
@@ -1142,7 +1144,11 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
 // score -> select -> append / gather (-> merge) of a group's units
 void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
   const int32_t* comp_dev = reinterpret_cast<const int32_t*>(g.dev + g.o_comp);
-  if (g.n_comp > 0) {
+  if (g.n_comp > 0 && g.small) {
+    launch_score_select(s, ctx->cfg.head_dim, g.ddev(), comp_dev, g.n_comp, g.max_t, a.q,
+                        reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, a.kept, a.kstride,
+                        ctx->seam, ctx->fault);
+  } else if (g.n_comp > 0) {
     run_score(ctx, s, g.two_pass, g.slots, g.ddev(), comp_dev, g.n_comp, g.max_t,
               reinterpret_cast<const ScoreItem*>(g.dev + g.o_sit), g.item_keys, g.launches, a.q,
               reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->importance,

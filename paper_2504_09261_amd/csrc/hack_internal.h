@@ -155,6 +155,12 @@ void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const 
                       const void* k_cache, const void* k_new, double* stats, float* importance,
                       int64_t imp_stride);
 
+// bf16: score and selection of short units in one launch, one work-group per listed unit, no importance in memory.
+bool use_score_select(int head_dim, int n_units, int max_t_in);
+void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,
+                         const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
+                         const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault);
+
 // Budgeted selection; one work-group per listed unit.  seam[unit id] (or NULL) gets the number of
 // kept rows below len_in; every unit must then have new rows.
 void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list,

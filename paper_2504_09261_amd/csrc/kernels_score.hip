@@ -26,6 +26,7 @@
 
 #include "device_util.h"
 #include "hack_internal.h"
+#include "select_device.h"
 
 namespace hack {
 
@@ -610,6 +611,173 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
   }
 }
 
+// ---------------------------------------------------------------------------
+// bf16, short units: score and selection in one launch
+// ---------------------------------------------------------------------------
+// A work-group of NW waves owns a unit of at most 64 NW keys (NW = 4, 8, 16): wave w takes the tiles w and w + NW, the row
+// sums meet in LDS instead of the exchange area, importance goes to LDS only and thread j ranks key j.  The numbers
+// are those of score_fused up to the order in which the row sums are added in fp64.  Latency bounds these launches: a
+// score launch, whose work-groups wait for each other through L2, and a selection launch behind it take 8 + 4.4 us (kernel trace) at
+// 60 units of 46 to 475 keys (one 256^2 image: 108.6 -> 100.6 us, 960 units 349 -> 318).
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW) void score_select(
+    const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, const __bf16* __restrict__ q,
+    const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale, const __bf16* __restrict__ k_cache,
+    const __bf16* __restrict__ k_new, int32_t* __restrict__ kept_idx, int64_t idx_stride, int32_t* __restrict__ seam,
+    int* __restrict__ fault) {
+  constexpr int KK = D / 16, CPR = D / 8, RPI = 64 / CPR, IPT = 32 / RPI, TILE = 32 * D;   // as in score_fused
+  constexpr int TILES = 2;
+  constexpr int kBufs = 8192 / (TILE * 2);   // tile buffers per wave: the row sums need 8 KiB
+  using Shared = SelectShared<64 * NW, 11, 11>;
+  static_assert(Shared::kHist * 4 <= NW * 8192, "histograms fit the tile buffers");
+  __shared__ __attribute__((aligned(1024))) char bufs[NW][8192];
+  __shared__ double red[NW][kMaxObs], inv_s[NW][kMaxObs];
+  __shared__ uint32_t keys[64 * NW];
+  __shared__ Shared sh;
+
+  const UnitDesc d = descs[list[blockIdx.x]];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 31, half = lane >> 5;
+  const int T_in = d.len_in + d.n_new;
+  const int n_tiles = w * 32 >= T_in ? 0 : (w + NW) * 32 >= T_in ? 1 : 2;   // of this wave
+  const unsigned lds0 = lds_addr_of(&bufs[w][0]);
+
+  int src_off[IPT];
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int r = i * RPI + lane / CPR, c = lane % CPR;
+    src_off[i] = (r * D + ((c ^ swz_k<D>(r)) & (CPR - 1)) * 8) * 2;
+  }
+  auto issue = [&](int t) {
+    const int j0 = (w + t * NW) * 32;
+    const unsigned dst = lds0 + (unsigned)((t % kBufs) * TILE * 2);
+    const bool in_cache = j0 + 32 <= d.len_in;
+    const bool in_new = j0 >= d.len_in && j0 + 32 <= T_in;
+    if (in_cache || in_new) {
+      const __bf16* base = in_cache ? k_cache + (d.in_off + j0) * D : k_new + ((int64_t)d.unit * N_k + (j0 - d.len_in)) * D;
+#pragma unroll
+      for (int i = 0; i < IPT; ++i) load_to_lds(base, (unsigned)src_off[i], dst + i * 1024);
+    } else {   // rows past the end repeat the last key
+#pragma unroll
+      for (int i = 0; i < IPT; ++i) {
+        const int r = i * RPI + lane / CPR, c = lane % CPR;
+        const int j = min(j0 + r, T_in - 1);
+        const __bf16* row = (j < d.len_in) ? k_cache + (d.in_off + j) * D : k_new + ((int64_t)d.unit * N_k + (j - d.len_in)) * D;
+        load_to_lds(row + ((c ^ swz_k<D>(r)) & (CPR - 1)) * 8, dst + i * 1024);
+      }
+    }
+  };
+  if (n_tiles > 0) issue(0);
+  if (kBufs > 1 && n_tiles > 1) issue(1);
+
+  bf16x8 qf[KK];
+  {
+    const bool qv = col < n_obs;
+    const __bf16* qrow = q + ((int64_t)d.unit * N_k + (qv ? q_rows[col] : 0)) * D;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      bf16x8 z = {0};
+      qf[kk] = qv ? *reinterpret_cast<const bf16x8*>(qrow + 16 * kk + 8 * half) : z;
+    }
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) asm volatile("" ::"v"(qf[kk]));
+  }
+  const double c2 = (double)scale * kLog2e * kFixOne;
+  const double dot_safe = (double)(kFixLimit - 1) / c2;
+  int k_off[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) k_off[kk] = col * D + (((2 * kk + half) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
+
+  // ---- logits (see score_fused) ----
+  double pq[TILES][16];
+  bool clamped = false;
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) {
+    if (t < n_tiles) {                 // wave-uniform
+      if (kBufs > 1 && t + 1 < n_tiles) dma_wait_but<IPT>();
+      else dma_wait_but<0>();
+      const __bf16* Kt = reinterpret_cast<const __bf16*>(&bufs[w][(t % kBufs) * TILE * 2]);
+      double sd[16];
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kt[k_off[kk]]);
+        floatx16 c = {0};
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[kk], kf, c, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sd[r] = (kk == 0) ? (double)c[r] : sd[r] + (double)c[r];
+      }
+      if (kBufs == 1 && t + 1 < n_tiles) {
+        // the sums above have consumed every operand read: the buffer may be refilled
+#pragma unroll
+        for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(sd[r]) : : "memory");
+        issue(t + 1);
+      }
+      double top = 0.0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) top = fmax(top, fabs(sd[r]));
+      int qv[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) qv[r] = fix_from_small(sd[r], c2);
+      if (__any(!(top < dot_safe))) {  // rare
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          qv[r] = fix_from(sd[r] * c2);
+          clamped |= qv[r] >= kFixLimit || qv[r] <= -kFixLimit;
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) pq[t][r] = exp2_fix(qv[r]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) pq[t][r] = 0.0;
+    }
+  }
+  if (__any(clamped)) {
+    if (lane == 0) __hip_atomic_store(fault + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+
+  // ---- normalisers ----
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    double lsum = 0.0;
+#pragma unroll
+    for (int t = 0; t < TILES; ++t)
+      if (t < n_tiles && (w + t * NW) * 32 + col < T_in) lsum += pq[t][r];
+    put_row(&bufs[w][0], r, col, half, lsum);
+  }
+  const double l = take_rows(&bufs[w][0], lane);
+  if ((lane & 1) == 0) red[w][lane >> 1] = l;
+  __syncthreads();                     // tile buffers are free from here on
+  if (lane < kMaxObs) {
+    double tot = 0.0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) tot += red[k][lane];
+    inv_s[w][lane] = (lane < n_obs) ? 1.0 / tot : 0.0;
+  }
+  double inv_r[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) inv_r[r] = inv_s[w][c_row(r, half)];
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) {
+    if (t < n_tiles) {
+      double imp = 0.0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) imp = fma(pq[t][r], inv_r[r], imp);
+      imp += shfl_xor_f64(imp, 32);
+      if (half == 0) keys[(w + t * NW) * 32 + col] = __float_as_uint((float)imp);
+    }
+  }
+  __syncthreads();
+
+  // ---- selection ----
+  uint32_t key[1] = {0};
+  const unsigned in_seg = tid >= d.sel_lo && tid < d.sel_hi ? 1u : 0u;
+  if (in_seg) key[0] = keys[tid];
+  select_rows<64 * NW, 1, 11, 11>(d, key, in_seg, reinterpret_cast<uint32_t*>(&bufs[0][0]), sh,
+                                  kept_idx + (int64_t)d.unit * idx_stride, seam);
+}
+
 template <int D, int TPW>
 void launch_f32(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in, const float* q,
                 const int32_t* q_rows, int n_obs, int N_k, float scale, const float* k_cache, const float* k_new, double* stats,
@@ -783,6 +951,35 @@ hipError_t launch_score_static(hipStream_t s, int device, int head_dim, const St
                      sc->slots, kMaxGroups, sc->counters, importance, imp_stride, fault, 0,
                      sc->counters + 2 * kStaticUnitsMax, -1);
   return hipGetLastError();
+}
+
+// Where one work-group per unit beats two launches.  Measured, us a schedule of four steps whose last compresses, two
+// launches / one, at 8, 32, 128, 512 units: head_dim 64, 210 keys 33.0 / 30.3, 33.7 / 31.0, 37.4 / 34.6, 62.5 / 57.0; 498 keys
+// 33.9 / 32.6, 35.8 / 34.5, 54.0 / 50.8, 91 / 88; 690 keys 35.0 / 36.3, 38.8 / 39.8, 61.9 / 59.9, 131 / 129.5; 975 keys 37.5 / 39.6,
+// 44 / 46.4, 74.7 / 71.9, 178 / 179; head_dim 128, 210 keys 38.0 / 35.8, 39.9 / 37.3, 51.3 / 48.5, 80.3 / 77.0; 303 keys 38.4 / 37.4, 41 / 39.9,
+// 60.5 / 57.4, 103 / 104.6; 498 keys 40.2 / 40.4, 47.1 / 46.6, 67 / 64.2, 145 / 147.4; 690 keys 41.8 / 46.6, 55.5 / 58.7, 84.4 / 84.8,
+// 214 / 211 (16 waves of 128 registers, dropped).
+bool use_score_select(int head_dim, int n_units, int max_t_in) {
+  if (head_dim == 64) return max_t_in <= 512 || (max_t_in <= 1024 && n_units >= 128);
+  return max_t_in <= 256 || (max_t_in <= 512 && n_units <= 256);
+}
+
+void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,
+                         const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
+                         const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault) {
+  if (n_list <= 0) return;
+#define HACK_SMALL(D_, NW_)                                                                                                  \
+  hipLaunchKernelGGL((score_select<D_, NW_>), dim3(n_list), dim3(64 * NW_), 0, s, descs, list, (const __bf16*)q, q_rows, n_obs, \
+                     N_k, scale, (const __bf16*)k_cache, (const __bf16*)k_new, kept_idx, idx_stride, seam, fault)
+  if (head_dim == 64) {
+    if (max_t_in <= 256) HACK_SMALL(64, 4);
+    else if (max_t_in <= 512) HACK_SMALL(64, 8);
+    else HACK_SMALL(64, 16);
+  } else {
+    if (max_t_in <= 256) HACK_SMALL(128, 4);
+    else HACK_SMALL(128, 8);
+  }
+#undef HACK_SMALL
 }
 
 void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,

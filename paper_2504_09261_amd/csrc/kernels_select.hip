@@ -25,45 +25,14 @@
 // More threads with fewer keys each won throughout (4000 keys: 256, 512, 1024 threads
 // 8.1, 6.4, 5.9; 560 keys, 60 / 960 units: 128 threads 6.1 / 9.8, 256 4.5 / 7.0, 512 3.9 / 6.4,
 // 1024 4.1 / 9.2, the last for want of resident work-groups).
-#include <type_traits>
-
 #include "hack_internal.h"
+#include "select_device.h"
 
 namespace hack {
 
 namespace {
 
-__device__ __forceinline__ uint32_t orderable(float f) {
-  uint32_t u = __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// Inclusive prefix over the wave: four shifts inside the 16-lane rows, then the row totals handed on.
-__device__ __forceinline__ int wave_inclusive_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // lane 15 of rows 0, 2 -> rows 1, 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 -> rows 2, 3
-  return v;
-}
-
-// Exclusive prefix of v over the work-group in thread order.  wave_tot is used by this call only (one barrier).
-template <int kWaves>
-__device__ __forceinline__ int block_exclusive_scan(int v, int* wave_tot) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int incl = wave_inclusive_scan(v);
-  if (lane == 63) wave_tot[w] = incl;
-  __syncthreads();
-  int base = 0;
-#pragma unroll
-  for (int i = 0; i < kWaves; ++i) {
-    const int t = wave_tot[i];
-    if (i < w) base += t;
-  }
-  return base + incl - v;
-}
+using namespace dev;
 
 // NT threads, PER keys each (T <= NT * PER); digits of B0, B1 and 32 - B0 - B1 bits.
 template <int NT, int PER, int B0, int B1>
@@ -71,17 +40,13 @@ __global__ __launch_bounds__(NT) void select_kernel(
     const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list,
     const float* __restrict__ importance, int64_t imp_stride, int32_t* __restrict__ kept_idx,
     int64_t idx_stride, int32_t* __restrict__ seam) {
-  constexpr int kWaves = NT / 64;
-  constexpr int B2 = 32 - B0 - B1;
-  constexpr int kHist = (1 << B0) + (1 << B1) + (1 << B2);
-  __shared__ __attribute__((aligned(16))) uint32_t hist[kHist];
-  __shared__ int wave_tot[5][kWaves];
-  __shared__ int found[3][3];   // per pass: bin, rows still wanted from it, keys in it
+  using Shared = SelectShared<NT, B0, B1>;
+  __shared__ __attribute__((aligned(16))) uint32_t hist[Shared::kHist];
+  __shared__ Shared sh;
 
   const UnitDesc d = descs[list[blockIdx.x]];
   const float* imp = importance + (int64_t)d.unit * imp_stride;
   int32_t* out = kept_idx + (int64_t)d.unit * idx_stride;
-  const int T = d.len_in + d.n_new;
   const int tid = threadIdx.x;
   const int j0 = tid * PER;                   // first row of this thread
 
@@ -117,88 +82,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     }
   }
 
-  // ---- threshold of the ranked segment ----
-  uint32_t pre = 0;     // keys with (key >> shift) > pre are kept, those equal to pre are candidates
-  int shift = 0;
-  int want = d.sel_m;   // candidates to keep
-  bool all_candidates = true;
-  if (ranked) {
-    for (int i = tid * 4; i < kHist; i += NT * 4) *reinterpret_cast<uint4*>(&hist[i]) = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-    for (int e = 0; e < PER; ++e) key[e] = orderable(__uint_as_float(key[e]));
-    __syncthreads();
-    // One pass over a digit of BITS bits at bit SH; bins in descending order of the digit.
-    auto pass = [&](auto idx_tag, auto bits_tag, auto sh_tag, uint32_t* h) {
-      constexpr int P = decltype(idx_tag)::value, BITS = decltype(bits_tag)::value, SH = decltype(sh_tag)::value;
-      constexpr uint32_t M = (1u << BITS) - 1u;
-      constexpr int BPT = (1 << BITS) / NT > 0 ? (1 << BITS) / NT : 1;   // bins per thread
-#pragma unroll
-      for (int e = 0; e < PER; ++e)
-        if (((in_seg >> e) & 1u) && (P == 0 || (key[e] >> ((SH + BITS) & 31)) == pre))
-          atomicAdd(&h[(~(key[e] >> SH)) & M], 1u);
-      __syncthreads();
-      int c[BPT], tot = 0;
-#pragma unroll
-      for (int b = 0; b < BPT; ++b) {
-        c[b] = tid * BPT + b < (1 << BITS) ? (int)h[tid * BPT + b] : 0;
-        tot += c[b];
-      }
-      int run = block_exclusive_scan<kWaves>(tot, wave_tot[P]);
-      if (run < want && want <= run + tot) {
-#pragma unroll
-        for (int b = 0; b < BPT; ++b) {
-          if (run < want && want <= run + c[b]) {
-            found[P][0] = tid * BPT + b;
-            found[P][1] = want - run;
-            found[P][2] = c[b];
-          }
-          run += c[b];
-        }
-      }
-      __syncthreads();
-      pre = (P == 0 ? 0u : pre << BITS) | (M - (uint32_t)found[P][0]);
-      shift = SH;
-      want = found[P][1];
-      return want == found[P][2];   // the whole bin is kept
-    };
-    using std::integral_constant;
-    all_candidates = pass(integral_constant<int, 0>{}, integral_constant<int, B0>{}, integral_constant<int, 32 - B0>{}, hist) ||
-                     pass(integral_constant<int, 1>{}, integral_constant<int, B1>{}, integral_constant<int, B2>{}, hist + (1 << B0)) ||
-                     pass(integral_constant<int, 2>{}, integral_constant<int, B2>{}, integral_constant<int, 0>{},
-                          hist + (1 << B0) + (1 << B1));
-  }
-
-  // ---- ordered emission ----
-  // forced rows, rows above the threshold and, as a rule, all candidates; if some equal rows are left out (only
-  // whole keys are equal then), the lowest rows are taken
-  unsigned keep = 0, cand = 0;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int j = j0 + e;
-    const bool forced = j < d.keep_a || j >= d.keep_b;
-    const bool seg = (in_seg >> e) & 1u;
-    const uint32_t v = key[e] >> shift;
-    const bool hit = forced || (seg && (take_all || (ranked && v > pre)));
-    if (j < T && hit) keep |= 1u << e;
-    if (seg && !forced && ranked && v == pre) cand |= 1u << e;
-  }
-  if (all_candidates) {
-    keep |= cand;
-  } else {
-    int left = want - block_exclusive_scan<kWaves>(__popc(cand), wave_tot[3]);   // how many of this thread's candidates may stay
-#pragma unroll
-    for (int e = 0; e < PER; ++e)
-      if (((cand >> e) & 1u) && left > 0) {
-        keep |= 1u << e;
-        --left;
-      }
-  }
-  int pos = block_exclusive_scan<kWaves>(__popc(keep), wave_tot[4]);
-  // how many kept rows precede row len_in, the first new one
-  if (seam != nullptr && d.len_in >= j0 && d.len_in < j0 + PER) seam[d.unit] = pos + __popc(keep & ((1u << (d.len_in - j0)) - 1u));
-#pragma unroll
-  for (int e = 0; e < PER; ++e)
-    if ((keep >> e) & 1u) out[pos++] = j0 + e;
+  select_rows<NT, PER, B0, B1>(d, key, in_seg, hist, sh, out, seam);
 }
 
 }  // namespace

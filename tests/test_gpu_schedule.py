@@ -446,6 +446,53 @@ def test_steps_that_read_kept_rows_in_place(head_dim, with_pos):
     hk.close()
 
 
+@pytest.mark.parametrize("head_dim,B,sides_n", [
+    (64, 1, [5, 40, 41, 170]),          # units of up to 256 keys
+    (64, 1, [5, 200, 51, 256]),         # up to 512: exactly 512 at the last step
+    (64, 16, [5, 700, 300, 323]),       # up to 1024: 128 units, exactly 1023
+    (64, 1, [5, 300, 300, 300]),        # few long units: two launches
+    (128, 1, [5, 40, 33, 178]),
+    (128, 1, [3, 210, 97, 202]),
+    (128, 1, [3, 300, 300, 411]),       # two launches
+])
+def test_short_units_score_and_select_in_one_launch(head_dim, B, sides_n):
+    """hack_step's kept lists for units around the sizes at which score and selection share a launch, against the single
+    entry points (which never do): the same importance up to fp64 summation order, 1e-16 of a value whose float32
+    rounding decides, hence equal lists on random data.  The last step holds one unit of the largest size."""
+    from tests import gpu_util as u
+    H = 8
+    hk = u.make_hack(heads=H, head_dim=head_dim, dtype="bf16", max_units=B * H, max_cache_len=sum(sides_n), max_queries=max(sides_n))
+    types = np.array([0, 1] * (H // 2), np.uint8)
+    U = B * H
+    caps = np.maximum(sum(sides_n[:3]) - 17 * np.arange(U) % 190, 30).astype(np.int32)   # unit 0 keeps everything until the last step
+    mc = hk.managed_cache(np.maximum(caps, sum(sides_n[:2])))
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(sum(sides_n))
+    scale, stride = float(np.float32(head_dim ** -0.5)), (sum(sides_n) + 63) // 64 * 64
+    lists = 0
+    for step, n in enumerate(sides_n):
+        q, kn, vn = (torch.randn((B, H, n, head_dim), generator=gen, device=u.DEV).to(torch.bfloat16) for _ in range(3))
+        before = mc.as_cache()
+        src = type(before)(mc.k.clone(), mc.v.clone(), before.off, before.len, mc.pos.clone())
+        budget = np.full(U, 10**6, np.int32) if step < 2 else caps
+        kept = torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV)
+        hk.step(mc, q, kn, vn, types, budget, 5, scale, torch.empty_like(q), kept_idx=kept)
+        imp = torch.zeros((U, stride), device=u.DEV)
+        want = torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV)
+        hk.score(q, src, scale, imp, k_new=kn)
+        t_in = src.len + n
+        ln = hk.select(B, imp, t_in, types, budget, 5, n, want)
+        torch.cuda.synchronize()
+        for x in range(U):
+            if budget[x] < t_in[x]:
+                lists += 1
+                assert torch.equal(kept[x, :ln[x]], want[x, :ln[x]]), (step, x)
+    assert lists > U // 2
+    hk.check()
+    mc.close()
+    hk.close()
+
+
 def test_step_capacity_and_argument_errors():
     u = _u()
     from paper_2504_09261_amd.binding import HackError
