@@ -83,21 +83,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
   __shared__ floatx4 o_sh[NW][NG][64];
   __shared__ float m_sh[NW][QT], l_sh[NW][QT];
 
-  // ---- cache update of this tile's rows ----
-  if (fuse) {
-    constexpr int LPR = D / 4;   // 16-byte pieces per row
-    const int nr = min(QT, N_k - q0);
-    const uint4* ks = reinterpret_cast<const uint4*>(k_new) + (new_row0 + q0) * LPR;
-    const uint4* vs = reinterpret_cast<const uint4*>(v_new) + (new_row0 + q0) * LPR;
-    uint4* kd = reinterpret_cast<uint4*>(k_app) + (it.in_off + it.len_in + q0) * LPR;
-    uint4* vd = reinterpret_cast<uint4*>(v_app) + (it.in_off + it.len_in + q0) * LPR;
-    for (int e = tid; e < nr * LPR; e += 64 * NW) {
-      kd[e] = ks[e];
-      vd[e] = vs[e];
-    }
-    if (pos_app != nullptr && tid < nr) pos_app[it.in_off + it.len_in + q0 + tid] = pos_new + q0 + tid;
-  }
-
   // ---- Q operands ----
   floatx4 qf[R][C];
 #pragma unroll
@@ -189,6 +174,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
 #pragma unroll
           for (int j = 0; j < R; ++j)
             o[j][m][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][m][e], sc[j][r], o[j][m][e], 0, 0, 0);
+  }
+
+  // ---- cache update of this tile's rows, off the way of the loads above ----
+  if (fuse) {
+    constexpr int LPR = D / 4;   // 16-byte pieces per row
+    const int nr = min(QT, N_k - q0);
+    const uint4* ks = reinterpret_cast<const uint4*>(k_new) + (new_row0 + q0) * LPR;
+    const uint4* vs = reinterpret_cast<const uint4*>(v_new) + (new_row0 + q0) * LPR;
+    uint4* kd = reinterpret_cast<uint4*>(k_app) + (it.in_off + it.len_in + q0) * LPR;
+    uint4* vd = reinterpret_cast<uint4*>(v_app) + (it.in_off + it.len_in + q0) * LPR;
+    for (int e = tid; e < nr * LPR; e += 64 * NW) {
+      kd[e] = ks[e];
+      vd[e] = vs[e];
+    }
+    if (pos_app != nullptr && tid < nr) pos_app[it.in_off + it.len_in + q0 + tid] = pos_new + q0 + tid;
   }
 
   // ---- merge the waves' partial results ----
