@@ -22,8 +22,8 @@
 //                  combined at the end;
 //   merge_apply    a work-group takes 32 kept rows: its waves scan the assignment once,
 //                  each a contiguous quarter, and leave the rows that go to one of the 32
-//                  in LDS lists (ascending); every wave then folds the listed rows into
-//                  its 8 kept rows in ascending row order (so the float32 sums are formed
+//                  in LDS lists (ascending); every wave then folds the listed rows, eight
+//                  loads in flight, into its 8 kept rows in ascending row order (so the float32 sums are formed
 //                  in a fixed order: the result is reproducible bit for bit) and rewrites
 //                  them in place.
 // bf16 only.  The products of bf16 values are exact in float32; dots accumulate in
@@ -50,6 +50,8 @@ constexpr int kNearTile = kWaves * 32 * kNearBlocks;   // cache rows per work-gr
 constexpr int kFillRows = 1024;                     // rows per work-group in merge_fill
 constexpr int kMarkRows = kThreads / 8;             // kept rows per work-group in merge_mark (8 lanes per row)
 constexpr int kApplyRows = 32;                      // kept rows per work-group in merge_apply
+constexpr int kScanSteps = 8;                        // 64-row steps of that scan in flight
+constexpr int kFold = 8;                             // evicted rows a wave of merge_apply folds in at a time
 constexpr int kScanPerWave = 2048;                  // cache rows a wave of merge_apply scans per round = capacity of its list
 
 __global__ __launch_bounds__(kThreads) void merge_fill(const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list,
@@ -270,15 +272,15 @@ __global__ __launch_bounds__(kThreads) void merge_apply(
     // wave w scans cache rows [seg0 + per w, + per): the rows assigned to one of this work-group's kept rows
     int n = 0;
     const int base = seg0 + w * per;
-    for (int t0 = 0; t0 < per && base + t0 < T; t0 += 4 * 64) {
-      int v[4];                                               // four steps' loads in flight together
+    for (int t0 = 0; t0 < per && base + t0 < T; t0 += kScanSteps * 64) {
+      int v[kScanSteps];                                      // these steps' loads in flight together
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < kScanSteps; ++u) {
         const int j = base + t0 + 64 * u + lane;
         v[u] = (t0 + 64 * u < per && j < T) ? nn[j] : -1;
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < kScanSteps; ++u) {
         const int j = base + t0 + 64 * u + lane;
         const unsigned rl = (unsigned)(v[u] - r0);            // kept (-1) and unassigned rows wrap to large values
         const bool hit = rl < (unsigned)kApplyRows;
@@ -290,33 +292,27 @@ __global__ __launch_bounds__(kThreads) void merge_apply(
     if (lane == 0) cnt[w] = n;
     __syncthreads();
     // The lists of waves 0..3 one after the other are in ascending row order: a fixed summation order per kept
-    // row.  The wave's 8 kept rows advance side by side: per pass each row that has a listed row left takes its
-    // next one, the loads of all of them are issued together, then each row adds its own.
+    // row.  A wave takes the entries of its 8 kept rows kFold at a time, whatever rows they go to: the loads of all of
+    // them are issued together, then each is added to its row.
     for (int q = 0; q < kWaves; ++q) {
       const int nq = cnt[q];
       for (int t0 = 0; t0 < nq; t0 += 64) {
         const bool in = t0 + lane < nq;
         const unsigned ent = in ? lst[q * cap + t0 + lane] : 0u;
-        unsigned long long m[RPW];
-        unsigned long long any = 0;
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-          m[i] = __ballot(in && (ent & 31u) == (unsigned)(w * RPW + i));
-          any |= m[i];
-        }
-        while (any) {
-          float we[RPW];
-          bf16x2 kx[RPW], vx[RPW];
+        unsigned long long left = __ballot(in && (int)((ent & 31u) / RPW) == w);
+        while (left) {
           static_assert(EPL == 1 || EPL == 2, "one or two elements per lane");
-          any = 0;
+          float we[kFold];
+          bf16x2 kx[kFold], vx[kFold];
+          int to[kFold];                                      // kept row of the wave, -1: no entry left
 #pragma unroll
-          for (int i = 0; i < RPW; ++i) {
-            we[i] = -1.f;                                     // no row taken in this pass
-            if (m[i]) {                                       // wave-uniform
-              const int src = __builtin_ctzll(m[i]);
-              m[i] &= m[i] - 1;
-              any |= m[i];
-              const int e = seg0 + (int)(__shfl(ent, src, 64) >> 5);
+          for (int i = 0; i < kFold; ++i) {
+            to[i] = -1;
+            if (left) {                                       // wave-uniform
+              const unsigned x = __builtin_amdgcn_readlane(ent, __builtin_ctzll(left));
+              left &= left - 1;
+              to[i] = (int)(x & 31u) % RPW;
+              const int e = seg0 + (int)(x >> 5);
               we[i] = wt[e];
               const bool cached = e < d.len_in;
               const int64_t row = cached ? d.in_off + e : (int64_t)d.unit * N_k + (e - d.len_in);
@@ -332,16 +328,18 @@ __global__ __launch_bounds__(kThreads) void merge_apply(
             }
           }
 #pragma unroll
-          for (int i = 0; i < RPW; ++i) {
-            if (we[i] >= 0.f) {                               // weights are >= 0; wave-uniform
+          for (int i = 0; i < kFold; ++i)
+            if (to[i] >= 0 && we[i] >= 0.f)                   // wave-uniform; weights are >= 0
 #pragma unroll
-              for (int x = 0; x < EPL; ++x) {
-                ak[i][x] = fmaf(we[i], (float)kx[i][x], ak[i][x]);
-                av[i][x] = fmaf(we[i], (float)vx[i][x], av[i][x]);
-              }
-              wsum[i] += we[i];
-            }
-          }
+              for (int r = 0; r < RPW; ++r)
+                if (to[i] == r) {
+#pragma unroll
+                  for (int x = 0; x < EPL; ++x) {
+                    ak[r][x] = fmaf(we[i], (float)kx[i][x], ak[r][x]);
+                    av[r][x] = fmaf(we[i], (float)vx[i][x], av[r][x]);
+                  }
+                  wsum[r] += we[i];
+                }
         }
       }
     }
