@@ -124,10 +124,10 @@ __device__ __forceinline__ double half_sum_f64(double v) {
 
 // ---- cache update beside another kernel's work --------------------------------
 // A work-group takes one item: kMoveItemRows rows of a unit go to where the next step expects them.  All loads of a
-// thread (up to 8 pieces of K and of V, their positions) are in flight before its first store.
-template <int D, int THREADS>
+// thread (up to 16 pieces of K and of V, their positions) are in flight before its first store.
+template <int LPR, int THREADS>   // 16-byte pieces per row
 __device__ __forceinline__ void move_rows(const UnitDesc* __restrict__ descs, const GatherArgs& g, int item, int N_k) {
-  constexpr int LPR = D / 8, RPP = THREADS / LPR, PASSES = kMoveItemRows / RPP;   // 16-byte pieces per row, rows per pass
+  constexpr int RPP = THREADS / LPR, PASSES = kMoveItemRows / RPP;   // rows per pass
   const int lane = threadIdx.x % LPR;
   const MoveItem it = g.moves[item];
   const UnitDesc d = descs[it.desc];

@@ -65,8 +65,8 @@ struct hack_ctx {
   // workspace
   float* importance = nullptr;   // [max_units, ws_stride]
   int32_t* kept = nullptr;       // [max_units, ws_stride]
-  int32_t* seam = nullptr;       // bf16 path: [max_units] kept rows of the step's selection that come from the cache
-  int32_t* iota = nullptr;       // bf16 path: [kIotaRows] 0, 1, 2, ...
+  int32_t* seam = nullptr;       // [max_units] kept rows of the step's selection that come from the cache
+  int32_t* iota = nullptr;       // [kIotaRows] 0, 1, 2, ...
   double* stats = nullptr;       // fp32 path: [max_units, max_chunks, 32, 2] softmax partials
   unsigned long long* rowstat = nullptr;  // bf16 path: [max_units, score_groups, 32] row-sum exchange slots, all-ones between launches
   unsigned long long* rowstat_side = nullptr;  // the same for the side branch of hack_step (two-pass form: its slots are not re-armed)
@@ -580,9 +580,9 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   const size_t n_ws = (size_t)cfg->max_units * ctx->ws_stride;
   if (e == hipSuccess) e = hipMalloc((void**)&ctx->importance, n_ws * sizeof(float));
   if (e == hipSuccess) e = hipMalloc((void**)&ctx->kept, n_ws * sizeof(int32_t));
-  if (e == hipSuccess && cfg->dtype == HACK_BF16) e = hipMalloc((void**)&ctx->seam, (size_t)cfg->max_units * sizeof(int32_t));
-  if (e == hipSuccess && cfg->dtype == HACK_BF16) e = hipMalloc((void**)&ctx->iota, kIotaRows * sizeof(int32_t));
-  if (e == hipSuccess && cfg->dtype == HACK_BF16) {
+  if (e == hipSuccess) e = hipMalloc((void**)&ctx->seam, (size_t)cfg->max_units * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMalloc((void**)&ctx->iota, kIotaRows * sizeof(int32_t));
+  if (e == hipSuccess) {
     std::unique_ptr<int32_t[]> rows(new (std::nothrow) int32_t[kIotaRows]);
     for (int i = 0; rows && i < kIotaRows; ++i) rows[i] = i;
     e = rows ? hipMemcpy(ctx->iota, rows.get(), kIotaRows * sizeof(int32_t), hipMemcpyHostToDevice) : hipErrorOutOfMemory;
@@ -1113,10 +1113,10 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->small = ctx->cfg.dtype == HACK_BF16 && use_score_select(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t);
   if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty() && !g->small)
     g->item_keys = plan_score_items(ctx, u.descs, u.comp, g->two_pass, &sitems, &g->launches);
-  // The key-split kernel reads the rows in place unless they change on the way (merge) or a unit's cache is longer than
+  // The key-split and the float32 kernel read the rows in place unless they change on the way (merge) or a unit's cache is longer than
   // the list of a unit that keeps everything.
   std::vector<MoveItem> moves;
-  g->gathered = n.split && !n.fuse_append && u.merging.empty();
+  g->gathered = (n.split || ctx->cfg.dtype == HACK_F32) && !n.fuse_append && u.merging.empty();
   for (const UnitDesc& d : u.descs) g->gathered = g->gathered && (d.mode == MOVE_GATHER || d.n_out <= kIotaRows);
   if (g->gathered)
     for (size_t i = 0; i < u.descs.size(); ++i)
@@ -1169,7 +1169,10 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
   if (g.gathered) {
     const GatherArgs ga{a.kept, a.kstride, ctx->seam, ctx->iota, reinterpret_cast<const MoveItem*>(g.dev + g.o_moves), g.n_moves,
                         a.pos_new, a.k_new, a.v_new, a.cp};
-    launch_attn_split_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
+    if (ctx->cfg.dtype == HACK_F32)
+      launch_attn_f32_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, n.tile, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
+    else
+      launch_attn_split_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
     return;
   }
   if (g.streamed)

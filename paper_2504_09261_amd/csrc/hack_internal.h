@@ -181,6 +181,10 @@ int attn_f32_q_tile_rows(int n_units, int N_k);
 void launch_attn_f32(hipStream_t s, int head_dim, const AttnItem* items, int n_items, int q_tile_rows, const void* q,
                      const void* k_cache, const void* v_cache, const void* k_new, const void* v_new, void* k_app, void* v_app,
                      int32_t* pos_app, int pos_new, int fuse, int N_k, float scale, void* out);
+// Over the rows the units keep, read in place through g; g.n_moves further work-groups update the cache.
+void launch_attn_f32_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int q_tile_rows,
+                            const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k, float scale,
+                            void* out);
 // Streamed form of the 128-query bf16 kernel: work-group i serves segs[seg_begin[i] .. seg_begin[i+1]).
 // part_o: n_slots * 128 * head_dim floats, part_ml: n_slots * 256 floats, part_count: one zeroed
 // counter per cut work item (left zero).  Launches that share these arrays must not overlap.

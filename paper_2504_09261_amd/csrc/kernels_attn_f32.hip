@@ -58,16 +58,26 @@ __device__ __forceinline__ float rows_sum(float v) {
 // their position ids) behind the cached ones (k_app / v_app / pos_app, which k_cache /
 // v_cache then alias: reads stay below row len_in, writes at or above it).
 // fuse == 0: keys are rows [out_off, out_off + n_out) of the cache.
-template <int D, int R, int NW>
+// GATHER (fuse == 0): keys are the rows the unit keeps, read in place through its list, whose entries are loaded a block
+// ahead; ga.n_moves further work-groups move those rows (as in the bf16 key-split kernel).  A step less one launch: the 680-token
+// schedule 130.9 -> 124.3 us; single compressing steps of 8 to 64 units, 78 to 414 keys, 0 to 2 us of 35 to 100 less.
+template <int D, int R, int NW, bool GATHER>
 __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
     const AttnItem* __restrict__ items, const float* __restrict__ q, const float* k_cache, const float* v_cache,
     const float* k_new, const float* v_new, float* k_app, float* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k,
-    float scale, float* __restrict__ out) {
+    float scale, float* __restrict__ out, const UnitDesc* __restrict__ descs, GatherArgs ga) {
   constexpr int C = D / 16;          // 16-byte pieces of a K / Q row per lane
   constexpr int M = D / 64;          // 16-byte pieces of a V row per lane
   constexpr int QT = 16 * R;         // queries per work item
   constexpr int NG = R * M * 4;      // groups of four output registers per lane
 
+  if constexpr (GATHER) {
+    const int mover = (int)blockIdx.x - ((int)gridDim.x - ga.n_moves);
+    if (mover >= 0) {
+      move_rows<D / 4, 64 * NW>(descs, ga, mover, N_k);
+      return;
+    }
+  }
   const AttnItem it = items[blockIdx.x];
   if (it.desc < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -93,20 +103,34 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
   }
 
   // key row in its home; rows past the end repeat the last one (their scores are masked)
-  auto row_of = [&](const float* cache, const float* fresh, int key) -> const float* {
+  const int32_t* list = nullptr;
+  if constexpr (GATHER) list = it.mode == MOVE_GATHER ? ga.kept + (int64_t)it.unit * ga.kept_stride : ga.iota;
+  auto entry = [&](int key) -> int {
     const int j = min(key, total - 1);
-    return j < len_c ? cache + (base + j) * D : fresh + (new_row0 + (j - len_c)) * D;
+    if constexpr (GATHER) return list[j];
+    else return j;
+  };
+  const int64_t cache0 = GATHER ? it.in_off : base;
+  const int home = GATHER ? it.len_in : len_c;   // entries below are cached rows
+  auto row_of = [&](const float* cache, const float* fresh, int x) -> const float* {
+    return x < home ? cache + (cache0 + x) * D : fresh + (new_row0 + (x - home)) * D;
   };
   floatx4 kf[C], vf[4][M];
-  auto load_k = [&](int b) {
-    const float* p = row_of(k_cache, k_new, b * kKB + i) + 4 * g;
+  int xk = 0, xv[4];   // entries of the next K block, of this V block
+  auto entry_k = [&](int b) { xk = entry(b * kKB + i); };
+  auto entries_v = [&](int b) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) xv[r] = entry(b * kKB + 4 * g + r);
+  };
+  auto load_k = [&]() {
+    const float* p = row_of(k_cache, k_new, xk) + 4 * g;
 #pragma unroll
     for (int c = 0; c < C; ++c) kf[c] = *reinterpret_cast<const floatx4*>(p + 16 * c);
   };
-  auto load_v = [&](int b) {
+  auto load_v = [&]() {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float* p = row_of(v_cache, v_new, b * kKB + 4 * g + r) + 4 * i;
+      const float* p = row_of(v_cache, v_new, xv[r]) + 4 * i;
 #pragma unroll
       for (int m = 0; m < M; ++m) vf[r][m] = *reinterpret_cast<const floatx4*>(p + 64 * m);
     }
@@ -126,9 +150,18 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
   const float c2 = scale * kLog2eF;
 
   const int n_blocks = (total + kKB - 1) / kKB;
-  if (w < n_blocks) load_k(w);
+  if (w < n_blocks) {
+    entry_k(w);
+    entries_v(w);
+    load_k();
+  }
   for (int b = w; b < n_blocks; b += NW) {
-    load_v(b);   // lands behind the score MFMAs
+    const bool more = b + NW < n_blocks;
+    load_v();   // lands behind the score MFMAs
+    if (more) {
+      entry_k(b + NW);
+      entries_v(b + NW);
+    }
     floatx4 sc[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) sc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -138,7 +171,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int j = 0; j < R; ++j) sc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[j][c][e], sc[j], 0, 0, 0);
-    if (b + NW < n_blocks) load_k(b + NW);   // lands behind the softmax and the value MFMAs
+    if (more) load_k();   // lands behind the softmax and the value MFMAs
     if ((b + 1) * kKB > total) {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -229,13 +262,22 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
 }
 
 template <int D, int R, int NW>
+void launch_gather_t(hipStream_t s, const UnitDesc* descs, const AttnItem* items, int n_items, const GatherArgs& g, const void* q,
+                     const void* k_cache, const void* v_cache, int N_k, float scale, void* out) {
+  typedef float T;
+  hipLaunchKernelGGL((attn_f32<D, R, NW, true>), dim3(n_items + g.n_moves), dim3(64 * NW), 0, s, items, (const T*)q,
+                     (const T*)k_cache, (const T*)v_cache, (const T*)g.k_new, (const T*)g.v_new, nullptr, nullptr, nullptr, 0, 0, N_k,
+                     scale, (T*)out, descs, g);
+}
+
+template <int D, int R, int NW>
 void launch_t(hipStream_t s, const AttnItem* items, int n_items, const void* q, const void* k_cache, const void* v_cache,
               const void* k_new, const void* v_new, void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k,
               float scale, void* out) {
   typedef float T;
-  hipLaunchKernelGGL((attn_f32<D, R, NW>), dim3(n_items), dim3(64 * NW), 0, s, items, (const T*)q, (const T*)k_cache,
+  hipLaunchKernelGGL((attn_f32<D, R, NW, false>), dim3(n_items), dim3(64 * NW), 0, s, items, (const T*)q, (const T*)k_cache,
                      (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app, pos_app, pos_new, fuse, N_k,
-                     scale, (T*)out);
+                     scale, (T*)out, nullptr, GatherArgs{});
 }
 
 }  // namespace
@@ -253,6 +295,21 @@ void launch_attn_f32(hipStream_t s, int head_dim, const AttnItem* items, int n_i
   } else {
     if (q_tile_rows == 16) launch_t<128, 1, 8>(HACK_ARGS);
     else launch_t<128, 2, 4>(HACK_ARGS);
+  }
+#undef HACK_ARGS
+}
+
+void launch_attn_f32_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int q_tile_rows,
+                            const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k, float scale,
+                            void* out) {
+  if (n_items + g.n_moves <= 0) return;
+#define HACK_ARGS s, descs, items, n_items, g, q, k_cache, v_cache, N_k, scale, out
+  if (head_dim == 64) {
+    if (q_tile_rows == 16) launch_gather_t<64, 1, 8>(HACK_ARGS);
+    else launch_gather_t<64, 2, 4>(HACK_ARGS);
+  } else {
+    if (q_tile_rows == 16) launch_gather_t<128, 1, 8>(HACK_ARGS);
+    else launch_gather_t<128, 2, 4>(HACK_ARGS);
   }
 #undef HACK_ARGS
 }

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
   if constexpr (GATHER) {
     const int mover = (int)blockIdx.x - ((int)gridDim.x - ga.n_moves);
     if (mover >= 0) {
-      move_rows<D, 64 * kWaves>(descs, ga, mover, N_k);
+      move_rows<D / 8, 64 * kWaves>(descs, ga, mover, N_k);
       return;
     }
   }

@@ -390,20 +390,22 @@ def test_step_plans_are_kept_per_state_and_dropped_when_there_are_too_many():
     hk.close()
 
 
+@pytest.mark.parametrize("dtype,B", [("bf16", 2), ("f32", 2), ("f32", 32)])   # float32: 16- and 32-query items
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("with_pos", [True, False])
-def test_steps_that_read_kept_rows_in_place(head_dim, with_pos):
-    """The key-split kernel attends over the kept rows where they lie and moves them in the same launch.  The outputs
+def test_steps_that_read_kept_rows_in_place(head_dim, with_pos, dtype, B):
+    """The key-split kernel and the float32 kernel attend over the kept rows where they lie and move them in the
+    same launch.  The outputs
     must be the bits that the same kernel gives over the moved rows, and the moved rows copies of the listed ones:
     lists whose seam between cached and new rows falls inside a block, between blocks, before the first and behind the
     last row; lengths around block and mover sizes; units that keep everything beside units that compress."""
     from tests import gpu_util as u
-    B, H = 2, 4
+    H = 4
     sides_n = [7, 90, 64, 131, 33, 200, 1, 95]
-    hk = u.make_hack(heads=H, head_dim=head_dim, dtype="bf16", max_units=B * H, max_cache_len=sum(sides_n), max_queries=max(sides_n),
+    hk = u.make_hack(heads=H, head_dim=head_dim, dtype=dtype, max_units=B * H, max_cache_len=sum(sides_n), max_queries=max(sides_n),
                      attention="split")
     types = np.array([0, 0, 1, 1], np.uint8)
-    budget = np.array([40, 64, 230, 10**6, 129, 31, 161, 10**6], np.int32)
+    budget = np.tile(np.array([40, 64, 230, 10**6, 129, 31, 161, 10**6], np.int32), B // 2)
     mc = hk.managed_cache(np.minimum(np.maximum(budget, 100), sum(sides_n)), with_pos=with_pos)
     gen = torch.Generator(u.DEV)
     gen.manual_seed(head_dim)
@@ -415,7 +417,7 @@ def test_steps_that_read_kept_rows_in_place(head_dim, with_pos):
         # heads 0: queries along e_0, keys of odd steps towards them and of even steps away from them
         q[:, 0, :, 0] += 4
         kn[:, 0, :, 0] += 6 if step % 2 else -6
-        q, kn, vn = (x.to(torch.bfloat16).contiguous() for x in (q, kn, vn))
+        q, kn, vn = (x.to(hk.torch_dtype).contiguous() for x in (q, kn, vn))
         off0, len0 = mc.view()
         k0, v0 = mc.k.clone(), mc.v.clone()
         p0 = mc.pos.clone() if with_pos else None
