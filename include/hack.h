@@ -127,6 +127,10 @@ hack_status hack_check(hack_ctx* ctx);
  *                        twice and never wait inside a kernel: safe when other
  *                        streams or processes share the device.  Same results
  *                        bit for bit.
+ * hack_step scores and selects the short units of a bf16 context (up to 256 to
+ * 1024 keys, by head_dim and number of units) with one work-group per unit in
+ * either mode: no exchange, the same importance up to the order in which a row's
+ * fp64 sum is formed.
  * Switching drains the device (it re-arms the exchange workspace); do it
  * outside stream captures.  fp32 contexts always score in two passes. */
 enum { HACK_SCORE_FUSED = 0, HACK_SCORE_TWO_PASS = 1 };
@@ -263,7 +267,8 @@ hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q,
  *   1  work items of 32 queries whose four waves split the keys and merge their
  *      partial softmax results at the end (bf16, early scale steps: few
  *      queries); in hack_step this kernel also performs the append when no unit
- *      of the step compresses.
+ *      of the step compresses, and otherwise reads the kept rows where they lie
+ *      while further work-groups of the launch move them.
  * The choice depends only on B * H, N_k and the context's head_dim.
  * Returns a negative hack_status for a NULL context or B, N_k < 1. */
 int32_t hack_attn_variant(const hack_ctx* ctx, int32_t B, int32_t N_k);
