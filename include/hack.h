@@ -31,7 +31,9 @@
  *  - Small per-call launch tables (offsets, lengths, work lists) are uploaded
  *    the first time a particular table is seen and reused afterwards, so a
  *    repeated schedule issues kernel launches only and can be captured in a
- *    HIP graph after one eager warm-up pass.
+ *    HIP graph after one eager warm-up pass.  A table first seen while the
+ *    stream is being captured is copied by that graph whenever it is replayed,
+ *    and uploaded by the next call outside a capture that needs it.
  */
 #ifndef HACK_MI355X_H
 #define HACK_MI355X_H

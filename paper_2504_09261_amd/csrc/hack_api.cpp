@@ -118,6 +118,7 @@ struct StepGroup {
   std::vector<int> launches;              // score launch groups
   unsigned long long* slots = nullptr;    // row-sum exchange area of the group's score launches
   const uint8_t* dev = nullptr;
+  size_t table = 0;                       // its number in the table store
   size_t o_desc = 0, o_comp = 0, o_merge = 0, o_rows = 0, o_items = 0, o_sit = 0, o_segs = 0, o_segb = 0, o_moves = 0;
   const UnitDesc* ddev() const { return reinterpret_cast<const UnitDesc*>(dev + o_desc); }
 };
@@ -136,6 +137,7 @@ struct StepNode {
   // its plan
   int n_obs = 0, tile = 0, max_budget = 0;   // max_budget: rows the longest kept-index list needs
   bool split = false, fuse_append = false, two_groups = false;
+  bool uploaded = false;            // both tables are on the device (false while only graphs hold their copies)
   StepGroup g[2];
   // the state after it
   std::vector<uint8_t> cur;         // which slab holds the unit's rows
@@ -198,11 +200,12 @@ struct Table {
 };
 
 // Returns the device address of a table with these contents, uploading it on
-// the given stream the first time it is seen.  Tables are immutable and keep
+// the given stream the first time it is seen (again, if that stream was being
+// captured: see table_cache.h).  Tables are immutable and keep
 // their address until the context is destroyed, so queued kernels and captured
 // graphs may go on using them.
-hack_status table_device(hack_ctx* ctx, const Table& t, hipStream_t stream, const uint8_t** dev) {
-  switch (ctx->tables->get(t.bytes.data(), t.bytes.size(), stream, dev)) {
+hack_status table_device(hack_ctx* ctx, const Table& t, hipStream_t stream, const uint8_t** dev, size_t* id = nullptr) {
+  switch (ctx->tables->get(t.bytes.data(), t.bytes.size(), stream, dev, id)) {
     case TableStatus::kOk: return HACK_OK;
     case TableStatus::kTooLarge:
       return fail(ctx, HACK_ECAPACITY, "launch table of %zu bytes exceeds the %zu-byte table chunk", t.bytes.size(), kTableChunkBytes);
@@ -1138,7 +1141,7 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->o_segs = t.add(plan.segs.data(), plan.segs.size());
   g->o_segb = t.add(plan.seg_begin.data(), plan.seg_begin.size());
   g->o_moves = t.add(moves.data(), moves.size());
-  return table_device(ctx, t, s, &g->dev);
+  return table_device(ctx, t, s, &g->dev, &g->table);
 }
 
 // score -> select -> append / gather (-> merge) of a group's units
@@ -1189,8 +1192,22 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
     launch_attn(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out, ctx->attn_kernel);
 }
 
+// Sees to it that a known step's tables are on the device for the work that is issued on `s` next: a step that was
+// planned while its stream was being captured has them only where that graph is replayed.
+hack_status upload_step(hack_ctx* ctx, StepNode* n, hipStream_t s) {
+  n->uploaded = true;
+  for (int i = 0; i < (n->two_groups ? 2 : 1); ++i) {
+    if (ctx->tables->upload(n->g[i].table, s) != TableStatus::kOk) {
+      n->uploaded = false;
+      return fail(ctx, HACK_EHIP, "uploading a launch table failed");
+    }
+    n->uploaded = n->uploaded && ctx->tables->uploaded(n->g[i].table);
+  }
+  return HACK_OK;
+}
+
 // The child of the cache's current state that these arguments lead to, if it is known.
-const StepNode* find_step(const hack_kvcache* c, int32_t N_k, const uint8_t* head_type, int H, const int32_t* budget, int U,
+StepNode* find_step(const hack_kvcache* c, int32_t N_k, const uint8_t* head_type, int H, const int32_t* budget, int U,
                           int32_t n_init, bool final_merge, bool two_pass) {
   for (const auto& p : c->at->next)
     if (p->N_k == N_k && p->n_init == n_init && p->final_merge == final_merge && p->two_pass == two_pass &&
@@ -1201,7 +1218,7 @@ const StepNode* find_step(const hack_kvcache* c, int32_t N_k, const uint8_t* hea
 
 // Validates and plans a step from the cache's current state, uploads its tables and adds it to the tree.
 hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k, const uint8_t* head_type, const int32_t* budget,
-                      int32_t n_init, bool final_merge, hipStream_t s, const StepNode** out) {
+                      int32_t n_init, bool final_merge, hipStream_t s, StepNode** out) {
   const int U = B * ctx->cfg.heads, H = ctx->cfg.heads;
   for (int h = 0; h < H; ++h)
     if (head_type[h] > 1) return fail(ctx, HACK_EINVAL, "head_type[%d] = %d is not a head class", h, head_type[h]);
@@ -1267,6 +1284,7 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
     const hack_status st = upload_group(ctx, units[i], *n, n->two_groups, rows, s, &n->g[i]);
     if (st != HACK_OK) return st;
   }
+  n->uploaded = ctx->tables->uploaded(n->g[0].table) && (!n->two_groups || ctx->tables->uploaded(n->g[1].table));
   if (cache->n_nodes >= kMaxStepNodes) {
     // the tree is full (arguments that keep changing): keep the current state alone and start over
     std::unique_ptr<StepNode> base(new (std::nothrow) StepNode());
@@ -1325,8 +1343,12 @@ static hack_status step_impl(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int3
   a.pos_new = (int32_t)cache->tokens_seen;
 
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const StepNode* n = find_step(cache, N_k, head_type, H, budget, U, n_init, final_merge, ctx->score_mode == HACK_SCORE_TWO_PASS);
-  if (!n && (st = plan_step(ctx, cache, B, N_k, head_type, budget, n_init, final_merge, s, &n)) != HACK_OK) return st;
+  StepNode* n = find_step(cache, N_k, head_type, H, budget, U, n_init, final_merge, ctx->score_mode == HACK_SCORE_TWO_PASS);
+  if (n) {
+    if (!n->uploaded && (st = upload_step(ctx, n, s)) != HACK_OK) return st;
+  } else if ((st = plan_step(ctx, cache, B, N_k, head_type, budget, n_init, final_merge, s, &n)) != HACK_OK) {
+    return st;
+  }
   if (n->max_budget > a.kstride)
     return fail(ctx, HACK_ECAPACITY, "idx_stride %lld < largest budget %d of a compressing unit", (long long)a.kstride, n->max_budget);
 

@@ -7,6 +7,11 @@
 // is full another one is chained behind it; chunks are released together at the
 // end.  Growth is bounded by a total limit.
 //
+// A copy issued on a stream that is being captured is not carried out, it becomes a
+// node of the graph.  Such a table is known (it has its address and its host mirror)
+// but not uploaded: every call that needs it issues the copy again, to the same
+// address with the same bytes, until one outside a capture has done so.
+//
 // The memory back end is a template parameter, so that the bookkeeping can be
 // exercised on the host without a device (the unit test plugs in malloc).
 //   struct Backend {
@@ -39,15 +44,17 @@ class TableCache {
     for (Chunk& c : chunks_) be_.release(c.dev, c.host);
   }
 
-  // Device address of a table with exactly these bytes.
-  TableStatus get(const uint8_t* bytes, size_t n, void* stream, const uint8_t** dev) {
+  // Device address of a table with exactly these bytes, for work that is issued on `stream` next.  id (may be NULL)
+  // gets a number for upload() and uploaded(), valid as long as the store.
+  TableStatus get(const uint8_t* bytes, size_t n, void* stream, const uint8_t** dev, size_t* id = nullptr) {
     const uint64_t h = hash(bytes, n);
     auto range = index_.equal_range(h);
     for (auto it = range.first; it != range.second; ++it) {
-      const Entry& e = it->second;
+      const Entry& e = entries_[it->second];
       if (e.bytes == n && memcmp(chunks_[e.chunk].host + e.offset, bytes, n) == 0) {
         *dev = chunks_[e.chunk].dev + e.offset;
-        return TableStatus::kOk;
+        if (id) *id = it->second;
+        return upload(it->second, stream);
       }
     }
     const size_t need = (n + kAlign - 1) / kAlign * kAlign;
@@ -62,12 +69,30 @@ class TableCache {
     Chunk& c = chunks_.back();
     const size_t off = c.used;
     memcpy(c.host + off, bytes, n);
-    if (!be_.upload(c.dev + off, c.host + off, n, stream)) return TableStatus::kUploadFailed;
+    entries_.push_back(Entry{chunks_.size() - 1, off, n, false});
+    const TableStatus st = upload(entries_.size() - 1, stream);
+    if (st != TableStatus::kOk) {
+      entries_.pop_back();
+      return st;
+    }
+    index_.emplace(h, entries_.size() - 1);
     c.used += need;
-    index_.emplace(h, Entry{chunks_.size() - 1, off, n});
     *dev = c.dev + off;
+    if (id) *id = entries_.size() - 1;
     return TableStatus::kOk;
   }
+
+  // Issues the copy of table `id` on `stream` unless an earlier one, outside any capture, has been issued.
+  TableStatus upload(size_t id, void* stream) {
+    Entry& e = entries_[id];
+    if (e.uploaded) return TableStatus::kOk;
+    Chunk& c = chunks_[e.chunk];
+    const bool recorded = !be_.may_alloc(stream);
+    if (!be_.upload(c.dev + e.offset, c.host + e.offset, e.bytes, stream)) return TableStatus::kUploadFailed;
+    e.uploaded = !recorded;
+    return TableStatus::kOk;
+  }
+  bool uploaded(size_t id) const { return entries_[id].uploaded; }
 
   // Allocates the first chunk ahead of time (so that a first table seen during a
   // stream capture still finds room).  Returns false if the allocation failed.
@@ -91,6 +116,7 @@ class TableCache {
   };
   struct Entry {
     size_t chunk, offset, bytes;
+    bool uploaded;   // a copy has been issued outside a capture
   };
   // Four independent 8-byte lanes (multiply, fold the high half down), so that the multiplies overlap: a table of a
   // few hundred kilobytes is hashed at memory speed instead of one multiply latency per byte (960 units: 25 us of
@@ -120,7 +146,8 @@ class TableCache {
   Backend be_;
   size_t chunk_bytes_, limit_bytes_;
   std::vector<Chunk> chunks_;
-  std::unordered_multimap<uint64_t, Entry> index_;
+  std::vector<Entry> entries_;
+  std::unordered_multimap<uint64_t, size_t> index_;   // hash -> entry
 };
 
 }  // namespace hack

@@ -1,0 +1,28 @@
+"""csrc/hack_api.cpp compiled for the host over a stand-in for the HIP runtime and the kernels (tests/host/): what the
+entry points plan, upload and launch, without a GPU."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    exe = tmp_path_factory.mktemp("api") / "api_check"
+    src = os.path.join(ROOT, "tests", "host", "api_check.cpp")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wno-unused", "-fsanitize=address,undefined", "-D__HIP_PLATFORM_AMD__",
+                    "-I" + os.path.join(ROCM, "include"), src, "-o", str(exe)], check=True)
+
+    def run(name):
+        r = subprocess.run([str(exe), name], capture_output=True, text=True)
+        sys.stdout.write(r.stdout)
+        assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr[-2000:]
+    return run
+
+
+def test_tables_first_seen_during_a_capture_are_not_taken_for_uploaded(check):
+    check("capture")

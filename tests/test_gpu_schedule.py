@@ -589,6 +589,51 @@ def test_graph_replays_reproduce_the_eager_schedule(cfg_id, batch, attention):
     hk.close()
 
 
+def test_eager_steps_after_a_discarded_capture_of_unseen_steps():
+    """A schedule whose steps are first seen while the stream is being captured: the graph, which alone holds the copies of
+    the launch tables, is thrown away unplayed.  The same steps issued eagerly must find their tables on the device; a
+    capture after that is replayed like any other.  Outputs against a context that never captured anything."""
+    u = _u()
+    cfg = wl.get_config(1, batch=1)
+    types, data = wl.head_types(cfg, 0), wl.gen_layer(cfg, 0)
+    budgets = [wl.step_budgets(cfg, 0, k) for k in range(1, cfg.n_steps + 1)]
+    ten = [[u.to_dev(x, cfg.dtype) for x in (data[k].q, data[k].k, data[k].v)] for k in range(1, cfg.n_steps + 1)]
+    cap = np.minimum(np.tile(wl.head_budgets(cfg, 0), cfg.batch), cfg.T_K)
+
+    def run(hk, mc, out):
+        mc.reset()
+        for i, (q, k, v) in enumerate(ten):
+            hk.step(mc, q, k, v, types, budgets[i], cfg.n_init, cfg.scale, out[i])
+
+    ref_hk, hk = u.make_hack(cfg), u.make_hack(cfg)
+    ref_mc, mc = ref_hk.managed_cache(cap), hk.managed_cache(cap)
+    ref, out = ([torch.zeros_like(t[0]) for t in ten] for _ in range(2))
+    run(ref_hk, ref_mc, ref)
+    st = torch.cuda.Stream()
+    for replays in (0, 3):
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(st):
+            with torch.cuda.graph(g, stream=st):
+                run(hk, mc, out)
+        torch.cuda.synchronize()
+        for rep in range(max(replays, 1)):
+            for o in out:
+                o.zero_()
+            torch.cuda.synchronize()
+            if replays:
+                with torch.cuda.stream(st):
+                    g.replay()
+            else:
+                run(hk, mc, out)
+            torch.cuda.synchronize()
+            hk.check()
+            assert all(torch.equal(a, b) for a, b in zip(ref, out)), (replays, rep)
+        del g
+    for x in (ref_mc, mc, ref_hk, hk):
+        x.close()
+
+
 def test_largest_supported_cache_through_individual_calls():
     """One contextual and one structural unit at the library's limit, T_in = 32768 rows (the
     selection keeps a unit's keys in LDS): score, select, compact, attend, each against the oracle;
