@@ -322,7 +322,8 @@ hack_status hack_kvcache_view(const hack_kvcache* c, hack_cache* view);
  * score -> select -> compact; then attention over the resulting cache.
  * Observation rows are the evenly strided n_obs = min(cfg n_obs, N_k).
  *   head_type HOST [H]; budget HOST [B*H]; n_init as in hack_select
- *   out DEVICE [B, H, N_k, d]
+ *   out DEVICE [B, H, N_k, d]; may be k_new or v_new (the step then stores the
+ *     new rows in a launch of its own before it attends)
  *   kept_idx_opt DEVICE int32 [B*H, idx_stride] or NULL: receives the kept
  *     indices of compressing units (rows of other units untouched).
  * Errors: as the individual calls; HACK_ECAPACITY if a unit would outgrow its slab. */

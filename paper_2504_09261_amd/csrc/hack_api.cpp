@@ -1086,7 +1086,15 @@ struct StepArgs {
   int64_t kstride;
   CachePtrs cp;
   int32_t pos_new;
+  // Attention may read k_new / v_new in place and update the cache while other work-groups of the launch already store
+  // their outputs: not where `out` shares memory with them.  The rows are then moved by a launch in front of it.
+  bool in_place;
 };
+
+bool overlap(const void* a, const void* b, size_t bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + bytes && y < x + bytes;
+}
 
 void add_unit(GroupUnits* u, StepGroup* g, const UnitDesc& d, bool merges, int N_k) {
   const int idx = (int)u->descs.size();
@@ -1158,7 +1166,7 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
               ctx->ws_stride);
     launch_select(s, g.ddev(), comp_dev, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
   }
-  if (!n.fuse_append && !g.gathered)
+  if (!a.in_place || (!n.fuse_append && !g.gathered))
     launch_move(s, ctx->elem_bytes, ctx->cfg.head_dim, g.ddev(), g.n_desc, g.max_rows, a.cp, a.cp, a.k_new, a.v_new, n.N_k,
                 a.pos_new, a.kept, a.kstride);
   if (g.n_merge > 0)   // compression, the merge included, precedes the attention of the step
@@ -1169,7 +1177,8 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
 
 void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
   const AttnItem* items = reinterpret_cast<const AttnItem*>(g.dev + g.o_items);
-  if (g.gathered) {
+  const int fuse = n.fuse_append && a.in_place ? 1 : 0;
+  if (g.gathered && a.in_place) {
     const GatherArgs ga{a.kept, a.kstride, ctx->seam, ctx->iota, reinterpret_cast<const MoveItem*>(g.dev + g.o_moves), g.n_moves,
                         a.pos_new, a.k_new, a.v_new, a.cp};
     if (ctx->cfg.dtype == HACK_F32)
@@ -1184,10 +1193,10 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
                        ctx->part_o, ctx->part_ml, ctx->part_count);
   else if (n.split)
     launch_attn_split(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v,
-                      a.cp.pos, a.pos_new, n.fuse_append ? 1 : 0, n.N_k, a.scale, a.out);
+                      a.cp.pos, a.pos_new, fuse, n.N_k, a.scale, a.out);
   else if (ctx->cfg.dtype == HACK_F32)
     launch_attn_f32(s, ctx->cfg.head_dim, items, g.n_items, n.tile, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v, a.cp.pos,
-                    a.pos_new, n.fuse_append ? 1 : 0, n.N_k, a.scale, a.out);
+                    a.pos_new, fuse, n.N_k, a.scale, a.out);
   else
     launch_attn(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out, ctx->attn_kernel);
 }
@@ -1341,6 +1350,8 @@ static hack_status step_impl(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int3
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out; a.scale = scale;
   a.cp = CachePtrs{cache->k, cache->v, cache->pos};
   a.pos_new = (int32_t)cache->tokens_seen;
+  const size_t new_bytes = (size_t)U * N_k * ctx->cfg.head_dim * ctx->elem_bytes;
+  a.in_place = !overlap(out, k_new, new_bytes) && !overlap(out, v_new, new_bytes);
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   StepNode* n = find_step(cache, N_k, head_type, H, budget, U, n_init, final_merge, ctx->score_mode == HACK_SCORE_TWO_PASS);

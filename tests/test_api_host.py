@@ -26,3 +26,7 @@ def check(tmp_path_factory):
 
 def test_tables_first_seen_during_a_capture_are_not_taken_for_uploaded(check):
     check("capture")
+
+
+def test_steps_whose_outputs_lie_over_the_new_rows_move_them_first(check):
+    check("out_over_new_rows")

@@ -448,6 +448,37 @@ def test_steps_that_read_kept_rows_in_place(head_dim, with_pos, dtype, B):
     hk.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("over", ["k", "v"])
+def test_outputs_stored_over_the_new_keys_or_values(dtype, over):
+    """hack_step with out = k_new or v_new, steps with and without compression: outputs and cache as with a tensor of
+    their own, bit for bit."""
+    u = _u()
+    H, d, sides_n = 3, 64, [30, 64, 150, 97]
+    hk = u.make_hack(heads=H, head_dim=d, dtype=dtype, max_units=2 * H, max_cache_len=sum(sides_n), max_queries=max(sides_n))
+    types, budget = np.array([0, 1, 0], np.uint8), np.array([100, 180, 70, 10**6, 120, 90], np.int32)
+    caps = np.minimum(np.maximum(budget, 94), sum(sides_n))
+    mcs = [hk.managed_cache(caps) for _ in range(2)]
+    for m in mcs:
+        m.k.zero_(), m.v.zero_(), m.pos.zero_()
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(17)
+    for step, n in enumerate(sides_n):
+        q, kn, vn = (torch.randn((2, H, n, d), generator=gen, device=u.DEV).to(hk.torch_dtype) for _ in range(3))
+        now = np.full_like(budget, 10**6) if step < 2 else budget
+        want = torch.empty_like(q)
+        hk.step(mcs[0], q, kn.clone(), vn.clone(), types, now, 5, 0.125, want)
+        got = kn if over == "k" else vn
+        hk.step(mcs[1], q, kn, vn, types, now, 5, 0.125, got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), step
+        assert all(torch.equal(getattr(mcs[0], x), getattr(mcs[1], x)) for x in ("k", "v", "pos")), step
+    hk.check()
+    for m in mcs:
+        m.close()
+    hk.close()
+
+
 @pytest.mark.parametrize("head_dim,B,sides_n", [
     (64, 1, [5, 40, 41, 170]),          # units of up to 256 keys
     (64, 1, [5, 200, 51, 256]),         # up to 512: exactly 512 at the last step
