@@ -392,6 +392,9 @@ __global__ __launch_bounds__(kThreads, 2) void hv_colmoments(
       acc = fma(-c, c, acc);   // all keys together: sum_j Var_i(A[i, j])
     }
   }
+  // What the rounding of the two totals can leave where there is next to no variance: one query has none at all, and
+  // a sum of variances is not negative.  (NaN stays NaN.)
+  if (N_k == 1 || acc < 0.0) acc -= acc;
   if (col == 0 && t0 < len) atomicAdd(&sigma[d.unit], acc);
 }
 

@@ -78,6 +78,24 @@ def test_head_variance_ragged_shapes_and_degenerate_cases():
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
+def test_head_variance_without_variance(head_dim):
+    """One query: exactly zero whatever the keys.  The same query many times over: never negative, and within the fp64
+    rounding of the two moments, whose size is at most N sum_j A_j^2 / N <= 1 (2^-53 per sum, some 1e3 of them)."""
+    u = _u()
+    rng = np.random.default_rng(head_dim)
+    lens = [1, 33, 64, 257, 300, 1000]
+    hk = u.make_hack(heads=6, head_dim=head_dim, dtype="bf16", max_units=6, max_cache_len=1000, max_queries=70)
+    cache, _ = u.build_cache([(k, k) for k in (u.rand_values(rng, (n, head_dim), "bf16") for n in lens)], head_dim, "bf16")
+    row = u.rand_values(rng, (1, 6, 1, head_dim), "bf16")
+    for Nk in (1, 70):
+        sigma = torch.full((6,), -1.0, dtype=torch.float64, device=u.DEV)
+        hk.head_variance(u.to_dev(np.repeat(row, Nk, axis=2), "bf16"), cache, 0.125, sigma)
+        got = sigma.cpu().numpy()
+        assert np.all(got == 0.0) if Nk == 1 else np.all((got >= 0.0) & (got < 1e-12)), (Nk, got)
+    hk.close()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("Nk,lens", [(96, [1, 96, 224]), (225, [225, 256, 257]), (257, [320, 353, 640])])
 def test_head_variance_pipeline_lengths_and_rising_logits(head_dim, Nk, lens):
     """Lengths around the pipeline's fill, steady loop and drain on both sides, with keys that grow along the cache so
