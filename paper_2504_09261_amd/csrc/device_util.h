@@ -76,6 +76,14 @@ template <int N> __device__ __forceinline__ void dma_wait_but() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Between LDS words that lanes of a wave write and other lanes of the same wave read (or the other way round): the
+// hardware carries out a wave's LDS operations in order, this keeps the compiler from changing that order.  No
+// instruction is emitted.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---- lane-pair exchanges ----------------------------------------------------
 // The 32x32 accumulator splits a column over the lane pair (l, l ^ 32); one VALU
 // swap instead of an LDS permute brings the two halves together.

@@ -262,7 +262,8 @@ __device__ __forceinline__ double exp2_fix(int qv) {
 // Row sums of a wave, through 8 KiB of LDS: put_row leaves the value of register r (observation row c_row(r, half), column
 // col) of every lane, take_rows returns the sum of row lane / 2 over the 32 columns.  256 bytes a row, the 16-byte chunk at
 // position c holds columns 2 (c ^ row % 16) and the next: 16 writes and 8 reads without bank conflicts and
-// 16 additions, where a shuffle tree for each of the 16 registers takes 240 vector instructions.
+// 16 additions, where a shuffle tree for each of the 16 registers takes 240 vector instructions.  wave_lds_order() goes
+// between the two, and before the buffer is written again.
 __device__ __forceinline__ void put_row(char* buf, int r, int col, int half, double v) {
   const int row = c_row(r, half);
   *reinterpret_cast<double*>(buf + row * 256 + (((col >> 1) ^ (row & 15)) << 4) + (col & 1) * 8) = v;
@@ -513,7 +514,9 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
         put_row(buf, r, col, half, lsum);
       }
     }
+    wave_lds_order();
     const double l = take_rows(buf, lane);
+    wave_lds_order();
     if ((lane & 1) == 0) red[lane >> 1] = l;
   }
   __syncthreads();
@@ -746,6 +749,7 @@ __global__ __launch_bounds__(64 * NW) void score_select(
       if (t < n_tiles && (w + t * NW) * 32 + col < T_in) lsum += pq[t][r];
     put_row(&bufs[w][0], r, col, half, lsum);
   }
+  wave_lds_order();
   const double l = take_rows(&bufs[w][0], lane);
   if ((lane & 1) == 0) red[w][lane >> 1] = l;
   __syncthreads();                     // tile buffers are free from here on
@@ -755,6 +759,7 @@ __global__ __launch_bounds__(64 * NW) void score_select(
     for (int k = 0; k < NW; ++k) tot += red[k][lane];
     inv_s[w][lane] = (lane < n_obs) ? 1.0 / tot : 0.0;
   }
+  wave_lds_order();
   double inv_r[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) inv_r[r] = inv_s[w][c_row(r, half)];
