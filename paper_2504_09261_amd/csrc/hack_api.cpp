@@ -172,10 +172,18 @@ hack_status fail(hack_ctx* ctx, hack_status s, const char* fmt, ...) {
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    ctx->err = buf;
+    try {
+      ctx->err = buf;
+    } catch (...) {   // no memory for the message: the status says enough
+      ctx->err.clear();
+    }
   }
   return s;
 }
+
+// Ends the body of an entry point that allocates host memory (`try { ... } HACK_NO_THROW(ctx)`): exceptions stop here.
+#define HACK_NO_THROW(ctx) \
+  catch (...) { return fail(ctx, HACK_EHIP, "out of host memory"); }
 
 #define HIP_TRY(ctx, call)                                                              \
   do {                                                                                  \
@@ -619,8 +627,12 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   if (e == hipSuccess) e = hipMemset(ctx->rowstat, 0xFF, n_slots * sizeof(unsigned long long));   // every slot empty
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e == hipSuccess) {
-    ctx->tables = new (std::nothrow) TableCache<HipTableBackend>(HipTableBackend{}, kTableChunkBytes, kTableLimitBytes);
-    if (!ctx->tables || !ctx->tables->reserve_first_chunk()) e = hipErrorOutOfMemory;
+    try {
+      ctx->tables = new TableCache<HipTableBackend>(HipTableBackend{}, kTableChunkBytes, kTableLimitBytes);
+      if (!ctx->tables->reserve_first_chunk()) e = hipErrorOutOfMemory;
+    } catch (...) {
+      e = hipErrorOutOfMemory;
+    }
   }
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->aux_stream, hipStreamNonBlocking);   // default priority
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming);
@@ -673,7 +685,7 @@ extern "C" void hack_destroy(hack_ctx* ctx) {
 extern "C" hack_status hack_score(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q, const int32_t* q_idx,
                                   int32_t n_obs, float scale, const hack_cache* in, const void* k_new,
                                   const uint8_t* active, float* importance, int64_t imp_stride,
-                                  hack_stream stream) {
+                                  hack_stream stream) try {
   hack_status st = check_common(ctx, B, N_k, true);
   if (st != HACK_OK) return st;
   const int U = B * ctx->cfg.heads;
@@ -723,13 +735,13 @@ extern "C" hack_status hack_score(hack_ctx* ctx, int32_t B, int32_t N_k, const v
             importance, imp_stride);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 // The same call for callers that cannot allocate (see hack.h): scratch in the library's fixed device array.
 extern "C" hack_status hack_score_static(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q, const int32_t* q_idx,
                                          int32_t n_obs, float scale, const hack_cache* in, const void* k_new,
                                          const uint8_t* active, float* importance, int64_t imp_stride,
-                                         hack_stream stream) {
+                                         hack_stream stream) try {
   hack_status st = check_common(ctx, B, N_k, true);
   if (st != HACK_OK) return st;
   if (ctx->cfg.dtype != HACK_BF16) return fail(ctx, HACK_EUNSUPPORTED, "hack_score_static is implemented for bf16 contexts");
@@ -768,7 +780,7 @@ extern "C" hack_status hack_score_static(hack_ctx* ctx, int32_t B, int32_t N_k, 
   HIP_TRY(ctx, launch_score_static(static_cast<hipStream_t>(stream), ctx->cfg.device, ctx->cfg.head_dim, plan, q, n_obs, N_k, scale,
                                    in->k, k_new, importance, imp_stride, ctx->fault));
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 // ---------------------------------------------------------------------------
 // a2: select
@@ -776,7 +788,7 @@ extern "C" hack_status hack_score_static(hack_ctx* ctx, int32_t B, int32_t N_k, 
 extern "C" hack_status hack_select(hack_ctx* ctx, int32_t B, const float* importance, int64_t imp_stride,
                                    const int32_t* t_in, const uint8_t* head_type, const int32_t* budget,
                                    int32_t n_init, int32_t n_recent, int32_t* kept_idx, int64_t idx_stride,
-                                   int32_t* len_out, hack_stream stream) {
+                                   int32_t* len_out, hack_stream stream) try {
   hack_status st = check_common(ctx, B, 0, false);
   if (st != HACK_OK) return st;
   const int U = B * ctx->cfg.heads, H = ctx->cfg.heads;
@@ -813,14 +825,14 @@ extern "C" hack_status hack_select(hack_ctx* ctx, int32_t B, const float* import
                 kept_idx, idx_stride, nullptr);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 // ---------------------------------------------------------------------------
 // a3: compact
 // ---------------------------------------------------------------------------
 extern "C" hack_status hack_compact(hack_ctx* ctx, int32_t B, int32_t N_k, const hack_cache* in, const void* k_new,
                                     const void* v_new, int32_t pos_new, const int32_t* kept_idx, int64_t idx_stride,
-                                    const hack_cache* out, hack_stream stream) {
+                                    const hack_cache* out, hack_stream stream) try {
   const bool has_new = (k_new != nullptr);
   hack_status st = check_common(ctx, B, N_k, has_new);
   if (st != HACK_OK) return st;
@@ -867,14 +879,14 @@ extern "C" hack_status hack_compact(hack_ctx* ctx, int32_t B, int32_t N_k, const
               pout, k_new, v_new, N_k, pos_new, kept_idx, idx_stride);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 // ---------------------------------------------------------------------------
 // final-step merge of contextual heads
 // ---------------------------------------------------------------------------
 extern "C" hack_status hack_merge(hack_ctx* ctx, int32_t B, int32_t N_k, const hack_cache* in, const void* k_new,
                                   const void* v_new, const int32_t* kept_idx, int64_t idx_stride, const uint8_t* active,
-                                  const hack_cache* out, hack_stream stream) {
+                                  const hack_cache* out, hack_stream stream) try {
   const bool has_new = (k_new != nullptr);
   hack_status st = check_common(ctx, B, N_k, has_new);
   if (st != HACK_OK) return st;
@@ -921,13 +933,13 @@ extern "C" hack_status hack_merge(hack_ctx* ctx, int32_t B, int32_t N_k, const h
                ctx->merge_inv, ctx->ws_stride);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 // ---------------------------------------------------------------------------
 // a4: attention
 // ---------------------------------------------------------------------------
 extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q, const hack_cache* kv,
-                                 float scale, void* out, hack_stream stream) {
+                                 float scale, void* out, hack_stream stream) try {
   hack_status st = check_common(ctx, B, N_k, true);
   if (st != HACK_OK) return st;
   const int U = B * ctx->cfg.heads;
@@ -972,7 +984,7 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
                 kv->k, kv->v, N_k, scale, out, ctx->attn_kernel);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 extern "C" int32_t hack_attn_variant(const hack_ctx* ctx, int32_t B, int32_t N_k) {
   if (!ctx || B < 1 || N_k < 1) return (int32_t)HACK_EINVAL;
@@ -983,7 +995,7 @@ extern "C" int32_t hack_attn_variant(const hack_ctx* ctx, int32_t B, int32_t N_k
 // offline head classification: attention variance
 // ---------------------------------------------------------------------------
 extern "C" hack_status hack_head_variance(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q, const hack_cache* kv,
-                                          float scale, double* sigma, hack_stream stream) {
+                                          float scale, double* sigma, hack_stream stream) try {
   hack_status st = check_common(ctx, B, N_k, true);
   if (st != HACK_OK) return st;
   if (ctx->cfg.dtype != HACK_BF16) return fail(ctx, HACK_EUNSUPPORTED, "head variance is implemented for bf16 contexts");
@@ -1010,7 +1022,7 @@ extern "C" hack_status hack_head_variance(hack_ctx* ctx, int32_t B, int32_t N_k,
                        ctx->hv_stats, sigma);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 // ---------------------------------------------------------------------------
 // a5: managed cache + fused step
@@ -1027,7 +1039,7 @@ extern "C" hack_status hack_kvcache_rows_required(int32_t n_units, const int32_t
 }
 
 extern "C" hack_status hack_kvcache_create(hack_ctx* ctx, int32_t n_units, const int32_t* cap, void* k_mem,
-                                           void* v_mem, int32_t* pos_mem, int64_t mem_rows, hack_kvcache** out) {
+                                           void* v_mem, int32_t* pos_mem, int64_t mem_rows, hack_kvcache** out) try {
   if (!ctx) return HACK_EINVAL;
   if (!out || !cap || !k_mem || !v_mem) return fail(ctx, HACK_EINVAL, "NULL argument");
   *out = nullptr;
@@ -1037,8 +1049,7 @@ extern "C" hack_status hack_kvcache_create(hack_ctx* ctx, int32_t n_units, const
   int64_t need;
   if (hack_kvcache_rows_required(n_units, cap, &need) != HACK_OK) return fail(ctx, HACK_EINVAL, "cap entries must be >= 1");
   if (need > mem_rows) return fail(ctx, HACK_ECAPACITY, "cache needs %lld rows, %lld given", (long long)need, (long long)mem_rows);
-  hack_kvcache* c = new (std::nothrow) hack_kvcache();
-  if (!c) return fail(ctx, HACK_EHIP, "out of host memory");
+  std::unique_ptr<hack_kvcache> c(new hack_kvcache());
   c->ctx = ctx; c->n_units = n_units; c->k = k_mem; c->v = v_mem; c->pos = pos_mem; c->rows = mem_rows; c->tokens_seen = 0;
   c->cap.assign(cap, cap + n_units);
   c->slab[0].resize(n_units); c->slab[1].resize(n_units);
@@ -1050,9 +1061,9 @@ extern "C" hack_status hack_kvcache_create(hack_ctx* ctx, int32_t n_units, const
     c->slab[1][u] = r; r += round_up(cap[u], 8);
     c->root.off[u] = c->slab[0][u];
   }
-  *out = c;
+  *out = c.release();
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 extern "C" void hack_kvcache_destroy(hack_kvcache* c) { delete c; }
 
@@ -1231,8 +1242,7 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
   const int U = B * ctx->cfg.heads, H = ctx->cfg.heads;
   for (int h = 0; h < H; ++h)
     if (head_type[h] > 1) return fail(ctx, HACK_EINVAL, "head_type[%d] = %d is not a head class", h, head_type[h]);
-  std::unique_ptr<StepNode> n(new (std::nothrow) StepNode());
-  if (!n) return fail(ctx, HACK_EHIP, "out of host memory");
+  std::unique_ptr<StepNode> n(new StepNode());
   const StepNode& from = *cache->at;
   std::vector<UnitDesc> descs(U);
   int n_comp = 0, n_side = 0;
@@ -1296,8 +1306,7 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
   n->uploaded = ctx->tables->uploaded(n->g[0].table) && (!n->two_groups || ctx->tables->uploaded(n->g[1].table));
   if (cache->n_nodes >= kMaxStepNodes) {
     // the tree is full (arguments that keep changing): keep the current state alone and start over
-    std::unique_ptr<StepNode> base(new (std::nothrow) StepNode());
-    if (!base) return fail(ctx, HACK_EHIP, "out of host memory");
+    std::unique_ptr<StepNode> base(new StepNode());
     base->cur = from.cur; base->off = from.off; base->len = from.len;
     const bool at_root = cache->at == &cache->root;
     cache->root.next.clear();
@@ -1331,7 +1340,7 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
 static hack_status step_impl(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k, const void* q,
                              const void* k_new, const void* v_new, const uint8_t* head_type,
                              const int32_t* budget, int32_t n_init, float scale, void* out,
-                             int32_t* kept_idx_opt, int64_t idx_stride, hack_stream stream, bool final_merge) {
+                             int32_t* kept_idx_opt, int64_t idx_stride, hack_stream stream, bool final_merge) try {
   hack_status st = check_common(ctx, B, N_k, true);
   if (st != HACK_OK) return st;
   if (final_merge && ctx->cfg.dtype != HACK_BF16)
@@ -1379,7 +1388,7 @@ static hack_status step_impl(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int3
   cache->at = n;
   cache->tokens_seen += N_k;
   return HACK_OK;
-}
+} HACK_NO_THROW(ctx)
 
 extern "C" hack_status hack_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k, const void* q,
                                  const void* k_new, const void* v_new, const uint8_t* head_type,

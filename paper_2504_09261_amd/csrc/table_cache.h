@@ -62,9 +62,7 @@ class TableCache {
     if (chunks_.empty() || chunks_.back().used + need > chunk_bytes_) {
       if (!be_.may_alloc(stream)) return TableStatus::kFullDuringCapture;
       if ((chunks_.size() + 1) * chunk_bytes_ > limit_bytes_) return TableStatus::kLimit;
-      Chunk c{};
-      if (!be_.alloc(chunk_bytes_, &c.dev, &c.host)) return TableStatus::kAllocFailed;
-      chunks_.push_back(c);
+      if (!add_chunk()) return TableStatus::kAllocFailed;
     }
     Chunk& c = chunks_.back();
     const size_t off = c.used;
@@ -97,11 +95,7 @@ class TableCache {
   // Allocates the first chunk ahead of time (so that a first table seen during a
   // stream capture still finds room).  Returns false if the allocation failed.
   bool reserve_first_chunk() {
-    if (!chunks_.empty()) return true;
-    Chunk c{};
-    if (!be_.alloc(chunk_bytes_, &c.dev, &c.host)) return false;
-    chunks_.push_back(c);
-    return true;
+    return !chunks_.empty() || add_chunk();
   }
 
   size_t chunks() const { return chunks_.size(); }
@@ -114,6 +108,13 @@ class TableCache {
     uint8_t* host;
     size_t used;
   };
+  bool add_chunk() {
+    chunks_.reserve(chunks_.size() + 1);   // first, so that an exception leaks no chunk
+    Chunk c{};
+    if (!be_.alloc(chunk_bytes_, &c.dev, &c.host)) return false;
+    chunks_.push_back(c);
+    return true;
+  }
   struct Entry {
     size_t chunk, offset, bytes;
     bool uploaded;   // a copy has been issued outside a capture

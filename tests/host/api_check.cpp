@@ -42,9 +42,9 @@ struct Setup {
   }
   hack_status step(int n, int budget, bool final_merge = false, int n_init = 5, void* to = nullptr) {
     const uint8_t types[kH] = {0, 1, 0, 1};
-    std::vector<int32_t> b(kH, budget);
+    const int32_t b[kH] = {budget, budget, budget, budget};
     auto fn = final_merge ? hack_step_final : hack_step;
-    return fn(ctx, cache, 1, n, q, k, v, types, b.data(), n_init, 0.125f, to ? to : out, nullptr, 0, kStream);
+    return fn(ctx, cache, 1, n, q, k, v, types, b, n_init, 0.125f, to ? to : out, nullptr, 0, kStream);
   }
   // three steps, the last one compresses
   bool schedule() {
@@ -147,6 +147,90 @@ int out_over_new_rows() {
   return 0;
 }
 
+// Every allocation of a call fails once: the call returns an error, and the same call succeeds afterwards.
+template <typename Call>
+bool survives(Call call) {
+  for (long k = 0;; ++k) {
+    if (k > 5000) return false;
+    stub::allocation_failed = false;
+    stub::allocations_left = k;
+    const hack_status st = call();
+    stub::allocations_left = -1;
+    if (!stub::allocation_failed) return st == HACK_OK && k > 0;
+    // (an allocation that has a fallback, as the buffer of a stable sort, may fail without failing the call)
+    if (st != HACK_OK && st != HACK_EHIP) return false;
+  }
+}
+
+int no_exceptions() {
+  for (int dtype : {HACK_BF16, HACK_F32}) {
+    CHECK(survives([&] {
+      hack_config cfg{0, kH, kD, dtype, kH, 128, 64, 32};
+      hack_ctx* ctx;
+      const hack_status st = hack_create(&ctx, &cfg);
+      if (st == HACK_OK) hack_destroy(ctx);
+      return st;
+    }));
+    CHECK(stub::device_memory.empty());
+    const std::vector<int32_t> caps(kH, 200);
+    {
+      Setup s(dtype, 64, 128, 64);
+      int64_t rows;
+      hack_kvcache_rows_required(kH, caps.data(), &rows);
+      CHECK(survives([&] {
+        hack_kvcache* c;
+        const hack_status st = hack_kvcache_create(s.ctx, kH, caps.data(), s.q, s.q, nullptr, rows, &c);
+        if (st == HACK_OK) hack_kvcache_destroy(c);
+        return st;
+      }));
+    }
+    // steps: a fresh cache each time, so that every call plans; a failed step leaves the state alone
+    for (int last = 0; last < 3; ++last) {
+      if (last == 2 && dtype == HACK_F32) continue;
+      CHECK(survives([&] {
+        ++stub::quiet;
+        Setup s(dtype, 64, 128, 64);
+        s.step(8, 1 << 30);
+        s.step(40, 1 << 30);
+        --stub::quiet;
+        const hack_status st = s.step(last == 0 ? 10 : 30, last == 0 ? 1 << 30 : 50, last == 2);
+        const stub::Quiet checks;
+        hack_cache view;
+        hack_kvcache_view(s.cache, &view);
+        for (int u = 0; u < kH; ++u)
+          if (view.len[u] != (st != HACK_OK ? 48 : last == 0 ? 58 : 50)) return HACK_EINVAL;
+        if (s.step(last == 0 ? 2 : 5, 50) != HACK_OK) return HACK_EINVAL;
+        return st;
+      }));
+    }
+    {
+      Setup s(dtype, 64, 128, 64);
+      const int64_t off[kH] = {0, 128, 256, 384}, off_out[kH] = {512, 640, 768, 896};
+      const int32_t len[kH] = {60, 50, 40, 30}, len_out[kH] = {20, 20, 20, 20}, t_in[kH] = {80, 70, 60, 50};
+      const uint8_t types[kH] = {0, 1, 0, 1};
+      std::vector<uint8_t> rows(1024 * kD * 4 + 64);
+      void* p = reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(rows.data()) + 63) / 64 * 64);
+      const hack_cache in{p, p, nullptr, 1024, off, len}, out{p, p, nullptr, 1024, off_out, len_out};
+      int32_t* kept = static_cast<int32_t*>(p);
+      float* imp = static_cast<float*>(p);
+      double* sigma = static_cast<double*>(p);
+      int n = 0;
+      // other arguments each time, so that every call builds and uploads a table
+      CHECK(survives([&] { return hack_score(s.ctx, 1, 20 + n++ % 40, s.q, nullptr, 16, 0.1f, &in, s.k, nullptr, imp, 128, kStream); }));
+      CHECK(survives([&] { return hack_select(s.ctx, 1, imp, 128, t_in, types, len_out, n++ % 30, 20, kept, 128, nullptr, kStream); }));
+      CHECK(survives([&] { return hack_compact(s.ctx, 1, 20 + n++ % 40, &in, s.k, s.v, 0, kept, 128, &out, kStream); }));
+      CHECK(survives([&] { return hack_attn(s.ctx, 1, 20 + n++ % 40, s.q, &in, 0.1f, s.out, kStream); }));
+      if (dtype == HACK_BF16) {
+        CHECK(survives([&] { return hack_score_static(s.ctx, 1, 20, s.q, nullptr, 16, 0.1f, &in, s.k, nullptr, imp, 128, kStream); }));
+        CHECK(survives([&] { return hack_merge(s.ctx, 1, 20 + n++ % 40, &in, s.k, s.v, kept, 128, nullptr, &out, kStream); }));
+        CHECK(survives([&] { return hack_head_variance(s.ctx, 1, 20, s.q, n++ % 2 ? &in : &out, 0.1f, sigma, kStream); }));
+      }
+    }
+    CHECK(stub::bad_launches == 0 && stub::device_memory.empty());
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -154,6 +238,7 @@ int main(int argc, char** argv) {
   int rc = 2;
   if (which == "capture") rc = capture();
   if (which == "out_over_new_rows") rc = out_over_new_rows();
+  if (which == "no_exceptions") rc = no_exceptions();
   if (rc == 0) printf("ok\n");
   return rc;
 }

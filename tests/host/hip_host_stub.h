@@ -11,12 +11,29 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <new>
 #include <string>
 #include <vector>
 
 #include "../../paper_2504_09261_amd/csrc/hack_internal.h"
 
 namespace stub {
+
+// Allocations of the code under test that succeed before the next one fails (-1: all do); the stand-in's own do not count.
+inline long allocations_left = -1;
+inline bool allocation_failed = false;
+inline int quiet = 0;
+struct Quiet {
+  Quiet() { ++quiet; }
+  ~Quiet() { --quiet; }
+};
+inline void* allocate(size_t n) {
+  if (!quiet && allocations_left >= 0 && allocations_left-- == 0) {
+    allocation_failed = true;
+    return nullptr;
+  }
+  return malloc(n ? n : 1);
+}
 
 struct Graph {
   std::vector<std::function<void()>> nodes;
@@ -42,6 +59,7 @@ inline void replay(const Graph& g) {
 
 // A launch over n descriptors: all of them must have been written.
 inline void launch(const char* name, void* stream, const hack::UnitDesc* descs, const int32_t* list, int n) {
+  Quiet q;
   submit(stream, [=] {
     launches.push_back(name);
     for (int i = 0; i < n; ++i) {
@@ -55,6 +73,7 @@ inline void launch(const char* name, void* stream, const hack::UnitDesc* descs, 
   });
 }
 inline void launch_items(const char* name, void* stream, const hack::AttnItem* items, int n) {
+  Quiet q;
   submit(stream, [=] {
     launches.push_back(name);
     for (int i = 0; i < n; ++i)
@@ -67,8 +86,18 @@ inline void launch_items(const char* name, void* stream, const hack::AttnItem* i
 
 }  // namespace stub
 
+void* operator new(size_t n) {
+  if (void* p = stub::allocate(n)) return p;
+  throw std::bad_alloc();
+}
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return stub::allocate(n); }
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+void operator delete(void* p, const std::nothrow_t&) noexcept { free(p); }
+
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
+  stub::Quiet q;
   *p = malloc(n);
   if (!*p) return hipErrorOutOfMemory;
   memset(*p, 0xEE, n);
@@ -85,6 +114,7 @@ hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t stream) {
+  stub::Quiet q;
   if (stub::captured(stream)) ++stub::capture->copies;
   stub::submit(stream, [=] { ++stub::copies; memcpy(d, s, n); });
   return hipSuccess;
@@ -123,6 +153,7 @@ void launch_select(hipStream_t s, const UnitDesc* d, const int32_t* l, int n, in
 }
 void launch_score_fused(hipStream_t s, int, int, bool two_pass, const ScoreItem* items, int n, const void*, const int32_t*, int, int, float,
                         const void*, const void*, unsigned long long*, int, unsigned*, float*, int64_t, int*, int, const unsigned*, int) {
+  stub::Quiet q;
   stub::submit(s, [=] {
     stub::launches.push_back(two_pass ? "score_two_pass" : "score_fused");
     for (int i = 0; i < n; ++i)
@@ -140,6 +171,7 @@ void launch_attn(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n,
 }
 void launch_attn_stream(hipStream_t s, int, const UnitDesc*, const AttnSeg*, const int32_t* begin, int n, const void*, const void*,
                         const void*, int, float, void*, float*, float*, unsigned*) {
+  stub::Quiet q;
   stub::submit(s, [=] {
     stub::launches.push_back("attn_stream");
     for (int i = 0; i < n; ++i) if (begin[i] < 0 || begin[i + 1] < begin[i]) { ++stub::bad_launches; return; }

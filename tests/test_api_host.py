@@ -30,3 +30,7 @@ def test_tables_first_seen_during_a_capture_are_not_taken_for_uploaded(check):
 
 def test_steps_whose_outputs_lie_over_the_new_rows_move_them_first(check):
     check("out_over_new_rows")
+
+
+def test_no_exception_crosses_the_abi_when_host_memory_runs_out(check):
+    check("no_exceptions")
