@@ -67,7 +67,7 @@ struct hack_ctx {
   int32_t* kept = nullptr;       // [max_units, ws_stride]
   int32_t* seam = nullptr;       // [max_units] kept rows of the step's selection that come from the cache
   int32_t* iota = nullptr;       // [kIotaRows] 0, 1, 2, ...
-  double* stats = nullptr;       // fp32 path: [max_units, max_chunks, 32, 2] softmax partials
+  double* stats = nullptr;       // fp32 path: [score_f32_max_groups, 32, 2] softmax partials
   unsigned long long* rowstat = nullptr;  // bf16 path: [max_units, score_groups, 32] row-sum exchange slots, all-ones between launches
   unsigned long long* rowstat_side = nullptr;  // the same for the side branch of hack_step (two-pass form: its slots are not re-armed)
   int score_groups = 0;          // work-groups a unit of max_cache_len keys is scored by
@@ -98,7 +98,6 @@ struct hack_ctx {
   hipStream_t aux_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   int64_t ws_stride = 0;
-  int max_chunks = 0;
   // launch-table cache: tables keep their device address for the life of the context
   TableCache<HipTableBackend>* tables = nullptr;
   std::string err;
@@ -574,7 +573,6 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   ctx->cfg = *cfg;
   ctx->elem_bytes = cfg->dtype == HACK_F32 ? 4 : 2;
   ctx->ws_stride = round_up(cfg->max_cache_len, 64);
-  ctx->max_chunks = (cfg->max_cache_len + kScoreF32Chunk - 1) / kScoreF32Chunk;
   ctx->split_max_items = split_max_items_default(cfg->head_dim);
   ctx->spin_limit = kScoreSpinLimit;
   // test hook: a tiny limit makes the score kernel's bounded wait give up (every work-group still exits normally)
@@ -599,7 +597,7 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
     e = rows ? hipMemcpy(ctx->iota, rows.get(), kIotaRows * sizeof(int32_t), hipMemcpyHostToDevice) : hipErrorOutOfMemory;
   }
   if (e == hipSuccess && cfg->dtype == HACK_F32)
-    e = hipMalloc((void**)&ctx->stats, (size_t)cfg->max_units * ctx->max_chunks * kMaxObs * 2 * sizeof(double));
+    e = hipMalloc((void**)&ctx->stats, (size_t)score_f32_max_groups(cfg->max_units, cfg->max_cache_len) * kMaxObs * 2 * sizeof(double));
   ctx->score_groups = score_max_groups();   // exchange slots per unit: enough for every item size
   const size_t n_slots = (size_t)cfg->max_units * ctx->score_groups * kMaxObs;
   ctx->n_slots = n_slots;

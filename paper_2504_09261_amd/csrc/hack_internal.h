@@ -82,7 +82,16 @@ struct GatherArgs {
   CachePtrs cache;         // written by the moving work-groups
 };
 
-constexpr int kScoreF32Chunk = 64; // keys per score work-group, the smallest of the fp32 path (sizes its workspace)
+// fp32 score: keys per work-group of a launch over n_list units of up to max_t_in keys (see kernels_score.hip for the line
+// between the two), and how many work-groups a launch over at most max_units units of at most max_len keys has (sizes the
+// workspace).
+constexpr int kF32SmallGroups = 640;
+inline int64_t score_f32_groups(int n_list, int max_t_in, int chunk) { return (int64_t)n_list * ((max_t_in + chunk - 1) / chunk); }
+inline int score_f32_chunk(int n_list, int max_t_in) { return score_f32_groups(n_list, max_t_in, 64) <= kF32SmallGroups ? 64 : 256; }
+inline int64_t score_f32_max_groups(int max_units, int max_len) {
+  const int64_t small = score_f32_groups(max_units, max_len, 64), large = score_f32_groups(max_units, max_len, 256);
+  return small <= kF32SmallGroups ? small : large > kF32SmallGroups ? large : kF32SmallGroups;
+}
 constexpr int kMaxObs = 32;        // observation queries (one MFMA column block)
 
 // ---- kernel launchers (each validates nothing: the API layer has done so) ----
@@ -149,7 +158,7 @@ hipError_t launch_score_static(hipStream_t s, int device, int head_dim, const St
                                int N_k, float scale, const void* k_cache, const void* k_new, float* importance,
                                int64_t imp_stride, int* fault);
 // fp32: two passes over (chunk of keys, listed unit); list[n_list] indexes
-// descs; stats is a workspace of n_list * ceil(max_t_in / kScoreF32Chunk) * 64 doubles.
+// descs; stats is a workspace of 64 doubles per work-group (score_f32_groups).
 void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,
                       int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
                       const void* k_cache, const void* k_new, double* stats, float* importance,

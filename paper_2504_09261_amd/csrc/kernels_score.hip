@@ -35,7 +35,6 @@ namespace {
 using namespace dev;
 
 constexpr int kThreads = 256;
-constexpr int kF32SmallGroups = 640;   // float32: launches of up to this many work-groups of 64 keys take them
 constexpr double kLog2e = 1.4426950408889634074;
 
 // 2^t for a double t with ~1 ulp float32 accuracy: the range reduction is done
@@ -992,7 +991,7 @@ void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const 
                       const void* k_cache, const void* k_new, double* stats, float* importance,
                       int64_t imp_stride) {
   if (n_list <= 0 || max_t_in <= 0) return;
-  const bool small = (int64_t)n_list * ((max_t_in + kScoreF32Chunk - 1) / kScoreF32Chunk) <= kF32SmallGroups;
+  const bool small = score_f32_chunk(n_list, max_t_in) == 64;
   typedef float T;
 #define HACK_ARGS s, descs, list, n_list, max_t_in, (const T*)q, q_rows, n_obs, N_k, scale, (const T*)k_cache, (const T*)k_new, \
                   stats, importance, imp_stride

@@ -231,6 +231,27 @@ int no_exceptions() {
   return 0;
 }
 
+// The float32 score workspace covers every launch the context accepts (chunk of 64 keys for small ones, 256 beyond) and
+// is no larger than those need.
+int f32_workspace() {
+  for (int units : {4, 16, 60, 64, 132}) {
+    for (int max_len : {1, 64, 65, 680, 2048, 10521, 32768}) {
+      hack_config cfg{0, kH, kD, HACK_F32, units, max_len, 16, 32};
+      hack_ctx* ctx;
+      CHECK(hack_create(&ctx, &cfg) == HACK_OK);
+      const int64_t have = (int64_t)(stub::device_memory.at(ctx->stats) / (kMaxObs * 2 * sizeof(double)));   // (unit, chunk) pairs
+      int64_t most = 0;
+      for (int n = 1; n <= units; ++n)
+        for (int t = 1; t <= max_len; t += t < max_len && t + 61 > max_len ? max_len - t : 61)
+          most = std::max(most, (int64_t)n * ((t + score_f32_chunk(n, t) - 1) / score_f32_chunk(n, t)));
+      CHECK(most <= have);
+      CHECK(have <= std::max<int64_t>(640, (int64_t)units * ((max_len + 255) / 256)));
+      hack_destroy(ctx);
+    }
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -239,6 +260,7 @@ int main(int argc, char** argv) {
   if (which == "capture") rc = capture();
   if (which == "out_over_new_rows") rc = out_over_new_rows();
   if (which == "no_exceptions") rc = no_exceptions();
+  if (which == "f32_workspace") rc = f32_workspace();
   if (rc == 0) printf("ok\n");
   return rc;
 }

@@ -34,3 +34,7 @@ def test_steps_whose_outputs_lie_over_the_new_rows_move_them_first(check):
 
 def test_no_exception_crosses_the_abi_when_host_memory_runs_out(check):
     check("no_exceptions")
+
+
+def test_float32_score_workspace_covers_every_launch_and_no_more(check):
+    check("f32_workspace")
