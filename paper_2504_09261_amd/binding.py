@@ -41,7 +41,13 @@ class hack_config(C.Structure):
 
 class hack_cache(C.Structure):
     _fields_ = [("k", C.c_void_p), ("v", C.c_void_p), ("pos", C.c_void_p), ("rows", C.c_int64),
-                ("off", C.c_void_p), ("len", C.c_void_p)]   # int64 / int32 host arrays
+                ("off", C.POINTER(C.c_int64)), ("len", C.POINTER(C.c_int32))]
+
+
+class _raw_cache(C.Structure):
+    """The same memory with the host arrays as plain addresses (making a pointer object takes longer than a call)."""
+    _fields_ = [("k", C.c_void_p), ("v", C.c_void_p), ("pos", C.c_void_p), ("rows", C.c_int64),
+                ("off", C.c_void_p), ("len", C.c_void_p)]
 
 
 _lib = None
@@ -60,7 +66,7 @@ def load_library() -> C.CDLL:
             "(there is no fallback path)")
     lib = C.CDLL(LIB_PATH)
     vp, i32, i64, f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
-    pi32 = pi64 = pu8 = vp   # host arrays: an address, byref() or a ctypes array
+    pi32, pi64, pu8 = C.POINTER(C.c_int32), C.POINTER(C.c_int64), C.POINTER(C.c_uint8)
     pcache = C.POINTER(hack_cache)
     lib.hack_create.argtypes = [C.POINTER(vp), C.POINTER(hack_config)]
     lib.hack_destroy.argtypes = [vp]
@@ -110,15 +116,15 @@ def _u8(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.uint8)
 
 
-def _h(a: Optional[np.ndarray]):
-    """A host array as a pointer argument.  (ndarray.ctypes.data_as costs 5 us an array, more than a kernel launch;
-    this 0.4.)  The object keeps the array alive; for read-only or empty arrays the caller does."""
+def _p(a: Optional[np.ndarray], ctype):
+    """A host array as a typed pointer argument.  (ndarray.ctypes.data_as, for read-only or empty arrays, costs 3 us an
+    array, as much as a kernel launch; the other way 0.4.)  The object keeps the array alive."""
     if a is None:
         return None
     try:
-        return C.byref(C.c_char.from_buffer(a))
+        return C.byref(ctype.from_buffer(a))
     except (TypeError, ValueError):
-        return a.__array_interface__["data"][0]
+        return a.ctypes.data_as(C.POINTER(ctype))
 
 
 def _addr(a: np.ndarray) -> int:
@@ -159,8 +165,8 @@ class Cache:
         self.rows = int(k.shape[0])
 
     def struct(self) -> hack_cache:
-        return hack_cache(_dev(self.k), _dev(self.v), _dev(self.pos), self.rows,
-                          _addr(self.off), _addr(self.len))
+        return hack_cache.from_buffer(_raw_cache(_dev(self.k), _dev(self.v), _dev(self.pos), self.rows,
+                                                 _addr(self.off), _addr(self.len)))
 
 
 class ManagedCache:
@@ -172,14 +178,14 @@ class ManagedCache:
         self.cap = _i32(cap)
         lib = hack.lib
         rows = C.c_int64()
-        hack._check(lib.hack_kvcache_rows_required(len(self.cap), _h(self.cap), C.byref(rows)))
+        hack._check(lib.hack_kvcache_rows_required(len(self.cap), _p(self.cap, C.c_int32), C.byref(rows)))
         self.rows = rows.value
         dev = torch.device("cuda", hack.device)
         self.k = torch.empty((self.rows, hack.head_dim), dtype=hack.torch_dtype, device=dev)
         self.v = torch.empty((self.rows, hack.head_dim), dtype=hack.torch_dtype, device=dev)
         self.pos = torch.empty((self.rows,), dtype=torch.int32, device=dev) if with_pos else None
         h = C.c_void_p()
-        hack._check(lib.hack_kvcache_create(hack.ctx, len(self.cap), _h(self.cap), _dev(self.k),
+        hack._check(lib.hack_kvcache_create(hack.ctx, len(self.cap), _p(self.cap, C.c_int32), _dev(self.k),
                                             _dev(self.v), _dev(self.pos), self.rows, C.byref(h)))
         self.handle = h
 
@@ -188,8 +194,8 @@ class ManagedCache:
 
     def view(self):
         """(off int64[U], len int32[U]) copies of the current state."""
-        s = hack_cache()
-        self.hack._check(self.hack.lib.hack_kvcache_view(self.handle, C.byref(s)))
+        s = _raw_cache()
+        self.hack._check(self.hack.lib.hack_kvcache_view(self.handle, hack_cache.from_buffer(s)))
         n = len(self.cap)
         return (np.frombuffer((C.c_int64 * n).from_address(s.off), np.int64).copy(),
                 np.frombuffer((C.c_int32 * n).from_address(s.len), np.int32).copy())
@@ -262,8 +268,8 @@ class Hack:
         qi = None if q_idx is None else _i32(q_idx)
         act = None if active is None else _u8(active)
         cs = cache.struct()
-        self._check(self.lib.hack_score(self.ctx, B, Nk, _dev(q), _h(qi), n_obs, scale, C.byref(cs),
-                                        _dev(k_new), _h(act), _dev(importance),
+        self._check(self.lib.hack_score(self.ctx, B, Nk, _dev(q), _p(qi, C.c_int32), n_obs, scale, C.byref(cs),
+                                        _dev(k_new), _p(act, C.c_uint8), _dev(importance),
                                         importance.stride(0), _stream()))
 
     def score_static(self, q, cache: Cache, scale: float, importance, k_new=None, q_idx=None,
@@ -274,17 +280,17 @@ class Hack:
         qi = None if q_idx is None else _i32(q_idx)
         act = None if active is None else _u8(active)
         cs = cache.struct()
-        self._check(self.lib.hack_score_static(self.ctx, B, Nk, _dev(q), _h(qi), n_obs, scale, C.byref(cs),
-                                               _dev(k_new), _h(act), _dev(importance),
+        self._check(self.lib.hack_score_static(self.ctx, B, Nk, _dev(q), _p(qi, C.c_int32), n_obs, scale, C.byref(cs),
+                                               _dev(k_new), _p(act, C.c_uint8), _dev(importance),
                                                importance.stride(0), _stream()))
 
     # ---- a2 ----
     def select(self, B: int, importance, t_in, head_type, budget, n_init: int, n_recent: int, kept_idx) -> np.ndarray:
         t_in, budget, ht = _i32(t_in), _i32(budget), _u8(head_type)
         len_out = np.zeros(len(t_in), np.int32)
-        self._check(self.lib.hack_select(self.ctx, B, _dev(importance), importance.stride(0), _h(t_in),
-                                         _h(ht), _h(budget), n_init, n_recent,
-                                         _dev(kept_idx), kept_idx.stride(0), _h(len_out), _stream()))
+        self._check(self.lib.hack_select(self.ctx, B, _dev(importance), importance.stride(0), _p(t_in, C.c_int32),
+                                         _p(ht, C.c_uint8), _p(budget, C.c_int32), n_init, n_recent,
+                                         _dev(kept_idx), kept_idx.stride(0), _p(len_out, C.c_int32), _stream()))
         return len_out
 
     # ---- a3 ----
@@ -299,7 +305,7 @@ class Hack:
         ci, co = cache_in.struct(), cache_out.struct()
         act = None if active is None else _u8(active)
         self._check(self.lib.hack_merge(self.ctx, B, Nk, C.byref(ci), _dev(k_new), _dev(v_new), _dev(kept_idx),
-                                        kept_idx.stride(0), _h(act), C.byref(co), _stream()))
+                                        kept_idx.stride(0), _p(act, C.c_uint8), C.byref(co), _stream()))
 
     # ---- a4 ----
     def attn(self, q, cache: Cache, scale: float, out):
@@ -332,5 +338,5 @@ class Hack:
         ht, bud = _u8(head_type), _i32(budget)
         fn = self.lib.hack_step_final if final else self.lib.hack_step
         self._check(fn(self.ctx, cache.handle, B, Nk, _dev(q), _dev(k_new), _dev(v_new),
-                                       _h(ht), _h(bud), n_init, scale, _dev(out),
+                                       _p(ht, C.c_uint8), _p(bud, C.c_int32), n_init, scale, _dev(out),
                                        _dev(kept_idx), 0 if kept_idx is None else kept_idx.stride(0), _stream()))
