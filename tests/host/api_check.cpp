@@ -231,6 +231,39 @@ int no_exceptions() {
   return 0;
 }
 
+// A step that is remembered is found again only with the same arguments: sink rows, score mode, plain or final.
+int step_keys() {
+  Setup s(HACK_BF16, 400, 1000, 300);
+  auto last_step = [&](int n_init, bool final_merge, int mode) -> const StepNode* {
+    if (hack_set_score_mode(s.ctx, mode) != HACK_OK) return nullptr;
+    hack_kvcache_reset(s.cache);
+    stub::launches.clear();
+    if (s.step(300, 1 << 30) != HACK_OK || s.step(200, 250, final_merge, n_init) != HACK_OK) return nullptr;
+    return s.cache->at;
+  };
+  auto launched = [](const char* name) { return std::find(stub::launches.begin(), stub::launches.end(), name) != stub::launches.end(); };
+  std::vector<const StepNode*> nodes;
+  for (int pass = 0; pass < 2; ++pass) {
+    size_t i = 0;
+    for (int mode : {HACK_SCORE_FUSED, HACK_SCORE_TWO_PASS})
+      for (int n_init : {5, 9})
+        for (bool final_merge : {false, true}) {
+          const StepNode* n = last_step(n_init, final_merge, mode);
+          CHECK(n != nullptr);
+          CHECK(launched("merge") == final_merge && launched("score_two_pass") == (mode == HACK_SCORE_TWO_PASS) &&
+                launched("score_fused") == (mode == HACK_SCORE_FUSED));
+          if (pass == 0) {
+            CHECK(std::find(nodes.begin(), nodes.end(), n) == nodes.end());
+            nodes.push_back(n);
+          } else {
+            CHECK(nodes[i++] == n);
+          }
+        }
+  }
+  CHECK(stub::bad_launches == 0);
+  return 0;
+}
+
 // The float32 score workspace covers every launch the context accepts (chunk of 64 keys for small ones, 256 beyond) and
 // is no larger than those need.
 int f32_workspace() {
@@ -260,6 +293,7 @@ int main(int argc, char** argv) {
   if (which == "capture") rc = capture();
   if (which == "out_over_new_rows") rc = out_over_new_rows();
   if (which == "no_exceptions") rc = no_exceptions();
+  if (which == "step_keys") rc = step_keys();
   if (which == "f32_workspace") rc = f32_workspace();
   if (rc == 0) printf("ok\n");
   return rc;

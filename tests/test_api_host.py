@@ -38,3 +38,7 @@ def test_no_exception_crosses_the_abi_when_host_memory_runs_out(check):
 
 def test_float32_score_workspace_covers_every_launch_and_no_more(check):
     check("f32_workspace")
+
+
+def test_remembered_steps_are_found_by_all_their_arguments(check):
+    check("step_keys")

@@ -390,6 +390,84 @@ def test_step_plans_are_kept_per_state_and_dropped_when_there_are_too_many():
     hk.close()
 
 
+def test_steps_from_one_state_that_differ_in_sinks_merge_or_score_mode():
+    """The same budgets from the same state of one managed cache, with other sink rows, as a final step, in the other score
+    mode and back: kept lists, rows and outputs of a cache that has seen nothing else.  Units of 1000 keys at head_dim 128
+    are scored by the launches that the score mode decides on."""
+    u = _u()
+    H, d, n0, n1 = 4, 128, 700, 300
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=n0 + n1, max_queries=n0)
+    types, caps = np.array([0, 1, 0, 1], np.uint8), np.array([700, 800, 900, 700], np.int32)
+    budget = np.array([250, 480, 333, 420], np.int32)
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(5)
+    ten = [[torch.randn((1, H, n, d), generator=gen, device=u.DEV).to(torch.bfloat16) for _ in range(3)] for n in (n0, n1)]
+    mc = hk.managed_cache(caps)
+
+    def walk(cache, n_init, final, mode):
+        hk.set_score_mode(mode)
+        cache.reset()
+        outs = [torch.zeros_like(t[0]) for t in ten]
+        kept = torch.full((H, 512), -1, dtype=torch.int32, device=u.DEV)
+        hk.step(cache, *ten[0], types, [1 << 30] * H, 5, 0.0884, outs[0])
+        hk.step(cache, *ten[1], types, budget, n_init, 0.0884, outs[1], kept_idx=kept, final=final)
+        torch.cuda.synchronize()
+        hk.check()
+        off, ln = cache.view()
+        assert list(ln) == list(budget)
+        return [kept, outs[1]] + [x[o:o + n].clone() for o, n in zip(off, ln) for x in (cache.k, cache.v, cache.pos)]
+
+    seen = {}
+    for args in ((5, False, 0), (9, False, 0), (5, True, 0), (5, False, 1), (9, True, 1), (5, False, 0), (9, False, 1), (5, True, 0)):
+        got = walk(mc, *args)
+        fresh = hk.managed_cache(caps)
+        assert all(torch.equal(a, b) for a, b in zip(got, walk(fresh, *args))), args
+        fresh.close()
+        seen[args] = got
+    assert not torch.equal(seen[5, False, 0][0], seen[9, False, 0][0])          # sink rows decide a structural head's list
+    assert not torch.equal(seen[5, False, 0][2], seen[5, True, 0][2])           # merged rows of a contextual head
+    assert all(torch.equal(a, b) for a, b in zip(seen[5, False, 0], seen[5, False, 1]))
+    mc.close()
+    hk.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_a_unit_longer_than_the_list_of_kept_rows_beside_a_compressing_one(dtype):
+    """Kept rows are read in place only while a unit that keeps everything has at most 32768 rows: at 32768 exactly, and with
+    50 rows more, where the rows are moved by a launch of their own, the step's outputs are those of the attention over its
+    cache, and its rows copies."""
+    u = _u()
+    H, d, n, caps = 2, 64, 4096, [32768 + 64, 600]
+    hk = u.make_hack(heads=H, head_dim=d, dtype=dtype, max_units=H, max_cache_len=32768, max_queries=n)
+    mc = hk.managed_cache(caps)
+    types, budget = np.array([1, 0], np.uint8), np.array([1 << 30, 600], np.int32)
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(23)
+    rows = 0
+    for step, m in enumerate([n] * 7 + [n - 100, 100, 50]):
+        q, kn, vn = (torch.randn((1, H, m, d), generator=gen, device=u.DEV).to(hk.torch_dtype) for _ in range(3))
+        off0, len0 = mc.view()
+        old = [x[off0[1]:off0[1] + len0[1]].clone() for x in (mc.k, mc.v)]
+        kept = torch.full((H, 600), -1, dtype=torch.int32, device=u.DEV)
+        out, want = torch.zeros_like(q), torch.zeros_like(q)
+        hk.step(mc, q, kn, vn, types, budget, 5, 0.125, out, kept_idx=kept)
+        rows += m
+        off, ln = mc.view()
+        assert list(ln) == [rows, 600]
+        if step < 7:
+            continue
+        hk.attn(q, mc.as_cache(), 0.125, want)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), rows
+        for x, new, was in zip((mc.k, mc.v), (kn, vn), old):
+            assert torch.equal(x[off[0] + rows - m:off[0] + rows], new[0, 0]), rows
+            assert torch.equal(x[off[1]:off[1] + 600], torch.cat([was, new[0, 1]])[kept[1].long()]), rows
+        assert torch.equal(mc.pos[off[0]:off[0] + rows], torch.arange(rows, dtype=torch.int32, device=u.DEV))
+    hk.check()
+    mc.close()
+    hk.close()
+
+
 @pytest.mark.parametrize("dtype,B", [("bf16", 2), ("f32", 2), ("f32", 32)])   # float32: 16- and 32-query items
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("with_pos", [True, False])
@@ -667,7 +745,7 @@ def test_eager_steps_after_a_discarded_capture_of_unseen_steps():
 
 def test_largest_supported_cache_through_individual_calls():
     """One contextual and one structural unit at the library's limit, T_in = 32768 rows (the
-    selection keeps a unit's keys in LDS): score, select, compact, attend, each against the oracle;
+    selection keeps a unit's keys in registers): score, select, compact, attend, each against the oracle;
     one row more is refused."""
     u = _u()
     from paper_2504_09261_amd.binding import HackError
