@@ -142,17 +142,18 @@ def _dev(t) -> Optional[int]:
     return t.data_ptr()
 
 
-_raw_stream = None
+_raw_stream = _device = None
 
 
 def _stream() -> int:
     """hipStream_t of the current device's current stream."""
-    global _raw_stream
-    import torch
+    global _raw_stream, _device
     if _raw_stream is None:
+        import torch   # once: looking the module up in every call takes as long as the two typed pointers of a step
+        _device = torch.cuda.current_device
         # the raw handle without building a torch.cuda.Stream object for every call
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", lambda _: torch.cuda.current_stream().cuda_stream)
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_device())
 
 
 class Cache:
