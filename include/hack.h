@@ -54,7 +54,7 @@ typedef enum {
   HACK_EINVAL = -1,       /* bad argument (shape, range, alignment, NULL) */
   HACK_ECAPACITY = -2,    /* exceeds what the context / cache was sized for */
   HACK_EUNSUPPORTED = -3, /* valid request this build does not implement */
-  HACK_EHIP = -4          /* a HIP runtime call failed */
+  HACK_EHIP = -4          /* a HIP runtime call failed, or host memory ran out */
 } hack_status;
 
 typedef enum { HACK_BF16 = 0, HACK_F32 = 1 } hack_dtype;
@@ -261,11 +261,13 @@ hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q,
 /* Which kernel hack_attn / hack_step use for the attention of a launch with B
  * batch elements and N_k queries per unit (same attention equation, same
  * tolerances; reported so that measurements can be attributed to a kernel):
- *   0  work items of 128 queries that share every K/V block (large steps; fp32
- *      contexts always); in a bf16 launch with no more work items than the
+ *   0  bf16: work items of 128 queries that share every K/V block (large
+ *      steps); in a launch with no more work items than the
  *      device holds work-groups, a few work items may be served by two
  *      work-groups each (half of the keys each, the partial results added up
- *      in float32 in a fixed order) where that shortens the launch,
+ *      in float32 in a fixed order) where that shortens the launch.
+ *      fp32 contexts (always 0): work items of 16 or 32 queries whose waves
+ *      split the keys; appends and kept rows as variant 1 does,
  *   1  work items of 32 queries whose four waves split the keys and merge their
  *      partial softmax results at the end (bf16, early scale steps: few
  *      queries); in hack_step this kernel also performs the append when no unit

@@ -208,9 +208,9 @@ struct Table {
 
 // Returns the device address of a table with these contents, uploading it on
 // the given stream the first time it is seen (again, if that stream was being
-// captured: see table_cache.h).  Tables are immutable and keep
-// their address until the context is destroyed, so queued kernels and captured
-// graphs may go on using them.
+// captured: see table_cache.h).  Tables are immutable and keep their address
+// until the context is destroyed, so queued kernels and captured graphs may go
+// on using them.
 hack_status table_device(hack_ctx* ctx, const Table& t, hipStream_t stream, const uint8_t** dev, size_t* id = nullptr) {
   switch (ctx->tables->get(t.bytes.data(), t.bytes.size(), stream, dev, id)) {
     case TableStatus::kOk: return HACK_OK;
@@ -567,7 +567,7 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   if (cfg->dtype != HACK_BF16 && cfg->dtype != HACK_F32) return HACK_EINVAL;
   if (cfg->heads < 1 || cfg->max_units < cfg->heads || cfg->max_cache_len < 1 || cfg->max_queries < 1) return HACK_EINVAL;
   if (cfg->n_obs < 1 || cfg->n_obs > kMaxObs) return HACK_EINVAL;
-  if (cfg->max_cache_len > 32768) return HACK_EUNSUPPORTED;  // selection keeps a unit's keys in LDS
+  if (cfg->max_cache_len > 32768) return HACK_EUNSUPPORTED;  // selection: 1024 threads of 32 keys in registers
   hack_ctx* ctx = new (std::nothrow) hack_ctx();
   if (!ctx) return HACK_EHIP;
   ctx->cfg = *cfg;

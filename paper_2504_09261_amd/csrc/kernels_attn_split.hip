@@ -21,7 +21,7 @@
 // so a step that does not compress needs a single launch.  A step that compresses
 // (GATHER) reads keys and values in place through the units' lists of kept rows,
 // and further work-groups of the launch move those rows: one launch less, and the
-// move beside the attention (one 256^2 image, seven compressing steps of 60 units,
+// move beside the attention (one 256^2 image, four compressing steps of 60 units,
 // 120 -> 111 us; odd sides 128 -> 121 us).  A wave copies the list entries of its next-but-one
 // block into an LDS ring of its own; all but one block of a unit lie wholly in the
 // cached or wholly in the new rows, so their rows are a wave-uniform base plus 32 bits.

@@ -24,7 +24,8 @@
 // holds the MFMAs of block b + 1 and the softmax arithmetic of block b, interleaved by
 // hand, one barrier a stage.  16 heads x batch 2, 4096 queries x 10521 keys, D = 128:
 // pass 1 426 -> 365 us, pass 2 566 -> 475 us against blocks computed one after the other
-// (kernel trace), the call 878 -> 766 us.  Matrix cores 60 % busy in pass 1; the chip holds 1.6-1.7 GHz
+// (under the profiler, which lengthens both), the call without it 873 -> 755 us.  Matrix cores 60 % busy in pass 1
+// and 42 % in pass 2; the chip holds 1.67-1.74 GHz
 // in this mix (power), so that fewer cycles buy less time than their share.  The
 // steady loop holds no branch: with one, the compiler sinks the fp64 sums past it and spills.
 #include <type_traits>
