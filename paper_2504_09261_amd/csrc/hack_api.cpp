@@ -107,7 +107,7 @@ struct hack_ctx {
 // the uploaded table, launch shapes); built by upload_group.
 struct StepGroup {
   int n_desc = 0, n_comp = 0, n_merge = 0, n_items = 0, n_stream = 0;   // units, compressing / merging ones, attention work items, streamed work-groups
-  int max_t = 0, max_rows = 0, merge_t = 0, merge_out = 0;
+  int max_t = 0, max_rows = 0, max_keys = 0, merge_t = 0, merge_out = 0;
   bool streamed = false;                  // attention in the streamed form (then n_items is 0)
   bool gathered = false;                  // attention reads the kept rows in place and updates the cache beside it (n_moves work-groups)
   int n_moves = 0;
@@ -946,11 +946,13 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
   if (!scale_ok(scale)) return fail(ctx, HACK_EINVAL, "scale must be finite and > 0");
   if ((st = check_cache(ctx, kv, U, "kv", true)) != HACK_OK) return st;
   std::vector<UnitDesc> descs(U);
+  int max_keys = 0;
   for (int u = 0; u < U; ++u) {
     if (kv->len[u] < 1) return fail(ctx, HACK_EINVAL, "unit %d has an empty cache", u);
     UnitDesc d{};
     d.in_off = kv->off[u]; d.out_off = kv->off[u]; d.len_in = kv->len[u]; d.n_out = kv->len[u]; d.unit = u;
     descs[u] = d;
+    max_keys = std::max(max_keys, d.n_out);
   }
   const bool split = use_split_attention(ctx, U, N_k);
   const int tile = attn_tile_rows(ctx, U, N_k);
@@ -972,7 +974,7 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
                        ctx->part_ml, ctx->part_count);
   else if (split)
     launch_attn_split(s, ctx->cfg.head_dim, (const UnitDesc*)(dev + o_desc), (const AttnItem*)(dev + o_items),
-                      (int)items.size(), q, kv->k, kv->v, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale,
+                      (int)items.size(), max_keys, q, kv->k, kv->v, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale,
                       out);
   else if (ctx->cfg.dtype == HACK_F32)
     launch_attn_f32(s, ctx->cfg.head_dim, (const AttnItem*)(dev + o_items), (int)items.size(), tile, q, kv->k, kv->v, nullptr,
@@ -1108,6 +1110,7 @@ bool overlap(const void* a, const void* b, size_t bytes) {
 void add_unit(GroupUnits* u, StepGroup* g, const UnitDesc& d, bool merges, int N_k) {
   const int idx = (int)u->descs.size();
   u->descs.push_back(d);
+  g->max_keys = std::max(g->max_keys, d.n_out);
   if (d.mode == MOVE_GATHER) {
     u->comp.push_back(idx);
     g->max_t = std::max(g->max_t, d.len_in + d.n_new);
@@ -1193,7 +1196,7 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
     if (ctx->cfg.dtype == HACK_F32)
       launch_attn_f32_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, n.tile, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
     else
-      launch_attn_split_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
+      launch_attn_split_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, g.max_keys, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
     return;
   }
   if (g.streamed)
@@ -1201,7 +1204,7 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
                        reinterpret_cast<const int32_t*>(g.dev + g.o_segb), g.n_stream, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out,
                        ctx->part_o, ctx->part_ml, ctx->part_count);
   else if (n.split)
-    launch_attn_split(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v,
+    launch_attn_split(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, g.max_keys, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v,
                       a.cp.pos, a.pos_new, fuse, n.N_k, a.scale, a.out);
   else if (ctx->cfg.dtype == HACK_F32)
     launch_attn_f32(s, ctx->cfg.head_dim, items, g.n_items, n.tile, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v, a.cp.pos,

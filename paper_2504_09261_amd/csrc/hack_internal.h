@@ -208,13 +208,14 @@ void launch_attn_stream(hipStream_t s, int head_dim, const UnitDesc* descs, cons
 // of k_new / v_new] (n_out = len_in + N_k) and also writes those rows (and their
 // positions pos_new + row, if pos_app != nullptr) behind the cached ones in
 // k_app / v_app / pos_app, i.e. it performs the append of the step as well.
+// max_keys: the most rows any item attends over.
 // launch_attn_split_gather: over the rows the units keep (n_out of each), read in place through g; g.n_moves further
 // work-groups update the cache.
 int attn_split_q_tile_rows();
-void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
+void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int max_keys,
                               const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
                               float scale, void* out);
-void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
+void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int max_keys,
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
                        void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale,
                        void* out);

@@ -39,7 +39,6 @@ namespace {
 using namespace dev;
 
 constexpr int kKB = 32;        // keys per block
-constexpr int kWaves = 4;      // waves per work-group = key splits
 constexpr int kQTile = 32;     // queries per work item
 
 // fuse != 0: keys are [rows in_off .. in_off+len_in of the cache | the unit's n_new
@@ -47,8 +46,8 @@ constexpr int kQTile = 32;     // queries per work item
 // ones (k_app / v_app / pos_app are the cache arrays, which k_cache / v_cache then
 // alias: reads stay below row len_in, writes at or above it).
 // fuse == 0: keys are rows [out_off, out_off + n_out) of the cache.
-template <int D, bool GATHER>
-__global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
+template <int D, bool GATHER, int kWaves>   // kWaves waves per work-group = key splits
+__global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     const UnitDesc* __restrict__ descs, const AttnItem* __restrict__ items, const __bf16* __restrict__ q,
     const __bf16* k_cache, const __bf16* v_cache, const __bf16* k_new, const __bf16* v_new, __bf16* k_app,
     __bf16* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale, __bf16* __restrict__ out, GatherArgs ga) {
@@ -60,7 +59,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
   constexpr int BLK = kKB * D;      // elements per block
 
   constexpr int XI = GATHER ? 1 : 0;   // list copies per block
-  // list entries of this wave's blocks w, w + 4, ...: block b in slot (b / 4) % 4 (a copy also fills the 32 words behind it)
+  // list entries of this wave's blocks w, w + kWaves, ...: block b in slot (b / kWaves) % 4 (a copy also fills the 32 words behind it)
   __shared__ __attribute__((aligned(256))) int idx_ring[GATHER ? kWaves : 1][GATHER ? 4 * 2 * kKB : 1];
   if constexpr (GATHER) {
     const int mover = (int)blockIdx.x - ((int)gridDim.x - ga.n_moves);
@@ -93,7 +92,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
   // cache or wholly in the new rows is a contiguous piece of memory: uniform base
   // plus loop-invariant lane offsets.  The ragged last block and a block that
   // straddles the two sources take per-lane addresses (rows past the end repeat
-  // the last key; their scores are masked).
+  // the last key; their scores are masked): a uniform row of either source plus 32
+  // bits.  Formed from 64-bit row numbers they stood 1 us in front of the first
+  // scales' only block (head_dim 128, four steps of 32 units 25.2 -> 23.8 us).
   const unsigned vs_lds = lds_addr_of(&Vs[0][0][0]);
   unsigned k_src[IPB], v_src[IPB];
 #pragma unroll
@@ -103,8 +104,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
     v_src[i] = (unsigned)(r * D + ((c ^ swz_v<D>(r)) & (CPR - 1)) * 8) * 2u;
   }
   const unsigned k_lds = vs_lds + (unsigned)((w * 2 + 0) * BLK * 2), v_lds = vs_lds + (unsigned)((w * 2 + 1) * BLK * 2);
-  auto issue = [&](int b, const __bf16* cache, const __bf16* fresh, const unsigned (&src)[IPB], unsigned lds, bool is_k) {
+  auto issue = [&](int b, const __bf16* cache, const __bf16* fresh, const unsigned (&src)[IPB], unsigned lds) {
     const int j0 = b * kKB;
+    const __bf16* const in_cache = cache + (base + j0) * D;              // row j0 of the unit, were it cached
+    const __bf16* const in_fresh = fresh + (new_row0 + (j0 - len_c)) * D;   // ... or a new one
+    const int last = total - 1 - j0;
     const __bf16* blk = nullptr;
     if (j0 + kKB <= len_c) blk = cache + (base + j0) * D;
     else if (j0 >= len_c && j0 + kKB <= total) blk = fresh + (new_row0 + (j0 - len_c)) * D;
@@ -114,11 +118,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
     } else {
 #pragma unroll
       for (int i = 0; i < IPB; ++i) {
-        const int r = i * RPI + lane / CPR, c = lane % CPR;
-        const int j = min(j0 + r, total - 1);
-        const int sw = is_k ? swz_k<D>(r) : swz_v<D>(r);
-        const __bf16* p = (j < len_c ? cache + (base + j) * D : fresh + (new_row0 + (j - len_c)) * D) + ((c ^ sw) & (CPR - 1)) * 8;
-        load_to_lds(p, lds + (unsigned)(i * 1024));
+        const int r = min(i * RPI + lane / CPR, last);
+        load_to_lds(reinterpret_cast<const char*>(j0 + r < len_c ? in_cache : in_fresh) + ((unsigned)(r * (D * 2)) | (src[i] & (D * 2 - 1))),
+                    lds + (unsigned)(i * 1024));
       }
     }
   };
@@ -138,13 +140,13 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
   }
   int* const ring = &idx_ring[GATHER ? w : 0][0];
   const unsigned ring_lds = lds_addr_of(ring);
-  auto issue_x = [&](int b) {   // b = w + 4 i; past the end: entries of the last block
+  auto issue_x = [&](int b) {   // b = w + kWaves i; past the end: entries of the last block
     const int b0 = min(b, n_blocks - 1);
-    load_to_lds_dword(list + b0 * kKB, (unsigned)(min(lane, total - 1 - b0 * kKB) * 4), ring_lds + (unsigned)(((b >> 2) & 3) * 2 * kKB * 4));
+    load_to_lds_dword(list + b0 * kKB, (unsigned)(min(lane, total - 1 - b0 * kKB) * 4), ring_lds + (unsigned)(((b / kWaves) & 3) * 2 * kKB * 4));
   };
   auto issue_rows = [&](int b, const char* cached, const char* fresh, const unsigned (&src)[IPB], unsigned lds) {
     const int j0 = b * kKB;
-    const int* x = ring + ((b >> 2) & 3) * 2 * kKB + lane / CPR;
+    const int* x = ring + ((b / kWaves) & 3) * 2 * kKB + lane / CPR;
     if (j0 + kKB <= seam || j0 >= seam) {
       const char* base = j0 >= seam ? fresh : cached;
 #pragma unroll
@@ -162,12 +164,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
       issue_x(b + 2 * kWaves);
       issue_rows(b, kc, kn, k_src, k_lds);
     } else {
-      issue(b, k_cache, k_new, k_src, k_lds, true);
+      issue(b, k_cache, k_new, k_src, k_lds);
     }
   };
   auto issue_v = [&](int b) {
     if constexpr (GATHER) issue_rows(b, vc, vn, v_src, v_lds);
-    else issue(b, v_cache, v_new, v_src, v_lds, false);
+    else issue(b, v_cache, v_new, v_src, v_lds);
   };
 
   if (w < n_blocks) {
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
   // Cache update of this tile's rows: loaded behind the first K and V blocks, stored when the loop is done (stored at
   // once they would put a memory round trip in front of everything else: one 256^2 image 99.6 against 96.5 us).
   constexpr int LPR = D / 8;                               // 16-byte pieces per row
-  constexpr int APP = kQTile * LPR / (64 * kWaves);        // pieces per thread
+  constexpr int APP = (kQTile * LPR + 64 * kWaves - 1) / (64 * kWaves);   // pieces per thread
   uintx4 app_k[APP], app_v[APP];
   const int n_app = fuse ? min(kQTile, N_k - q0) * LPR : 0;
   if (!GATHER && fuse) {
@@ -319,47 +321,69 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
     if (pos_app != nullptr && tid < n_app / LPR) pos_app[d.in_off + d.len_in + q0 + tid] = pos_new + q0 + tid;
   }
 
-  // ---- merge the four partial results ----
+  // ---- merge the partial results ----
   // This wave's copies have all landed and its LDS reads are done: its two slots
-  // become its O^T partial, register-major so that lanes are contiguous.
-  l_run = pair_sum(l_run);
-  float* mine = reinterpret_cast<float*>(&Vs[w][0][0]);
+  // become its O^T partial, four registers of a lane together, lanes contiguous (b128 accesses, a quarter of the
+  // instructions of a register at a time).
+  // A unit of one block has one partial result (the first scales).
+  const bool alone = n_blocks == 1;
+  if (!alone || w == 0) {
+    l_run = pair_sum(l_run);
+    float4* mine = reinterpret_cast<float4*>(&Vs[w][0][0]) + lane;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mine[(mb * 16 + r) * 64 + lane] = o[mb][r];
-  if (half == 0) {
-    m_sh[w][col] = m_run;
-    l_sh[w][col] = l_run;
+      for (int r4 = 0; r4 < 4; ++r4)
+        mine[(mb * 4 + r4) * 64] = make_float4(o[mb][4 * r4], o[mb][4 * r4 + 1], o[mb][4 * r4 + 2], o[mb][4 * r4 + 3]);
+    if (half == 0) {
+      m_sh[w][col] = m_run;
+      l_sh[w][col] = l_run;
+    }
   }
   __syncthreads();
-  float M = -INFINITY;
-#pragma unroll
-  for (int x = 0; x < kWaves; ++x) M = fmaxf(M, m_sh[x][col]);   // finite: wave 0 saw block 0
-  float f[kWaves], L = 0.f;
-#pragma unroll
-  for (int x = 0; x < kWaves; ++x) {
-    f[x] = __builtin_amdgcn_exp2f((m_sh[x][col] - M) * c2);       // a wave without blocks: exp2(-inf) = 0
-    L = fmaf(f[x], l_sh[x][col], L);
-  }
-  const float inv = 1.f / L;
   // wave w finishes registers [w CH, (w+1) CH) of the 16 MB per lane; register
   // 16 mb + r of lane (col, half) is head-dim 32mb + 8(r/4) + 4 half + r%4 of query col
   constexpr int CH = 16 * MB / kWaves;
+  static_assert(CH % 4 == 0, "whole groups of four registers");
+  const float4* const part = reinterpret_cast<const float4*>(&Vs[0][0][0]) + w * (CH / 4) * 64 + lane;
+  constexpr int kPart = 2 * BLK * 2 / 16;   // float4 per partial result
+  float4 acc[CH / 4];
+  float L;
+  if (alone) {
+    L = l_sh[0][col];
+#pragma unroll
+    for (int i4 = 0; i4 < CH / 4; ++i4) acc[i4] = part[i4 * 64];
+  } else {
+    float M = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < kWaves; ++x) M = fmaxf(M, m_sh[x][col]);   // finite: wave 0 saw block 0
+    float f[kWaves];
+    L = 0.f;
+#pragma unroll
+    for (int x = 0; x < kWaves; ++x) {
+      f[x] = __builtin_amdgcn_exp2f((m_sh[x][col] - M) * c2);       // a wave without blocks: exp2(-inf) = 0
+      L = fmaf(f[x], l_sh[x][col], L);
+    }
+#pragma unroll
+    for (int i4 = 0; i4 < CH / 4; ++i4) {
+      acc[i4] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int x = 0; x < kWaves; ++x) {
+        const float4 p = part[x * kPart + i4 * 64];
+        acc[i4].x = fmaf(f[x], p.x, acc[i4].x);
+        acc[i4].y = fmaf(f[x], p.y, acc[i4].y);
+        acc[i4].z = fmaf(f[x], p.z, acc[i4].z);
+        acc[i4].w = fmaf(f[x], p.w, acc[i4].w);
+      }
+    }
+  }
+  const float inv = 1.f / L;
   const int qi = q0 + col;
   __bf16* orow = out + (new_row0 + min(qi, N_k - 1)) * D;
 #pragma unroll
   for (int i4 = 0; i4 < CH / 4; ++i4) {
     const int reg0 = w * CH + 4 * i4;
-    bf16x4 pk;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float acc = 0.f;
-#pragma unroll
-      for (int x = 0; x < kWaves; ++x)
-        acc = fmaf(f[x], reinterpret_cast<const float*>(&Vs[x][0][0])[(reg0 + i) * 64 + lane], acc);
-      pk[i] = (__bf16)(acc * inv);
-    }
+    const bf16x4 pk = {(__bf16)(acc[i4].x * inv), (__bf16)(acc[i4].y * inv), (__bf16)(acc[i4].z * inv), (__bf16)(acc[i4].w * inv)};
     const int mb = reg0 >> 4, r4 = (reg0 & 15) >> 2;
     if (qi < N_k) *reinterpret_cast<bf16x4*>(orow + 32 * mb + 8 * r4 + 4 * half) = pk;
   }
@@ -369,36 +393,49 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_split(
 
 int attn_split_q_tile_rows() { return kQTile; }
 
-void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
+// Eight waves instead of four halve the blocks that a wave walks one after the other.  At head_dim 128 they leave room for one
+// work-group on a compute unit, and below twenty blocks the larger merge costs what the shorter walk gains.  Measured, us a launch,
+// four / eight waves, 128 work items of 22, 47, 125 blocks: head_dim 64 7.9 / 7.1, 11.9 / 9.9, 25.4 / 19.4; 128 10.7 / 10.4, 16.6 / 14.6,
+// 34.8 / 28.1; 256 items of 13 and 22: 64 6.7 / 6.7, 8.2 / 7.6; 128 9.4 / 9.9, 11.6 / 11.5; 480 items of 22: 10.4 / 11.0; 16.3 / 21.9.
+// The rule counts the attention's own work-groups only: a step gives the bits of hack_attn over the rows that it kept.
+static bool split_in_eight(int n_items, int max_keys) { return max_keys > 20 * kKB && n_items <= 256; }
+
+#define HACK_SPLIT(D_, G_, ...)                                                                                  \
+  do {                                                                                                           \
+    if (eight) hipLaunchKernelGGL((attn_split<D_, G_, 8>), dim3(n), dim3(512), 0, s, descs, items, __VA_ARGS__); \
+    else hipLaunchKernelGGL((attn_split<D_, G_, 4>), dim3(n), dim3(256), 0, s, descs, items, __VA_ARGS__);       \
+  } while (0)
+
+void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int max_keys,
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
                        void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale,
                        void* out) {
-  if (n_items <= 0) return;
+  const int n = n_items;
+  if (n <= 0) return;
   typedef __bf16 T;
+  const bool eight = split_in_eight(n_items, max_keys);
   if (head_dim == 64)
-    hipLaunchKernelGGL((attn_split<64, false>), dim3(n_items), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
-                       (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
-                       pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
+    HACK_SPLIT(64, false, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
+               pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
   else
-    hipLaunchKernelGGL((attn_split<128, false>), dim3(n_items), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
-                       (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
-                       pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
+    HACK_SPLIT(128, false, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
+               pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
 }
 
-void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
+void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int max_keys,
                               const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
                               float scale, void* out) {
   const int n = n_items + g.n_moves;
   if (n <= 0) return;
   typedef __bf16 T;
+  const bool eight = split_in_eight(n_items, max_keys);
   if (head_dim == 64)
-    hipLaunchKernelGGL((attn_split<64, true>), dim3(n), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
-                       (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale,
-                       (T*)out, g);
+    HACK_SPLIT(64, true, (const T*)q, (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k,
+               scale, (T*)out, g);
   else
-    hipLaunchKernelGGL((attn_split<128, true>), dim3(n), dim3(64 * kWaves), 0, s, descs, items, (const T*)q,
-                       (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale,
-                       (T*)out, g);
+    HACK_SPLIT(128, true, (const T*)q, (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k,
+               scale, (T*)out, g);
 }
+#undef HACK_SPLIT
 
 }  // namespace hack

@@ -537,6 +537,33 @@ def test_cut_and_streamed_attention_launches_agree_with_whole_work_items():
                 assert err < 2e-2, (case, kernel, which, d, U, Nk, int(lens.max()), err)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Nk,lens", [
+    (3, 33, [1, 32, 33]), (3, 5, [640, 640, 31]), (4, 40, [641, 1, 32, 2049]), (2, 100, [672, 700]), (3, 64, [1, 897, 4001]),
+    (65, 128, [641] * 65), (64, 128, [641] * 63 + [7]),     # 260 and 256 work items, the line between four and eight waves
+])
+def test_key_split_attention_block_and_wave_edges(d, H, Nk, lens):
+    """Key-split work items of one block, of fewer and of more blocks than waves, with four and with eight waves."""
+    u = _u()
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(d + len(lens))
+    lens = np.asarray(lens, np.int32)
+    off = np.concatenate([[0], np.cumsum((lens + 7) // 8 * 8)]).astype(np.int64)
+    q = torch.randn((1, H, Nk, d), generator=gen, device=u.DEV).bfloat16()
+    K, V = (torch.randn((int(off[-1]), d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    scale = float(np.float32(d ** -0.5))
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=int(lens.max()), max_queries=Nk, attention="split")
+    out = torch.full_like(q, 7.0)
+    hk.attn(q, Cache(K, V, off[:-1], lens), scale, out)
+    torch.cuda.synchronize()
+    for h in range(H):
+        k, v = (x[off[h]:off[h] + lens[h]].double() for x in (K, V))
+        want = torch.softmax(scale * (q[0, h].double() @ k.T.contiguous()), -1) @ v
+        # P and O are rounded to bf16: 2^-8 of the largest value each
+        assert float((out[0, h].double() - want).abs().max()) < 2e-2, (h, int(lens[h]))
+    hk.close()
+
+
 def test_attention_rejects_empty_unit_and_bad_scale():
     u = _u()
     hk = u.make_hack(heads=1, head_dim=64, dtype="bf16", max_units=1, max_cache_len=64, max_queries=8)
