@@ -80,6 +80,7 @@ struct GatherArgs {
   const void* k_new;
   const void* v_new;
   CachePtrs cache;         // written by the moving work-groups
+  bool eight;              // bf16: eight waves a work-group (attn_split_in_eight)
 };
 
 // fp32 score: keys per work-group of a launch over n_list units of up to max_t_in keys (see kernels_score.hip for the line
@@ -203,19 +204,26 @@ void launch_attn_stream(hipStream_t s, int head_dim, const UnitDesc* descs, cons
                         void* out, float* part_o, float* part_ml, unsigned* part_count);
 // bf16 attention for steps with few queries: work item = (unit, tile of
 // attn_split_q_tile_rows() queries), keys split over the waves of a work-group.
-// fuse == 0: attends over rows [out_off, out_off + n_out) of k_cache / v_cache.
-// fuse != 0: attends over [rows in_off .. +len_in of the cache | the unit's N_k rows
+// No kSplitAppend: attends over rows [out_off, out_off + n_out) of k_cache / v_cache.
+// fuse & kSplitAppend: attends over [rows in_off .. +len_in of the cache | the unit's N_k rows
 // of k_new / v_new] (n_out = len_in + N_k) and also writes those rows (and their
 // positions pos_new + row, if pos_app != nullptr) behind the cached ones in
 // k_app / v_app / pos_app, i.e. it performs the append of the step as well.
-// max_keys: the most rows any item attends over.
+// fuse & kSplitEight, GatherArgs::eight: eight waves a work-group instead of four.
 // launch_attn_split_gather: over the rows the units keep (n_out of each), read in place through g; g.n_moves further
 // work-groups update the cache.
+// Eight waves instead of four halve the blocks that a wave walks one after the other.  At head_dim 128 they leave room for one
+// work-group on a compute unit, and below twenty blocks the larger merge costs what the shorter walk gains.  Measured, us a launch,
+// four / eight waves, 128 work items of 22, 47, 125 blocks: head_dim 64 7.9 / 7.1, 11.9 / 9.9, 25.4 / 19.4; 128 10.7 / 10.4, 16.6 / 14.6,
+// 34.8 / 28.1; 256 items of 13 and 22: 64 6.7 / 6.7, 8.2 / 7.6; 128 9.4 / 9.9, 11.6 / 11.5; 480 items of 22: 10.4 / 11.0; 16.3 / 21.9.
+// The rule counts the attention's own work-groups only: a step gives the bits of hack_attn over the rows that it kept.
+inline bool attn_split_in_eight(int n_items, int max_keys) { return max_keys > 20 * 32 && n_items <= 256; }
+enum : int { kSplitAppend = 1, kSplitEight = 2 };
 int attn_split_q_tile_rows();
-void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int max_keys,
+void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                               const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
                               float scale, void* out);
-void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int max_keys,
+void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
                        void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale,
                        void* out);

@@ -393,27 +393,21 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
 
 int attn_split_q_tile_rows() { return kQTile; }
 
-// Eight waves instead of four halve the blocks that a wave walks one after the other.  At head_dim 128 they leave room for one
-// work-group on a compute unit, and below twenty blocks the larger merge costs what the shorter walk gains.  Measured, us a launch,
-// four / eight waves, 128 work items of 22, 47, 125 blocks: head_dim 64 7.9 / 7.1, 11.9 / 9.9, 25.4 / 19.4; 128 10.7 / 10.4, 16.6 / 14.6,
-// 34.8 / 28.1; 256 items of 13 and 22: 64 6.7 / 6.7, 8.2 / 7.6; 128 9.4 / 9.9, 11.6 / 11.5; 480 items of 22: 10.4 / 11.0; 16.3 / 21.9.
-// The rule counts the attention's own work-groups only: a step gives the bits of hack_attn over the rows that it kept.
-static bool split_in_eight(int n_items, int max_keys) { return max_keys > 20 * kKB && n_items <= 256; }
-
 #define HACK_SPLIT(D_, G_, ...)                                                                                  \
   do {                                                                                                           \
     if (eight) hipLaunchKernelGGL((attn_split<D_, G_, 8>), dim3(n), dim3(512), 0, s, descs, items, __VA_ARGS__); \
     else hipLaunchKernelGGL((attn_split<D_, G_, 4>), dim3(n), dim3(256), 0, s, descs, items, __VA_ARGS__);       \
   } while (0)
 
-void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int max_keys,
+void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
                        void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale,
                        void* out) {
   const int n = n_items;
   if (n <= 0) return;
   typedef __bf16 T;
-  const bool eight = split_in_eight(n_items, max_keys);
+  const bool eight = fuse & kSplitEight;
+  fuse &= kSplitAppend;
   if (head_dim == 64)
     HACK_SPLIT(64, false, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
                pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
@@ -422,13 +416,13 @@ void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const
                pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
 }
 
-void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, int max_keys,
+void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                               const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
                               float scale, void* out) {
   const int n = n_items + g.n_moves;
   if (n <= 0) return;
   typedef __bf16 T;
-  const bool eight = split_in_eight(n_items, max_keys);
+  const bool eight = g.eight;
   if (head_dim == 64)
     HACK_SPLIT(64, true, (const T*)q, (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k,
                scale, (T*)out, g);
