@@ -264,11 +264,13 @@ hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q,
  *   0  bf16: work items of 128 queries that share every K/V block (large
  *      steps); in a launch with no more work items than the
  *      device holds work-groups, a few work items may be served by two
- *      work-groups each (half of the keys each, the partial results added up
- *      in float32 in a fixed order) where that shortens the launch.
+ *      work-groups each, and in one with no more than compute units every
+ *      item by a work-group of twice as many waves (half of the keys each,
+ *      the partial results added up in float32 in a fixed order) where that
+ *      shortens the launch.
  *      fp32 contexts (always 0): work items of 16 or 32 queries whose waves
  *      split the keys; appends and kept rows as variant 1 does,
- *   1  work items of 32 queries whose four waves split the keys and merge their
+ *   1  work items of 32 queries whose four or eight waves split the keys and merge their
  *      partial softmax results at the end (bf16, early scale steps: few
  *      queries); in hack_step this kernel also performs the append when no unit
  *      of the step compresses, and otherwise reads the kept rows where they lie

@@ -85,7 +85,7 @@ struct hack_ctx {
                                  // [1] a logit exceeded the range the bf16 score kernel supports
   int score_capacity[4] = {0, 0, 0, 0};   // bf16 path: score items one fused launch may hold (resident waves) for items of 32, 64, 128, 256 keys
   int split_max_items = 0;       // launches with at most this many 32-query attention items use the key-split kernel
-  int attn_kernel = 1;           // bf16 kernel of the 128-query items: 1 = deeper pipeline, 0 = plain (HACK_ATTN_PIPE=0)
+  int attn_kernel = -1;          // bf16 kernel of the 128-query items (kAttnPlain ...); -1 (default): the deeper pipeline, keys in halves where use_key_halves says so
   // streamed form of that kernel: the launch is cut into equal runs of key blocks, one per resident work-group
   int attn_stream = -1;          // HACK_ATTN_STREAM; -1 (default): cut single work items where the pair model gains, 0: never, 1: equal runs
                                  // for every launch of the 128-query kernel, 2: A/B aid, 4: every cut the model likes (see use_stream_attention)
@@ -111,6 +111,7 @@ struct StepGroup {
   bool streamed = false;                  // attention in the streamed form (then n_items is 0)
   bool gathered = false;                  // attention reads the kept rows in place and updates the cache beside it (n_moves work-groups)
   int n_moves = 0;
+  int attn_kernel = 0;                    // of the 128-query work items
   int item_keys = 0;
   bool two_pass = false;
   bool small = false;                     // score and selection in one launch
@@ -344,12 +345,39 @@ void build_attn_items(const std::vector<UnitDesc>& descs, int N_k, int tile_rows
 // that the 128-query kernel, which shares every K/V block among four times as
 // many queries, is faster.  Measured cross-overs on MI355X: head_dim 128 between
 // 416 and 576 items (16 heads, batch 2); head_dim 64 between 1920 and 3840 items
-// (30 heads, batch 32).
+// (30 heads, batch 32), where those items are a few queries each: with more than 128 queries a unit the line lies near
+// 1200 (60 units, split / 128 queries: 576 queries, 1080 items over 300, 800, 2000 keys 14.0 / 13.5, 21.0 / 20.5, 39.8 / 40.9 us;
+// 1024 queries, 1920 items over 800, 2000, 5000 keys 31 / 23, 59 / 45, 138 / 98 us, an append launch 5 to 9).
+constexpr int kSplitItemsManyQueries64 = 1200;
 int split_max_items_default(int head_dim) { return head_dim == 64 ? 2048 : 512; }
 bool use_split_attention(const hack_ctx* ctx, int n_units, int N_k) {
   if (ctx->cfg.dtype != HACK_BF16) return false;
   const int tile = attn_split_q_tile_rows();
-  return (int64_t)n_units * ((N_k + tile - 1) / tile) <= ctx->split_max_items;
+  int limit = ctx->split_max_items;
+  if (ctx->cfg.head_dim == 64 && N_k > kAttnTileRows && limit == split_max_items_default(64)) limit = kSplitItemsManyQueries64;
+  return (int64_t)n_units * ((N_k + tile - 1) / tile) <= limit;
+}
+
+// Launches of 128-query work items that leave a compute unit one of them take the form that walks the two halves of the keys
+// side by side: one work-group alone feeds a compute unit's matrix cores at half of their rate.  Measured, us a launch, whole
+// keys / halves (head_dim 128): 256 items of 28, 41, 79 blocks 26.4 / 24.3, 31.7 / 30.4, 54.9 / 49.7; 160 items of 25, 41, 47, 157
+// 21.4 / 22.0, 29.4 / 27.9, 33.2 / 31.1, 91 / 76; of 17 blocks 20.0 / 21.2.  A compute unit holds one such work-group: beyond one per
+// compute unit of an XCD it loses (416 items 113 / 126).
+constexpr int kHalvesMinBlocks = 28;
+bool use_key_halves(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, int N_k, std::vector<AttnItem>* items) {
+  if (ctx->cfg.dtype != HACK_BF16 || ctx->cfg.head_dim != 128 || (ctx->attn_kernel != -1 && ctx->attn_kernel != kAttnHalves) || ctx->attn_stream > 0) return false;
+  const bool forced = ctx->attn_kernel == kAttnHalves;
+  int longest = 0;
+  for (const UnitDesc& d : descs) {
+    if (d.n_out <= kAttnKeyBlock) return false;   // either half needs a block
+    longest = std::max(longest, d.n_out);
+  }
+  const int64_t n = (int64_t)descs.size() * ((N_k + kAttnTileRows - 1) / kAttnTileRows);
+  if (!forced && (n > ctx->attn_slots / 2 || longest <= (kHalvesMinBlocks - 1) * kAttnKeyBlock)) return false;
+  build_attn_items(descs, N_k, kAttnTileRows, items);   // padded to as many for every XCD
+  if (forced || (int)items->size() <= ctx->attn_slots / 2) return true;
+  items->clear();
+  return false;
 }
 
 // Queries per attention work item of a launch.
@@ -583,7 +611,7 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   if (const char* v = std::getenv("HACK_SCORE_MODE")) ctx->score_mode = std::atoi(v) == 1 ? HACK_SCORE_TWO_PASS : HACK_SCORE_FUSED;
   if (const char* v = std::getenv("HACK_ATTN_SPLIT_ITEMS")) ctx->split_max_items = std::atoi(v);   // tuning / test override
   if (const char* v = std::getenv("HACK_STEP_OVERLAP")) ctx->step_overlap = std::atoi(v) != 0;
-  if (const char* v = std::getenv("HACK_ATTN_PIPE")) ctx->attn_kernel = std::atoi(v) != 0;   // A/B and test override
+  if (const char* v = std::getenv("HACK_ATTN_PIPE")) ctx->attn_kernel = std::min(std::max(std::atoi(v), 0), 2);   // A/B and test override
   if (const char* v = std::getenv("HACK_ATTN_STREAM")) ctx->attn_stream = std::atoi(v);       // A/B and test override
   hipError_t e = hipSetDevice(cfg->device);
   const size_t n_ws = (size_t)cfg->max_units * ctx->ws_stride;
@@ -958,8 +986,9 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
   const int tile = attn_tile_rows(ctx, U, N_k);
   std::vector<AttnItem> items;
   AttnStreamPlan plan;
-  const bool streamed = !split && use_stream_attention(ctx, descs, N_k, false, &plan);
-  if (!streamed) build_attn_items(descs, N_k, tile, &items);
+  const bool halves = !split && use_key_halves(ctx, descs, N_k, &items);
+  const bool streamed = !split && !halves && use_stream_attention(ctx, descs, N_k, false, &plan);
+  if (!streamed && !halves) build_attn_items(descs, N_k, tile, &items);
   Table t;
   const size_t o_desc = t.add(descs.data(), descs.size());
   const size_t o_items = t.add(items.data(), items.size());
@@ -982,7 +1011,7 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
                     nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale, out);
   else
     launch_attn(s, ctx->cfg.head_dim, (const UnitDesc*)(dev + o_desc), (const AttnItem*)(dev + o_items), (int)items.size(), q,
-                kv->k, kv->v, N_k, scale, out, ctx->attn_kernel);
+                kv->k, kv->v, N_k, scale, out, halves ? kAttnHalves : ctx->attn_kernel == kAttnPlain ? kAttnPlain : kAttnPipe);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
 } HACK_NO_THROW(ctx)
@@ -1132,8 +1161,10 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   AttnStreamPlan plan;
   std::vector<AttnItem> items;
   std::vector<ScoreItem> sitems;
-  g->streamed = !n.split && use_stream_attention(ctx, u.descs, n.N_k, shared, &plan);
-  if (!g->streamed) build_attn_items(u.descs, n.N_k, n.tile, &items);
+  g->attn_kernel = ctx->attn_kernel == kAttnPlain ? kAttnPlain : kAttnPipe;
+  if (!n.split && !shared && use_key_halves(ctx, u.descs, n.N_k, &items)) g->attn_kernel = kAttnHalves;
+  g->streamed = !n.split && g->attn_kernel != kAttnHalves && use_stream_attention(ctx, u.descs, n.N_k, shared, &plan);
+  if (!g->streamed && g->attn_kernel != kAttnHalves) build_attn_items(u.descs, n.N_k, n.tile, &items);
   g->small = ctx->cfg.dtype == HACK_BF16 && use_score_select(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t);
   if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty() && !g->small)
     g->item_keys = plan_score_items(ctx, u.descs, u.comp, g->two_pass, &sitems, &g->launches);
@@ -1211,7 +1242,7 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
     launch_attn_f32(s, ctx->cfg.head_dim, items, g.n_items, n.tile, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v, a.cp.pos,
                     a.pos_new, fuse, n.N_k, a.scale, a.out);
   else
-    launch_attn(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out, ctx->attn_kernel);
+    launch_attn(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out, g.attn_kernel);
 }
 
 // Sees to it that a known step's tables are on the device for the work that is issued on `s` next: a step that was

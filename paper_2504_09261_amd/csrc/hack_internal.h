@@ -178,10 +178,11 @@ void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, in
                    int64_t idx_stride, int32_t* seam);
 
 // bf16 attention of N_k queries per unit over rows [out_off, out_off + n_out), work items of 128 queries.
-// bf16_kernel: which kernel serves the 128-query work items, 1 = the deeper
-// software pipeline (default), 0 = the plain one-block pipeline (kept for A/B timing
-// and as a second implementation the tests run over the same shapes).
+// bf16_kernel: which kernel serves the 128-query work items: the deeper software pipeline, the plain one-block
+// pipeline (kept for A/B timing and as a second implementation the tests run over the same shapes), or the deeper one
+// with the two halves of a unit's keys side by side in a work-group (head_dim 128; every unit needs more than 32 rows).
 constexpr int kAttnTileRows = 128;
+enum : int { kAttnPlain = 0, kAttnPipe = 1, kAttnHalves = 2 };
 void launch_attn(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, const void* q,
                  const void* k_cache, const void* v_cache, int N_k, float scale, void* out, int bf16_kernel);
 // float32 attention; work items of q_tile_rows = attn_f32_q_tile_rows(units, N_k) queries (16 or 32); fuse and the

@@ -376,8 +376,13 @@ __device__ __forceinline__ void sched_interleave() {
 // the last of the item's n_parts tickets (every other part has been stored and published by then)
 // adds the parts first_part .. first_part + n_parts - 1 up and stores the output rows, then leaves the
 // counter at zero for the next launch.  Nobody waits for anybody.
-template <int D, int NW, bool STREAM>
-__global__ __launch_bounds__(64 * NW, 2) void attn_pipe(
+//
+// KS = 2: two groups of NW waves hold the same queries and walk the two halves of the unit's blocks, each through rings of
+// its own but from the same barriers, and exchange half of their unnormalised O^T through LDS at the end: a lone
+// work-group's stage (0.7 us at 128 queries, d = 128) is a chain of latencies that two waves a SIMD overlap (1.16 us a pair of
+// stages).  96 KiB of LDS, so one work-group a compute unit.
+template <int D, int NW, int KS, bool STREAM>
+__global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
     const UnitDesc* __restrict__ descs, const AttnItem* __restrict__ items,
     const AttnSeg* __restrict__ segs, const int32_t* __restrict__ seg_begin,
     const __bf16* __restrict__ q, const __bf16* __restrict__ k_cache,
@@ -393,11 +398,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_pipe(
   static_assert(IPW >= 1, "a block must give every wave at least one copy instruction");
   static_assert(KK == 2 * MB, "as many score MFMAs as PV MFMAs per block");
 
-  const int tid = threadIdx.x;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  static_assert(KS == 1 || (KS == 2 && !STREAM), "whole work items only when the keys are split");
 
-  __shared__ __attribute__((aligned(1024))) __bf16 Ks[NS][BLK];
-  __shared__ __attribute__((aligned(1024))) __bf16 Vs[NS][BLK];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = KS == 1 ? wave : wave % NW, ks = KS == 1 ? 0 : wave / NW;   // 32 queries and half of the keys of this wave
+
+  __shared__ __attribute__((aligned(1024))) __bf16 K_ring[KS][NS][BLK];
+  __shared__ __attribute__((aligned(1024))) __bf16 V_ring[KS][NS][BLK];
+  __bf16 (&Ks)[NS][BLK] = K_ring[ks];
+  __bf16 (&Vs)[NS][BLK] = V_ring[ks];
+  __shared__ float2 ml_sh[KS == 2 ? 2 * NW * 32 : 1];
   __shared__ int last_ticket;
 
   int seg_lo = blockIdx.x, seg_hi = blockIdx.x + 1;
@@ -422,6 +433,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_pipe(
     d = items[si];
     if (d.desc < 0) return;
     sg = AttnSeg{d.desc, d.q_tile, 0, 0x3fffffff, -1, 0, 0, 0};
+  }
+  if (KS == 2) {   // the first half of the blocks, the larger one if they are odd, and the rest (the host sees to it that there is one)
+    const int h = ((d.n_out + kKB - 1) / kKB + 1) / 2;
+    sg.blk0 = ks == 0 ? 0 : h;
+    sg.blk1 = ks == 0 ? h : 0x3fffffff;
   }
   const int key0 = sg.blk0 * kKB;                                               // first key of the segment
   const int len = (int)min((int64_t)sg.blk1 * kKB, (int64_t)d.n_out) - key0;    // its keys
@@ -653,6 +669,48 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_pipe(
 
   // ---- normalise and store: lane holds query col, head-dim rows 32mb + 8(r/4) + 4h + r%4 ----
   float l = pair_sum(l_run);
+  if constexpr (KS == 2) {
+    // The waves (w, 0) and (w, 1) hold the same queries over the two halves of the keys: each adds up and stores half of
+    // the head-dim, what the other one needs goes through the rings, which nobody reads any more.
+    if (ks == 1 && (((d.n_out + kKB - 1) / kKB) & 1)) __syncthreads();   // this half had one stage less
+    constexpr int HB = MB / 2;   // head-dim blocks of a half
+    float4* const xo = reinterpret_cast<float4*>(ks == 0 ? &K_ring[0][0][0] : &V_ring[0][0][0]) + w * HB * 4 * 64 + lane;
+    const float4* const xi = reinterpret_cast<const float4*>(ks == 0 ? &V_ring[0][0][0] : &K_ring[0][0][0]) + w * HB * 4 * 64 + lane;
+    __syncthreads();
+    if (half == 0) ml_sh[wave * 32 + col] = make_float2(mc, l);
+    const int qi = q0 + col;
+    __bf16* orow = out + ((int64_t)d.unit * N_k + min(qi, N_k - 1)) * D;
+    auto finish = [&](auto half_tag) {
+      constexpr int MINE = decltype(half_tag)::value * HB, THEIRS = HB - MINE;
+#pragma unroll
+      for (int m = 0; m < HB; ++m)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+          xo[(m * 4 + r4) * 64] = make_float4(o[THEIRS + m][4 * r4], o[THEIRS + m][4 * r4 + 1], o[THEIRS + m][4 * r4 + 2], o[THEIRS + m][4 * r4 + 3]);
+      __syncthreads();
+      const float2 ml = ml_sh[(wave ^ NW) * 32 + col];
+      const float M = fmaxf(mc, ml.x);   // finite: both halves hold a valid key
+      float f = __builtin_amdgcn_exp2f(mc - M), g = __builtin_amdgcn_exp2f(ml.x - M);
+      const float inv = 1.f / fmaf(f, l, g * ml.y);
+      f *= inv;
+      g *= inv;
+#pragma unroll
+      for (int m = 0; m < HB; ++m)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const float4 x = xi[(m * 4 + r4) * 64];
+          bf16x4 pk;
+          pk[0] = (__bf16)fmaf(g, x.x, f * o[MINE + m][4 * r4]);
+          pk[1] = (__bf16)fmaf(g, x.y, f * o[MINE + m][4 * r4 + 1]);
+          pk[2] = (__bf16)fmaf(g, x.z, f * o[MINE + m][4 * r4 + 2]);
+          pk[3] = (__bf16)fmaf(g, x.w, f * o[MINE + m][4 * r4 + 3]);
+          if (qi < N_k) *reinterpret_cast<bf16x4*>(orow + 32 * (MINE + m) + 8 * r4 + 4 * half) = pk;
+        }
+    };
+    if (ks == 0) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, 1>{});
+    return;
+  }
   bool store = true;
   if (STREAM && sg.part >= 0) {
     // Partial result, register-major (every store instruction of a wave writes 512 contiguous bytes).
@@ -744,8 +802,15 @@ static void launch_mfma_t(hipStream_t s, const UnitDesc* descs, const AttnItem* 
                           const void* q, const void* k_cache, const void* v_cache, int N_k,
                           float scale, void* out, int kernel) {
   typedef __bf16 T;
-  if (kernel != 0)
-    hipLaunchKernelGGL((attn_pipe<D, NW, false>), dim3(n_items), dim3(64 * NW), 0, s, descs, items, nullptr, nullptr,
+  if constexpr (D == 128) {
+    if (kernel == kAttnHalves) {
+      hipLaunchKernelGGL((attn_pipe<D, NW, 2, false>), dim3(n_items), dim3(128 * NW), 0, s, descs, items, nullptr, nullptr,
+                         (const T*)q, (const T*)k_cache, (const T*)v_cache, N_k, scale, (T*)out, nullptr, nullptr, nullptr);
+      return;
+    }
+  }
+  if (kernel != kAttnPlain)
+    hipLaunchKernelGGL((attn_pipe<D, NW, 1, false>), dim3(n_items), dim3(64 * NW), 0, s, descs, items, nullptr, nullptr,
                        (const T*)q, (const T*)k_cache, (const T*)v_cache, N_k, scale, (T*)out, nullptr, nullptr, nullptr);
   else
     hipLaunchKernelGGL((attn_mfma<D, NW>), dim3(n_items), dim3(64 * NW), 0, s, descs, items,
@@ -765,8 +830,8 @@ int attn_stream_slots(int head_dim) {
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
   const hipError_t e = head_dim == 64
-      ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, attn_pipe<64, 4, true>, 256, 0)
-      : hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, attn_pipe<128, 4, true>, 256, 0);
+      ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, attn_pipe<64, 4, 1, true>, 256, 0)
+      : hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, attn_pipe<128, 4, 1, true>, 256, 0);
   if (e != hipSuccess) return 0;
   return blocks * cus;
 }
@@ -777,10 +842,10 @@ void launch_attn_stream(hipStream_t s, int head_dim, const UnitDesc* descs, cons
   if (n_groups <= 0) return;
   typedef __bf16 T;
   if (head_dim == 64)
-    hipLaunchKernelGGL((attn_pipe<64, 4, true>), dim3(n_groups), dim3(256), 0, s, descs, nullptr, segs, seg_begin,
+    hipLaunchKernelGGL((attn_pipe<64, 4, 1, true>), dim3(n_groups), dim3(256), 0, s, descs, nullptr, segs, seg_begin,
                        (const T*)q, (const T*)k_cache, (const T*)v_cache, N_k, scale, (T*)out, part_o, part_ml, part_count);
   else
-    hipLaunchKernelGGL((attn_pipe<128, 4, true>), dim3(n_groups), dim3(256), 0, s, descs, nullptr, segs, seg_begin,
+    hipLaunchKernelGGL((attn_pipe<128, 4, 1, true>), dim3(n_groups), dim3(256), 0, s, descs, nullptr, segs, seg_begin,
                        (const T*)q, (const T*)k_cache, (const T*)v_cache, N_k, scale, (T*)out, part_o, part_ml, part_count);
 }
 

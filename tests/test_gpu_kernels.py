@@ -564,6 +564,41 @@ def test_key_split_attention_block_and_wave_edges(d, H, Nk, lens):
     hk.close()
 
 
+@pytest.mark.parametrize("forced,H,Nk,lens", [
+    (True, 3, 1, [33, 64, 65]), (True, 4, 127, [96, 97, 128, 129]), (True, 3, 128, [160, 191, 193]), (True, 5, 129, [224, 225, 256, 321, 1000]),
+    (False, 20, 832, [865] * 10 + [897, 900] * 5),       # 140 work items of 128 queries: halves by the library's own rule
+    (False, 20, 832, [864] + [40] * 19),                 # one block short of it
+])
+def test_attention_with_the_keys_in_two_halves(forced, H, Nk, lens, monkeypatch):
+    """Odd and even numbers of blocks, halves of a single ragged block, steady loops entered by neither, one or both halves."""
+    u = _u()
+    if forced:
+        monkeypatch.setenv("HACK_ATTN_PIPE", "2")
+        monkeypatch.setenv("HACK_ATTN_SPLIT_ITEMS", "0")
+    d = 128
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(Nk + len(lens))
+    lens = np.asarray(lens, np.int32)
+    off = np.concatenate([[0], np.cumsum((lens + 7) // 8 * 8)]).astype(np.int64)
+    q = torch.randn((1, H, Nk, d), generator=gen, device=u.DEV).bfloat16()
+    K, V = (torch.randn((int(off[-1]), d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    K[off[0]:off[0] + 16] *= 12      # the halves' references lie far apart
+    scale = float(np.float32(d ** -0.5))
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=int(lens.max()), max_queries=Nk)
+    assert hk.attn_variant(1, Nk) == 0
+    out, again = torch.full_like(q, 7.0), torch.full_like(q, 7.0)
+    hk.attn(q, Cache(K, V, off[:-1], lens), scale, out)
+    hk.attn(q, Cache(K, V, off[:-1], lens), scale, again)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again)
+    for h in range(H):
+        k, v = (x[off[h]:off[h] + lens[h]].double() for x in (K, V))
+        want = torch.softmax(scale * (q[0, h].double() @ k.T.contiguous()), -1) @ v
+        # P and O are rounded to bf16: 2^-8 of the largest value each, |V| up to 4.5
+        assert float((out[0, h].double() - want).abs().max()) < 4e-2, (h, int(lens[h]))
+    hk.close()
+
+
 def test_attention_rejects_empty_unit_and_bad_scale():
     u = _u()
     hk = u.make_hack(heads=1, head_dim=64, dtype="bf16", max_units=1, max_cache_len=64, max_queries=8)
