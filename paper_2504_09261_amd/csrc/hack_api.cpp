@@ -532,12 +532,12 @@ int finish_score_plan(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, c
 }
 
 // Scores the listed units of a table that is already on the device.
-void run_score(hack_ctx* ctx, hipStream_t s, bool two_pass, unsigned long long* slots, const UnitDesc* ddev, const int32_t* list_dev, int n_list, int max_t,
+void run_score(hack_ctx* ctx, hipStream_t s, bool two_pass, unsigned long long* slots, const UnitDesc* ddev, int n_list, int max_t,
                const ScoreItem* items_dev, int item_keys, const std::vector<int>& group_begin, const void* q,
                const int32_t* rows_dev, int n_obs, int N_k, float scale, const void* k_cache, const void* k_new,
                float* importance, int64_t imp_stride) {
   if (ctx->cfg.dtype == HACK_F32) {
-    launch_score_f32(s, ctx->cfg.head_dim, ddev, list_dev, n_list, max_t, q, rows_dev, n_obs, N_k, scale, k_cache, k_new,
+    launch_score_f32(s, ctx->cfg.head_dim, ddev, nullptr, n_list, max_t, q, rows_dev, n_obs, N_k, scale, k_cache, k_new,
                      ctx->stats, importance, imp_stride);
     return;
   }
@@ -750,13 +750,12 @@ extern "C" hack_status hack_score(hack_ctx* ctx, int32_t B, int32_t N_k, const v
   if (ctx->cfg.dtype == HACK_BF16) item_keys = plan_score_items(ctx, descs, list, two_pass, &sitems, &groups);
   Table t;
   const size_t o_desc = t.add(descs.data(), descs.size());
-  const size_t o_list = t.add(list.data(), list.size());
   const size_t o_rows = t.add(rows, kMaxObs);
   const size_t o_sit = t.add(sitems.data(), sitems.size());
   const uint8_t* dev;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = table_device(ctx, t, s, &dev)) != HACK_OK) return st;
-  run_score(ctx, s, two_pass, ctx->rowstat, (const UnitDesc*)(dev + o_desc), (const int32_t*)(dev + o_list), (int)list.size(), max_t,
+  run_score(ctx, s, two_pass, ctx->rowstat, (const UnitDesc*)(dev + o_desc), (int)list.size(), max_t,
             (const ScoreItem*)(dev + o_sit), item_keys, groups, q, (const int32_t*)(dev + o_rows), n_obs, N_k, scale, in->k, k_new,
             importance, imp_stride);
   HIP_TRY(ctx, hipGetLastError());
@@ -823,7 +822,6 @@ extern "C" hack_status hack_select(hack_ctx* ctx, int32_t B, const float* import
   for (int h = 0; h < H; ++h)
     if (head_type[h] > 1) return fail(ctx, HACK_EINVAL, "head_type[%d] = %d is not a head class", h, head_type[h]);
   std::vector<UnitDesc> descs(U);
-  std::vector<int32_t> list(U);
   int max_t = 0;
   for (int u = 0; u < U; ++u) {
     const int T = t_in[u];
@@ -837,17 +835,15 @@ extern "C" hack_status hack_select(hack_ctx* ctx, int32_t B, const float* import
     d.len_in = T; d.n_new = 0; d.n_out = b; d.unit = u;
     plan_select(head_type[u % H], T, b, n_init, n_recent, &d);
     descs[u] = d;
-    list[u] = u;
     max_t = std::max(max_t, T);
     if (len_out) len_out[u] = b;
   }
   Table t;
   const size_t o_desc = t.add(descs.data(), descs.size());
-  const size_t o_list = t.add(list.data(), list.size());
   const uint8_t* dev;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = table_device(ctx, t, s, &dev)) != HACK_OK) return st;
-  launch_select(s, (const UnitDesc*)(dev + o_desc), (const int32_t*)(dev + o_list), U, max_t, importance, imp_stride,
+  launch_select(s, (const UnitDesc*)(dev + o_desc), nullptr, U, max_t, importance, imp_stride,
                 kept_idx, idx_stride, nullptr);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
@@ -1185,7 +1181,9 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->n_stream = plan.n_groups;
   Table t;
   g->o_desc = t.add(u.descs.data(), u.descs.size());
-  g->o_comp = t.add(u.comp.data(), u.comp.size());
+  std::vector<UnitDesc> comp;   // the compressing units' descriptors, together
+  for (const int32_t i : u.comp) comp.push_back(u.descs[i]);
+  g->o_comp = t.add(comp.data(), comp.size());
   g->o_merge = t.add(u.merging.data(), u.merging.size());
   g->o_rows = t.add(rows, kMaxObs);
   g->o_items = t.add(items.data(), items.size());
@@ -1198,17 +1196,17 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
 
 // score -> select -> append / gather (-> merge) of a group's units
 void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
-  const int32_t* comp_dev = reinterpret_cast<const int32_t*>(g.dev + g.o_comp);
+  const UnitDesc* comp_dev = reinterpret_cast<const UnitDesc*>(g.dev + g.o_comp);
   if (g.n_comp > 0 && g.small) {
-    launch_score_select(s, ctx->cfg.head_dim, g.ddev(), comp_dev, g.n_comp, g.max_t, a.q,
+    launch_score_select(s, ctx->cfg.head_dim, comp_dev, nullptr, g.n_comp, g.max_t, a.q,
                         reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, a.kept, a.kstride,
                         ctx->seam, ctx->fault);
   } else if (g.n_comp > 0) {
-    run_score(ctx, s, g.two_pass, g.slots, g.ddev(), comp_dev, g.n_comp, g.max_t,
+    run_score(ctx, s, g.two_pass, g.slots, comp_dev, g.n_comp, g.max_t,
               reinterpret_cast<const ScoreItem*>(g.dev + g.o_sit), g.item_keys, g.launches, a.q,
               reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->importance,
               ctx->ws_stride);
-    launch_select(s, g.ddev(), comp_dev, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
+    launch_select(s, comp_dev, nullptr, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
   }
   if (!a.in_place || (!n.fuse_append && !g.gathered))
     launch_move(s, ctx->elem_bytes, ctx->cfg.head_dim, g.ddev(), g.n_desc, g.max_rows, a.cp, a.cp, a.k_new, a.v_new, n.N_k,

@@ -158,8 +158,8 @@ hipError_t score_static_setup(int device);   // once per device: finds the devic
 hipError_t launch_score_static(hipStream_t s, int device, int head_dim, const StaticScorePlan& plan, const void* q, int n_obs,
                                int N_k, float scale, const void* k_cache, const void* k_new, float* importance,
                                int64_t imp_stride, int* fault);
-// fp32: two passes over (chunk of keys, listed unit); list[n_list] indexes
-// descs; stats is a workspace of 64 doubles per work-group (score_f32_groups).
+// Launches over listed units: list[n_list] indexes descs, or is NULL where the n_list descriptors stand together.
+// fp32: two passes over (chunk of keys, listed unit); stats is a workspace of 64 doubles per work-group (score_f32_groups).
 void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,
                       int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
                       const void* k_cache, const void* k_new, double* stats, float* importance,

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void score_f32(
     float* __restrict__ importance, int64_t imp_stride) {
   constexpr int C = D / 16;             // 16-byte pieces of a row per lane
   constexpr int kChunk = 64 * TPW;      // keys per work-group
-  const UnitDesc d = descs[list[blockIdx.y]];
+  const UnitDesc d = listed_desc(descs, list, blockIdx.y);
   const int T_in = d.len_in + d.n_new;
   if ((int)blockIdx.x * kChunk >= T_in) return;
   const int n_chunks = (T_in + kChunk - 1) / kChunk;
@@ -616,19 +616,18 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
 // ---------------------------------------------------------------------------
 // bf16, short units: score and selection in one launch
 // ---------------------------------------------------------------------------
-// A work-group of NW waves owns a unit of at most 64 NW keys (NW = 4, 8, 16): wave w takes the tiles w and w + NW, the row
+// A work-group of NW waves owns a unit of at most 32 TILES NW keys (NW = 4, 8, 16): wave w takes the tiles w and (TILES = 2) w + NW, the row
 // sums meet in LDS instead of the exchange area, importance goes to LDS only and thread j ranks key j.  The numbers
 // are those of score_fused up to the order in which the row sums are added in fp64.  Latency bounds these launches: a
 // score launch, whose work-groups wait for each other through L2, and a selection launch behind it take 8 + 4.4 us (kernel trace) at
 // 60 units of 46 to 475 keys (one 256^2 image: 108.6 -> 100.6 us, 960 units 349 -> 318).
-template <int D, int NW>
+template <int D, int NW, int TILES>
 __global__ __launch_bounds__(64 * NW) void score_select(
     const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, const __bf16* __restrict__ q,
     const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale, const __bf16* __restrict__ k_cache,
     const __bf16* __restrict__ k_new, int32_t* __restrict__ kept_idx, int64_t idx_stride, int32_t* __restrict__ seam,
     int* __restrict__ fault) {
   constexpr int KK = D / 16, CPR = D / 8, RPI = 64 / CPR, IPT = 32 / RPI, TILE = 32 * D;   // as in score_fused
-  constexpr int TILES = 2;
   constexpr int kBufs = 8192 / (TILE * 2);   // tile buffers per wave: the row sums need 8 KiB
   using Shared = SelectShared<64 * NW, 11, 11>;
   static_assert(Shared::kHist * 4 <= NW * 8192, "histograms fit the tile buffers");
@@ -637,12 +636,12 @@ __global__ __launch_bounds__(64 * NW) void score_select(
   __shared__ uint32_t keys[64 * NW];
   __shared__ Shared sh;
 
-  const UnitDesc d = descs[list[blockIdx.x]];
+  const UnitDesc d = listed_desc(descs, list, blockIdx.x);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int T_in = d.len_in + d.n_new;
-  const int n_tiles = w * 32 >= T_in ? 0 : (w + NW) * 32 >= T_in ? 1 : 2;   // of this wave
+  const int n_tiles = w * 32 >= T_in ? 0 : TILES == 1 || (w + NW) * 32 >= T_in ? 1 : 2;   // of this wave
   const unsigned lds0 = lds_addr_of(&bufs[w][0]);
 
   int src_off[IPT];
@@ -671,7 +670,7 @@ __global__ __launch_bounds__(64 * NW) void score_select(
     }
   };
   if (n_tiles > 0) issue(0);
-  if (kBufs > 1 && n_tiles > 1) issue(1);
+  if (TILES > 1 && kBufs > 1 && n_tiles > 1) issue(1);
 
   bf16x8 qf[KK];
   {
@@ -697,7 +696,7 @@ __global__ __launch_bounds__(64 * NW) void score_select(
 #pragma unroll
   for (int t = 0; t < TILES; ++t) {
     if (t < n_tiles) {                 // wave-uniform
-      if (kBufs > 1 && t + 1 < n_tiles) dma_wait_but<IPT>();
+      if (kBufs > 1 && t + 1 < TILES && t + 1 < n_tiles) dma_wait_but<IPT>();
       else dma_wait_but<0>();
       const __bf16* Kt = reinterpret_cast<const __bf16*>(&bufs[w][(t % kBufs) * TILE * 2]);
       double sd[16];
@@ -709,7 +708,7 @@ __global__ __launch_bounds__(64 * NW) void score_select(
 #pragma unroll
         for (int r = 0; r < 16; ++r) sd[r] = (kk == 0) ? (double)c[r] : sd[r] + (double)c[r];
       }
-      if (kBufs == 1 && t + 1 < n_tiles) {
+      if (kBufs == 1 && t + 1 < TILES && t + 1 < n_tiles) {
         // the sums above have consumed every operand read: the buffer may be refilled
 #pragma unroll
         for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(sd[r]) : : "memory");
@@ -972,16 +971,21 @@ void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, con
                          const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
                          const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault) {
   if (n_list <= 0) return;
-#define HACK_SMALL(D_, NW_)                                                                                                  \
-  hipLaunchKernelGGL((score_select<D_, NW_>), dim3(n_list), dim3(64 * NW_), 0, s, descs, list, (const __bf16*)q, q_rows, n_obs, \
+#define HACK_SMALL(D_, NW_, TILES_)                                                                                          \
+  hipLaunchKernelGGL((score_select<D_, NW_, TILES_>), dim3(n_list), dim3(64 * NW_), 0, s, descs, list, (const __bf16*)q, q_rows, n_obs, \
                      N_k, scale, (const __bf16*)k_cache, (const __bf16*)k_new, kept_idx, idx_stride, seam, fault)
+  // one tile a wave while every unit has a compute unit to itself: 30 units of 155 keys 7.6 -> 7.1 us (kernel trace); sixteen waves of
+  // one tile lose (60 units of 420 keys 9.2 -> 10.2)
+  const bool few = n_list <= 256;
   if (head_dim == 64) {
-    if (max_t_in <= 256) HACK_SMALL(64, 4);
-    else if (max_t_in <= 512) HACK_SMALL(64, 8);
-    else HACK_SMALL(64, 16);
+    if (max_t_in <= 256 && few) HACK_SMALL(64, 8, 1);
+    else if (max_t_in <= 256) HACK_SMALL(64, 4, 2);
+    else if (max_t_in <= 512) HACK_SMALL(64, 8, 2);
+    else HACK_SMALL(64, 16, 2);
   } else {
-    if (max_t_in <= 256) HACK_SMALL(128, 4);
-    else HACK_SMALL(128, 8);
+    if (max_t_in <= 256 && few) HACK_SMALL(128, 8, 1);
+    else if (max_t_in <= 256) HACK_SMALL(128, 4, 2);
+    else HACK_SMALL(128, 8, 2);
   }
 #undef HACK_SMALL
 }

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
   __shared__ __attribute__((aligned(16))) uint32_t hist[Shared::kHist];
   __shared__ Shared sh;
 
-  const UnitDesc d = descs[list[blockIdx.x]];
+  const UnitDesc d = listed_desc(descs, list, blockIdx.x);
   const float* imp = importance + (int64_t)d.unit * imp_stride;
   int32_t* out = kept_idx + (int64_t)d.unit * idx_stride;
   const int tid = threadIdx.x;
