@@ -165,6 +165,26 @@ void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const 
                       const void* k_cache, const void* k_new, double* stats, float* importance,
                       int64_t imp_stride);
 
+// fp32: score and selection of short units in one launch.  tiles: workspace of 4 entries per work-group of 64 keys
+// (score_f32_groups(n_units, max_t_in, 64)); counters: 2 uint32 per unit of the launch, zero on entry and left zero.  Weak: host
+// code that is linked without the kernels' file goes without.
+struct F32Tile {                     // what 16 keys contribute to their unit's rows
+  double m[kMaxObs], l[kMaxObs];     // maximum logit, sum of exp(logit - maximum)
+  float e[kMaxObs][16];              // exp(logit - maximum)
+};
+constexpr int kF32SmallKeys = 1024;   // longest unit of such a launch
+inline bool use_score_select_f32(int n_units, int max_t_in) {
+  return max_t_in <= kF32SmallKeys && score_f32_groups(n_units, max_t_in, 64) <= kF32SmallGroups;
+}
+inline int64_t score_select_f32_max_groups(int max_units, int max_len) {
+  const int64_t n = score_f32_groups(max_units, max_len < kF32SmallKeys ? max_len : kF32SmallKeys, 64);
+  return n < kF32SmallGroups ? n : kF32SmallGroups;
+}
+__attribute__((weak)) void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in,
+                                                   const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
+                                                   const void* k_cache, const void* k_new, F32Tile* tiles, unsigned* counters,
+                                                   int32_t* kept_idx, int64_t idx_stride, int32_t* seam);
+
 // bf16: score and selection of short units in one launch, one work-group per listed unit, no importance in memory.
 bool use_score_select(int head_dim, int n_units, int max_t_in);
 void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,

@@ -222,6 +222,172 @@ __global__ __launch_bounds__(kThreads) void score_f32(
 }
 
 // ---------------------------------------------------------------------------
+// float32, short units: score and selection in one launch
+// ---------------------------------------------------------------------------
+// Pass 1 as above with every tile of 16 keys a chunk of its own: a wave stores its tile's maxima, sums and weights
+// e = exp(logit - maximum) (float32 values by construction, see exp2_split), and the work-group that draws its unit's last ticket
+// weighs them, importance_j = sum_i e_ij exp(m_tile,i - m_i) / l_i, and ranks what it has just formed.  The tiles come from
+// different XCDs: weights, partials and tickets travel as device-scope relaxed atomics, a ticket drawn only after the
+// work-group's stores have been acknowledged; nobody waits for anybody.  Pass 2's operands, products and exponentials, its launch and the selection's
+// are saved: these launches are chains of latencies (8 to 16 units of 155, 255, 424, 561 keys: three launches 15.5 us,
+// this one 10.3, 10.2, 11.2, 14.4 in the kernel trace; a 256^2 schedule 116.6 -> 107.6 us).
+// 2^t for t <= 0 to 1e-11: the weights already carry float32's rounding, the factors that join tiles shall add none.
+__device__ __forceinline__ double exp2_double(double t) {
+  const double n = rint(fmax(t, -1100.0));
+  const double x = (fmax(t, -1100.0) - n) * 0.69314718055994530942;   // |x| <= 0.3466: the series of exp to x^9
+  double p = 1.0 / 362880;
+  p = fma(p, x, 1.0 / 40320);
+  p = fma(p, x, 1.0 / 5040);
+  p = fma(p, x, 1.0 / 720);
+  p = fma(p, x, 1.0 / 120);
+  p = fma(p, x, 1.0 / 24);
+  p = fma(p, x, 1.0 / 6);
+  p = fma(p, x, 0.5);
+  p = fma(p, x, 1.0);
+  p = fma(p, x, 1.0);
+  return ldexp(p, (int)n);
+}
+template <typename T>
+__device__ __forceinline__ void store_agent(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ T load_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// PER: rows per thread of the selection (T_in <= 256 PER)
+template <int D, int PER>
+__global__ __launch_bounds__(kThreads) void score_select_f32(
+    const UnitDesc* __restrict__ descs, const float* __restrict__ q, const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale,
+    const float* __restrict__ k_cache, const float* __restrict__ k_new, F32Tile* __restrict__ tiles, unsigned* __restrict__ counters,
+    int32_t* __restrict__ kept_idx, int64_t idx_stride, int32_t* __restrict__ seam) {
+  constexpr int C = D / 16;
+  constexpr int kMaxTiles = kThreads * PER / 16;
+  using Shared = SelectShared<kThreads, 11, 11>;
+  __shared__ __attribute__((aligned(16))) uint32_t hist[Shared::kHist];
+  __shared__ Shared sh;
+  __shared__ double factor[kMaxTiles][kMaxObs];   // exp(m_tile,i - m_i) / l_i
+  __shared__ double red[8][kMaxObs];
+  __shared__ int last_ticket;
+  const UnitDesc d = descs[blockIdx.y];
+  const int T_in = d.len_in + d.n_new;
+  const int n_groups = (T_in + 63) / 64;
+  if ((int)blockIdx.x >= n_groups) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int i = lane & 15, g = lane >> 4;
+  const int tile = blockIdx.x * 4 + w, key0 = tile * 16, n_tiles = (T_in + 15) / 16;
+  F32Tile* const unit_tiles = tiles + (int64_t)blockIdx.y * gridDim.x * 4;
+
+  if (tile < n_tiles) {
+    floatx4 qf[2][C], kf[C];
+    const int j = min(key0 + i, T_in - 1);
+    const float* p = (j < d.len_in ? k_cache + (d.in_off + j) * D : k_new + ((int64_t)d.unit * N_k + (j - d.len_in)) * D) + 4 * g;
+#pragma unroll
+    for (int c = 0; c < C; ++c) kf[c] = *reinterpret_cast<const floatx4*>(p + 16 * c);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int row = 16 * h + i;
+      const float* p = q + ((int64_t)d.unit * N_k + q_rows[row < n_obs ? row : 0]) * D + 4 * g;
+#pragma unroll
+      for (int c = 0; c < C; ++c) qf[h][c] = *reinterpret_cast<const floatx4*>(p + 16 * c);
+    }
+    doublex4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double kd = (double)kf[c][e];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qf[h][c][e], kd, acc[h], 0, 0, 0);
+      }
+    F32Tile* const out = unit_tiles + tile;
+    const bool valid = key0 + i < T_in;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * h + 4 * r + g;
+        const double s = acc[h][r] * (double)scale;
+        const double m = row16_reduce(valid ? s : -INFINITY, [](double a, double b) { return fmax(a, b); });   // finite: the tile's first key exists
+        const float e = valid ? exp2_split((s - m) * kLog2e) : 0.f;
+        const double l = row16_reduce((double)e, [](double a, double b) { return a + b; });
+        store_agent(&out->e[row][i], e);
+        if (i == 0) {
+          store_agent(&out->m[row], m);
+          store_agent(&out->l[row], l);
+        }
+      }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores have been acknowledged
+  __syncthreads();                                    // ... and so have the work-group's
+  if (tid == 0)
+    last_ticket = __hip_atomic_fetch_add(&counters[2 * blockIdx.y], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(n_groups - 1);
+  __syncthreads();
+  if (!last_ticket) return;
+  if (tid == 0) store_agent(&counters[2 * blockIdx.y], 0u);   // as the next launch expects it
+
+  // ---- rows: thread (t8, row) takes the tiles t8, t8 + 8, ... ----
+  const int row = tid & 31, t8 = tid >> 5;
+  constexpr int TPT = kMaxTiles / 8;
+  double mt[TPT], lt[TPT];
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) {
+    const F32Tile* t = unit_tiles + min(t8 + 8 * k, n_tiles - 1);
+    mt[k] = load_agent(&t->m[row]);
+    lt[k] = load_agent(&t->l[row]);
+  }
+  double m = mt[0];   // a tile that stands in for one past the end changes no maximum
+#pragma unroll
+  for (int k = 1; k < TPT; ++k) m = fmax(m, mt[k]);
+  red[t8][row] = m;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 8; ++k) m = fmax(m, red[k][row]);
+  __syncthreads();
+  double l = 0.0;
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) {
+    mt[k] = t8 + 8 * k < n_tiles ? exp2_double((mt[k] - m) * kLog2e) : 0.0;
+    l = fma(lt[k], mt[k], l);
+  }
+  red[t8][row] = l;
+  __syncthreads();
+  l = 0.0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) l += red[k][row];
+  const double inv = row < n_obs ? 1.0 / l : 0.0;   // unused rows repeat row 0 with weight zero
+#pragma unroll
+  for (int k = 0; k < TPT; ++k)
+    if (t8 + 8 * k < n_tiles) factor[t8 + 8 * k][row] = mt[k] * inv;
+  __syncthreads();
+
+  // ---- keys: importance of rows tid PER .. of the unit, then their rank ----
+  const int j0 = tid * PER;
+  uint32_t key[PER];
+  unsigned in_seg = 0;
+  double imp[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    imp[e] = 0.0;
+    if (j0 + e >= d.sel_lo && j0 + e < d.sel_hi) in_seg |= 1u << e;
+  }
+  if (j0 < T_in) {
+    const F32Tile* t = unit_tiles + j0 / 16;
+    const double* f = factor[j0 / 16];
+    typedef unsigned long long u64;
+#pragma unroll 16
+    for (int r = 0; r < kMaxObs; ++r) {
+#pragma unroll
+      for (int e = 0; e < PER; e += 2) {
+        const u64 x = load_agent(reinterpret_cast<const u64*>(&t->e[r][(j0 & 15) + e]));
+        imp[e] = fma((double)__uint_as_float((unsigned)x), f[r], imp[e]);
+        imp[e + 1] = fma((double)__uint_as_float((unsigned)(x >> 32)), f[r], imp[e + 1]);
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < PER; ++e) key[e] = (in_seg >> e) & 1u ? __float_as_uint((float)imp[e]) : 0u;
+  select_rows<kThreads, PER, 11, 11>(d, key, in_seg, hist, sh, kept_idx + (int64_t)d.unit * idx_stride, seam);
+}
+
+// ---------------------------------------------------------------------------
 // bf16 MFMA path
 // ---------------------------------------------------------------------------
 // C = Q~ K^T per 32-key tile: A operand = Q~ (row = observation query lane%32),
@@ -986,6 +1152,24 @@ void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, con
     if (max_t_in <= 256 && few) HACK_SMALL(128, 8, 1);
     else if (max_t_in <= 256) HACK_SMALL(128, 4, 2);
     else HACK_SMALL(128, 8, 2);
+  }
+#undef HACK_SMALL
+}
+
+void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in, const void* q,
+                             const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache, const void* k_new,
+                             F32Tile* tiles, unsigned* counters, int32_t* kept_idx, int64_t idx_stride, int32_t* seam) {
+  if (n_units <= 0 || max_t_in <= 0) return;
+  const dim3 grid((max_t_in + 63) / 64, n_units);
+#define HACK_SMALL(D_, PER_)                                                                                                     \
+  hipLaunchKernelGGL((score_select_f32<D_, PER_>), grid, dim3(kThreads), 0, s, descs, (const float*)q, q_rows, n_obs, N_k, scale, \
+                     (const float*)k_cache, (const float*)k_new, tiles, counters, kept_idx, idx_stride, seam)
+  if (head_dim == 64) {
+    if (max_t_in <= 512) HACK_SMALL(64, 2);
+    else HACK_SMALL(64, 4);
+  } else {
+    if (max_t_in <= 512) HACK_SMALL(128, 2);
+    else HACK_SMALL(128, 4);
   }
 #undef HACK_SMALL
 }

@@ -604,6 +604,65 @@ def test_short_units_score_and_select_in_one_launch(head_dim, B, sides_n):
     hk.close()
 
 
+@pytest.mark.parametrize("head_dim,B,sides_n", [
+    (64, 1, [5, 30, 6, 7]),              # units of two and three tiles, fewer queries than observation rows
+    (64, 2, [5, 16, 43, 64]),            # the last tile, the last work-group full: 64 and 128 keys
+    (64, 1, [5, 200, 51, 256]),          # exactly 512
+    (64, 1, [5, 200, 52, 256]),          # 513
+    (64, 2, [5, 400, 300, 319]),         # exactly 1024
+    (64, 2, [5, 400, 300, 320]),         # 1025: three launches
+    (128, 1, [5, 40, 33, 178]),
+    (128, 3, [3, 300, 300, 400]),
+])
+def test_short_float32_units_score_and_select_in_one_launch(head_dim, B, sides_n):
+    """hack_step's kept lists of float32 units around tile, work-group and launch sizes, against the single entry points: float32
+    weights are joined by exact factors instead of being formed anew, 2^-24 relative each way, so a row that only one list
+    has lies within 4 x 2^-24 of the weakest row that both keep.  A second pass gives the same lists."""
+    from tests import gpu_util as u
+    H = 8
+    U = B * H
+    hk = u.make_hack(heads=H, head_dim=head_dim, dtype="f32", max_units=U, max_cache_len=sum(sides_n), max_queries=max(sides_n))
+    types = np.array([0, 1] * (H // 2), np.uint8)
+    caps = np.maximum(sum(sides_n[:3]) - 17 * np.arange(U) % 190, 30).astype(np.int32)   # unit 0 keeps everything until the last step
+    mc = hk.managed_cache(np.maximum(caps, sum(sides_n[:2])))
+    scale, stride = float(np.float32(head_dim ** -0.5)), (sum(sides_n) + 63) // 64 * 64
+    lists, first = 0, []
+    for rounds in range(2):
+        gen = torch.Generator(u.DEV)
+        gen.manual_seed(sum(sides_n))
+        mc.reset()
+        for step, n in enumerate(sides_n):
+            q, kn, vn = (torch.randn((B, H, n, head_dim), generator=gen, device=u.DEV) for _ in range(3))
+            q *= 3
+            before = mc.as_cache()
+            src = type(before)(mc.k.clone(), mc.v.clone(), before.off, before.len, mc.pos.clone())
+            budget = np.full(U, 10**6, np.int32) if step < 2 else caps
+            kept = torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV)
+            hk.step(mc, q, kn, vn, types, budget, 5, scale, torch.empty_like(q), kept_idx=kept)
+            if rounds:
+                torch.cuda.synchronize()
+                assert torch.equal(kept, first[step])
+                continue
+            first.append(kept)
+            imp = torch.zeros((U, stride), device=u.DEV)
+            want = torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV)
+            hk.score(q, src, scale, imp, k_new=kn, n_obs=min(32, n))
+            t_in = src.len + n
+            ln = hk.select(B, imp, t_in, types, budget, 5, n, want)
+            torch.cuda.synchronize()
+            for x in range(U):
+                if budget[x] < t_in[x]:
+                    lists += 1
+                    a, b = set(kept[x, :ln[x]].tolist()), set(want[x, :ln[x]].tolist())
+                    assert len(a) == ln[x] and kept[x, :ln[x]].tolist() == sorted(a) and max(a) < t_in[x], (step, x)
+                    odd = imp[x][sorted(a ^ b)].double()
+                    assert odd.numel() == 0 or float(odd.max() / odd.min()) < 1 + 4 * 2.0 ** -24 * 2, (step, x)
+    assert lists > U // 2
+    hk.check()
+    mc.close()
+    hk.close()
+
+
 def test_step_capacity_and_argument_errors():
     u = _u()
     from paper_2504_09261_amd.binding import HackError
