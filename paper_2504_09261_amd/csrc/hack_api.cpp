@@ -1186,8 +1186,9 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->n_stream = plan.n_groups;
   Table t;
   g->o_desc = t.add(u.descs.data(), u.descs.size());
-  std::vector<UnitDesc> comp;   // the compressing units' descriptors, together
+  std::vector<UnitDesc> comp;   // the compressing units' descriptors, together, then the others'
   for (const int32_t i : u.comp) comp.push_back(u.descs[i]);
+  for (const UnitDesc& d : u.descs) if (d.mode != MOVE_GATHER) comp.push_back(d);
   g->o_comp = t.add(comp.data(), comp.size());
   g->o_merge = t.add(u.merging.data(), u.merging.size());
   g->o_rows = t.add(rows, kMaxObs);
@@ -1202,9 +1203,15 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
 // score -> select -> append / gather (-> merge) of a group's units
 void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
   const UnitDesc* comp_dev = reinterpret_cast<const UnitDesc*>(g.dev + g.o_comp);
+  bool moves = !a.in_place || (!n.fuse_append && !g.gathered);   // rows move in front of the attention launch
   if (g.n_comp > 0 && g.small && ctx->cfg.dtype == HACK_F32) {
     launch_score_select_f32(s, ctx->cfg.head_dim, comp_dev, g.n_comp, g.max_t, a.q, reinterpret_cast<const int32_t*>(g.dev + g.o_rows),
                             n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->f32_tiles, ctx->counters, a.kept, a.kstride, ctx->seam);
+  } else if (g.n_comp > 0 && g.small && moves && launch_score_select_move != nullptr) {
+    launch_score_select_move(s, ctx->cfg.head_dim, comp_dev, g.n_comp, comp_dev + g.n_comp, g.n_desc - g.n_comp, g.max_t, a.q,
+                             reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp, a.k_new, a.v_new, a.pos_new,
+                             a.kept, a.kstride, ctx->fault);
+    moves = false;
   } else if (g.n_comp > 0 && g.small) {
     launch_score_select(s, ctx->cfg.head_dim, comp_dev, nullptr, g.n_comp, g.max_t, a.q,
                         reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, a.kept, a.kstride,
@@ -1216,7 +1223,7 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
               ctx->ws_stride);
     launch_select(s, comp_dev, nullptr, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
   }
-  if (!a.in_place || (!n.fuse_append && !g.gathered))
+  if (moves)
     launch_move(s, ctx->elem_bytes, ctx->cfg.head_dim, g.ddev(), g.n_desc, g.max_rows, a.cp, a.cp, a.k_new, a.v_new, n.N_k,
                 a.pos_new, a.kept, a.kstride);
   if (g.n_merge > 0)   // compression, the merge included, precedes the attention of the step

@@ -191,6 +191,14 @@ void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, con
                          const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
                          const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault);
 
+// The same, and the rows of the step moved to where the next step expects them: the kept ones of the n_units compressing units,
+// all new ones of the n_append others (launch_move's work).  Weak as launch_score_select_f32.
+__attribute__((weak)) void launch_score_select_move(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units,
+                                                    const UnitDesc* append_descs, int n_append, int max_t_in, const void* q,
+                                                    const int32_t* q_rows, int n_obs, int N_k, float scale, CachePtrs cache,
+                                                    const void* k_new, const void* v_new, int pos_new, int32_t* kept_idx,
+                                                    int64_t idx_stride, int* fault);
+
 // Budgeted selection; one work-group per listed unit.  seam[unit id] (or NULL) gets the number of
 // kept rows below len_in; every unit must then have new rows.
 void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list,

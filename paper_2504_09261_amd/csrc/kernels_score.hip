@@ -787,12 +787,62 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
 // are those of score_fused up to the order in which the row sums are added in fp64.  Latency bounds these launches: a
 // score launch, whose work-groups wait for each other through L2, and a selection launch behind it take 8 + 4.4 us (kernel trace) at
 // 60 units of 46 to 475 keys (one 256^2 image: 108.6 -> 100.6 us, 960 units 349 -> 318).
-template <int D, int NW, int TILES>
+// MOVE: the work-group also moves the rows that it keeps, and further work-groups append the new rows of the n_append units
+// that keep everything (append_descs), in place of a launch of move_kernel behind this one: its copies run beside other
+// work-groups' arithmetic, and nobody reads the list back.  Schedules whose last step compresses, us, two launches / one: 128 units of 500
+// keys 40.8 / 38.2 (half of them compressing 42.9 / 39.5), 256 of 240 33.5 / 29.7, 512 of 1000 181 / 179; head_dim 128, 128 of 250 38.9 / 35.8, 256 of
+// 500 84 / 80; 60 units of 1000 45.6 / 45.7; a batch of 32 256^2 images (960 units, three such steps) 307.6 / 295.
+struct StepMove {
+  const UnitDesc* append_descs;
+  CachePtrs cache;
+  const __bf16* v_new;
+  int pos_new;
+};
+
+// Rows of K, V and position ids of one unit to where the next step expects them, by a work-group of THREADS: rows list[i] (LDS) of
+// [cached | new] behind out_off, or, list NULL, all new rows behind the cached ones.
+template <int D, int THREADS>
+__device__ __forceinline__ void move_unit(const UnitDesc& d, const uint32_t* list, const __bf16* k_new, const StepMove& mv, int N_k) {
+  constexpr int LPR = D / 8, RPP = THREADS / LPR, BATCH = 4;   // lanes per row, rows per pass, passes in flight
+  const int lane = threadIdx.x % LPR;
+  const int n_rows = list ? d.n_out : d.n_new;
+  const int64_t dst0 = list ? d.out_off : d.in_off + d.len_in, new0 = (int64_t)d.unit * N_k;
+  for (int i0 = threadIdx.x / LPR; i0 < n_rows; i0 += BATCH * RPP) {
+    uintx4 kr[BATCH], vr[BATCH];
+    int pos[BATCH];
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) {
+      const int i = min(i0 + b * RPP, n_rows - 1);
+      const int s = list ? (int)list[i] : d.len_in + i;
+      const bool cached = s < d.len_in;
+      const int64_t row = cached ? d.in_off + s : new0 + (s - d.len_in);
+      kr[b] = (cached ? static_cast<const uintx4*>(mv.cache.k) : reinterpret_cast<const uintx4*>(k_new))[row * LPR + lane];
+      vr[b] = (cached ? static_cast<const uintx4*>(mv.cache.v) : reinterpret_cast<const uintx4*>(mv.v_new))[row * LPR + lane];
+      pos[b] = mv.pos_new + (s - d.len_in);
+      if (cached && mv.cache.pos != nullptr) pos[b] = mv.cache.pos[row];
+    }
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) {
+      const int i = i0 + b * RPP;
+      if (i < n_rows) {
+        static_cast<uintx4*>(mv.cache.k)[(dst0 + i) * LPR + lane] = kr[b];
+        static_cast<uintx4*>(mv.cache.v)[(dst0 + i) * LPR + lane] = vr[b];
+        if (mv.cache.pos != nullptr && lane == 0) mv.cache.pos[dst0 + i] = pos[b];
+      }
+    }
+  }
+}
+
+template <int D, int NW, int TILES, bool MOVE>
 __global__ __launch_bounds__(64 * NW) void score_select(
     const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, const __bf16* __restrict__ q,
     const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale, const __bf16* __restrict__ k_cache,
     const __bf16* __restrict__ k_new, int32_t* __restrict__ kept_idx, int64_t idx_stride, int32_t* __restrict__ seam,
-    int* __restrict__ fault) {
+    int* __restrict__ fault, int n_units, StepMove mv) {
+  if (MOVE && (int)blockIdx.x >= n_units) {
+    move_unit<D, 64 * NW>(mv.append_descs[blockIdx.x - n_units], nullptr, k_new, mv, N_k);
+    return;
+  }
   constexpr int KK = D / 16, CPR = D / 8, RPI = 64 / CPR, IPT = 32 / RPI, TILE = 32 * D;   // as in score_fused
   constexpr int kBufs = 8192 / (TILE * 2);   // tile buffers per wave: the row sums need 8 KiB
   using Shared = SelectShared<64 * NW, 11, 11>;
@@ -944,7 +994,11 @@ __global__ __launch_bounds__(64 * NW) void score_select(
   const unsigned in_seg = tid >= d.sel_lo && tid < d.sel_hi ? 1u : 0u;
   if (in_seg) key[0] = keys[tid];
   select_rows<64 * NW, 1, 11, 11>(d, key, in_seg, reinterpret_cast<uint32_t*>(&bufs[0][0]), sh,
-                                  kept_idx + (int64_t)d.unit * idx_stride, seam);
+                                  kept_idx + (int64_t)d.unit * idx_stride, seam, MOVE ? keys : nullptr);
+  if constexpr (MOVE) {
+    __syncthreads();
+    move_unit<D, 64 * NW>(d, keys, k_new, mv, N_k);
+  }
 }
 
 template <int D, int TPW>
@@ -1133,13 +1187,16 @@ bool use_score_select(int head_dim, int n_units, int max_t_in) {
   return max_t_in <= 256 || (max_t_in <= 512 && n_units <= 256);
 }
 
-void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,
+template <bool MOVE>
+static void launch_small(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,
                          const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
-                         const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault) {
+                         const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault, int n_append,
+                         const StepMove& mv) {
   if (n_list <= 0) return;
 #define HACK_SMALL(D_, NW_, TILES_)                                                                                          \
-  hipLaunchKernelGGL((score_select<D_, NW_, TILES_>), dim3(n_list), dim3(64 * NW_), 0, s, descs, list, (const __bf16*)q, q_rows, n_obs, \
-                     N_k, scale, (const __bf16*)k_cache, (const __bf16*)k_new, kept_idx, idx_stride, seam, fault)
+  hipLaunchKernelGGL((score_select<D_, NW_, TILES_, MOVE>), dim3(n_list + n_append), dim3(64 * NW_), 0, s, descs, list, \
+                     (const __bf16*)q, q_rows, n_obs, N_k, scale, (const __bf16*)k_cache, (const __bf16*)k_new, kept_idx, idx_stride, seam, \
+                     fault, n_list, mv)
   // one tile a wave while every unit has a compute unit to itself: 30 units of 155 keys 7.6 -> 7.1 us (kernel trace); sixteen waves of
   // one tile lose (60 units of 420 keys 9.2 -> 10.2)
   const bool few = n_list <= 256;
@@ -1154,6 +1211,20 @@ void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, con
     else HACK_SMALL(128, 8, 2);
   }
 #undef HACK_SMALL
+}
+
+void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,
+                         const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
+                         const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault) {
+  launch_small<false>(s, head_dim, descs, list, n_list, max_t_in, q, q_rows, n_obs, N_k, scale, k_cache, k_new, kept_idx, idx_stride,
+                      seam, fault, 0, StepMove{});
+}
+
+void launch_score_select_move(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, const UnitDesc* append_descs, int n_append,
+                              int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, CachePtrs cache,
+                              const void* k_new, const void* v_new, int pos_new, int32_t* kept_idx, int64_t idx_stride, int* fault) {
+  launch_small<true>(s, head_dim, descs, nullptr, n_units, max_t_in, q, q_rows, n_obs, N_k, scale, cache.k, k_new, kept_idx, idx_stride,
+                     nullptr, fault, n_append, StepMove{append_descs, cache, (const __bf16*)v_new, pos_new});
 }
 
 void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in, const void* q,

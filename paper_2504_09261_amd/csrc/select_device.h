@@ -59,10 +59,12 @@ struct SelectShared {
 
 // The work-group (NT threads) writes the kept rows of d to out in ascending order.  Thread tid holds the keys of the PER
 // rows from tid * PER on: float bits where in_seg says that the row is ranked.  Digits of B0, B1 and 32 - B0 - B1 bits;
-// hist: SelectShared::kHist words of LDS.
+// hist: SelectShared::kHist words of LDS; kept_lds, if given, gets the list as well (words nobody reads any more once a barrier
+// has been passed).
 template <int NT, int PER, int B0, int B1>
 __device__ __forceinline__ void select_rows(const UnitDesc& d, uint32_t (&key)[PER], unsigned in_seg, uint32_t* hist,
-                                            SelectShared<NT, B0, B1>& sh, int32_t* __restrict__ out, int32_t* __restrict__ seam) {
+                                            SelectShared<NT, B0, B1>& sh, int32_t* __restrict__ out, int32_t* __restrict__ seam,
+                                            uint32_t* kept_lds = nullptr) {
   constexpr int kWaves = NT / 64;
   constexpr int B2 = 32 - B0 - B1;
   constexpr int kHist = SelectShared<NT, B0, B1>::kHist;
@@ -155,7 +157,10 @@ __device__ __forceinline__ void select_rows(const UnitDesc& d, uint32_t (&key)[P
   if (seam != nullptr && d.len_in >= j0 && d.len_in < j0 + PER) seam[d.unit] = pos + __popc(keep & ((1u << (d.len_in - j0)) - 1u));
 #pragma unroll
   for (int e = 0; e < PER; ++e)
-    if ((keep >> e) & 1u) out[pos++] = j0 + e;
+    if ((keep >> e) & 1u) {
+      if (kept_lds != nullptr) kept_lds[pos] = (uint32_t)(j0 + e);
+      out[pos++] = j0 + e;
+    }
 }
 
 }  // namespace dev

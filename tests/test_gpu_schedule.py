@@ -663,6 +663,50 @@ def test_short_float32_units_score_and_select_in_one_launch(head_dim, B, sides_n
     hk.close()
 
 
+@pytest.mark.parametrize("head_dim,sides_n", [
+    (64, [3, 70, 60, 1]), (64, [5, 200, 51, 256]), (64, [9, 500, 100, 415]), (128, [3, 70, 31, 152]), (128, [3, 210, 97, 202]),
+])
+@pytest.mark.parametrize("with_pos", [True, False])
+def test_short_units_move_their_rows_in_the_score_launch(head_dim, sides_n, with_pos):
+    """Steps whose attention reads the cache (128-query work items): kept rows, appended rows and position ids are copies of the
+    listed ones, in units that compress (from one row to all but one) beside units that keep everything."""
+    from tests import gpu_util as u
+    H, B, T = 8, 16 if sum(sides_n) > 512 else 2, sum(sides_n)
+    U = B * H
+    hk = u.make_hack(heads=H, head_dim=head_dim, dtype="bf16", max_units=U, max_cache_len=T, max_queries=max(sides_n), attention="tile128")
+    types = np.array([0, 1] * (H // 2), np.uint8)
+    budget = np.full(U, 10**6, np.int32)
+    budget[1::2] = np.linspace(1, T - 1, len(budget[1::2])).astype(np.int32)
+    mc = hk.managed_cache(np.minimum(np.maximum(budget, sum(sides_n[:2])), T), with_pos=with_pos)
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(T)
+    scale, stride, ids = float(np.float32(head_dim ** -0.5)), (T + 63) // 64 * 64, 0
+    for step, n in enumerate(sides_n):
+        q, kn, vn = (torch.randn((B, H, n, head_dim), generator=gen, device=u.DEV).to(torch.bfloat16) for _ in range(3))
+        off0, len0 = mc.view()
+        k0, v0 = mc.k.clone(), mc.v.clone()
+        p0 = mc.pos.clone() if with_pos else None
+        kept = torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV)
+        now = np.full_like(budget, 10**6) if step < 2 else budget
+        hk.step(mc, q, kn, vn, types, now, 5, scale, torch.empty_like(q), kept_idx=kept)
+        torch.cuda.synchronize()
+        off, ln = mc.view()
+        for x in range(U):
+            b, h = divmod(x, H)
+            o0, l0, t = int(off0[x]), int(len0[x]), int(len0[x]) + n
+            rows = kept[x, :ln[x]].long() if now[x] < t else torch.arange(t, device=u.DEV)
+            assert ln[x] == min(int(now[x]), t) and bool((rows[1:] > rows[:-1]).all()) and 0 <= int(rows[0]) and int(rows[-1]) < t
+            for got, old, new in ((mc.k, k0, kn), (mc.v, v0, vn)):
+                assert torch.equal(got[off[x]:off[x] + ln[x]], torch.cat([old[o0:o0 + l0], new[b, h]])[rows]), (step, x)
+            if with_pos:
+                src = torch.cat([p0[o0:o0 + l0], torch.arange(ids, ids + n, dtype=torch.int32, device=u.DEV)])
+                assert torch.equal(mc.pos[off[x]:off[x] + ln[x]], src[rows]), (step, x)
+        ids += n
+    hk.check()
+    mc.close()
+    hk.close()
+
+
 def test_step_capacity_and_argument_errors():
     u = _u()
     from paper_2504_09261_amd.binding import HackError
