@@ -290,4 +290,62 @@ inline bool plan_attn_cuts(const std::vector<AttnLaneItem> (&lanes)[kAttnXcds], 
   return true;
 }
 
+// ---- cutting the last round of a launch of equal work items ------------------------------------
+// Work items of one length leave the device in rounds: an XCD that holds `slots` work-groups and has q * slots + r of them ends with
+// r items on its own compute units, each at the pace of a lone work-group (the longest items of a launch come first, so items of
+// different lengths even this out by themselves, and cutting them measured slower).  The r last items are cut into as many
+// pieces as give every compute unit of the XCD at most one, four at most: the parts of an item are added up one after the other.
+// Measured (head_dim 128, 32 compute units an XCD), us a launch, whole / 2 / 3 / 4 pieces: 72 items an XCD of 50, 100, 200 blocks 88 / 80 / 77 / 77,
+// 151 / 134 / 129 / 129, 287 / 246 / 235 / 229; of 25 blocks 50.3 / 49.5 / 49.3 / 50.1; 68 of 200 280 / 237 / 225 / 220; 80 of 50 and 200 88 / 82 / 90 / 90,
+// 287 / 255 / 266 / 258; 84 of 100 160 / 160 / 151 / 157; 136 of 100 247 / 231 / 226 / 224; 200 of 100 339 / 322 / 315 / 312.
+constexpr int kTailMinBlocks = 40;
+constexpr int kTailMaxPieces = 4;
+
+// lanes[x]: the work items of XCD x (work-group id % 8 == x), longest first.  Fills *plan (one segment per work-group) and returns
+// true if the longest lane ends with a round that is to be cut.
+inline bool plan_attn_tail(const std::vector<AttnLaneItem> (&lanes)[kAttnXcds], int cus_per_xcd, AttnStreamPlan* plan) {
+  const int slots = 2 * cus_per_xcd;
+  int most = 0, longest = 0, shortest = 0x7fffffff;
+  for (const auto& l : lanes) {
+    most = std::max(most, (int)l.size());
+    for (const AttnLaneItem& it : l) {
+      longest = std::max(longest, it.n_blocks);
+      shortest = std::min(shortest, it.n_blocks);
+    }
+  }
+  auto pieces = [&](int items) {   // of each of the items % slots last items of a lane
+    const int r = items % slots;
+    return items > slots && r > 0 ? std::min(kTailMaxPieces, cus_per_xcd / r) : 1;
+  };
+  if (slots <= 0 || longest < kTailMinBlocks || longest - shortest > longest / 16 || pieces(most) < 2) return false;
+  plan->segs.clear();
+  plan->n_parts = plan->n_counters = 0;
+  std::vector<AttnSeg> out[kAttnXcds];
+  size_t rows = 0;
+  for (int x = 0; x < kAttnXcds; ++x) {
+    const int n = (int)lanes[x].size(), P = pieces(n);
+    for (int i = 0; i < n; ++i) {
+      const AttnLaneItem& it = lanes[x][i];
+      if (P < 2 || i < n - n % slots) {
+        out[x].push_back(AttnSeg{it.desc, it.q_tile, 0, 0x3fffffff, -1, 0, 0, 0});
+        continue;
+      }
+      for (int p = 0; p < P; ++p)
+        out[x].push_back(AttnSeg{it.desc, it.q_tile, it.n_blocks * p / P, it.n_blocks * (p + 1) / P, plan->n_parts + p, plan->n_parts, P,
+                                 plan->n_counters});
+      plan->n_parts += P;
+      plan->n_counters += 1;
+    }
+    rows = std::max(rows, out[x].size());
+  }
+  plan->seg_begin.assign(1, 0);
+  for (size_t r = 0; r < rows; ++r)
+    for (int x = 0; x < kAttnXcds; ++x) {
+      if (r < out[x].size()) plan->segs.push_back(out[x][r]);
+      plan->seg_begin.push_back((int32_t)plan->segs.size());
+    }
+  plan->n_groups = (int)rows * kAttnXcds;
+  return true;
+}
+
 }  // namespace hack

@@ -408,8 +408,9 @@ int attn_tile_rows(const hack_ctx* ctx, int n_units, int N_k) {
 // kCutMinGain.  On the 1024^2 benchmark workloads this fires at scale step 11 with 16 heads x batch 2 (416 work
 // items on 256 compute units: the long items that would share a compute unit with another long one are
 // halved; 113.7 -> 98.8 us measured, 111.8 -> 89.3 modelled) and at step 9 with 32 heads x batch 2 (50.3 ->
-// 42.8 us measured, 45.3 -> 35.0 modelled); launches with more work items than resident work-groups are
-// left alone (there the model is 10-15 % off).  HACK_ATTN_STREAM=0 switches it off, =4 applies every cut
+// 42.8 us measured, 45.3 -> 35.0 modelled).  Launches with more work items than resident work-groups are
+// left alone (there the model is 10-15 % off), unless all items are of one length and a few of them make up a last round
+// (plan_attn_tail: the whole cache of a 1024^2 image, scale step 12, 285 -> 237 us).  HACK_ATTN_STREAM=0 switches it off, =4 applies every cut
 // the model likes (tests).
 constexpr AttnPairModel kPairModel128{0.55, 0.75, 1.0, 4.0, 14.0};   // us per key block alone / first / second of a pair; fixed costs in blocks
 constexpr double kCutMinGain = 0.05;
@@ -450,7 +451,8 @@ bool use_stream_attention(const hack_ctx* ctx, const std::vector<UnitDesc>& desc
       if (items[i].desc >= 0)
         lanes[i % kAttnXcds].push_back(AttnLaneItem{items[i].desc, items[i].q_tile, (items[i].n_out + kAttnKeyBlock - 1) / kAttnKeyBlock});
     double before = 0.0, after = 0.0;
-    if (!plan_attn_cuts(lanes, cus / kAttnXcds, kCutMinBlocks, kPairModel128, forced ? 1e-9 : kCutMinGain, plan, &before, &after)) return false;
+    if (!(!forced && plan_attn_tail(lanes, cus / kAttnXcds, plan)) &&
+        !plan_attn_cuts(lanes, cus / kAttnXcds, kCutMinBlocks, kPairModel128, forced ? 1e-9 : kCutMinGain, plan, &before, &after)) return false;
     return plan->n_groups > 0 && plan->n_parts <= 2 * ctx->attn_slots && plan->n_counters <= ctx->attn_slots;
   }
   plan_attn_stream(n_keys.data(), (int)descs.size(), (N_k + tile - 1) / tile, ctx->attn_slots, kStreamOverheadBlocks,

@@ -599,6 +599,35 @@ def test_attention_with_the_keys_in_two_halves(forced, H, Nk, lens, monkeypatch)
     hk.close()
 
 
+@pytest.mark.parametrize("tiles,T", [(65, 1541), (72, 1280), (73, 1249), (80, 1300), (129, 1281), (81, 1300)])
+def test_last_round_of_equal_work_items_in_pieces(tiles, T):
+    """Eight units of one length whose work items fill the device once or twice and leave 1, 8, 9, 16, 1 (cut in four, four, three, two,
+    four) or 17 (left whole) an XCD: against whole work items, and every launch with the bits of the first."""
+    u = _u()
+    H, d, Nk = 8, 128, tiles * 128 - 5
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(tiles)
+    q = torch.randn((1, H, Nk, d), generator=gen, device=u.DEV).bfloat16()
+    stride = (T + 7) // 8 * 8
+    K, V = (torch.randn((H * stride, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    kv = Cache(K, V, np.arange(H, dtype=np.int64) * stride, np.full(H, T, np.int32))
+    scale = float(np.float32(d ** -0.5))
+    outs = {}
+    for name in (None, "tile128"):
+        hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=T, max_queries=Nk, attention=name)
+        out = torch.full_like(q, 7.0)
+        hk.attn(q, kv, scale, out)
+        for _ in range(5):
+            again = torch.full_like(q, 7.0)
+            hk.attn(q, kv, scale, again)
+            assert torch.equal(out, again)
+        outs[name] = out.float()
+        hk.close()
+    # both round P and O to bf16
+    assert float((outs[None] - outs["tile128"]).abs().max()) < 1e-2
+    assert torch.equal(outs[None], outs["tile128"]) == (tiles == 81)
+
+
 def test_attention_rejects_empty_unit_and_bad_scale():
     u = _u()
     hk = u.make_hack(heads=1, head_dim=64, dtype="bf16", max_units=1, max_cache_len=64, max_queries=8)
