@@ -1,4 +1,5 @@
-"""Thin ctypes binding over the C ABI of include/hack.h.
+"""Thin binding over the C ABI of include/hack.h: ctypes, and for hack_step, which an image calls layers x scales
+times, a CPython entry of its own (csrc/py_step.cpp).
 
 Argument marshalling only: every step of the path runs in the HIP kernels of
 libhack_mi355x.so.  PyTorch is used for device memory and the current stream.
@@ -51,12 +52,13 @@ class _raw_cache(C.Structure):
 
 
 _lib = None
+_step_call = _step_addr = None    # CPython entry; addresses of hack_step and hack_step_final
 
 
 def load_library() -> C.CDLL:
     """dlopen the in-tree library; torch is imported first so that both use the
     same HIP runtime."""
-    global _lib
+    global _lib, _step_call, _step_addr
     if _lib is not None:
         return _lib
     import torch  # noqa: F401  (loads libamdhip64 with the soname the library needs)
@@ -64,7 +66,13 @@ def load_library() -> C.CDLL:
         raise FileNotFoundError(
             f"{LIB_PATH} is missing: build it with `python -m paper_2504_09261_amd.build` "
             "(there is no fallback path)")
+    try:
+        from paper_2504_09261_amd._step_call import step as _step_call
+    except ImportError as e:
+        raise FileNotFoundError(f"the step entry beside {LIB_PATH} is missing: build it with "
+                                "`python -m paper_2504_09261_amd.build` (there is no fallback path)") from e
     lib = C.CDLL(LIB_PATH)
+    _step_addr = tuple(C.cast(f, C.c_void_p).value for f in (lib.hack_step, lib.hack_step_final))
     vp, i32, i64, f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
     pi32, pi64, pu8 = C.POINTER(C.c_int32), C.POINTER(C.c_int64), C.POINTER(C.c_uint8)
     pcache = C.POINTER(hack_cache)
@@ -335,9 +343,10 @@ class Hack:
     def step(self, cache: ManagedCache, q, k_new, v_new, head_type, budget, n_init: int, scale: float, out,
              kept_idx=None, final: bool = False):
         """final=True: hack_step_final (the last scale step; contextual units merge what they discard)."""
-        B, H, Nk, d = q.shape
-        ht, bud = _u8(head_type), _i32(budget)
-        fn = self.lib.hack_step_final if final else self.lib.hack_step
-        self._check(fn(self.ctx, cache.handle, B, Nk, _dev(q), _dev(k_new), _dev(v_new),
-                                       _p(ht, C.c_uint8), _p(bud, C.c_int32), n_init, scale, _dev(out),
-                                       _dev(kept_idx), 0 if kept_idx is None else kept_idx.stride(0), _stream()))
+        fn, kstride = _step_addr[1 if final else 0], 0 if kept_idx is None else kept_idx.stride(0)
+        ctx, handle, stream = self.ctx and self.ctx.value, cache.handle and cache.handle.value, _stream()
+        st = _step_call(fn, ctx, handle, q, k_new, v_new, head_type, budget, n_init, scale, out, kept_idx, kstride, stream)
+        if st is None:
+            st = _step_call(fn, ctx, handle, q, k_new, v_new, _u8(head_type), _i32(budget), n_init, scale, out, kept_idx, kstride, stream)
+        if st != 0:
+            self._check(st)

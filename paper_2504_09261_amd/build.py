@@ -4,12 +4,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_NAME = "libhack_mi355x.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
+STEP_CALL_PATH = os.path.join(HERE, "_step_call.so")   # CPython entry to hack_step
 SOURCES = ["hack_api.cpp", "kernels_move.hip", "kernels_select.hip", "kernels_score.hip", "kernels_attn.hip", "kernels_attn_split.hip", "kernels_attn_f32.hip",
            "kernels_headvar.hip", "kernels_merge.hip"]
 
@@ -41,7 +43,7 @@ def _compile(src: str, objdir: str, extra) -> str:
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every source for gfx950 and link libhack_mi355x.so next to this file."""
+    """Compile every source for gfx950, link libhack_mi355x.so and the CPython step entry next to this file."""
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
@@ -52,6 +54,13 @@ def build(verbose: bool = False, extra_flags=()) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, LIB_PATH)
+    tmp = STEP_CALL_PATH + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "py_step.cpp"), "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for py_step.cpp:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, STEP_CALL_PATH)
     if verbose:
         print(f"built {LIB_PATH}")
     return LIB_PATH
