@@ -29,6 +29,8 @@
 // the way through the list, and beside matrix work that already draws all the power the
 // chip may take, the moving work-groups cost what they cost alone (1024^2 schedules
 // 784 / 1267 / 3326 us as separate launches, 763 / 1254 / 3355 fused).
+#include <type_traits>
+
 #include "device_util.h"
 #include "hack_internal.h"
 
@@ -93,8 +95,9 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
   // plus loop-invariant lane offsets.  The ragged last block and a block that
   // straddles the two sources take per-lane addresses (rows past the end repeat
   // the last key; their scores are masked): a uniform row of either source plus 32
-  // bits.  Formed from 64-bit row numbers they stood 1 us in front of the first
-  // scales' only block (head_dim 128, four steps of 32 units 25.2 -> 23.8 us).
+  // bits.  The first scales' only block is ragged: formed from 64-bit row numbers those addresses stood 1 us in front of it
+  // (head_dim 128, four steps of 32 units 25.2 -> 23.8 us), and copying 32 rows where there are 1 to 21 half a microsecond
+  // (with a one-block unit stored straight from its wave's registers 24.0 -> 23.3; one 256^2 image 91.3 -> 90.3).
   const unsigned vs_lds = lds_addr_of(&Vs[0][0][0]);
   unsigned k_src[IPB], v_src[IPB];
 #pragma unroll
@@ -104,11 +107,9 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     v_src[i] = (unsigned)(r * D + ((c ^ swz_v<D>(r)) & (CPR - 1)) * 8) * 2u;
   }
   const unsigned k_lds = vs_lds + (unsigned)((w * 2 + 0) * BLK * 2), v_lds = vs_lds + (unsigned)((w * 2 + 1) * BLK * 2);
-  auto issue = [&](int b, const __bf16* cache, const __bf16* fresh, const unsigned (&src)[IPB], unsigned lds) {
+  auto issue = [&](auto k_tag, bool first, int b, const __bf16* cache, const __bf16* fresh, const unsigned (&src)[IPB], unsigned lds) {
+    constexpr bool IS_K = decltype(k_tag)::value;
     const int j0 = b * kKB;
-    const __bf16* const in_cache = cache + (base + j0) * D;              // row j0 of the unit, were it cached
-    const __bf16* const in_fresh = fresh + (new_row0 + (j0 - len_c)) * D;   // ... or a new one
-    const int last = total - 1 - j0;
     const __bf16* blk = nullptr;
     if (j0 + kKB <= len_c) blk = cache + (base + j0) * D;
     else if (j0 >= len_c && j0 + kKB <= total) blk = fresh + (new_row0 + (j0 - len_c)) * D;
@@ -116,11 +117,22 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
 #pragma unroll
       for (int i = 0; i < IPB; ++i) load_to_lds(blk, src[i], lds + (unsigned)(i * 1024));
     } else {
-#pragma unroll
-      for (int i = 0; i < IPB; ++i) {
-        const int r = min(i * RPI + lane / CPR, last);
-        load_to_lds(reinterpret_cast<const char*>(j0 + r < len_c ? in_cache : in_fresh) + ((unsigned)(r * (D * 2)) | (src[i] & (D * 2 - 1))),
-                    lds + (unsigned)(i * 1024));
+      const __bf16* const in_cache = cache + (base + j0) * D;                 // row j0 of the unit, were it cached
+      const __bf16* const in_fresh = fresh + (new_row0 + (j0 - len_c)) * D;   // ... or a new one
+      const int last = total - 1 - j0;
+      // The loop below counts a block's copies in flight.  In front of it only the rows there are travel; what the K slot holds
+      // behind them is masked, and the V slot is cleared.
+      const int n = first ? min(IPB, last / RPI + 1) : IPB;
+#pragma unroll 1
+      for (int i = 0; i < n; ++i) {
+        const int r = i * RPI + lane / CPR, rc = min(r, last);
+        const unsigned off = (unsigned)(rc * D + (((lane % CPR) ^ (IS_K ? swz_k<D>(r) : swz_v<D>(r))) & (CPR - 1)) * 8) * 2u;
+        load_to_lds(reinterpret_cast<const char*>(j0 + rc < len_c ? in_cache : in_fresh) + off, lds + (unsigned)(i * 1024));
+      }
+      if (!IS_K) {
+        uintx4* slot = reinterpret_cast<uintx4*>(&Vs[w][1][0]) + lane;
+#pragma unroll 1
+        for (int i = n; i < IPB; ++i) slot[i * 64] = uintx4{0u, 0u, 0u, 0u};
       }
     }
   };
@@ -159,17 +171,17 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
       }
     }
   };
-  auto issue_k = [&](int b) {
+  auto issue_k = [&](int b, bool first = false) {
     if constexpr (GATHER) {
       issue_x(b + 2 * kWaves);
       issue_rows(b, kc, kn, k_src, k_lds);
     } else {
-      issue(b, k_cache, k_new, k_src, k_lds);
+      issue(std::true_type{}, first, b, k_cache, k_new, k_src, k_lds);
     }
   };
-  auto issue_v = [&](int b) {
+  auto issue_v = [&](int b, bool first = false) {
     if constexpr (GATHER) issue_rows(b, vc, vn, v_src, v_lds);
-    else issue(b, v_cache, v_new, v_src, v_lds);
+    else issue(std::false_type{}, first, b, v_cache, v_new, v_src, v_lds);
   };
 
   if (w < n_blocks) {
@@ -178,8 +190,8 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
       issue_x(w + kWaves);
       dma_wait_but<0>();
     }
-    issue_k(w);
-    issue_v(w);
+    issue_k(w, true);
+    issue_v(w, true);
   }
 
   // Cache update of this tile's rows: loaded behind the first K and V blocks, stored when the loop is done (stored at
@@ -265,10 +277,12 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     if (__any(m_new != m_run)) {
       const float a = __builtin_amdgcn_exp2f((m_run - m_new) * c2);   // first block: exp2(-inf) = 0
       l_run *= a;
+      if (b != w) {   // nothing has been added up in front of the first block
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[mb][r] *= a;
+          for (int r = 0; r < 16; ++r) o[mb][r] *= a;
+      }
       m_run = m_new;
     }
     const float mc = m_run * c2;
@@ -307,38 +321,57 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     if (more) issue_v(b + kWaves);
   }
   dma_wait_but<0>();   // nothing is outstanding when the slots are reused below
-  if (!GATHER && fuse) {
-    uintx4* kd = reinterpret_cast<uintx4*>(k_app) + (d.in_off + d.len_in + q0) * LPR;
-    uintx4* vd = reinterpret_cast<uintx4*>(v_app) + (d.in_off + d.len_in + q0) * LPR;
+  auto append = [&] {
+    if (!GATHER && fuse) {
+      uintx4* kd = reinterpret_cast<uintx4*>(k_app) + (d.in_off + d.len_in + q0) * LPR;
+      uintx4* vd = reinterpret_cast<uintx4*>(v_app) + (d.in_off + d.len_in + q0) * LPR;
 #pragma unroll
-    for (int i = 0; i < APP; ++i) {
-      const int e = tid + i * 64 * kWaves;
-      if (e < n_app) {
-        kd[e] = app_k[i];
-        vd[e] = app_v[i];
+      for (int i = 0; i < APP; ++i) {
+        const int e = tid + i * 64 * kWaves;
+        if (e < n_app) {
+          kd[e] = app_k[i];
+          vd[e] = app_v[i];
+        }
       }
+      if (pos_app != nullptr && tid < n_app / LPR) pos_app[d.in_off + d.len_in + q0 + tid] = pos_new + q0 + tid;
     }
-    if (pos_app != nullptr && tid < n_app / LPR) pos_app[d.in_off + d.len_in + q0 + tid] = pos_new + q0 + tid;
+  };
+  const int qi = q0 + col;
+  __bf16* orow = out + (new_row0 + min(qi, N_k - 1)) * D;
+
+  // A unit of one block (the first scales): wave 0 holds the whole result.
+  if (n_blocks == 1) {
+    if (w == 0) {
+      const float inv = 1.f / pair_sum(l_run);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          bf16x4 pk;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pk[i] = (__bf16)(o[mb][4 * r4 + i] * inv);
+          if (qi < N_k) *reinterpret_cast<bf16x4*>(orow + 32 * mb + 8 * r4 + 4 * half) = pk;
+        }
+    }
+    append();
+    return;
   }
+  append();
 
   // ---- merge the partial results ----
   // This wave's copies have all landed and its LDS reads are done: its two slots
   // become its O^T partial, four registers of a lane together, lanes contiguous (b128 accesses, a quarter of the
   // instructions of a register at a time).
-  // A unit of one block has one partial result (the first scales).
-  const bool alone = n_blocks == 1;
-  if (!alone || w == 0) {
-    l_run = pair_sum(l_run);
-    float4* mine = reinterpret_cast<float4*>(&Vs[w][0][0]) + lane;
+  l_run = pair_sum(l_run);
+  float4* mine = reinterpret_cast<float4*>(&Vs[w][0][0]) + lane;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-        mine[(mb * 4 + r4) * 64] = make_float4(o[mb][4 * r4], o[mb][4 * r4 + 1], o[mb][4 * r4 + 2], o[mb][4 * r4 + 3]);
-    if (half == 0) {
-      m_sh[w][col] = m_run;
-      l_sh[w][col] = l_run;
-    }
+    for (int r4 = 0; r4 < 4; ++r4)
+      mine[(mb * 4 + r4) * 64] = make_float4(o[mb][4 * r4], o[mb][4 * r4 + 1], o[mb][4 * r4 + 2], o[mb][4 * r4 + 3]);
+  if (half == 0) {
+    m_sh[w][col] = m_run;
+    l_sh[w][col] = l_run;
   }
   __syncthreads();
   // wave w finishes registers [w CH, (w+1) CH) of the 16 MB per lane; register
@@ -347,39 +380,29 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
   static_assert(CH % 4 == 0, "whole groups of four registers");
   const float4* const part = reinterpret_cast<const float4*>(&Vs[0][0][0]) + w * (CH / 4) * 64 + lane;
   constexpr int kPart = 2 * BLK * 2 / 16;   // float4 per partial result
+  float M = -INFINITY;
+#pragma unroll
+  for (int x = 0; x < kWaves; ++x) M = fmaxf(M, m_sh[x][col]);   // finite: wave 0 saw block 0
+  float f[kWaves], L = 0.f;
+#pragma unroll
+  for (int x = 0; x < kWaves; ++x) {
+    f[x] = __builtin_amdgcn_exp2f((m_sh[x][col] - M) * c2);       // a wave without blocks: exp2(-inf) = 0
+    L = fmaf(f[x], l_sh[x][col], L);
+  }
   float4 acc[CH / 4];
-  float L;
-  if (alone) {
-    L = l_sh[0][col];
 #pragma unroll
-    for (int i4 = 0; i4 < CH / 4; ++i4) acc[i4] = part[i4 * 64];
-  } else {
-    float M = -INFINITY;
-#pragma unroll
-    for (int x = 0; x < kWaves; ++x) M = fmaxf(M, m_sh[x][col]);   // finite: wave 0 saw block 0
-    float f[kWaves];
-    L = 0.f;
+  for (int i4 = 0; i4 < CH / 4; ++i4) {
+    acc[i4] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int x = 0; x < kWaves; ++x) {
-      f[x] = __builtin_amdgcn_exp2f((m_sh[x][col] - M) * c2);       // a wave without blocks: exp2(-inf) = 0
-      L = fmaf(f[x], l_sh[x][col], L);
-    }
-#pragma unroll
-    for (int i4 = 0; i4 < CH / 4; ++i4) {
-      acc[i4] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int x = 0; x < kWaves; ++x) {
-        const float4 p = part[x * kPart + i4 * 64];
-        acc[i4].x = fmaf(f[x], p.x, acc[i4].x);
-        acc[i4].y = fmaf(f[x], p.y, acc[i4].y);
-        acc[i4].z = fmaf(f[x], p.z, acc[i4].z);
-        acc[i4].w = fmaf(f[x], p.w, acc[i4].w);
-      }
+      const float4 p = part[x * kPart + i4 * 64];
+      acc[i4].x = fmaf(f[x], p.x, acc[i4].x);
+      acc[i4].y = fmaf(f[x], p.y, acc[i4].y);
+      acc[i4].z = fmaf(f[x], p.z, acc[i4].z);
+      acc[i4].w = fmaf(f[x], p.w, acc[i4].w);
     }
   }
   const float inv = 1.f / L;
-  const int qi = q0 + col;
-  __bf16* orow = out + (new_row0 + min(qi, N_k - 1)) * D;
 #pragma unroll
   for (int i4 = 0; i4 < CH / 4; ++i4) {
     const int reg0 = w * CH + 4 * i4;
