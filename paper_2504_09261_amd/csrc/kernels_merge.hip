@@ -20,10 +20,10 @@
 //                  their inverse norms, two 32-row blocks per barrier; per lane a running
 //                  (best, arg-best) over 16 kept rows per block, the lane pair (l, l^32)
 //                  combined at the end;
-//   merge_apply    a work-group takes 32 kept rows: its waves scan the assignment once,
-//                  each a contiguous quarter, and leave the rows that go to one of the 32
+//   merge_apply    a work-group takes 8 or 32 kept rows: its waves scan the assignment once,
+//                  each a contiguous quarter, and leave the rows that go to one of them
 //                  in LDS lists (ascending); every wave then folds the listed rows, eight
-//                  loads in flight, into its 8 kept rows in ascending row order (so the float32 sums are formed
+//                  loads in flight, into its 2 or 8 kept rows in ascending row order (so the float32 sums are formed
 //                  in a fixed order: the result is reproducible bit for bit) and rewrites
 //                  them in place.
 // bf16 only.  The products of bf16 values are exact in float32; dots accumulate in
@@ -49,7 +49,11 @@ constexpr int kNearBlocks = 1;                      // 32-row candidate blocks p
 constexpr int kNearTile = kWaves * 32 * kNearBlocks;   // cache rows per work-group in merge_nearest
 constexpr int kFillRows = 1024;                     // rows per work-group in merge_fill
 constexpr int kMarkRows = kThreads / 8;             // kept rows per work-group in merge_mark (8 lanes per row)
-constexpr int kApplyRows = 32;                      // kept rows per work-group in merge_apply
+// Cache rows that the work-groups of merge_apply may scan together while each takes 8 kept rows; beyond that it takes 32.  Measured, us
+// a schedule that ends with the merge, 32 / 16 / 8 rows (rows scanned at 8): 12 units of 5500 and 648 kept rows (5.3M) 512 / 506 / 503;
+// 60 of 358 and 102 (0.1M) 128 / 118 / 114; 480 such units (2.2M) 352 / 348 / 346; 32 of 1200 and 190 (0.9M) 126 / 109 / 100; 12 of 6039 and 1943
+// (17.6M) 821 / 820 / 825; 48 of 5500 and 648 (21M) 1305 / 1296 / 1301; 12 of 8700 and 3900 (35M) 1190 / 1194 / 1208.
+constexpr int64_t kApplyScan = 16 << 20;
 constexpr int kScanSteps = 8;                        // 64-row steps of that scan in flight
 constexpr int kFold = 8;                             // evicted rows a wave of merge_apply folds in at a time
 constexpr int kScanPerWave = 2048;                  // cache rows a wave of merge_apply scans per round = capacity of its list
@@ -239,22 +243,24 @@ __global__ __launch_bounds__(kThreads, 4) void merge_nearest(
   }
 }
 
-// Work item = (merging unit, 32 kept rows [r0, r0 + 32)); wave w owns rows r0 + 8 w .. + 8.
-template <int D>
+// Work item = (merging unit, ROWS kept rows from r0 on); wave w owns the ROWS / 4 from r0 + w ROWS / 4 on.
+// Folding is a chain of loads per wave, as long as the rows that go to its kept rows are many: few kept rows per wave keep it
+// short.  Every work-group scans the whole assignment, so their number is bounded by what all of them scan (kApplyScan).
+template <int D, int ROWS>
 __global__ __launch_bounds__(kThreads) void merge_apply(
     const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, const __bf16* __restrict__ k_in,
     const __bf16* __restrict__ v_in, const __bf16* __restrict__ k_new, const __bf16* __restrict__ v_new, int N_k,
     const int32_t* __restrict__ nearest, const float* __restrict__ weight, int64_t ws_stride,
     __bf16* __restrict__ k_out, __bf16* __restrict__ v_out, int cap) {
   constexpr int EPL = D / 64;                   // elements per lane
-  constexpr int RPW = kApplyRows / kWaves;      // kept rows per wave
-  static_assert(kApplyRows == 32, "a list entry keeps the row's offset in 5 bits");
+  constexpr int RPW = ROWS / kWaves;            // kept rows per wave
+  static_assert(ROWS <= 32, "a list entry keeps the row's offset in 5 bits");
   // entry: (cache row - first row of the round) << 5 | (kept row - r0); each wave's list is ascending
   extern __shared__ uint32_t lst[];   // [kWaves][cap]
   __shared__ int cnt[kWaves];
   const UnitDesc d = descs[list[blockIdx.y]];
   const int T = d.len_in + d.n_new, b = d.n_out;
-  const int r0 = blockIdx.x * kApplyRows;
+  const int r0 = blockIdx.x * ROWS;
   if (r0 >= b) return;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t* nn = nearest + (int64_t)d.unit * ws_stride;
@@ -283,7 +289,7 @@ __global__ __launch_bounds__(kThreads) void merge_apply(
       for (int u = 0; u < kScanSteps; ++u) {
         const int j = base + t0 + 64 * u + lane;
         const unsigned rl = (unsigned)(v[u] - r0);            // kept (-1) and unassigned rows wrap to large values
-        const bool hit = rl < (unsigned)kApplyRows;
+        const bool hit = rl < (unsigned)ROWS;
         const unsigned long long m = __ballot(hit);
         if (hit) lst[w * cap + n + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = ((unsigned)(j - seg0) << 5) | rl;
         n += __builtin_popcountll(m);
@@ -375,9 +381,13 @@ void launch_t(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_l
                      list, (const T*)k_in, (const T*)k_new, (const T*)k_out, N_k, inv_norm, nearest, weight, ws_stride);
   // list capacity of a wave of merge_apply: a quarter of the longest cache in whole 64-row steps, at most kScanPerWave
   const int cap = std::min(kScanPerWave, (max_t_in + 64 * kWaves - 1) / (64 * kWaves) * 64);
-  hipLaunchKernelGGL(merge_apply<D>, dim3((max_out + kApplyRows - 1) / kApplyRows, n_list), dim3(kThreads),
-                     (size_t)kWaves * cap * sizeof(uint32_t), s, descs, list, (const T*)k_in, (const T*)v_in, (const T*)k_new,
-                     (const T*)v_new, N_k, nearest, weight, ws_stride, (T*)k_out, (T*)v_out, cap);
+#define HACK_APPLY(ROWS_)                                                                                                   \
+  hipLaunchKernelGGL((merge_apply<D, ROWS_>), dim3((max_out + ROWS_ - 1) / ROWS_, n_list), dim3(kThreads),                  \
+                     (size_t)kWaves * cap * sizeof(uint32_t), s, descs, list, (const T*)k_in, (const T*)v_in, (const T*)k_new, \
+                     (const T*)v_new, N_k, nearest, weight, ws_stride, (T*)k_out, (T*)v_out, cap)
+  if ((int64_t)((max_out + 7) / 8) * n_list * max_t_in <= kApplyScan) HACK_APPLY(8);
+  else HACK_APPLY(32);
+#undef HACK_APPLY
 }
 
 }  // namespace

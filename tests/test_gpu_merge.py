@@ -148,3 +148,37 @@ def test_schedules_with_final_merge():
     units = [int(np.where(types == 0)[0][0]), int(np.where(types == 1)[0][0]), cfg.heads + int(np.where(types == 0)[0][1])]
     stats = run_free(cfg, 0, units, final_merge=True)
     assert stats["mismatch"] == 0 and stats["merged_rows"] > 500
+
+
+def test_merge_gives_the_same_bits_whatever_shares_the_launch():
+    """Few units: 8 kept rows per work-group of the fold; many: 32.  Each row's sum is formed in the same order in both, so a unit's
+    merged rows are the same bits; caches longer than one round of the fold's scan, kept rows that fill no work-group."""
+    u = _u()
+    H, d, Nk, b = 48, 128, 64, 701
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(3)
+    lens = np.full(H, 9000, np.int32)
+    lens[1::4] = 8200
+    lens[2::4] = 700
+    off = np.arange(H, dtype=np.int64) * 9008
+    K, V = (torch.randn((H * 9008, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    K[:, :4] += 2                                              # keys that have something in common
+    kn, vn = (torch.randn((1, H, Nk, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=9064, max_queries=Nk)
+    kept = torch.zeros((H, 704), dtype=torch.int32, device=u.DEV)
+    for x in range(H):
+        rows = torch.randperm(int(lens[x]) + Nk, generator=gen, device=u.DEV)[:b]
+        kept[x, :b] = rows.sort().values.int()
+    results = []
+    for active in (np.arange(H) < 4, np.ones(H, bool)):
+        k_out, v_out = (torch.zeros((H * 704, d), dtype=torch.bfloat16, device=u.DEV) for _ in range(2))
+        cin, cout = Cache(K, V, off, lens), Cache(k_out, v_out, np.arange(H, dtype=np.int64) * 704, np.full(H, b, np.int32))
+        hk.compact(1, Nk, cin, kept, cout, kn, vn)
+        before = k_out.clone()
+        hk.merge(1, Nk, cin, kept, cout, kn, vn, active=active.astype(np.uint8))
+        torch.cuda.synchronize()
+        assert not torch.equal(k_out[:4 * 704], before[:4 * 704])
+        results.append((k_out[:4 * 704], v_out[:4 * 704]))
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+    hk.check()
+    hk.close()
