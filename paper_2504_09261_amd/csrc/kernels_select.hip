@@ -25,6 +25,8 @@
 // More threads with fewer keys each won throughout (4000 keys: 256, 512, 1024 threads
 // 8.1, 6.4, 5.9; 560 keys, 60 / 960 units: 128 threads 6.1 / 9.8, 256 4.5 / 7.0, 512 3.9 / 6.4,
 // 1024 4.1 / 9.2, the last for want of resident work-groups).
+// Keys are dealt as evenly as their number allows: 6 a thread up to 6144 keys and 12 up to 12288 instead of 8 and 16 (4186, 5000, 6039 keys
+// 6.9 / 6.3, 6.8 / 6.3, 7.0 / 6.6 us; 8831, 9500, 10521 11.0 / 9.3, 11.9 / 10.2, 10.5 / 8.9).
 #include "hack_internal.h"
 #include "select_device.h"
 
@@ -62,17 +64,17 @@ __global__ __launch_bounds__(NT) void select_kernel(
     if (j0 + e >= d.sel_lo && j0 + e < d.sel_hi) in_seg |= 1u << e;
   }
   if (ranked && in_seg) {
-    // a whole piece of four stays inside the unit's row (j0 < T <= imp_stride, both multiples of four)
-    const bool vec = PER % 4 == 0 && (imp_stride & 3) == 0 && ((uintptr_t)importance & 15) == 0;
+    // a whole piece of V stays inside the unit's row (j0 < T <= imp_stride, both multiples of it)
+    constexpr int V = PER % 4 == 0 ? 4 : 2;
+    typedef __attribute__((__vector_size__(V * sizeof(uint32_t)))) uint32_t piece;
+    const bool vec = PER % V == 0 && (imp_stride & 3) == 0 && ((uintptr_t)importance & 15) == 0;
     if (vec) {
 #pragma unroll
-      for (int e4 = 0; e4 < PER / 4; ++e4) {
-        if ((in_seg >> (4 * e4)) & 15u) {
-          const float4 x = *reinterpret_cast<const float4*>(imp + j0 + 4 * e4);
-          key[4 * e4] = __float_as_uint(x.x);
-          key[4 * e4 + 1] = __float_as_uint(x.y);
-          key[4 * e4 + 2] = __float_as_uint(x.z);
-          key[4 * e4 + 3] = __float_as_uint(x.w);
+      for (int ev = 0; ev < PER / V; ++ev) {
+        if ((in_seg >> (V * ev)) & ((1u << V) - 1u)) {
+          const piece x = *reinterpret_cast<const piece*>(imp + j0 + V * ev);
+#pragma unroll
+          for (int e = 0; e < V; ++e) key[V * ev + e] = x[e];
         }
       }
     } else {
@@ -97,7 +99,9 @@ void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, in
   if (max_t_in <= 1024) HACK_SELECT(512, 2, 11, 11);
   else if (max_t_in <= 2048) HACK_SELECT(1024, 2, 12, 10);
   else if (max_t_in <= 4096) HACK_SELECT(1024, 4, 12, 10);
+  else if (max_t_in <= 6144) HACK_SELECT(1024, 6, 12, 10);
   else if (max_t_in <= 8192) HACK_SELECT(1024, 8, 12, 10);
+  else if (max_t_in <= 12288) HACK_SELECT(1024, 12, 12, 10);
   else if (max_t_in <= 16384) HACK_SELECT(1024, 16, 12, 10);
   else HACK_SELECT(1024, 32, 12, 10);
 #undef HACK_SELECT

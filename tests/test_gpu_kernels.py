@@ -180,6 +180,11 @@ def test_select_every_size_class_and_digit(T):
     hk.close()
 
 
+@pytest.mark.parametrize("T", [4100, 6143, 6144, 6145, 12284, 12287, 12288, 12289])
+def test_select_forms_of_6_and_12_keys_a_thread(T):
+    test_select_every_size_class_and_digit(T)
+
+
 def test_select_rejects_bad_arguments():
     u = _u()
     hk = u.make_hack(heads=1, head_dim=64, dtype="bf16", max_units=1, max_cache_len=128, max_queries=16)
