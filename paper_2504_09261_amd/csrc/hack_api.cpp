@@ -67,7 +67,7 @@ struct hack_ctx {
   int32_t* kept = nullptr;       // [max_units, ws_stride]
   int32_t* seam = nullptr;       // [max_units] kept rows of the step's selection that come from the cache
   int32_t* iota = nullptr;       // [kIotaRows] 0, 1, 2, ...
-  F32Tile* f32_tiles = nullptr;  // fp32 path: [4 score_select_f32_max_groups] partial results of short units
+  double* f32_logits = nullptr;  // fp32 path: [score_select_f32_max_groups, kF32GroupLogits] logits of short units
   double* stats = nullptr;       // fp32 path: [score_f32_max_groups, 32, 2] softmax partials
   unsigned long long* rowstat = nullptr;  // bf16 path: [max_units, score_groups, 32] row-sum exchange slots, all-ones between launches
   unsigned long long* rowstat_side = nullptr;  // the same for the side branch of hack_step (two-pass form: its slots are not re-armed)
@@ -628,7 +628,7 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
     e = rows ? hipMemcpy(ctx->iota, rows.get(), kIotaRows * sizeof(int32_t), hipMemcpyHostToDevice) : hipErrorOutOfMemory;
   }
   if (e == hipSuccess && cfg->dtype == HACK_F32)
-    e = hipMalloc((void**)&ctx->f32_tiles, 4 * (size_t)score_select_f32_max_groups(cfg->max_units, cfg->max_cache_len) * sizeof(F32Tile));
+    e = hipMalloc((void**)&ctx->f32_logits, (size_t)score_select_f32_max_groups(cfg->max_units, cfg->max_cache_len) * kF32GroupLogits * sizeof(double));
   if (e == hipSuccess && cfg->dtype == HACK_F32)
     e = hipMalloc((void**)&ctx->stats, (size_t)score_f32_max_groups(cfg->max_units, cfg->max_cache_len) * kMaxObs * 2 * sizeof(double));
   ctx->score_groups = score_max_groups();   // exchange slots per unit: enough for every item size
@@ -691,7 +691,7 @@ extern "C" void hack_destroy(hack_ctx* ctx) {
   if (ctx->kept) (void)hipFree(ctx->kept);
   if (ctx->seam) (void)hipFree(ctx->seam);
   if (ctx->iota) (void)hipFree(ctx->iota);
-  if (ctx->f32_tiles) (void)hipFree(ctx->f32_tiles);
+  if (ctx->f32_logits) (void)hipFree(ctx->f32_logits);
   if (ctx->stats) (void)hipFree(ctx->stats);
   if (ctx->rowstat) (void)hipFree(ctx->rowstat);
   if (ctx->rowstat_side) (void)hipFree(ctx->rowstat_side);
@@ -1168,7 +1168,7 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->streamed = !n.split && g->attn_kernel != kAttnHalves && use_stream_attention(ctx, u.descs, n.N_k, shared, &plan);
   if (!g->streamed && g->attn_kernel != kAttnHalves) build_attn_items(u.descs, n.N_k, n.tile, &items);
   g->small = ctx->cfg.dtype == HACK_BF16 ? use_score_select(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t)
-                                         : launch_score_select_f32 != nullptr && use_score_select_f32((int)u.comp.size(), g->max_t);
+                                         : launch_score_select_f32 != nullptr && use_score_select_f32(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t);
   if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty() && !g->small)
     g->item_keys = plan_score_items(ctx, u.descs, u.comp, g->two_pass, &sitems, &g->launches);
   // The key-split and the float32 kernel read the rows in place unless they change on the way (merge) or a unit's cache is longer than
@@ -1208,7 +1208,7 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
   bool moves = !a.in_place || (!n.fuse_append && !g.gathered);   // rows move in front of the attention launch
   if (g.n_comp > 0 && g.small && ctx->cfg.dtype == HACK_F32) {
     launch_score_select_f32(s, ctx->cfg.head_dim, comp_dev, g.n_comp, g.max_t, a.q, reinterpret_cast<const int32_t*>(g.dev + g.o_rows),
-                            n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->f32_tiles, ctx->counters, a.kept, a.kstride, ctx->seam);
+                            n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->f32_logits, ctx->stats, ctx->counters, a.kept, a.kstride, ctx->seam);
   } else if (g.n_comp > 0 && g.small && moves && launch_score_select_move != nullptr) {
     launch_score_select_move(s, ctx->cfg.head_dim, comp_dev, g.n_comp, comp_dev + g.n_comp, g.n_desc - g.n_comp, g.max_t, a.q,
                              reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp, a.k_new, a.v_new, a.pos_new,

@@ -165,16 +165,19 @@ void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const 
                       const void* k_cache, const void* k_new, double* stats, float* importance,
                       int64_t imp_stride);
 
-// fp32: score and selection of short units in one launch.  tiles: workspace of 4 entries per work-group of 64 keys
-// (score_f32_groups(n_units, max_t_in, 64)); counters: 2 uint32 per unit of the launch, zero on entry and left zero.  Weak: host
-// code that is linked without the kernels' file goes without.
-struct F32Tile {                     // what 16 keys contribute to their unit's rows
-  double m[kMaxObs], l[kMaxObs];     // maximum logit, sum of exp(logit - maximum)
-  float e[kMaxObs][16];              // exp(logit - maximum)
-};
-constexpr int kF32SmallKeys = 1024;   // longest unit of such a launch
-inline bool use_score_select_f32(int n_units, int max_t_in) {
-  return max_t_in <= kF32SmallKeys && score_f32_groups(n_units, max_t_in, 64) <= kF32SmallGroups;
+// fp32: score and selection of short units in one launch.  logits: workspace of kF32GroupLogits doubles per work-group of 64 keys
+// (score_f32_groups(n_units, max_t_in, 64)); stats as launch_score_f32; counters: 2 uint32 per unit of the launch, zero on entry and
+// left zero.  Weak: host code that is linked without the kernels' file goes without.
+constexpr int kF32GroupLogits = 64 * kMaxObs;
+// Where: units of up to 512 keys (one a thread); longer ones, whose work-groups leave room for one on a compute
+// unit, as far as all of the launch's are resident at once and the last work-group's walk over the unit is shorter than the launches that it
+// saves.  Measured, us a compressing step, three launches / one: head_dim 64, 16 units of 130, 256, 384, 512, 576, 768 keys 19.5 / 16.0,
+// 22.0 / 19.2, 24.2 / 22.3, 26.2 / 25.5, 27.5 / 27.1, 30.6 / 31.9; 64 of 512 34.7 / 34.0; 32 of 576 (288 work-groups) 33.8 / 35.0, of 1024
+// 41.2 / 55.7; head_dim 128, 16 units of 130, 512, 768, 900, 1024 26.9 / 20.4, 39.4 / 35.6, 47.3 / 45.2, 50.4 / 49.6, 53.7 / 53.6.
+constexpr int kF32SmallKeys = 896;    // longest unit of such a launch
+inline bool use_score_select_f32(int head_dim, int n_units, int max_t_in) {
+  const int64_t groups = score_f32_groups(n_units, max_t_in, 64);
+  return max_t_in <= 512 ? groups <= kF32SmallGroups : max_t_in <= (head_dim == 64 ? 576 : kF32SmallKeys) && groups <= 256;
 }
 inline int64_t score_select_f32_max_groups(int max_units, int max_len) {
   const int64_t n = score_f32_groups(max_units, max_len < kF32SmallKeys ? max_len : kF32SmallKeys, 64);
@@ -182,7 +185,7 @@ inline int64_t score_select_f32_max_groups(int max_units, int max_len) {
 }
 __attribute__((weak)) void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in,
                                                    const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
-                                                   const void* k_cache, const void* k_new, F32Tile* tiles, unsigned* counters,
+                                                   const void* k_cache, const void* k_new, double* logits, double* stats, unsigned* counters,
                                                    int32_t* kept_idx, int64_t idx_stride, int32_t* seam);
 
 // bf16: score and selection of short units in one launch, one work-group per listed unit, no importance in memory.

@@ -48,36 +48,44 @@ __device__ __forceinline__ float exp2_split(double t) {
 __device__ __forceinline__ double exp_neg(double x) { return (double)exp2_split(x * kLog2e); }
 
 // Combine the per-chunk (maximum, sum) partials of one unit into sm[i] (maximum) and
-// sinv[i] (1 / normaliser) for the rows i < n_obs.  All 256
+// sinv[i] (1 / normaliser) for the rows i < n_obs.  The first 256 of the NT
 // threads take part: thread (g, i) = (tid / 32, tid % 32) folds the chunks
 // g, g + 8, ... of row i, then the eight groups are merged through LDS.
+// m: maximum over this thread's chunks; sum(m): their sums relative to m.
 // Ends with a barrier: sm / sinv are ready for every thread on return.
-__device__ __forceinline__ void combine_stats(const double* __restrict__ st, int n_chunks, int n_obs,
-                                              double* sm, double* sinv, double (*red)[kMaxObs]) {
+template <int NT, typename Sum>
+__device__ __forceinline__ void combine_rows(double m, Sum sum, int n_obs, double* sm, double* sinv, double (*red)[kMaxObs]) {
   const int i = threadIdx.x & 31, g = threadIdx.x >> 5;
-  double m = -INFINITY;
-  for (int c = g; c < n_chunks; c += 8) m = fmax(m, st[(c * kMaxObs + i) * 2]);
-  red[g][i] = m;
+  if (NT == 256 || g < 8) red[g][i] = m;
   __syncthreads();
   m = red[0][i];
 #pragma unroll
   for (int k = 1; k < 8; ++k) m = fmax(m, red[k][i]);
   __syncthreads();
-  double l = 0.0;
-  for (int c = g; c < n_chunks; c += 8) {
-    const double mc = st[(c * kMaxObs + i) * 2], lc = st[(c * kMaxObs + i) * 2 + 1];
-    l += lc * exp_neg(mc - m);
-  }
-  red[g][i] = l;
+  if (NT == 256 || g < 8) red[g][i] = sum(m);
   __syncthreads();
   if (g == 0) {
-    l = red[0][i];
+    double l = red[0][i];
 #pragma unroll
     for (int k = 1; k < 8; ++k) l += red[k][i];
     sm[i] = m;                          // unused rows repeat row 0: exponents stay <= 0, weight zero
     sinv[i] = (i < n_obs) ? 1.0 / l : 0.0;
   }
   __syncthreads();
+}
+__device__ __forceinline__ void combine_stats(const double* __restrict__ st, int n_chunks, int n_obs,
+                                              double* sm, double* sinv, double (*red)[kMaxObs]) {
+  const int i = threadIdx.x & 31, g = threadIdx.x >> 5;
+  double m = -INFINITY;
+  for (int c = g; c < n_chunks; c += 8) m = fmax(m, st[(c * kMaxObs + i) * 2]);
+  combine_rows<kThreads>(m, [&](double top) {
+    double l = 0.0;
+    for (int c = g; c < n_chunks; c += 8) {
+      const double mc = st[(c * kMaxObs + i) * 2], lc = st[(c * kMaxObs + i) * 2 + 1];
+      l += lc * exp_neg(mc - top);
+    }
+    return l;
+  }, n_obs, sm, sinv, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -107,6 +115,76 @@ __device__ __forceinline__ double row16_reduce(double v, Op op) {
   v = op(v, dpp_mov_f64<0x4E>(v));
   v = op(v, dpp_mov_f64<0x141>(v));
   return op(v, dpp_mov_f64<0x140>(v));
+}
+
+// The float32 kernels form every number with the same operations in the same order: a step that scores and selects in one launch
+// keeps what hack_score and hack_select keep, and a weight depends on its logit alone, so equal keys have equal importance.
+// Logits of a tile: s[h][r] of lane (i, g) is observation row 16 h + 4 r + g, key i.
+template <int C>
+__device__ __forceinline__ void tile_logits(const floatx4 (&qf)[2][C], const floatx4 (&kf)[C], doublex4 (&acc)[2]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) acc[h] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double kd = (double)kf[c][e];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qf[h][c][e], kd, acc[h], 0, 0, 0);
+    }
+}
+
+// Maximum and sum of exp(logit - maximum) per observation row: of this wave's TPW tiles from key0 on into red_m[w], red[w], and,
+// behind a barrier, of the chunk of four such waves.
+template <int TPW>
+__device__ __forceinline__ void wave_stats(const double (&s)[TPW][2][4], int key0, int T_in, double (*red_m)[kMaxObs], double (*red)[kMaxObs]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double m = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+        if (key0 + 16 * t + i < T_in) m = fmax(m, s[t][h][r]);
+      m = row16_reduce(m, [](double a, double b) { return fmax(a, b); });
+      double l = 0.0;
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+        if (key0 + 16 * t + i < T_in) l += exp_neg(s[t][h][r] - m);
+      l = row16_reduce(l, [](double a, double b) { return a + b; });
+      if (i == 0) {
+        red_m[w][16 * h + 4 * r + g] = m;
+        red[w][16 * h + 4 * r + g] = l;
+      }
+    }
+}
+__device__ __forceinline__ void chunk_stats(int row, const double (*red_m)[kMaxObs], const double (*red)[kMaxObs], double* m_out, double* l_out) {
+  double m = red_m[0][row];     // finite: the chunk's first key exists, and wave 0 holds it
+#pragma unroll
+  for (int k = 1; k < 4; ++k) m = fmax(m, red_m[k][row]);
+  double l = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (red_m[k][row] > -INFINITY) l += red[k][row] * exp_neg(red_m[k][row] - m);
+  *m_out = m;
+  *l_out = l;
+}
+
+// Importance of key i of a tile, in all four lanes that share it.
+__device__ __forceinline__ double tile_importance(const double (&s)[2][4], int g, const double* sm, const double* sinv) {
+  double imp = 0.0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * h + 4 * r + g;
+      imp += exp_neg(s[h][r] - sm[row]) * sinv[row];
+    }
+  imp += shfl_xor_f64(imp, 16);
+  imp += shfl_xor_f64(imp, 32);
+  return imp;
 }
 
 template <int D, int TPW, int PASS>
@@ -148,18 +226,11 @@ __global__ __launch_bounds__(kThreads) void score_f32(
   double* st_unit = stats + (int64_t)blockIdx.y * max_chunks * kMaxObs * 2;
   if (PASS == 2) combine_stats(st_unit, n_chunks, n_obs, sm, sinv, red);
 
-  double s[TPW][2][4];   // logits of tile t: observation row 16 h + 4 r + g, key i
+  double s[TPW][2][4];   // logits of tile t
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
-    doublex4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double kd = (double)kf[c][e];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qf[h][c][e], kd, acc[h], 0, 0, 0);
-      }
+    doublex4 acc[2];
+    tile_logits(qf, kf, acc);
     if (t + 1 < TPW) load_k(t + 1);
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -168,53 +239,19 @@ __global__ __launch_bounds__(kThreads) void score_f32(
   }
 
   if (PASS == 1) {
-    // this wave's maximum and sum per row, then the work-group's
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        double m = -INFINITY;
-#pragma unroll
-        for (int t = 0; t < TPW; ++t)
-          if (key0 + 16 * t + i < T_in) m = fmax(m, s[t][h][r]);
-        m = row16_reduce(m, [](double a, double b) { return fmax(a, b); });
-        double l = 0.0;
-#pragma unroll
-        for (int t = 0; t < TPW; ++t)
-          if (key0 + 16 * t + i < T_in) l += exp_neg(s[t][h][r] - m);
-        l = row16_reduce(l, [](double a, double b) { return a + b; });
-        if (i == 0) {
-          red_m[w][16 * h + 4 * r + g] = m;
-          red[w][16 * h + 4 * r + g] = l;
-        }
-      }
+    wave_stats<TPW>(s, key0, T_in, red_m, red);
     __syncthreads();
     if (threadIdx.x < kMaxObs) {
-      const int row = threadIdx.x;
-      double m = red_m[0][row];     // finite: the chunk's first key exists, and wave 0 holds it
-#pragma unroll
-      for (int k = 1; k < 4; ++k) m = fmax(m, red_m[k][row]);
-      double l = 0.0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (red_m[k][row] > -INFINITY) l += red[k][row] * exp_neg(red_m[k][row] - m);
-      double* o2 = st_unit + ((int64_t)blockIdx.x * kMaxObs + row) * 2;
+      double m, l;
+      chunk_stats(threadIdx.x, red_m, red, &m, &l);
+      double* o2 = st_unit + ((int64_t)blockIdx.x * kMaxObs + threadIdx.x) * 2;
       o2[0] = m;
       o2[1] = l;
     }
   } else {
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
-      double imp = 0.0;
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = 16 * h + 4 * r + g;
-          imp += exp_neg(s[t][h][r] - sm[row]) * sinv[row];
-        }
-      imp += shfl_xor_f64(imp, 16);
-      imp += shfl_xor_f64(imp, 32);
+      const double imp = tile_importance(s[t], g, sm, sinv);
       const int j = key0 + 16 * t + i;
       if (g == 0 && j < T_in) importance[(int64_t)d.unit * imp_stride + j] = (float)imp;
     }
@@ -224,58 +261,47 @@ __global__ __launch_bounds__(kThreads) void score_f32(
 // ---------------------------------------------------------------------------
 // float32, short units: score and selection in one launch
 // ---------------------------------------------------------------------------
-// Pass 1 as above with every tile of 16 keys a chunk of its own: a wave stores its tile's maxima, sums and weights
-// e = exp(logit - maximum) (float32 values by construction, see exp2_split), and the work-group that draws its unit's last ticket
-// weighs them, importance_j = sum_i e_ij exp(m_tile,i - m_i) / l_i, and ranks what it has just formed.  The tiles come from
-// different XCDs: weights, partials and tickets travel as device-scope relaxed atomics, a ticket drawn only after the
-// work-group's stores have been acknowledged; nobody waits for anybody.  Pass 2's operands, products and exponentials, its launch and the selection's
-// are saved: these launches are chains of latencies (8 to 16 units of 155, 255, 424, 561 keys: three launches 15.5 us,
-// this one 10.3, 10.2, 11.2, 14.4 in the kernel trace; a 256^2 schedule 116.6 -> 107.6 us).
-// 2^t for t <= 0 to 1e-11: the weights already carry float32's rounding, the factors that join tiles shall add none.
-__device__ __forceinline__ double exp2_double(double t) {
-  const double n = rint(fmax(t, -1100.0));
-  const double x = (fmax(t, -1100.0) - n) * 0.69314718055994530942;   // |x| <= 0.3466: the series of exp to x^9
-  double p = 1.0 / 362880;
-  p = fma(p, x, 1.0 / 40320);
-  p = fma(p, x, 1.0 / 5040);
-  p = fma(p, x, 1.0 / 720);
-  p = fma(p, x, 1.0 / 120);
-  p = fma(p, x, 1.0 / 24);
-  p = fma(p, x, 1.0 / 6);
-  p = fma(p, x, 0.5);
-  p = fma(p, x, 1.0);
-  p = fma(p, x, 1.0);
-  return ldexp(p, (int)n);
-}
+// Pass 1 of chunks of 64 keys, whose waves also store their logits; the work-group that draws its unit's last ticket does pass 2 over
+// the stored logits and ranks what it has just formed.  The chunks come from
+// different XCDs: logits, partials and tickets travel as device-scope relaxed atomics, a ticket drawn only after the
+// work-group's stores have been acknowledged; nobody waits for anybody.  Pass 2's operands and products, its launch and the selection's
+// are saved: these launches are chains of latencies (a 256^2 schedule 118.0 -> 105.8 us; use_score_select_f32 has the steps).
+// Keeping the weights instead, rounded against their tile's own maximum, would spare the last work-group the exponentials, but equal keys
+// of two tiles would round differently and no longer rank by index.
 template <typename T>
 __device__ __forceinline__ void store_agent(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 template <typename T>
 __device__ __forceinline__ T load_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// PER: rows per thread of the selection (T_in <= 256 PER)
+// Four waves score, eight do pass 2, whose float64 chains one wave a SIMD does not hide (16 units of 384 keys, us a step, four / eight:
+// 24.1 / 22.3), and rank, PER rows a thread (T_in <= 512 PER).  logits: 2048 doubles per work-group; stats as score_f32.
 template <int D, int PER>
-__global__ __launch_bounds__(kThreads) void score_select_f32(
+__global__ __launch_bounds__(512) void score_select_f32(
     const UnitDesc* __restrict__ descs, const float* __restrict__ q, const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale,
-    const float* __restrict__ k_cache, const float* __restrict__ k_new, F32Tile* __restrict__ tiles, unsigned* __restrict__ counters,
-    int32_t* __restrict__ kept_idx, int64_t idx_stride, int32_t* __restrict__ seam) {
+    const float* __restrict__ k_cache, const float* __restrict__ k_new, double* __restrict__ logits, double* __restrict__ stats,
+    unsigned* __restrict__ counters, int32_t* __restrict__ kept_idx, int64_t idx_stride, int32_t* __restrict__ seam) {
   constexpr int C = D / 16;
-  constexpr int kMaxTiles = kThreads * PER / 16;
-  using Shared = SelectShared<kThreads, 11, 11>;
+  constexpr int kTile = 8 * 64;                    // logits of a tile, as its wave holds them
+  constexpr int NT = 512, NW = NT / 64;
+  constexpr int kPerWave = NT * PER / 16 / NW;     // tiles per wave at most, all of them in flight
+  using Shared = SelectShared<NT, 11, 11>;
   __shared__ __attribute__((aligned(16))) uint32_t hist[Shared::kHist];
   __shared__ Shared sh;
-  __shared__ double factor[kMaxTiles][kMaxObs];   // exp(m_tile,i - m_i) / l_i
-  __shared__ double red[8][kMaxObs];
+  __shared__ double red[8][kMaxObs], red_m[4][kMaxObs];
+  __shared__ double sm[kMaxObs], sinv[kMaxObs];
+  __shared__ float imp_sh[NT * PER];
   __shared__ int last_ticket;
   const UnitDesc d = descs[blockIdx.y];
   const int T_in = d.len_in + d.n_new;
-  const int n_groups = (T_in + 63) / 64;
-  if ((int)blockIdx.x >= n_groups) return;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int n_chunks = (T_in + 63) / 64, n_tiles = (T_in + 15) / 16;
+  if ((int)blockIdx.x >= n_chunks) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
-  const int tile = blockIdx.x * 4 + w, key0 = tile * 16, n_tiles = (T_in + 15) / 16;
-  F32Tile* const unit_tiles = tiles + (int64_t)blockIdx.y * gridDim.x * 4;
+  const int key0 = (blockIdx.x * 4 + w) * 16;
+  double* const unit_logits = logits + (int64_t)blockIdx.y * gridDim.x * 4 * kTile + lane;
+  double* const unit_stats = stats + (int64_t)blockIdx.y * gridDim.x * kMaxObs * 2;
 
-  if (tile < n_tiles) {
+  if (w < 4) {
     floatx4 qf[2][C], kf[C];
     const int j = min(key0 + i, T_in - 1);
     const float* p = (j < d.len_in ? k_cache + (d.in_off + j) * D : k_new + ((int64_t)d.unit * N_k + (j - d.len_in)) * D) + 4 * g;
@@ -288,103 +314,90 @@ __global__ __launch_bounds__(kThreads) void score_select_f32(
 #pragma unroll
       for (int c = 0; c < C; ++c) qf[h][c] = *reinterpret_cast<const floatx4*>(p + 16 * c);
     }
-    doublex4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double kd = (double)kf[c][e];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qf[h][c][e], kd, acc[h], 0, 0, 0);
-      }
-    F32Tile* const out = unit_tiles + tile;
-    const bool valid = key0 + i < T_in;
+    doublex4 acc[2];
+    tile_logits(qf, kf, acc);
+    double s[1][2][4];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * h + 4 * r + g;
-        const double s = acc[h][r] * (double)scale;
-        const double m = row16_reduce(valid ? s : -INFINITY, [](double a, double b) { return fmax(a, b); });   // finite: the tile's first key exists
-        const float e = valid ? exp2_split((s - m) * kLog2e) : 0.f;
-        const double l = row16_reduce((double)e, [](double a, double b) { return a + b; });
-        store_agent(&out->e[row][i], e);
-        if (i == 0) {
-          store_agent(&out->m[row], m);
-          store_agent(&out->l[row], l);
-        }
-      }
+      for (int r = 0; r < 4; ++r) s[0][h][r] = acc[h][r] * (double)scale;
+    if (key0 < T_in) {
+      double* out = unit_logits + (key0 / 16) * kTile;
+#pragma unroll
+      for (int x = 0; x < 8; ++x) store_agent(out + x * 64, s[0][x / 4][x % 4]);
+    }
+    wave_stats<1>(s, key0, T_in, red_m, red);
+  }
+  __syncthreads();
+  if (tid < kMaxObs) {
+    double m, l;
+    chunk_stats(tid, red_m, red, &m, &l);
+    double* o2 = unit_stats + ((int64_t)blockIdx.x * kMaxObs + tid) * 2;
+    store_agent(o2, m);
+    store_agent(o2 + 1, l);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores have been acknowledged
   __syncthreads();                                    // ... and so have the work-group's
   if (tid == 0)
-    last_ticket = __hip_atomic_fetch_add(&counters[2 * blockIdx.y], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(n_groups - 1);
+    last_ticket = __hip_atomic_fetch_add(&counters[2 * blockIdx.y], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(n_chunks - 1);
   __syncthreads();
   if (!last_ticket) return;
   if (tid == 0) store_agent(&counters[2 * blockIdx.y], 0u);   // as the next launch expects it
 
-  // ---- rows: thread (t8, row) takes the tiles t8, t8 + 8, ... ----
-  const int row = tid & 31, t8 = tid >> 5;
-  constexpr int TPT = kMaxTiles / 8;
-  double mt[TPT], lt[TPT];
+  // ---- pass 2: wave w takes the tiles w, w + NW, ..., whose logits arrive while the rows' partials are combined ----
+  double s[kPerWave][2][4];
+  auto load = [&](int slot, int t) {
+    if (t < n_tiles) {
+      const double* in = unit_logits + t * kTile;
 #pragma unroll
-  for (int k = 0; k < TPT; ++k) {
-    const F32Tile* t = unit_tiles + min(t8 + 8 * k, n_tiles - 1);
-    mt[k] = load_agent(&t->m[row]);
-    lt[k] = load_agent(&t->l[row]);
-  }
-  double m = mt[0];   // a tile that stands in for one past the end changes no maximum
+      for (int x = 0; x < 8; ++x) s[slot][x / 4][x % 4] = load_agent(in + x * 64);
+    }
+  };
+  constexpr int kChunks = (NT * PER / 64 + 7) / 8;   // of a thread in combine_rows
+  double mc[kChunks], lc[kChunks];
 #pragma unroll
-  for (int k = 1; k < TPT; ++k) m = fmax(m, mt[k]);
-  red[t8][row] = m;
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) m = fmax(m, red[k][row]);
-  __syncthreads();
-  double l = 0.0;
-#pragma unroll
-  for (int k = 0; k < TPT; ++k) {
-    mt[k] = t8 + 8 * k < n_tiles ? exp2_double((mt[k] - m) * kLog2e) : 0.0;
-    l = fma(lt[k], mt[k], l);
-  }
-  red[t8][row] = l;
-  __syncthreads();
-  l = 0.0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) l += red[k][row];
-  const double inv = row < n_obs ? 1.0 / l : 0.0;   // unused rows repeat row 0 with weight zero
-#pragma unroll
-  for (int k = 0; k < TPT; ++k)
-    if (t8 + 8 * k < n_tiles) factor[t8 + 8 * k][row] = mt[k] * inv;
-  __syncthreads();
-
-  // ---- keys: importance of rows tid PER .. of the unit, then their rank ----
-  const int j0 = tid * PER;
-  uint32_t key[PER];
-  unsigned in_seg = 0;
-  double imp[PER];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    imp[e] = 0.0;
-    if (j0 + e >= d.sel_lo && j0 + e < d.sel_hi) in_seg |= 1u << e;
-  }
-  if (j0 < T_in) {
-    const F32Tile* t = unit_tiles + j0 / 16;
-    const double* f = factor[j0 / 16];
-    typedef unsigned long long u64;
-#pragma unroll 16
-    for (int r = 0; r < kMaxObs; ++r) {
-#pragma unroll
-      for (int e = 0; e < PER; e += 2) {
-        const u64 x = load_agent(reinterpret_cast<const u64*>(&t->e[r][(j0 & 15) + e]));
-        imp[e] = fma((double)__uint_as_float((unsigned)x), f[r], imp[e]);
-        imp[e + 1] = fma((double)__uint_as_float((unsigned)(x >> 32)), f[r], imp[e + 1]);
-      }
+  for (int k = 0; k < kChunks; ++k) {
+    const int c = (tid >> 5) + 8 * k;
+    mc[k] = -INFINITY;
+    lc[k] = 0.0;
+    if (tid < 256 && c < n_chunks) {
+      mc[k] = load_agent(unit_stats + (c * kMaxObs + (tid & 31)) * 2);
+      lc[k] = load_agent(unit_stats + (c * kMaxObs + (tid & 31)) * 2 + 1);
     }
   }
 #pragma unroll
-  for (int e = 0; e < PER; ++e) key[e] = (in_seg >> e) & 1u ? __float_as_uint((float)imp[e]) : 0u;
-  select_rows<kThreads, PER, 11, 11>(d, key, in_seg, hist, sh, kept_idx + (int64_t)d.unit * idx_stride, seam);
+  for (int k = 0; k < kPerWave; ++k) load(k, w + NW * k);
+  double top = mc[0];
+#pragma unroll
+  for (int k = 1; k < kChunks; ++k) top = fmax(top, mc[k]);
+  combine_rows<NT>(top, [&](double m) {
+    double l = 0.0;
+#pragma unroll
+    for (int k = 0; k < kChunks; ++k)
+      if ((tid >> 5) + 8 * k < n_chunks) l += lc[k] * exp_neg(mc[k] - m);
+    return l;
+  }, n_obs, sm, sinv, red);
+#pragma unroll
+  for (int k = 0; k < kPerWave; ++k) {
+    const int t = w + NW * k;
+    if (t < n_tiles) {
+      const double imp = tile_importance(s[k], g, sm, sinv);
+      if (g == 0) imp_sh[16 * t + i] = (float)imp;
+    }
+  }
+  __syncthreads();
+
+  // ---- rank of rows tid PER .. of the unit ----
+  const int j0 = tid * PER;
+  uint32_t key[PER];
+  unsigned in_seg = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const bool ranked = j0 + e >= d.sel_lo && j0 + e < d.sel_hi;
+    if (ranked) in_seg |= 1u << e;
+    key[e] = ranked ? __float_as_uint(imp_sh[j0 + e]) : 0u;
+  }
+  select_rows<NT, PER, 11, 11>(d, key, in_seg, hist, sh, kept_idx + (int64_t)d.unit * idx_stride, seam);
 }
 
 // ---------------------------------------------------------------------------
@@ -1229,18 +1242,18 @@ void launch_score_select_move(hipStream_t s, int head_dim, const UnitDesc* descs
 
 void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in, const void* q,
                              const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache, const void* k_new,
-                             F32Tile* tiles, unsigned* counters, int32_t* kept_idx, int64_t idx_stride, int32_t* seam) {
+                             double* logits, double* stats, unsigned* counters, int32_t* kept_idx, int64_t idx_stride, int32_t* seam) {
   if (n_units <= 0 || max_t_in <= 0) return;
   const dim3 grid((max_t_in + 63) / 64, n_units);
 #define HACK_SMALL(D_, PER_)                                                                                                     \
-  hipLaunchKernelGGL((score_select_f32<D_, PER_>), grid, dim3(kThreads), 0, s, descs, (const float*)q, q_rows, n_obs, N_k, scale, \
-                     (const float*)k_cache, (const float*)k_new, tiles, counters, kept_idx, idx_stride, seam)
+  hipLaunchKernelGGL((score_select_f32<D_, PER_>), grid, dim3(512), 0, s, descs, (const float*)q, q_rows, n_obs, N_k, scale, \
+                     (const float*)k_cache, (const float*)k_new, logits, stats, counters, kept_idx, idx_stride, seam)
   if (head_dim == 64) {
-    if (max_t_in <= 512) HACK_SMALL(64, 2);
-    else HACK_SMALL(64, 4);
+    if (max_t_in <= 512) HACK_SMALL(64, 1);
+    else HACK_SMALL(64, 2);
   } else {
-    if (max_t_in <= 512) HACK_SMALL(128, 2);
-    else HACK_SMALL(128, 4);
+    if (max_t_in <= 512) HACK_SMALL(128, 1);
+    else HACK_SMALL(128, 2);
   }
 #undef HACK_SMALL
 }

@@ -609,15 +609,18 @@ def test_short_units_score_and_select_in_one_launch(head_dim, B, sides_n):
     (64, 2, [5, 16, 43, 64]),            # the last tile, the last work-group full: 64 and 128 keys
     (64, 1, [5, 200, 51, 256]),          # exactly 512
     (64, 1, [5, 200, 52, 256]),          # 513
-    (64, 2, [5, 400, 300, 319]),         # exactly 1024
-    (64, 2, [5, 400, 300, 320]),         # 1025: three launches
+    (64, 2, [5, 200, 100, 271]),         # exactly 576
+    (64, 2, [5, 200, 100, 272]),         # 577: three launches
+    (64, 2, [5, 400, 300, 319]),
+    (64, 2, [5, 400, 300, 320]),
     (128, 1, [5, 40, 33, 178]),
+    (128, 2, [5, 400, 200, 291]),        # exactly 896, 224 work-groups
+    (128, 2, [5, 400, 200, 292]),        # 897: three launches
     (128, 3, [3, 300, 300, 400]),
 ])
 def test_short_float32_units_score_and_select_in_one_launch(head_dim, B, sides_n):
-    """hack_step's kept lists of float32 units around tile, work-group and launch sizes, against the single entry points: float32
-    weights are joined by exact factors instead of being formed anew, 2^-24 relative each way, so a row that only one list
-    has lies within 4 x 2^-24 of the weakest row that both keep.  A second pass gives the same lists."""
+    """hack_step's kept lists of float32 units around tile, work-group and launch sizes, against the single entry points: the same
+    operations in the same order, hence the same lists.  A second pass gives them again."""
     from tests import gpu_util as u
     H = 8
     U = B * H
@@ -653,11 +656,62 @@ def test_short_float32_units_score_and_select_in_one_launch(head_dim, B, sides_n
             for x in range(U):
                 if budget[x] < t_in[x]:
                     lists += 1
-                    a, b = set(kept[x, :ln[x]].tolist()), set(want[x, :ln[x]].tolist())
-                    assert len(a) == ln[x] and kept[x, :ln[x]].tolist() == sorted(a) and max(a) < t_in[x], (step, x)
-                    odd = imp[x][sorted(a ^ b)].double()
-                    assert odd.numel() == 0 or float(odd.max() / odd.min()) < 1 + 4 * 2.0 ** -24 * 2, (step, x)
+                    assert torch.equal(kept[x, :ln[x]], want[x, :ln[x]]), (step, x)
     assert lists > U // 2
+    hk.check()
+    mc.close()
+    hk.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("head_dim,B,n0,n1", [(64, 1, 60, 40), (64, 2, 300, 212), (64, 2, 310, 390), (64, 1, 700, 324), (128, 1, 150, 95), (128, 2, 400, 200)])
+def test_equal_keys_of_short_units_rank_by_index(dtype, head_dim, B, n0, n1):
+    """Every key has a copy some rows further on, in another tile of 16 or 32 keys: equal keys have equal importance, so of a pair
+    of which one is kept it is the lower index, and the lists are those of the single entry points."""
+    from tests import gpu_util as u
+    H, T, n_init = 8, n0 + n1, 5
+    U = B * H
+    hk = u.make_hack(heads=H, head_dim=head_dim, dtype=dtype, max_units=U, max_cache_len=T, max_queries=max(n0, n1))
+    types = np.array([0, 1] * (H // 2), np.uint8)
+    mc = hk.managed_cache(np.full(U, T, np.int32))
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(T)
+    scale, stride = float(np.float32(head_dim ** -0.5)), (T + 63) // 64 * 64
+    never = np.full(U, 10**6, np.int32)
+    pairs = 0
+    for trial, apart in enumerate([16, 17, 37, 16, 37, 48, 17, 33, 16, 37]):
+        q = 3 * torch.randn((B, H, n1, head_dim), generator=gen, device=u.DEV)
+        k, v = (torch.randn((B, H, T, head_dim), generator=gen, device=u.DEV) for _ in range(2))
+        first = torch.arange(T, device=u.DEV) % (2 * apart) < apart
+        first[T - apart:] = True                               # (no copy)
+        lower = torch.nonzero(first & (torch.arange(T, device=u.DEV) + apart < T)).flatten()
+        lower = lower[~first[lower + apart]]
+        k[:, :, lower + apart] = k[:, :, lower]
+        q, k, v = (x.to(hk.torch_dtype) for x in (q, k, v))
+        k0, v0, kn, vn = (x.contiguous() for x in (k[:, :, :n0], v[:, :, :n0], k[:, :, n0:], v[:, :, n0:]))
+        # structural units rank the rows in front of the new ones
+        budget = np.where(np.tile(types, B) == 0, T // 4 + 3 * np.arange(U) + trial, n_init + n1 + n0 // 5 + np.arange(U) + trial)
+        budget = np.minimum(budget, T - 1).astype(np.int32)
+        mc.reset()
+        hk.step(mc, k0, k0, v0, types, never, n_init, scale, torch.empty_like(k0))
+        before = mc.as_cache()
+        src = type(before)(mc.k.clone(), mc.v.clone(), before.off, before.len, mc.pos.clone())
+        kept, want = (torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV) for _ in range(2))
+        hk.step(mc, q, kn, vn, types, budget, n_init, scale, torch.empty_like(q), kept_idx=kept)
+        imp = torch.zeros((U, stride), device=u.DEV)
+        hk.score(q, src, scale, imp, k_new=kn, n_obs=min(32, n1))
+        ln = hk.select(B, imp, src.len + n1, types, budget, n_init, n1, want)
+        torch.cuda.synchronize()
+        assert torch.equal(imp[:, lower], imp[:, lower + apart])
+        for x in range(U):
+            has = torch.zeros(T, dtype=torch.bool, device=u.DEV)
+            has[kept[x, :ln[x]].long()] = True
+            ranked = lower if types[x % H] == 0 else lower[(lower >= n_init) & (lower + apart < n0)]
+            wrong = ranked[has[ranked + apart] & ~has[ranked]]
+            assert wrong.numel() == 0, (trial, x, wrong.tolist())
+            pairs += int((has[ranked] & ~has[ranked + apart]).sum())
+            assert torch.equal(kept[x, :ln[x]], want[x, :ln[x]]), (trial, x)
+    assert pairs > U
     hk.check()
     mc.close()
     hk.close()
