@@ -1168,7 +1168,7 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->streamed = !n.split && g->attn_kernel != kAttnHalves && use_stream_attention(ctx, u.descs, n.N_k, shared, &plan);
   if (!g->streamed && g->attn_kernel != kAttnHalves) build_attn_items(u.descs, n.N_k, n.tile, &items);
   g->small = ctx->cfg.dtype == HACK_BF16 ? use_score_select(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t)
-                                         : launch_score_select_f32 != nullptr && use_score_select_f32(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t);
+                                         : use_score_select_f32(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t);
   if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty() && !g->small)
     g->item_keys = plan_score_items(ctx, u.descs, u.comp, g->two_pass, &sitems, &g->launches);
   // The key-split and the float32 kernel read the rows in place unless they change on the way (merge) or a unit's cache is longer than
@@ -1209,7 +1209,7 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
   if (g.n_comp > 0 && g.small && ctx->cfg.dtype == HACK_F32) {
     launch_score_select_f32(s, ctx->cfg.head_dim, comp_dev, g.n_comp, g.max_t, a.q, reinterpret_cast<const int32_t*>(g.dev + g.o_rows),
                             n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->f32_logits, ctx->stats, ctx->counters, a.kept, a.kstride, ctx->seam);
-  } else if (g.n_comp > 0 && g.small && moves && launch_score_select_move != nullptr) {
+  } else if (g.n_comp > 0 && g.small && moves) {
     launch_score_select_move(s, ctx->cfg.head_dim, comp_dev, g.n_comp, comp_dev + g.n_comp, g.n_desc - g.n_comp, g.max_t, a.q,
                              reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp, a.k_new, a.v_new, a.pos_new,
                              a.kept, a.kstride, ctx->fault);

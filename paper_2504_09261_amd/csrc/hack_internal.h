@@ -167,7 +167,7 @@ void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const 
 
 // fp32: score and selection of short units in one launch.  logits: workspace of kF32GroupLogits doubles per work-group of 64 keys
 // (score_f32_groups(n_units, max_t_in, 64)); stats as launch_score_f32; counters: 2 uint32 per unit of the launch, zero on entry and
-// left zero.  Weak: host code that is linked without the kernels' file goes without.
+// left zero.
 constexpr int kF32GroupLogits = 64 * kMaxObs;
 // Where: units of up to 512 keys (one a thread); longer ones, whose work-groups leave room for one on a compute
 // unit, as far as all of the launch's are resident at once and the last work-group's walk over the unit is shorter than the launches that it
@@ -183,10 +183,9 @@ inline int64_t score_select_f32_max_groups(int max_units, int max_len) {
   const int64_t n = score_f32_groups(max_units, max_len < kF32SmallKeys ? max_len : kF32SmallKeys, 64);
   return n < kF32SmallGroups ? n : kF32SmallGroups;
 }
-__attribute__((weak)) void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in,
-                                                   const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
-                                                   const void* k_cache, const void* k_new, double* logits, double* stats, unsigned* counters,
-                                                   int32_t* kept_idx, int64_t idx_stride, int32_t* seam);
+void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in, const void* q,
+                             const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache, const void* k_new,
+                             double* logits, double* stats, unsigned* counters, int32_t* kept_idx, int64_t idx_stride, int32_t* seam);
 
 // bf16: score and selection of short units in one launch, one work-group per listed unit, no importance in memory.
 bool use_score_select(int head_dim, int n_units, int max_t_in);
@@ -195,12 +194,10 @@ void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, con
                          const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault);
 
 // The same, and the rows of the step moved to where the next step expects them: the kept ones of the n_units compressing units,
-// all new ones of the n_append others (launch_move's work).  Weak as launch_score_select_f32.
-__attribute__((weak)) void launch_score_select_move(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units,
-                                                    const UnitDesc* append_descs, int n_append, int max_t_in, const void* q,
-                                                    const int32_t* q_rows, int n_obs, int N_k, float scale, CachePtrs cache,
-                                                    const void* k_new, const void* v_new, int pos_new, int32_t* kept_idx,
-                                                    int64_t idx_stride, int* fault);
+// all new ones of the n_append others (launch_move's work).
+void launch_score_select_move(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, const UnitDesc* append_descs, int n_append,
+                              int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, CachePtrs cache,
+                              const void* k_new, const void* v_new, int pos_new, int32_t* kept_idx, int64_t idx_stride, int* fault);
 
 // Budgeted selection; one work-group per listed unit.  seam[unit id] (or NULL) gets the number of
 // kept rows below len_in; every unit must then have new rows.

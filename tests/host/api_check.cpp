@@ -41,10 +41,13 @@ struct Setup {
     hack_destroy(ctx);
   }
   hack_status step(int n, int budget, bool final_merge = false, int n_init = 5, void* to = nullptr) {
-    const uint8_t types[kH] = {0, 1, 0, 1};
     const int32_t b[kH] = {budget, budget, budget, budget};
+    return step_each(n, b, final_merge, n_init, to);
+  }
+  hack_status step_each(int n, const int32_t (&budget)[kH], bool final_merge = false, int n_init = 5, void* to = nullptr) {
+    const uint8_t types[kH] = {0, 1, 0, 1};
     auto fn = final_merge ? hack_step_final : hack_step;
-    return fn(ctx, cache, 1, n, q, k, v, types, b, n_init, 0.125f, to ? to : out, nullptr, 0, kStream);
+    return fn(ctx, cache, 1, n, q, k, v, types, budget, n_init, 0.125f, to ? to : out, nullptr, 0, kStream);
   }
   // three steps, the last one compresses
   bool schedule() {
@@ -144,6 +147,68 @@ int out_over_new_rows() {
     CHECK(stub::bad_launches == 0);
     stub::launches.clear();
   }
+  return 0;
+}
+
+// Short units: which launches serve a step that compresses all, some or one of its units, with outputs of their own and over the new
+// rows, eagerly and from a graph; the launch that moves rows gets every unit once, on the side that it belongs to.
+int short_units() {
+  typedef std::vector<std::string> Names;
+  const int32_t all[kH] = {50, 50, 50, 50}, some[kH] = {50, 1 << 30, 1 << 30, 40}, one[kH] = {1 << 30, 1 << 30, 30, 1 << 30};
+  for (int dtype : {HACK_BF16, HACK_F32})
+    for (int over = 0; over < 2; ++over)
+      for (int last = 0; last < (dtype == HACK_BF16 ? 2 : 1); ++last)
+        for (const auto* budget : {&all, &some, &one}) {
+          Setup s(dtype, 96, 128, 64);
+          void* to = over ? s.v : s.out;
+          auto run = [&] {
+            hack_kvcache_reset(s.cache);
+            if (s.step(8, 1 << 30) != HACK_OK || s.step(40, 1 << 30) != HACK_OK) return false;
+            stub::launches.clear();
+            stub::moving_launches.clear();
+            return s.step_each(30, *budget, last == 1, 5, to) == HACK_OK;
+          };
+          const int n_comp = budget == &all ? 4 : budget == &some ? 2 : 1;
+          const bool merges = last == 1, moved = over || merges, f32 = dtype == HACK_F32;   // unit 2, contextual, or units 0 and 2 merge
+          Names want{f32 ? "score_select_f32" : "score_select"};
+          if (moved) want.push_back("move");
+          if (merges) want.push_back("merge");
+          want.push_back(f32 ? (moved ? "attn_f32" : "attn_f32_gather") : moved ? "attn_split" : "attn_split_gather");
+          auto as_wanted = [&] {
+            if (stub::launches != want || stub::bad_launches) return false;
+            if (f32 || !moved) return stub::moving_launches.empty();
+            return stub::moving_launches.size() == 1 && stub::moving_launches[0].n_units == n_comp && stub::moving_launches[0].n_append == kH - n_comp;
+          };
+          CHECK(run() && as_wanted());
+          hack_kvcache_reset(s.cache);
+          CHECK(s.step(8, 1 << 30) == HACK_OK && s.step(40, 1 << 30) == HACK_OK);
+          stub::Graph g;
+          stub::begin_capture(&g, kStream);
+          CHECK(s.step_each(30, *budget, last == 1, 5, to) == HACK_OK);
+          stub::end_capture();
+          for (int replay = 0; replay < 2; ++replay) {
+            stub::launches.clear();
+            stub::moving_launches.clear();
+            stub::replay(g);
+            CHECK(as_wanted());
+          }
+        }
+  // the float32 workspace covers every launch of a context
+  for (int units : {4, 12, 60, 132})
+    for (int max_len : {1, 64, 65, 511, 512, 513, 700, 2048}) {
+      hack_config cfg{0, kH, kD, HACK_F32, units, max_len, 16, 32};
+      hack_ctx* ctx;
+      CHECK(hack_create(&ctx, &cfg) == HACK_OK);
+      const int64_t have = (int64_t)(stub::device_memory.at(ctx->f32_logits) / (kF32GroupLogits * sizeof(double)));
+      const int64_t partials = (int64_t)(stub::device_memory.at(ctx->stats) / (kMaxObs * 2 * sizeof(double)));
+      int64_t most = 0;
+      for (int d : {64, 128})
+        for (int n = 1; n <= units; ++n)
+          for (int t = 1; t <= max_len; ++t)
+            if (use_score_select_f32(d, n, t)) most = std::max(most, score_f32_groups(n, t, 64));
+      CHECK(most <= have && most <= partials && have <= kF32SmallGroups);
+      hack_destroy(ctx);
+    }
   return 0;
 }
 
@@ -292,6 +357,7 @@ int main(int argc, char** argv) {
   int rc = 2;
   if (which == "capture") rc = capture();
   if (which == "out_over_new_rows") rc = out_over_new_rows();
+  if (which == "short_units") rc = short_units();
   if (which == "no_exceptions") rc = no_exceptions();
   if (which == "step_keys") rc = step_keys();
   if (which == "f32_workspace") rc = f32_workspace();

@@ -46,6 +46,19 @@ inline int bad_launches = 0;                  // ... over tables that were never
 inline int copies = 0;                        // asynchronous copies carried out
 inline std::map<void*, size_t> device_memory; // live allocations
 
+struct ShortUnits { int n_units, n_append; };
+inline std::vector<ShortUnits> moving_launches;   // launches that score, select and move the rows of a step
+
+// Whether n bytes from p on lie in one live allocation.
+inline bool owned(const void* p, size_t n) {
+  const char* at = static_cast<const char*>(p);
+  auto it = device_memory.upper_bound(const_cast<void*>(p));
+  if (it == device_memory.begin()) return false;
+  --it;
+  const char* base = static_cast<const char*>(it->first);
+  return at >= base && at + n <= base + it->second;
+}
+
 inline bool captured(void* stream) { return capture != nullptr && stream == capture_stream; }
 inline void submit(void* stream, std::function<void()> f) {
   if (captured(stream)) capture->nodes.push_back(std::move(f));
@@ -162,6 +175,30 @@ void launch_score_fused(hipStream_t s, int, int, bool two_pass, const ScoreItem*
 }
 void launch_score_select(hipStream_t s, int, const UnitDesc* d, const int32_t* l, int n, int, const void*, const int32_t*, int, int, float,
                          const void*, const void*, int32_t*, int64_t, int32_t*, int*) { stub::launch("score_select", s, d, l, n); }
+// The move of such a launch is recorded as the launch that it stands for.
+void launch_score_select_move(hipStream_t s, int, const UnitDesc* d, int n, const UnitDesc* app, int n_app, int max_t, const void*, const int32_t*,
+                              int, int, float, CachePtrs, const void*, const void*, int, int32_t*, int64_t, int*) {
+  stub::launch("score_select", s, d, nullptr, n);
+  stub::launch("move", s, app, nullptr, n_app);
+  stub::Quiet q;
+  stub::submit(s, [=] {
+    stub::moving_launches.push_back({n, n_app});
+    for (int i = 0; i < n; ++i) if (d[i].mode != MOVE_GATHER || d[i].len_in + d[i].n_new > max_t || d[i].n_new < 1) ++stub::bad_launches;
+    for (int i = 0; i < n_app; ++i) if (app[i].mode != MOVE_APPEND) ++stub::bad_launches;
+  });
+}
+void launch_score_select_f32(hipStream_t s, int, const UnitDesc* d, int n, int max_t, const void*, const int32_t*, int, int, float, const void*,
+                             const void*, double* logits, double* stats, unsigned* counters, int32_t*, int64_t, int32_t*) {
+  const size_t groups = (size_t)score_f32_groups(n, max_t, 64);
+  if (!stub::owned(logits, groups * kF32GroupLogits * sizeof(double)) || !stub::owned(stats, groups * kMaxObs * 2 * sizeof(double)) ||
+      !stub::owned(counters, 2 * n * sizeof(unsigned)) || logits == stats)
+    ++stub::bad_launches;
+  stub::launch("score_select_f32", s, d, nullptr, n);
+  stub::Quiet q;
+  stub::submit(s, [=] {
+    for (int i = 0; i < n; ++i) if (d[i].mode != MOVE_GATHER || d[i].len_in + d[i].n_new > max_t || d[i].n_new < 1) ++stub::bad_launches;
+  });
+}
 void launch_score_f32(hipStream_t s, int, const UnitDesc* d, const int32_t* l, int n, int, const void*, const int32_t*, int, int, float,
                       const void*, const void*, double*, float*, int64_t) { stub::launch("score_f32", s, d, l, n); }
 hipError_t launch_score_static(hipStream_t, int, int, const StaticScorePlan&, const void*, int, int, float, const void*, const void*, float*,

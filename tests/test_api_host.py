@@ -32,6 +32,10 @@ def test_steps_whose_outputs_lie_over_the_new_rows_move_them_first(check):
     check("out_over_new_rows")
 
 
+def test_short_units_take_one_launch_and_every_unit_once(check):
+    check("short_units")
+
+
 def test_no_exception_crosses_the_abi_when_host_memory_runs_out(check):
     check("no_exceptions")
 
