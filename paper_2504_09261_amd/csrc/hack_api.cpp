@@ -85,7 +85,7 @@ struct hack_ctx {
   int* fault = nullptr;          // pinned, device-visible int[2]: [0] a score wave's bounded wait gave up (fatal),
                                  // [1] a logit exceeded the range the bf16 score kernel supports
   int score_capacity[4] = {0, 0, 0, 0};   // bf16 path: score items one fused launch may hold (resident waves) for items of 32, 64, 128, 256 keys
-  int split_max_items = 0;       // launches with at most this many 32-query attention items use the key-split kernel
+  int split_max_items = -1;      // launches with at most this many 32-query attention items use the key-split kernel (HACK_ATTN_SPLIT_ITEMS); -1 (default): see use_split_attention
   int attn_kernel = -1;          // bf16 kernel of the 128-query items (kAttnPlain ...); -1 (default): the deeper pipeline, keys in halves where use_key_halves says so
   // streamed form of that kernel: the launch is cut into equal runs of key blocks, one per resident work-group
   int attn_stream = -1;          // HACK_ATTN_STREAM; -1 (default): cut single work items where the pair model gains, 0: never, 1: equal runs
@@ -349,13 +349,11 @@ void build_attn_items(const std::vector<UnitDesc>& descs, int N_k, int tile_rows
 // (30 heads, batch 32), where those items are a few queries each: with more than 128 queries a unit the line lies near
 // 1200 (60 units, split / 128 queries: 576 queries, 1080 items over 300, 800, 2000 keys 14.0 / 13.5, 21.0 / 20.5, 39.8 / 40.9 us;
 // 1024 queries, 1920 items over 800, 2000, 5000 keys 31 / 23, 59 / 45, 138 / 98 us, an append launch 5 to 9).
-constexpr int kSplitItemsManyQueries64 = 1200;
-int split_max_items_default(int head_dim) { return head_dim == 64 ? 2048 : 512; }
+int split_max_items_default(int head_dim, int N_k) { return head_dim != 64 ? 512 : N_k <= kAttnTileRows ? 2048 : 1200; }
 bool use_split_attention(const hack_ctx* ctx, int n_units, int N_k) {
   if (ctx->cfg.dtype != HACK_BF16) return false;
   const int tile = attn_split_q_tile_rows();
-  int limit = ctx->split_max_items;
-  if (ctx->cfg.head_dim == 64 && N_k > kAttnTileRows && limit == split_max_items_default(64)) limit = kSplitItemsManyQueries64;
+  const int limit = ctx->split_max_items >= 0 ? ctx->split_max_items : split_max_items_default(ctx->cfg.head_dim, N_k);
   return (int64_t)n_units * ((N_k + tile - 1) / tile) <= limit;
 }
 
@@ -604,7 +602,6 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   ctx->cfg = *cfg;
   ctx->elem_bytes = cfg->dtype == HACK_F32 ? 4 : 2;
   ctx->ws_stride = round_up(cfg->max_cache_len, 64);
-  ctx->split_max_items = split_max_items_default(cfg->head_dim);
   ctx->spin_limit = kScoreSpinLimit;
   // test hook: a tiny limit makes the score kernel's bounded wait give up (every work-group still exits normally)
   if (const char* v = std::getenv("HACK_SCORE_SPIN_LIMIT")) ctx->spin_limit = std::max(0, std::atoi(v));
@@ -612,7 +609,7 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   // unit run into the (tiny) spin limit deterministically
   if (const char* v = std::getenv("HACK_SCORE_TEST_SKIP_PUBLISH")) ctx->skip_publish = std::atoi(v);
   if (const char* v = std::getenv("HACK_SCORE_MODE")) ctx->score_mode = std::atoi(v) == 1 ? HACK_SCORE_TWO_PASS : HACK_SCORE_FUSED;
-  if (const char* v = std::getenv("HACK_ATTN_SPLIT_ITEMS")) ctx->split_max_items = std::atoi(v);   // tuning / test override
+  if (const char* v = std::getenv("HACK_ATTN_SPLIT_ITEMS")) ctx->split_max_items = std::max(std::atoi(v), 0);   // tuning / test override
   if (const char* v = std::getenv("HACK_STEP_OVERLAP")) ctx->step_overlap = std::atoi(v) != 0;
   if (const char* v = std::getenv("HACK_ATTN_PIPE")) ctx->attn_kernel = std::min(std::max(std::atoi(v), 0), 2);   // A/B and test override
   if (const char* v = std::getenv("HACK_ATTN_STREAM")) ctx->attn_stream = std::atoi(v);       // A/B and test override

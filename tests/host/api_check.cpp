@@ -329,6 +329,31 @@ int step_keys() {
   return 0;
 }
 
+// Which launches the key-split attention kernel serves, and that a limit given in the environment is taken as it is.
+int attn_rule() {
+  const auto variants = [](int head_dim, const char* limit, std::vector<std::pair<int, int>> shapes) {   // (units, queries)
+    if (limit) setenv("HACK_ATTN_SPLIT_ITEMS", limit, 1);
+    hack_config cfg{0, 1, head_dim, HACK_BF16, 4096, 64, 4096, 32};
+    hack_ctx* ctx = nullptr;
+    std::string got;
+    if (hack_create(&ctx, &cfg) != HACK_OK) return got;
+    for (const auto& x : shapes) got += (char)('0' + hack_attn_variant(ctx, x.first, x.second));
+    hack_destroy(ctx);
+    unsetenv("HACK_ATTN_SPLIT_ITEMS");
+    return got;
+  };
+  // head_dim 64: 2048 items of 32 queries, 1200 where a unit has more than 128 queries; head_dim 128: 512
+  CHECK(variants(64, nullptr, {{2048, 32}, {2049, 32}, {512, 128}, {513, 128}, {240, 129}, {241, 129}, {60, 640}, {60, 641}}) == "10101010");
+  CHECK(variants(128, nullptr, {{512, 32}, {513, 32}, {128, 128}, {129, 128}, {102, 129}, {103, 129}}) == "101010");
+  for (const char* limit : {"2047", "2048", "2049"}) {
+    const int n = atoi(limit);
+    CHECK(variants(64, limit, {{n, 32}, {n + 1, 32}, {n / 5, 129}, {n / 5 + 1, 129}, {60, 1024}}) == "10101");
+  }
+  CHECK(variants(64, "0", {{1, 1}, {1, 129}}) == "00" && variants(64, "-1", {{1, 1}}) == "0" && variants(64, "1", {{1, 32}, {1, 33}, {1, 129}}) == "100");
+  CHECK(variants(128, "512", {{512, 32}, {513, 32}, {102, 129}, {103, 129}}) == "1010");
+  return 0;
+}
+
 // The float32 score workspace covers every launch the context accepts (chunk of 64 keys for small ones, 256 beyond) and
 // is no larger than those need.
 int f32_workspace() {
@@ -360,6 +385,7 @@ int main(int argc, char** argv) {
   if (which == "short_units") rc = short_units();
   if (which == "no_exceptions") rc = no_exceptions();
   if (which == "step_keys") rc = step_keys();
+  if (which == "attn_rule") rc = attn_rule();
   if (which == "f32_workspace") rc = f32_workspace();
   if (rc == 0) printf("ok\n");
   return rc;

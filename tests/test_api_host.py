@@ -46,3 +46,7 @@ def test_float32_score_workspace_covers_every_launch_and_no_more(check):
 
 def test_remembered_steps_are_found_by_all_their_arguments(check):
     check("step_keys")
+
+
+def test_attention_kernel_rule_and_its_override(check):
+    check("attn_rule")

@@ -647,7 +647,7 @@ def test_attention_rejects_empty_unit_and_bad_scale():
     hk.close()
 
 
-def test_attention_variant_query_matches_the_documented_rule():
+def test_attention_variant_query_matches_the_documented_rule(monkeypatch):
     u = _u()
     hk = u.make_hack(heads=16, head_dim=128, dtype="bf16", max_units=32, max_cache_len=256, max_queries=4096)
     # 32-query work items of a launch: B*H*ceil(N_k/32); the key-split kernel serves launches up to 512 of them at d = 128
@@ -656,6 +656,11 @@ def test_attention_variant_query_matches_the_documented_rule():
     hk.close()
     hk = u.make_hack(heads=30, head_dim=64, dtype="bf16", max_units=960, max_cache_len=256, max_queries=256)
     assert hk.attn_variant(32, 64) == 1 and hk.attn_variant(32, 100) == 0     # 1920 and 3840 items against 2048 at d = 64
+    assert hk.attn_variant(8, 160) == 1 and hk.attn_variant(8, 161) == 0      # 1200 and 1440 against 1200 beyond 128 queries
+    hk.close()
+    monkeypatch.setenv("HACK_ATTN_SPLIT_ITEMS", "2048")                       # a limit that is given is taken as it is
+    hk = u.make_hack(heads=30, head_dim=64, dtype="bf16", max_units=960, max_cache_len=256, max_queries=256)
+    assert hk.attn_variant(8, 256) == 1 and hk.attn_variant(9, 256) == 0      # 1920 and 2160 items
     hk.close()
     hk = u.make_hack(heads=2, head_dim=64, dtype="f32", max_units=2, max_cache_len=64, max_queries=16)
     assert hk.attn_variant(1, 1) == 0                                          # fp32 contexts have one attention kernel
