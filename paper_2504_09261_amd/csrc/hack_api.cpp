@@ -120,7 +120,7 @@ struct StepGroup {
   unsigned long long* slots = nullptr;    // row-sum exchange area of the group's score launches
   const uint8_t* dev = nullptr;
   size_t table = 0;                       // its number in the table store
-  size_t o_desc = 0, o_comp = 0, o_merge = 0, o_rows = 0, o_items = 0, o_sit = 0, o_segs = 0, o_segb = 0, o_moves = 0;
+  size_t o_desc = 0, o_merge = 0, o_rows = 0, o_items = 0, o_sit = 0, o_segs = 0, o_segb = 0, o_moves = 0;
   const UnitDesc* ddev() const { return reinterpret_cast<const UnitDesc*>(dev + o_desc); }
 };
 
@@ -321,7 +321,10 @@ void build_attn_items(const std::vector<UnitDesc>& descs, int N_k, int tile_rows
   const int n = (int)descs.size();
   std::vector<int> order(n);
   for (int i = 0; i < n; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return descs[a].n_out > descs[b].n_out; });
+  // equal lengths: in the order of the units, wherever their descriptors stand
+  std::sort(order.begin(), order.end(), [&](int a, int b) {
+    return descs[a].n_out != descs[b].n_out ? descs[a].n_out > descs[b].n_out : descs[a].unit < descs[b].unit;
+  });
   const int tiles = (N_k + tile_rows - 1) / tile_rows;
   constexpr int X = 8;
   std::vector<AttnItem> per[X];
@@ -363,6 +366,7 @@ bool use_split_attention(const hack_ctx* ctx, int n_units, int N_k) {
 // 21.4 / 22.0, 29.4 / 27.9, 33.2 / 31.1, 91 / 76; of 17 blocks 20.0 / 21.2.  A compute unit holds one such work-group: beyond one per
 // compute unit of an XCD it loses (416 items 113 / 126).
 constexpr int kHalvesMinBlocks = 28;
+// items: left empty, or the launch's whole work items.
 bool use_key_halves(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, int N_k, std::vector<AttnItem>* items) {
   if (ctx->cfg.dtype != HACK_BF16 || ctx->cfg.head_dim != 128 || (ctx->attn_kernel != -1 && ctx->attn_kernel != kAttnHalves) || ctx->attn_stream > 0) return false;
   const bool forced = ctx->attn_kernel == kAttnHalves;
@@ -374,9 +378,7 @@ bool use_key_halves(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, int
   const int64_t n = (int64_t)descs.size() * ((N_k + kAttnTileRows - 1) / kAttnTileRows);
   if (!forced && (n > ctx->attn_slots / 2 || longest <= (kHalvesMinBlocks - 1) * kAttnKeyBlock)) return false;
   build_attn_items(descs, N_k, kAttnTileRows, items);   // padded to as many for every XCD
-  if (forced || (int)items->size() <= ctx->attn_slots / 2) return true;
-  items->clear();
-  return false;
+  return forced || (int)items->size() <= ctx->attn_slots / 2;
 }
 
 // Queries per attention work item of a launch.
@@ -415,7 +417,9 @@ constexpr double kCutMinGain = 0.05;
 constexpr int kCutMinBlocks = 8;
 constexpr int kStreamOverheadBlocks = 4;   // start and end of a segment, in key blocks of the steady loop
 constexpr int kStreamMinBlocks = 4;        // shortest segment a work item is cut into
-bool use_stream_attention(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, int N_k, bool shared, AttnStreamPlan* plan) {
+// items: the launch's whole work items if they are known, else empty; filled where the decision needed them.
+bool use_stream_attention(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, int N_k, bool shared, std::vector<AttnItem>* items,
+                          AttnStreamPlan* plan) {
   if (ctx->cfg.dtype != HACK_BF16 || ctx->attn_kernel == 0 || ctx->attn_stream == 0 || ctx->attn_slots <= 0 || shared) return false;
   if (descs.empty()) return false;
   const int tile = kAttnTileRows;
@@ -423,15 +427,14 @@ bool use_stream_attention(const hack_ctx* ctx, const std::vector<UnitDesc>& desc
   for (size_t i = 0; i < descs.size(); ++i) n_keys[i] = descs[i].n_out;
   if (ctx->attn_stream == 2) {
     // A/B aid: the streamed kernel on uncut work items, one per work-group, in the order of the plain launch
-    std::vector<AttnItem> items;
-    build_attn_items(descs, N_k, tile, &items);
+    if (items->empty()) build_attn_items(descs, N_k, tile, items);
     plan->segs.clear();
     plan->seg_begin.assign(1, 0);
-    for (const AttnItem& it : items) {
+    for (const AttnItem& it : *items) {
       if (it.desc >= 0) plan->segs.push_back(AttnSeg{it.desc, it.q_tile, 0, 0x3fffffff, -1, 0, 0, 0});
       plan->seg_begin.push_back((int32_t)plan->segs.size());
     }
-    plan->n_groups = (int)items.size();
+    plan->n_groups = (int)items->size();
     plan->n_parts = plan->n_counters = 0;
     return plan->n_groups > 0;
   }
@@ -442,12 +445,12 @@ bool use_stream_attention(const hack_ctx* ctx, const std::vector<UnitDesc>& desc
     const bool forced = ctx->attn_stream == 4;
     // the model's constants were measured for head_dim 128, two work-groups per compute unit
     if (!forced && (ctx->cfg.head_dim != 128 || ctx->attn_slots != 2 * cus)) return false;
-    std::vector<AttnItem> items;
-    build_attn_items(descs, N_k, tile, &items);
+    if (items->empty()) build_attn_items(descs, N_k, tile, items);
     std::vector<AttnLaneItem> lanes[kAttnXcds];
-    for (size_t i = 0; i < items.size(); ++i)
-      if (items[i].desc >= 0)
-        lanes[i % kAttnXcds].push_back(AttnLaneItem{items[i].desc, items[i].q_tile, (items[i].n_out + kAttnKeyBlock - 1) / kAttnKeyBlock});
+    for (size_t i = 0; i < items->size(); ++i) {
+      const AttnItem& it = (*items)[i];
+      if (it.desc >= 0) lanes[i % kAttnXcds].push_back(AttnLaneItem{it.desc, it.q_tile, (it.n_out + kAttnKeyBlock - 1) / kAttnKeyBlock});
+    }
     double before = 0.0, after = 0.0;
     if (!(!forced && plan_attn_tail(lanes, cus / kAttnXcds, plan)) &&
         !plan_attn_cuts(lanes, cus / kAttnXcds, kCutMinBlocks, kPairModel128, forced ? 1e-9 : kCutMinGain, plan, &before, &after)) return false;
@@ -986,8 +989,9 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
   std::vector<AttnItem> items;
   AttnStreamPlan plan;
   const bool halves = !split && use_key_halves(ctx, descs, N_k, &items);
-  const bool streamed = !split && !halves && use_stream_attention(ctx, descs, N_k, false, &plan);
-  if (!streamed && !halves) build_attn_items(descs, N_k, tile, &items);
+  const bool streamed = !split && !halves && use_stream_attention(ctx, descs, N_k, false, &items, &plan);
+  if (streamed) items.clear();
+  else if (items.empty()) build_attn_items(descs, N_k, tile, &items);
   Table t;
   const size_t o_desc = t.add(descs.data(), descs.size());
   const size_t o_items = t.add(items.data(), items.size());
@@ -1114,7 +1118,8 @@ namespace {
 
 // The units of a step that are launched together on one stream, before their tables are uploaded.
 struct GroupUnits {
-  std::vector<UnitDesc> descs;            // copies of the group's unit descriptors
+  std::vector<UnitDesc> descs;            // copies of the group's unit descriptors: the compressing units' stand in front, so that
+                                          // launches over either kind find theirs together
   std::vector<int32_t> comp, merging;     // indices into descs: units that compress / that also merge
 };
 
@@ -1162,8 +1167,9 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   std::vector<ScoreItem> sitems;
   g->attn_kernel = ctx->attn_kernel == kAttnPlain ? kAttnPlain : kAttnPipe;
   if (!n.split && !shared && use_key_halves(ctx, u.descs, n.N_k, &items)) g->attn_kernel = kAttnHalves;
-  g->streamed = !n.split && g->attn_kernel != kAttnHalves && use_stream_attention(ctx, u.descs, n.N_k, shared, &plan);
-  if (!g->streamed && g->attn_kernel != kAttnHalves) build_attn_items(u.descs, n.N_k, n.tile, &items);
+  g->streamed = !n.split && g->attn_kernel != kAttnHalves && use_stream_attention(ctx, u.descs, n.N_k, shared, &items, &plan);
+  if (g->streamed) items.clear();
+  else if (items.empty()) build_attn_items(u.descs, n.N_k, n.tile, &items);
   g->small = ctx->cfg.dtype == HACK_BF16 ? use_score_select(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t)
                                          : use_score_select_f32(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t);
   if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty() && !g->small)
@@ -1185,10 +1191,6 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->n_stream = plan.n_groups;
   Table t;
   g->o_desc = t.add(u.descs.data(), u.descs.size());
-  std::vector<UnitDesc> comp;   // the compressing units' descriptors, together, then the others'
-  for (const int32_t i : u.comp) comp.push_back(u.descs[i]);
-  for (const UnitDesc& d : u.descs) if (d.mode != MOVE_GATHER) comp.push_back(d);
-  g->o_comp = t.add(comp.data(), comp.size());
   g->o_merge = t.add(u.merging.data(), u.merging.size());
   g->o_rows = t.add(rows, kMaxObs);
   g->o_items = t.add(items.data(), items.size());
@@ -1201,26 +1203,25 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
 
 // score -> select -> append / gather (-> merge) of a group's units
 void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
-  const UnitDesc* comp_dev = reinterpret_cast<const UnitDesc*>(g.dev + g.o_comp);
   bool moves = !a.in_place || (!n.fuse_append && !g.gathered);   // rows move in front of the attention launch
   if (g.n_comp > 0 && g.small && ctx->cfg.dtype == HACK_F32) {
-    launch_score_select_f32(s, ctx->cfg.head_dim, comp_dev, g.n_comp, g.max_t, a.q, reinterpret_cast<const int32_t*>(g.dev + g.o_rows),
+    launch_score_select_f32(s, ctx->cfg.head_dim, g.ddev(), g.n_comp, g.max_t, a.q, reinterpret_cast<const int32_t*>(g.dev + g.o_rows),
                             n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->f32_logits, ctx->stats, ctx->counters, a.kept, a.kstride, ctx->seam);
   } else if (g.n_comp > 0 && g.small && moves) {
-    launch_score_select_move(s, ctx->cfg.head_dim, comp_dev, g.n_comp, comp_dev + g.n_comp, g.n_desc - g.n_comp, g.max_t, a.q,
+    launch_score_select_move(s, ctx->cfg.head_dim, g.ddev(), g.n_comp, g.ddev() + g.n_comp, g.n_desc - g.n_comp, g.max_t, a.q,
                              reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp, a.k_new, a.v_new, a.pos_new,
                              a.kept, a.kstride, ctx->fault);
     moves = false;
   } else if (g.n_comp > 0 && g.small) {
-    launch_score_select(s, ctx->cfg.head_dim, comp_dev, nullptr, g.n_comp, g.max_t, a.q,
+    launch_score_select(s, ctx->cfg.head_dim, g.ddev(), nullptr, g.n_comp, g.max_t, a.q,
                         reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, a.kept, a.kstride,
                         ctx->seam, ctx->fault);
   } else if (g.n_comp > 0) {
-    run_score(ctx, s, g.two_pass, g.slots, comp_dev, g.n_comp, g.max_t,
+    run_score(ctx, s, g.two_pass, g.slots, g.ddev(), g.n_comp, g.max_t,
               reinterpret_cast<const ScoreItem*>(g.dev + g.o_sit), g.item_keys, g.launches, a.q,
               reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->importance,
               ctx->ws_stride);
-    launch_select(s, comp_dev, nullptr, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
+    launch_select(s, g.ddev(), nullptr, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
   }
   if (moves)
     launch_move(s, ctx->elem_bytes, ctx->cfg.head_dim, g.ddev(), g.n_desc, g.max_rows, a.cp, a.cp, a.k_new, a.v_new, n.N_k,
@@ -1289,8 +1290,9 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
     if (head_type[h] > 1) return fail(ctx, HACK_EINVAL, "head_type[%d] = %d is not a head class", h, head_type[h]);
   std::unique_ptr<StepNode> n(new StepNode());
   const StepNode& from = *cache->at;
-  std::vector<UnitDesc> descs(U);
-  int n_comp = 0, n_side = 0;
+  std::vector<UnitDesc> descs[2];   // compressing units, the others
+  for (auto& v : descs) v.reserve(U);
+  int n_side = 0;
   n->cur = from.cur;
   n->off = from.off;
   n->len.resize(U);
@@ -1308,7 +1310,6 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
       n->max_budget = std::max(n->max_budget, budget[u]);
       d.mode = MOVE_GATHER; d.n_out = budget[u];
       plan_select(head_type[u % H], (int)T, budget[u], n_init, N_k, &d);
-      ++n_comp;
       if (head_type[u % H] == HACK_CONTEXTUAL) ++n_side;
     } else {
       if (T > cache->cap[u]) return fail(ctx, HACK_ECAPACITY, "unit %d: %lld rows do not fit its slab of %d", u, (long long)T, cache->cap[u]);
@@ -1316,7 +1317,7 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
     }
     d.out_off = n->off[u];
     n->len[u] = d.n_out;
-    descs[u] = d;
+    descs[d.mode == MOVE_GATHER ? 0 : 1].push_back(d);
   }
   n->N_k = N_k;
   n->n_init = n_init;
@@ -1327,7 +1328,7 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
   n->n_obs = std::min(ctx->cfg.n_obs, N_k);
   n->split = use_split_attention(ctx, U, N_k);
   // no unit compresses: the key-split bf16 kernel and the float32 kernel append as well
-  n->fuse_append = (n->split || ctx->cfg.dtype == HACK_F32) && n_comp == 0;
+  n->fuse_append = (n->split || ctx->cfg.dtype == HACK_F32) && descs[0].empty();
   n->tile = attn_tile_rows(ctx, U, N_k);
   int32_t rows[kMaxObs];
   fill_q_rows(nullptr, n->n_obs, N_k, rows);
@@ -1339,11 +1340,13 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
   n->g[0].slots = ctx->rowstat;
   n->g[1].two_pass = true;          // leaves its sums in the slots, hence an exchange area of its own
   n->g[1].slots = ctx->rowstat_side;
-  for (int u = 0; u < U; ++u) {
-    const bool ctxl = head_type[u % H] == HACK_CONTEXTUAL, compresses = descs[u].mode == MOVE_GATHER;
-    const int i = n->two_groups && ctxl && compresses ? 1 : 0;
-    add_unit(&units[i], &n->g[i], descs[u], final_merge && ctxl && compresses, N_k);
+  for (GroupUnits& g : units) g.descs.reserve(U);
+  for (const UnitDesc& d : descs[0]) {
+    const bool ctxl = head_type[d.unit % H] == HACK_CONTEXTUAL;
+    const int i = n->two_groups && ctxl ? 1 : 0;
+    add_unit(&units[i], &n->g[i], d, final_merge && ctxl, N_k);
   }
+  for (const UnitDesc& d : descs[1]) add_unit(&units[0], &n->g[0], d, false, N_k);
   for (int i = 0; i < (n->two_groups ? 2 : 1); ++i) {
     const hack_status st = upload_group(ctx, units[i], *n, n->two_groups, rows, s, &n->g[i]);
     if (st != HACK_OK) return st;

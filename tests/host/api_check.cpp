@@ -329,6 +329,36 @@ int step_keys() {
   return 0;
 }
 
+// The table of a step holds every unit's descriptor once: the compressing units first, either kind in the order of the units.
+int step_tables() {
+  for (int dtype : {HACK_BF16, HACK_F32})
+    for (int long_units = 0; long_units < 2; ++long_units)   // score and selection in one launch, in launches of their own
+      for (int compress = 0; compress < 16; ++compress) {    // bit u: unit u compresses
+        Setup s(dtype, long_units ? 1100 : 96, 1200, 900);
+        const int n[2] = {long_units ? 900 : 40, 30};
+        int32_t budget[kH];
+        for (int u = 0; u < kH; ++u) budget[u] = compress >> u & 1 ? n[0] - u : 1 << 30;
+        CHECK(s.step(n[0], 1 << 30) == HACK_OK && s.step_each(n[1], budget) == HACK_OK);
+        const StepGroup& g = s.cache->at->g[0];
+        const int n_comp = __builtin_popcount(compress);
+        CHECK(g.n_desc == kH && g.n_comp == n_comp);
+        const UnitDesc* d = g.ddev();
+        int at = 0;
+        for (const int kind : {MOVE_GATHER, MOVE_APPEND})
+          for (int u = 0; u < kH; ++u)
+            if ((compress >> u & 1) == (kind == MOVE_GATHER)) {
+              CHECK(d[at].unit == u && d[at].mode == kind);
+              ++at;
+            }
+        int copies = 0;
+        for (size_t o = 0; o + sizeof(UnitDesc) <= stub::copied; o += 16)   // of the step's table
+          for (int u = 0; u < kH; ++u) copies += memcmp(g.dev + o, &d[u], sizeof(UnitDesc)) == 0;
+        CHECK(copies == kH);
+      }
+  CHECK(stub::bad_launches == 0);
+  return 0;
+}
+
 // Which launches the key-split attention kernel serves, and that a limit given in the environment is taken as it is.
 int attn_rule() {
   const auto variants = [](int head_dim, const char* limit, std::vector<std::pair<int, int>> shapes) {   // (units, queries)
@@ -385,6 +415,7 @@ int main(int argc, char** argv) {
   if (which == "short_units") rc = short_units();
   if (which == "no_exceptions") rc = no_exceptions();
   if (which == "step_keys") rc = step_keys();
+  if (which == "step_tables") rc = step_tables();
   if (which == "attn_rule") rc = attn_rule();
   if (which == "f32_workspace") rc = f32_workspace();
   if (rc == 0) printf("ok\n");

@@ -44,6 +44,7 @@ inline void* capture_stream = nullptr;
 inline std::vector<std::string> launches;     // names of the launches carried out
 inline int bad_launches = 0;                  // ... over tables that were never written
 inline int copies = 0;                        // asynchronous copies carried out
+inline size_t copied = 0;                     // bytes of the last one
 inline std::map<void*, size_t> device_memory; // live allocations
 
 struct ShortUnits { int n_units, n_append; };
@@ -129,7 +130,7 @@ hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return hipSucc
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t stream) {
   stub::Quiet q;
   if (stub::captured(stream)) ++stub::capture->copies;
-  stub::submit(stream, [=] { ++stub::copies; memcpy(d, s, n); });
+  stub::submit(stream, [=] { ++stub::copies; stub::copied = n; memcpy(d, s, n); });
   return hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {

@@ -36,6 +36,10 @@ def test_short_units_take_one_launch_and_every_unit_once(check):
     check("short_units")
 
 
+def test_a_step_table_holds_every_unit_once(check):
+    check("step_tables")
+
+
 def test_no_exception_crosses_the_abi_when_host_memory_runs_out(check):
     check("no_exceptions")
 
