@@ -77,7 +77,7 @@ struct hack_ctx {
   size_t n_slots = 0;            // 64-bit words in rowstat
   int score_mode = HACK_SCORE_FUSED;   // hack_score_mode: fused single launch / two launches without in-kernel waits
   int skip_publish = -1;         // test hook: work-group of a fused score launch that withholds its sums
-  unsigned* counters = nullptr;  // bf16 path: [max_units, 2] reader counters, zero between launches
+  unsigned* counters = nullptr;  // [max_units, 2], zero between launches; bf16 path: reader counters, fp32 path: tickets of short units
   float* hv_stats = nullptr;     // head variance: [max_units, max_queries, 2] softmax statistics of every query
   int32_t* merge_nn = nullptr;   // final-step merge (bf16): [max_units, ws_stride] nearest kept row of every cache row
   float* merge_w = nullptr;      //   ... its weight
@@ -461,23 +461,20 @@ bool use_stream_attention(const hack_ctx* ctx, const std::vector<UnitDesc>& desc
   return plan->n_groups > 0 && plan->n_parts <= 2 * ctx->attn_slots && plan->n_counters <= ctx->attn_slots;
 }
 
-int finish_score_plan(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, const std::vector<int32_t>& list, int keys,
-                      bool two_pass, std::vector<ScoreItem>* items, std::vector<int>* group_begin);
-
-// One score work item per chunk of every listed unit, longest units first so the
+// One score work item per chunk of each of the first n units, longest units first so the
 // tail of a launch is made of short units.  All items of a unit go into the same
 // launch group and no group exceeds `capacity` items; group_begin gets the first
 // item of every group plus the total as its last entry.
-void build_score_items(const std::vector<UnitDesc>& descs, const std::vector<int32_t>& list, int item_keys,
-                       int capacity, std::vector<ScoreItem>* items, std::vector<int>* group_begin) {
+void build_score_items(const std::vector<UnitDesc>& descs, int n, int item_keys, int capacity,
+                       std::vector<ScoreItem>* items, std::vector<int>* group_begin) {
   items->clear();
   group_begin->assign(1, 0);
-  std::vector<int> order(list.size());
-  for (size_t i = 0; i < list.size(); ++i) order[i] = (int)i;
-  auto t_in = [&](int pos) { return descs[list[pos]].len_in + descs[list[pos]].n_new; };
+  std::vector<int> order(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  auto t_in = [&](int pos) { return descs[pos].len_in + descs[pos].n_new; };
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return t_in(a) > t_in(b); });
   for (int pos : order) {
-    const UnitDesc& d = descs[list[pos]];
+    const UnitDesc& d = descs[pos];
     const int wgs = ((t_in(pos) + item_keys - 1) / item_keys + 3) / 4;  // 4 items per work-group, same unit
     if ((int)items->size() - group_begin->back() + 4 * wgs > capacity) group_begin->push_back((int)items->size());
     for (int c = 0; c < 4 * wgs; ++c)
@@ -486,7 +483,7 @@ void build_score_items(const std::vector<UnitDesc>& descs, const std::vector<int
   group_begin->push_back((int)items->size());
 }
 
-// bf16: builds the score items of the listed units and returns the item size (keys per wave) chosen.
+// bf16: builds the score items of the first n units and returns the item size (keys per wave) chosen.
 // Smaller items spread a launch over more compute units and shorten every wave's serial tile work, so the
 // smallest size is taken whose items all fit one launch (the fused kernel's work-groups wait for each other
 // inside a launch, so a launch holds at most what the device keeps resident) and whose work-groups per unit the
@@ -518,30 +515,26 @@ int choose_score_item_keys(const hack_ctx* ctx, std::vector<int> t_in) {
   return best_keys ? best_keys : 256;
 }
 
-int plan_score_items(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, const std::vector<int32_t>& list, bool two_pass,
-                     std::vector<ScoreItem>* items, std::vector<int>* group_begin) {
-  std::vector<int> t_in;
-  for (int32_t pos : list) t_in.push_back(descs[pos].len_in + descs[pos].n_new);
-  return finish_score_plan(ctx, descs, list, choose_score_item_keys(ctx, std::move(t_in)), two_pass, items, group_begin);
-}
-
-// Builds the final item list for the chosen size: launch groups for the fused form, one group for the two-pass
+// Builds the item list of the first n units for the size chosen: launch groups for the fused form, one group for the two-pass
 // form (no in-kernel wait: one launch pair holds any number of items).
-int finish_score_plan(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, const std::vector<int32_t>& list, int keys,
-                      bool two_pass, std::vector<ScoreItem>* items, std::vector<int>* group_begin) {
+int plan_score_items(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, int n, bool two_pass, std::vector<ScoreItem>* items,
+                     std::vector<int>* group_begin) {
+  std::vector<int> t_in;
+  for (int i = 0; i < n; ++i) t_in.push_back(descs[i].len_in + descs[i].n_new);
+  const int keys = choose_score_item_keys(ctx, std::move(t_in));
   int idx = 0;
   while ((32 << idx) != keys) ++idx;
-  build_score_items(descs, list, keys, two_pass ? INT32_MAX : ctx->score_capacity[idx], items, group_begin);
+  build_score_items(descs, n, keys, two_pass ? INT32_MAX : ctx->score_capacity[idx], items, group_begin);
   return keys;
 }
 
-// Scores the listed units of a table that is already on the device.
-void run_score(hack_ctx* ctx, hipStream_t s, bool two_pass, unsigned long long* slots, const UnitDesc* ddev, int n_list, int max_t,
+// Scores units whose descriptors are on the device already.
+void run_score(hack_ctx* ctx, hipStream_t s, bool two_pass, unsigned long long* slots, const UnitDesc* ddev, int n_units, int max_t,
                const ScoreItem* items_dev, int item_keys, const std::vector<int>& group_begin, const void* q,
                const int32_t* rows_dev, int n_obs, int N_k, float scale, const void* k_cache, const void* k_new,
                float* importance, int64_t imp_stride) {
   if (ctx->cfg.dtype == HACK_F32) {
-    launch_score_f32(s, ctx->cfg.head_dim, ddev, nullptr, n_list, max_t, q, rows_dev, n_obs, N_k, scale, k_cache, k_new,
+    launch_score_f32(s, ctx->cfg.head_dim, ddev, n_units, max_t, q, rows_dev, n_obs, N_k, scale, k_cache, k_new,
                      ctx->stats, importance, imp_stride);
     return;
   }
@@ -732,7 +725,6 @@ extern "C" hack_status hack_score(hack_ctx* ctx, int32_t B, int32_t N_k, const v
   if ((st = check_cache(ctx, in, U, "in", false)) != HACK_OK) return st;
   const int n_new = k_new ? N_k : 0;
   std::vector<UnitDesc> descs;
-  std::vector<int32_t> list;
   int max_t = 0;
   for (int u = 0; u < U; ++u) {
     if (active && !active[u]) continue;
@@ -742,7 +734,6 @@ extern "C" hack_status hack_score(hack_ctx* ctx, int32_t B, int32_t N_k, const v
     if (T > imp_stride) return fail(ctx, HACK_ECAPACITY, "imp_stride %lld < T_in %lld of unit %d", (long long)imp_stride, (long long)T, u);
     UnitDesc d{};
     d.in_off = in->off[u]; d.out_off = in->off[u]; d.len_in = in->len[u]; d.n_new = n_new; d.n_out = (int)T; d.unit = u;
-    list.push_back((int32_t)descs.size());
     descs.push_back(d);
     max_t = std::max(max_t, (int)T);
   }
@@ -753,7 +744,7 @@ extern "C" hack_status hack_score(hack_ctx* ctx, int32_t B, int32_t N_k, const v
   std::vector<int> groups;
   int item_keys = 0;
   const bool two_pass = ctx->score_mode == HACK_SCORE_TWO_PASS;
-  if (ctx->cfg.dtype == HACK_BF16) item_keys = plan_score_items(ctx, descs, list, two_pass, &sitems, &groups);
+  if (ctx->cfg.dtype == HACK_BF16) item_keys = plan_score_items(ctx, descs, (int)descs.size(), two_pass, &sitems, &groups);
   Table t;
   const size_t o_desc = t.add(descs.data(), descs.size());
   const size_t o_rows = t.add(rows, kMaxObs);
@@ -761,7 +752,7 @@ extern "C" hack_status hack_score(hack_ctx* ctx, int32_t B, int32_t N_k, const v
   const uint8_t* dev;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = table_device(ctx, t, s, &dev)) != HACK_OK) return st;
-  run_score(ctx, s, two_pass, ctx->rowstat, (const UnitDesc*)(dev + o_desc), (int)list.size(), max_t,
+  run_score(ctx, s, two_pass, ctx->rowstat, (const UnitDesc*)(dev + o_desc), (int)descs.size(), max_t,
             (const ScoreItem*)(dev + o_sit), item_keys, groups, q, (const int32_t*)(dev + o_rows), n_obs, N_k, scale, in->k, k_new,
             importance, imp_stride);
   HIP_TRY(ctx, hipGetLastError());
@@ -849,7 +840,7 @@ extern "C" hack_status hack_select(hack_ctx* ctx, int32_t B, const float* import
   const uint8_t* dev;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = table_device(ctx, t, s, &dev)) != HACK_OK) return st;
-  launch_select(s, (const UnitDesc*)(dev + o_desc), nullptr, U, max_t, importance, imp_stride,
+  launch_select(s, (const UnitDesc*)(dev + o_desc), U, max_t, importance, imp_stride,
                 kept_idx, idx_stride, nullptr);
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
@@ -1119,8 +1110,10 @@ namespace {
 // The units of a step that are launched together on one stream, before their tables are uploaded.
 struct GroupUnits {
   std::vector<UnitDesc> descs;            // copies of the group's unit descriptors: the compressing units' stand in front, so that
-                                          // launches over either kind find theirs together
-  std::vector<int32_t> comp, merging;     // indices into descs: units that compress / that also merge
+                                          // launches over either kind find theirs together (through an index list, one more memory round trip
+                                          // each, a 256^2 schedule took 117.3 us instead of 116.7 in float32, 93.3 instead of 92.8 in bf16)
+  int n_comp = 0;                         // units that compress
+  std::vector<int32_t> merging;           // indices into descs: units that also merge
 };
 
 struct StepArgs {
@@ -1146,7 +1139,7 @@ void add_unit(GroupUnits* u, StepGroup* g, const UnitDesc& d, bool merges, int N
   u->descs.push_back(d);
   g->max_keys = std::max(g->max_keys, d.n_out);
   if (d.mode == MOVE_GATHER) {
-    u->comp.push_back(idx);
+    ++u->n_comp;
     g->max_t = std::max(g->max_t, d.len_in + d.n_new);
     g->max_rows = std::max(g->max_rows, d.n_out);
     if (merges) {
@@ -1170,10 +1163,10 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   g->streamed = !n.split && g->attn_kernel != kAttnHalves && use_stream_attention(ctx, u.descs, n.N_k, shared, &items, &plan);
   if (g->streamed) items.clear();
   else if (items.empty()) build_attn_items(u.descs, n.N_k, n.tile, &items);
-  g->small = ctx->cfg.dtype == HACK_BF16 ? use_score_select(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t)
-                                         : use_score_select_f32(ctx->cfg.head_dim, (int)u.comp.size(), g->max_t);
-  if (ctx->cfg.dtype == HACK_BF16 && !u.comp.empty() && !g->small)
-    g->item_keys = plan_score_items(ctx, u.descs, u.comp, g->two_pass, &sitems, &g->launches);
+  g->small = ctx->cfg.dtype == HACK_BF16 ? use_score_select(ctx->cfg.head_dim, u.n_comp, g->max_t)
+                                         : use_score_select_f32(ctx->cfg.head_dim, u.n_comp, g->max_t);
+  if (ctx->cfg.dtype == HACK_BF16 && u.n_comp > 0 && !g->small)
+    g->item_keys = plan_score_items(ctx, u.descs, u.n_comp, g->two_pass, &sitems, &g->launches);
   // The key-split and the float32 kernel read the rows in place unless they change on the way (merge) or a unit's cache is longer than
   // the list of a unit that keeps everything.
   std::vector<MoveItem> moves;
@@ -1185,7 +1178,7 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
         moves.push_back(MoveItem{(int32_t)i, r});
   g->n_moves = (int)moves.size();
   g->n_desc = (int)u.descs.size();
-  g->n_comp = (int)u.comp.size();
+  g->n_comp = u.n_comp;
   g->n_merge = (int)u.merging.size();
   g->n_items = (int)items.size();
   g->n_stream = plan.n_groups;
@@ -1213,7 +1206,7 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
                              a.kept, a.kstride, ctx->fault);
     moves = false;
   } else if (g.n_comp > 0 && g.small) {
-    launch_score_select(s, ctx->cfg.head_dim, g.ddev(), nullptr, g.n_comp, g.max_t, a.q,
+    launch_score_select(s, ctx->cfg.head_dim, g.ddev(), g.n_comp, g.max_t, a.q,
                         reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, a.kept, a.kstride,
                         ctx->seam, ctx->fault);
   } else if (g.n_comp > 0) {
@@ -1221,7 +1214,7 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
               reinterpret_cast<const ScoreItem*>(g.dev + g.o_sit), g.item_keys, g.launches, a.q,
               reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->importance,
               ctx->ws_stride);
-    launch_select(s, g.ddev(), nullptr, g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
+    launch_select(s, g.ddev(), g.n_comp, g.max_t, ctx->importance, ctx->ws_stride, a.kept, a.kstride, ctx->seam);
   }
   if (moves)
     launch_move(s, ctx->elem_bytes, ctx->cfg.head_dim, g.ddev(), g.n_desc, g.max_rows, a.cp, a.cp, a.k_new, a.v_new, n.N_k,

@@ -158,9 +158,9 @@ hipError_t score_static_setup(int device);   // once per device: finds the devic
 hipError_t launch_score_static(hipStream_t s, int device, int head_dim, const StaticScorePlan& plan, const void* q, int n_obs,
                                int N_k, float scale, const void* k_cache, const void* k_new, float* importance,
                                int64_t imp_stride, int* fault);
-// Launches over listed units: list[n_list] indexes descs, or is NULL where the n_list descriptors stand together.
-// fp32: two passes over (chunk of keys, listed unit); stats is a workspace of 64 doubles per work-group (score_f32_groups).
-void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,
+// Launches over the n_units units whose descriptors stand at descs.
+// fp32: two passes over (chunk of keys, unit); stats is a workspace of 64 doubles per work-group (score_f32_groups).
+void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units,
                       int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
                       const void* k_cache, const void* k_new, double* stats, float* importance,
                       int64_t imp_stride);
@@ -187,9 +187,9 @@ void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs,
                              const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache, const void* k_new,
                              double* logits, double* stats, unsigned* counters, int32_t* kept_idx, int64_t idx_stride, int32_t* seam);
 
-// bf16: score and selection of short units in one launch, one work-group per listed unit, no importance in memory.
+// bf16: score and selection of short units in one launch, one work-group per unit, no importance in memory.
 bool use_score_select(int head_dim, int n_units, int max_t_in);
-void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,
+void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in,
                          const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
                          const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault);
 
@@ -199,9 +199,9 @@ void launch_score_select_move(hipStream_t s, int head_dim, const UnitDesc* descs
                               int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, CachePtrs cache,
                               const void* k_new, const void* v_new, int pos_new, int32_t* kept_idx, int64_t idx_stride, int* fault);
 
-// Budgeted selection; one work-group per listed unit.  seam[unit id] (or NULL) gets the number of
+// Budgeted selection; one work-group per unit.  seam[unit id] (or NULL) gets the number of
 // kept rows below len_in; every unit must then have new rows.
-void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list,
+void launch_select(hipStream_t s, const UnitDesc* descs, int n_units,
                    int max_t_in, const float* importance, int64_t imp_stride, int32_t* kept_idx,
                    int64_t idx_stride, int32_t* seam);
 

@@ -189,13 +189,13 @@ __device__ __forceinline__ double tile_importance(const double (&s)[2][4], int g
 
 template <int D, int TPW, int PASS>
 __global__ __launch_bounds__(kThreads) void score_f32(
-    const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, int max_chunks,
+    const UnitDesc* __restrict__ descs, int max_chunks,
     const float* __restrict__ q, const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale,
     const float* __restrict__ k_cache, const float* __restrict__ k_new, double* __restrict__ stats,
     float* __restrict__ importance, int64_t imp_stride) {
   constexpr int C = D / 16;             // 16-byte pieces of a row per lane
   constexpr int kChunk = 64 * TPW;      // keys per work-group
-  const UnitDesc d = listed_desc(descs, list, blockIdx.y);
+  const UnitDesc d = descs[blockIdx.y];
   const int T_in = d.len_in + d.n_new;
   if ((int)blockIdx.x * kChunk >= T_in) return;
   const int n_chunks = (T_in + kChunk - 1) / kChunk;
@@ -848,7 +848,7 @@ __device__ __forceinline__ void move_unit(const UnitDesc& d, const uint32_t* lis
 
 template <int D, int NW, int TILES, bool MOVE>
 __global__ __launch_bounds__(64 * NW) void score_select(
-    const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, const __bf16* __restrict__ q,
+    const UnitDesc* __restrict__ descs, const __bf16* __restrict__ q,
     const int32_t* __restrict__ q_rows, int n_obs, int N_k, float scale, const __bf16* __restrict__ k_cache,
     const __bf16* __restrict__ k_new, int32_t* __restrict__ kept_idx, int64_t idx_stride, int32_t* __restrict__ seam,
     int* __restrict__ fault, int n_units, StepMove mv) {
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(64 * NW) void score_select(
   __shared__ uint32_t keys[64 * NW];
   __shared__ Shared sh;
 
-  const UnitDesc d = listed_desc(descs, list, blockIdx.x);
+  const UnitDesc d = descs[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
@@ -1015,14 +1015,14 @@ __global__ __launch_bounds__(64 * NW) void score_select(
 }
 
 template <int D, int TPW>
-void launch_f32(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in, const float* q,
+void launch_f32(hipStream_t s, const UnitDesc* descs, int n_units, int max_t_in, const float* q,
                 const int32_t* q_rows, int n_obs, int N_k, float scale, const float* k_cache, const float* k_new, double* stats,
                 float* importance, int64_t imp_stride) {
   const int max_chunks = (max_t_in + 64 * TPW - 1) / (64 * TPW);
-  const dim3 grid(max_chunks, n_list);
-  hipLaunchKernelGGL((score_f32<D, TPW, 1>), grid, dim3(kThreads), 0, s, descs, list, max_chunks, q, q_rows, n_obs, N_k, scale,
+  const dim3 grid(max_chunks, n_units);
+  hipLaunchKernelGGL((score_f32<D, TPW, 1>), grid, dim3(kThreads), 0, s, descs, max_chunks, q, q_rows, n_obs, N_k, scale,
                      k_cache, k_new, stats, importance, imp_stride);
-  hipLaunchKernelGGL((score_f32<D, TPW, 2>), grid, dim3(kThreads), 0, s, descs, list, max_chunks, q, q_rows, n_obs, N_k, scale,
+  hipLaunchKernelGGL((score_f32<D, TPW, 2>), grid, dim3(kThreads), 0, s, descs, max_chunks, q, q_rows, n_obs, N_k, scale,
                      k_cache, k_new, stats, importance, imp_stride);
 }
 
@@ -1201,18 +1201,18 @@ bool use_score_select(int head_dim, int n_units, int max_t_in) {
 }
 
 template <bool MOVE>
-static void launch_small(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,
+static void launch_small(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in,
                          const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
                          const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault, int n_append,
                          const StepMove& mv) {
-  if (n_list <= 0) return;
+  if (n_units <= 0) return;
 #define HACK_SMALL(D_, NW_, TILES_)                                                                                          \
-  hipLaunchKernelGGL((score_select<D_, NW_, TILES_, MOVE>), dim3(n_list + n_append), dim3(64 * NW_), 0, s, descs, list, \
+  hipLaunchKernelGGL((score_select<D_, NW_, TILES_, MOVE>), dim3(n_units + n_append), dim3(64 * NW_), 0, s, descs, \
                      (const __bf16*)q, q_rows, n_obs, N_k, scale, (const __bf16*)k_cache, (const __bf16*)k_new, kept_idx, idx_stride, seam, \
-                     fault, n_list, mv)
+                     fault, n_units, mv)
   // one tile a wave while every unit has a compute unit to itself: 30 units of 155 keys 7.6 -> 7.1 us (kernel trace); sixteen waves of
   // one tile lose (60 units of 420 keys 9.2 -> 10.2)
-  const bool few = n_list <= 256;
+  const bool few = n_units <= 256;
   if (head_dim == 64) {
     if (max_t_in <= 256 && few) HACK_SMALL(64, 8, 1);
     else if (max_t_in <= 256) HACK_SMALL(64, 4, 2);
@@ -1226,17 +1226,17 @@ static void launch_small(hipStream_t s, int head_dim, const UnitDesc* descs, con
 #undef HACK_SMALL
 }
 
-void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list, int max_t_in,
+void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in,
                          const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
                          const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault) {
-  launch_small<false>(s, head_dim, descs, list, n_list, max_t_in, q, q_rows, n_obs, N_k, scale, k_cache, k_new, kept_idx, idx_stride,
+  launch_small<false>(s, head_dim, descs, n_units, max_t_in, q, q_rows, n_obs, N_k, scale, k_cache, k_new, kept_idx, idx_stride,
                       seam, fault, 0, StepMove{});
 }
 
 void launch_score_select_move(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, const UnitDesc* append_descs, int n_append,
                               int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, CachePtrs cache,
                               const void* k_new, const void* v_new, int pos_new, int32_t* kept_idx, int64_t idx_stride, int* fault) {
-  launch_small<true>(s, head_dim, descs, nullptr, n_units, max_t_in, q, q_rows, n_obs, N_k, scale, cache.k, k_new, kept_idx, idx_stride,
+  launch_small<true>(s, head_dim, descs, n_units, max_t_in, q, q_rows, n_obs, N_k, scale, cache.k, k_new, kept_idx, idx_stride,
                      nullptr, fault, n_append, StepMove{append_descs, cache, (const __bf16*)v_new, pos_new});
 }
 
@@ -1258,14 +1258,14 @@ void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs,
 #undef HACK_SMALL
 }
 
-void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, const int32_t* list, int n_list,
+void launch_score_f32(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units,
                       int max_t_in, const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale,
                       const void* k_cache, const void* k_new, double* stats, float* importance,
                       int64_t imp_stride) {
-  if (n_list <= 0 || max_t_in <= 0) return;
-  const bool small = score_f32_chunk(n_list, max_t_in) == 64;
+  if (n_units <= 0 || max_t_in <= 0) return;
+  const bool small = score_f32_chunk(n_units, max_t_in) == 64;
   typedef float T;
-#define HACK_ARGS s, descs, list, n_list, max_t_in, (const T*)q, q_rows, n_obs, N_k, scale, (const T*)k_cache, (const T*)k_new, \
+#define HACK_ARGS s, descs, n_units, max_t_in, (const T*)q, q_rows, n_obs, N_k, scale, (const T*)k_cache, (const T*)k_new, \
                   stats, importance, imp_stride
   if (head_dim == 64) {
     if (small) launch_f32<64, 1>(HACK_ARGS);

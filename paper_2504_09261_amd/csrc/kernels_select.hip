@@ -39,14 +39,14 @@ using namespace dev;
 // NT threads, PER keys each (T <= NT * PER); digits of B0, B1 and 32 - B0 - B1 bits.
 template <int NT, int PER, int B0, int B1>
 __global__ __launch_bounds__(NT) void select_kernel(
-    const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list,
+    const UnitDesc* __restrict__ descs,
     const float* __restrict__ importance, int64_t imp_stride, int32_t* __restrict__ kept_idx,
     int64_t idx_stride, int32_t* __restrict__ seam) {
   using Shared = SelectShared<NT, B0, B1>;
   __shared__ __attribute__((aligned(16))) uint32_t hist[Shared::kHist];
   __shared__ Shared sh;
 
-  const UnitDesc d = listed_desc(descs, list, blockIdx.x);
+  const UnitDesc d = descs[blockIdx.x];
   const float* imp = importance + (int64_t)d.unit * imp_stride;
   int32_t* out = kept_idx + (int64_t)d.unit * idx_stride;
   const int tid = threadIdx.x;
@@ -89,12 +89,12 @@ __global__ __launch_bounds__(NT) void select_kernel(
 
 }  // namespace
 
-void launch_select(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_list,
+void launch_select(hipStream_t s, const UnitDesc* descs, int n_units,
                    int max_t_in, const float* importance, int64_t imp_stride, int32_t* kept_idx,
                    int64_t idx_stride, int32_t* seam) {
-  if (n_list <= 0) return;
+  if (n_units <= 0) return;
 #define HACK_SELECT(NT_, PER_, B0_, B1_)                                                                                      \
-  hipLaunchKernelGGL((select_kernel<NT_, PER_, B0_, B1_>), dim3(n_list), dim3(NT_), 0, s, descs, list, importance, imp_stride, \
+  hipLaunchKernelGGL((select_kernel<NT_, PER_, B0_, B1_>), dim3(n_units), dim3(NT_), 0, s, descs, importance, imp_stride, \
                      kept_idx, idx_stride, seam)
   if (max_t_in <= 1024) HACK_SELECT(512, 2, 11, 11);
   else if (max_t_in <= 2048) HACK_SELECT(1024, 2, 12, 10);

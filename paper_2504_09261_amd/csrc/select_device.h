@@ -12,12 +12,6 @@
 namespace hack {
 namespace dev {
 
-// Descriptor i of a launch over listed units.  Without a list the descriptors stand together, which spares a memory round
-// trip at the head of launches that are chains of such (float32 256^2 schedule with twelve of them 117.3 -> 116.7 us, bf16 93.3 -> 92.8).
-__device__ __forceinline__ UnitDesc listed_desc(const UnitDesc* descs, const int32_t* list, int i) {
-  return descs[list == nullptr ? i : list[i]];
-}
-
 __device__ __forceinline__ uint32_t orderable(float f) {
   uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);

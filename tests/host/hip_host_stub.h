@@ -162,8 +162,8 @@ hipError_t score_static_setup(int) { return hipSuccess; }
 
 void launch_move(hipStream_t s, int, int, const UnitDesc* d, int n, int, CachePtrs, CachePtrs, const void*, const void*, int, int,
                  const int32_t*, int64_t) { stub::launch("move", s, d, nullptr, n); }
-void launch_select(hipStream_t s, const UnitDesc* d, const int32_t* l, int n, int, const float*, int64_t, int32_t*, int64_t, int32_t*) {
-  stub::launch("select", s, d, l, n);
+void launch_select(hipStream_t s, const UnitDesc* d, int n, int, const float*, int64_t, int32_t*, int64_t, int32_t*) {
+  stub::launch("select", s, d, nullptr, n);
 }
 void launch_score_fused(hipStream_t s, int, int, bool two_pass, const ScoreItem* items, int n, const void*, const int32_t*, int, int, float,
                         const void*, const void*, unsigned long long*, int, unsigned*, float*, int64_t, int*, int, const unsigned*, int) {
@@ -174,8 +174,8 @@ void launch_score_fused(hipStream_t s, int, int, bool two_pass, const ScoreItem*
       if (items[i].t_in < 1 || items[i].n_groups < 1 || items[i].n_groups > 64) { ++stub::bad_launches; return; }
   });
 }
-void launch_score_select(hipStream_t s, int, const UnitDesc* d, const int32_t* l, int n, int, const void*, const int32_t*, int, int, float,
-                         const void*, const void*, int32_t*, int64_t, int32_t*, int*) { stub::launch("score_select", s, d, l, n); }
+void launch_score_select(hipStream_t s, int, const UnitDesc* d, int n, int, const void*, const int32_t*, int, int, float,
+                         const void*, const void*, int32_t*, int64_t, int32_t*, int*) { stub::launch("score_select", s, d, nullptr, n); }
 // The move of such a launch is recorded as the launch that it stands for.
 void launch_score_select_move(hipStream_t s, int, const UnitDesc* d, int n, const UnitDesc* app, int n_app, int max_t, const void*, const int32_t*,
                               int, int, float, CachePtrs, const void*, const void*, int, int32_t*, int64_t, int*) {
@@ -200,8 +200,8 @@ void launch_score_select_f32(hipStream_t s, int, const UnitDesc* d, int n, int m
     for (int i = 0; i < n; ++i) if (d[i].mode != MOVE_GATHER || d[i].len_in + d[i].n_new > max_t || d[i].n_new < 1) ++stub::bad_launches;
   });
 }
-void launch_score_f32(hipStream_t s, int, const UnitDesc* d, const int32_t* l, int n, int, const void*, const int32_t*, int, int, float,
-                      const void*, const void*, double*, float*, int64_t) { stub::launch("score_f32", s, d, l, n); }
+void launch_score_f32(hipStream_t s, int, const UnitDesc* d, int n, int, const void*, const int32_t*, int, int, float,
+                      const void*, const void*, double*, float*, int64_t) { stub::launch("score_f32", s, d, nullptr, n); }
 hipError_t launch_score_static(hipStream_t, int, int, const StaticScorePlan&, const void*, int, int, float, const void*, const void*, float*,
                                int64_t, int*) { return hipSuccess; }
 void launch_attn(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const void*, const void*, const void*, int, float, void*, int) {
