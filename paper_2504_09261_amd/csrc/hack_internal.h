@@ -245,8 +245,19 @@ void launch_attn_stream(hipStream_t s, int head_dim, const UnitDesc* descs, cons
 // work-group on a compute unit, and below twenty blocks the larger merge costs what the shorter walk gains.  Measured, us a launch,
 // four / eight waves, 128 work items of 22, 47, 125 blocks: head_dim 64 7.9 / 7.1, 11.9 / 9.9, 25.4 / 19.4; 128 10.7 / 10.4, 16.6 / 14.6,
 // 34.8 / 28.1; 256 items of 13 and 22: 64 6.7 / 6.7, 8.2 / 7.6; 128 9.4 / 9.9, 11.6 / 11.5; 480 items of 22: 10.4 / 11.0; 16.3 / 21.9.
-// The rule counts the attention's own work-groups only: a step gives the bits of hack_attn over the rows that it kept.
-inline bool attn_split_in_eight(int n_items, int max_keys) { return max_keys > 20 * 32 && n_items <= 256; }
+// The work-groups beside them that move a step's rows have the same LDS, so at head_dim 128 they also take a compute unit each, and where
+// attention leaves few of those they become a round of their own (a few per unit: units stand for them).  Whole compressing
+// steps, four / eight waves, items + units: 192 + 32, 700, 1500, 3000 keys 26.9 / 24.9, 37.1 / 34.7, 56.6 / 48.9 us; 224 + 16 26.7 / 24.9, 35.1 / 31.5,
+// 52.9 / 45.8; 224 + 32 27.1 / 27.6, 37.5 / 36.8, 57.2 / 54.0; 192 + 64 30.1 / 30.5, 44.0 / 43.9, 75.0 / 71.4; 256 + 16 26.7 / 27.5, 34.8 / 33.9, 53.6 / 51.3;
+// 256 + 32 27.3 / 28.8, 38.3 / 40.2, 58.2 / 59.6; 192 + 96 34.5 / 36.0, 56.4 / 58.0, 110.8 / 113.0; 256 + 64 30.6 / 34.1, 43.3 / 48.9, 73.6 / 80.2
+// (moves in a launch in front, eight waves: 700 and 1500 keys of 256 + 32 29.7, 40.7; 3000 of 256 + 64 81.6).
+// hack_attn alone would take eight waves on to 256 items (256 + 32: 10.9 / 10.7, 16.3 / 14.7, 26.9 / 24.0), but the number of waves
+// decides how the keys are summed, and a step gives the bits of hack_attn over the rows that it kept.
+inline bool attn_split_in_eight(int head_dim, int n_items, int n_units, int max_keys) {
+  if (max_keys <= 20 * 32 || n_items > 256) return false;
+  const int busy = n_items + n_units;
+  return head_dim == 64 || busy <= 240 || (busy <= 272 && max_keys > 32 * 32);
+}
 enum : int { kSplitAppend = 1, kSplitEight = 2 };
 int attn_split_q_tile_rows();
 void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,

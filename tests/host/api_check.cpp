@@ -384,6 +384,51 @@ int attn_rule() {
   return 0;
 }
 
+// Waves of a key-split work-group: a step that compresses to n_keys rows and hack_attn over as many take the same number (the bits depend
+// on it), eight where that is the faster one for both.
+int split_waves() {
+  struct Case { int head_dim, units, queries, keys, waves; };
+  const Case cases[] = {
+      {64, 32, 32, 640, 4}, {64, 32, 32, 641, 8}, {64, 64, 128, 700, 8}, {64, 72, 128, 700, 4}, {64, 256, 32, 2000, 8},
+      {128, 16, 64, 640, 4}, {128, 16, 64, 641, 8}, {128, 32, 160, 700, 8}, {128, 32, 192, 700, 8}, {128, 16, 448, 700, 8},
+      // compute units left for the work-groups that move a step's rows
+      {128, 32, 224, 1024, 4}, {128, 32, 224, 1025, 8}, {128, 16, 512, 700, 4}, {128, 16, 512, 1500, 8}, {128, 64, 96, 700, 4},
+      {128, 64, 96, 1500, 8}, {128, 32, 256, 700, 4}, {128, 32, 256, 1500, 4}, {128, 64, 128, 3000, 4}, {128, 96, 64, 1500, 4}, {128, 128, 64, 3000, 4},
+  };
+  std::vector<uint8_t> mem(64 << 20);
+  void* p = reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(mem.data()) + 63) / 64 * 64);
+  uint8_t* const fresh = static_cast<uint8_t*>(p);
+  for (const Case& c : cases) {
+    hack_config cfg{0, c.units, c.head_dim, HACK_BF16, c.units, c.keys + c.queries, std::max(c.keys, c.queries), 32};
+    hack_ctx* ctx;
+    CHECK(hack_create(&ctx, &cfg) == HACK_OK);
+    const std::vector<int32_t> cap(c.units, c.keys), all(c.units, 1 << 30);
+    const std::vector<uint8_t> types(c.units, 0);
+    int64_t rows;
+    hack_kvcache* cache;
+    CHECK(hack_kvcache_rows_required(c.units, cap.data(), &rows) == HACK_OK);
+    CHECK(hack_kvcache_create(ctx, c.units, cap.data(), p, p, nullptr, rows, &cache) == HACK_OK);
+    auto step = [&](int n, const std::vector<int32_t>& b) {
+      return hack_step(ctx, cache, 1, n, fresh, fresh, fresh, types.data(), b.data(), 5, 0.1f, fresh + (48 << 20), nullptr, 0, kStream);
+    };
+    CHECK(step(c.keys, all) == HACK_OK);
+    stub::waves.clear();
+    stub::launches.clear();
+    CHECK(step(c.queries, cap) == HACK_OK);
+    CHECK(stub::launches.back() == "attn_split_gather");
+    hack_cache view;
+    CHECK(hack_kvcache_view(cache, &view) == HACK_OK);
+    CHECK(hack_attn(ctx, 1, c.queries, fresh, &view, 0.1f, fresh, kStream) == HACK_OK);
+    if (stub::waves != std::vector<int>{c.waves, c.waves}) {
+      printf("head_dim %d, %d units, %d queries, %d keys: %d and %d waves\n", c.head_dim, c.units, c.queries, c.keys, stub::waves[0], stub::waves[1]);
+      return 1;
+    }
+    hack_kvcache_destroy(cache);
+    hack_destroy(ctx);
+  }
+  return 0;
+}
+
 // The float32 score workspace covers every launch the context accepts (chunk of 64 keys for small ones, 256 beyond) and
 // is no larger than those need.
 int f32_workspace() {
@@ -416,6 +461,7 @@ int main(int argc, char** argv) {
   if (which == "no_exceptions") rc = no_exceptions();
   if (which == "step_keys") rc = step_keys();
   if (which == "step_tables") rc = step_tables();
+  if (which == "split_waves") rc = split_waves();
   if (which == "attn_rule") rc = attn_rule();
   if (which == "f32_workspace") rc = f32_workspace();
   if (rc == 0) printf("ok\n");

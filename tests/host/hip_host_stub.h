@@ -41,6 +41,7 @@ struct Graph {
 };
 inline Graph* capture = nullptr;              // graph being recorded, of stream capture_stream
 inline void* capture_stream = nullptr;
+inline std::vector<int> waves;                // ... of a work-group of each key-split attention launch
 inline std::vector<std::string> launches;     // names of the launches carried out
 inline int bad_launches = 0;                  // ... over tables that were never written
 inline int copies = 0;                        // asynchronous copies carried out
@@ -217,10 +218,17 @@ void launch_attn_stream(hipStream_t s, int, const UnitDesc*, const AttnSeg*, con
 }
 void launch_attn_split(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const void*, const void*, const void*, const void*,
                        const void*, void*, void*, int32_t*, int, int fuse, int, float, void*) {
-  stub::launch_items(fuse ? "attn_split_append" : "attn_split", s, it, n);
+  stub::launch_items(fuse & kSplitAppend ? "attn_split_append" : "attn_split", s, it, n);
+  stub::Quiet q;
+  stub::submit(s, [=] { stub::waves.push_back(fuse & kSplitEight ? 8 : 4); });
 }
-void launch_attn_split_gather(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const GatherArgs&, const void*, const void*,
-                              const void*, int, float, void*) { stub::launch_items("attn_split_gather", s, it, n); }
+void launch_attn_split_gather(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const GatherArgs& g, const void*,
+                              const void*, const void*, int, float, void*) {
+  stub::launch_items("attn_split_gather", s, it, n);
+  stub::Quiet q;
+  const bool eight = g.eight;
+  stub::submit(s, [=] { stub::waves.push_back(eight ? 8 : 4); });
+}
 void launch_attn_f32(hipStream_t s, int, const AttnItem* it, int n, int, const void*, const void*, const void*, const void*, const void*,
                      void*, void*, int32_t*, int, int fuse, int, float, void*) {
   stub::launch_items(fuse ? "attn_f32_append" : "attn_f32", s, it, n);

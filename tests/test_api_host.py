@@ -54,3 +54,7 @@ def test_remembered_steps_are_found_by_all_their_arguments(check):
 
 def test_attention_kernel_rule_and_its_override(check):
     check("attn_rule")
+
+
+def test_a_step_and_single_attention_take_the_same_waves(check):
+    check("split_waves")

@@ -546,6 +546,7 @@ def test_cut_and_streamed_attention_launches_agree_with_whole_work_items():
 @pytest.mark.parametrize("H,Nk,lens", [
     (3, 33, [1, 32, 33]), (3, 5, [640, 640, 31]), (4, 40, [641, 1, 32, 2049]), (2, 100, [672, 700]), (3, 64, [1, 897, 4001]),
     (65, 128, [641] * 65), (64, 128, [641] * 63 + [7]),     # 260 and 256 work items, the line between four and eight waves
+    (48, 128, [641] * 47 + [7]), (32, 224, [1025] * 31 + [9]), (32, 224, [1024] * 32),   # ... and at head_dim 128: 240 and 256 items + units
 ])
 def test_key_split_attention_block_and_wave_edges(d, H, Nk, lens):
     """Key-split work items of one block, of fewer and of more blocks than waves, with four and with eight waves."""
