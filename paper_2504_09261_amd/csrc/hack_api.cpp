@@ -349,15 +349,21 @@ void build_attn_items(const std::vector<UnitDesc>& descs, int N_k, int tile_rows
 // that the 128-query kernel, which shares every K/V block among four times as
 // many queries, is faster.  Measured cross-overs on MI355X: head_dim 128 between
 // 416 and 576 items (16 heads, batch 2); head_dim 64 between 1920 and 3840 items
-// (30 heads, batch 32), where those items are a few queries each: with more than 128 queries a unit the line lies near
-// 1200 (60 units, split / 128 queries: 576 queries, 1080 items over 300, 800, 2000 keys 14.0 / 13.5, 21.0 / 20.5, 39.8 / 40.9 us;
-// 1024 queries, 1920 items over 800, 2000, 5000 keys 31 / 23, 59 / 45, 138 / 98 us, an append launch 5 to 9).
-int split_max_items_default(int head_dim, int N_k) { return head_dim != 64 ? 512 : N_k <= kAttnTileRows ? 2048 : 1200; }
+// (30 heads, batch 32).  At head_dim 64 tiles of 128 queries win earlier where they are nearly full and all start together.  Whole steps,
+// split / 128 queries, us; compressing to 102 and 1200 rows, appending to as many: 960 queries, 1800 items 26.4 / 25.5, 59.3 / 52.8; 56.9 / 46.0,
+// 81.1 / 64.2; 900, 1450 23.8 / 23.3, 53.8 / 49.4; 46.7 / 41.8, 69.7 / 58.2; 512, 1920 26.6 / 25.8, 66.7 / 62.3; 39.5 / 33.1, 65.3 / 51.8; 256, 1920
+// 21.9 / 19.6, 88.2 / 84.1; 26.6 / 24.6, 57.0 / 46.7; 256, 1600 20.5 / 18.6, 78.0 / 79.6; 22.6 / 22.9, 47.9 / 42.9; 256, 1440 20.0 / 18.5, 70.1 / 74.0;
+// 20.9 / 22.4, 40.9 / 38.3; 256, 1280 18.5 / 17.7, 58.7 / 64.3; 18.5 / 20.5, 37.9 / 39.3.  In two rounds of them or part empty they lose: 576, 1980 27.2 / 27.2,
+// 63.6 / 66.5; 41.1 / 43.1, 66.7 / 67.8; 224, 1960 25.6 / 24.8, 92.1 / 96.7; 24.7 / 29.0, 51.4 / 53.6; 140, 2000 24.6 / 25.9, 131 / 146; 21.9 / 29.1, 52.3 / 64.9.
 bool use_split_attention(const hack_ctx* ctx, int n_units, int N_k) {
   if (ctx->cfg.dtype != HACK_BF16) return false;
   const int tile = attn_split_q_tile_rows();
-  const int limit = ctx->split_max_items >= 0 ? ctx->split_max_items : split_max_items_default(ctx->cfg.head_dim, N_k);
-  return (int64_t)n_units * ((N_k + tile - 1) / tile) <= limit;
+  const int64_t items = (int64_t)n_units * ((N_k + tile - 1) / tile);
+  if (ctx->split_max_items >= 0) return items <= ctx->split_max_items;
+  if (ctx->cfg.head_dim != 64) return items <= 512;
+  const int64_t large = (int64_t)n_units * ((N_k + kAttnTileRows - 1) / kAttnTileRows);   // items of 128 queries
+  if (N_k > kAttnTileRows && items > (N_k > 512 ? 1400 : 1500) && large <= 512 && 5 * items >= 18 * large) return false;
+  return items <= 2048;
 }
 
 // Launches of 128-query work items that leave a compute unit one of them take the form that walks the two halves of the keys

@@ -372,8 +372,11 @@ int attn_rule() {
     unsetenv("HACK_ATTN_SPLIT_ITEMS");
     return got;
   };
-  // head_dim 64: 2048 items of 32 queries, 1200 where a unit has more than 128 queries; head_dim 128: 512
-  CHECK(variants(64, nullptr, {{2048, 32}, {2049, 32}, {512, 128}, {513, 128}, {240, 129}, {241, 129}, {60, 640}, {60, 641}}) == "10101010");
+  // head_dim 64: 2048 items of 32 queries, fewer where tiles of 128 queries are well filled and start together; head_dim 128: 512
+  CHECK(variants(64, nullptr, {{2048, 32}, {2049, 32}, {512, 128}, {513, 128}}) == "1010");
+  CHECK(variants(64, nullptr, {{187, 256}, {188, 256}, {256, 256}, {257, 256}, {48, 900}, {49, 900}, {77, 576}, {78, 576}, {60, 1024}}) == "100010100");
+  CHECK(variants(64, nullptr, {{300, 160}, {409, 130}, {410, 130}, {400, 140}, {341, 192}, {342, 192}, {280, 224}, {156, 400}}) == "11011011");   // half-empty tiles
+  CHECK(variants(64, nullptr, {{102, 576}, {103, 576}, {113, 576}, {114, 576}}) == "0110");   // 510 and 515 of 128 queries
   CHECK(variants(128, nullptr, {{512, 32}, {513, 32}, {128, 128}, {129, 128}, {102, 129}, {103, 129}}) == "101010");
   for (const char* limit : {"2047", "2048", "2049"}) {
     const int n = atoi(limit);

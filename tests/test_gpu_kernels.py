@@ -657,7 +657,8 @@ def test_attention_variant_query_matches_the_documented_rule(monkeypatch):
     hk.close()
     hk = u.make_hack(heads=30, head_dim=64, dtype="bf16", max_units=960, max_cache_len=256, max_queries=256)
     assert hk.attn_variant(32, 64) == 1 and hk.attn_variant(32, 100) == 0     # 1920 and 3840 items against 2048 at d = 64
-    assert hk.attn_variant(8, 160) == 1 and hk.attn_variant(8, 161) == 0      # 1200 and 1440 against 1200 beyond 128 queries
+    assert hk.attn_variant(6, 256) == 1 and hk.attn_variant(8, 256) == 0      # 1440 and 1920 against 1500 where tiles of 128 queries are full
+    assert hk.attn_variant(8, 224) == 1                                        # 1680; they are not
     hk.close()
     monkeypatch.setenv("HACK_ATTN_SPLIT_ITEMS", "2048")                       # a limit that is given is taken as it is
     hk = u.make_hack(heads=30, head_dim=64, dtype="bf16", max_units=960, max_cache_len=256, max_queries=256)
