@@ -432,6 +432,40 @@ int split_waves() {
   return 0;
 }
 
+// 128-query launches of at most one work item per compute unit: the two halves of the keys side by side where most items are long,
+// whole items (the long ones cut) where few are.
+int key_halves() {
+  struct Case { int units, tiles, n_long, long_blocks, short_blocks; bool halves; };
+  const Case cases[] = {
+      {32, 8, 32, 79, 79, true}, {32, 8, 20, 79, 61, true}, {32, 5, 32, 41, 41, true}, {16, 16, 16, 28, 28, true}, {16, 16, 16, 27, 27, false},
+      {8, 32, 2, 160, 16, true},      // one unit an XCD: the long ones' XCDs hold nothing else
+      {16, 15, 8, 160, 16, false}, {32, 8, 8, 80, 24, false}, {32, 6, 8, 160, 80, false}, {64, 4, 16, 160, 80, false}, {32, 5, 16, 80, 24, false},
+      {33, 8, 33, 79, 79, false},     // 264 items
+      {32, 8, 31, 79, 1, false},      // a unit of one block has no second half
+  };
+  std::vector<uint8_t> mem(64);
+  void* p = reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(mem.data()) + 15) / 16 * 16);
+  for (const Case& c : cases) {
+    hack_config cfg{0, c.units, 128, HACK_BF16, c.units, 8192, 4096, 32};
+    hack_ctx* ctx;
+    CHECK(hack_create(&ctx, &cfg) == HACK_OK);
+    std::vector<int64_t> off(c.units);
+    std::vector<int32_t> len(c.units, 32 * c.short_blocks);
+    for (int i = 0; i < c.n_long; ++i) len[i * c.units / c.n_long] = 32 * c.long_blocks;
+    for (int u = 0; u < c.units; ++u) off[u] = 8192 * u;
+    const hack_cache kv{p, p, nullptr, 8192 * c.units, off.data(), len.data()};
+    stub::launches.clear();
+    CHECK(hack_attn(ctx, 1, 128 * c.tiles, p, &kv, 0.1f, p, kStream) == HACK_OK);
+    const bool halves = stub::launches.back() == "attn_halves";
+    hack_destroy(ctx);
+    if (halves != c.halves) {
+      printf("%d units of %d tiles, %d of %d blocks and the rest of %d: %s\n", c.units, c.tiles, c.n_long, c.long_blocks, c.short_blocks, stub::launches.back().c_str());
+      return 1;
+    }
+  }
+  return 0;
+}
+
 // The float32 score workspace covers every launch the context accepts (chunk of 64 keys for small ones, 256 beyond) and
 // is no larger than those need.
 int f32_workspace() {
@@ -465,6 +499,7 @@ int main(int argc, char** argv) {
   if (which == "step_keys") rc = step_keys();
   if (which == "step_tables") rc = step_tables();
   if (which == "split_waves") rc = split_waves();
+  if (which == "key_halves") rc = key_halves();
   if (which == "attn_rule") rc = attn_rule();
   if (which == "f32_workspace") rc = f32_workspace();
   if (rc == 0) printf("ok\n");

@@ -205,8 +205,8 @@ void launch_score_f32(hipStream_t s, int, const UnitDesc* d, int n, int, const v
                       const void*, const void*, double*, float*, int64_t) { stub::launch("score_f32", s, d, nullptr, n); }
 hipError_t launch_score_static(hipStream_t, int, int, const StaticScorePlan&, const void*, int, int, float, const void*, const void*, float*,
                                int64_t, int*) { return hipSuccess; }
-void launch_attn(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const void*, const void*, const void*, int, float, void*, int) {
-  stub::launch_items("attn", s, it, n);
+void launch_attn(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const void*, const void*, const void*, int, float, void*, int kernel) {
+  stub::launch_items(kernel == kAttnHalves ? "attn_halves" : "attn", s, it, n);
 }
 void launch_attn_stream(hipStream_t s, int, const UnitDesc*, const AttnSeg*, const int32_t* begin, int n, const void*, const void*,
                         const void*, int, float, void*, float*, float*, unsigned*) {

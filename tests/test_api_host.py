@@ -58,3 +58,7 @@ def test_attention_kernel_rule_and_its_override(check):
 
 def test_a_step_and_single_attention_take_the_same_waves(check):
     check("split_waves")
+
+
+def test_keys_in_halves_only_where_most_work_items_are_long(check):
+    check("key_halves")
