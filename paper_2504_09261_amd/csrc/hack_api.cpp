@@ -1014,9 +1014,8 @@ extern "C" hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const vo
                        ctx->part_ml, ctx->part_count);
   else if (split)
     launch_attn_split(s, ctx->cfg.head_dim, (const UnitDesc*)(dev + o_desc), (const AttnItem*)(dev + o_items),
-                      (int)items.size(), q, kv->k, kv->v, nullptr, nullptr, nullptr, nullptr, nullptr, 0,
-                      attn_split_in_eight(ctx->cfg.head_dim, (int)items.size(), U, max_keys) ? kSplitEight : 0, N_k, scale,
-                      out);
+                      (int)items.size(), q, kv->k, kv->v, nullptr, nullptr, nullptr, nullptr, nullptr, 0, false,
+                      attn_split_in_eight(ctx->cfg.head_dim, (int)items.size(), U, max_keys), N_k, scale, out);
   else if (ctx->cfg.dtype == HACK_F32)
     launch_attn_f32(s, ctx->cfg.head_dim, (const AttnItem*)(dev + o_items), (int)items.size(), tile, q, kv->k, kv->v, nullptr,
                     nullptr, nullptr, nullptr, nullptr, 0, 0, N_k, scale, out);
@@ -1244,10 +1243,11 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
 
 void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
   const AttnItem* items = reinterpret_cast<const AttnItem*>(g.dev + g.o_items);
-  const int fuse = n.fuse_append && a.in_place ? kSplitAppend : 0;
+  const bool append = n.fuse_append && a.in_place;
+  const bool eight = n.split && attn_split_in_eight(ctx->cfg.head_dim, g.n_items, g.n_desc, g.max_keys);
   if (g.gathered && a.in_place) {
     const GatherArgs ga{a.kept, a.kstride, ctx->seam, ctx->iota, reinterpret_cast<const MoveItem*>(g.dev + g.o_moves), g.n_moves,
-                        a.pos_new, a.k_new, a.v_new, a.cp, attn_split_in_eight(ctx->cfg.head_dim, g.n_items, g.n_desc, g.max_keys)};
+                        a.pos_new, a.k_new, a.v_new, a.cp, eight};
     if (ctx->cfg.dtype == HACK_F32)
       launch_attn_f32_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, n.tile, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
     else
@@ -1260,10 +1260,10 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
                        ctx->part_o, ctx->part_ml, ctx->part_count);
   else if (n.split)
     launch_attn_split(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v,
-                      a.cp.pos, a.pos_new, fuse | (attn_split_in_eight(ctx->cfg.head_dim, g.n_items, g.n_desc, g.max_keys) ? kSplitEight : 0), n.N_k, a.scale, a.out);
+                      a.cp.pos, a.pos_new, append, eight, n.N_k, a.scale, a.out);
   else if (ctx->cfg.dtype == HACK_F32)
     launch_attn_f32(s, ctx->cfg.head_dim, items, g.n_items, n.tile, a.q, a.cp.k, a.cp.v, a.k_new, a.v_new, a.cp.k, a.cp.v, a.cp.pos,
-                    a.pos_new, fuse, n.N_k, a.scale, a.out);
+                    a.pos_new, append ? 1 : 0, n.N_k, a.scale, a.out);
   else
     launch_attn(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out, g.attn_kernel);
 }

@@ -233,12 +233,12 @@ void launch_attn_stream(hipStream_t s, int head_dim, const UnitDesc* descs, cons
                         void* out, float* part_o, float* part_ml, unsigned* part_count);
 // bf16 attention for steps with few queries: work item = (unit, tile of
 // attn_split_q_tile_rows() queries), keys split over the waves of a work-group.
-// No kSplitAppend: attends over rows [out_off, out_off + n_out) of k_cache / v_cache.
-// fuse & kSplitAppend: attends over [rows in_off .. +len_in of the cache | the unit's N_k rows
+// append == false: attends over rows [out_off, out_off + n_out) of k_cache / v_cache.
+// append: attends over [rows in_off .. +len_in of the cache | the unit's N_k rows
 // of k_new / v_new] (n_out = len_in + N_k) and also writes those rows (and their
 // positions pos_new + row, if pos_app != nullptr) behind the cached ones in
 // k_app / v_app / pos_app, i.e. it performs the append of the step as well.
-// fuse & kSplitEight, GatherArgs::eight: eight waves a work-group instead of four.
+// eight, GatherArgs::eight: eight waves a work-group instead of four.
 // launch_attn_split_gather: over the rows the units keep (n_out of each), read in place through g; g.n_moves further
 // work-groups update the cache.
 // Eight waves instead of four halve the blocks that a wave walks one after the other.  At head_dim 128 they leave room for one
@@ -258,14 +258,13 @@ inline bool attn_split_in_eight(int head_dim, int n_items, int n_units, int max_
   const int busy = n_items + n_units;
   return head_dim == 64 || busy <= 240 || (busy <= 272 && max_keys > 32 * 32);
 }
-enum : int { kSplitAppend = 1, kSplitEight = 2 };
 int attn_split_q_tile_rows();
 void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                               const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
                               float scale, void* out);
 void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
-                       void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale,
+                       void* k_app, void* v_app, int32_t* pos_app, int pos_new, bool append, bool eight, int N_k, float scale,
                        void* out);
 // Attention variance of the listed units (bf16): sigma[desc.unit] = sum over the
 // unit's n_out keys of the population variance, across its N_k queries, of the

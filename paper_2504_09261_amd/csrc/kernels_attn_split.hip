@@ -424,19 +424,17 @@ int attn_split_q_tile_rows() { return kQTile; }
 
 void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
-                       void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale,
+                       void* k_app, void* v_app, int32_t* pos_app, int pos_new, bool append, bool eight, int N_k, float scale,
                        void* out) {
   const int n = n_items;
   if (n <= 0) return;
   typedef __bf16 T;
-  const bool eight = fuse & kSplitEight;
-  fuse &= kSplitAppend;
   if (head_dim == 64)
     HACK_SPLIT(64, false, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
-               pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
+               pos_app, pos_new, append ? 1 : 0, N_k, scale, (T*)out, GatherArgs{});
   else
     HACK_SPLIT(128, false, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
-               pos_app, pos_new, fuse, N_k, scale, (T*)out, GatherArgs{});
+               pos_app, pos_new, append ? 1 : 0, N_k, scale, (T*)out, GatherArgs{});
 }
 
 void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,

@@ -217,10 +217,10 @@ void launch_attn_stream(hipStream_t s, int, const UnitDesc*, const AttnSeg*, con
   });
 }
 void launch_attn_split(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const void*, const void*, const void*, const void*,
-                       const void*, void*, void*, int32_t*, int, int fuse, int, float, void*) {
-  stub::launch_items(fuse & kSplitAppend ? "attn_split_append" : "attn_split", s, it, n);
+                       const void*, void*, void*, int32_t*, int, bool append, bool eight, int, float, void*) {
+  stub::launch_items(append ? "attn_split_append" : "attn_split", s, it, n);
   stub::Quiet q;
-  stub::submit(s, [=] { stub::waves.push_back(fuse & kSplitEight ? 8 : 4); });
+  stub::submit(s, [=] { stub::waves.push_back(eight ? 8 : 4); });
 }
 void launch_attn_split_gather(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const GatherArgs& g, const void*,
                               const void*, const void*, int, float, void*) {
