@@ -88,7 +88,8 @@ typedef struct {
  * kept indices, softmax partials, launch tables; for bf16 contexts also the
  * merge workspace and the partial-result slots of cut attention work items:
  * 2 x resident work-groups x 128 x head_dim floats, 64 MiB at head_dim 128 on
- * MI355X).  Returns HACK_EINVAL for an
+ * MI355X; for fp32 contexts the logits of short units, 16 KiB per 64 keys and
+ * unit, 10 MiB at most).  Returns HACK_EINVAL for an
  * unsupported head_dim/dtype/n_obs or non-positive sizes, HACK_EHIP if the
  * device cannot be used. */
 hack_status hack_create(hack_ctx** out, const hack_config* cfg);
@@ -134,7 +135,11 @@ hack_status hack_check(hack_ctx* ctx);
  * either mode: no exchange, the same importance up to the order in which a row's
  * fp64 sum is formed.
  * Switching drains the device (it re-arms the exchange workspace); do it
- * outside stream captures.  fp32 contexts always score in two passes. */
+ * outside stream captures.  fp32 contexts score in two passes in either mode;
+ * for short units (up to 512 to 896 keys, by head_dim and number of units)
+ * hack_step does both passes and the selection in one launch, in which the last
+ * work-group of a unit does the second pass: nobody waits, the same kept rows as
+ * hack_score and hack_select. */
 enum { HACK_SCORE_FUSED = 0, HACK_SCORE_TWO_PASS = 1 };
 hack_status hack_set_score_mode(hack_ctx* ctx, int32_t mode);
 int32_t hack_get_score_mode(const hack_ctx* ctx);
@@ -262,12 +267,13 @@ hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q,
  * batch elements and N_k queries per unit (same attention equation, same
  * tolerances; reported so that measurements can be attributed to a kernel):
  *   0  bf16: work items of 128 queries that share every K/V block (large
- *      steps); in a launch with no more work items than the
- *      device holds work-groups, a few work items may be served by two
- *      work-groups each, and in one with no more than compute units every
- *      item by a work-group of twice as many waves (half of the keys each,
- *      the partial results added up in float32 in a fixed order) where that
- *      shortens the launch.
+ *      steps); where that shortens the launch, some work items are served by
+ *      several work-groups, a share of the keys each: a few by two in a launch
+ *      with no more work items than the device holds work-groups, those of the
+ *      last round by up to four in a larger one whose items are about equally long; or,
+ *      in a launch with no more work items than compute units, every item by a work-group
+ *      of twice as many waves, half of the keys each.  Partial results are
+ *      added up in float32 in a fixed order.
  *      fp32 contexts (always 0): work items of 16 or 32 queries whose waves
  *      split the keys; appends and kept rows as variant 1 does,
  *   1  work items of 32 queries whose four or eight waves split the keys and merge their

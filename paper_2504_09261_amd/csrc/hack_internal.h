@@ -213,8 +213,8 @@ constexpr int kAttnTileRows = 128;
 enum : int { kAttnPlain = 0, kAttnPipe = 1, kAttnHalves = 2 };
 void launch_attn(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items, const void* q,
                  const void* k_cache, const void* v_cache, int N_k, float scale, void* out, int bf16_kernel);
-// float32 attention; work items of q_tile_rows = attn_f32_q_tile_rows(units, N_k) queries (16 or 32); fuse and the
-// append arguments as in launch_attn_split.
+// float32 attention; work items of q_tile_rows = attn_f32_q_tile_rows(units, N_k) queries (16 or 32); fuse != 0
+// and its arguments as append in launch_attn_split.
 constexpr int kAttnF32SmallItems = 384;   // launches with at most this many 16-query items take those
 int attn_f32_q_tile_rows(int n_units, int N_k);
 void launch_attn_f32(hipStream_t s, int head_dim, const AttnItem* items, int n_items, int q_tile_rows, const void* q,

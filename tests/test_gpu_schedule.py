@@ -663,6 +663,43 @@ def test_short_float32_units_score_and_select_in_one_launch(head_dim, B, sides_n
     hk.close()
 
 
+@pytest.mark.parametrize("dtype,head_dim,attention", [
+    ("bf16", 64, "split"), ("bf16", 64, "tile128"), ("bf16", 128, "split"), ("bf16", 128, "tile128"), ("f32", 64, None), ("f32", 128, None),
+])
+@pytest.mark.parametrize("over", ["k_new", "v_new"])
+def test_outputs_over_the_new_rows(dtype, head_dim, attention, over):
+    """Outputs stored over the new keys or values: lists, cache and outputs of every step are the bits of a step with a buffer of its own,
+    for units that append, compress as short units and compress as long ones, and all kinds in one step."""
+    from tests import gpu_util as u
+    H, B, sides_n = 8, 2, [9, 150, 90, 200, 700, 130]
+    U, T = H * B, sum(sides_n)
+    hk = u.make_hack(heads=H, head_dim=head_dim, dtype=dtype, max_units=U, max_cache_len=T, max_queries=max(sides_n), attention=attention)
+    types = np.array([0, 1] * (H // 2), np.uint8)
+    budget = np.full(U, 10**6, np.int32)
+    budget[1::2] = 60 + 15 * np.arange(U // 2)
+    caches = [hk.managed_cache(np.minimum(np.maximum(budget, sum(sides_n[:2])), T)) for _ in range(2)]
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(head_dim)
+    scale, stride = float(np.float32(head_dim ** -0.5)), (T + 63) // 64 * 64
+    for step, n in enumerate(sides_n):
+        q, kn, vn = (torch.randn((B, H, n, head_dim), generator=gen, device=u.DEV).to(hk.torch_dtype) for _ in range(3))
+        now = np.full_like(budget, 10**6) if step < 2 else budget
+        got = []
+        for mc, aliased in zip(caches, (False, True)):
+            k, v = kn.clone(), vn.clone()
+            out = torch.zeros_like(q) if not aliased else k if over == "k_new" else v
+            kept = torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV)
+            hk.step(mc, q, k, v, types, now, 5, scale, out, kept_idx=kept)
+            torch.cuda.synchronize()
+            off, ln = mc.view()
+            got.append([out, kept] + [x[o:o + m] for x in (mc.k, mc.v, mc.pos) for o, m in zip(off, ln)])
+        assert all(torch.equal(a, b) for a, b in zip(*got)), (step, n)
+    hk.check()
+    for mc in caches:
+        mc.close()
+    hk.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("head_dim,B,n0,n1", [(64, 1, 60, 40), (64, 2, 300, 212), (64, 2, 310, 390), (64, 1, 700, 324), (128, 1, 150, 95), (128, 2, 400, 200)])
 def test_equal_keys_of_short_units_rank_by_index(dtype, head_dim, B, n0, n1):
