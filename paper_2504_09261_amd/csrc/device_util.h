@@ -16,6 +16,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned uintx4;
 
@@ -76,6 +77,13 @@ template <int N> __device__ __forceinline__ void dma_wait_but() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// The same wait, and a barrier that does not wait for LDS reads: what was read before it must not be overwritten before the next one.
+template <int N> __device__ __forceinline__ void wait_and_sync() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Between LDS words that lanes of a wave write and other lanes of the same wave read (or the other way round): the
 // hardware carries out a wave's LDS operations in order, this keeps the compiler from changing that order.  No
 // instruction is emitted.
@@ -96,6 +104,12 @@ __device__ __forceinline__ float pair_sum(float v) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// The 16x16 accumulator splits a column over the lanes l % 16 of all four rows of 16.
+__device__ __forceinline__ float quad_max(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return pair_max(fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])));
 }
 // the partner lane's value
 __device__ __forceinline__ unsigned pair_other(unsigned u) {

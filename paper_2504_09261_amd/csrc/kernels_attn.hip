@@ -336,32 +336,73 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma(
 // ---------------------------------------------------------------------------
 // bf16 MFMA path, deeper software pipeline (the kernel that serves the large steps)
 // ---------------------------------------------------------------------------
-// Same work item, operand layouts, swizzles and softmax as attn_mfma above; what
-// differs is what one stage holds.  Stage b (one barrier) is a single branch-free
-// region with three independent strands:
-//     S(b+1)   the 8 score MFMAs of the next block       (matrix core)
+// The work item of attn_mfma above, with 16x16x32 MFMAs: the chip runs these launches at its power limit, where the bare 16x16x32
+// instruction on random operands sustains 2.05 PFLOP/s and the 32x32x16 one 1.78 (and the bf16 dot product for row sums runs on the matrix
+// core as well, 17 cycles each).  A wave holds 32 queries as two tiles of 16, S^T of a block as 2x2 tiles: a lane has one query column
+// and four keys of each, P^T goes from the accumulators into the B operand of O^T += V^T P^T in that order of keys, and V^T is read
+// from LDS in the same order.  Row sums are one more tile of that product, with a V^T of ones (the bf16-rounded probabilities, summed in float32).
+// A stage (one barrier) holds three independent strands:
+//     S(b+1)   the score MFMAs of the next block          (matrix core)
 //     PV(b-1)  O^T += V^T P^T of the previous block       (matrix core)
-//     softmax(b): exponentials, bf16 packing, row sum    (vector ALU)
-// so every MFMA of the loop has vector work of another block beside it and the LDS
-// reads of both products are issued ahead of their use.  The probabilities of block
-// b wait in registers for one stage; the check "did a probability leave the safe
-// range" (and the rare rescale that follows it) sits at the end of the stage, after
-// PV(b-1) has been added, so a rescale always meets accumulators that are complete
-// up to block b-1.
-// LDS: three slots per tensor.  K(j) is read in stage j-1, V(j) in stage j+1; stage
-// b issues the copies K(b+3) and V(b+1) right after its opening barrier, into the
-// slots of K(b) and V(b-2), which every wave finished reading in stage b-1.  Each
-// copy has two full stages to land; one s_waitcnt vmcnt(2 groups) + barrier per stage.
-// Scheduling hints for one pipelined stage: N times {one MFMA, VALU_PER vector ops,
-// up to two LDS reads while any are left}.
-template <int I, int N, int VALU_PER, int DS_LEFT>
-__device__ __forceinline__ void sched_interleave() {
+//     softmax(b): multiply-adds, exponentials, packing    (vector ALU)
+// in slots of one MFMA, one LDS read and a share of the vector work, in the order written: an MFMA takes 8 cycles of the issue port that
+// vector instructions share and leaves 8 of its 16, so work that bunches up stands still in the matrix core (left to the scheduler's
+// group hints, the same stage took 970 cycles instead of 770).  Operands are read a step (eight slots) ahead, across stages too.
+// The probabilities of block b wait in registers for one stage; the check "did a probability leave the safe range" travels beside
+// the last MFMAs, and the rare rescale that follows it sits at the end of the stage, after PV(b-1) has been added, so a rescale
+// always meets accumulators that are complete up to block b-1.
+// LDS: four slots per tensor.  K(j) is read from the end of stage j-2 on through stage j-1, V(j) from the end of stage j on through
+// stage j+1.  The barrier in the middle of stage b publishes K(b+2) and V(b); behind it the copies K(b+4) and V(b+2) go into the
+// slots of K(b) and V(b-2), which every wave finished reading in stage b-1.  Each copy has two stages to land.
+// Compiled without -amdgpu-codegenprepare-break-large-phis: its pieces of the accumulators cost 36 register copies a stage.
+// Measured, us a launch, 32x32x16 in a three-slot ring / this: head_dim 128, 32 units of 4096 queries over 10521 keys 603 / 552
+// (1.28 PFLOP/s), 128 units of 4096 over 3010 or 6020 1215 / 1106, 32 units of 4096 over 1943 or 3885 204 / 185; 576 queries over 1497 33.0 / 30.7.
+// Counters at the first of them: clock 1.65 -> 1.9 GHz.
+
+// Reference: 2^15 above the running maximum, so that the exponent's top bit says that a probability reached 2 (or inf, as in the very
+// first block): bf16 and float32 keep their precision down to 2^-126, 2^-111 of a row's largest probability.
+constexpr float kHeadroom = 15.f;
+
+// The vector work of a stage: 16 scores a lane become probabilities; conversions take two of them.  Listed in the order of issue with
+// a fixed distance between dependent operations, and dealt out over the stage's MFMAs by their issue time.
+struct SoftmaxOp {
+  enum Kind { kFma, kExp, kPack } kind;
+  int index;   // element; of a pack, the first of two
+};
+struct SoftmaxOrder {
+  static constexpr int kOps = 40, kCycles = 16 * 4 + 16 * 8 + 8 * 4;
+  SoftmaxOp op[kOps];
+  constexpr SoftmaxOrder() : op() {
+    int n = 0;
+    op[n++] = SoftmaxOp{SoftmaxOp::kFma, 0};
+    op[n++] = SoftmaxOp{SoftmaxOp::kFma, 1};
+    for (int j = 0; j < 16; ++j) {
+      op[n++] = SoftmaxOp{SoftmaxOp::kExp, j};
+      if (j + 2 < 16) op[n++] = SoftmaxOp{SoftmaxOp::kFma, j + 2};
+      if (j >= 2 && j % 2 == 0) op[n++] = SoftmaxOp{SoftmaxOp::kPack, j - 2};
+    }
+    op[n++] = SoftmaxOp{SoftmaxOp::kPack, 14};
+  }
+  // operations in front of MFMA slot s of n
+  static constexpr int before(int s, int n) {
+    if (s >= n) return kOps;
+    const SoftmaxOrder o;
+    int c = 0, t = 0;
+    while (t < kOps) {
+      c += o.op[t].kind == SoftmaxOp::kExp ? 8 : 4;
+      if (c * n > kCycles * s) break;
+      ++t;
+    }
+    return t;
+  }
+};
+constexpr SoftmaxOrder kSoftmaxOrder;
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void for_range(F&& f) {
   if constexpr (I < N) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, VALU_PER, 0);
-    if constexpr (DS_LEFT >= 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    else if constexpr (DS_LEFT == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    sched_interleave<I + 1, N, VALU_PER, (DS_LEFT > 2 ? DS_LEFT - 2 : 0)>();
+    f(std::integral_constant<int, I>{});
+    for_range<I + 1, N>(f);
   }
 }
 
@@ -379,8 +420,7 @@ __device__ __forceinline__ void sched_interleave() {
 //
 // KS = 2: two groups of NW waves hold the same queries and walk the two halves of the unit's blocks, each through rings of
 // its own but from the same barriers, and exchange half of their unnormalised O^T through LDS at the end: a lone
-// work-group's stage (0.7 us at 128 queries, d = 128) is a chain of latencies that two waves a SIMD overlap (1.16 us a pair of
-// stages).  96 KiB of LDS, so one work-group a compute unit.
+// work-group's stage is a chain of latencies that two waves a SIMD overlap.  128 KiB of LDS, so one work-group a compute unit.
 template <int D, int NW, int KS, bool STREAM>
 __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
     const UnitDesc* __restrict__ descs, const AttnItem* __restrict__ items,
@@ -388,16 +428,13 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k_cache,
     const __bf16* __restrict__ v_cache, int N_k, float scale,
     __bf16* __restrict__ out, float* part_o, float* part_ml, unsigned* part_count) {
-  constexpr int KK = D / 16;        // MFMA steps over head_dim for S^T
-  constexpr int MB = D / 32;        // 32-row blocks of O^T
-  constexpr int CPR = D / 8;        // 16-byte chunks per row
-  constexpr int RPI = 64 / CPR;     // block rows covered by one wave-wide copy instruction
+  constexpr int KC = D / 32;        // MFMA steps over head_dim for S^T
+  constexpr int MT = D / 16;        // 16-row tiles of O^T
+  constexpr int RPI = 512 / D;      // block rows covered by one wave-wide copy instruction
   constexpr int IPW = (kKB / RPI) / NW;  // copy instructions per wave, block and tensor
   constexpr int BLK = kKB * D;      // elements per block and tensor
-  constexpr int NS = 3;             // ring slots per tensor
+  constexpr int NS = 4;             // ring slots per tensor
   static_assert(IPW >= 1, "a block must give every wave at least one copy instruction");
-  static_assert(KK == 2 * MB, "as many score MFMAs as PV MFMAs per block");
-
   static_assert(KS == 1 || (KS == 2 && !STREAM), "whole work items only when the keys are split");
 
   const int tid = threadIdx.x;
@@ -422,7 +459,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
   // through the main loop in registers.
   int lane = tid & 63;
   if (STREAM) asm volatile("" : "+v"(lane));
-  const int col = lane & 31, half = lane >> 5;
+  const int col = lane & 15, g = lane >> 4;
   AttnSeg sg;
   AttnItem d;      // unit, n_out, out_off of the work item
   if (STREAM) {
@@ -445,267 +482,293 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
   const __bf16* kg = k_cache + (d.out_off + key0) * D;
   const __bf16* vg = v_cache + (d.out_off + key0) * D;
   const int n_blocks = (len + kKB - 1) / kKB;
-  const int n_full = len / kKB;
+  // LDS layout of a block: rows in groups of four, a group's 64-byte pieces row after row (piece c of row r at
+  // (r / 4) 8D + 256 c + 64 (r % 4)), the 16-byte chunks of a piece permuted by the group: chunk x holds x ^ (group & 3) in K and
+  // x ^ 2 (group & 1) in V.  A phase of the operand reads (16 rows x 16 bytes of K, 8 rows x 32 bytes of V) then covers all banks, the lanes
+  // of a copy read whole 64-byte pieces, and all operands of a block stand at constant distances from one address in K and two in V.
+  // The copy instructions of a block are 16 rows apart: same lane offsets, another base.
+  static_assert(IPW == 1 || NW * RPI == 16, "lane offsets are those of the first instruction");
+  constexpr int GPI = RPI / 4;                     // groups of four rows covered by one copy instruction
+  auto copy_src = [&](int ln, int first_row, int n_rows, bool is_v) -> unsigned {   // lane ln's source in the copy from first_row on
+    const int cg = w * GPI + (GPI == 2 ? ln >> 5 : 0), row = min(first_row + 4 * cg + ((ln >> 2) & 3), n_rows - 1);
+    const int flip = is_v ? 2 * (cg & 1) : cg & 3;
+    return (unsigned)(row * D + (4 * ((ln >> 4) & (D / 32 - 1)) + ((ln & 3) ^ flip)) * 8) * 2u;
+  };
   unsigned k_src[IPW], v_src[IPW];
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
-    const int r = (w + i * NW) * RPI + lane / CPR, c = lane % CPR;
-    k_src[i] = (unsigned)(r * D + ((c ^ swz_k<D>(r)) & (CPR - 1)) * 8) * 2u;
-    v_src[i] = (unsigned)(r * D + ((c ^ swz_v<D>(r)) & (CPR - 1)) * 8) * 2u;
+    k_src[i] = copy_src(lane, i * (NW * RPI), kKB, false);
+    v_src[i] = copy_src(lane, i * (NW * RPI), kKB, true);
   }
   const unsigned ks_lds = lds_addr_of(&Ks[0][0]), vs_lds = lds_addr_of(&Vs[0][0]);
-  // Copy of block blk of one tensor into ring slot `slot`.  Rows past the end of a
-  // ragged last block repeat the last valid row (finite data); their scores are
-  // masked to -inf, so their probabilities are exactly 0.
-  auto issue_one = [&](const __bf16* g, const unsigned (&src)[IPW], unsigned lds, bool is_v, int blk, int slot, bool full) {
-    const int t0 = blk * kKB;
-    const __bf16* gb = g + (int64_t)t0 * D;
-    if (full || t0 + kKB <= len) {
+  // Block 0 is the unit's last one, ragged or not, blocks 1 .. n_blocks - 1 are the full ones in front of it: what is particular about
+  // a ragged block (rows past the end repeat the last valid row, their scores are masked to -inf) stays in front of the main loop.
+  // Copies past the last block repeat it into slots that nobody reads any more, so that every stage issues and awaits as many.
+  const unsigned last_off = (unsigned)max(n_blocks - 2, 0) * (BLK * 2);
+  unsigned k_at = 0, v_at = 0;             // byte offsets of the next blocks to copy
+  auto issue_next = [&](const __bf16* base, unsigned& at, const unsigned (&src)[IPW], unsigned lds, int slot) {
+    const char* gb = reinterpret_cast<const char*>(base) + at;
 #pragma unroll
-      for (int i = 0; i < IPW; ++i)
-        load_to_lds(gb, src[i], lds + (unsigned)((slot * BLK + (w + i * NW) * 512) * 2));
-    } else {
-#pragma unroll
-      for (int i = 0; i < IPW; ++i) {
-        const int r = (w + i * NW) * RPI + lane / CPR, c = lane % CPR;
-        const int rc = min(r, len - 1 - t0);
-        const int f = is_v ? swz_v<D>(r) : swz_k<D>(r);
-        load_to_lds(gb, (unsigned)(rc * D + ((c ^ f) & (CPR - 1)) * 8) * 2u,
-                    lds + (unsigned)((slot * BLK + (w + i * NW) * 512) * 2));
-      }
-    }
+    for (int i = 0; i < IPW; ++i) load_to_lds(gb, src[i], lds + (unsigned)((slot * BLK + (w + i * NW) * 512) * 2));
+    at = min(at + BLK * 2, last_off);
   };
-  auto issue_k = [&](int blk, int slot, bool full = false) { issue_one(kg, k_src, ks_lds, false, blk, slot, full); };
-  auto issue_v = [&](int blk, int slot, bool full = false) { issue_one(vg, v_src, vs_lds, true, blk, slot, full); };
-
-  issue_k(0, 0);
-  if (n_blocks > 1) issue_k(1, 1);
-  if (n_blocks > 2) issue_k(2, 2);
-  issue_v(0, 0);
-
-  // Q fragments (B operand of S^T = K Q^T): query col, head-dim slice [16kk + 8h, +8).
-  const int q0 = sg.q_tile * (NW * 32) + w * 32;
-  bf16x8 qf[KK];
+  auto issue_k = [&](int slot) { issue_next(kg, k_at, k_src, ks_lds, slot); };
+  auto issue_v = [&](int slot) { issue_next(vg, v_at, v_src, vs_lds, slot); };
   {
-    const int qi = min(q0 + col, N_k - 1);
-    const __bf16* qrow = q + ((int64_t)d.unit * N_k + qi) * D;
+    const int t0 = (n_blocks - 1) * kKB;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + 16 * kk + 8 * half);
-    // Consumed here so that their loads are waited for before the main loop (a vmcnt
-    // wait inside the loop would also drain the block copies meant to stay in flight).
-    // The copies issued above are older than these loads and have landed with them.
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) asm volatile("" ::"v"(qf[kk]));
+    for (int i = 0; i < IPW; ++i) {
+      load_to_lds(kg + (int64_t)t0 * D, copy_src(lane, i * (NW * RPI), len - t0, false), ks_lds + (unsigned)((w + i * NW) * 1024));
+      load_to_lds(vg + (int64_t)t0 * D, copy_src(lane, i * (NW * RPI), len - t0, true), vs_lds + (unsigned)((w + i * NW) * 1024));
+    }
+  }
+  if (n_blocks > 1) {
+    issue_k(1);
+    issue_k(2);
+    issue_k(3);
+    issue_v(1);
   }
 
-  floatx16 o[MB];
+  // Q fragments (B operand of S^T = K Q^T): query 16 qt + col, head-dim slice [32kc + 8g, +8).
+  const int q0 = sg.q_tile * (NW * 32) + w * 32;
+  bf16x8 qf[2][KC];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int qt = 0; qt < 2; ++qt) {
+    const int qi = min(q0 + 16 * qt + col, N_k - 1);
+    const __bf16* qrow = q + ((int64_t)d.unit * N_k + qi) * D;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[mb][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  const float c2 = scale * kLog2eF;
-  float mc = -INFINITY;   // m_run * c2
+    for (int kc = 0; kc < KC; ++kc) qf[qt][kc] = *reinterpret_cast<const bf16x8*>(qrow + 32 * kc + 8 * g);
+  }
+  // Consumed here so that their loads are waited for before the main loop (a vmcnt
+  // wait inside the loop would also drain the block copies meant to stay in flight).
+  // The copies issued above are older than these loads and have landed with them.
+#pragma unroll
+  for (int kc = 0; kc < KC; ++kc) asm volatile("" ::"v"(qf[0][kc]), "v"(qf[1][kc]));
 
-  int k_off[KK];           // K operand: row col, chunk 2kk + half
+  floatx4 o[MT][2];        // O^T: head-dim 16mt + 4g + r, query 16qt + col
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) k_off[kk] = col * D + (((2 * kk + half) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
-  const int g = lane >> 4, e = (lane >> 2) & 3, qd = lane & 3;
-  int v_off[MB];           // V^T operand: row 4 half + e (+16 sg, +8), head-dim 32mb + 16(g&1) + 4qd
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-    v_off[mb] = (4 * half + e) * D + (((4 * mb + 2 * (g & 1) + (qd >> 1)) ^ swz_v<D>(e)) & (CPR - 1)) * 8 + 4 * (qd & 1);
+  for (int mt = 0; mt < MT; ++mt) o[mt][0] = o[mt][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+  floatx4 ls[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};   // row sums of P (equal in all four rows)
+  const float c2 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2eF)));
+  float mc[2] = {-INFINITY, -INFINITY};   // reference: probabilities are 2^(c2 s - mc)
 
-  const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
-
-  auto mask_tail = [&](floatx16& sc, int b) {
-    if ((b + 1) * kKB > len) {
+  const int e = col >> 2, qd = col & 3;
+  const int k_off = e * 4 * D + (col & 3) * 32 + (g ^ e) * 8;   // K operand: row 16kt + col, chunk 4kc + g
+  // V^T operand: rows 4g + e and 16 + 4g + e, head-dim 16mt + 4qd; even and odd mt
+  const int v_even = g * 4 * D + e * 32 + (2 * (g & 1) + (qd >> 1)) * 8 + 4 * (qd & 1), v_odd = v_even ^ 16;
+  bf16x8 ones;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = b * kKB + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (key >= len) sc[r] = -INFINITY;
+  for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.0f;
+  asm volatile("" : "+v"(ones));   // stays in registers
+
+  // Scores of a block: sc[kt][qt], keys 16kt + 4g + r, query 16qt + col.
+  struct Scores { floatx4 t[2][2]; };
+  // Probabilities of a block's 32 keys for one query column, in the order of the B operand of the PV product: element j of lane
+  // group g is key 4g + j (j < 4) or 16 + 4g + j - 4, and the V^T operand is read in the same order.
+  auto probs = [&](const Scores& sc, int qt, bf16x8& pf) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pf[j] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sc.t[j >> 2][qt][j & 3], c2, -mc[qt]));
+  };
+  // Some probability reached 2 (or is inf, as in the very first block): the exponent field's top bit is set
+  auto too_large = [&](const bf16x8 (&pf)[2]) -> bool {
+    const uintx4 a = __builtin_bit_cast(uintx4, pf[0]), b = __builtin_bit_cast(uintx4, pf[1]);
+    return (((a[0] | a[1] | a[2]) | a[3] | b[0]) | b[1] | b[2] | b[3]) & 0x40004000u;
+  };
+  auto rescale = [&](const Scores& sc, bf16x8 (&pf)[2]) {
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+      float mx = sc.t[0][qt][0];
+#pragma unroll
+      for (int j = 1; j < 8; ++j) mx = fmaxf(mx, sc.t[j >> 2][qt][j & 3]);
+      const float m_new = fmaxf(mc[qt], fmaf(quad_max(mx), c2, kHeadroom));   // finite: the block holds a valid key
+      const float a = __builtin_amdgcn_exp2f(mc[qt] - m_new);
+      mc[qt] = m_new;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        ls[qt][r] *= a;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) o[mt][qt][r] *= a;
       }
+      probs(sc, qt, pf[qt]);
     }
   };
-  auto probs = [&](const floatx16& sc, bf16x8 (&pf)[2]) -> float {
-    float psum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) pf[r >> 3][r & 7] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sc[r], c2, -mc));
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const bf16x2 pr = {pf[r >> 3][r & 7], pf[r >> 3][(r & 7) + 1]};
-      psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, psum, false);
-    }
-    return psum;
+  auto k_frag = [&](const __bf16* Kt, int kt, int kc) -> bf16x8 { return *reinterpret_cast<const bf16x8*>(&Kt[16 * kt * D + 128 * kc + k_off]); };
+  auto v_half = [&](const __bf16* Vt, int mt, int h) -> bf16x4 {   // keys 16h + 4g ..
+    return lds_read_tr(&Vt[16 * h * D + 128 * (mt >> 1) + (mt & 1 ? v_odd : v_even)]);
   };
-  auto rescale = [&](const floatx16& sc, bf16x8 (&pf)[2]) -> float {
-    float mx = sc[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
-    mx = pair_max(mx);
-    const float m_new = fmaxf(m_run, mx);   // finite: the block holds a valid key
-    const float a = __builtin_amdgcn_exp2f((m_run - m_new) * c2);
-    l_run *= a;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[mb][r] *= a;
-    m_run = m_new;
-    mc = m_new * c2;
-    return probs(sc, pf);
+  // Operands of step i of a stage: head-dim slice i of S^T and two head-dim tiles of O^T.  Four tiles each, one operand of an MFMA kept for the next.
+  struct Frags {
+    bf16x8 k[2];
+    bf16x4 v[2][2];
   };
-  auto k_frag = [&](const __bf16* Kt, int kk) -> bf16x8 { return *reinterpret_cast<const bf16x8*>(&Kt[k_off[kk]]); };
-  auto v_frag = [&](const __bf16* Vt, int i) -> bf16x8 {   // PV MFMA i: key group sg = i / MB, head-dim block mb = i % MB
-    const __bf16* vp = &Vt[16 * (i / MB) * D + v_off[i % MB]];
-    const bf16x4 v0 = lds_read_tr(vp);
-    const bf16x4 v1 = lds_read_tr(vp + 8 * D);
-    bf16x8 vf;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      vf[j] = v0[j];
-      vf[4 + j] = v1[j];
-    }
-    return vf;
+  auto load_frag = [&](Frags& f, const __bf16* Kt, const __bf16* Vt, int i, int part) {   // one LDS read, parts 0 .. 5
+    if (part < 2) f.k[part] = k_frag(Kt, part, i);
+    else f.v[(part >> 1) - 1][part & 1] = v_half(Vt, 2 * i + (part >> 1) - 1, part & 1);
   };
+  auto joined = [](const bf16x4 (&v)[2]) { return bf16x8{v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3]}; };
+  auto qk = [&](Scores& sn, const Frags& f, int kc, int n) {
+    const int kt = n >> 1, qt = kt ^ (n & 1);
+    sn.t[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.k[kt], qf[qt][kc], sn.t[kt][qt], 0, 0, 0);
+  };
+  auto pv = [&](const Frags& f, const bf16x8 (&p)[2], int i, int n) {
+    const int m = n >> 1, qt = m ^ (n & 1);
+    o[2 * i + m][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(joined(f.v[m]), p[qt], o[2 * i + m][qt], 0, 0, 0);
+  };
+  auto row_sums = [&](const bf16x8 (&p)[2], int qt) { ls[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, p[qt], ls[qt], 0, 0, 0); };
 
-  bf16x8 pp[2];   // probabilities of the previous block, waiting for their PV product
+  bf16x8 P[2][2];   // probabilities of block b in P[b & 1]: those of the previous block wait for their PV product
+  Frags pre;      // operands of the next stage's first step
 
-  // Stage b, ring slot S = b % 3 (compile time).  On entry sc = scores of block b and
+  // Stage b, ring slot S = b % 4 (compile time).  On entry sc = scores of block b and
   // pp = probabilities of block b-1; on exit sc = scores of block b+1, pp = those of block b.
-  // FIRST: b == 0 (no previous block).  LAST: block b is the unit's last (no next scores).
-  // STEADY: every block this stage touches exists and is full, so copies, waits and
-  // masks need no tests.
-  auto stage = [&](auto slot_tag, auto first_tag, auto last_tag, auto steady_tag, int b, floatx16& sc) {
+  // FIRST: b == 0 (no previous block).
+  auto stage = [&](auto slot_tag, auto first_tag, Scores& sc) {
     constexpr int S = decltype(slot_tag)::value;
     constexpr bool FIRST = decltype(first_tag)::value;
-    constexpr bool LAST = decltype(last_tag)::value;
-    constexpr bool STEADY = decltype(steady_tag)::value;
-    // K(b+1) and V(b-1) have landed: everything but what the previous stage issued, which is V(b) and, if that
-    // block exists, K(b+2) (short caches never reach the steady loop: waiting for everything there would put a
-    // whole memory latency into every stage)
-    if (STEADY || b + 2 < n_blocks) dma_wait_but<2 * IPW>();
-    else dma_wait_but<IPW>();
-    __syncthreads();   // both are visible to every wave; the slots of K(b) and V(b-2) are free
-    if (STEADY || b + 3 < n_blocks) issue_k(b + 3, S, STEADY);
-    if (STEADY || b + 1 < n_blocks) issue_v(b + 1, (S + 1) % NS, STEADY);
-    __builtin_amdgcn_sched_barrier(0);
-    const __bf16* Kt = &Ks[(S + 1) % NS][0];
-    const __bf16* Vt = &Vs[(S + 2) % NS][0];
-    floatx16 sn;
+    const __bf16* const Kt = &Ks[(S + 1) % NS][0];
+    const __bf16* const Vt = &Vs[(S + 3) % NS][0];
+    Scores sn;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sn[r] = 0.f;
-#pragma unroll
-    for (int i = 0; i < KK; ++i) {
-      if (!LAST) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(Kt, i), qf[i], sn, 0, 0, 0);
-      if (!FIRST) o[i % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(Vt, i), pp[i / MB], o[i % MB], 0, 0, 0);
-    }
-    bf16x8 pf[2];
-    float psum = probs(sc, pf);
-    {
-      // a few operand reads ahead, then per MFMA a slice of the softmax arithmetic and the next reads
-      constexpr int N_MFMA = (LAST ? 0 : KK) + (FIRST ? 0 : KK);
-      constexpr int N_DS = (LAST ? 0 : KK) + (FIRST ? 0 : 2 * KK);
-      constexpr int AHEAD = N_DS < 6 ? N_DS : 6;
-      constexpr int VALU_PER = N_MFMA ? (48 + N_MFMA - 1) / N_MFMA : 0;
-      if constexpr (N_MFMA > 0) {
-        __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
-        sched_interleave<0, N_MFMA, VALU_PER, N_DS - AHEAD>();
+    for (int i = 0; i < 4; ++i) sn.t[i >> 1][i & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 (&pp)[2] = P[(S + 1) & 1], (&pf)[2] = P[S & 1];
+    Frags f = pre, nx;
+    float x[16];
+    auto vec_op = [&](auto t_tag) {
+      constexpr SoftmaxOp op = kSoftmaxOrder.op[decltype(t_tag)::value];
+      constexpr int j = op.index, qt = (j >> 3) & 1, jj = j & 7;
+      if constexpr (op.kind == SoftmaxOp::kFma) x[j] = fmaf(sc.t[jj >> 2][qt][jj & 3], c2, -mc[qt]);
+      else if constexpr (op.kind == SoftmaxOp::kExp) x[j] = __builtin_amdgcn_exp2f(x[j]);
+      else { pf[qt][jj] = (__bf16)x[j]; pf[qt][jj + 1] = (__bf16)x[j + 1]; }
+    };
+    constexpr int SLOTS = 8 * KC + 2, VEC_SLOTS = SLOTS - 3 * KC / 4;   // the vector work ends early: its test travels beside the last MFMAs
+    bool large = false;
+    // one MFMA, one LDS read, a share of the vector work
+    auto slot = [&](auto s_tag) {
+      constexpr int T = decltype(s_tag)::value, I = T / 8 < KC ? T / 8 : KC - 1, N = T - 8 * I;   // the last step has two more
+      // one wait for both K operands (lgkmcnt(4)) and one for both of V^T (lgkmcnt(2)) instead of one for each
+      if constexpr (N == 0) __builtin_amdgcn_s_waitcnt(0xC47F);
+      if constexpr (N == 4) __builtin_amdgcn_s_waitcnt(0xC27F);
+      if constexpr (N < 4) qk(sn, f, I, N);
+      else if constexpr (N < 8) { if (!FIRST) pv(f, pp, I, N - 4); }
+      else { if (!FIRST) row_sums(pp, N - 8); }
+      for_range<SoftmaxOrder::before(T, VEC_SLOTS), SoftmaxOrder::before(T + 1, VEC_SLOTS)>(vec_op);
+      if constexpr (T == VEC_SLOTS) large = __any(too_large(pf));
+      if constexpr (N < 2 || (N >= 4 && N < 8)) {
+        constexpr int P = N < 2 ? N : N - 2;
+        if constexpr (I + 1 < KC) load_frag(nx, Kt, Vt, I + 1, P);
+        else load_frag(nx, &Ks[(S + 2) % NS][0], &Vs[S][0], 0, P);
       }
-    }
-    if (!STEADY && !LAST) mask_tail(sn, b + 1);
-    if (__any(!(psum < kRescaleAbove))) psum = rescale(sc, pf);
-    l_run += psum;
-    pp[0] = pf[0];
-    pp[1] = pf[1];
-    if (!LAST) sc = sn;
+      if constexpr (N == 7 && I + 1 < KC) f = nx;
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for_range<0, 4 * KC>(slot);
+    wait_and_sync<2 * IPW>();   // K(b+2) and V(b) have landed: everything but what the previous stage issued
+    issue_k(S);              // K(b+4)
+    issue_v((S + 2) % NS);   // V(b+2)
+    __builtin_amdgcn_sched_barrier(0);
+    for_range<4 * KC, SLOTS>(slot);
+    pre = nx;
+    if (__builtin_expect(large, 0)) rescale(sc, pf);
+    sc = sn;
   };
-
-  using R0 = std::integral_constant<int, 0>;
-  using R1 = std::integral_constant<int, 1>;
-  using R2 = std::integral_constant<int, 2>;
-  using No = std::false_type;
-  using Yes = std::true_type;
 
   // block 0 has landed (see the Q fragments above) -> its scores
   dma_wait_but<0>();
   __syncthreads();
-  floatx16 sc;
-  {
-    const __bf16* Kt = &Ks[0][0];
+  Scores sc;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+  for (int i = 0; i < 4; ++i) sc.t[i >> 1][i & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(Kt, kk), qf[kk], sc, 0, 0, 0);
+  for (int kc = 0; kc < KC; ++kc) {
+    Frags f;
+    for (int n = 0; n < 2; ++n) load_frag(f, &Ks[0][0], nullptr, kc, n);
+    for (int n = 0; n < 4; ++n) qk(sc, f, kc, n);
   }
-  mask_tail(sc, 0);
+  for (int n = 0; n < 2; ++n) load_frag(pre, &Ks[1][0], nullptr, 0, n);
+  for (int n = 2; n < 6; ++n) load_frag(pre, nullptr, &Vs[0][0], 0, n);
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if ((n_blocks - 1) * kKB + 16 * kt + 4 * g + r >= len) sc.t[kt][0][r] = sc.t[kt][1][r] = -INFINITY;
 
-  // stage 0 on its own (no previous block), then the steady loop: stages whose blocks b-1 .. b+3 all exist and are full
-  if (n_blocks == 1) stage(R0{}, Yes{}, Yes{}, No{}, 0, sc);
-  else stage(R0{}, Yes{}, No{}, No{}, 0, sc);
-  int b = 1;
-  for (; b + 5 < n_full; b += 3) {
-    stage(R1{}, No{}, No{}, Yes{}, b, sc);
-    stage(R2{}, No{}, No{}, Yes{}, b + 1, sc);
-    stage(R0{}, No{}, No{}, Yes{}, b + 2, sc);
-  }
-  // the remaining blocks, one stage at a time (b % 3 == 1 here)
-  for (; b < n_blocks; ++b) {
-    const bool last = (b + 1 == n_blocks);
-    switch (b % 3) {
-      case 0: if (last) stage(R0{}, No{}, Yes{}, No{}, b, sc); else stage(R0{}, No{}, No{}, No{}, b, sc); break;
-      case 1: if (last) stage(R1{}, No{}, Yes{}, No{}, b, sc); else stage(R1{}, No{}, No{}, No{}, b, sc); break;
-      default: if (last) stage(R2{}, No{}, Yes{}, No{}, b, sc); else stage(R2{}, No{}, No{}, No{}, b, sc); break;
+  using No = std::false_type;
+  using Yes = std::true_type;
+  if (n_blocks > 1) {
+    stage(std::integral_constant<int, 0>{}, Yes{}, sc);
+    for (int b = 1;; b += 4) {
+      if (b >= n_blocks - 1) break;
+      stage(std::integral_constant<int, 1>{}, No{}, sc);
+      if (b + 1 >= n_blocks - 1) break;
+      stage(std::integral_constant<int, 2>{}, No{}, sc);
+      if (b + 2 >= n_blocks - 1) break;
+      stage(std::integral_constant<int, 3>{}, No{}, sc);
+      if (b + 3 >= n_blocks - 1) break;
+      stage(std::integral_constant<int, 0>{}, No{}, sc);
     }
   }
-  // PV of the last block
-  dma_wait_but<0>();
-  __syncthreads();
-  {
-    const __bf16* Vt = &Vs[(n_blocks - 1) % NS][0];
+  // the last block: its probabilities, its PV product and the one of the block before
+  auto pv_block = [&](const __bf16* Vt, const bf16x8 (&p)[2]) {
 #pragma unroll
-    for (int i = 0; i < KK; ++i)
-      o[i % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(Vt, i), pp[i / MB], o[i % MB], 0, 0, 0);
+    for (int i = 0; i < KC; ++i) {
+      Frags f;
+      for (int n = 2; n < 6; ++n) load_frag(f, nullptr, Vt, i, n);
+      for (int n = 0; n < 4; ++n) pv(f, p, i, n);
+    }
+    row_sums(p, 0);
+    row_sums(p, 1);
+  };
+  if (n_blocks > 1) {
+    const bool odd = n_blocks & 1;   // the block before the last has an odd number
+    const bf16x8 pl[2] = {odd ? P[1][0] : P[0][0], odd ? P[1][1] : P[0][1]};
+    pv_block(&Vs[(n_blocks - 2) % NS][0], pl);
   }
+  wait_and_sync<0>();
+  probs(sc, 0, P[0][0]);
+  probs(sc, 1, P[0][1]);
+  if (__any(too_large(P[0]))) rescale(sc, P[0]);
+  pv_block(&Vs[(n_blocks - 1) % NS][0], P[0]);
 
-  // ---- normalise and store: lane holds query col, head-dim rows 32mb + 8(r/4) + 4h + r%4 ----
-  float l = pair_sum(l_run);
+  // ---- normalise and store: a lane holds head-dim 16mt + 4g .. +4 of queries 16qt + col ----
+  float l[2] = {ls[0][0], ls[1][0]};
   if constexpr (KS == 2) {
     // The waves (w, 0) and (w, 1) hold the same queries over the two halves of the keys: each adds up and stores half of
     // the head-dim, what the other one needs goes through the rings, which nobody reads any more.
     if (ks == 1 && (((d.n_out + kKB - 1) / kKB) & 1)) __syncthreads();   // this half had one stage less
-    constexpr int HB = MB / 2;   // head-dim blocks of a half
-    float4* const xo = reinterpret_cast<float4*>(ks == 0 ? &K_ring[0][0][0] : &V_ring[0][0][0]) + w * HB * 4 * 64 + lane;
-    const float4* const xi = reinterpret_cast<const float4*>(ks == 0 ? &V_ring[0][0][0] : &K_ring[0][0][0]) + w * HB * 4 * 64 + lane;
+    constexpr int HT = MT / 2;   // head-dim tiles of a half
+    float4* const xo = reinterpret_cast<float4*>(ks == 0 ? &K_ring[0][0][0] : &V_ring[0][0][0]) + w * HT * 2 * 64 + lane;
+    const float4* const xi = reinterpret_cast<const float4*>(ks == 0 ? &V_ring[0][0][0] : &K_ring[0][0][0]) + w * HT * 2 * 64 + lane;
     __syncthreads();
-    if (half == 0) ml_sh[wave * 32 + col] = make_float2(mc, l);
-    const int qi = q0 + col;
-    __bf16* orow = out + ((int64_t)d.unit * N_k + min(qi, N_k - 1)) * D;
+    if (g < 2) ml_sh[wave * 32 + 16 * g + col] = make_float2(g ? mc[1] : mc[0], g ? l[1] : l[0]);
     auto finish = [&](auto half_tag) {
-      constexpr int MINE = decltype(half_tag)::value * HB, THEIRS = HB - MINE;
+      constexpr int MINE = decltype(half_tag)::value * HT, THEIRS = HT - MINE;
 #pragma unroll
-      for (int m = 0; m < HB; ++m)
+      for (int m = 0; m < HT; ++m)
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-          xo[(m * 4 + r4) * 64] = make_float4(o[THEIRS + m][4 * r4], o[THEIRS + m][4 * r4 + 1], o[THEIRS + m][4 * r4 + 2], o[THEIRS + m][4 * r4 + 3]);
+        for (int qt = 0; qt < 2; ++qt)
+          xo[(m * 2 + qt) * 64] = make_float4(o[THEIRS + m][qt][0], o[THEIRS + m][qt][1], o[THEIRS + m][qt][2], o[THEIRS + m][qt][3]);
       __syncthreads();
-      const float2 ml = ml_sh[(wave ^ NW) * 32 + col];
-      const float M = fmaxf(mc, ml.x);   // finite: both halves hold a valid key
-      float f = __builtin_amdgcn_exp2f(mc - M), g = __builtin_amdgcn_exp2f(ml.x - M);
-      const float inv = 1.f / fmaf(f, l, g * ml.y);
-      f *= inv;
-      g *= inv;
 #pragma unroll
-      for (int m = 0; m < HB; ++m)
+      for (int qt = 0; qt < 2; ++qt) {
+        const float2 ml = ml_sh[(wave ^ NW) * 32 + 16 * qt + col];
+        const float M = fmaxf(mc[qt], ml.x);   // finite: both halves hold a valid key
+        float f = __builtin_amdgcn_exp2f(mc[qt] - M), h = __builtin_amdgcn_exp2f(ml.x - M);
+        const float inv = 1.f / fmaf(f, l[qt], h * ml.y);
+        f *= inv;
+        h *= inv;
+        const int qi = q0 + 16 * qt + col;
+        __bf16* orow = out + ((int64_t)d.unit * N_k + min(qi, N_k - 1)) * D;
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const float4 x = xi[(m * 4 + r4) * 64];
+        for (int m = 0; m < HT; ++m) {
+          const float4 x = xi[(m * 2 + qt) * 64];
           bf16x4 pk;
-          pk[0] = (__bf16)fmaf(g, x.x, f * o[MINE + m][4 * r4]);
-          pk[1] = (__bf16)fmaf(g, x.y, f * o[MINE + m][4 * r4 + 1]);
-          pk[2] = (__bf16)fmaf(g, x.z, f * o[MINE + m][4 * r4 + 2]);
-          pk[3] = (__bf16)fmaf(g, x.w, f * o[MINE + m][4 * r4 + 3]);
-          if (qi < N_k) *reinterpret_cast<bf16x4*>(orow + 32 * (MINE + m) + 8 * r4 + 4 * half) = pk;
+          pk[0] = (__bf16)fmaf(h, x.x, f * o[MINE + m][qt][0]);
+          pk[1] = (__bf16)fmaf(h, x.y, f * o[MINE + m][qt][1]);
+          pk[2] = (__bf16)fmaf(h, x.z, f * o[MINE + m][qt][2]);
+          pk[3] = (__bf16)fmaf(h, x.w, f * o[MINE + m][qt][3]);
+          if (qi < N_k) *reinterpret_cast<bf16x4*>(orow + 16 * (MINE + m) + 4 * g) = pk;
         }
+      }
     };
     if (ks == 0) finish(std::integral_constant<int, 0>{});
     else finish(std::integral_constant<int, 1>{});
@@ -725,16 +788,14 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
       return (u64)__builtin_bit_cast(unsigned, a) | ((u64)__builtin_bit_cast(unsigned, b) << 32);
     };
     {
-      u64* po = reinterpret_cast<u64*>(part_o + (int64_t)sg.part * (QT * D)) + (w * MB * 8) * 64 + lane;
+      u64* po = reinterpret_cast<u64*>(part_o + (int64_t)sg.part * (QT * D)) + (w * MT * 4) * 64 + lane;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int h2 = 0; h2 < 8; ++h2)
-          __hip_atomic_store(po + (mb * 8 + h2) * 64, pack2(o[mb][2 * h2], o[mb][2 * h2 + 1]), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-      if (half == 0)   // reference in log2 units (finite: the segment holds a valid key) and normaliser
-        __hip_atomic_store(reinterpret_cast<u64*>(part_ml + (int64_t)sg.part * (2 * QT)) + w * 32 + col, pack2(mc, l),
+      for (int i = 0; i < MT * 4; ++i)
+        __hip_atomic_store(po + i * 64, pack2(o[i >> 2][(i >> 1) & 1][2 * (i & 1)], o[i >> 2][(i >> 1) & 1][2 * (i & 1) + 1]),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (g < 2)   // reference in log2 units (finite: the segment holds a valid key) and normaliser
+        __hip_atomic_store(reinterpret_cast<u64*>(part_ml + (int64_t)sg.part * (2 * QT)) + w * 32 + 16 * g + col,
+                           pack2(g ? mc[1] : mc[0], g ? l[1] : l[0]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's stores have been acknowledged
     __syncthreads();                                    // ... and so have the whole work-group's
@@ -745,48 +806,50 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
     store = last_ticket != 0;
     if (store) {
       // every other part was acknowledged before its ticket was drawn, and all tickets before this one
-      float M = -INFINITY;
-      for (int p = 0; p < sg.n_parts; ++p) {
-        const u64 ml = __hip_atomic_load(reinterpret_cast<const u64*>(part_ml + (int64_t)(sg.first_part + p) * (2 * QT)) + w * 32 + col,
-                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        M = fmaxf(M, __builtin_bit_cast(float, (unsigned)ml));
-      }
+      auto part_ml_of = [&](int p, int qt) -> u64 {
+        return __hip_atomic_load(reinterpret_cast<const u64*>(part_ml + (int64_t)(sg.first_part + p) * (2 * QT)) + w * 32 + 16 * qt + col,
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      };
+      float M[2] = {-INFINITY, -INFINITY};
+      for (int p = 0; p < sg.n_parts; ++p)
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+        for (int qt = 0; qt < 2; ++qt) M[qt] = fmaxf(M[qt], __builtin_bit_cast(float, (unsigned)part_ml_of(p, qt)));
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[mb][r] = 0.f;
-      l = 0.f;
+      for (int mt = 0; mt < MT; ++mt) o[mt][0] = o[mt][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+      l[0] = l[1] = 0.f;
       for (int p = 0; p < sg.n_parts; ++p) {   // in slot order: the sum does not depend on who adds it up
-        const u64 ml = __hip_atomic_load(reinterpret_cast<const u64*>(part_ml + (int64_t)(sg.first_part + p) * (2 * QT)) + w * 32 + col,
-                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float f = __builtin_amdgcn_exp2f(__builtin_bit_cast(float, (unsigned)ml) - M);
-        l = fmaf(f, __builtin_bit_cast(float, (unsigned)(ml >> 32)), l);
-        const u64* po = reinterpret_cast<const u64*>(part_o + (int64_t)(sg.first_part + p) * (QT * D)) + (w * MB * 8) * 64 + lane;
+        float f[2];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int qt = 0; qt < 2; ++qt) {
+          const u64 ml = part_ml_of(p, qt);
+          f[qt] = __builtin_amdgcn_exp2f(__builtin_bit_cast(float, (unsigned)ml) - M[qt]);
+          l[qt] = fmaf(f[qt], __builtin_bit_cast(float, (unsigned)(ml >> 32)), l[qt]);
+        }
+        const u64* po = reinterpret_cast<const u64*>(part_o + (int64_t)(sg.first_part + p) * (QT * D)) + (w * MT * 4) * 64 + lane;
 #pragma unroll
-          for (int h2 = 0; h2 < 8; ++h2) {
-            const u64 v2 = __hip_atomic_load(po + (mb * 8 + h2) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            o[mb][2 * h2] = fmaf(f, __builtin_bit_cast(float, (unsigned)v2), o[mb][2 * h2]);
-            o[mb][2 * h2 + 1] = fmaf(f, __builtin_bit_cast(float, (unsigned)(v2 >> 32)), o[mb][2 * h2 + 1]);
-          }
+        for (int i = 0; i < MT * 4; ++i) {
+          const int mt = i >> 2, qt = (i >> 1) & 1, r = 2 * (i & 1);
+          const u64 v2 = __hip_atomic_load(po + i * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          o[mt][qt][r] = fmaf(f[qt], __builtin_bit_cast(float, (unsigned)v2), o[mt][qt][r]);
+          o[mt][qt][r + 1] = fmaf(f[qt], __builtin_bit_cast(float, (unsigned)(v2 >> 32)), o[mt][qt][r + 1]);
+        }
       }
       if (tid == 0)   // as the next launch expects it
         __hip_atomic_store(&part_count[sg.counter], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  const float inv = 1.f / l;
-  const int qi = q0 + col;
-  if (store && qi < N_k) {
-    __bf16* orow = out + ((int64_t)d.unit * N_k + qi) * D;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
+  for (int qt = 0; qt < 2; ++qt) {
+    const float inv = 1.f / l[qt];
+    const int qi = q0 + 16 * qt + col;
+    if (store && qi < N_k) {
+      __bf16* orow = out + ((int64_t)d.unit * N_k + qi) * D;
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
+      for (int mt = 0; mt < MT; ++mt) {
         bf16x4 pk;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) pk[i] = (__bf16)(o[mb][4 * r4 + i] * inv);
-        *reinterpret_cast<bf16x4*>(orow + 32 * mb + 8 * r4 + 4 * half) = pk;
+        for (int r = 0; r < 4; ++r) pk[r] = (__bf16)(o[mt][qt][r] * inv);
+        *reinterpret_cast<bf16x4*>(orow + 16 * mt + 4 * g) = pk;
       }
     }
   }

@@ -570,6 +570,34 @@ def test_key_split_attention_block_and_wave_edges(d, H, Nk, lens):
     hk.close()
 
 
+@pytest.mark.parametrize("form", ["tile128", "stream"])
+@pytest.mark.parametrize("d,Nk", [(64, 130), (128, 33), (128, 257)])
+def test_tile_attention_block_edges_and_moving_reference(d, Nk, form):
+    """One to ten key blocks, full and ragged, in the 128-query kernel; keys that grow move the softmax reference in every stage."""
+    u = _u()
+    lens = np.array([1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 256, 288, 289, 320], np.int32)
+    H = len(lens)
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(d + Nk)
+    off = np.concatenate([[0], np.cumsum((lens + 7) // 8 * 8)]).astype(np.int64)
+    q = torch.randn((1, H, Nk, d), generator=gen, device=u.DEV).bfloat16()
+    K, V = (torch.randn((int(off[-1]), d), generator=gen, device=u.DEV) for _ in range(2))
+    for h in range(1, H, 2):   # up to 120 nats, some 10 more in every block than in the one before
+        K[off[h]:off[h] + lens[h]] *= (1 + torch.arange(int(lens[h]), device=u.DEV) / 8)[:, None]
+    K, V = K.bfloat16(), V.bfloat16()
+    scale = float(np.float32(d ** -0.5))
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=int(lens.max()), max_queries=Nk, attention=form)
+    out = torch.full_like(q, 7.0)
+    hk.attn(q, Cache(K, V, off[:-1], lens), scale, out)
+    torch.cuda.synchronize()
+    for h in range(H):
+        k, v = (x[off[h]:off[h] + lens[h]].double() for x in (K, V))
+        want = torch.softmax(scale * (q[0, h].double() @ k.T.contiguous()), -1) @ v
+        # P and O are rounded to bf16: 2^-8 of the largest value each, |V| up to 4.5
+        assert float((out[0, h].double() - want).abs().max()) < 4e-2, (h, int(lens[h]))
+    hk.close()
+
+
 @pytest.mark.parametrize("forced,H,Nk,lens", [
     (True, 3, 1, [33, 64, 65]), (True, 4, 127, [96, 97, 128, 129]), (True, 3, 128, [160, 191, 193]), (True, 5, 129, [224, 225, 256, 321, 1000]),
     (False, 20, 832, [865] * 10 + [897, 900] * 5),       # 140 work items of 128 queries: halves by the library's own rule
