@@ -116,6 +116,7 @@ struct StepGroup {
   int item_keys = 0;
   bool two_pass = false;
   bool small = false;                     // score and selection in one launch
+  int n_short = 0;                        // of the compressing units, the first ones: those of a launch of their own (split_score_select)
   std::vector<int> launches;              // score launch groups
   unsigned long long* slots = nullptr;    // row-sum exchange area of the group's score launches
   const uint8_t* dev = nullptr;
@@ -1168,6 +1169,8 @@ void add_unit(GroupUnits* u, StepGroup* g, const UnitDesc& d, bool merges, int N
   }
 }
 
+bool score_select_short(const UnitDesc& d) { return d.len_in + d.n_new <= kScoreSelectHalf; }
+
 // shared: another group of the step may attend at the same time
 hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, bool shared, const int32_t* rows, hipStream_t s,
                          StepGroup* g) {
@@ -1181,6 +1184,10 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   else if (items.empty()) build_attn_items(u.descs, n.N_k, n.tile, &items);
   g->small = ctx->cfg.dtype == HACK_BF16 ? use_score_select(ctx->cfg.head_dim, u.n_comp, g->max_t)
                                          : use_score_select_f32(ctx->cfg.head_dim, u.n_comp, g->max_t);
+  if (ctx->cfg.dtype == HACK_BF16 && g->small && g->max_t > kScoreSelectHalf) {
+    while (g->n_short < u.n_comp && score_select_short(u.descs[g->n_short])) ++g->n_short;
+    if (!split_score_select(u.n_comp, g->n_short)) g->n_short = 0;
+  }
   if (ctx->cfg.dtype == HACK_BF16 && u.n_comp > 0 && !g->small)
     g->item_keys = plan_score_items(ctx, u.descs, u.n_comp, g->two_pass, &sitems, &g->launches);
   // The key-split and the float32 kernel read the rows in place unless they change on the way (merge) or a unit's cache is longer than
@@ -1217,14 +1224,22 @@ void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const St
     launch_score_select_f32(s, ctx->cfg.head_dim, g.ddev(), g.n_comp, g.max_t, a.q, reinterpret_cast<const int32_t*>(g.dev + g.o_rows),
                             n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->f32_logits, ctx->stats, ctx->counters, a.kept, a.kstride, ctx->seam);
   } else if (g.n_comp > 0 && g.small && moves) {
-    launch_score_select_move(s, ctx->cfg.head_dim, g.ddev(), g.n_comp, g.ddev() + g.n_comp, g.n_desc - g.n_comp, g.max_t, a.q,
-                             reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp, a.k_new, a.v_new, a.pos_new,
-                             a.kept, a.kstride, ctx->fault);
+    auto go = [&](int first, int n_units, int n_append, int max_t) {
+      launch_score_select_move(s, ctx->cfg.head_dim, g.ddev() + first, n_units, g.ddev() + g.n_comp, n_append, max_t, a.q,
+                               reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp, a.k_new, a.v_new, a.pos_new,
+                               a.kept, a.kstride, ctx->fault);
+    };
+    if (g.n_short > 0) go(0, g.n_short, 0, kScoreSelectHalf);
+    go(g.n_short, g.n_comp - g.n_short, g.n_desc - g.n_comp, g.max_t);
     moves = false;
   } else if (g.n_comp > 0 && g.small) {
-    launch_score_select(s, ctx->cfg.head_dim, g.ddev(), g.n_comp, g.max_t, a.q,
-                        reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, a.kept, a.kstride,
-                        ctx->seam, ctx->fault);
+    auto go = [&](int first, int n_units, int max_t) {
+      launch_score_select(s, ctx->cfg.head_dim, g.ddev() + first, n_units, max_t, a.q,
+                          reinterpret_cast<const int32_t*>(g.dev + g.o_rows), n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, a.kept, a.kstride,
+                          ctx->seam, ctx->fault);
+    };
+    if (g.n_short > 0) go(0, g.n_short, kScoreSelectHalf);
+    go(g.n_short, g.n_comp - g.n_short, g.max_t);
   } else if (g.n_comp > 0) {
     run_score(ctx, s, g.two_pass, g.slots, g.ddev(), g.n_comp, g.max_t,
               reinterpret_cast<const ScoreItem*>(g.dev + g.o_sit), g.item_keys, g.launches, a.q,
@@ -1351,6 +1366,8 @@ hack_status plan_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int32_t N_k
   n->g[1].two_pass = true;          // leaves its sums in the slots, hence an exchange area of its own
   n->g[1].slots = ctx->rowstat_side;
   for (GroupUnits& g : units) g.descs.reserve(U);
+  if (ctx->cfg.dtype == HACK_BF16 && descs[0].size() > 512)   // where a launch may be over the short ones alone it finds them together
+    std::stable_partition(descs[0].begin(), descs[0].end(), score_select_short);
   for (const UnitDesc& d : descs[0]) {
     const bool ctxl = head_type[d.unit % H] == HACK_CONTEXTUAL;
     const int i = n->two_groups && ctxl ? 1 : 0;

@@ -189,6 +189,15 @@ void launch_score_select_f32(hipStream_t s, int head_dim, const UnitDesc* descs,
 
 // bf16: score and selection of short units in one launch, one work-group per unit, no importance in memory.
 bool use_score_select(int head_dim, int n_units, int max_t_in);
+// Beyond kScoreSelectHalf keys a unit takes a compute unit for itself (16 waves), up to there two share one.  n_short of n_units units are that
+// short: do they get a launch of their own?  Where that spares a round of work-groups over the 256 compute units; a round takes 17 to 19 us
+// whichever form it is of.  480 units of 358 keys and 480 of 562: 64.6 -> 18.5 + 38.7 us (kernel trace; a batch of 32 256^2 images 282.1 -> 276.8,
+// at half of the cache 295 -> 290).  Launches of their own for units of at most 256 keys, four of which share a compute unit, lose: 300 units of
+// 213 and 300 of 281 keys in a schedule of 136.8 us 143.4.
+constexpr int kScoreSelectHalf = 512;
+inline bool split_score_select(int n_units, int n_short) {
+  return n_short > 0 && n_short < n_units && (n_short + 511) / 512 + (n_units - n_short + 255) / 256 < (n_units + 255) / 256;
+}
 void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in,
                          const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,
                          const void* k_new, int32_t* kept_idx, int64_t idx_stride, int32_t* seam, int* fault);

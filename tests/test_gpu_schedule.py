@@ -798,6 +798,56 @@ def test_short_units_move_their_rows_in_the_score_launch(head_dim, sides_n, with
     hk.close()
 
 
+@pytest.mark.parametrize("attention", ["split", "tile128"])
+@pytest.mark.parametrize("H,n_long", [(7, 1), (8, 300), (9, 575)])
+def test_short_units_beside_longer_ones_in_a_launch_of_their_own(H, n_long, attention):
+    """More units than compute units, up to 512 keys and beyond (at 512, 513, 1024), some of them keeping everything: the kept lists
+    of the single entry points, which know no such launches, and the listed rows in the cache."""
+    from tests import gpu_util as u
+    B, d, n0, n = 100, 64, 900, 124
+    U = B * H
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=U, max_cache_len=n0 + n, max_queries=n0, attention=attention)
+    types = (np.arange(H) % 2).astype(np.uint8)
+    # rows after the first compression: long units first, then short ones, in an order of their own; a few keep everything at the end
+    order = np.random.default_rng(H).permutation(U)
+    rows = np.empty(U, np.int32)
+    rows[order[:n_long]] = np.linspace(513 - n, n0, n_long).astype(np.int32)
+    rows[order[n_long:]] = np.linspace(40, 512 - n, U - n_long).astype(np.int32)
+    last = (rows // 2).astype(np.int32)
+    last[order[n_long::97]] = 10**6
+    mc = hk.managed_cache(np.maximum(rows + n, n0))
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(n_long)
+    scale, stride = float(np.float32(d ** -0.5)), (n0 + n + 63) // 64 * 64
+    for n_k, budget in ((n0, np.where(rows < n0, rows, 10**6).astype(np.int32)), (n, last)):
+        q, kn, vn = (torch.randn((B, H, n_k, d), generator=gen, device=u.DEV).to(torch.bfloat16) for _ in range(3))
+        before = mc.as_cache()
+        src = type(before)(mc.k.clone(), mc.v.clone(), before.off, before.len, mc.pos.clone())
+        kept = torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV)
+        hk.step(mc, q, kn, vn, types, budget, 5, scale, torch.empty_like(q), kept_idx=kept)
+        if n_k == n0:
+            continue
+        imp = torch.zeros((U, stride), device=u.DEV)
+        want = torch.full((U, stride), -1, dtype=torch.int32, device=u.DEV)
+        hk.score(q, src, scale, imp, k_new=kn)
+        t_in = (src.len + n).astype(np.int32)
+        ln = hk.select(B, imp, t_in, types, budget, 5, n, want)
+        torch.cuda.synchronize()
+        mine = torch.from_numpy((np.arange(stride)[None, :] < ln[:, None]) & (budget < t_in)[:, None]).to(u.DEV)
+        assert int((mine & (kept != want)).sum()) == 0
+        off, length = mc.view()
+        assert np.array_equal(length, np.minimum(budget, t_in))
+        for x in list(order[:3]) + list(order[-200:]) + list(order[n_long::97]):
+            b, h = divmod(int(x), H)
+            o0, l0 = int(src.off[x]), int(src.len[x])
+            at = want[x, :ln[x]].long() if budget[x] < t_in[x] else torch.arange(int(t_in[x]), device=u.DEV)
+            for got, old, new in ((mc.k, src.k, kn), (mc.v, src.v, vn)):
+                assert torch.equal(got[off[x]:off[x] + length[x]], torch.cat([old[o0:o0 + l0], new[b, h]])[at]), x
+    hk.check()
+    mc.close()
+    hk.close()
+
+
 def test_step_capacity_and_argument_errors():
     u = _u()
     from paper_2504_09261_amd.binding import HackError
