@@ -19,6 +19,7 @@
 //     ring of four slots per tensor, one barrier per block; an XOR swizzle of
 //     16-byte chunks keeps the b128 K reads and the transposing V reads
 //     bank-conflict free.
+#include <cfloat>
 #include <type_traits>
 
 #include "device_util.h"
@@ -550,7 +551,9 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
   for (int mt = 0; mt < MT; ++mt) o[mt][0] = o[mt][1] = floatx4{0.f, 0.f, 0.f, 0.f};
   floatx4 ls[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};   // row sums of P (equal in all four rows)
   const float c2 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2eF)));
-  float mc[2] = {-INFINITY, -INFINITY};   // reference: probabilities are 2^(c2 s - mc)
+  // Reference: probabilities are 2^(c2 s - mc).  Finite from the start: keys whose score is -inf get a probability of 0 also where nothing
+  // else has been seen, and whatever finite score comes first is far too large for it.
+  float mc[2] = {-FLT_MAX, -FLT_MAX};
 
   const int e = col >> 2, qd = col & 3;
   const int k_off = e * 4 * D + (col & 3) * 32 + (g ^ e) * 8;   // K operand: row 16kt + col, chunk 4kc + g
@@ -580,7 +583,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
       float mx = sc.t[0][qt][0];
 #pragma unroll
       for (int j = 1; j < 8; ++j) mx = fmaxf(mx, sc.t[j >> 2][qt][j & 3]);
-      const float m_new = fmaxf(mc[qt], fmaf(quad_max(mx), c2, kHeadroom));   // finite: the block holds a valid key
+      const float m_new = fmaxf(mc[qt], fmaf(quad_max(mx), c2, kHeadroom));
       const float a = __builtin_amdgcn_exp2f(mc[qt] - m_new);
       mc[qt] = m_new;
 #pragma unroll
@@ -751,7 +754,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
 #pragma unroll
       for (int qt = 0; qt < 2; ++qt) {
         const float2 ml = ml_sh[(wave ^ NW) * 32 + 16 * qt + col];
-        const float M = fmaxf(mc[qt], ml.x);   // finite: both halves hold a valid key
+        const float M = fmaxf(mc[qt], ml.x);
         float f = __builtin_amdgcn_exp2f(mc[qt] - M), h = __builtin_amdgcn_exp2f(ml.x - M);
         const float inv = 1.f / fmaf(f, l[qt], h * ml.y);
         f *= inv;
@@ -793,7 +796,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
       for (int i = 0; i < MT * 4; ++i)
         __hip_atomic_store(po + i * 64, pack2(o[i >> 2][(i >> 1) & 1][2 * (i & 1)], o[i >> 2][(i >> 1) & 1][2 * (i & 1) + 1]),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (g < 2)   // reference in log2 units (finite: the segment holds a valid key) and normaliser
+      if (g < 2)   // reference in log2 units and normaliser
         __hip_atomic_store(reinterpret_cast<u64*>(part_ml + (int64_t)sg.part * (2 * QT)) + w * 32 + 16 * g + col,
                            pack2(g ? mc[1] : mc[0], g ? l[1] : l[0]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

@@ -598,6 +598,45 @@ def test_tile_attention_block_edges_and_moving_reference(d, Nk, form):
     hk.close()
 
 
+@pytest.mark.parametrize("form", ["tile128", "stream", "halves"])
+@pytest.mark.parametrize("d,Nk", [(64, 130), (128, 33), (128, 257)])
+def test_tile_attention_where_whole_blocks_score_minus_infinity(d, Nk, form):
+    """Keys that score -inf for every query fill the block that a work item, a segment or a half begins with: what is left decides."""
+    if form == "halves" and d != 128:
+        pytest.skip("halves: head_dim 128")
+    u = _u()
+    lens = np.array([33, 65, 129, 289, 64, 320, 77, 160, 225, 288], np.int32)
+    H = len(lens)
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(d + Nk)
+    off = np.concatenate([[0], np.cumsum((lens + 7) // 8 * 8)]).astype(np.int64)
+    q = torch.randn((1, H, Nk, d), generator=gen, device=u.DEV)
+    q[..., 0] = q[..., 0].abs() + 0.1
+    q = q.bfloat16()
+    K, V = (torch.randn((int(off[-1]), d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    for h in range(H):
+        n, k = int(lens[h]), K[off[h]:off[h] + lens[h]]
+        if h < 6:
+            k[(n - 1) // 32 * 32:, 0] = -torch.inf    # the last block, of one key, full
+        elif h == 6:
+            k[torch.arange(n, device=u.DEV) != 40, 0] = -torch.inf
+        elif h == 7:
+            k[:96, 0] = -torch.inf                    # the first of its halves
+        else:
+            k[32:, 0] = -torch.inf
+    scale = float(np.float32(d ** -0.5))
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=int(lens.max()), max_queries=Nk, attention=form)
+    out = torch.full_like(q, 7.0)
+    hk.attn(q, Cache(K, V, off[:-1], lens), scale, out)
+    torch.cuda.synchronize()
+    for h in range(H):
+        k, v = (x[off[h]:off[h] + lens[h]].double() for x in (K, V))
+        want = torch.softmax(scale * (q[0, h].double() @ k.T.contiguous()), -1) @ v
+        # P and O are rounded to bf16: 2^-8 of the largest value each, |V| up to 4.5
+        assert float((out[0, h].double() - want).abs().max()) < 4e-2, (h, int(lens[h]))   # (a NaN is not)
+    hk.close()
+
+
 @pytest.mark.parametrize("forced,H,Nk,lens", [
     (True, 3, 1, [33, 64, 65]), (True, 4, 127, [96, 97, 128, 129]), (True, 3, 128, [160, 191, 193]), (True, 5, 129, [224, 225, 256, 321, 1000]),
     (False, 20, 832, [865] * 10 + [897, 900] * 5),       # 140 work items of 128 queries: halves by the library's own rule
