@@ -505,13 +505,13 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
   // Block 0 is the unit's last one, ragged or not, blocks 1 .. n_blocks - 1 are the full ones in front of it: what is particular about
   // a ragged block (rows past the end repeat the last valid row, their scores are masked to -inf) stays in front of the main loop.
   // Copies past the last block repeat it into slots that nobody reads any more, so that every stage issues and awaits as many.
-  const unsigned last_off = (unsigned)max(n_blocks - 2, 0) * (BLK * 2);
-  unsigned k_at = 0, v_at = 0;             // byte offsets of the next blocks to copy
+  const unsigned last_full = (unsigned)max(n_blocks - 2, 0);
+  unsigned k_at = 0, v_at = 0;             // the next blocks to copy (their byte offsets do not fit 32 bits)
   auto issue_next = [&](const __bf16* base, unsigned& at, const unsigned (&src)[IPW], unsigned lds, int slot) {
-    const char* gb = reinterpret_cast<const char*>(base) + at;
+    const __bf16* gb = base + (uint64_t)at * BLK;
 #pragma unroll
     for (int i = 0; i < IPW; ++i) load_to_lds(gb, src[i], lds + (unsigned)((slot * BLK + (w + i * NW) * 512) * 2));
-    at = min(at + BLK * 2, last_off);
+    at = min(at + 1, last_full);
   };
   auto issue_k = [&](int slot) { issue_next(kg, k_at, k_src, ks_lds, slot); };
   auto issue_v = [&](int slot) { issue_next(vg, v_at, v_src, vs_lds, slot); };

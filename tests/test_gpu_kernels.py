@@ -637,6 +637,25 @@ def test_tile_attention_where_whole_blocks_score_minus_infinity(d, Nk, form):
     hk.close()
 
 
+@pytest.mark.parametrize("form", ["tile128", "tile128_plain"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_tile_attention_over_more_rows_than_32_bits_of_bytes(d, form):
+    """A unit whose keys take more than 4 GiB: the one key that matters lies behind them, in a block that is not the last one."""
+    u = _u()
+    line = 2**32 // (2 * d)
+    n, at = line + 100, line + 40
+    K, V = (torch.zeros((n + 4, d), dtype=torch.bfloat16, device=u.DEV) for _ in range(2))
+    K[at] = 8.0     # 8 sqrt(d) = 64 nats and more above all other keys, of which there are e^17
+    V[at] = torch.arange(d, device=u.DEV).bfloat16()
+    q = torch.ones((1, 1, 1, d), dtype=torch.bfloat16, device=u.DEV)
+    hk = u.make_hack(heads=1, head_dim=d, dtype="bf16", max_units=1, max_cache_len=64, max_queries=1, attention=form)
+    out = torch.full_like(q, 7.0)
+    hk.attn(q, Cache(K, V, np.zeros(1, np.int64), np.array([n], np.int32)), float(np.float32(d ** -0.5)), out)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0, 0, 0], V[at])
+    hk.close()
+
+
 @pytest.mark.parametrize("forced,H,Nk,lens", [
     (True, 3, 1, [33, 64, 65]), (True, 4, 127, [96, 97, 128, 129]), (True, 3, 128, [160, 191, 193]), (True, 5, 129, [224, 225, 256, 321, 1000]),
     (False, 20, 832, [865] * 10 + [897, 900] * 5),       # 140 work items of 128 queries: halves by the library's own rule
