@@ -1184,10 +1184,6 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   else if (items.empty()) build_attn_items(u.descs, n.N_k, n.tile, &items);
   g->small = ctx->cfg.dtype == HACK_BF16 ? use_score_select(ctx->cfg.head_dim, u.n_comp, g->max_t)
                                          : use_score_select_f32(ctx->cfg.head_dim, u.n_comp, g->max_t);
-  if (ctx->cfg.dtype == HACK_BF16 && g->small && g->max_t > kScoreSelectHalf) {
-    while (g->n_short < u.n_comp && score_select_short(u.descs[g->n_short])) ++g->n_short;
-    if (!split_score_select(u.n_comp, g->n_short)) g->n_short = 0;
-  }
   if (ctx->cfg.dtype == HACK_BF16 && u.n_comp > 0 && !g->small)
     g->item_keys = plan_score_items(ctx, u.descs, u.n_comp, g->two_pass, &sitems, &g->launches);
   // The key-split and the float32 kernel read the rows in place unless they change on the way (merge) or a unit's cache is longer than
@@ -1199,6 +1195,10 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
     for (size_t i = 0; i < u.descs.size(); ++i)
       for (int r = 0; r < (u.descs[i].mode == MOVE_GATHER ? u.descs[i].n_out : u.descs[i].n_new); r += kMoveItemRows)
         moves.push_back(MoveItem{(int32_t)i, r});
+  if (ctx->cfg.dtype == HACK_BF16 && g->small && g->max_t > kScoreSelectHalf) {
+    while (g->n_short < u.n_comp && score_select_short(u.descs[g->n_short])) ++g->n_short;
+    if (!split_score_select(u.n_comp, g->n_short, g->gathered ? 0 : (int)u.descs.size() - u.n_comp)) g->n_short = 0;
+  }
   g->n_moves = (int)moves.size();
   g->n_desc = (int)u.descs.size();
   g->n_comp = u.n_comp;

@@ -195,8 +195,14 @@ bool use_score_select(int head_dim, int n_units, int max_t_in);
 // at half of the cache 295 -> 290).  Launches of their own for units of at most 256 keys, four of which share a compute unit, lose: 300 units of
 // 213 and 300 of 281 keys in a schedule of 136.8 us 143.4.
 constexpr int kScoreSelectHalf = 512;
-inline bool split_score_select(int n_units, int n_short) {
-  return n_short > 0 && n_short < n_units && (n_short + 511) / 512 + (n_units - n_short + 255) / 256 < (n_units + 255) / 256;
+// n_append work-groups that append rows ride in the launch of the longer units, or in the only one, where they fill the compute units that its
+// last round leaves idle: the round has to be spared with them as well.  264 units of 401 keys, 256 of 824 and 200, 504, 1000 that append (three
+// rounds, four and six either way), one launch / two, us a step: 40 rows 61.4 / 59.0, 69.0 / 67.1, 76.2 / 78.5; 124 rows 67.5 / 65.6, 77.3 / 77.5,
+// 100.7 / 99.5; 300 rows 85 / 88, 118.5 / 121.6, 170.7 / 174.4.
+inline bool split_score_select(int n_units, int n_short, int n_append) {
+  auto rounds = [](int n, int at_once) { return (n + at_once - 1) / at_once; };
+  auto spared = [&](int more) { return rounds(n_units + more, 256) - rounds(n_short, 512) - rounds(n_units - n_short + more, 256); };
+  return n_short > 0 && n_short < n_units && spared(0) > 0 && spared(n_append) > 0;
 }
 void launch_score_select(hipStream_t s, int head_dim, const UnitDesc* descs, int n_units, int max_t_in,
                          const void* q, const int32_t* q_rows, int n_obs, int N_k, float scale, const void* k_cache,

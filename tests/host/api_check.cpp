@@ -212,6 +212,64 @@ int short_units() {
   return 0;
 }
 
+// Units of up to 512 keys beside longer ones: two launches where that spares a round of work-groups over the device, those that
+// append rows included where they ride along (128-query attention).
+int short_units_apart() {
+  struct Case { int n_short, n_long, n_append; bool rows_move, apart; };
+  const Case cases[] = {
+      {512, 256, 0, true, true}, {512, 257, 0, true, true}, {513, 256, 0, true, true}, {513, 255, 0, true, false},   // 2 + 1 rounds for 4; for 3
+      {1, 768, 0, true, false}, {768, 1, 0, true, true}, {767, 1, 0, true, false}, {256, 257, 0, true, false}, {257, 256, 0, true, true},
+      {769, 0, 0, true, false}, {0, 769, 0, true, false}, {504, 8, 0, true, false}, {504, 9, 0, true, true},
+      {264, 256, 200, true, false}, {264, 256, 200, false, true}, {264, 256, 256, true, true}, {264, 256, 504, true, false},
+      {264, 256, 504, false, true}, {512, 256, 512, true, true}, {512, 256, 1504, true, true}, {300, 300, 400, true, false},
+      {300, 100, 150, true, false},   // only the appending ones make it three rounds
+  };
+  std::vector<uint8_t> mem(64);
+  void* p = reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(mem.data()) + 15) / 16 * 16);
+  uint8_t* const fresh = static_cast<uint8_t*>(p);
+  for (const Case& c : cases) {
+    const int U = c.n_short + c.n_long + c.n_append, n0 = 600, n1 = 100;
+    setenv("HACK_ATTN_SPLIT_ITEMS", c.rows_move ? "0" : "2000000000", 1);
+    hack_config cfg{0, 1, kD, HACK_BF16, U, n0 + n1, n0, 32};
+    hack_ctx* ctx;
+    CHECK(hack_create(&ctx, &cfg) == HACK_OK);
+    unsetenv("HACK_ATTN_SPLIT_ITEMS");
+    std::vector<int32_t> first(U), last(U);
+    for (int i = 0; i < U; ++i) {   // the three kinds in turn through the units
+      const int u = (int)((int64_t)i * 7919 % U);
+      first[u] = i < c.n_short ? 412 - i % 300 : i < c.n_short + c.n_long ? 413 + i % 80 : 30;   // rows; 100 come on top: 512 and fewer, 513 and more
+      last[u] = i < c.n_short + c.n_long ? first[u] : 1 << 30;
+    }
+    const std::vector<int32_t> cap(U, n0);
+    const uint8_t type = 0;
+    int64_t rows;
+    hack_kvcache* cache;
+    CHECK(U % 7919 != 0 && hack_kvcache_rows_required(U, cap.data(), &rows) == HACK_OK);
+    CHECK(hack_kvcache_create(ctx, U, cap.data(), p, p, nullptr, rows, &cache) == HACK_OK);
+    auto step = [&](int n, const std::vector<int32_t>& b) {
+      return hack_step(ctx, cache, U, n, fresh, fresh + 16, fresh + 32, &type, b.data(), 5, 0.1f, fresh + ((size_t)1 << 40), nullptr, 0, kStream);
+    };
+    CHECK(step(n0, first) == HACK_OK);
+    stub::launches.clear();
+    stub::moving_launches.clear();
+    CHECK(step(n1, last) == HACK_OK);
+    const int n_launches = (int)std::count(stub::launches.begin(), stub::launches.end(), "score_select");
+    int n_units = 0, n_append = 0;
+    for (const auto& l : stub::moving_launches) {
+      n_units += l.n_units;
+      n_append += l.n_append;
+    }
+    const bool each_once = c.rows_move ? n_units == c.n_short + c.n_long && n_append == c.n_append : stub::moving_launches.empty();
+    hack_kvcache_destroy(cache);
+    hack_destroy(ctx);
+    if (n_launches != 1 + c.apart || !each_once || stub::bad_launches) {
+      printf("%d short, %d long, %d appending: %d launches, %d and %d units\n", c.n_short, c.n_long, c.n_append, n_launches, n_units, n_append);
+      return 1;
+    }
+  }
+  return 0;
+}
+
 // Every allocation of a call fails once: the call returns an error, and the same call succeeds afterwards.
 template <typename Call>
 bool survives(Call call) {
@@ -495,6 +553,7 @@ int main(int argc, char** argv) {
   if (which == "capture") rc = capture();
   if (which == "out_over_new_rows") rc = out_over_new_rows();
   if (which == "short_units") rc = short_units();
+  if (which == "short_units_apart") rc = short_units_apart();
   if (which == "no_exceptions") rc = no_exceptions();
   if (which == "step_keys") rc = step_keys();
   if (which == "step_tables") rc = step_tables();

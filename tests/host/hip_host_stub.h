@@ -158,7 +158,7 @@ int score_fused_capacity(int, int) { return 2048; }
 int attn_stream_slots(int) { return 512; }
 int attn_split_q_tile_rows() { return 32; }
 int attn_f32_q_tile_rows(int n_units, int N_k) { return n_units * ((N_k + 15) / 16) <= kAttnF32SmallItems ? 16 : 32; }
-bool use_score_select(int, int, int max_t_in) { return max_t_in <= 256; }
+bool use_score_select(int, int n_units, int max_t_in) { return max_t_in <= 256 || (max_t_in <= 1024 && n_units >= 128); }
 hipError_t score_static_setup(int) { return hipSuccess; }
 
 void launch_move(hipStream_t s, int, int, const UnitDesc* d, int n, int, CachePtrs, CachePtrs, const void*, const void*, int, int,

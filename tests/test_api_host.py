@@ -36,6 +36,10 @@ def test_short_units_take_one_launch_and_every_unit_once(check):
     check("short_units")
 
 
+def test_short_units_take_a_launch_of_their_own_where_that_spares_a_round(check):
+    check("short_units_apart")
+
+
 def test_a_step_table_holds_every_unit_once(check):
     check("step_tables")
 
