@@ -570,40 +570,58 @@ def test_key_split_attention_block_and_wave_edges(d, H, Nk, lens):
     hk.close()
 
 
-@pytest.mark.parametrize("form", ["tile128", "stream"])
-@pytest.mark.parametrize("d,Nk", [(64, 130), (128, 33), (128, 257)])
+# the forms of the 128-query kernel (halves: head_dim 128)
+TILE_FORMS = [(d, n, f) for d, n in ((64, 130), (128, 33), (128, 257)) for f in ("tile128", "stream", "halves") if d == 128 or f != "halves"]
+
+
+@pytest.mark.parametrize("d,Nk,form", TILE_FORMS)
 def test_tile_attention_block_edges_and_moving_reference(d, Nk, form):
-    """One to ten key blocks, full and ragged, in the 128-query kernel; keys that grow move the softmax reference in every stage."""
+    """One to ten key blocks, full and ragged, in the 128-query kernel, with keys of one size, and with keys that grow from block to block in
+    the order in which a work item or a half walks them, by more than its reference leaves room for: every query moves it in every stage."""
     u = _u()
-    lens = np.array([1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 256, 288, 289, 320], np.int32)
+    lens = [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 256, 288, 289, 320]
+    lens = np.array([n for n in lens if n > 32 or form != "halves"], np.int32)   # either half needs a block
     H = len(lens)
     gen = torch.Generator(u.DEV)
     gen.manual_seed(d + Nk)
     off = np.concatenate([[0], np.cumsum((lens + 7) // 8 * 8)]).astype(np.int64)
-    q = torch.randn((1, H, Nk, d), generator=gen, device=u.DEV).bfloat16()
+    q = torch.randn((1, H, Nk, d), generator=gen, device=u.DEV)
+    q[..., 0] = 4.0
+    q = q.bfloat16()
     K, V = (torch.randn((int(off[-1]), d), generator=gen, device=u.DEV) for _ in range(2))
-    for h in range(1, H, 2):   # up to 120 nats, some 10 more in every block than in the one before
-        K[off[h]:off[h] + lens[h]] *= (1 + torch.arange(int(lens[h]), device=u.DEV) / 8)[:, None]
-    K, V = K.bfloat16(), V.bfloat16()
     scale = float(np.float32(d ** -0.5))
-    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=int(lens.max()), max_queries=Nk, attention=form)
-    out = torch.full_like(q, 7.0)
-    hk.attn(q, Cache(K, V, off[:-1], lens), scale, out)
-    torch.cuda.synchronize()
+    grown = K.clone()
+    walks = []   # per unit: the blocks of a whole item (last one first), or those of either half
     for h in range(H):
-        k, v = (x[off[h]:off[h] + lens[h]].double() for x in (K, V))
-        want = torch.softmax(scale * (q[0, h].double() @ k.T.contiguous()), -1) @ v
-        # P and O are rounded to bf16: 2^-8 of the largest value each, |V| up to 4.5
-        assert float((out[0, h].double() - want).abs().max()) < 4e-2, (h, int(lens[h]))
+        nb = (int(lens[h]) + 31) // 32
+        parts = [(0, (nb + 1) // 2), ((nb + 1) // 2, nb)] if form == "halves" else [(0, nb)]
+        walks.append([[hi - 1] + list(range(lo, hi - 1)) for lo, hi in parts])
+        for walk in walks[h]:
+            for step, b in enumerate(walk):
+                rows = slice(int(off[h]) + 32 * b, int(off[h]) + min(32 * b + 32, int(lens[h])))
+                grown[rows] *= 0.25
+                grown[rows, 0] = (step - 5) * 18 / (4.0 * scale)    # 18 nats a block, 26 of the 16 bits that the reference leaves
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=int(lens.max()), max_queries=Nk, attention=form)
+    V = V.bfloat16()
+    for K, grows in ((K.bfloat16(), False), (grown.bfloat16(), form != "stream")):   # (a stream's segments start where its cuts fall)
+        out = torch.full_like(q, 7.0)
+        hk.attn(q, Cache(K, V, off[:-1], lens), scale, out)
+        torch.cuda.synchronize()
+        for h in range(H):
+            k, v = (x[off[h]:off[h] + lens[h]].double() for x in (K, V))
+            logits = scale * (q[0, h].double() @ k.T.contiguous())
+            for walk in walks[h] if grows else []:
+                tops = torch.stack([logits[:, 32 * b:32 * b + 32].amax(1) for b in walk])
+                assert len(walk) < 2 or float((tops[1:] - tops[:-1]).min()) > 12, h    # 16 bits are 11.1 nats
+            want = torch.softmax(logits, -1) @ v
+            # P and O are rounded to bf16: 2^-8 of the largest value each, |V| up to 4.5
+            assert float((out[0, h].double() - want).abs().max()) < 4e-2, (h, int(lens[h]))
     hk.close()
 
 
-@pytest.mark.parametrize("form", ["tile128", "stream", "halves"])
-@pytest.mark.parametrize("d,Nk", [(64, 130), (128, 33), (128, 257)])
+@pytest.mark.parametrize("d,Nk,form", TILE_FORMS)
 def test_tile_attention_where_whole_blocks_score_minus_infinity(d, Nk, form):
     """Keys that score -inf for every query fill the block that a work item, a segment or a half begins with: what is left decides."""
-    if form == "halves" and d != 128:
-        pytest.skip("halves: head_dim 128")
     u = _u()
     lens = np.array([33, 65, 129, 289, 64, 320, 77, 160, 225, 288], np.int32)
     H = len(lens)

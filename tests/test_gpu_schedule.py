@@ -799,22 +799,39 @@ def test_short_units_move_their_rows_in_the_score_launch(head_dim, sides_n, with
 
 
 @pytest.mark.parametrize("attention", ["split", "tile128"])
-@pytest.mark.parametrize("H,n_long", [(7, 1), (8, 300), (9, 575)])
-def test_short_units_beside_longer_ones_in_a_launch_of_their_own(H, n_long, attention):
+@pytest.mark.parametrize("H,n_short,n_long,n_append,apart", [
+    (7, 768, 1, 8, "both"),           # two rounds of short units and one long one
+    (8, 767, 1, 8, "neither"),        # one fewer: no round is spared
+    (9, 495, 300, 6, "both"), (4, 513, 256, 3, "split"),
+    (8, 264, 256, 200, "split"),      # the appending units ride along in front of 128-query attention, where they fill the spared round
+    (9, 321, 575, 4, "neither"),
+])
+def test_short_units_beside_longer_ones_in_a_launch_of_their_own(H, n_short, n_long, n_append, apart, attention):
     """More units than compute units, up to 512 keys and beyond (at 512, 513, 1024), some of them keeping everything: the kept lists
     of the single entry points, which know no such launches, and the listed rows in the cache."""
     from tests import gpu_util as u
-    B, d, n0, n = 100, 64, 900, 124
-    U = B * H
+    d, n0, n = 64, 900, 124
+    U = n_short + n_long + n_append
+    B = U // H
+    assert B * H == U
     hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=U, max_cache_len=n0 + n, max_queries=n0, attention=attention)
     types = (np.arange(H) % 2).astype(np.uint8)
-    # rows after the first compression: long units first, then short ones, in an order of their own; a few keep everything at the end
+    # rows after the first compression: long units first, then short ones and those that keep everything at the end, in an order of their own
     order = np.random.default_rng(H).permutation(U)
     rows = np.empty(U, np.int32)
     rows[order[:n_long]] = np.linspace(513 - n, n0, n_long).astype(np.int32)
     rows[order[n_long:]] = np.linspace(40, 512 - n, U - n_long).astype(np.int32)
     last = (rows // 2).astype(np.int32)
-    last[order[n_long::97]] = 10**6
+    appends = order[n_long + (np.arange(n_append) * (U - n_long)) // max(n_append, 1)]
+    last[appends] = 10**6
+    compressing = last < rows + n
+    short = compressing & (rows + n <= 512)
+    assert (int(compressing.sum()), int(short.sum())) == (n_short + n_long, n_short) and int((rows + n).max()) > 512
+
+    def spared(more):   # rounds over 256 compute units, of which two short units share one
+        return -(-(n_short + n_long + more) // 256) - -(-n_short // 512) - -(-(n_long + more) // 256)
+    rides = n_append if attention == "tile128" else 0
+    assert (spared(0) > 0 and spared(rides) > 0) == (apart in ("both", attention))
     mc = hk.managed_cache(np.maximum(rows + n, n0))
     gen = torch.Generator(u.DEV)
     gen.manual_seed(n_long)
@@ -837,7 +854,7 @@ def test_short_units_beside_longer_ones_in_a_launch_of_their_own(H, n_long, atte
         assert int((mine & (kept != want)).sum()) == 0
         off, length = mc.view()
         assert np.array_equal(length, np.minimum(budget, t_in))
-        for x in list(order[:3]) + list(order[-200:]) + list(order[n_long::97]):
+        for x in list(order[:3]) + list(order[-200:]) + list(appends[:8]):
             b, h = divmod(int(x), H)
             o0, l0 = int(src.off[x]), int(src.len[x])
             at = want[x, :ln[x]].long() if budget[x] < t_in[x] else torch.arange(int(t_in[x]), device=u.DEV)
