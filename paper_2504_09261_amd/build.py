@@ -24,7 +24,8 @@ DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang"
                 "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 # The score kernels read every MFMA result with the vector ALU straight away:
 # keeping the accumulators in VGPRs spares one AGPR copy per result register.
-# The attention kernels' accumulators pass a rare branch in every stage: cut into pieces there, they are copied on both ways.
+# The attention kernels' accumulators pass a rare branch in every stage: cut into pieces there, they no longer fit the
+# registers (a launch of 568 us takes 8840).
 PER_SOURCE = {"kernels_attn.hip": ["-mllvm", "-amdgpu-codegenprepare-break-large-phis=false"],
               "kernels_score.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option", "-Wno-inline-asm",

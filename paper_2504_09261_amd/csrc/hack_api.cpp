@@ -348,14 +348,14 @@ void build_attn_items(const std::vector<UnitDesc>& descs, int N_k, int tile_rows
 // and a step that does not compress then needs no separate append launch.  It is
 // used while all of its work items are resident at once or nearly so; beyond
 // that the 128-query kernel, which shares every K/V block among four times as
-// many queries, is faster.  Measured cross-overs on MI355X: head_dim 128 between
-// 416 and 576 items (16 heads, batch 2); head_dim 64 between 1920 and 3840 items
-// (30 heads, batch 32).  At head_dim 64 tiles of 128 queries win earlier where they are nearly full and all start together.  Whole steps,
-// split / 128 queries, us; compressing to 102 and 1200 rows, appending to as many: 960 queries, 1800 items 26.4 / 25.5, 59.3 / 52.8; 56.9 / 46.0,
-// 81.1 / 64.2; 900, 1450 23.8 / 23.3, 53.8 / 49.4; 46.7 / 41.8, 69.7 / 58.2; 512, 1920 26.6 / 25.8, 66.7 / 62.3; 39.5 / 33.1, 65.3 / 51.8; 256, 1920
-// 21.9 / 19.6, 88.2 / 84.1; 26.6 / 24.6, 57.0 / 46.7; 256, 1600 20.5 / 18.6, 78.0 / 79.6; 22.6 / 22.9, 47.9 / 42.9; 256, 1440 20.0 / 18.5, 70.1 / 74.0;
-// 20.9 / 22.4, 40.9 / 38.3; 256, 1280 18.5 / 17.7, 58.7 / 64.3; 18.5 / 20.5, 37.9 / 39.3.  In two rounds of them or part empty they lose: 576, 1980 27.2 / 27.2,
-// 63.6 / 66.5; 41.1 / 43.1, 66.7 / 67.8; 224, 1960 25.6 / 24.8, 92.1 / 96.7; 24.7 / 29.0, 51.4 / 53.6; 140, 2000 24.6 / 25.9, 131 / 146; 21.9 / 29.1, 52.3 / 64.9.
+// many queries, is faster.  Whole steps on their own, split / 128 queries, us.  head_dim 128, compressing to 300 and 1943 rows, appending to as
+// many: 512 queries, 512 items 29.5 / 31.9, 61.9 / 60.6; 22.5 / 29.4, 40.9 / 40.4; 576, 576 33.8 / 31.9, 76.6 / 66.1; 29.5 / 29.2, 57.8 / 47.6.
+// head_dim 64: up to 2048 items, but tiles of 128 queries win earlier where they are nearly full and all start together.  Compressing to 102
+// and 1200 rows, appending to as many: 960 queries, 1800 items 32.4 / 29.8, 64.5 / 56.6; 40.0 / 36.9, 64.9 / 54.8; 900, 1450 27.5 / 27.4, 59.3 / 54.3;
+// 33.7 / 33.6, 56.2 / 51.0; 512, 1920 30.6 / 29.9, 67.7 / 61.8; 29.7 / 29.8, 56.0 / 46.4; 256, 1920 25.6 / 23.4, 86.6 / 82.9; 24.3 / 26.1, 51.6 / 42.1;
+// 256, 1600 24.1 / 22.4, 76.6 / 78.6; 22.6 / 25.8, 45.0 / 41.5; 256, 1440 23.2 / 22.2, 73.1 / 76.9; 21.5 / 24.6, 41.4 / 40.8; 256, 1280 22.6 / 21.9,
+// 60.4 / 65.3; 20.4 / 23.6, 37.6 / 40.2.  In two rounds of them or part empty they lose: 576, 1980 31.1 / 31.5, 67.0 / 68.4; 32.0 / 34.9, 57.5 / 58.2;
+// 224, 1960 29.1 / 28.7, 94.6 / 97.9; 23.8 / 30.4, 51.9 / 51.0; 140, 2000 28.4 / 30.3, 128.5 / 142.3; 21.7 / 29.2, 49.6 / 60.0.
 bool use_split_attention(const hack_ctx* ctx, int n_units, int N_k) {
   if (ctx->cfg.dtype != HACK_BF16) return false;
   const int tile = attn_split_q_tile_rows();
@@ -369,14 +369,15 @@ bool use_split_attention(const hack_ctx* ctx, int n_units, int N_k) {
 
 // Launches of 128-query work items that leave a compute unit one of them take the form that walks the two halves of the keys
 // side by side: one work-group alone feeds a compute unit's matrix cores at half of their rate.  Measured, us a launch, whole
-// keys / halves (head_dim 128): 256 items of 28, 41, 79 blocks 26.4 / 24.3, 31.7 / 30.4, 54.9 / 49.7; 160 items of 25, 41, 47, 157
-// 21.4 / 22.0, 29.4 / 27.9, 33.2 / 31.1, 91 / 76; of 17 blocks 20.0 / 21.2.  A compute unit holds one such work-group: beyond one per
-// compute unit of an XCD it loses (416 items 113 / 126).
+// keys / halves (head_dim 128): 256 items of 28, 41, 79 blocks 23.3 / 23.0, 30.5 / 29.0, 51.5 / 47.2; 160 items of 25, 41, 47, 157
+// 19.9 / 19.7, 27.7 / 26.2, 30.6 / 29.0, 84.7 / 71.1; of 17 blocks 15.6 / 16.2.  A compute unit holds one such work-group: beyond one per
+// compute unit of an XCD it loses (416 items 102 / 110).
 // Where few items are long, whole items with the long ones cut over the idle compute units (plan_attn_cuts) are the better form: 144 to 256
-// items of 16 to 64 units, a quarter of them of 160 blocks and the rest of 16: 65 to 67 us in halves, 39 to 53 so; half of 80, the rest of 24: 38 to 41
-// and 33 to 40; three quarters of 160, the rest of 16: 67 to 83 and 55 to 88.  A pair of blocks takes a microsecond in halves, and otherwise a
-// compute unit works off 1.7 blocks in one and the launch takes 8 besides: over 576 such launches this picks a form that is 0.2 % slower than the better
-// one on average, 8 % at most (always halves: 6 and 77 %).
+// items of 16 to 64 units, a quarter of them of 160 blocks and the rest of 16: 66 to 70 us in halves, 41 to 46 so; half of 80, the rest of 24: 40 to 43
+// and 37 to 40; three quarters of 160, the rest of 16: 71 to 78 and 58 to 82.  The rule puts a pair of blocks at a microsecond in halves, and otherwise a
+// compute unit at 1.7 blocks in one and 8 for the launch besides.  These rates were fitted to a stage that took longer (a pair now takes 0.78); with the
+// present one, over 480 such launches, it picks a form that is 0.2 % slower than the better one on average, 10 % at most (always halves: 13 and 77 %,
+// never: 2 and 15 %).
 constexpr int kHalvesMinBlocks = 28;
 // items: left empty, or the launch's whole work items.
 bool use_key_halves(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, int N_k, std::vector<AttnItem>* items) {
@@ -409,14 +410,14 @@ int attn_tile_rows(const hack_ctx* ctx, int n_units, int N_k) {
 // key blocks per resident work-group (plan_attn_stream), so that every work-group holds the same number of
 // blocks whatever the number and the lengths of the work items are; work items that a cut falls into are
 // put together from partial results.  OFF by default (HACK_ATTN_STREAM=1 when the context is created
-// switches it on for every launch of the 128-query kernel): on MI355X it measured slower than one work
-// item per work-group on all but one step of the benchmark workloads (1024^2 schedules, scale steps 9-13,
-// us per launch, plain / streamed: 16 heads x batch 2: 34 / 39, 56 / 64, 113 / 104, 136 / 140, 222 / 230;
-// 32 heads x batch 2: 51 / 54, 74 / 92, 159 / 175, 253 / 270, 425 / 527).  In-kernel time stamps show why:
-// of the two work-groups that share a compute unit the older one is served first and runs the steady
-// loop at 0.73-0.76 us per key block, the younger one at 0.97-1.0 (0.55 alone), so equal shares finish
+// switches it on for every launch of the 128-query kernel): on MI355X it measured no faster than one work
+// item per work-group on any step of the benchmark workloads (1024^2 schedules, scale steps 9-13,
+// us per launch, plain / streamed: 16 heads x batch 2: 30 / 37, 48 / 59, 100 / 100, 116 / 135, 186 / 220;
+// 32 heads x batch 2: 46 / 53, 65 / 90, 141 / 172, 214 / 254, 356 / 428).  In-kernel time stamps, taken with an earlier
+// stage of 32x32x16 instructions, show why: of the two work-groups that share a compute unit the older one is served first and ran the
+// steady loop at 0.73-0.76 us per key block, the younger one at 0.97-1.0 (0.55 alone), so equal shares finish
 // up to 30 % apart and the launch lasts as long as the slowest; the hardware's own dispatch of whole work
-// items absorbs that difference.  On top come about 3 us per extra segment (pipeline fill), 3-4 us per
+// items absorbs that difference.  On top came about 3 us per extra segment (pipeline fill), 3-4 us per
 // partial result written and 3-4 us per part added up.
 // `shared` says that another attention launch of the context may run at the same time (the partial-result
 // arrays are the context's), which rules the streamed form out.
@@ -425,12 +426,14 @@ int attn_tile_rows(const hack_ctx* ctx, int n_units, int N_k) {
 // whose compute unit would finish last under the measured pair model, if that shortens the modelled launch by
 // kCutMinGain.  On the 1024^2 benchmark workloads this fires at scale step 11 with 16 heads x batch 2 (416 work
 // items on 256 compute units: the long items that would share a compute unit with another long one are
-// halved; 113.7 -> 98.8 us measured, 111.8 -> 89.3 modelled) and at step 9 with 32 heads x batch 2 (50.3 ->
-// 42.8 us measured, 45.3 -> 35.0 modelled).  Launches with more work items than resident work-groups are
+// halved; 99.8 -> 83.8 us) and at step 9 with 32 heads x batch 2 (46.4 -> 37.9 us).  Launches with more work items than resident work-groups are
 // left alone (there the model is 10-15 % off), unless all items are of one length and a few of them make up a last round
-// (plan_attn_tail: the whole cache of a 1024^2 image, scale step 12, 285 -> 237 us).  HACK_ATTN_STREAM=0 switches it off, =4 applies every cut
+// (plan_attn_tail: the whole cache of a 1024^2 image, scale step 12, 250 -> 204 us).  HACK_ATTN_STREAM=0 switches it off, =4 applies every cut
 // the model likes (tests).
-constexpr AttnPairModel kPairModel128{0.55, 0.75, 1.0, 4.0, 14.0};   // us per key block alone / first / second of a pair; fixed costs in blocks
+// The model's rates, us per key block alone / first / second of a pair, are those of the earlier stage; equal pairs take 0.89 a block by them.  The
+// present stage takes 0.53 alone and 0.87 in pairs (slopes of 256 and 512 equal items of 50 to 300 blocks).  0.5 / 0.7 / 0.92, 0.5 / 0.78 / 0.85 and
+// 8, 10 or 20 blocks for the fixed cost of a piece changed no schedule by more than 0.3 %.
+constexpr AttnPairModel kPairModel128{0.55, 0.75, 1.0, 4.0, 14.0};   // and fixed costs in blocks: a whole item, a piece of a cut one
 constexpr double kCutMinGain = 0.05;
 constexpr int kCutMinBlocks = 8;
 constexpr int kStreamOverheadBlocks = 4;   // start and end of a segment, in key blocks of the steady loop

@@ -2,23 +2,13 @@
 // (Preliminaries, attention equation: O = Softmax(scale * Q K^T) V, no mask
 // inside a scale step) on gfx950.
 //
-// bf16 path (flash-style, one pass over K/V with an online softmax):
-//   * work item = (unit, tile of 4 waves x 32 queries); K/V blocks of 32 keys
-//     are staged once per work-group in LDS and shared by the four waves.
-//   * S^T = K Q^T with v_mfma_f32_32x32x16_bf16: the accumulator then holds,
-//     per lane, one query column and 16 key rows, so the softmax row reductions
-//     are in-lane plus one exchange with lane^32, and the running max / rescale
-//     factor are per-lane scalars.
-//   * O^T += V^T P^T: P^T goes from the accumulator registers straight into the
-//     B operand (C rows 8(r/4)+4h+r%4 of registers 8s..8s+7 are exactly two runs
-//     of four consecutive keys), and V^T comes from row-major V in LDS through
-//     the transposing LDS read (ds_read_b64_tr_b16), four keys per read.
-//   * the loop runs over 32-key blocks, software-pipelined by one block: the
-//     scores of block b+1 are formed while block b is exponentiated.
-//   * K/V blocks travel HBM -> LDS directly (no register round trip) through a
-//     ring of four slots per tensor, one barrier per block; an XOR swizzle of
-//     16-byte chunks keeps the b128 K reads and the transposing V reads
-//     bank-conflict free.
+// bf16, flash-style: one pass over K/V with an online softmax; a work item is a unit and 128 queries, four waves of 32, which share every
+// block of 32 keys through LDS.  S^T = K Q^T and O^T += V^T P^T, so that a lane owns query columns: the softmax reductions are in-lane plus an
+// exchange between lanes that hold the same query, the probabilities go from the accumulator registers straight into the B operand,
+// and V^T comes from row-major V through the transposing LDS read (ds_read_b64_tr_b16).  K/V blocks travel HBM -> LDS directly (no
+// register round trip) through a ring of four slots per tensor.
+//   * attn_pipe, which serves the launches: 16x16x32 matrix instructions, scores, softmax and PV product of three blocks side by side.
+//   * attn_mfma, a second implementation that tests and A/B timings select (HACK_ATTN_PIPE=0): 32x32x16 matrix instructions, one block ahead.
 #include <cfloat>
 #include <type_traits>
 
@@ -37,7 +27,9 @@ using namespace dev;
 constexpr int kKB = 32;      // keys per block (one LDS ring slot)
 constexpr float kRescaleAbove = 65536.f;  // a block sum of probabilities at or above this moves the reference
 
-// NW waves per work-group, each wave owns 32 queries; two work-groups share a CU.
+// NW waves per work-group, each wave owns 32 queries; two work-groups share a CU.  The accumulator of v_mfma_f32_32x32x16_bf16 holds one query
+// column and 16 key rows a lane, the other 16 are lane ^ 32's; registers 8s .. 8s+7 are two runs of four consecutive keys (C rows
+// 8(r/4)+4h+r%4), the order in which V^T is read.  A swizzle of 16-byte chunks keeps both LDS reads free of bank conflicts.
 //
 // The loop runs over 32-key blocks and is software-pipelined by one block: while
 // the vector ALU turns the scores of block b into probabilities, the matrix core
@@ -338,27 +330,29 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma(
 // bf16 MFMA path, deeper software pipeline (the kernel that serves the large steps)
 // ---------------------------------------------------------------------------
 // The work item of attn_mfma above, with 16x16x32 MFMAs: the chip runs these launches at its power limit, where the bare 16x16x32
-// instruction on random operands sustains 2.05 PFLOP/s and the 32x32x16 one 1.78 (and the bf16 dot product for row sums runs on the matrix
-// core as well, 17 cycles each).  A wave holds 32 queries as two tiles of 16, S^T of a block as 2x2 tiles: a lane has one query column
-// and four keys of each, P^T goes from the accumulators into the B operand of O^T += V^T P^T in that order of keys, and V^T is read
-// from LDS in the same order.  Row sums are one more tile of that product, with a V^T of ones (the bf16-rounded probabilities, summed in float32).
+// instruction on random operands sustains 2.07 PFLOP/s (at 2.03 GHz) and the 32x32x16 one 1.83 (at 1.78 GHz).  A wave holds 32 queries as two
+// tiles of 16, S^T of a block as 2x2 tiles: a lane has one query column and four keys of each, P^T goes from the accumulators into the B operand of
+// O^T += V^T P^T in that order of keys, and V^T is read from LDS in the same order.  Row sums are one more tile of that product, with a V^T of ones
+// (the bf16-rounded probabilities, summed in float32): between MFMAs a bf16 dot product adds 17 cycles, a multiply-add half a cycle.
 // A stage (one barrier) holds three independent strands:
 //     S(b+1)   the score MFMAs of the next block          (matrix core)
 //     PV(b-1)  O^T += V^T P^T of the previous block       (matrix core)
 //     softmax(b): multiply-adds, exponentials, packing    (vector ALU)
 // in slots of one MFMA, one LDS read and a share of the vector work, in the order written: an MFMA takes 8 cycles of the issue port that
-// vector instructions share and leaves 8 of its 16, so work that bunches up stands still in the matrix core (left to the scheduler's
-// group hints, the same stage took 970 cycles instead of 770).  Operands are read a step (eight slots) ahead, across stages too.
+// vector instructions share and leaves 8 of its 16, so work that bunches up stands still in the matrix core.  Operands are read a step
+// (eight slots) ahead, across stages too.
 // The probabilities of block b wait in registers for one stage; the check "did a probability leave the safe range" travels beside
 // the last MFMAs, and the rare rescale that follows it sits at the end of the stage, after PV(b-1) has been added, so a rescale
 // always meets accumulators that are complete up to block b-1.
 // LDS: four slots per tensor.  K(j) is read from the end of stage j-2 on through stage j-1, V(j) from the end of stage j on through
 // stage j+1.  The barrier in the middle of stage b publishes K(b+2) and V(b); behind it the copies K(b+4) and V(b+2) go into the
 // slots of K(b) and V(b-2), which every wave finished reading in stage b-1.  Each copy has two stages to land.
-// Compiled without -amdgpu-codegenprepare-break-large-phis: its pieces of the accumulators cost 36 register copies a stage.
-// Measured, us a launch, 32x32x16 in a three-slot ring / this: head_dim 128, 32 units of 4096 queries over 10521 keys 603 / 552
-// (1.28 PFLOP/s), 128 units of 4096 over 3010 or 6020 1215 / 1106, 32 units of 4096 over 1943 or 3885 204 / 185; 576 queries over 1497 33.0 / 30.7.
-// Counters at the first of them: clock 1.65 -> 1.9 GHz.
+// Measured, us a launch of whole items, 32x32x16 in a three-slot ring / this: head_dim 128, 32 units of 4096 queries over 10521 keys 613 / 568
+// (1.24 PFLOP/s), 128 units of 4096 over 3010 or 6020 1226 / 1120, 64 units of 4096 over 1579 or 4735 384 / 356, 32 units of 4096 over 1943 or 3885
+// 205 / 187; 576 queries over 1497 31.9 / 29.7.  Counters at the first of them: 1021 / 983 thousand shader cycles (747 a stage and SIMD, the matrix core
+// busy in 73 % of them, 66 % before), so 1.67 / 1.73 GHz.  Of this, at the first two: with the order of a stage left to the compiler 580 and 1141, with row
+// sums by dot products 574 and 1147.  The accumulators pass a branch in every stage and must not be cut into pieces there (compiled without
+// -amdgpu-codegenprepare-break-large-phis=false they do not fit the registers: 8840 us).
 
 // Reference: 2^15 above the running maximum, so that the exponent's top bit says that a probability reached 2 (or inf, as in the very
 // first block): bf16 and float32 keep their precision down to 2^-126, 2^-111 of a row's largest probability.
@@ -485,8 +479,10 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_pipe(
   const int n_blocks = (len + kKB - 1) / kKB;
   // LDS layout of a block: rows in groups of four, a group's 64-byte pieces row after row (piece c of row r at
   // (r / 4) 8D + 256 c + 64 (r % 4)), the 16-byte chunks of a piece permuted by the group: chunk x holds x ^ (group & 3) in K and
-  // x ^ 2 (group & 1) in V.  A phase of the operand reads (16 rows x 16 bytes of K, 8 rows x 32 bytes of V) then covers all banks, the lanes
-  // of a copy read whole 64-byte pieces, and all operands of a block stand at constant distances from one address in K and two in V.
+  // x ^ 2 (group & 1) in V.  A phase of the V reads (8 rows x 32 bytes) then covers all banks; a phase of the K reads takes four lanes each of
+  // all four groups, two of them at the same chunks (SQ_LDS_BANK_CONFLICT a third of SQ_LDS_IDX_ACTIVE; with x ^ (group & 2 ? 3 : 0) none, and no
+  // faster: 580 us for 578 over 10521 keys).  The lanes of a copy read whole 64-byte pieces, and all operands of a block stand at constant distances
+  // from one address in K and two in V.
   // The copy instructions of a block are 16 rows apart: same lane offsets, another base.
   static_assert(IPW == 1 || NW * RPI == 16, "lane offsets are those of the first instruction");
   constexpr int GPI = RPI / 4;                     // groups of four rows covered by one copy instruction
