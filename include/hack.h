@@ -67,7 +67,8 @@ typedef struct {
   int32_t head_dim;      /* 64 or 128 */
   int32_t dtype;         /* hack_dtype of q/k/v/out and of the cache */
   int32_t max_units;     /* largest B*H of any call */
-  int32_t max_cache_len; /* largest T_in (cache rows + current scale) of any unit */
+  int32_t max_cache_len; /* largest T_in (cache rows + current scale) of any unit that is scored, selected or compressed;
+                             attention and steps that only append take longer units */
   int32_t max_queries;   /* largest N_k */
   int32_t n_obs;         /* observation queries N_obs, 1..32 (paper: 32) */
 } hack_config;

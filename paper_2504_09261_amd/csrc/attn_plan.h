@@ -295,7 +295,7 @@ inline bool plan_attn_cuts(const std::vector<AttnLaneItem> (&lanes)[kAttnXcds], 
 // r items on its own compute units, each at the pace of a lone work-group (the longest items of a launch come first, so items of
 // different lengths even this out by themselves, and cutting them measured slower).  The r last items are cut into as many
 // pieces as give every compute unit of the XCD at most one, four at most: the parts of an item are added up one after the other.
-// Measured (head_dim 128, 32 compute units an XCD), us a launch, whole / cut by this rule: 72 items an XCD of 40, 50, 100, 200 blocks 61 / 57,
+// Measured (head_dim 128, 32 compute units an XCD), us a launch, whole / cut by this rule: 72 items an XCD of 40, 50, 100, 200 blocks 62 / 57,
 // 74 / 69, 132 / 115, 251 / 207; of 25 blocks 45 / 44; 68 of 200 249 / 202; 80 of 50 and 200 74 / 70, 258 / 232; 84 of 100 137 / 135; 136 of 100
 // 216 / 200; 200 of 100 302 / 290.  Pieces, with an earlier stage that took longer, whole / 2 / 3 / 4: 72 items of 50, 100, 200 blocks
 // 88 / 80 / 77 / 77, 151 / 134 / 129 / 129, 287 / 246 / 235 / 229; 80 of 200 287 / 255 / 266 / 258; 84 of 100 160 / 160 / 151 / 157.
