@@ -4,16 +4,23 @@
 // The first scale steps of a next-scale schedule have a handful to a few
 // hundred queries per unit: tiles of 128 queries leave most of the chip idle
 // and every work-group walks the whole cache alone.  Here a work item is
-// (unit, 32 queries) and its four waves split the KEYS: wave w takes the 32-key
-// blocks w, w+4, ... with a private online softmax, and the four partial
-// results (running max, normaliser, unnormalised O) are merged through LDS at
+// (unit, 32 queries), a work-group takes one or half of one (sixteen_queries), and its four or eight waves split the KEYS: wave w
+// of four takes the 32-key blocks w, w+4, ... with a private online softmax, and the partial
+// results (reference, normaliser, unnormalised O) are merged through LDS at
 // the end.  There is no work-group barrier inside the loop: K and V blocks
 // travel HBM -> LDS directly (global_load_lds, whole rows, so the copies are
 // fully coalesced) into one private K slot and one private V slot per wave; the
 // copy of the next K block is issued as soon as the score MFMAs have read the
 // current one, the copy of the next V block as soon as the PV MFMAs have read
 // theirs.  K fragments are read with ds_read_b128, V^T through the transposing
-// LDS read, with the same bank-conflict-free swizzles as the large-step kernel.
+// LDS read, with swizzles free of bank conflicts.  S^T = K Q^T and O^T += V^T P^T in 16x16x32 matrix instructions; row sums are one
+// more tile of the latter, against ones.
+// The queries come through LDS too: read straight from memory into the operand registers of all waves, 32 rows x 32 bytes an instruction, they
+// kept the memory pipeline busy for longer than a block takes (in-kernel time stamps, 32 units of 256 queries over 521 keys, head_dim 128: 1.1 us
+// of 10.5).  With that and the first block of V awaited behind the first scores, us a launch, before / now: head_dim 128, 32 units, queries over
+// keys: 4 over 5 4.0 / 3.1, 64 over 121 5.4 / 4.5, 144 over 265 8.0 / 6.9, 256 over 521 10.2 / 9.0, 400 over 921 16.9 / 14.2; head_dim 64: 60 units, 64 over 155
+// 5.2 / 4.1, 256 over 306 7.4 / 6.5, 960 units, 36 over 91 11.6 / 9.9, 27 units, 1369 over 640 19.4 / 18.2.  What is left is a chain: at 121 keys some 0.3 us for the
+// item, 0.6 to issue the copies, 0.4 until they have landed, 0.8 the block and 0.7 the merge (first passes through the code), in front of it the launch.
 // Optionally the kernel also performs the cache update of the step (cache-update
 // equation of the Preliminaries): keys are then read from the virtual
 // concatenation [cached rows | rows of the current scale] and work item t
@@ -29,6 +36,7 @@
 // the way through the list, and beside matrix work that already draws all the power the
 // chip may take, the moving work-groups cost what they cost alone (1024^2 schedules
 // 784 / 1267 / 3326 us as separate launches, 763 / 1254 / 3355 fused).
+#include <cfloat>
 #include <type_traits>
 
 #include "device_util.h"
@@ -41,28 +49,37 @@ namespace {
 using namespace dev;
 
 constexpr int kKB = 32;        // keys per block
-constexpr int kQTile = 32;     // queries per work item
+constexpr int kItemRows = 32;  // queries per work item
+
+// V rows are read by v_mfma_f32_16x16x32_bf16 operand: one phase of the transposing read covers 8 rows x 32 bytes.
+template <int D> __device__ __forceinline__ int swz_v16(int r) { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); }
+
+// The reference of a row's probabilities lies 2^15 above its running maximum, so that the exponent's top bit says that one of them
+// reached 2: float32 and bf16 keep their precision down to 2^-111 of the row's largest probability.
+constexpr float kHeadroom = 15.f;
 
 // fuse != 0: keys are [rows in_off .. in_off+len_in of the cache | the unit's n_new
 // rows of k_new / v_new], and those new rows are also written behind the cached
 // ones (k_app / v_app / pos_app are the cache arrays, which k_cache / v_cache then
 // alias: reads stay below row len_in, writes at or above it).
 // fuse == 0: keys are rows [out_off, out_off + n_out) of the cache.
-template <int D, bool GATHER, int kWaves>   // kWaves waves per work-group = key splits
+// NQ tiles of 16 queries a work-group (2: a work item, 1: half of one), kWaves waves = key splits.
+template <int D, bool GATHER, int NQ, int kWaves>
 __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     const UnitDesc* __restrict__ descs, const AttnItem* __restrict__ items, const __bf16* __restrict__ q,
     const __bf16* k_cache, const __bf16* v_cache, const __bf16* k_new, const __bf16* v_new, __bf16* k_app,
     __bf16* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k, float scale, __bf16* __restrict__ out, GatherArgs ga) {
-  constexpr int KK = D / 16;        // MFMA steps over head_dim for S^T
-  constexpr int MB = D / 32;        // 32-row blocks of O^T
+  constexpr int KC = D / 32;        // MFMA steps over head_dim for S^T
+  constexpr int MT = D / 16;        // 16-row tiles of O^T
   constexpr int CPR = D / 8;        // 16-byte chunks per row
   constexpr int RPI = 64 / CPR;     // block rows covered by one wave-wide copy instruction
-  constexpr int IPB = kKB / RPI;    // copy instructions per V block
+  constexpr int IPB = kKB / RPI;    // copy instructions per block and tensor
   constexpr int BLK = kKB * D;      // elements per block
+  constexpr int QROWS = 16 * NQ;    // queries of this work-group
 
   constexpr int XI = GATHER ? 1 : 0;   // list copies per block
-  // list entries of this wave's blocks w, w + kWaves, ...: block b in slot (b / kWaves) % 4 (a copy also fills the 32 words behind it)
-  __shared__ __attribute__((aligned(256))) int idx_ring[GATHER ? kWaves : 1][GATHER ? 4 * 2 * kKB : 1];
+  // list entries of this wave's blocks w, w + kWaves, ...: block b in slot (b / kWaves) % 4
+  __shared__ __attribute__((aligned(256))) int idx_ring[GATHER ? kWaves : 1][GATHER ? 4 * kKB : 1];
   if constexpr (GATHER) {
     const int mover = (int)blockIdx.x - ((int)gridDim.x - ga.n_moves);
     if (mover >= 0) {
@@ -70,25 +87,26 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
       return;
     }
   }
-  const AttnItem it = items[blockIdx.x];
-  if (it.desc < 0) return;
+  // The halves of an item follow each other on its XCD (work-group id mod 8).
+  const AttnItem it = items[NQ == 1 ? (blockIdx.x >> 4) * 8 + (blockIdx.x & 7) : blockIdx.x];
+  const int q0 = it.q_tile * kItemRows + (NQ == 1 ? 16 * ((blockIdx.x >> 3) & 1) : 0);
+  if (it.desc < 0 || q0 >= N_k) return;
   const AttnItem& d = it;   // the item carries the descriptor fields read here
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int col = lane & 31, half = lane >> 5;
+  const int col = lane & 15, g = lane >> 4;
 
   const int total = d.n_out;                       // keys attended over
   const int len_c = fuse ? d.len_in : d.n_out;     // of which come from the cache
   const int64_t base = fuse ? d.in_off : d.out_off;
   const int64_t new_row0 = (int64_t)d.unit * N_k;  // first row of the unit in q / k_new / v_new / out
-  const int q0 = it.q_tile * kQTile;
 
-  // per wave one K slot [0] and one V slot [1]; after the loop the pair holds the
-  // wave's unnormalised O^T (same size)
-  __shared__ __attribute__((aligned(1024))) __bf16 Vs[kWaves][2][BLK];
-  __shared__ float m_sh[kWaves][32], l_sh[kWaves][32];
+  // [0]: K, [1]: V; after the loop a wave's pair holds its unnormalised O^T
+  __shared__ __attribute__((aligned(1024))) __bf16 ring[kWaves][2][BLK];
+  __shared__ __attribute__((aligned(1024))) __bf16 q_sh[QROWS * D];
+  __shared__ float m_sh[kWaves][QROWS], l_sh[kWaves][QROWS];
 
-  // Block b of K (slot 0) or V (slot 1) into this wave's LDS: lane l of copy
+  // Block b of K or V into this wave's LDS: lane l of copy
   // instruction i fills LDS row r = i RPI + l / CPR, chunk position c = l % CPR, from
   // global chunk c ^ swz(r) of key row b*32 + r.  A block that lies wholly in the
   // cache or wholly in the new rows is a contiguous piece of memory: uniform base
@@ -98,41 +116,51 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
   // bits.  The first scales' only block is ragged: formed from 64-bit row numbers those addresses stood 1 us in front of it
   // (head_dim 128, four steps of 32 units 25.2 -> 23.8 us), and copying 32 rows where there are 1 to 21 half a microsecond
   // (with a one-block unit stored straight from its wave's registers 24.0 -> 23.3; one 256^2 image 91.3 -> 90.3).
-  const unsigned vs_lds = lds_addr_of(&Vs[0][0][0]);
-  unsigned k_src[IPB], v_src[IPB];
+  // Copies KP (K) or VP (V) apart differ by whole rows only.
+  constexpr int KP = D == 128 ? 4 : 2, VP = D == 128 ? 2 : 1;
+  unsigned k_src[KP], v_src[VP];
 #pragma unroll
-  for (int i = 0; i < IPB; ++i) {
+  for (int i = 0; i < KP; ++i) {
     const int r = i * RPI + lane / CPR, c = lane % CPR;
     k_src[i] = (unsigned)(r * D + ((c ^ swz_k<D>(r)) & (CPR - 1)) * 8) * 2u;
-    v_src[i] = (unsigned)(r * D + ((c ^ swz_v<D>(r)) & (CPR - 1)) * 8) * 2u;
+    if (i < VP) v_src[i] = (unsigned)(r * D + ((c ^ swz_v16<D>(r)) & (CPR - 1)) * 8) * 2u;
   }
-  const unsigned k_lds = vs_lds + (unsigned)((w * 2 + 0) * BLK * 2), v_lds = vs_lds + (unsigned)((w * 2 + 1) * BLK * 2);
-  auto issue = [&](auto k_tag, bool first, int b, const __bf16* cache, const __bf16* fresh, const unsigned (&src)[IPB], unsigned lds) {
+  auto lds_of = [&](int wave, int v) { return lds_addr_of(&ring[0][0][0]) + (unsigned)((wave * 2 + v) * BLK * 2); };
+  // first: in front of the loop, which counts a block's copies in flight; only the rows there are travel then, of these the
+  // copies i0, i0 + di, ...; what the K slot holds behind them is masked, and the V slot is cleared.
+  auto issue = [&](auto k_tag, bool first, int i0, int di, int b, const __bf16* cache, const __bf16* fresh, const auto& src, unsigned lds) {
     constexpr bool IS_K = decltype(k_tag)::value;
     const int j0 = b * kKB;
     const __bf16* blk = nullptr;
     if (j0 + kKB <= len_c) blk = cache + (base + j0) * D;
     else if (j0 >= len_c && j0 + kKB <= total) blk = fresh + (new_row0 + (j0 - len_c)) * D;
-    if (blk != nullptr) {
+    if (blk != nullptr && di == 1) {
 #pragma unroll
-      for (int i = 0; i < IPB; ++i) load_to_lds(blk, src[i], lds + (unsigned)(i * 1024));
+      for (int i = 0; i < IPB; ++i) {
+        constexpr int P = IS_K ? KP : VP;
+        load_to_lds(blk + i / P * (P * RPI * D), src[i % P], lds + (unsigned)(i * 1024));
+      }
     } else {
       const __bf16* const in_cache = cache + (base + j0) * D;                 // row j0 of the unit, were it cached
       const __bf16* const in_fresh = fresh + (new_row0 + (j0 - len_c)) * D;   // ... or a new one
       const int last = total - 1 - j0;
-      // The loop below counts a block's copies in flight.  In front of it only the rows there are travel; what the K slot holds
-      // behind them is masked, and the V slot is cleared.
-      const int n = first ? min(IPB, last / RPI + 1) : IPB;
-#pragma unroll 1
-      for (int i = 0; i < n; ++i) {
+      auto row_copy = [&](int i) {
         const int r = i * RPI + lane / CPR, rc = min(r, last);
-        const unsigned off = (unsigned)(rc * D + (((lane % CPR) ^ (IS_K ? swz_k<D>(r) : swz_v<D>(r))) & (CPR - 1)) * 8) * 2u;
+        const unsigned off = (unsigned)(rc * D + (((lane % CPR) ^ (IS_K ? swz_k<D>(r) : swz_v16<D>(r))) & (CPR - 1)) * 8) * 2u;
         load_to_lds(reinterpret_cast<const char*>(j0 + rc < len_c ? in_cache : in_fresh) + off, lds + (unsigned)(i * 1024));
+      };
+      if (!first) {
+#pragma unroll
+        for (int i = 0; i < IPB; ++i) row_copy(i);
+        return;
       }
-      if (!IS_K) {
-        uintx4* slot = reinterpret_cast<uintx4*>(&Vs[w][1][0]) + lane;
+      const int n = min(IPB, last / RPI + 1);
 #pragma unroll 1
-        for (int i = n; i < IPB; ++i) slot[i * 64] = uintx4{0u, 0u, 0u, 0u};
+      for (int i = i0; i < n; i += di) row_copy(i);
+      if (!IS_K) {
+        uintx4* slot = reinterpret_cast<uintx4*>(&ring[0][0][0]) + (lds - lds_of(0, 0)) / 16 + lane;
+#pragma unroll 1
+        for (int i = n + (i0 - n % di + di) % di; i < IPB; i += di) slot[i * 64] = uintx4{0u, 0u, 0u, 0u};
       }
     }
   };
@@ -150,56 +178,80 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     kn = static_cast<const char*>(ga.k_new) + rn;
     vn = static_cast<const char*>(ga.v_new) + rn;
   }
-  int* const ring = &idx_ring[GATHER ? w : 0][0];
-  const unsigned ring_lds = lds_addr_of(ring);
+  int* const xring = &idx_ring[GATHER ? w : 0][0];
+  const unsigned ring_lds = lds_addr_of(xring);
   auto issue_x = [&](int b) {   // b = w + kWaves i; past the end: entries of the last block
     const int b0 = min(b, n_blocks - 1);
-    load_to_lds_dword(list + b0 * kKB, (unsigned)(min(lane, total - 1 - b0 * kKB) * 4), ring_lds + (unsigned)(((b / kWaves) & 3) * 2 * kKB * 4));
+    if (lane < kKB)
+      load_to_lds_dword(list + b0 * kKB, (unsigned)(min(lane, total - 1 - b0 * kKB) * 4), ring_lds + (unsigned)(((b / kWaves) & 3) * kKB * 4));
   };
-  auto issue_rows = [&](int b, const char* cached, const char* fresh, const unsigned (&src)[IPB], unsigned lds) {
+  auto issue_rows = [&](int i0, int di, int b, const char* cached, const char* fresh, const auto& src, unsigned lds) {
+    constexpr int P = sizeof(src) / sizeof(src[0]);
     const int j0 = b * kKB;
-    const int* x = ring + ((b / kWaves) & 3) * 2 * kKB + lane / CPR;
+    const int* x = xring + ((b / kWaves) & 3) * kKB + lane / CPR;
     if (j0 + kKB <= seam || j0 >= seam) {
       const char* base = j0 >= seam ? fresh : cached;
 #pragma unroll
-      for (int i = 0; i < IPB; ++i) load_to_lds(base, (unsigned)x[i * RPI] * (unsigned)(D * 2) + (src[i] & (D * 2 - 1)), lds + (unsigned)(i * 1024));
+      for (int i = 0; i < IPB; ++i)
+        if (di == 1 || i % di == i0)
+          load_to_lds(base, (unsigned)x[i * RPI] * (unsigned)(D * 2) + (src[i % P] & (D * 2 - 1)), lds + (unsigned)(i * 1024));
     } else {
 #pragma unroll
       for (int i = 0; i < IPB; ++i) {
+        if (di != 1 && i % di != i0) continue;
         const int j = x[i * RPI];
-        load_to_lds((j < d.len_in ? cached : fresh) + (int64_t)j * (D * 2) + (src[i] & (D * 2 - 1)), lds + (unsigned)(i * 1024));
+        load_to_lds((j < d.len_in ? cached : fresh) + (int64_t)j * (D * 2) + (src[i % P] & (D * 2 - 1)), lds + (unsigned)(i * 1024));
       }
     }
   };
-  auto issue_k = [&](int b, bool first = false) {
-    if constexpr (GATHER) {
-      issue_x(b + 2 * kWaves);
-      issue_rows(b, kc, kn, k_src, k_lds);
-    } else {
-      issue(std::true_type{}, first, b, k_cache, k_new, k_src, k_lds);
-    }
+  auto issue_k = [&](int b, unsigned lds, bool first = false, int i0 = 0, int di = 1) {
+    if constexpr (GATHER) issue_rows(i0, di, b, kc, kn, k_src, lds);
+    else issue(std::true_type{}, first, i0, di, b, k_cache, k_new, k_src, lds);
   };
-  auto issue_v = [&](int b, bool first = false) {
-    if constexpr (GATHER) issue_rows(b, vc, vn, v_src, v_lds);
-    else issue(std::false_type{}, first, b, v_cache, v_new, v_src, v_lds);
+  auto issue_v = [&](int b, unsigned lds, bool first = false, int i0 = 0, int di = 1) {
+    if constexpr (GATHER) issue_rows(i0, di, b, vc, vn, v_src, lds);
+    else issue(std::false_type{}, first, i0, di, b, v_cache, v_new, v_src, lds);
   };
 
-  if (w < n_blocks) {
+  // The queries travel through LDS as well, row col of tile qt in the K layout: one row a lane, straight from memory into the
+  // operand registers of every wave, they take the memory pipeline at a quarter of its rate.
+  {
+    const char* const qbase = reinterpret_cast<const char*>(q + (new_row0 + q0) * D);
+    const int last = min(QROWS, N_k - q0) - 1;
+#pragma unroll
+    for (int i = 0; i < QROWS / RPI; ++i)
+      if (i % kWaves == w) {
+        const int r = i * RPI + lane / CPR;
+        load_to_lds(qbase, (unsigned)(min(r, last) * D + (((lane % CPR) ^ swz_k<D>(r)) & (CPR - 1)) * 8) * 2u, lds_addr_of(q_sh) + (unsigned)(i * 1024));
+      }
+  }
+
+  // The first scales' units have one block: all waves copy and score it, and each forms a share of the head-dim.
+  const bool lone = n_blocks == 1;
+  if (lone) {
+    if constexpr (GATHER) {
+      if (lane < kKB) load_to_lds_dword(list, (unsigned)(min(lane, total - 1) * 4), ring_lds);
+      dma_wait_but<0>();
+    }
+    issue_k(0, lds_of(0, 0), true, w, kWaves);
+    issue_v(0, lds_of(0, 1), true, w, kWaves);
+  } else if (w < n_blocks) {
     if constexpr (GATHER) {
       issue_x(w);
       issue_x(w + kWaves);
       dma_wait_but<0>();
     }
-    issue_k(w, true);
-    issue_v(w, true);
+    if constexpr (GATHER) issue_x(w + 2 * kWaves);
+    issue_k(w, lds_of(w, 0), true);
+    issue_v(w, lds_of(w, 1), true);
   }
 
   // Cache update of this tile's rows: loaded behind the first K and V blocks, stored when the loop is done (stored at
   // once they would put a memory round trip in front of everything else: one 256^2 image 99.6 against 96.5 us).
   constexpr int LPR = D / 8;                               // 16-byte pieces per row
-  constexpr int APP = (kQTile * LPR + 64 * kWaves - 1) / (64 * kWaves);   // pieces per thread
+  constexpr int APP = (QROWS * LPR + 64 * kWaves - 1) / (64 * kWaves);   // pieces per thread
   uintx4 app_k[APP], app_v[APP];
-  const int n_app = fuse ? min(kQTile, N_k - q0) * LPR : 0;
+  const int n_app = fuse ? min(QROWS, N_k - q0) * LPR : 0;
   if (!GATHER && fuse) {
 #pragma unroll
     for (int i = 0; i < APP; ++i) {
@@ -209,118 +261,119 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     }
   }
 
-  // Q fragments (B operand): query col, head-dim slice [16kk + 8 half, +8)
-  bf16x8 qf[KK];
-  {
-    const __bf16* qrow = q + (new_row0 + min(q0 + col, N_k - 1)) * D;
+  floatx4 o[MT][NQ];       // O^T: head-dim 16 mt + 4 g + r, query 16 qt + col
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + 16 * kk + 8 * half);
-    // consumed here so that the compiler's wait for them sits before the loop,
-    // whose vector-memory waits are all placed by hand
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) asm volatile("" ::"v"(qf[kk]));
+    for (int qt = 0; qt < NQ; ++qt) o[mt][qt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  floatx4 ls[NQ];          // row sums of P: all four rows hold the same
+  float mc[NQ];            // probabilities are 2^(c2 s - mc); finite from the start, so that keys whose score is -inf get 0
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) {
+    ls[qt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    mc[qt] = -FLT_MAX;
   }
-  dma_wait_but<0>();   // first K and V blocks (and everything above) have landed
-
-  floatx16 o[MB];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[mb][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
   const float c2 = scale * kLog2eF;
+  bf16x8 ones;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.0f;
 
-  // V^T operand reads: row 4 half + e (+16 sg, +8), head-dim 32mb + 16(g&1) + 4qd
-  const int g = lane >> 4, e = (lane >> 2) & 3, qd = lane & 3;
-  int v_off[MB];
+  int k_off[KC];   // K operand: row 16 kt + col, chunk 4 c + g
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-    v_off[mb] = (4 * half + e) * D + (((4 * mb + 2 * (g & 1) + (qd >> 1)) ^ swz_v<D>(e)) & (CPR - 1)) * 8 + 4 * (qd & 1);
-  int k_off[KK];   // K operand reads: row col, chunk 2kk + half
+  for (int c = 0; c < KC; ++c) k_off[c] = col * D + (((4 * c + g) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
+  const int e = col >> 2, qd = col & 3;
+  int v_off[MT];   // V^T operand: rows 4 g + e and 16 + 4 g + e, head-dim 16 mt + 4 qd
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) k_off[kk] = col * D + (((2 * kk + half) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
-  const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
+  for (int mt = 0; mt < MT; ++mt)
+    v_off[mt] = (4 * g + e) * D + (((2 * mt + (qd >> 1)) ^ swz_v16<D>(4 * g + e)) & (CPR - 1)) * 8 + 4 * (qd & 1);
 
-  // Vector-memory traffic of a wave inside the loop, all hand-issued copies, in
-  // order: ... K(b), V(b) | K(next) after the score MFMAs of b, V(next) after the
-  // PV MFMAs of b.  Copies complete in order, so "all but the newest IPB
-  // instructions" is K(b) at the top of an iteration and V(b) before its PV.
-  const __bf16* Kt = &Vs[w][0][0];
-  const __bf16* Vt = &Vs[w][1][0];
-  for (int b = w; b < n_blocks; b += kWaves) {
-    const bool more = b + kWaves < n_blocks;
-    dma_wait_but<IPB>();                 // K(b) has landed (V(b) may still be in flight)
-    // S^T of block b: per lane one query column and 16 key rows
-    floatx16 sc;
+  // The queries and the first K block have landed; what was issued behind them, the first V block and the rows to append, may still be
+  // on its way.  A wave that has issued fewer copies (a ragged block, a share of the only block, none) waits for all of them.
+  if (lone || (w + 1) * kKB > total) dma_wait_but<0>();
+  else if (!GATHER && fuse) dma_wait_but<IPB + 2 * APP>();
+  else dma_wait_but<IPB>();
+  __syncthreads();     // ... of every wave
+  // Q fragments (B operand of S^T = K Q^T): query 16 qt + col, head-dim slice [32 c + 8 g, +8)
+  bf16x8 qf[NQ][KC];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+  for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kt[k_off[kk]]);
-      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], sc, 0, 0, 0);
-    }
-    // the MFMAs above have consumed every K read, so the slot may be refilled;
-    // nothing below moves above this point
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-    if (more) issue_k(b + kWaves);
+    for (int c = 0; c < KC; ++c) qf[qt][c] = *reinterpret_cast<const bf16x8*>(&q_sh[16 * qt * D + k_off[c]]);
+
+  // Scores of a block: sc[kt][qt], keys 16 kt + 4 g + r, query 16 qt + col.
+  auto scores = [&](const __bf16* Kt, floatx4 (&sc)[2][NQ]) {
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) sc[kt][qt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kt[16 * kt * D + k_off[c]]);
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt) sc[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[qt][c], sc[kt][qt], 0, 0, 0);
+      }
+  };
+  auto mask = [&](floatx4 (&sc)[2][NQ], int b) {   // keys past the end
     if ((b + 1) * kKB > total) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (b * kKB + 8 * (r >> 2) + 4 * half + (r & 3) >= total) sc[r] = -INFINITY;
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (b * kKB + 16 * kt + 4 * g + r >= total) {
+#pragma unroll
+            for (int qt = 0; qt < NQ; ++qt) sc[kt][qt][r] = -INFINITY;
+          }
     }
-    float mx = sc[0];
+  };
+  // Probabilities of a block in the order of the B operand of the PV product: element j of lane group g is key 4 g + j (j < 4) or
+  // 16 + 4 g + j - 4, and the V^T operand is read in the same order.
+  auto probs = [&](const floatx4 (&sc)[2][NQ], bf16x8 (&pf)[NQ]) {
 #pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
-    mx = pair_max(mx);                       // finite: the block holds a valid key
-    const float m_new = fmaxf(m_run, mx);
-    if (__any(m_new != m_run)) {
-      const float a = __builtin_amdgcn_exp2f((m_run - m_new) * c2);   // first block: exp2(-inf) = 0
-      l_run *= a;
-      if (b != w) {   // nothing has been added up in front of the first block
+    for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+      for (int j = 0; j < 8; ++j) pf[qt][j] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sc[j >> 2][qt][j & 3], c2, -mc[qt]));
+  };
+  // The reference follows the scores; what has been summed against the old one is brought to the new one.
+  auto follow = [&](const floatx4 (&sc)[2][NQ], bool nothing_yet) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) o[mb][r] *= a;
-      }
-      m_run = m_new;
-    }
-    const float mc = m_run * c2;
-    bf16x8 pf[2];
+    for (int qt = 0; qt < NQ; ++qt) {
+      float mx = sc[0][qt][0];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) pf[r >> 3][r & 7] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sc[r], c2, -mc));
-    // the row sum is taken over the rounded probabilities, the numbers the PV product uses
-    float psum = 0.f;
+      for (int j = 1; j < 8; ++j) mx = fmaxf(mx, sc[j >> 2][qt][j & 3]);
+      const float m_new = fmaxf(mc[qt], fmaf(quad_max(mx), c2, kHeadroom));
+      if (!nothing_yet) {
+        const float a = __builtin_amdgcn_exp2f(mc[qt] - m_new);
 #pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const bf16x2 pr = {pf[r >> 3][r & 7], pf[r >> 3][(r & 7) + 1]};
-      psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, psum, false);
-    }
-    l_run += psum;
-    if (more) dma_wait_but<IPB + XI>();  // V(b) has landed (K(next) and list entries may still be in flight)
-    else dma_wait_but<0>();
+        for (int r = 0; r < 4; ++r) {
+          ls[qt][r] *= a;
 #pragma unroll
-    for (int sg = 0; sg < 2; ++sg) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const __bf16* vp = &Vt[16 * sg * D + v_off[mb]];
-        const bf16x4 v0 = lds_read_tr(vp);
-        const bf16x4 v1 = lds_read_tr(vp + 8 * D);
-        bf16x8 vf;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          vf[i] = v0[i];
-          vf[4 + i] = v1[i];
+          for (int mt = 0; mt < MT; ++mt) o[mt][qt][r] *= a;
         }
-        o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sg], o[mb], 0, 0, 0);
       }
+      mc[qt] = m_new;
     }
-    // every V read has been consumed by an MFMA above: the slot may be refilled
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-    if (more) issue_v(b + kWaves);
-  }
-  dma_wait_but<0>();   // nothing is outstanding when the slots are reused below
+  };
+  auto too_large = [&](const bf16x8 (&pf)[NQ]) -> bool {
+    unsigned x = 0;
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      const uintx4 a = __builtin_bit_cast(uintx4, pf[qt]);
+      x |= a[0] | a[1] | a[2] | a[3];
+    }
+    return x & 0x40004000u;
+  };
+  auto pv = [&](const __bf16* Vt, const bf16x8 (&pf)[NQ], int mt) {
+    const bf16x4 v0 = lds_read_tr(&Vt[v_off[mt]]), v1 = lds_read_tr(&Vt[16 * D + v_off[mt]]);
+    const bf16x8 vf = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) o[mt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qt], o[mt][qt], 0, 0, 0);
+  };
+  auto row_sums = [&](const bf16x8 (&pf)[NQ]) {   // over the rounded probabilities, the numbers the PV product uses
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) ls[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qt], ls[qt], 0, 0, 0);
+  };
   auto append = [&] {
     if (!GATHER && fuse) {
       uintx4* kd = reinterpret_cast<uintx4*>(k_app) + (d.in_off + d.len_in + q0) * LPR;
@@ -336,121 +389,170 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
       if (pos_app != nullptr && tid < n_app / LPR) pos_app[d.in_off + d.len_in + q0 + tid] = pos_new + q0 + tid;
     }
   };
-  const int qi = q0 + col;
-  __bf16* orow = out + (new_row0 + min(qi, N_k - 1)) * D;
+  auto store = [&](int mt, int qt, const floatx4& x, float inv) {
+    const int qi = q0 + 16 * qt + col;
+    const bf16x4 pk = {(__bf16)(x[0] * inv), (__bf16)(x[1] * inv), (__bf16)(x[2] * inv), (__bf16)(x[3] * inv)};
+    if (qi < N_k) *reinterpret_cast<bf16x4*>(out + (new_row0 + qi) * D + 16 * mt + 4 * g) = pk;
+  };
 
-  // A unit of one block (the first scales): wave 0 holds the whole result.
-  if (n_blocks == 1) {
-    if (w == 0) {
-      const float inv = 1.f / pair_sum(l_run);
+  if (lone) {
+    floatx4 sc[2][NQ];
+    bf16x8 pf[NQ];
+    scores(&ring[0][0][0], sc);
+    mask(sc, 0);
+    follow(sc, true);
+    probs(sc, pf);
+    row_sums(pf);
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+    for (int mt = 0; mt < MT; ++mt)
+      if (mt % kWaves == w) {
+        pv(&ring[0][1][0], pf, mt);
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          bf16x4 pk;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) pk[i] = (__bf16)(o[mb][4 * r4 + i] * inv);
-          if (qi < N_k) *reinterpret_cast<bf16x4*>(orow + 32 * mb + 8 * r4 + 4 * half) = pk;
-        }
-    }
+        for (int qt = 0; qt < NQ; ++qt) store(mt, qt, o[mt][qt], 1.f / ls[qt][0]);
+      }
     append();
     return;
   }
+
+  // Vector-memory traffic of a wave inside the loop, all hand-issued copies, in
+  // order: ... K(b), V(b) | K(next) after the score MFMAs of b, V(next) after the
+  // PV MFMAs of b.  Copies complete in order, so "all but the newest IPB
+  // instructions" is K(b) at the top of an iteration and V(b) before its PV.
+  for (int b = w; b < n_blocks; b += kWaves) {
+    const bool more = b + kWaves < n_blocks;
+    dma_wait_but<IPB>();                 // K(b) has landed (V(b) may still be in flight)
+    floatx4 sc[2][NQ];
+    scores(&ring[w][0][0], sc);
+    // the MFMAs above have consumed every K read, so the slot may be refilled;
+    // nothing below moves above this point
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    if (more) {
+      if constexpr (GATHER) issue_x(b + 3 * kWaves);
+      issue_k(b + kWaves, lds_of(w, 0));
+    }
+    mask(sc, b);
+    bf16x8 pf[NQ];
+    if (b == w) {
+      follow(sc, true);
+      probs(sc, pf);
+    } else {
+      probs(sc, pf);
+      if (__any(too_large(pf))) {
+        follow(sc, false);
+        probs(sc, pf);
+      }
+    }
+    if (more) dma_wait_but<IPB + XI>();  // V(b) has landed (K(next) and list entries may still be in flight)
+    else dma_wait_but<0>();
+    row_sums(pf);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) pv(&ring[w][1][0], pf, mt);
+    // every V read has been consumed by an MFMA above: the slot may be refilled
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    if (more) issue_v(b + kWaves, lds_of(w, 1));
+  }
+  dma_wait_but<0>();   // nothing is outstanding when the slots are reused below
   append();
 
   // ---- merge the partial results ----
-  // This wave's copies have all landed and its LDS reads are done: its two slots
-  // become its O^T partial, four registers of a lane together, lanes contiguous (b128 accesses, a quarter of the
-  // instructions of a register at a time).
-  l_run = pair_sum(l_run);
-  float4* mine = reinterpret_cast<float4*>(&Vs[w][0][0]) + lane;
+  // This wave's copies have all landed and its LDS reads are done: its pair of slots becomes its O^T partial, four registers of a
+  // lane together, lanes contiguous (b128 accesses, a quarter of the instructions of a register at a time).
+  constexpr int kPart = 2 * BLK * 2 / 16;   // float4 per wave
+  static_assert(NQ * MT * 64 <= kPart && kWaves % NQ == 0, "partial results fit the slots");
+  float4* mine = reinterpret_cast<float4*>(&ring[w][0][0]) + lane;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4)
-      mine[(mb * 4 + r4) * 64] = make_float4(o[mb][4 * r4], o[mb][4 * r4 + 1], o[mb][4 * r4 + 2], o[mb][4 * r4 + 3]);
-  if (half == 0) {
-    m_sh[w][col] = m_run;
-    l_sh[w][col] = l_run;
+    for (int qt = 0; qt < NQ; ++qt) mine[(mt * NQ + qt) * 64] = make_float4(o[mt][qt][0], o[mt][qt][1], o[mt][qt][2], o[mt][qt][3]);
+  if (g == 0) {
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      m_sh[w][16 * qt + col] = mc[qt];
+      l_sh[w][16 * qt + col] = ls[qt][0];
+    }
   }
   __syncthreads();
-  // wave w finishes registers [w CH, (w+1) CH) of the 16 MB per lane; register
-  // 16 mb + r of lane (col, half) is head-dim 32mb + 8(r/4) + 4 half + r%4 of query col
-  constexpr int CH = 16 * MB / kWaves;
-  static_assert(CH % 4 == 0, "whole groups of four registers");
-  const float4* const part = reinterpret_cast<const float4*>(&Vs[0][0][0]) + w * (CH / 4) * 64 + lane;
-  constexpr int kPart = 2 * BLK * 2 / 16;   // float4 per partial result
-  float M = -INFINITY;
+  // wave w finishes query tile w % NQ, head-dim tiles w / NQ, w / NQ + kWaves / NQ, ...
+  const int qt = w % NQ;
+  float M = -FLT_MAX;
 #pragma unroll
-  for (int x = 0; x < kWaves; ++x) M = fmaxf(M, m_sh[x][col]);   // finite: wave 0 saw block 0
+  for (int x = 0; x < kWaves; ++x) M = fmaxf(M, m_sh[x][16 * qt + col]);
   float f[kWaves], L = 0.f;
 #pragma unroll
   for (int x = 0; x < kWaves; ++x) {
-    f[x] = __builtin_amdgcn_exp2f((m_sh[x][col] - M) * c2);       // a wave without blocks: exp2(-inf) = 0
-    L = fmaf(f[x], l_sh[x][col], L);
-  }
-  float4 acc[CH / 4];
-#pragma unroll
-  for (int i4 = 0; i4 < CH / 4; ++i4) {
-    acc[i4] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int x = 0; x < kWaves; ++x) {
-      const float4 p = part[x * kPart + i4 * 64];
-      acc[i4].x = fmaf(f[x], p.x, acc[i4].x);
-      acc[i4].y = fmaf(f[x], p.y, acc[i4].y);
-      acc[i4].z = fmaf(f[x], p.z, acc[i4].z);
-      acc[i4].w = fmaf(f[x], p.w, acc[i4].w);
-    }
+    f[x] = __builtin_amdgcn_exp2f(m_sh[x][16 * qt + col] - M);   // a wave without blocks has summed nothing
+    L = fmaf(f[x], l_sh[x][16 * qt + col], L);
   }
   const float inv = 1.f / L;
+  const float4* const part = reinterpret_cast<const float4*>(&ring[0][0][0]) + lane;
 #pragma unroll
-  for (int i4 = 0; i4 < CH / 4; ++i4) {
-    const int reg0 = w * CH + 4 * i4;
-    const bf16x4 pk = {(__bf16)(acc[i4].x * inv), (__bf16)(acc[i4].y * inv), (__bf16)(acc[i4].z * inv), (__bf16)(acc[i4].w * inv)};
-    const int mb = reg0 >> 4, r4 = (reg0 & 15) >> 2;
-    if (qi < N_k) *reinterpret_cast<bf16x4*>(orow + 32 * mb + 8 * r4 + 4 * half) = pk;
+  for (int m = 0; m < MT; m += kWaves / NQ) {
+    const int mt = m + w / NQ;
+    if (mt >= MT) break;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < kWaves; ++x) {
+      const float4 p = part[x * kPart + (mt * NQ + qt) * 64];
+      acc[0] = fmaf(f[x], p.x, acc[0]);
+      acc[1] = fmaf(f[x], p.y, acc[1]);
+      acc[2] = fmaf(f[x], p.z, acc[2]);
+      acc[3] = fmaf(f[x], p.w, acc[3]);
+    }
+    store(mt, qt, acc, inv);
   }
 }
 
 }  // namespace
 
-int attn_split_q_tile_rows() { return kQTile; }
+int attn_split_q_tile_rows() { return kItemRows; }
 
-#define HACK_SPLIT(D_, G_, ...)                                                                                  \
-  do {                                                                                                           \
-    if (eight) hipLaunchKernelGGL((attn_split<D_, G_, 8>), dim3(n), dim3(512), 0, s, descs, items, __VA_ARGS__); \
-    else hipLaunchKernelGGL((attn_split<D_, G_, 4>), dim3(n), dim3(256), 0, s, descs, items, __VA_ARGS__);       \
-  } while (0)
+// Which launches take 16 queries a work-group.  A launch of few work-groups is a chain of latencies over a few blocks: half of the queries
+// halve a wave's matrix and vector work, the partial results and the merge, and twice as many work-groups share it out; where compute units
+// have more than one of them to do anyway, they copy K and V twice as often.  Measured, us a launch, 32 / 16 queries, work items of 32: head_dim
+// 128, four waves, keys: 32 items of 21 3.4 / 3.1, 64 of 121 5.1 / 4.5, 128 of 300 7.0 / 6.0, 192 of 400 and 200 8.1 / 8.1, 6.1 / 5.9; 224 of 521 9.1 / 9.3,
+// 416 of 921 14.2 / 21.7; 64, four waves: 120 of 155 4.7 / 4.1, 256 of 400 6.3 / 5.8, 300 of 300 and 600 6.0 / 5.7, 7.8 / 7.9, 360 of 271 6.2 / 5.9; 448 of 450
+// 7.4 / 8.5.  Eight waves (longer caches), head_dim 128: 64 of 1500 11.2 / 9.9, 96 of 1500 11.5 / 10.9, but a step that compresses to as many 30.5 / 32.0
+// (the work-groups that move its rows find no room); 64: 128 of 1500 8.6 / 7.1, 160 8.5 / 10.3.
+static bool sixteen_queries(int head_dim, bool eight, int n_items) {
+  if (eight) return n_items <= (head_dim == 64 ? 128 : 64);
+  return n_items <= (head_dim == 64 ? 384 : 192);
+}
+
+template <int D, bool GATHER, typename... Args>
+static void launch_split(hipStream_t s, bool eight, int n_items, int n_moves, Args... args) {
+  const bool half = n_items % 8 == 0 && sixteen_queries(D, eight, n_items);   // items come dealt to eight XCDs
+  const dim3 grid((half ? 2 * n_items : n_items) + n_moves), block(eight ? 512 : 256);
+  if (half && eight) hipLaunchKernelGGL((attn_split<D, GATHER, 1, 8>), grid, block, 0, s, args...);
+  else if (half) hipLaunchKernelGGL((attn_split<D, GATHER, 1, 4>), grid, block, 0, s, args...);
+  else if (eight) hipLaunchKernelGGL((attn_split<D, GATHER, 2, 8>), grid, block, 0, s, args...);
+  else hipLaunchKernelGGL((attn_split<D, GATHER, 2, 4>), grid, block, 0, s, args...);
+}
 
 void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
                        void* k_app, void* v_app, int32_t* pos_app, int pos_new, bool append, bool eight, int N_k, float scale,
                        void* out) {
-  const int n = n_items;
-  if (n <= 0) return;
+  if (n_items <= 0) return;
   typedef __bf16 T;
-  if (head_dim == 64)
-    HACK_SPLIT(64, false, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
-               pos_app, pos_new, append ? 1 : 0, N_k, scale, (T*)out, GatherArgs{});
-  else
-    HACK_SPLIT(128, false, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app,
-               pos_app, pos_new, append ? 1 : 0, N_k, scale, (T*)out, GatherArgs{});
+#define HACK_ARGS s, eight, n_items, 0, descs, items, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, \
+                  (T*)v_app, pos_app, pos_new, append ? 1 : 0, N_k, scale, (T*)out, GatherArgs{}
+  if (head_dim == 64) launch_split<64, false>(HACK_ARGS);
+  else launch_split<128, false>(HACK_ARGS);
+#undef HACK_ARGS
 }
 
 void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                               const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
                               float scale, void* out) {
-  const int n = n_items + g.n_moves;
-  if (n <= 0) return;
+  if (n_items + g.n_moves <= 0) return;
   typedef __bf16 T;
-  const bool eight = g.eight;
-  if (head_dim == 64)
-    HACK_SPLIT(64, true, (const T*)q, (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k,
-               scale, (T*)out, g);
-  else
-    HACK_SPLIT(128, true, (const T*)q, (const T*)k_cache, (const T*)v_cache, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, N_k,
-               scale, (T*)out, g);
+#define HACK_ARGS s, g.eight, n_items, g.n_moves, descs, items, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)nullptr, (const T*)nullptr, \
+                  (T*)nullptr, (T*)nullptr, (int32_t*)nullptr, 0, 0, N_k, scale, (T*)out, g
+  if (head_dim == 64) launch_split<64, true>(HACK_ARGS);
+  else launch_split<128, true>(HACK_ARGS);
+#undef HACK_ARGS
 }
-#undef HACK_SPLIT
 
 }  // namespace hack

@@ -570,6 +570,58 @@ def test_key_split_attention_block_and_wave_edges(d, H, Nk, lens):
     hk.close()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("U,Nk,lens", [
+    (7, 15, [1, 32, 64, 33, 128, 129, 300]), (5, 16, [32, 31, 96, 160, 17]), (5, 17, [32, 1, 128, 255, 64]), (5, 31, [32, 63, 65, 127, 256]),
+    (3, 48, [32, 700, 1]), (9, 33, [700] * 8 + [32]),
+    (192, 17, [32, 200, 3]), (193, 17, [32, 129, 64]),      # 192 and 200 work items (dealt to eight XCDs): the lines between 16 and 32 queries,
+    (384, 16, [32, 45, 97]), (385, 16, [32, 128, 20]),      # 384 and 392,
+    (64, 32, [641, 32, 900]), (65, 20, [641, 32, 64]),      # 64 and 72 and
+    (128, 31, [641, 32, 64]), (129, 32, [641, 5, 256]),     # 128 and 136 with eight waves
+])
+def test_key_split_attention_with_16_and_32_queries_a_work_group(d, U, Nk, lens):
+    """Single blocks (exactly full ones among them), rows of queries on either side of 16 and 32, and work items on both sides of the lines at
+    which a work-group takes half of one: attention, a step that appends (its last Nk rows are new) and one that compresses give the same bits,
+    within the rounding of the probabilities and the output to bf16."""
+    u = _u()
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(U + Nk)
+    lens = np.resize(np.asarray(lens, np.int32), U)
+    scale = float(np.float32(d ** -0.5))
+    hk = u.make_hack(heads=U, head_dim=d, dtype="bf16", max_units=U, max_cache_len=int(lens.max()) + Nk, max_queries=max(Nk, int(lens.max())), attention="split")
+    q, kn, vn = (torch.randn((1, U, Nk, d), generator=gen, device=u.DEV).bfloat16() for _ in range(3))
+
+    def check(out, cache, what):
+        off, ln = cache.view()
+        for x in list(range(min(U, 12))) + [U - 1]:
+            k, v = (t[off[x]:off[x] + ln[x]].double() for t in (cache.k, cache.v))
+            p = torch.softmax(scale * (q[0, x].double() @ k.T.contiguous()), -1)
+            # every probability, their sum and the output carry 2^-9 each; float32 scores and sums are far below
+            bound = 3 * 2.0 ** -9 * (p @ v.abs()) * 1.02 + 1e-4
+            assert bool(((out[0, x].double() - p @ v).abs() <= bound).all()), (what, x, int(ln[x]))
+
+    types, never = np.zeros(U, np.uint8), np.full(U, 10**6, np.int32)
+    # rows in front of the steps: one step for all units, compressed to their lengths
+    first = max(int(lens.max()), 2)
+    k0, v0 = (torch.randn((1, U, first, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    mc = hk.managed_cache(np.maximum(np.maximum(lens, 2) + Nk, first))
+    hk.step(mc, k0, k0, v0, types, np.where(lens < first, lens, 10**6).astype(np.int32), 5, scale, torch.empty_like(k0))
+    assert list(mc.view()[1]) == list(lens)
+    out, want = torch.full_like(q, 7.0), torch.full_like(q, 7.0)
+    hk.attn(q, mc.as_cache(), scale, out)
+    torch.cuda.synchronize()
+    check(out, mc, "attention")
+    for what, budget in (("compressing", np.maximum(lens, 2)), ("appending", never)):
+        hk.step(mc, q, kn, vn, types, budget, 5, scale, out)
+        hk.attn(q, mc.as_cache(), scale, want)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), what
+        check(out, mc, what)
+    hk.check()
+    mc.close()
+    hk.close()
+
+
 # the forms of the 128-query kernel (halves: head_dim 128)
 TILE_FORMS = [(d, n, f) for d, n in ((64, 130), (128, 33), (128, 257)) for f in ("tile128", "stream", "halves") if d == 128 or f != "halves"]
 
