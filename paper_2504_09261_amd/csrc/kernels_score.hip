@@ -457,6 +457,35 @@ __device__ __forceinline__ double take_rows(const char* buf, int lane) {
   }
   return s + dpp_mov_f64<0xB1>(s);
 }
+// The observation rows of a unit on their way into LDS, in the layout of a tile of keys, shared out over the waves of a work-group.  Rows past
+// n_obs repeat the first one; they get weight zero.  (Read straight from memory into the operand registers of every wave, 32 rows x
+// 32 bytes an instruction, they kept the memory pipeline of a compute unit busy for 2000 cycles a work-group, against some 60 this way, and
+// a row number loaded behind the first tile's copies was waited for with them.  Kernel trace, us a launch: 32 units of 2500 / 4000 / 6000 / 8000 keys, D = 128
+// 11.0 / 16.0 / 19.8 / 20.6 -> 10.3 / 15.3 / 18.6 / 19.8; 480 units of 358 keys and 480 of 562, D = 64 18.6 + 38.5 -> 16.8 + 36.0.)
+template <int D, int WAVES>
+struct ObsRows {
+  static constexpr int CPR = D / 8, RPI = 64 / CPR, COPIES = 32 / RPI, PER = (COPIES + WAVES - 1) / WAVES;
+  int row[PER];
+  // in front of every hand-issued copy: the compiler's wait for these loads counts none of them
+  __device__ __forceinline__ void load(const int32_t* __restrict__ q_rows, int n_obs, int w, int lane) {
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int r = (w + p * WAVES) * RPI + lane / CPR;
+      row[p] = q_rows[r < n_obs ? r : 0];
+    }
+#pragma unroll
+    for (int p = 0; p < PER; ++p) asm volatile("" ::"v"(row[p]));
+  }
+  __device__ __forceinline__ void issue(const __bf16* q_unit, unsigned lds, int w, int lane) const {
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int i = w + p * WAVES, r = i * RPI + lane / CPR;
+      if (COPIES % WAVES == 0 || i < COPIES)
+        load_to_lds(q_unit + (int64_t)row[p] * D + (((lane % CPR) ^ swz_k<D>(r)) & (CPR - 1)) * 8, lds + (unsigned)(i * 1024));
+    }
+  }
+};
+
 // One launch, K read once.  Every wave
 //   A. forms the logits t_ij (log2 units) of its item, 32 observation rows x up
 //      to 32 TILES keys, and parks them in registers as fixed point;
@@ -523,6 +552,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int item = blockIdx.x * 4 + w;  // the host pads every unit to whole work-groups
   const ScoreItem it = items[item];
+  ObsRows<D, 4> obs;
+  obs.load(q_rows, n_obs, w, lane);
   const int T_in = it.t_in;
   constexpr int kItemTiles = TILES;
   const int key0 = it.chunk * (32 * TILES);
@@ -568,33 +599,28 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
       }
     }
   };
+  // Q~ goes into the second buffer of wave 0, which no tile uses before every wave has read it.
+  const __bf16* const q_lds = &tiles[0][1][0];
+  obs.issue(q + (int64_t)it.unit * N_k * D, lds_addr_of(q_lds), w, lane);
   if (n_tiles > 0) issue(0);
 
-  // Q~ fragments (rows beyond n_obs are zero and get zero weight below).
-  bf16x8 qf[KK];
-  {
-    const bool qv = col < n_obs;
-    const __bf16* qrow = q + ((int64_t)it.unit * N_k + (qv ? q_rows[col] : 0)) * D;
+  int k_off[KK];   // operand reads: row col, chunk 2 kk + half
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      bf16x8 z = {0};
-      qf[kk] = qv ? *reinterpret_cast<const bf16x8*>(qrow + 16 * kk + 8 * half) : z;
-    }
-  }
+  for (int kk = 0; kk < KK; ++kk) k_off[kk] = col * D + (((2 * kk + half) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
   const double c2 = (double)scale * kLog2e * kFixOne;  // logits in log2 units, fixed point: t * 2^22 = dot * c2
-  // everything the compiler loaded itself must have landed before the tiles are
-  // consumed, so that no compiler-placed vmcnt wait also drains the tile copies
+  // Q~ has landed, the first tile may still be on its way
+  if (n_tiles > 0) dma_wait_but<IPT>();
+  else dma_wait_but<0>();
+  __syncthreads();
+  bf16x8 qf[KK];
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) asm volatile("" ::"v"(qf[kk]));
+  for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(&q_lds[k_off[kk]]);
+  __syncthreads();   // (a wave's row sums need both of its buffers at head_dim 64, whatever TILES is)
   if (MODE == kScoreFused && __builtin_amdgcn_readfirstlane(aborted) != 0) {
     // an earlier launch gave up: its sums may still sit in the slots, so nothing here may be trusted
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the first tile's copy must not outlive the wave
     return;
   }
-
-  int k_off[KK];
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) k_off[kk] = col * D + (((2 * kk + half) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
 
   // ---- A: logits of the item's tiles ---------------------------------------
   // Between A and C a logit waits in registers either as its fixed-point value (one register; 2^t is
@@ -864,10 +890,13 @@ __global__ __launch_bounds__(64 * NW) void score_select(
   __shared__ double red[NW][kMaxObs], inv_s[NW][kMaxObs];
   __shared__ uint32_t keys[64 * NW];
   __shared__ Shared sh;
+  __shared__ __attribute__((aligned(1024))) __bf16 q_lds[TILE];
 
   const UnitDesc d = descs[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  ObsRows<D, NW> obs;
+  obs.load(q_rows, n_obs, w, lane);
   const int col = lane & 31, half = lane >> 5;
   const int T_in = d.len_in + d.n_new;
   const int n_tiles = w * 32 >= T_in ? 0 : TILES == 1 || (w + NW) * 32 >= T_in ? 1 : 2;   // of this wave
@@ -898,26 +927,24 @@ __global__ __launch_bounds__(64 * NW) void score_select(
       }
     }
   };
+  obs.issue(q + (int64_t)d.unit * N_k * D, lds_addr_of(q_lds), w, lane);
   if (n_tiles > 0) issue(0);
-  if (TILES > 1 && kBufs > 1 && n_tiles > 1) issue(1);
+  constexpr bool kBoth = TILES > 1 && kBufs > 1;   // both tiles of a wave are copied at once
+  if (kBoth && n_tiles > 1) issue(1);
 
-  bf16x8 qf[KK];
-  {
-    const bool qv = col < n_obs;
-    const __bf16* qrow = q + ((int64_t)d.unit * N_k + (qv ? q_rows[col] : 0)) * D;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      bf16x8 z = {0};
-      qf[kk] = qv ? *reinterpret_cast<const bf16x8*>(qrow + 16 * kk + 8 * half) : z;
-    }
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) asm volatile("" ::"v"(qf[kk]));
-  }
   const double c2 = (double)scale * kLog2e * kFixOne;
   const double dot_safe = (double)(kFixLimit - 1) / c2;
   int k_off[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) k_off[kk] = col * D + (((2 * kk + half) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
+  // Q~ has landed, the tiles may still be on their way
+  if (kBoth && n_tiles > 1) dma_wait_but<2 * IPT>();
+  else if (n_tiles > 0) dma_wait_but<IPT>();
+  else dma_wait_but<0>();
+  __syncthreads();
+  bf16x8 qf[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(&q_lds[k_off[kk]]);
 
   // ---- logits (see score_fused) ----
   double pq[TILES][16];
