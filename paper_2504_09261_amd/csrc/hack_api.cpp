@@ -84,7 +84,7 @@ struct hack_ctx {
   float* merge_inv = nullptr;    //   ... inverse key norms of the kept rows
   int* fault = nullptr;          // pinned, device-visible int[2]: [0] a score wave's bounded wait gave up (fatal),
                                  // [1] a logit exceeded the range the bf16 score kernel supports
-  int score_capacity[4] = {0, 0, 0, 0};   // bf16 path: score items one fused launch may hold (resident waves) for items of 32, 64, 128, 256 keys
+  int score_capacity[kScoreSizes] = {};   // bf16 path: score items one fused launch may hold (resident waves), by item size (kScoreItemKeys)
   int split_max_items = -1;      // launches with at most this many 32-query attention items use the key-split kernel (HACK_ATTN_SPLIT_ITEMS); -1 (default): see use_split_attention
   int attn_kernel = -1;          // bf16 kernel of the 128-query items (kAttnPlain ...); -1 (default): the deeper pipeline, keys in halves where use_key_halves says so
   // streamed form of that kernel: the launch is cut into equal runs of key blocks, one per resident work-group
@@ -508,15 +508,18 @@ void build_score_items(const std::vector<UnitDesc>& descs, int n, int item_keys,
 // Smaller items spread a launch over more compute units and shorten every wave's serial tile work, so the
 // smallest size is taken whose items all fit one launch (the fused kernel's work-groups wait for each other
 // inside a launch, so a launch holds at most what the device keeps resident) and whose work-groups per unit the
-// exchange area supports; if no size fits one launch, the size that needs the fewest launches.  The choice
+// exchange area supports; if no size fits one launch, the size that needs the fewest launches.  A wave's tiles take some 1.7 us each, one after
+// the other, hence sizes between the powers of two.  Without / with those of 96 and 192 keys, us a launch, head_dim 128: 32 units of 3543 or 5485
+// keys 16.8 / 15.2, of 4247 or 6189 17.2 / 15.9, 64 of 3883 or 7039 33.8 / 29.5; in two passes 26.0 / 23.0, 26.7 / 24.5, 48.0 / 43.5; 200 units of
+// 1200 or 1500, head_dim 64, 23.8 / 19.6.  The choice
 // does not depend on the score mode, so both modes (and the fixed-scratch entry point, which applies the same
 // rule) group the keys alike and give the same bits.
 int choose_score_item_keys(const hack_ctx* ctx, std::vector<int> t_in) {
   std::stable_sort(t_in.begin(), t_in.end(), [](int a, int b) { return a > b; });   // the order build_score_items fills launches in
   int best_keys = 0;
   long best_launches = 0;
-  for (int i = 0; i < 4; ++i) {
-    const int keys = 32 << i, cap = ctx->score_capacity[i];
+  for (int i = 0; i < kScoreSizes; ++i) {
+    const int keys = kScoreItemKeys[i], cap = ctx->score_capacity[i];
     if (cap <= 0) continue;
     long launches = 1, in_launch = 0;
     bool fits = true;
@@ -544,7 +547,7 @@ int plan_score_items(const hack_ctx* ctx, const std::vector<UnitDesc>& descs, in
   for (int i = 0; i < n; ++i) t_in.push_back(descs[i].len_in + descs[i].n_new);
   const int keys = choose_score_item_keys(ctx, std::move(t_in));
   int idx = 0;
-  while ((32 << idx) != keys) ++idx;
+  while (kScoreItemKeys[idx] != keys) ++idx;
   build_score_items(descs, n, keys, two_pass ? INT32_MAX : ctx->score_capacity[idx], items, group_begin);
   return keys;
 }
@@ -686,10 +689,10 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   if (e == hipSuccess && cfg->dtype == HACK_BF16) {
     // a unit's score items wait for each other inside one launch, so a launch may
     // hold at most as many items as the device keeps resident at once
-    for (int i = 0; i < 4; ++i) ctx->score_capacity[i] = score_fused_capacity(cfg->head_dim, 32 << i);
+    for (int i = 0; i < kScoreSizes; ++i) ctx->score_capacity[i] = score_fused_capacity(cfg->head_dim, kScoreItemKeys[i]);
     // the largest unit must fit one launch with the largest items
     const int per_unit = (cfg->max_cache_len + 255) / 256 + 3;
-    if (ctx->score_capacity[3] < per_unit || (per_unit + 3) / 4 > score_max_groups()) e = hipErrorInvalidConfiguration;
+    if (ctx->score_capacity[kScoreSizes - 1] < per_unit || (per_unit + 3) / 4 > score_max_groups()) e = hipErrorInvalidConfiguration;
   }
   if (e != hipSuccess) {
     hack_destroy(ctx);

@@ -407,7 +407,7 @@ __global__ __launch_bounds__(512) void score_select_f32(
 // B operand = K^T (column = key lane%32); see c_row() for where the results sit.
 
 // ---- wave-private tile pipeline -------------------------------------------
-// A work item is (unit, chunk of 32 TILES keys, TILES = 1, 2, 4 or 8) and belongs to ONE wave: the
+// A work item is (unit, chunk of 32 TILES keys, TILES = 1, 2, 3, 4, 6 or 8) and belongs to ONE wave: the
 // wave copies its 32-key tiles HBM -> LDS with global_load_lds (16 B per lane,
 // whole rows, fully coalesced), double-buffered in a private LDS region, and
 // reads MFMA operands back with ds_read_b128 (XOR-swizzled chunks, conflict
@@ -757,7 +757,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_fused(
       int polls = 0;
       while (MODE == kScoreFused && bits[k] == kEmpty) {
         if (++polls > spin_limit) { ok = false; break; }
-        __builtin_amdgcn_s_sleep(8);
+        __builtin_amdgcn_s_sleep(1);
         bits[k] = __hip_atomic_load(&unit_slots[(sub + 8 * k) * kMaxObs + row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       acc += __longlong_as_double((long long)bits[k]);
@@ -1067,7 +1067,9 @@ int score_fused_capacity(int head_dim, int item_keys) {
   switch (item_keys) {
     case 32: e = head_dim == 64 ? HACK_OCC(64, 1) : HACK_OCC(128, 1); break;
     case 64: e = head_dim == 64 ? HACK_OCC(64, 2) : HACK_OCC(128, 2); break;
+    case 96: e = head_dim == 64 ? HACK_OCC(64, 3) : HACK_OCC(128, 3); break;
     case 128: e = head_dim == 64 ? HACK_OCC(64, 4) : HACK_OCC(128, 4); break;
+    case 192: e = head_dim == 64 ? HACK_OCC(64, 6) : HACK_OCC(128, 6); break;
     case 256: e = head_dim == 64 ? HACK_OCC(64, 8) : HACK_OCC(128, 8); break;
     default: break;
   }
@@ -1109,6 +1111,8 @@ void launch_score_fused(hipStream_t s, int head_dim, int item_keys, bool two_pas
     switch (item_keys) {
       case 32: HACK_SCORE_CALL(64, 1); break;
       case 64: HACK_SCORE_CALL(64, 2); break;
+      case 96: HACK_SCORE_CALL(64, 3); break;
+      case 192: HACK_SCORE_CALL(64, 6); break;
       case 256: HACK_SCORE_CALL(64, 8); break;
       default: HACK_SCORE_CALL(64, 4); break;
     }
@@ -1116,6 +1120,8 @@ void launch_score_fused(hipStream_t s, int head_dim, int item_keys, bool two_pas
     switch (item_keys) {
       case 32: HACK_SCORE_CALL(128, 1); break;
       case 64: HACK_SCORE_CALL(128, 2); break;
+      case 96: HACK_SCORE_CALL(128, 3); break;
+      case 192: HACK_SCORE_CALL(128, 6); break;
       case 256: HACK_SCORE_CALL(128, 8); break;
       default: HACK_SCORE_CALL(128, 4); break;
     }

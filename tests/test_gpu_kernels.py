@@ -310,6 +310,46 @@ def test_score_many_units_split_into_launch_groups_and_repeated_calls():
     hk.close()
 
 
+@pytest.mark.parametrize("d,longest", [(128, 2240), (128, 4800), (64, 4352), (64, 4800)])   # items of 96, 192, 96, 192 keys
+def test_score_items_of_three_and_six_tiles(d, longest):
+    """Item sizes between the powers of two, chosen where smaller items do not fit one launch: units that end on and around item, tile and
+    work-group boundaries, in one launch, in two passes and with fixed scratch (the same bits), against float64."""
+    u = _u()
+    H, Nk = 64, 40
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(d + longest)
+    t_in = np.full(H, longest, np.int32)
+    ends = [41, 95, 96, 97, 191, 192, 193, 383, 384, 385, 767, 768, 769]
+    for i, t in enumerate(ends):
+        t_in[5 + i] = max(t, Nk + 1)
+    t_in[30:40] = longest - np.arange(10) * 11
+    lens = (t_in - Nk).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum((lens + 7) // 8 * 8)]).astype(np.int64)
+    q, kn = (torch.randn((1, H, Nk, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    K = torch.randn((int(off[-1]), d), generator=gen, device=u.DEV).bfloat16()
+    scale = float(np.float32(d ** -0.5))
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=longest, max_queries=Nk)
+    src = Cache(K, K, off[:-1], lens)
+    stride = (longest + 63) // 64 * 64
+    imps = []
+    for form in ("fused", "fused", "two-pass", "static"):
+        imp = torch.full((H, stride), -1.0, device=u.DEV)
+        if form == "two-pass":
+            hk.set_score_mode(1)
+        (hk.score_static if form == "static" else hk.score)(q, src, scale, imp, k_new=kn)
+        torch.cuda.synchronize()
+        imps.append(imp)
+    assert all(torch.equal(imps[0], x) for x in imps[1:])
+    rows = [i * Nk // 32 for i in range(32)]
+    for x in list(range(5, 5 + len(ends))) + [0, 30, 39, 63]:
+        k = torch.cat([K[off[x]:off[x] + lens[x]], kn[0, x]]).double()
+        want = torch.softmax(scale * (q[0, x, rows].double() @ k.T.contiguous()), -1).sum(0)
+        assert float(((imps[0][x, :t_in[x]].double() - want) / want).abs().max()) < 1e-6, (x, int(t_in[x]))   # the bar of the entry point
+        assert bool((imps[0][x, t_in[x]:] == -1).all())
+    hk.check()
+    hk.close()
+
+
 def test_score_extreme_logits_bf16():
     """Logits of a few hundred nats: the row normalisers live in fp64, so peaked
     rows must still follow the fp64 oracle over 100+ orders of magnitude (entries
