@@ -24,10 +24,12 @@ DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang"
                 "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 # The score kernels read every MFMA result with the vector ALU straight away:
 # keeping the accumulators in VGPRs spares one AGPR copy per result register.
+# Its atomics come from one lane each; combined over the wave by the compiler they would be waited for where they are issued, in
+# front of a barrier (score launches over 32 units, head_dim 128, 10.3 -> 9.8, 15.3 -> 14.7 us).
 # The attention kernels' accumulators pass a rare branch in every stage: cut into pieces there, they no longer fit the
 # registers (a launch of 568 us takes 8840).
 PER_SOURCE = {"kernels_attn.hip": ["-mllvm", "-amdgpu-codegenprepare-break-large-phis=false"],
-              "kernels_score.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+              "kernels_score.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option", "-Wno-inline-asm",
           "-Wno-unused-command-line-argument"]
 

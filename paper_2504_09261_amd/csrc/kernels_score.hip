@@ -140,25 +140,28 @@ template <int TPW>
 __device__ __forceinline__ void wave_stats(const double (&s)[TPW][2][4], int key0, int T_in, double (*red_m)[kMaxObs], double (*red)[kMaxObs]) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int i = lane & 15, g = lane >> 4;
+  double m[8], l[8];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int x = 0; x < 8; ++x) {
+    m[x] = -INFINITY;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double m = -INFINITY;
+    for (int t = 0; t < TPW; ++t) m[x] = fmax(m[x], key0 + 16 * t + i < T_in ? s[t][x / 4][x % 4] : -INFINITY);
+    m[x] = row16_reduce(m[x], [](double a, double b) { return fmax(a, b); });
+  }
 #pragma unroll
-      for (int t = 0; t < TPW; ++t)
-        if (key0 + 16 * t + i < T_in) m = fmax(m, s[t][h][r]);
-      m = row16_reduce(m, [](double a, double b) { return fmax(a, b); });
-      double l = 0.0;
+  for (int x = 0; x < 8; ++x) {
+    l[x] = 0.0;
 #pragma unroll
-      for (int t = 0; t < TPW; ++t)
-        if (key0 + 16 * t + i < T_in) l += exp_neg(s[t][h][r] - m);
-      l = row16_reduce(l, [](double a, double b) { return a + b; });
-      if (i == 0) {
-        red_m[w][16 * h + 4 * r + g] = m;
-        red[w][16 * h + 4 * r + g] = l;
-      }
+    for (int t = 0; t < TPW; ++t) l[x] += key0 + 16 * t + i < T_in ? exp_neg(s[t][x / 4][x % 4] - m[x]) : 0.0;
+    l[x] = row16_reduce(l[x], [](double a, double b) { return a + b; });
+  }
+  if (i == 0) {   // one branch behind all eight chains, which then overlap
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      red_m[w][16 * (x / 4) + 4 * (x % 4) + g] = m[x];
+      red[w][16 * (x / 4) + 4 * (x % 4) + g] = l[x];
     }
+  }
 }
 __device__ __forceinline__ void chunk_stats(int row, const double (*red_m)[kMaxObs], const double (*red)[kMaxObs], double* m_out, double* l_out) {
   double m = red_m[0][row];     // finite: the chunk's first key exists, and wave 0 holds it
@@ -303,14 +306,16 @@ __global__ __launch_bounds__(512) void score_select_f32(
 
   if (w < 4) {
     floatx4 qf[2][C], kf[C];
+    // (the row numbers come in front: behind the keys they would be waited for with them)
+    const int row0 = q_rows[i < n_obs ? i : 0], row1 = q_rows[16 + i < n_obs ? 16 + i : 0];
+    asm volatile("" ::"v"(row0), "v"(row1));
     const int j = min(key0 + i, T_in - 1);
     const float* p = (j < d.len_in ? k_cache + (d.in_off + j) * D : k_new + ((int64_t)d.unit * N_k + (j - d.len_in)) * D) + 4 * g;
 #pragma unroll
     for (int c = 0; c < C; ++c) kf[c] = *reinterpret_cast<const floatx4*>(p + 16 * c);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int row = 16 * h + i;
-      const float* p = q + ((int64_t)d.unit * N_k + q_rows[row < n_obs ? row : 0]) * D + 4 * g;
+      const float* p = q + ((int64_t)d.unit * N_k + (h == 0 ? row0 : row1)) * D + 4 * g;
 #pragma unroll
       for (int c = 0; c < C; ++c) qf[h][c] = *reinterpret_cast<const floatx4*>(p + 16 * c);
     }
@@ -343,6 +348,7 @@ __global__ __launch_bounds__(512) void score_select_f32(
   __syncthreads();
   if (!last_ticket) return;
   if (tid == 0) store_agent(&counters[2 * blockIdx.y], 0u);   // as the next launch expects it
+  clear_hist<NT, 11, 11>(hist, tid);
 
   // ---- pass 2: wave w takes the tiles w, w + NW, ..., whose logits arrive while the rows' partials are combined ----
   double s[kPerWave][2][4];
@@ -397,7 +403,7 @@ __global__ __launch_bounds__(512) void score_select_f32(
     if (ranked) in_seg |= 1u << e;
     key[e] = ranked ? __float_as_uint(imp_sh[j0 + e]) : 0u;
   }
-  select_rows<NT, PER, 11, 11>(d, key, in_seg, hist, sh, kept_idx + (int64_t)d.unit * idx_stride, seam);
+  select_rows<NT, PER, 11, 11, true>(d, key, in_seg, hist, sh, kept_idx + (int64_t)d.unit * idx_stride, seam);
 }
 
 // ---------------------------------------------------------------------------
@@ -1027,14 +1033,15 @@ __global__ __launch_bounds__(64 * NW) void score_select(
       if (half == 0) keys[(w + t * NW) * 32 + col] = __float_as_uint((float)imp);
     }
   }
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(&bufs[0][0]);
+  clear_hist<64 * NW, 11, 11>(hist, tid);
   __syncthreads();
 
   // ---- selection ----
   uint32_t key[1] = {0};
   const unsigned in_seg = tid >= d.sel_lo && tid < d.sel_hi ? 1u : 0u;
   if (in_seg) key[0] = keys[tid];
-  select_rows<64 * NW, 1, 11, 11>(d, key, in_seg, reinterpret_cast<uint32_t*>(&bufs[0][0]), sh,
-                                  kept_idx + (int64_t)d.unit * idx_stride, seam, MOVE ? keys : nullptr);
+  select_rows<64 * NW, 1, 11, 11, true>(d, key, in_seg, hist, sh, kept_idx + (int64_t)d.unit * idx_stride, seam, MOVE ? keys : nullptr);
   if constexpr (MOVE) {
     __syncthreads();
     move_unit<D, 64 * NW>(d, keys, k_new, mv, N_k);

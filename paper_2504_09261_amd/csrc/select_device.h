@@ -51,17 +51,21 @@ struct SelectShared {
   int found[3][3];   // per pass: bin, rows still wanted from it, keys in it
 };
 
+template <int NT, int B0, int B1>
+__device__ __forceinline__ void clear_hist(uint32_t* hist, int tid) {
+  for (int i = tid * 4; i < SelectShared<NT, B0, B1>::kHist; i += NT * 4) *reinterpret_cast<uint4*>(&hist[i]) = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // The work-group (NT threads) writes the kept rows of d to out in ascending order.  Thread tid holds the keys of the PER
 // rows from tid * PER on: float bits where in_seg says that the row is ranked.  Digits of B0, B1 and 32 - B0 - B1 bits;
-// hist: SelectShared::kHist words of LDS; kept_lds, if given, gets the list as well (words nobody reads any more once a barrier
+// hist: SelectShared::kHist words of LDS, 16-byte aligned, cleared in here unless the caller has done so in front of a barrier (CLEARED); kept_lds, if given, gets the list as well (words nobody reads any more once a barrier
 // has been passed).
-template <int NT, int PER, int B0, int B1>
+template <int NT, int PER, int B0, int B1, bool CLEARED = false>
 __device__ __forceinline__ void select_rows(const UnitDesc& d, uint32_t (&key)[PER], unsigned in_seg, uint32_t* hist,
                                             SelectShared<NT, B0, B1>& sh, int32_t* __restrict__ out, int32_t* __restrict__ seam,
                                             uint32_t* kept_lds = nullptr) {
   constexpr int kWaves = NT / 64;
   constexpr int B2 = 32 - B0 - B1;
-  constexpr int kHist = SelectShared<NT, B0, B1>::kHist;
   auto& wave_tot = sh.wave_tot;
   auto& found = sh.found;
   const int T = d.len_in + d.n_new;
@@ -76,10 +80,10 @@ __device__ __forceinline__ void select_rows(const UnitDesc& d, uint32_t (&key)[P
   int want = d.sel_m;   // candidates to keep
   bool all_candidates = true;
   if (ranked) {
-    for (int i = tid * 4; i < kHist; i += NT * 4) *reinterpret_cast<uint4*>(&hist[i]) = make_uint4(0u, 0u, 0u, 0u);
+    if (!CLEARED) clear_hist<NT, B0, B1>(hist, tid);
 #pragma unroll
     for (int e = 0; e < PER; ++e) key[e] = orderable(__uint_as_float(key[e]));
-    __syncthreads();
+    if (!CLEARED) __syncthreads();
     // One pass over a digit of BITS bits at bit SH; bins in descending order of the digit.
     auto pass = [&](auto idx_tag, auto bits_tag, auto sh_tag, uint32_t* h) {
       constexpr int P = decltype(idx_tag)::value, BITS = decltype(bits_tag)::value, SH = decltype(sh_tag)::value;
