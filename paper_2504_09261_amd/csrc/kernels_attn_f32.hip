@@ -25,7 +25,8 @@
 // R = 1 / R = 2: head_dim 64, 256 items of 306 keys 8.5 / 11.2, 512 items 13.7 / 11.9, 800
 // items of 700 keys 42 / 36; head_dim 128: 13.7 / 18.3, 26.2 / 19.8, 81 / 69; at 64 units x
 // 1024 queries x 2000 keys R = 2 reaches 90 (d = 64) and 108 TFLOP/s (d = 128) of the 157
-// the float32 matrix rate allows.  One query per lane with K/V rows broadcast from LDS, the
+// the float32 matrix rate allows.  The rows to append loaded with the operands instead of behind the loop, and units of one block (the first
+// scales) stored without the merge: launches over 1 to 14 keys 4.4 -> 3.5 us (kernel trace), a 680-token schedule 105.3 -> 103.4.  One query per lane with K/V rows broadcast from LDS, the
 // form this replaces, took 135 us on average over the ten launches of a 680-token
 // schedule (16 heads x 64, batch 1); the whole schedule went from 1699 to 379 us.
 #include "device_util.h"
@@ -93,13 +94,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
   __shared__ floatx4 o_sh[NW][NG][64];
   __shared__ float m_sh[NW][QT], l_sh[NW][QT];
 
+  const int n_blocks = (total + kKB - 1) / kKB;
   // ---- Q operands ----
   floatx4 qf[R][C];
+  if (w < n_blocks) {
 #pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const float* qrow = q + (new_row0 + min(q0 + 16 * j + i, N_k - 1)) * D + 4 * g;
+    for (int j = 0; j < R; ++j) {
+      const float* qrow = q + (new_row0 + min(q0 + 16 * j + i, N_k - 1)) * D + 4 * g;
 #pragma unroll
-    for (int c = 0; c < C; ++c) qf[j][c] = *reinterpret_cast<const floatx4*>(qrow + 16 * c);
+      for (int c = 0; c < C; ++c) qf[j][c] = *reinterpret_cast<const floatx4*>(qrow + 16 * c);
+    }
   }
 
   // key row in its home; rows past the end repeat the last one (their scores are masked)
@@ -136,6 +140,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
     }
   };
 
+  // Cache update of this tile's rows: loaded behind the first operands, stored when the loop is done (loaded there they put a memory
+  // round trip in front of the merge).
+  constexpr int LPR = D / 4;                                       // 16-byte pieces per row
+  constexpr int APP = (QT * LPR + 64 * NW - 1) / (64 * NW);        // pieces per thread
+  uint4 app_k[APP], app_v[APP];
+  const int n_app = !GATHER && fuse ? min(QT, N_k - q0) * LPR : 0;
+
   floatx4 o[R][M][4];   // [query block][64-row block of O^T][MFMA e]: C register r of lane (i, g) is O[query i][64 m + 16 g + 4 r + e]
   float m_run[R], l_run[R];
 #pragma unroll
@@ -149,11 +160,18 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
   }
   const float c2 = scale * kLog2eF;
 
-  const int n_blocks = (total + kKB - 1) / kKB;
   if (w < n_blocks) {
     entry_k(w);
     entries_v(w);
     load_k();
+  }
+  if (!GATHER && fuse) {
+#pragma unroll
+    for (int x = 0; x < APP; ++x) {
+      const int e = min(tid + x * 64 * NW, n_app - 1);
+      app_k[x] = (reinterpret_cast<const uint4*>(k_new) + (new_row0 + q0) * LPR)[e];
+      app_v[x] = (reinterpret_cast<const uint4*>(v_new) + (new_row0 + q0) * LPR)[e];
+    }
   }
   for (int b = w; b < n_blocks; b += NW) {
     const bool more = b + NW < n_blocks;
@@ -209,19 +227,38 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
             o[j][m][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][m][e], sc[j][r], o[j][m][e], 0, 0, 0);
   }
 
-  // ---- cache update of this tile's rows, off the way of the loads above ----
-  if (fuse) {
-    constexpr int LPR = D / 4;   // 16-byte pieces per row
-    const int nr = min(QT, N_k - q0);
-    const uint4* ks = reinterpret_cast<const uint4*>(k_new) + (new_row0 + q0) * LPR;
-    const uint4* vs = reinterpret_cast<const uint4*>(v_new) + (new_row0 + q0) * LPR;
+  if (!GATHER && fuse) {
     uint4* kd = reinterpret_cast<uint4*>(k_app) + (it.in_off + it.len_in + q0) * LPR;
     uint4* vd = reinterpret_cast<uint4*>(v_app) + (it.in_off + it.len_in + q0) * LPR;
-    for (int e = tid; e < nr * LPR; e += 64 * NW) {
-      kd[e] = ks[e];
-      vd[e] = vs[e];
+#pragma unroll
+    for (int x = 0; x < APP; ++x) {
+      const int e = tid + x * 64 * NW;
+      if (e < n_app) {
+        kd[e] = app_k[x];
+        vd[e] = app_v[x];
+      }
     }
-    if (pos_app != nullptr && tid < nr) pos_app[it.in_off + it.len_in + q0 + tid] = pos_new + q0 + tid;
+    if (pos_app != nullptr && tid < n_app / LPR) pos_app[it.in_off + it.len_in + q0 + tid] = pos_new + q0 + tid;
+  }
+
+  // A unit of one block (the first scales): wave 0 holds the whole result.
+  if (n_blocks == 1) {
+    if (w == 0) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const float inv = 1.f / rows_sum(l_run[j]);
+        const int qi = q0 + 16 * j + i;
+        if (qi < N_k) {
+#pragma unroll
+          for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              *reinterpret_cast<floatx4*>(out + (new_row0 + qi) * D + 64 * m + 16 * g + 4 * r) =
+                  floatx4{o[j][m][0][r], o[j][m][1][r], o[j][m][2][r], o[j][m][3][r]} * inv;
+        }
+      }
+    }
+    return;
   }
 
   // ---- merge the waves' partial results ----
