@@ -132,7 +132,7 @@ hack_status hack_check(hack_ctx* ctx);
  *                        streams or processes share the device.  Same results
  *                        bit for bit.
  * hack_step scores and selects the short units of a bf16 context (up to 256 to
- * 1024 keys, by head_dim and number of units) with one work-group per unit in
+ * 1024 keys, by head_dim and number of units) inside one work-group in
  * either mode: no exchange, the same importance up to the order in which a row's
  * fp64 sum is formed.
  * Switching drains the device (it re-arms the exchange workspace); do it
@@ -281,7 +281,13 @@ hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q,
  *      partial softmax results at the end (bf16, early scale steps: few
  *      queries); in hack_step this kernel also performs the append when no unit
  *      of the step compresses, and otherwise reads the kept rows where they lie
- *      while further work-groups of the launch move them.
+ *      while further work-groups of the launch move them.  In launches of few
+ *      work items a work-group takes 16 of an item's queries.
+ * A compressing step of a bf16 context whose units are short (up to 1024 keys, by
+ * head_dim, number of units and queries; kept rows of a unit within a work-group's
+ * LDS) hack_step does in one launch of its own: score, selection, compaction and
+ * attention, probabilities summed in an order of its own, so that its outputs are
+ * not the bits of hack_attn over the same rows.
  * The choice depends only on B * H, N_k and the context's head_dim.
  * Returns a negative hack_status for a NULL context or B, N_k < 1. */
 int32_t hack_attn_variant(const hack_ctx* ctx, int32_t B, int32_t N_k);

@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_NAME = "libhack_mi355x.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
 STEP_CALL_PATH = os.path.join(HERE, "_step_call.so")   # CPython entry to hack_step
-SOURCES = ["hack_api.cpp", "kernels_move.hip", "kernels_select.hip", "kernels_score.hip", "kernels_attn.hip", "kernels_attn_split.hip", "kernels_attn_f32.hip",
+SOURCES = ["hack_api.cpp", "kernels_move.hip", "kernels_select.hip", "kernels_score.hip", "kernels_attn.hip", "kernels_attn_split.hip", "kernels_attn_f32.hip", "kernels_step.hip",
            "kernels_headvar.hip", "kernels_merge.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -29,6 +29,7 @@ DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang"
 # The attention kernels' accumulators pass a rare branch in every stage: cut into pieces there, they no longer fit the
 # registers (a launch of 568 us takes 8840).
 PER_SOURCE = {"kernels_attn.hip": ["-mllvm", "-amdgpu-codegenprepare-break-large-phis=false"],
+              "kernels_step.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "kernels_score.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option", "-Wno-inline-asm",
           "-Wno-unused-command-line-argument"]

@@ -39,6 +39,13 @@ constexpr float kLog2eF = 1.4426950408889634f;
 template <int D> __device__ __forceinline__ int swz_k(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
 template <int D> __device__ __forceinline__ int swz_v(int r) { return D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
 
+// swz_v16: V tiles read as operands of v_mfma_f32_16x16x32_bf16, whose transposing reads cover 8 rows x 32 bytes a phase.
+template <int D> __device__ __forceinline__ int swz_v16(int r) { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); }
+
+// The reference of a row's probabilities lies 2^15 above its running maximum, so that the exponent's top bit says that one of them
+// reached 2: float32 and bf16 keep their precision down to 2^-111 of the row's largest probability.
+constexpr float kRowHeadroom = 15.f;
+
 __device__ __forceinline__ unsigned lds_addr_of(const void* p) {
   return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }

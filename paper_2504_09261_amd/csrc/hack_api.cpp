@@ -95,6 +95,7 @@ struct hack_ctx {
   float* part_ml = nullptr;      // [2 * attn_slots, 2, 128] their references and normalisers
   unsigned* part_count = nullptr; // [attn_slots] ticket counters, zero between launches
   // hack_step overlap: the compression chain of one group of units runs beside the attention of the other group
+  int lds_bytes = 0;             // of a work-group, as the device has it
   bool step_overlap = false;     // off by default (measured slower on MI355X, see step_impl); HACK_STEP_OVERLAP=1 switches it on
   hipStream_t aux_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -116,6 +117,7 @@ struct StepGroup {
   int item_keys = 0;
   bool two_pass = false;
   bool small = false;                     // score and selection in one launch
+  int whole = 0;                          // queries per work-group of a launch that does the whole step (use_whole_step), 0: none
   int n_short = 0;                        // of the compressing units, the first ones: those of a launch of their own (split_score_select)
   std::vector<int> launches;              // score launch groups
   unsigned long long* slots = nullptr;    // row-sum exchange area of the group's score launches
@@ -664,6 +666,7 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
   if (e == hipSuccess && cfg->dtype == HACK_BF16) e = hipMalloc((void**)&ctx->merge_inv, n_ws * sizeof(float));
   if (e == hipSuccess && cfg->dtype == HACK_BF16) {
     ctx->attn_slots = attn_stream_slots(cfg->head_dim);
+    if (hipDeviceGetAttribute(&ctx->lds_bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, cfg->device) != hipSuccess) ctx->lds_bytes = 0;
     const size_t n_part = 2 * (size_t)std::max(ctx->attn_slots, 1);
     e = hipMalloc((void**)&ctx->part_o, n_part * 128 * cfg->head_dim * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->part_ml, n_part * 256 * sizeof(float));
@@ -1150,6 +1153,7 @@ struct StepArgs {
   // Attention may read k_new / v_new in place and update the cache while other work-groups of the launch already store
   // their outputs: not where `out` shares memory with them.  The rows are then moved by a launch in front of it.
   bool in_place;
+  bool apart;      // ... nor with q: a launch that scores, too, reads rows of q that other work-groups of it attend for
 };
 
 bool overlap(const void* a, const void* b, size_t bytes) {
@@ -1173,6 +1177,14 @@ void add_unit(GroupUnits* u, StepGroup* g, const UnitDesc& d, bool merges, int N
   } else {
     g->max_rows = std::max(g->max_rows, N_k);
   }
+}
+
+// Queries per work-group of a launch that does the whole step, 0 where the step takes launches of its own.
+int use_whole_step(const hack_ctx* ctx, const GroupUnits& u, const StepNode& n, const StepGroup& g) {
+  // (a kernel that the environment asks for serves every step)
+  if (ctx->cfg.dtype != HACK_BF16 || ctx->split_max_items >= 0 || ctx->attn_kernel != -1 || ctx->attn_stream != -1) return 0;
+  if (u.n_comp == 0 || !u.merging.empty()) return 0;
+  return whole_step_queries(ctx->cfg.head_dim, (int)u.descs.size(), n.N_k, g.max_t, g.max_keys, ctx->lds_bytes);
 }
 
 bool score_select_short(const UnitDesc& d) { return d.len_in + d.n_new <= kScoreSelectHalf; }
@@ -1205,6 +1217,7 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
     while (g->n_short < u.n_comp && score_select_short(u.descs[g->n_short])) ++g->n_short;
     if (!split_score_select(u.n_comp, g->n_short, g->gathered ? 0 : (int)u.descs.size() - u.n_comp)) g->n_short = 0;
   }
+  g->whole = shared ? 0 : use_whole_step(ctx, u, n, *g);
   g->n_moves = (int)moves.size();
   g->n_desc = (int)u.descs.size();
   g->n_comp = u.n_comp;
@@ -1225,7 +1238,8 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
 
 // score -> select -> append / gather (-> merge) of a group's units
 void launch_chain(hack_ctx* ctx, const StepNode& n, const StepGroup& g, const StepArgs& a, hipStream_t s) {
-  bool moves = !a.in_place || (!n.fuse_append && !g.gathered);   // rows move in front of the attention launch
+  if (g.whole && a.apart) return;
+  bool moves = g.whole || !a.in_place || (!n.fuse_append && !g.gathered);   // rows move in front of the attention launch
   if (g.n_comp > 0 && g.small && ctx->cfg.dtype == HACK_F32) {
     launch_score_select_f32(s, ctx->cfg.head_dim, g.ddev(), g.n_comp, g.max_t, a.q, reinterpret_cast<const int32_t*>(g.dev + g.o_rows),
                             n.n_obs, n.N_k, a.scale, a.cp.k, a.k_new, ctx->f32_logits, ctx->stats, ctx->counters, a.kept, a.kstride, ctx->seam);
@@ -1266,9 +1280,11 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
   const AttnItem* items = reinterpret_cast<const AttnItem*>(g.dev + g.o_items);
   const bool append = n.fuse_append && a.in_place;
   const bool eight = n.split && attn_split_in_eight(ctx->cfg.head_dim, g.n_items, g.n_desc, g.max_keys);
-  if (g.gathered && a.in_place) {
-    const GatherArgs ga{a.kept, a.kstride, ctx->seam, ctx->iota, reinterpret_cast<const MoveItem*>(g.dev + g.o_moves), g.n_moves,
-                        a.pos_new, a.k_new, a.v_new, a.cp, eight};
+  if (g.whole || (g.gathered && a.in_place)) {
+    GatherArgs ga{a.kept, a.kstride, ctx->seam, ctx->iota, reinterpret_cast<const MoveItem*>(g.dev + g.o_moves), g.n_moves,
+                  a.pos_new, a.k_new, a.v_new, a.cp, eight, WholeStep{}};
+    if (g.whole)
+      ga.whole = WholeStep{g.n_desc, g.max_t, g.max_keys, g.whole, n.n_obs, reinterpret_cast<const int32_t*>(g.dev + g.o_rows), ctx->fault, !a.apart, 0};
     if (ctx->cfg.dtype == HACK_F32)
       launch_attn_f32_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, n.tile, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
     else
@@ -1442,6 +1458,7 @@ static hack_status step_impl(hack_ctx* ctx, hack_kvcache* cache, int32_t B, int3
   a.pos_new = (int32_t)cache->tokens_seen;
   const size_t new_bytes = (size_t)U * N_k * ctx->cfg.head_dim * ctx->elem_bytes;
   a.in_place = !overlap(out, k_new, new_bytes) && !overlap(out, v_new, new_bytes);
+  a.apart = a.in_place && !overlap(out, q, new_bytes);
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   StepNode* n = find_step(cache, N_k, head_type, H, budget, U, n_init, final_merge, ctx->score_mode == HACK_SCORE_TWO_PASS);

@@ -69,6 +69,47 @@ struct alignas(8) MoveItem {
   int32_t desc;   // index into the UnitDesc table
   int32_t row0;   // first of the rows it moves
 };
+// A whole compressing step of short units in one launch (launch_step_units): every work-group scores and selects for its unit, holds the rows
+// that the unit keeps in LDS, moves a share of them and attends for its queries.
+struct WholeStep {
+  int32_t n_units;          // 0: not such a step
+  int32_t max_t, max_rows;  // longest compressing unit with its new rows (at most kWholeStepKeys), most rows a unit attends over
+  int32_t queries;          // per work-group: 16, 32, 64, 128 or 256
+  int32_t n_obs;
+  const int32_t* q_rows;
+  int* fault;
+  bool moved;               // rows have been moved already: attention over the cache
+  int32_t region;           // LDS in front of the list; set by the launcher
+};
+constexpr int kWholeStepKeys = 1024;
+// LDS of such a work-group: the tiles of the scores, the rows or the partial results, whichever is most; the list of kept rows; the rest.
+inline size_t whole_step_region(int head_dim, int max_rows) {
+  const size_t held = (size_t)(max_rows + 31) / 32 * 32 * head_dim * 4, least = head_dim == 64 ? 65536 : 131072;
+  return held > least ? held : least;
+}
+inline size_t whole_step_lds(int head_dim, int max_rows) {
+  return whole_step_region(head_dim, max_rows) + (size_t)(max_rows + 31) / 32 * 32 * 4 + 18432;
+}
+// Queries per work-group of such a launch, 0 where launches of their own are the better form.  Work-groups of one unit repeat its scores and
+// selection, so a unit gets several only while each of them has a compute unit to itself; one for all of a unit's queries repeats nothing, and
+// its key splits need no merge at 256.  Measured, us a compressing step (queries per work-group), launches of their own / this; head_dim 64, units, queries,
+// keys: 60 of 64, 166 10.5 / 9.2 (16, 32), 27 of 100, 300 11.9 / 9.8 (16), 10.3 (32), 60 of 140, 250 11.6 / 11.0 (256), 11.2 (64), 60 of 169, 424 15.5 / 13.8 (64),
+// 120 of 256, 500 20.5 / 17.4 (128), 18.6 (256), 60 of 256, 562 19.4 / 16.9 (64), 480 of 140, 250 26.8 / 18.8 (256), 960 of 256, 562 104 / 87; 128: 32 of
+// 100, 250 13.9 / 11.2 (16), 128 of 100, 250 22.0 / 16.2 (256), 64 of 200, 480 21.0 / 19.4 (64), 512 of 256, 480 86 / 63.  More work-groups than compute
+// units, several a unit: 240 of 400, 700 30.9 / 36.2; many units of few queries, whose launches are short: 640 of 25, 60 14.6 / 16.1, head_dim 128, 512 of 36, 90
+// 18.3 / 20.6, 512 of 100, 250 35.0 / 34.8; few long units, whose scores would spread over more compute units: 16 of 300, 800 and 1000 15.8 / 15.0, 16.1 /
+// 16.2, 16 of 700, 1000 15.8 / 17.1, head_dim 128, 16 of 300, 700 and 1000 17.9 / 17.8, 18.2 / 19.5, 32 of 300, 1000 22.9 / 23.2, 64 of 300, 1000 26.3 / 24.4.
+inline int whole_step_queries(int head_dim, int n_units, int N_k, int max_t, int max_rows, int lds_bytes) {
+  if (max_t > kWholeStepKeys || max_t > 640 + 8 * n_units || whole_step_lds(head_dim, max_rows) > (size_t)lds_bytes) return 0;
+  const auto groups = [&](int queries) { return (int64_t)n_units * ((N_k + queries - 1) / queries); };
+  if (groups(16) <= 224) return 16;
+  if (groups(32) <= 256) return 32;
+  if (N_k > 144)
+    for (int queries : {64, 128})
+      if (groups(queries) <= 256) return queries;
+  if (groups(256) <= 256) return 256;
+  return N_k <= 256 && N_k > (head_dim == 64 ? 32 : 96) ? 256 : 0;
+}
 struct GatherArgs {
   const int32_t* kept;     // [unit id, kept_stride] lists of the compressing units
   int64_t kept_stride;
@@ -81,6 +122,7 @@ struct GatherArgs {
   const void* v_new;
   CachePtrs cache;         // written by the moving work-groups
   bool eight;              // bf16: eight waves a work-group (attn_split_in_eight)
+  WholeStep whole;
 };
 
 // fp32 score: keys per work-group of a launch over n_list units of up to max_t_in keys (see kernels_score.hip for the line
@@ -268,7 +310,7 @@ void launch_attn_stream(hipStream_t s, int head_dim, const UnitDesc* descs, cons
 // 256 + 32 27.3 / 28.8, 38.3 / 40.2, 58.2 / 59.6; 192 + 96 34.5 / 36.0, 56.4 / 58.0, 110.8 / 113.0; 256 + 64 30.6 / 34.1, 43.3 / 48.9, 73.6 / 80.2
 // (moves in a launch in front, eight waves: 700 and 1500 keys of 256 + 32 29.7, 40.7; 3000 of 256 + 64 81.6).
 // hack_attn alone would take eight waves on to 256 items (256 + 32: 10.9 / 10.7, 16.3 / 14.7, 26.9 / 24.0), but the number of waves
-// decides how the keys are summed, and a step gives the bits of hack_attn over the rows that it kept.
+// decides how the keys are summed, and a step gives the bits of hack_attn over the rows that it kept (unless one launch does all of it: WholeStep).
 inline bool attn_split_in_eight(int head_dim, int n_items, int n_units, int max_keys) {
   if (max_keys <= 20 * 32 || n_items > 256) return false;
   const int busy = n_items + n_units;
@@ -282,6 +324,9 @@ void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
                        void* k_app, void* v_app, int32_t* pos_app, int pos_new, bool append, bool eight, int N_k, float scale,
                        void* out);
+// A whole step (see WholeStep); reached through launch_attn_split_gather, whose arguments it takes.
+void launch_step_units(hipStream_t s, int head_dim, const UnitDesc* descs, WholeStep st, const GatherArgs& g, const void* q, const void* k_cache,
+                       const void* v_cache, int N_k, float scale, void* out);
 // Attention variance of the listed units (bf16): sigma[desc.unit] = sum over the
 // unit's n_out keys of the population variance, across its N_k queries, of the
 // softmax probabilities.  stats: workspace of 2 floats per (unit, query).

@@ -51,13 +51,6 @@ using namespace dev;
 constexpr int kKB = 32;        // keys per block
 constexpr int kItemRows = 32;  // queries per work item
 
-// V rows are read by v_mfma_f32_16x16x32_bf16 operand: one phase of the transposing read covers 8 rows x 32 bytes.
-template <int D> __device__ __forceinline__ int swz_v16(int r) { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); }
-
-// The reference of a row's probabilities lies 2^15 above its running maximum, so that the exponent's top bit says that one of them
-// reached 2: float32 and bf16 keep their precision down to 2^-111 of the row's largest probability.
-constexpr float kHeadroom = 15.f;
-
 // fuse != 0: keys are [rows in_off .. in_off+len_in of the cache | the unit's n_new
 // rows of k_new / v_new], and those new rows are also written behind the cached
 // ones (k_app / v_app / pos_app are the cache arrays, which k_cache / v_cache then
@@ -342,7 +335,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
       float mx = sc[0][qt][0];
 #pragma unroll
       for (int j = 1; j < 8; ++j) mx = fmaxf(mx, sc[j >> 2][qt][j & 3]);
-      const float m_new = fmaxf(mc[qt], fmaf(quad_max(mx), c2, kHeadroom));
+      const float m_new = fmaxf(mc[qt], fmaf(quad_max(mx), c2, kRowHeadroom));
       if (!nothing_yet) {
         const float a = __builtin_amdgcn_exp2f(mc[qt] - m_new);
 #pragma unroll
@@ -546,6 +539,10 @@ void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const
 void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                               const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
                               float scale, void* out) {
+  if (g.whole.n_units > 0) {
+    launch_step_units(s, head_dim, descs, g.whole, g, q, k_cache, v_cache, N_k, scale, out);
+    return;
+  }
   if (n_items + g.n_moves <= 0) return;
   typedef __bf16 T;
 #define HACK_ARGS s, g.eight, n_items, g.n_moves, descs, items, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)nullptr, (const T*)nullptr, \

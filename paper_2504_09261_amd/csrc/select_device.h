@@ -56,7 +56,7 @@ __device__ __forceinline__ void clear_hist(uint32_t* hist, int tid) {
   for (int i = tid * 4; i < SelectShared<NT, B0, B1>::kHist; i += NT * 4) *reinterpret_cast<uint4*>(&hist[i]) = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// The work-group (NT threads) writes the kept rows of d to out in ascending order.  Thread tid holds the keys of the PER
+// The work-group (NT threads) writes the kept rows of d to out (or NULL) in ascending order.  Thread tid holds the keys of the PER
 // rows from tid * PER on: float bits where in_seg says that the row is ranked.  Digits of B0, B1 and 32 - B0 - B1 bits;
 // hist: SelectShared::kHist words of LDS, 16-byte aligned, cleared in here unless the caller has done so in front of a barrier (CLEARED); kept_lds, if given, gets the list as well (words nobody reads any more once a barrier
 // has been passed).
@@ -157,7 +157,8 @@ __device__ __forceinline__ void select_rows(const UnitDesc& d, uint32_t (&key)[P
   for (int e = 0; e < PER; ++e)
     if ((keep >> e) & 1u) {
       if (kept_lds != nullptr) kept_lds[pos] = (uint32_t)(j0 + e);
-      out[pos++] = j0 + e;
+      if (out != nullptr) out[pos] = j0 + e;
+      ++pos;
     }
 }
 

@@ -445,6 +445,82 @@ int attn_rule() {
   return 0;
 }
 
+// Steps of short units that one launch does: every unit once, in the routes that outputs over an input take (scores, selection and moves in
+// front of it; nothing may read queries or new rows that another work-group stores over), eagerly and from a graph; merging, appending and forced
+// steps take the launches that they took, and so do steps beyond the sizes.
+int whole_steps() {
+  typedef std::vector<std::string> Names;
+  stub::lds_bytes = 163840;
+  const int32_t all[kH] = {50, 50, 50, 50}, some[kH] = {50, 1 << 30, 1 << 30, 40}, none[kH] = {1 << 30, 1 << 30, 1 << 30, 1 << 30};
+  for (const auto* budget : {&all, &some, &none})
+    for (int over = 0; over < 4; ++over)
+      for (int last = 0; last < 2; ++last) {
+        Setup s(HACK_BF16, 96, 128, 64);
+        void* to = over == 0 ? s.out : over == 1 ? s.q : over == 2 ? s.k : s.v;
+        Names want;
+        if (budget == &none) want = over < 2 ? Names{"attn_split_append"} : Names{"move", "attn_split"};
+        else if (last) want = {"score_select", "move", "merge", "attn_split"};
+        else if (over == 0) want = {"step_whole"};
+        else want = {"score_select", "move", "attend_whole"};
+        auto before = [&] {
+          hack_kvcache_reset(s.cache);
+          return s.step(8, 1 << 30) == HACK_OK && s.step(40, 1 << 30) == HACK_OK;
+        };
+        auto as_wanted = [&] {
+          if (stub::launches != want || stub::bad_launches) return false;
+          if (budget == &none || last) return stub::whole_launches.empty();
+          if (stub::whole_launches.size() != 1) return false;
+          const stub::WholeLaunch& l = stub::whole_launches[0];
+          std::vector<int> seen(kH, 0);
+          int max_t = 0, max_rows = 0;
+          for (const UnitDesc& d : l.descs) {
+            ++seen[d.unit];
+            max_rows = std::max(max_rows, d.n_out);
+            if (d.mode == MOVE_GATHER) max_t = std::max(max_t, d.len_in + d.n_new);
+            if (d.n_out != std::min((*budget)[d.unit], 78) || d.n_new != 30) return false;
+          }
+          return seen == std::vector<int>(kH, 1) && l.step.max_t == max_t && l.step.max_rows == max_rows && l.step.n_obs == 30 && l.step.moved == (over != 0);
+        };
+        CHECK(before());
+        for (int pass = 0; pass < 2; ++pass) {   // planned, remembered
+          CHECK(before());
+          stub::launches.clear();
+          stub::whole_launches.clear();
+          CHECK(s.step_each(30, *budget, last == 1, 5, to) == HACK_OK && as_wanted());
+        }
+        CHECK(before());
+        stub::Graph g;
+        stub::begin_capture(&g, kStream);
+        CHECK(s.step_each(30, *budget, last == 1, 5, to) == HACK_OK);
+        stub::end_capture();
+        for (int replay = 0; replay < 2; ++replay) {
+          stub::launches.clear();
+          stub::whole_launches.clear();
+          stub::replay(g);
+          CHECK(as_wanted());
+        }
+      }
+  for (const char* name : {"HACK_ATTN_SPLIT_ITEMS", "HACK_ATTN_PIPE", "HACK_ATTN_STREAM", "HACK_STEP_OVERLAP"}) {   // a form that is asked for
+    setenv(name, "1", 1);
+    Setup s(HACK_BF16, 96, 128, 64);
+    unsetenv(name);
+    stub::launches.clear();
+    CHECK(s.schedule());
+    CHECK(std::find(stub::launches.begin(), stub::launches.end(), "step_whole") == stub::launches.end());
+  }
+  // queries per work-group: sixteen while every work-group finds a compute unit, one work-group a unit at 256; nothing beyond the LDS
+  const auto q = [](int d, int units, int n, int t, int rows) { return whole_step_queries(d, units, n, t, rows, 163840); };
+  CHECK(q(64, 56, 64, 166, 100) == 16 && q(64, 57, 64, 166, 100) == 32 && q(64, 128, 64, 166, 100) == 32 && q(64, 129, 64, 166, 100) == 256);
+  CHECK(q(64, 60, 144, 250, 100) == 256 && q(64, 60, 145, 250, 100) == 64 && q(64, 120, 256, 500, 300) == 128 && q(64, 256, 256, 500, 300) == 256);
+  CHECK(q(64, 960, 256, 562, 306) == 256 && q(64, 960, 257, 562, 306) == 0 && q(64, 960, 33, 80, 40) == 256 && q(64, 960, 32, 80, 40) == 0);
+  CHECK(q(128, 512, 97, 250, 140) == 256 && q(128, 512, 96, 250, 140) == 0 && q(128, 256, 36, 90, 60) == 256);
+  CHECK(q(64, 60, 100, 1024, 300) > 0 && q(64, 60, 100, 1025, 300) == 0 && q(64, 16, 100, 768, 300) == 16 && q(64, 16, 100, 769, 300) == 0);
+  CHECK(q(64, 60, 100, 600, 544) > 0 && q(64, 60, 100, 600, 560) == 0 && q(128, 60, 100, 300, 256) > 0 && q(128, 60, 100, 300, 288) == 0);
+  CHECK(whole_step_queries(64, 60, 100, 300, 100, 65536) == 0);
+  stub::lds_bytes = 256;
+  return 0;
+}
+
 // Waves of a key-split work-group: a step that compresses to n_keys rows and hack_attn over as many take the same number (the bits depend
 // on it), eight where that is the faster one for both.
 int split_waves() {
@@ -561,6 +637,7 @@ int main(int argc, char** argv) {
   if (which == "key_halves") rc = key_halves();
   if (which == "attn_rule") rc = attn_rule();
   if (which == "f32_workspace") rc = f32_workspace();
+  if (which == "whole_steps") rc = whole_steps();
   if (rc == 0) printf("ok\n");
   return rc;
 }

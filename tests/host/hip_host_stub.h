@@ -44,6 +44,9 @@ inline void* capture_stream = nullptr;
 inline std::vector<int> waves;                // ... of a work-group of each key-split attention launch
 inline std::vector<std::string> launches;     // names of the launches carried out
 inline int bad_launches = 0;                  // ... over tables that were never written
+inline int lds_bytes = 256;                   // of a work-group: no whole steps in one launch unless a check asks for more
+struct WholeLaunch { hack::WholeStep step; std::vector<hack::UnitDesc> descs; };
+inline std::vector<WholeLaunch> whole_launches;   // launches that do a whole step, with the descriptors they were given
 inline int copies = 0;                        // asynchronous copies carried out
 inline size_t copied = 0;                     // bytes of the last one
 inline std::map<void*, size_t> device_memory; // live allocations
@@ -138,7 +141,10 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
   *st = stub::captured(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;
 }
-hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+  *v = a == hipDeviceAttributeMaxSharedMemoryPerBlock ? stub::lds_bytes : 256;
+  return hipSuccess;
+}
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -222,8 +228,15 @@ void launch_attn_split(hipStream_t s, int, const UnitDesc*, const AttnItem* it, 
   stub::Quiet q;
   stub::submit(s, [=] { stub::waves.push_back(eight ? 8 : 4); });
 }
-void launch_attn_split_gather(hipStream_t s, int, const UnitDesc*, const AttnItem* it, int n, const GatherArgs& g, const void*,
+void launch_attn_split_gather(hipStream_t s, int, const UnitDesc* descs, const AttnItem* it, int n, const GatherArgs& g, const void*,
                               const void*, const void*, int, float, void*) {
+  if (g.whole.n_units > 0) {
+    stub::launch(g.whole.moved ? "attend_whole" : "step_whole", s, descs, nullptr, g.whole.n_units);
+    stub::Quiet q;
+    const WholeStep w = g.whole;
+    stub::submit(s, [=] { stub::whole_launches.push_back({w, std::vector<UnitDesc>(descs, descs + w.n_units)}); });
+    return;
+  }
   stub::launch_items("attn_split_gather", s, it, n);
   stub::Quiet q;
   const bool eight = g.eight;

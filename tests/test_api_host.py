@@ -66,3 +66,7 @@ def test_a_step_and_single_attention_take_the_same_waves(check):
 
 def test_keys_in_halves_only_where_most_work_items_are_long(check):
     check("key_halves")
+
+
+def test_short_compressing_steps_take_one_launch(check):
+    check("whole_steps")

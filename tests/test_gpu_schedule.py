@@ -1122,3 +1122,74 @@ def test_query_subset_variants_and_position_only_baseline():
         assert np.array_equal(kept.cpu().numpy()[uu, :len_out[uu]], want)
         assert np.array_equal(ho.select(imp.cpu().numpy()[uu, :T].astype(np.float64), 1, n_init + Nk, n_init, Nk), want)
     hk.close()
+
+
+# (head_dim, heads, new rows, rows in front of them: longest, kept: most), and the queries per work-group that the step then has
+WHOLE_STEPS = [
+    (64, 8, 17, 30, 20, 16), (64, 8, 96, 160, 255, 16), (64, 60, 65, 192, 100, 32), (64, 60, 146, 279, 280, 64), (64, 120, 150, 390, 300, 128),
+    (64, 60, 130, 110, 65, 256), (64, 300, 40, 30, 33, 256), (64, 257, 256, 256, 511, 256),
+    (64, 80, 40, 472, 320, 32), (64, 80, 40, 473, 321, 32), (64, 60, 100, 924, 544, 32),      # 512, 513 and 1024 keys; the most rows
+    (128, 4, 15, 20, 16, 16), (128, 32, 90, 167, 128, 16), (128, 32, 120, 392, 256, 32), (128, 64, 150, 300, 200, 64), (128, 100, 256, 256, 250, 128),
+    (128, 300, 100, 150, 97, 256), (128, 60, 33, 900, 250, 16),
+]
+
+
+@pytest.mark.parametrize("d,H,n,L,keep,queries", WHOLE_STEPS)
+@pytest.mark.parametrize("with_pos", [True, False])
+def test_short_steps_in_one_launch(d, H, n, L, keep, queries, with_pos):
+    """Compressing steps of short units, which one launch serves: units from one kept row to all but one beside units that keep everything, numbers of
+    queries, keys and rows around the sizes of tiles and forms.  Kept lists, rows and position ids are those of launches of their own (the same scores
+    and ranking) bit for bit, outputs within the rounding of probabilities and output to bf16; outputs over the queries, the new keys and the
+    new values, where the rows move first, are the bits of outputs of their own.  Two passes."""
+    u = _u()
+    rows = np.maximum(L - 3 * np.arange(H) % max(L // 2, 1), 1).astype(np.int32)
+    if keep > n:
+        rows[4::5] = min(L, keep - n)
+    budget = np.minimum(np.maximum(1, (np.linspace(0.05, 1.0, H) * keep).astype(np.int32)), rows + n - 1)
+    budget[0], rows[0], budget[1] = keep, L, min(keep, rows[1] + n - 1)
+    whole = np.flatnonzero((np.arange(H) % 5 == 4) & (rows + n <= keep))       # these keep everything
+    budget[whole] = 10**6
+    kept_rows = np.minimum(budget, rows + n)
+    compress = budget < rows + n
+    # the form that is under test: queries per work-group as the library's rule has them
+    groups = lambda m: H * -(-n // m)
+    form = 16 if groups(16) <= 224 else 32 if groups(32) <= 256 else next((m for m in (64, 128) if n > 144 and groups(m) <= 256), 256)
+    assert form == queries and (rows + n)[compress].max() == L + n and kept_rows.max() == keep
+    types = (np.arange(H) % 2).astype(np.uint8)
+    scale, top = float(np.float32(d ** -0.5)), max(L, n)
+    results = []
+    for attention in (None, "split"):
+        hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=L + n, max_queries=top, attention=attention)
+        mc = hk.managed_cache(np.maximum(np.maximum(kept_rows, L), rows), with_pos=with_pos)
+        gen = torch.Generator(u.DEV)
+        gen.manual_seed(d + n + H)
+        for over in ((None, "q", "k", "v", None) if attention is None else (None,)):
+            k0, v0 = (torch.randn((1, H, L, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2)) if over is None else (k0, v0)
+            q, kn, vn = (torch.randn((1, H, n, d), generator=gen, device=u.DEV).bfloat16() for _ in range(3)) if over is None else (q, kn, vn)
+            mc.reset()
+            hk.step(mc, k0, k0, v0, types, np.where(rows < L, rows, 10**6).astype(np.int32), 3, scale, torch.empty_like(k0))
+            assert list(mc.view()[1]) == list(rows)
+            kept = torch.full((H, L + n), -1, dtype=torch.int32, device=u.DEV)
+            x = dict(q=q.clone(), k=kn.clone(), v=vn.clone())
+            out = torch.full_like(q, 7.0) if over is None else x[over]
+            hk.step(mc, x["q"], x["k"], x["v"], types, budget, 3, scale, out, kept_idx=kept)
+            torch.cuda.synchronize()
+            off, ln = mc.view()
+            assert list(ln) == list(kept_rows)
+            got = [kept] + [t[o:o + m].clone() for t in (mc.k, mc.v) + ((mc.pos,) if with_pos else ()) for o, m in zip(off, ln)]
+            if over is not None:
+                assert torch.equal(out, first[0]) and all(torch.equal(a, b) for a, b in zip(got, first[1])), over
+                continue
+            first = (out, got)
+            results.append((attention, got))
+            for b in list(range(min(H, 6))) + [H // 2, H - 1] + list(whole[:2]):
+                ks, vs = (t[off[b]:off[b] + ln[b]].double() for t in (mc.k, mc.v))
+                p = torch.softmax(scale * (q[0, b].double() @ ks.T.contiguous()), -1)
+                bound = 3 * 2.0 ** -9 * (p @ vs.abs()) * 1.02 + 1e-4   # probabilities, their sum and the output carry 2^-9 each
+                assert bool(((out[0, b].double() - p @ vs).abs() <= bound).all()), (b, int(ln[b]))
+        hk.check()
+        mc.close()
+        hk.close()
+    # the first pass of either context saw the same inputs
+    assert [a for a, _ in results] == [None, None, "split"]
+    assert all(torch.equal(a, b) for a, b in zip(results[0][1], results[2][1]))
