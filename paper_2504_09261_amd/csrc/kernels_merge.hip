@@ -12,14 +12,15 @@
 // formulas above are this library's reading of "similarity-weighted averaging into the
 // nearest retained counterpart".)
 //
-// Four launches, after the gather has written K[I], V[I] into the unit's output rows:
-//   merge_fill     marks every row of the uncompressed cache "evicted" (-2);
-//   merge_mark     marks the kept rows (-1) and forms 1/|k_r| of the kept keys;
+// Three launches, after the gather has written K[I], V[I] into the unit's output rows:
+//   merge_norms    1/|k_r| of the kept keys;
 //   merge_nearest  MFMA pass: a wave holds 32 cache rows (candidates) as the B operand,
 //                  the kept keys stream through LDS as the A operand together with
-//                  their inverse norms, two 32-row blocks per barrier; per lane a running
-//                  (best, arg-best) over 16 kept rows per block, the lane pair (l, l^32)
-//                  combined at the end;
+//                  their inverse norms; per lane a running (best, arg-best) over 16 kept
+//                  rows per block, the lane pair (l, l^32) combined at the end.  Which of its
+//                  rows are kept a work-group finds from the kept indices (marks in LDS), so that no
+//                  launch has to mark them in memory: one launch and 2 us a merge less than with a
+//                  fill and a scatter of marks;
 //   merge_apply    a work-group takes 8 or 32 kept rows: its waves scan the assignment once,
 //                  each a contiguous quarter, and leave the rows that go to one of them
 //                  in LDS lists (ascending); every wave then folds the listed rows, eight
@@ -43,12 +44,17 @@ constexpr int kThreads = 256;
 constexpr int kWaves = 4;
 constexpr int kRing = 4;          // LDS ring slots (32-row blocks of kept keys): two stages of two blocks
 
-constexpr int kNearBlocks = 1;                      // 32-row candidate blocks per wave in merge_nearest (one keeps the kernel at four
-                                                    // work-groups per compute unit: the vector work of one wave then runs beside
-                                                    // the MFMAs of the others)
-constexpr int kNearTile = kWaves * 32 * kNearBlocks;   // cache rows per work-group in merge_nearest
-constexpr int kFillRows = 1024;                     // rows per work-group in merge_fill
-constexpr int kMarkRows = kThreads / 8;             // kept rows per work-group in merge_mark (8 lanes per row)
+constexpr int kNearRows = kWaves * 32;              // cache rows per work-group of merge_nearest in one part
+constexpr int kPartsRing = 12;                      // LDS ring slots in four parts: three stages of four blocks
+// Work-groups (32 cache rows each) of merge_nearest up to which it runs in four parts: as many as are resident at once, one on
+// a compute unit at head_dim 128 (103 KB LDS) and at least two at 64; a second wave of them costs what the shorter walk gains.
+// Measured, us a merge of all its launches, one part / four; head_dim 128, units of cache rows and kept rows (groups): 1 of 5024
+// and 2000 (157) 49.8 / 29.3, 7 of 656 and 40 (147) 19.2 / 18.9, 2 of 5024 and 1200 (314) 37.0 / 36.4, 8 of 1256 and 150 (320)
+// 18.7 / 21.9, 3 of 5024 and 600 (471) 28.1 / 29.5, 12 of 2704 and 400 (1020) 28.1 / 40.9; head_dim 64: 2 of 5024 and 1200 (314)
+// 33.3 / 25.1, 16 of 896 and 150 (448) 17.2 / 17.2, 12 of 1256 and 350 (480) 19.0 / 17.4, 40 of 656 and 150 (840) 17.7 / 20.8.
+template <int D>
+constexpr int64_t kPartsGroups = D == 128 ? 256 : 512;
+constexpr int kNormRows = kThreads / 8;             // kept rows per work-group in merge_norms (8 lanes per row)
 // Cache rows that the work-groups of merge_apply may scan together while each takes 8 kept rows; beyond that it takes 32.  Measured, us
 // a schedule that ends with the merge, 32 / 16 / 8 rows (rows scanned at 8): 12 units of 5500 and 648 kept rows (5.3M) 512 / 506 / 503;
 // 60 of 358 and 102 (0.1M) 128 / 118 / 114; 480 such units (2.2M) 352 / 348 / 346; 32 of 1200 and 190 (0.9M) 126 / 109 / 100; 12 of 6039 and 1943
@@ -58,24 +64,15 @@ constexpr int kScanSteps = 8;                        // 64-row steps of that sca
 constexpr int kFold = 8;                             // evicted rows a wave of merge_apply folds in at a time
 constexpr int kScanPerWave = 2048;                  // cache rows a wave of merge_apply scans per round = capacity of its list
 
-__global__ __launch_bounds__(kThreads) void merge_fill(const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list,
-                                                        int32_t* __restrict__ nearest, int64_t ws_stride) {
-  const UnitDesc d = descs[list[blockIdx.y]];
-  const int T = d.len_in + d.n_new;
-  int32_t* nn = nearest + (int64_t)d.unit * ws_stride;
-  for (int j = blockIdx.x * kFillRows + threadIdx.x; j < min(T, (int)(blockIdx.x + 1) * kFillRows); j += kThreads) nn[j] = -2;
-}
-
 // Work item = (merging unit, 32 kept rows): 8 lanes per row.
 template <int D>
-__global__ __launch_bounds__(kThreads) void merge_mark(
+__global__ __launch_bounds__(kThreads) void merge_norms(
     const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, const __bf16* __restrict__ k_out,
-    const int32_t* __restrict__ kept_idx, int64_t idx_stride, int32_t* __restrict__ nearest,
     float* __restrict__ inv_norm, int64_t ws_stride) {
   const UnitDesc d = descs[list[blockIdx.y]];
   const int b = d.n_out;
-  const int r = blockIdx.x * kMarkRows + (threadIdx.x >> 3), sub = threadIdx.x & 7;
-  if (blockIdx.x * kMarkRows >= b) return;
+  const int r = blockIdx.x * kNormRows + (threadIdx.x >> 3), sub = threadIdx.x & 7;
+  if (blockIdx.x * kNormRows >= b) return;
   // inverse norms of the kept keys (already gathered into the unit's output rows)
   constexpr int CPR = D / 8;
   float ss = 0.f;
@@ -91,29 +88,31 @@ __global__ __launch_bounds__(kThreads) void merge_mark(
   ss += __shfl_xor(ss, 1, 64);
   ss += __shfl_xor(ss, 2, 64);
   ss += __shfl_xor(ss, 4, 64);
-  if (r < b && sub == 0) {
-    inv_norm[(int64_t)d.unit * ws_stride + r] = ss > 0.f ? 1.f / sqrtf(ss) : 0.f;
-    nearest[(int64_t)d.unit * ws_stride + kept_idx[(int64_t)d.unit * idx_stride + r]] = -1;
-  }
+  if (r < b && sub == 0) inv_norm[(int64_t)d.unit * ws_stride + r] = ss > 0.f ? 1.f / sqrtf(ss) : 0.f;
 }
 
-// Work item = (merging unit, 32 kWaves kNearBlocks rows of its uncompressed cache): wave w takes rows
-// [e0, e0 + 32 kNearBlocks).  The kept keys K^ (rows [out_off, out_off + b)) stream through LDS; a
-// fragment read from LDS serves all of the wave's candidate blocks.
-template <int D>
-__global__ __launch_bounds__(kThreads, 4) void merge_nearest(
+// Work item = (merging unit, 128 / PARTS rows of its uncompressed cache).  PARTS = 1: wave w takes rows [e0, e0 + 32) of
+// them and meets every kept key; PARTS = 4: all waves take the same 32 rows and wave w meets every fourth block of the kept
+// keys, the four results are combined through LDS.  The kept keys K^ (rows [out_off, out_off + b)) stream through LDS.
+//
+// A stage is copied, waited for and met at a barrier, so the walk is a chain of stages whose length a copy's latency sets
+// while work-groups are few; four times as many work-groups of a quarter of the stages shorten it as long as the chip has room.
+template <int D, int PARTS>
+__global__ __launch_bounds__(kThreads, PARTS == 1 ? 4 : 1) void merge_nearest(
     const UnitDesc* __restrict__ descs, const int32_t* __restrict__ list, const __bf16* __restrict__ k_in,
-    const __bf16* __restrict__ k_new, const __bf16* __restrict__ k_out, int N_k,
-    const float* __restrict__ inv_norm, int32_t* __restrict__ nearest, float* __restrict__ weight,
+    const __bf16* __restrict__ k_new, const __bf16* __restrict__ k_out, int N_k, const int32_t* __restrict__ kept_idx,
+    int64_t idx_stride, const float* __restrict__ inv_norm, int32_t* __restrict__ nearest, float* __restrict__ weight,
     int64_t ws_stride) {
   using St = BlockStream<D, kWaves>;
   constexpr int KK = D / 16;
-  constexpr int NB = kNearBlocks;
-  __shared__ __attribute__((aligned(1024))) __bf16 ring[kRing][St::BLK];
-  __shared__ __attribute__((aligned(256))) float inv_ring[kRing][kWaves][64];
+  constexpr int TILE = kNearRows / PARTS;
+  constexpr int RING = PARTS == 1 ? kRing : kPartsRing;
+  __shared__ __attribute__((aligned(1024))) __bf16 ring[RING][St::BLK];
+  __shared__ __attribute__((aligned(256))) float inv_ring[RING][PARTS == 1 ? kWaves : 1][64];
+  __shared__ int kept[TILE];
   const UnitDesc d = descs[list[blockIdx.y]];
   const int T = d.len_in + d.n_new, b = d.n_out;
-  if ((int)blockIdx.x * kNearTile >= T) return;        // whole work-group past the end of this unit
+  if ((int)blockIdx.x * TILE >= T) return;             // whole work-group past the end of this unit
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int n_blocks = (b + 31) / 32;
@@ -121,51 +120,68 @@ __global__ __launch_bounds__(kThreads, 4) void merge_nearest(
   st.init(k_out + d.out_off * D, b, &ring[0][0], lane, w);
   const float* inv_base = inv_norm + (int64_t)d.unit * ws_stride;
   const unsigned inv_lds = lds_addr_of(&inv_ring[0][0][0]);
-  // block blk of the kept keys and its 32 inverse norms (every wave copies the norms itself,
-  // so all waves issue the same number of copies per block); a row past the end repeats the last one
-  auto issue = [&](int blk, int slot) {
-    st.issue(blk, slot);
+  // the 32 inverse norms of block blk (a row past the end repeats the last one)
+  auto issue_norms = [&](int blk, int at) {
     const int r = min(blk * 32 + (lane & 31), b - 1);
-    load_to_lds_dword(inv_base, (unsigned)r * 4u, inv_lds + (unsigned)(((blk % kRing) * kWaves + w) * 256));
+    load_to_lds_dword(inv_base, (unsigned)r * 4u, inv_lds + (unsigned)(at * 256));
   };
-  issue(0, 0);
-  if (n_blocks > 1) issue(1, 1);
+  // PARTS = 1: block blk and its norms (every wave copies the norms itself, so all waves issue the same number of copies)
+  auto issue = [&](int blk) {
+    st.issue(blk, blk % RING);
+    issue_norms(blk, (blk % RING) * kWaves + w);
+  };
+  // PARTS = 4: the four blocks of stage s, of them as many as there are, and the norms of the one that this wave meets
+  auto issue_stage = [&](int s) {
+    const int slot = (s * 4) % RING;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (4 * s + i < n_blocks) st.issue(4 * s + i, slot + i);
+    if (4 * s + w < n_blocks) issue_norms(4 * s + w, slot + w);
+  };
+  if constexpr (PARTS == 1) {
+    issue(0);
+    if (n_blocks > 1) issue(1);
+  } else {
+    issue_stage(0);
+    if (n_blocks > 4) issue_stage(1);
+  }
+  // which rows of the tile are kept
+  const int tile0 = blockIdx.x * TILE;
+  if (threadIdx.x < TILE) kept[threadIdx.x] = 0;
   // this wave's candidate rows of the virtual concatenation [cached rows | new rows] (B operands);
   // a wave whose rows all lie past the end still takes part in the copies and barriers
-  const int e0 = blockIdx.x * kNearTile + w * (32 * NB);
-  bf16x8 ef[NB][KK];
-  float inv_e[NB];
+  const int e0 = tile0 + (PARTS == 1 ? w * 32 : 0);
+  bf16x8 ef[KK];
+  const int e = min(e0 + col, T - 1);
+  const __bf16* erow = (e < d.len_in) ? k_in + (d.in_off + e) * D : k_new + ((int64_t)d.unit * N_k + (e - d.len_in)) * D;
 #pragma unroll
-  for (int c = 0; c < NB; ++c) {
-    const int e = min(e0 + 32 * c + col, T - 1);
-    const __bf16* erow = (e < d.len_in) ? k_in + (d.in_off + e) * D : k_new + ((int64_t)d.unit * N_k + (e - d.len_in)) * D;
-    float ss = 0.f;
+  for (int kk = 0; kk < KK; ++kk) ef[kk] = *reinterpret_cast<const bf16x8*>(erow + 16 * kk + 8 * half);
+  __syncthreads();                                        // the marks are clear
+  const int32_t* idx = kept_idx + (int64_t)d.unit * idx_stride;
+  for (int r0 = 0; r0 < b; r0 += kScanSteps * kThreads) {
+    int at[kScanSteps];                                   // these steps' loads in flight together
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      ef[c][kk] = *reinterpret_cast<const bf16x8*>(erow + 16 * kk + 8 * half);
+    for (int u = 0; u < kScanSteps; ++u) at[u] = idx[min(r0 + u * kThreads + (int)threadIdx.x, b - 1)] - tile0;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) ss = fmaf((float)ef[c][kk][i], (float)ef[c][kk][i], ss);
-    }
-    ss = pair_sum(ss);
-    inv_e[c] = ss > 0.f ? 1.f / sqrtf(ss) : 0.f;
+    for (int u = 0; u < kScanSteps; ++u)
+      if ((unsigned)at[u] < (unsigned)TILE) kept[at[u]] = 1;   // read behind the barriers of the loop below
   }
+  float ss = 0.f;
 #pragma unroll
-  for (int c = 0; c < NB; ++c)
+  for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) asm volatile("" ::"v"(ef[c][kk]));   // waited for here, not inside the loop
+    for (int i = 0; i < 8; ++i) ss = fmaf((float)ef[kk][i], (float)ef[kk][i], ss);
+  ss = pair_sum(ss);
+  const float inv_e = ss > 0.f ? 1.f / sqrtf(ss) : 0.f;
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) asm volatile("" ::"v"(ef[kk]));   // waited for here, not inside the loop
 
-  float best[NB];   // largest dot(k_e, k_r) / |k_r| so far among this lane's kept rows
-  int arg[NB];
-#pragma unroll
-  for (int c = 0; c < NB; ++c) {
-    best[c] = -INFINITY;
-    arg[c] = 0;
-  }
+  float best = -INFINITY;   // largest dot(k_e, k_r) / |k_r| so far among this lane's kept rows
+  int arg = 0;
   // One block against this lane's 16 kept rows: the block's largest value displaces the running best only if it
   // is strictly larger (an equal later row does not displace an earlier one), and among equal values of the block
   // the lowest row wins.  A short tree of maxima, then the lowest row that attains the maximum.
-  auto update = [&](const floatx16& sc, int blk, int nv, bool ragged, float& bst, int& ag) {
-    const float* invs = &inv_ring[blk % kRing][w][0];
+  auto update = [&](const floatx16& sc, const float* invs, int blk, int nv, bool ragged) {
     float v[16];
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
@@ -181,65 +197,85 @@ __global__ __launch_bounds__(kThreads, 4) void merge_nearest(
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) m4[g4] = fmaxf(fmaxf(v[4 * g4], v[4 * g4 + 1]), fmaxf(v[4 * g4 + 2], v[4 * g4 + 3]));
     const float vmax = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
-    const bool moved = vmax > bst;
+    const bool moved = vmax > best;
     if (__any(moved)) {                                   // the row is only looked for when some lane's best moved
       int first = 0;
 #pragma unroll
       for (int q = 15; q >= 0; --q)                       // descending, so the lowest matching row is written last
         first = (v[q] == vmax) ? 8 * (q >> 2) + 4 * half + (q & 3) : first;
-      bst = moved ? vmax : bst;
-      ag = moved ? blk * 32 + first : ag;
+      best = moved ? vmax : best;
+      arg = moved ? blk * 32 + first : arg;
     }
   };
-  auto scores = [&](int blk, floatx16& sc) {
-    const __bf16* slot = &ring[blk % kRing][0];
+  auto scores = [&](const __bf16* slot, floatx16& sc) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) sc[r] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
-      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag<D>(slot, col, half, kk), ef[0][kk], sc, 0, 0, 0);
+      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag<D>(slot, col, half, kk), ef[kk], sc, 0, 0, 0);
   };
-  static_assert(NB == 1, "the loop below is written for one candidate block per wave");
-  // A stage is two blocks of kept keys (one barrier per stage); while a stage is worked on, the copies of the
-  // next one are in flight into the other two ring slots.
-  for (int blk = 0; blk < n_blocks; blk += 2) {
-    dma_wait_but<0>();                                      // this wave's copies of blocks blk, blk+1 have landed
-    __syncthreads();                                        // ... and everybody's; the slots of blocks blk-2, blk-1 are free
-    if (blk + 2 < n_blocks) issue(blk + 2, (blk + 2) % kRing);
-    if (blk + 3 < n_blocks) issue(blk + 3, (blk + 3) % kRing);
-    floatx16 s0, s1;
-    const bool two = blk + 1 < n_blocks;                    // wave-uniform
-    scores(blk, s0);
-    if (two) scores(blk + 1, s1);
-    // the ragged form (rows past the end masked) is a separate instance, taken by the last block only
-    const int nv0 = min(32, b - blk * 32);
-    if (nv0 == 32) update(s0, blk, 32, false, best[0], arg[0]);
-    else update(s0, blk, nv0, true, best[0], arg[0]);
-    if (two) {
-      const int nv1 = min(32, b - (blk + 1) * 32);
-      if (nv1 == 32) update(s1, blk + 1, 32, false, best[0], arg[0]);
-      else update(s1, blk + 1, nv1, true, best[0], arg[0]);
+  // the ragged form (rows past the end masked) is a separate instance, taken by the last block only
+  auto meet = [&](const floatx16& sc, const float* invs, int blk) {
+    const int nv = min(32, b - blk * 32);
+    if (nv == 32) update(sc, invs, blk, 32, false);
+    else update(sc, invs, blk, nv, true);
+  };
+  if constexpr (PARTS == 1) {
+    // A stage is two blocks of kept keys (one barrier per stage); while a stage is worked on, the copies of the
+    // next one are in flight into the other two ring slots.
+    for (int blk = 0; blk < n_blocks; blk += 2) {
+      dma_wait_but<0>();                                    // this wave's copies of blocks blk, blk+1 have landed
+      __syncthreads();                                      // ... and everybody's; the slots of blocks blk-2, blk-1 are free
+      if (blk + 2 < n_blocks) issue(blk + 2);
+      if (blk + 3 < n_blocks) issue(blk + 3);
+      floatx16 s0, s1;
+      const bool two = blk + 1 < n_blocks;                  // wave-uniform
+      scores(&ring[blk % RING][0], s0);
+      if (two) scores(&ring[(blk + 1) % RING][0], s1);
+      meet(s0, &inv_ring[blk % RING][w][0], blk);
+      if (two) meet(s1, &inv_ring[(blk + 1) % RING][w][0], blk + 1);
     }
-  }
-#pragma unroll
-  for (int c = 0; c < NB; ++c) {
-    // the partner lane holds the other 16 rows of every block: larger value wins, equal values go to the lower index
-    const float best_o = __builtin_bit_cast(float, pair_other(__builtin_bit_cast(unsigned, best[c])));
-    const int arg_o = (int)pair_other((unsigned)arg[c]);
-    float bst = best[c];
-    int ag = arg[c];
-    if (best_o > bst || (best_o == bst && arg_o < ag)) {
-      bst = best_o;
-      ag = arg_o;
-    }
-    const int ej = e0 + 32 * c + col;
-    if (half == 0 && ej < T) {
-      int32_t* nn = nearest + (int64_t)d.unit * ws_stride;
-      if (nn[ej] == -2) {   // evicted row
-        nn[ej] = ag;
-        weight[(int64_t)d.unit * ws_stride + ej] = fmaxf(bst * inv_e[c], 0.f);
+  } else {
+    // A stage is four blocks, one per wave; two stages are in flight behind the one that is worked on.
+    for (int s = 0; 4 * s < n_blocks; ++s) {
+      if (4 * (s + 2) <= n_blocks) dma_wait_but<4 * St::IPW + 1>();   // stage s + 1, whole, may be in flight
+      else dma_wait_but<0>();
+      __syncthreads();                                      // all of stage s is visible; the slots of stage s - 1 are free
+      if (4 * (s + 2) < n_blocks) issue_stage(s + 2);
+      const int blk = 4 * s + w, slot = (4 * s) % RING + w;
+      if (blk < n_blocks) {                                 // wave-uniform
+        floatx16 sc;
+        scores(&ring[slot][0], sc);
+        meet(sc, &inv_ring[slot][0][0], blk);
       }
     }
+  }
+  // Larger value wins, equal values go to the lower index, whatever the order: the partner lane holds the other 16 rows
+  // of every block, the other waves (PARTS = 4) the other blocks.
+  auto combine = [&](float best_o, int arg_o) {
+    if (best_o > best || (best_o == best && arg_o < arg)) {
+      best = best_o;
+      arg = arg_o;
+    }
+  };
+  combine(__builtin_bit_cast(float, pair_other(__builtin_bit_cast(unsigned, best))), (int)pair_other((unsigned)arg));
+  if constexpr (PARTS > 1) {
+    __shared__ float best_sh[kWaves][32];
+    __shared__ int arg_sh[kWaves][32];
+    if (half == 0) {
+      best_sh[w][col] = best;
+      arg_sh[w][col] = arg;
+    }
+    __syncthreads();
+    if (w > 0) return;
+#pragma unroll
+    for (int o = 1; o < kWaves; ++o) combine(best_sh[o][col], arg_sh[o][col]);
+  }
+  const int ej = e0 + col;
+  if (half == 0 && ej < T) {
+    const bool keep = kept[ej - tile0] != 0;
+    nearest[(int64_t)d.unit * ws_stride + ej] = keep ? -1 : arg;
+    if (!keep) weight[(int64_t)d.unit * ws_stride + ej] = fmaxf(best * inv_e, 0.f);
   }
 }
 
@@ -373,12 +409,15 @@ void launch_t(hipStream_t s, const UnitDesc* descs, const int32_t* list, int n_l
               int64_t idx_stride, void* k_out, void* v_out, int32_t* nearest, float* weight, float* inv_norm,
               int64_t ws_stride) {
   typedef __bf16 T;
-  hipLaunchKernelGGL(merge_fill, dim3((max_t_in + kFillRows - 1) / kFillRows, n_list), dim3(kThreads), 0, s, descs, list, nearest,
-                     ws_stride);
-  hipLaunchKernelGGL(merge_mark<D>, dim3((max_out + kMarkRows - 1) / kMarkRows, n_list), dim3(kThreads), 0, s, descs, list,
-                     (const T*)k_out, kept_idx, idx_stride, nearest, inv_norm, ws_stride);
-  hipLaunchKernelGGL(merge_nearest<D>, dim3((max_t_in + kNearTile - 1) / kNearTile, n_list), dim3(kThreads), 0, s, descs,
-                     list, (const T*)k_in, (const T*)k_new, (const T*)k_out, N_k, inv_norm, nearest, weight, ws_stride);
+  hipLaunchKernelGGL(merge_norms<D>, dim3((max_out + kNormRows - 1) / kNormRows, n_list), dim3(kThreads), 0, s, descs, list,
+                     (const T*)k_out, inv_norm, ws_stride);
+#define HACK_NEAREST(PARTS_)                                                                                                   \
+  hipLaunchKernelGGL((merge_nearest<D, PARTS_>), dim3((max_t_in + kNearRows / PARTS_ - 1) / (kNearRows / PARTS_), n_list),     \
+                     dim3(kThreads), 0, s, descs, list, (const T*)k_in, (const T*)k_new, (const T*)k_out, N_k, kept_idx,       \
+                     idx_stride, inv_norm, nearest, weight, ws_stride)
+  if ((int64_t)((max_t_in + 31) / 32) * n_list <= kPartsGroups<D>) HACK_NEAREST(4);
+  else HACK_NEAREST(1);
+#undef HACK_NEAREST
   // list capacity of a wave of merge_apply: a quarter of the longest cache in whole 64-row steps, at most kScanPerWave
   const int cap = std::min(kScanPerWave, (max_t_in + 64 * kWaves - 1) / (64 * kWaves) * 64);
 #define HACK_APPLY(ROWS_)                                                                                                   \

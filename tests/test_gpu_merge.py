@@ -182,3 +182,34 @@ def test_merge_gives_the_same_bits_whatever_shares_the_launch():
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
     hk.check()
     hk.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("b", [1, 31, 33, 97, 128, 129, 260, 383, 500])
+def test_merge_of_few_units_shares_the_kept_rows_among_waves(d, b):
+    """One unit alone: every wave of a work-group meets a quarter of the kept rows (stages of 4 x 32, the last of them partly filled).
+    The same unit among 40: each wave meets all of them.  Same products, ties to the lower row in both: the same bits.  Kept rows
+    that repeat one another tie exactly, across the waves too; kept indices in no order are taken as they are."""
+    u = _u()
+    H, Nk, n = 40, 57, 472
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(7 + b)
+    off = np.arange(H, dtype=np.int64) * n
+    K, V = (torch.randn((H * n, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    K[0:n:5] = K[0]                                            # unit 0: every fifth cached key is the same
+    kn, vn = (torch.randn((1, H, Nk, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=n + Nk, max_queries=Nk)
+    kept = torch.stack([torch.randperm(n + Nk, generator=gen, device=u.DEV)[:b] for _ in range(H)]).int()
+    results = []
+    for active in (np.arange(H) < 1, np.ones(H, bool)):
+        k_out, v_out = (torch.zeros((H * 504, d), dtype=torch.bfloat16, device=u.DEV) for _ in range(2))
+        cin, cout = Cache(K, V, off, np.full(H, n, np.int32)), Cache(k_out, v_out, np.arange(H, dtype=np.int64) * 504, np.full(H, b, np.int32))
+        hk.compact(1, Nk, cin, kept, cout, kn, vn)
+        before = k_out.clone()
+        hk.merge(1, Nk, cin, kept, cout, kn, vn, active=active.astype(np.uint8))
+        torch.cuda.synchronize()
+        assert not torch.equal(k_out[:504], before[:504])
+        results.append((k_out[:504], v_out[:504]))
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+    hk.check()
+    hk.close()
