@@ -60,11 +60,12 @@ __device__ __forceinline__ int frag_off(int col, int half, int kk) {
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void hv_rowstats(
     const UnitDesc* __restrict__ descs, const __bf16* __restrict__ q, const __bf16* __restrict__ k_cache,
-    int N_k, float scale, float2* __restrict__ stats) {
+    int N_k, float scale, float2* __restrict__ stats, double* __restrict__ sigma) {
   using St = BlockStream<D, kWaves>;
   constexpr int KK = D / 16;
   __shared__ __attribute__((aligned(1024))) __bf16 ring[kRing][St::BLK];
   const UnitDesc d = descs[blockIdx.y];
+  if (blockIdx.x == 0 && threadIdx.x == 0) sigma[d.unit] = 0.0;   // pass 2 adds to it (a launch that cleared it cost 4 us)
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int q0 = blockIdx.x * kTile1 + w * (32 * kRB1);   // may lie past N_k: the wave still copies and synchronises
@@ -399,27 +400,21 @@ __global__ __launch_bounds__(kThreads, 2) void hv_colmoments(
   if (col == 0 && t0 < len) atomicAdd(&sigma[d.unit], acc);
 }
 
-__global__ void hv_zero(const UnitDesc* __restrict__ descs, int n, double* __restrict__ sigma) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) sigma[descs[i].unit] = 0.0;
-}
-
 }  // namespace
 
 void launch_head_variance(hipStream_t s, int head_dim, const UnitDesc* descs, int n_desc, int max_len, const void* q,
                           const void* k_cache, int N_k, float scale, float* stats, double* sigma) {
   if (n_desc <= 0) return;
   typedef __bf16 T;
-  hipLaunchKernelGGL(hv_zero, dim3((n_desc + 63) / 64), dim3(64), 0, s, descs, n_desc, sigma);
   const dim3 g1((N_k + kTile1 - 1) / kTile1, n_desc), g2((max_len + kTile2 - 1) / kTile2, n_desc);
   if (head_dim == 64) {
     hipLaunchKernelGGL(hv_rowstats<64>, g1, dim3(kThreads), 0, s, descs, (const T*)q, (const T*)k_cache, N_k, scale,
-                       (float2*)stats);
+                       (float2*)stats, sigma);
     hipLaunchKernelGGL(hv_colmoments<64>, g2, dim3(kThreads), 0, s, descs, (const T*)q, (const T*)k_cache, N_k, scale,
                        (const float2*)stats, sigma);
   } else {
     hipLaunchKernelGGL(hv_rowstats<128>, g1, dim3(kThreads), 0, s, descs, (const T*)q, (const T*)k_cache, N_k, scale,
-                       (float2*)stats);
+                       (float2*)stats, sigma);
     hipLaunchKernelGGL(hv_colmoments<128>, g2, dim3(kThreads), 0, s, descs, (const T*)q, (const T*)k_cache, N_k,
                        scale, (const float2*)stats, sigma);
   }
