@@ -283,12 +283,9 @@ hack_status hack_attn(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q,
  *      of the step compresses, and otherwise reads the kept rows where they lie
  *      while further work-groups of the launch move them.  In launches of few
  *      work items a work-group takes 16 of an item's queries.
- * A compressing step of a bf16 context whose units are short (up to 1024 keys, by
- * head_dim, number of units and queries; kept rows of a unit within a work-group's
- * LDS) hack_step does in one launch of its own: score, selection, compaction and
- * attention, probabilities summed in an order of its own, so that its outputs are
- * not the bits of hack_attn over the same rows.
- * The choice depends only on B * H, N_k and the context's head_dim.
+ * The choice between these depends only on B * H, N_k and the context's head_dim.
+ * Compressing steps of short units do not take part in it: see
+ * hack_kvcache_step_form.
  * Returns a negative hack_status for a NULL context or B, N_k < 1. */
 int32_t hack_attn_variant(const hack_ctx* ctx, int32_t B, int32_t N_k);
 
@@ -332,6 +329,11 @@ hack_status hack_kvcache_reset(hack_kvcache* c);
 /* Current state as a hack_cache; view->off/len point into c and stay valid
  * until the next hack_step / reset / destroy on c. */
 hack_status hack_kvcache_view(const hack_kvcache* c, hack_cache* view);
+/* The form of the step that led to the current state (reported, as hack_attn_variant,
+ * so that measurements can be attributed to a kernel): queries per work-group (16 to
+ * 256) of a compressing step that one launch serves; 0 where its stages are launches
+ * of their own, for the empty cache and for a NULL cache. */
+int32_t hack_kvcache_step_form(const hack_kvcache* c);
 
 /* One scale step for all units of a layer (Sec. 4.3: compression is applied
  * prior to the attention computation whenever a unit's cache exceeds its
@@ -343,7 +345,15 @@ hack_status hack_kvcache_view(const hack_kvcache* c, hack_cache* view);
  *     new rows in a launch of its own before it attends)
  *   kept_idx_opt DEVICE int32 [B*H, idx_stride] or NULL: receives the kept
  *     indices of compressing units (rows of other units untouched).
- * Errors: as the individual calls; HACK_ECAPACITY if a unit would outgrow its slab. */
+ * Errors: as the individual calls; HACK_ECAPACITY if a unit would outgrow its slab.
+ * A compressing step of a bf16 context whose units are short (up to 1024 keys, kept
+ * rows of a unit within a work-group's LDS) is one launch where that is the faster
+ * form: score, selection, compaction and attention by work-groups that serve one
+ * unit each.  Which steps take it depends on head_dim, the number of units and of
+ * queries, the longest compressing unit and the most rows a unit attends over.  Such
+ * a launch sums probabilities in an order of its own: kept rows and caches are the
+ * bits of the other form, outputs agree with it, and with hack_attn over the same
+ * rows, within the rounding of the probabilities and of the output to bf16. */
 hack_status hack_step(hack_ctx* ctx, hack_kvcache* cache, int32_t B,
                       int32_t N_k, const void* q, const void* k_new,
                       const void* v_new, const uint8_t* head_type,

@@ -23,7 +23,7 @@ EXPORTS = [
     "hack_create", "hack_destroy", "hack_strerror", "hack_last_error", "hack_check",
     "hack_score", "hack_select", "hack_compact", "hack_attn", "hack_attn_variant",
     "hack_kvcache_rows_required", "hack_kvcache_create", "hack_kvcache_destroy",
-    "hack_kvcache_reset", "hack_kvcache_view", "hack_step", "hack_head_variance",
+    "hack_kvcache_reset", "hack_kvcache_view", "hack_kvcache_step_form", "hack_step", "hack_head_variance",
     "hack_set_score_mode", "hack_get_score_mode", "hack_score_static", "hack_merge", "hack_step_final",
 ]
 
@@ -103,6 +103,8 @@ def load_library() -> C.CDLL:
     lib.hack_kvcache_destroy.restype = None
     lib.hack_kvcache_reset.argtypes = [vp]
     lib.hack_kvcache_view.argtypes = [vp, pcache]
+    lib.hack_kvcache_step_form.argtypes = [vp]
+    lib.hack_kvcache_step_form.restype = i32
     lib.hack_step.argtypes = [vp, vp, i32, i32, vp, vp, vp, pu8, pi32, i32, f32, vp, vp, i64, vp]
     for name in EXPORTS:
         fn = getattr(lib, name)
@@ -208,6 +210,10 @@ class ManagedCache:
         n = len(self.cap)
         return (np.frombuffer((C.c_int64 * n).from_address(s.off), np.int64).copy(),
                 np.frombuffer((C.c_int32 * n).from_address(s.len), np.int32).copy())
+
+    def step_form(self) -> int:
+        """Queries per work-group if one launch served the last step, else 0."""
+        return self.hack.lib.hack_kvcache_step_form(self.handle)
 
     def as_cache(self) -> Cache:
         off, ln = self.view()

@@ -1134,6 +1134,8 @@ extern "C" hack_status hack_kvcache_view(const hack_kvcache* c, hack_cache* view
   return HACK_OK;
 }
 
+extern "C" int32_t hack_kvcache_step_form(const hack_kvcache* c) { return c ? c->at->g[0].whole : 0; }
+
 namespace {
 
 // The units of a step that are launched together on one stream, before their tables are uploaded.

@@ -487,8 +487,9 @@ int whole_steps() {
           stub::launches.clear();
           stub::whole_launches.clear();
           CHECK(s.step_each(30, *budget, last == 1, 5, to) == HACK_OK && as_wanted());
+          CHECK(hack_kvcache_step_form(s.cache) == (stub::whole_launches.empty() ? 0 : 16));
         }
-        CHECK(before());
+        CHECK(before() && hack_kvcache_step_form(s.cache) == 0);
         stub::Graph g;
         stub::begin_capture(&g, kStream);
         CHECK(s.step_each(30, *budget, last == 1, 5, to) == HACK_OK);

@@ -48,6 +48,7 @@ def test_status_strings_and_null_handling():
     assert lib.hack_kvcache_rows_required(3, cap, ctypes.byref(rows)) == 0 and rows.value == 2 * (8 + 8 + 16)
     cap[1] = 0
     assert lib.hack_kvcache_rows_required(3, cap, ctypes.byref(rows)) == -1
+    assert lib.hack_kvcache_step_form(None) == 0
 
 
 def test_host_arrays_are_typed_pointers():

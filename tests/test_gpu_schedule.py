@@ -566,13 +566,16 @@ def test_outputs_stored_over_the_new_keys_or_values(dtype, over):
     (128, 1, [3, 210, 97, 202]),
     (128, 1, [3, 300, 300, 411]),       # two launches
 ])
-def test_short_units_score_and_select_in_one_launch(head_dim, B, sides_n):
+@pytest.mark.parametrize("attention", ["split", None])
+def test_short_units_score_and_select_in_one_launch(head_dim, B, sides_n, attention):
     """hack_step's kept lists for units around the sizes at which score and selection share a launch, against the single
     entry points (which never do): the same importance up to fp64 summation order, 1e-16 of a value whose float32
-    rounding decides, hence equal lists on random data.  The last step holds one unit of the largest size."""
+    rounding decides, hence equal lists on random data.  The last step holds one unit of the largest size.  With an attention
+    kernel asked for, attention has a launch of its own; otherwise it shares the launch too where that is the faster form."""
     from tests import gpu_util as u
     H = 8
-    hk = u.make_hack(heads=H, head_dim=head_dim, dtype="bf16", max_units=B * H, max_cache_len=sum(sides_n), max_queries=max(sides_n))
+    hk = u.make_hack(heads=H, head_dim=head_dim, dtype="bf16", max_units=B * H, max_cache_len=sum(sides_n), max_queries=max(sides_n),
+                     attention=attention)
     types = np.array([0, 1] * (H // 2), np.uint8)
     U = B * H
     caps = np.maximum(sum(sides_n[:3]) - 17 * np.arange(U) % 190, 30).astype(np.int32)   # unit 0 keeps everything until the last step
@@ -580,7 +583,7 @@ def test_short_units_score_and_select_in_one_launch(head_dim, B, sides_n):
     gen = torch.Generator(u.DEV)
     gen.manual_seed(sum(sides_n))
     scale, stride = float(np.float32(head_dim ** -0.5)), (sum(sides_n) + 63) // 64 * 64
-    lists = 0
+    lists, forms = 0, []
     for step, n in enumerate(sides_n):
         q, kn, vn = (torch.randn((B, H, n, head_dim), generator=gen, device=u.DEV).to(torch.bfloat16) for _ in range(3))
         before = mc.as_cache()
@@ -594,11 +597,13 @@ def test_short_units_score_and_select_in_one_launch(head_dim, B, sides_n):
         t_in = src.len + n
         ln = hk.select(B, imp, t_in, types, budget, 5, n, want)
         torch.cuda.synchronize()
+        forms.append(mc.step_form())
         for x in range(U):
             if budget[x] < t_in[x]:
                 lists += 1
                 assert torch.equal(kept[x, :ln[x]], want[x, :ln[x]]), (step, x)
     assert lists > U // 2
+    assert any(forms) == (attention is None and caps.max() <= 256), forms   # (longer lists of these do not fit a work-group)
     hk.check()
     mc.close()
     hk.close()
@@ -1151,10 +1156,7 @@ def test_short_steps_in_one_launch(d, H, n, L, keep, queries, with_pos):
     budget[whole] = 10**6
     kept_rows = np.minimum(budget, rows + n)
     compress = budget < rows + n
-    # the form that is under test: queries per work-group as the library's rule has them
-    groups = lambda m: H * -(-n // m)
-    form = 16 if groups(16) <= 224 else 32 if groups(32) <= 256 else next((m for m in (64, 128) if n > 144 and groups(m) <= 256), 256)
-    assert form == queries and (rows + n)[compress].max() == L + n and kept_rows.max() == keep
+    assert (rows + n)[compress].max() == L + n and kept_rows.max() == keep
     types = (np.arange(H) % 2).astype(np.uint8)
     scale, top = float(np.float32(d ** -0.5)), max(L, n)
     results = []
@@ -1174,6 +1176,7 @@ def test_short_steps_in_one_launch(d, H, n, L, keep, queries, with_pos):
             out = torch.full_like(q, 7.0) if over is None else x[over]
             hk.step(mc, x["q"], x["k"], x["v"], types, budget, 3, scale, out, kept_idx=kept)
             torch.cuda.synchronize()
+            assert mc.step_form() == (queries if attention is None else 0)      # the form that is under test
             off, ln = mc.view()
             assert list(ln) == list(kept_rows)
             got = [kept] + [t[o:o + m].clone() for t in (mc.k, mc.v) + ((mc.pos,) if with_pos else ()) for o, m in zip(off, ln)]
