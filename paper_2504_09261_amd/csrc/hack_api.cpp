@@ -1189,7 +1189,7 @@ int use_whole_step(const hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   // (a kernel that the environment asks for serves every step)
   if (ctx->cfg.dtype != HACK_BF16 || ctx->split_max_items >= 0 || ctx->attn_kernel != -1 || ctx->attn_stream != -1) return 0;
   if (u.n_comp == 0 || !u.merging.empty()) return 0;
-  return whole_step_queries(ctx->cfg.head_dim, (int)u.descs.size(), n.N_k, g.max_t, g.max_keys, ctx->lds_bytes);
+  return whole_step_queries(ctx->cfg.head_dim, (int)u.descs.size(), u.n_comp, n.N_k, g.max_t, g.max_keys, ctx->lds_bytes);
 }
 
 bool score_select_short(const UnitDesc& d) { return d.len_in + d.n_new <= kScoreSelectHalf; }

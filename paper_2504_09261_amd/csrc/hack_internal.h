@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "attn_plan.h"
 
 namespace hack {
@@ -90,25 +92,55 @@ inline size_t whole_step_region(int head_dim, int max_rows) {
 inline size_t whole_step_lds(int head_dim, int max_rows) {
   return whole_step_region(head_dim, max_rows) + (size_t)(max_rows + 31) / 32 * 32 * 4 + 18432;
 }
-// Queries per work-group of such a launch, 0 where launches of their own are the better form.  Work-groups of one unit repeat its scores and
-// selection, so a unit gets several only while each of them has a compute unit to itself; one for all of a unit's queries repeats nothing, and
-// its key splits need no merge at 256.  Measured, us a compressing step (queries per work-group), launches of their own / this; head_dim 64, units, queries,
-// keys: 60 of 64, 166 10.5 / 9.2 (16, 32), 27 of 100, 300 11.9 / 9.8 (16), 10.3 (32), 60 of 140, 250 11.6 / 11.0 (256), 11.2 (64), 60 of 169, 424 15.5 / 13.8 (64),
-// 120 of 256, 500 20.5 / 17.4 (128), 18.6 (256), 60 of 256, 562 19.4 / 16.9 (64), 480 of 140, 250 26.8 / 18.8 (256), 960 of 256, 562 104 / 87; 128: 32 of
-// 100, 250 13.9 / 11.2 (16), 128 of 100, 250 22.0 / 16.2 (256), 64 of 200, 480 21.0 / 19.4 (64), 512 of 256, 480 86 / 63.  More work-groups than compute
-// units, several a unit: 240 of 400, 700 30.9 / 36.2; many units of few queries, whose launches are short: 640 of 25, 60 14.6 / 16.1, head_dim 128, 512 of 36, 90
-// 18.3 / 20.6, 512 of 100, 250 35.0 / 34.8; few long units, whose scores would spread over more compute units: 16 of 300, 800 and 1000 15.8 / 15.0, 16.1 /
-// 16.2, 16 of 700, 1000 15.8 / 17.1, head_dim 128, 16 of 300, 700 and 1000 17.9 / 17.8, 18.2 / 19.5, 32 of 300, 1000 22.9 / 23.2, 64 of 300, 1000 26.3 / 24.4.
-inline int whole_step_queries(int head_dim, int n_units, int N_k, int max_t, int max_rows, int lds_bytes) {
-  if (max_t > kWholeStepKeys || max_t > 640 + 8 * n_units || whole_step_lds(head_dim, max_rows) > (size_t)lds_bytes) return 0;
-  const auto groups = [&](int queries) { return (int64_t)n_units * ((N_k + queries - 1) / queries); };
-  if (groups(16) <= 224) return 16;
-  if (groups(32) <= 256) return 32;
-  if (N_k > 144)
-    for (int queries : {64, 128})
-      if (groups(queries) <= 256) return queries;
-  if (groups(256) <= 256) return 256;
-  return N_k <= 256 && N_k > (head_dim == 64 ? 32 : 96) ? 256 : 0;
+// Queries per work-group of such a launch, 0 where launches of their own are the better form.  n_comp: compressing units, max_t: longest of them with
+// its new rows, max_rows: most rows a unit attends over.  An XCD (32 compute units) takes every eighth unit.
+//
+// Figures: us a compressing step, launches of their own / this; units of queries, keys, kept rows, all units alike unless said otherwise.
+//
+// Work-groups of one unit repeat its scores and selection, so a unit gets several only while each of them finds a compute unit of its XCD to itself.
+// (queries per work-group) head_dim 64: 4 of 462, 534, 236 13.6 / 12.7 (16), 60 of 64, 166, 102 10.5 / 9.2 (16, 32), 16 of 273, 345, 178 12.5 / 10.6 (32), 43 of
+// 134, 776, 81 16.4 / 14.2 (32), 63 of 172, 753, 364 20.8 / 17.7 (64), 42 of 599, 618, 287 19.7 / 17.6 (128); 128: 3 of 310, 318, 175 13.6 / 11.9 (16), 32 of 100,
+// 250, 100 13.9 / 11.2 (16), 59 of 142, 573, 256 23.1 / 20.4 (64).  A second round on an XCD costs what the first did: 3 of 567, 581, 95 (head_dim 128)
+// 14.6 / 27.5 (16: 36 work-groups on one XCD), 14.6 (32: 18); 27 of 277, 606, 71 (64) 14.5 / 22.8 (32: 36), 13.4 (64: 20).
+// With few queries or short lists one work-group for all of a unit's queries, which repeats and merges nothing, is as good as two or three: 90 of 84, 90, 37
+// (128) 12.0 (64), 10.3 (256), 142 of 125, 168, 92 (64) 11.0, 9.9; but 37 of 208, 492, 235 (128) 17.2, 20.5, 60 of 137, 403, 377 (64) 14.9, 17.6, 59 of 142, 573, 256 (128)
+// 20.4, 23.0.  For few units of many queries launches of their own are as fast, as attention alone fills the chip: in 64s 12 of 658, 688, 186 (128) 19.0 / 20.3,
+// 20 of 561, 600, 85 (128) 17.1 / 17.9, 27 of 277, 606, 71 (64) 14.5 / 13.4, over units of lengths of their own up to 40 units on average 1.02 of them at head_dim 128, 0.99 at
+// 64 (up to 300 queries 0.97), of more units 0.97; in 128s at head_dim 64 1.02 and 0.95.  Scores of few long units spread over more compute units in launches of
+// their own: 3 of 428, 647, 110 (128) 14.3 / 16.3, 4 of 446, 643, 256 (128) 15.7 / 17.4, 8 of 474, 613, 244 (128) 15.9 / 16.3, 2 of 412, 527, 256 (128) 14.8 / 15.6, 17 of
+// 17, 655, 256 (128) 15.7 / 17.2, 44 of 12, 891, 256 (128) 18.3 / 19.1, 6 of 392, 642, 158 (64) 13.1 / 13.6, 16 of 700, 1000 (64) 15.8 / 17.1.
+//
+// Beyond 256 units: one work-group a unit, in rounds.  A compute unit holds two of them at head_dim 64 up to 512 keys and 256 kept rows, otherwise one (LDS,
+// registers).  A round that is nearly empty costs as much here as in launches of their own, which wait for the same chains, so most steps gain whatever
+// the last round holds: 128, 264, 400, 512, 520 and 768 units of 256, 480, 144 42.7 / 39.3, 55.0 / 43.0, 65.4 / 49.6, 78.4 / 65.4, 99.9 / 79.4, of 256, 1000, 256 77.7 / 62.7,
+// 94.4 / 73.0, 98.2 / 84.3, 123 / 97, 151 / 120; 64, 264, 400, 520 and 960 of 140, 512, 256 25.7 / 21.8, 34.2 / 26.2, 43.1 / 37.2, 77.5 / 58.3, of 256, 562, 358 39.7 / 38.4, 47.9 / 43.2,
+// 63.8 / 60.1, 112 / 98.  Not so:
+// - 128, up to 256 keys, where attention of its own fills its tiles (up to 128 queries) or is short (few rows), unless few units score: 264, 400, 512, 520 and 768 of 100,
+//   250, 100 24.1 / 26.7, 28.1 / 28.8, 30.1 / 30.9, 35.0 / 42.1, 43.7 / 46.4, 520 of 200, 250, 60 38.0 / 42.7; 859 of 119, 143, 61 of which half compress 36.3 / 46.0; but 662 of 155, 248,
+//   195 of which 71 compress 62.3 / 45.3, 916 of 159, 204, 154 84.5 / 70.7, 298 of 121, 245, 218 of which 94 compress 28.0 / 23.4;
+// - 64, one work-group a compute unit though there are few keys: 264, 400, 520 and 960 of 256, 500, 300 29.2 / 34.5, 35.9 / 35.3, 48.0 / 51.5, 86.2 / 82.6; 1051 of 114, 318, 296 of
+//   which a quarter compress 34.9 / 47.8;
+// - 64, short units of few queries where most compress and the last round is at most half full: 520 of 100, 150, 45 18.6 / 19.8, 600 of 100, 200, 60 18.7 / 19.9, 1092 of
+//   39, 163, 96 29.1 / 31.0 (768 of 100, 200, 60 20.0 / 19.7, 597 of 86, 120, 94 of which half compress 22.6 / 15.1);
+// - few queries, whose launches are short: 640 of 25, 60 (64) 14.6 / 16.1, 512 of 36, 90 (128) 18.3 / 20.6.
+inline int whole_step_queries(int head_dim, int n_units, int n_comp, int N_k, int max_t, int max_rows, int lds_bytes) {
+  if (max_t > kWholeStepKeys || whole_step_lds(head_dim, max_rows) > (size_t)lds_bytes) return 0;
+  const int longest = head_dim == 64 ? (n_units > 8 ? 640 + 8 * n_units : 640) : n_units > 8 ? 640 + 8 * std::max(n_units - 32, 0) : 512;
+  if (max_t > longest) return 0;
+  const int per_xcd = (n_units + 7) / 8;
+  const auto groups = [&](int queries) { return (int64_t)per_xcd * ((N_k + queries - 1) / queries); };   // of the fullest XCD
+  if (groups(16) <= 28) return 16;
+  if (groups(32) <= 32) return 32;
+  if (N_k > 144 || (N_k > 64 && max_rows > (head_dim == 64 ? 256 : 192))) {
+    if (groups(64) <= 32) return n_units > 40 || (head_dim == 64 && N_k <= 300) ? 64 : 0;
+    if (groups(128) <= 32) return n_units > 40 || head_dim == 128 ? 128 : 0;
+  }
+  if (groups(256) <= 32) return 256;
+  if (N_k > 256 || N_k <= (head_dim == 64 ? 32 : 96)) return 0;
+  if (head_dim == 128) return max_t > 256 || (N_k > 128 && max_rows > 96) || n_comp <= 128 ? 256 : 0;
+  if (max_t <= 512 && max_rows > 256) return 0;
+  if (max_t <= 256 && N_k <= 112 && n_comp > 512 && (per_xcd - 1) % 64 < 32) return 0;
+  return 256;
 }
 struct GatherArgs {
   const int32_t* kept;     // [unit id, kept_stride] lists of the compressing units

@@ -509,15 +509,30 @@ int whole_steps() {
     CHECK(s.schedule());
     CHECK(std::find(stub::launches.begin(), stub::launches.end(), "step_whole") == stub::launches.end());
   }
-  // queries per work-group: sixteen while every work-group finds a compute unit, one work-group a unit at 256; nothing beyond the LDS
-  const auto q = [](int d, int units, int n, int t, int rows) { return whole_step_queries(d, units, n, t, rows, 163840); };
+  // queries per work-group: several work-groups a unit while each finds one of the 32 compute units of its XCD, which takes every eighth unit; one
+  // work-group a unit beyond; nothing beyond the LDS
+  const auto q = [](int d, int units, int n, int t, int rows, int comp = 1 << 20) {
+    return whole_step_queries(d, units, std::min(comp, units), n, t, rows, 163840);
+  };
   CHECK(q(64, 56, 64, 166, 100) == 16 && q(64, 57, 64, 166, 100) == 32 && q(64, 128, 64, 166, 100) == 32 && q(64, 129, 64, 166, 100) == 256);
   CHECK(q(64, 60, 144, 250, 100) == 256 && q(64, 60, 145, 250, 100) == 64 && q(64, 120, 256, 500, 300) == 128 && q(64, 256, 256, 500, 300) == 256);
+  CHECK(q(64, 60, 144, 400, 256) == 256 && q(64, 60, 144, 400, 257) == 64 && q(128, 60, 144, 400, 192) == 256 && q(128, 60, 144, 400, 193) == 64);
+  // few units hold many work-groups on few XCDs
+  CHECK(q(128, 3, 448, 500, 95) == 16 && q(128, 3, 449, 500, 95) == 32 && q(128, 8, 512, 512, 95) == 32 && q(128, 9, 256, 512, 95) == 32 && q(128, 9, 512, 600, 95) == 32);
+  CHECK(q(128, 9, 513, 600, 95) == 0 && q(64, 27, 256, 500, 71) == 32 && q(64, 27, 300, 500, 71) == 64 && q(64, 27, 301, 500, 71) == 0 && q(64, 40, 320, 500, 71) == 0 && q(64, 41, 320, 500, 71) == 64);
+  CHECK(q(128, 32, 600, 640, 71) == 128 && q(64, 32, 600, 640, 71) == 0 && q(64, 48, 600, 640, 71) == 128);
+  // more than 256 units: one work-group each, where the launch's own sizes do not make it the slower one
   CHECK(q(64, 960, 256, 562, 306) == 256 && q(64, 960, 257, 562, 306) == 0 && q(64, 960, 33, 80, 40) == 256 && q(64, 960, 32, 80, 40) == 0);
-  CHECK(q(128, 512, 97, 250, 140) == 256 && q(128, 512, 96, 250, 140) == 0 && q(128, 256, 36, 90, 60) == 256);
+  CHECK(q(128, 512, 97, 257, 140) == 256 && q(128, 512, 96, 257, 140) == 0 && q(128, 256, 36, 90, 60) == 256);
+  CHECK(q(128, 264, 128, 256, 256) == 0 && q(128, 264, 129, 256, 97) == 256 && q(128, 264, 129, 256, 96) == 0 && q(128, 264, 128, 256, 256, 128) == 256 && q(128, 264, 128, 256, 256, 129) == 0);
+  CHECK(q(64, 264, 256, 512, 256) == 256 && q(64, 264, 256, 512, 257) == 0 && q(64, 264, 256, 513, 257) == 256);
+  CHECK(q(64, 512, 100, 250, 150) == 256 && q(64, 513, 100, 250, 150) == 0 && q(64, 768, 100, 250, 150) == 0 && q(64, 769, 100, 250, 150) == 256);
+  CHECK(q(64, 520, 113, 250, 150) == 256 && q(64, 520, 100, 257, 150) == 256 && q(64, 1025, 100, 250, 150) == 0 && q(64, 600, 100, 250, 150, 513) == 0 && q(64, 600, 100, 250, 150, 512) == 256);
   CHECK(q(64, 60, 100, 1024, 300) > 0 && q(64, 60, 100, 1025, 300) == 0 && q(64, 16, 100, 768, 300) == 16 && q(64, 16, 100, 769, 300) == 0);
+  CHECK(q(64, 8, 100, 640, 300) == 16 && q(64, 8, 100, 641, 300) == 0 && q(128, 8, 100, 512, 200) == 16 && q(128, 8, 100, 513, 200) == 0);
+  CHECK(q(128, 32, 100, 640, 200) == 16 && q(128, 32, 100, 641, 200) == 0 && q(128, 64, 100, 896, 200) == 32 && q(128, 64, 100, 897, 200) == 0);
   CHECK(q(64, 60, 100, 600, 544) > 0 && q(64, 60, 100, 600, 560) == 0 && q(128, 60, 100, 300, 256) > 0 && q(128, 60, 100, 300, 288) == 0);
-  CHECK(whole_step_queries(64, 60, 100, 300, 100, 65536) == 0);
+  CHECK(whole_step_queries(64, 60, 60, 100, 300, 100, 65536) == 0);
   stub::lds_bytes = 256;
   return 0;
 }

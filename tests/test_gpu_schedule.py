@@ -1132,10 +1132,15 @@ def test_query_subset_variants_and_position_only_baseline():
 # (head_dim, heads, new rows, rows in front of them: longest, kept: most), and the queries per work-group that the step then has
 WHOLE_STEPS = [
     (64, 8, 17, 30, 20, 16), (64, 8, 96, 160, 255, 16), (64, 60, 65, 192, 100, 32), (64, 60, 146, 279, 280, 64), (64, 120, 150, 390, 300, 128),
-    (64, 60, 130, 110, 65, 256), (64, 300, 40, 30, 33, 256), (64, 257, 256, 256, 511, 256),
+    (64, 60, 130, 110, 65, 256), (64, 300, 40, 30, 33, 256), (64, 256, 256, 256, 511, 256),
     (64, 80, 40, 472, 320, 32), (64, 80, 40, 473, 321, 32), (64, 60, 100, 924, 544, 32),      # 512, 513 and 1024 keys; the most rows
     (128, 4, 15, 20, 16, 16), (128, 32, 90, 167, 128, 16), (128, 32, 120, 392, 256, 32), (128, 64, 150, 300, 200, 64), (128, 100, 256, 256, 250, 128),
-    (128, 300, 100, 150, 97, 256), (128, 60, 33, 900, 250, 16),
+    (128, 256, 100, 150, 97, 256), (128, 60, 33, 831, 250, 16),
+    (128, 300, 100, 157, 97, 256), (64, 300, 200, 57, 256, 256),                              # more than a work-group a compute unit
+    (64, 60, 140, 200, 257, 64), (128, 60, 135, 200, 193, 64),                                # long lists
+    (128, 3, 448, 40, 90, 16), (128, 3, 449, 40, 90, 32),                                     # all work-groups of a unit on one XCD
+    # launches of their own are the faster form
+    (128, 300, 100, 156, 97, 0), (64, 257, 256, 256, 511, 0), (64, 700, 100, 150, 120, 0), (64, 27, 301, 220, 71, 0), (128, 6, 300, 213, 90, 0),
 ]
 
 
