@@ -29,9 +29,10 @@ namespace {
 constexpr size_t kTableChunkBytes = 32u << 20;   // launch tables: one chunk (device memory + pinned mirror)
 constexpr size_t kTableLimitBytes = 1u << 30;    // ... and all chunks of a context together
 constexpr int kIotaRows = 32768;                 // rows a unit that keeps everything may have where its list is read
-// Polls (each an atomic round trip plus a short sleep, ~1 us) a score wave spends waiting for the
-// other items of its unit before it gives up; real waits last a few microseconds.
-constexpr int kScoreSpinLimit = 1 << 18;
+// Polls a score wave spends waiting for the other items of its unit before it gives up.  A poll, an atomic round trip and the shortest sleep,
+// takes 0.16 us (launches that give up after 4096 and 16384 polls: 695 and 2662 us), so the wait lasts 96 ms; real ones last a few
+// microseconds, longer only where other work keeps the unit's other work-groups from running.
+constexpr int kScoreSpinLimit = 600000;
 
 // Launch-table storage in device memory with a pinned host mirror.
 struct HipTableBackend {

@@ -928,6 +928,28 @@ def test_score_give_up_is_contained_reported_and_recovered(monkeypatch):
     hk.close()
 
 
+def test_a_score_waits_long_for_work_that_shares_the_device(monkeypatch):
+    """How long a fused score launch waits before it gives up and costs its context the fused form: a work-group withholds its
+    sums, and the default limit of polls has to last 80 ms (91 ms with the poll of 0.35 us that it was first chosen for)."""
+    u = _u()
+    monkeypatch.setenv("HACK_SCORE_TEST_SKIP_PUBLISH", "3")
+    hk = u.make_hack(heads=4, head_dim=64, dtype="bf16", max_units=4, max_cache_len=8192, max_queries=64)
+    monkeypatch.delenv("HACK_SCORE_TEST_SKIP_PUBLISH")
+    L = 8000
+    k = torch.ones((4 * L, 64), device=u.DEV, dtype=torch.bfloat16)
+    q = torch.ones((1, 4, 64, 64), device=u.DEV, dtype=torch.bfloat16)
+    imp = torch.empty((4, 8192), device=u.DEV)
+    begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    begin.record()
+    hk.score(q, Cache(k, k, np.arange(4, dtype=np.int64) * L, np.full(4, L, np.int32)), 0.05, imp)
+    end.record()
+    torch.cuda.synchronize()
+    with pytest.raises(HackError):
+        hk.check()
+    assert 80.0 < begin.elapsed_time(end) < 1000.0
+    hk.close()
+
+
 def test_score_two_pass_form_matches_fused_bit_for_bit_and_holds_any_number_of_items():
     """hack_set_score_mode: the two-pass form (no in-kernel waits) gives the same importance bit
     for bit, also where the fused form has to cut the work into several launches, and switching
