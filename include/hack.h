@@ -193,6 +193,14 @@ hack_status hack_score_static(hack_ctx* ctx, int32_t B, int32_t N_k, const void*
                               const uint8_t* active, float* importance,
                               int64_t imp_stride, hack_stream stream);
 
+/* Keys per wave (32 to 256) of the launches that hack_score and hack_score_static
+ * take for n units of t_in[i] keys, cached and new ones together (reported, as
+ * hack_attn_variant, so that measurements can be attributed to a kernel; units that
+ * hack_step scores and selects inside one work-group are another matter); 0 for fp32
+ * contexts, a negative hack_status for a NULL argument, n < 1 or keys outside
+ * [1, max_cache_len]. */
+int32_t hack_score_item_keys(const hack_ctx* ctx, int32_t n, const int32_t* t_in);
+
 /* ---- a2: budgeted selection per head class -----------------------------
  * Sec. 4.4, f_C and f_S.  For unit u with T = t_in[u], b = min(budget[u], T):
  *   contextual: the b keys of largest importance;

@@ -24,7 +24,7 @@ EXPORTS = [
     "hack_score", "hack_select", "hack_compact", "hack_attn", "hack_attn_variant",
     "hack_kvcache_rows_required", "hack_kvcache_create", "hack_kvcache_destroy",
     "hack_kvcache_reset", "hack_kvcache_view", "hack_kvcache_step_form", "hack_step", "hack_head_variance",
-    "hack_set_score_mode", "hack_get_score_mode", "hack_score_static", "hack_merge", "hack_step_final",
+    "hack_set_score_mode", "hack_get_score_mode", "hack_score_static", "hack_score_item_keys", "hack_merge", "hack_step_final",
 ]
 
 
@@ -89,6 +89,8 @@ def load_library() -> C.CDLL:
     lib.hack_get_score_mode.restype = i32
     lib.hack_score.argtypes = [vp, i32, i32, vp, pi32, i32, f32, pcache, vp, pu8, vp, i64, vp]
     lib.hack_score_static.argtypes = [vp, i32, i32, vp, pi32, i32, f32, pcache, vp, pu8, vp, i64, vp]
+    lib.hack_score_item_keys.argtypes = [vp, i32, pi32]
+    lib.hack_score_item_keys.restype = i32
     lib.hack_select.argtypes = [vp, i32, vp, i64, pi32, pu8, pi32, i32, i32, vp, i64, pi32, vp]
     lib.hack_compact.argtypes = [vp, i32, i32, pcache, vp, vp, i32, vp, i64, pcache, vp]
     lib.hack_merge.argtypes = [vp, i32, i32, pcache, vp, vp, vp, i64, pu8, pcache, vp]
@@ -298,6 +300,14 @@ class Hack:
         self._check(self.lib.hack_score_static(self.ctx, B, Nk, _dev(q), _p(qi, C.c_int32), n_obs, scale, C.byref(cs),
                                                _dev(k_new), _p(act, C.c_uint8), _dev(importance),
                                                importance.stride(0), _stream()))
+
+    def score_item_keys(self, t_in) -> int:
+        """Keys per wave of the launches that score units of t_in keys (bf16; 0 for fp32 contexts)."""
+        t = _i32(t_in)
+        v = int(self.lib.hack_score_item_keys(self.ctx, len(t), _p(t, C.c_int32)))
+        if v < 0:
+            self._check(v)
+        return v
 
     # ---- a2 ----
     def select(self, B: int, importance, t_in, head_type, budget, n_init: int, n_recent: int, kept_idx) -> np.ndarray:

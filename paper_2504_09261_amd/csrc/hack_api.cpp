@@ -85,6 +85,7 @@ struct hack_ctx {
   float* merge_inv = nullptr;    //   ... inverse key norms of the kept rows
   int* fault = nullptr;          // pinned, device-visible int[2]: [0] a score wave's bounded wait gave up (fatal),
                                  // [1] a logit exceeded the range the bf16 score kernel supports
+  int cus = 1;                   // compute units of the device
   int score_capacity[kScoreSizes] = {};   // bf16 path: score items one fused launch may hold (resident waves), by item size (kScoreItemKeys)
   int split_max_items = -1;      // launches with at most this many 32-query attention items use the key-split kernel (HACK_ATTN_SPLIT_ITEMS); -1 (default): see use_split_attention
   int attn_kernel = -1;          // bf16 kernel of the 128-query items (kAttnPlain ...); -1 (default): the deeper pipeline, keys in halves where use_key_halves says so
@@ -510,39 +511,52 @@ void build_score_items(const std::vector<UnitDesc>& descs, int n, int item_keys,
   group_begin->push_back((int)items->size());
 }
 
-// bf16: builds the score items of the first n units and returns the item size (keys per wave) chosen.
+// bf16: keys per score item (wave) for units of these many keys.
 // Smaller items spread a launch over more compute units and shorten every wave's serial tile work, so the
 // smallest size is taken whose items all fit one launch (the fused kernel's work-groups wait for each other
 // inside a launch, so a launch holds at most what the device keeps resident) and whose work-groups per unit the
 // exchange area supports; if no size fits one launch, the size that needs the fewest launches.  A wave's tiles take some 1.7 us each, one after
 // the other, hence sizes between the powers of two.  Without / with those of 96 and 192 keys, us a launch, head_dim 128: 32 units of 3543 or 5485
 // keys 16.8 / 15.2, of 4247 or 6189 17.2 / 15.9, 64 of 3883 or 7039 33.8 / 29.5; in two passes 26.0 / 23.0, 26.7 / 24.5, 48.0 / 43.5; 200 units of
-// 1200 or 1500, head_dim 64, 23.8 / 19.6.  The choice
-// does not depend on the score mode, so both modes (and the fixed-scratch entry point, which applies the same
+// 1200 or 1500, head_dim 64, 23.8 / 19.6.
+// At head_dim 64 a compute unit holds two work-groups of 128-key and 256-key items, three of 96-key and 192-key ones, four of 64-key ones, so items
+// of 192 keys spare a launch, or fit one, by putting a third work-group of many tiles on a compute unit; that takes as long as the launch spared.
+// They are taken instead of 256 where they spare a launch or put no more work-groups on a compute unit in the last one, and of no other
+// size; nor do single-tile items in two launches stand in for them.  Time of 192 over the other, graph replays, fused / two passes, launches and work-groups a
+// compute unit in the last one: 256 for 192, one launch, 2 for 2 0.82 / 0.82, 3 for 2 up to 1.10 / 1.11; two for three 0.70 to 0.80 / 0.80 to 0.86; two, 3 for 1 1.17 /
+// 1.15; three, 2 for 1 1.06 / 1.01; one launch against two of 64 0.96 to 1.02 / 1.12 to 1.17, two against three 1.09 to 1.14 / 1.18 to 1.24; one against
+// two of 96 0.96 / 1.07, two against three 1.10 to 1.30 / 1.12 to 1.31; two launches of 32 over two of 64 1.12 to 1.20 / 1.08 to 1.11.
+// The choice does not depend on the score mode, so both modes (and the fixed-scratch entry point, which applies the same
 // rule) group the keys alike and give the same bits.
 int choose_score_item_keys(const hack_ctx* ctx, std::vector<int> t_in) {
   std::stable_sort(t_in.begin(), t_in.end(), [](int a, int b) { return a > b; });   // the order build_score_items fills launches in
-  int best_keys = 0;
-  long best_launches = 0;
-  for (int i = 0; i < kScoreSizes; ++i) {
-    const int keys = kScoreItemKeys[i], cap = ctx->score_capacity[i];
-    if (cap <= 0) continue;
-    long launches = 1, in_launch = 0;
-    bool fits = true;
-    for (int t : t_in) {
-      const int wgs = ((t + keys - 1) / keys + 3) / 4;
-      if (wgs > score_max_groups()) { fits = false; break; }
-      if (in_launch + 4 * wgs > cap) { ++launches; in_launch = 0; }
-      in_launch += 4 * wgs;
+  struct Size { int keys; long launches, last; };   // last: work-groups of the last launch
+  auto choose = [&](bool others) {
+    Size best{256, 0, 0};
+    for (int i = 0; i < kScoreSizes; ++i) {
+      const int keys = kScoreItemKeys[i], cap = ctx->score_capacity[i] / 4;
+      if (cap <= 0 || (others && (keys == 192 || keys == 32))) continue;
+      Size x{keys, 1, 0};
+      bool fits = true;
+      for (int t : t_in) {
+        const int wgs = ((t + keys - 1) / keys + 3) / 4;
+        if (wgs > score_max_groups()) { fits = false; break; }
+        if (x.last + wgs > cap) { ++x.launches; x.last = 0; }
+        x.last += wgs;
+      }
+      if (!fits) continue;
+      if (x.launches <= 1) return x;
+      if (best.launches == 0 || x.launches < best.launches) best = x;
     }
-    if (!fits) continue;
-    if (launches <= 1) return keys;
-    if (best_keys == 0 || launches < best_launches) {
-      best_keys = keys;
-      best_launches = launches;
-    }
+    return best;
+  };
+  Size x = choose(false);
+  if (x.keys == 192 && ctx->cfg.head_dim == 64) {
+    const Size y = choose(true);
+    auto per_cu = [&](long groups) { return (groups + ctx->cus - 1) / ctx->cus; };
+    if (y.keys != 256 || (x.launches == y.launches && per_cu(x.last) > per_cu(y.last))) x = y;
   }
-  return best_keys ? best_keys : 256;
+  return x.keys;
 }
 
 // Builds the item list of the first n units for the size chosen: launch groups for the fused form, one group for the two-pass
@@ -697,6 +711,7 @@ extern "C" hack_status hack_create(hack_ctx** out, const hack_config* cfg) {
     // a unit's score items wait for each other inside one launch, so a launch may
     // hold at most as many items as the device keeps resident at once
     for (int i = 0; i < kScoreSizes; ++i) ctx->score_capacity[i] = score_fused_capacity(cfg->head_dim, kScoreItemKeys[i]);
+    if (hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, cfg->device) != hipSuccess || ctx->cus < 1) ctx->cus = 1;
     // the largest unit must fit one launch with the largest items
     const int per_unit = (cfg->max_cache_len + 255) / 256 + 3;
     if (ctx->score_capacity[kScoreSizes - 1] < per_unit || (per_unit + 3) / 4 > score_max_groups()) e = hipErrorInvalidConfiguration;
@@ -789,6 +804,14 @@ extern "C" hack_status hack_score(hack_ctx* ctx, int32_t B, int32_t N_k, const v
   HIP_TRY(ctx, hipGetLastError());
   return HACK_OK;
 } HACK_NO_THROW(ctx)
+
+extern "C" int32_t hack_score_item_keys(const hack_ctx* ctx, int32_t n, const int32_t* t_in) try {
+  if (!ctx || n < 1 || !t_in) return HACK_EINVAL;
+  if (ctx->cfg.dtype != HACK_BF16) return 0;
+  for (int i = 0; i < n; ++i)
+    if (t_in[i] < 1 || t_in[i] > ctx->cfg.max_cache_len) return HACK_EINVAL;
+  return choose_score_item_keys(ctx, std::vector<int>(t_in, t_in + n));
+} catch (...) { return HACK_EHIP; }
 
 // The same call for callers that cannot allocate (see hack.h): scratch in the library's fixed device array.
 extern "C" hack_status hack_score_static(hack_ctx* ctx, int32_t B, int32_t N_k, const void* q, const int32_t* q_idx,

@@ -639,6 +639,41 @@ int f32_workspace() {
 
 }  // namespace
 
+// Keys per score item: the smallest that fit one launch, otherwise those that need the fewest; at head_dim 64 items of 192 keys only in place of 256,
+// where they spare a launch or put no more work-groups on a compute unit in the last one.
+int score_items() {
+  hack_ctx* ctx[2] = {};
+  for (int i = 0; i < 2; ++i) {
+    hack_config cfg{0, 1, 64 << i, HACK_BF16, 1024, 8192, 64, 32};
+    CHECK(hack_create(&ctx[i], &cfg) == HACK_OK);
+  }
+  const auto keys = [&](int d, int n, int t, int n2 = 0, int t2 = 1) {   // n units of t keys, n2 of t2
+    std::vector<int32_t> ts(n, t);
+    ts.insert(ts.begin(), n2, t2);
+    return hack_score_item_keys(ctx[d == 128], n + n2, ts.data());
+  };
+  // head_dim 128: 512 work-groups a launch
+  CHECK(keys(128, 512, 128) == 32 && keys(128, 512, 129) == 64 && keys(128, 128, 1024) == 64 && keys(128, 128, 1025) == 96 && keys(128, 128, 1536) == 96);
+  CHECK(keys(128, 128, 1537) == 128 && keys(128, 128, 2048) == 128 && keys(128, 128, 2049) == 192 && keys(128, 128, 3072) == 192 && keys(128, 128, 3073) == 256);
+  CHECK(keys(128, 128, 4097) == 192 && keys(128, 513, 128) == 32 && keys(128, 513, 384) == 96 && keys(128, 400, 384, 112, 384) == 96);
+  // head_dim 64: 1280, 1024, 768, 512, 768 and 512
+  CHECK(keys(64, 256, 640) == 32 && keys(64, 256, 641) == 64 && keys(64, 256, 1024) == 64 && keys(64, 256, 1025) == 96 && keys(64, 256, 1152) == 96);
+  CHECK(keys(64, 128, 3072) == 192 && keys(64, 128, 3073) == 256 && keys(64, 129, 3072) == 256);      // 512, 640, 516 work-groups; 256: 384, 512, 387
+  CHECK(keys(64, 109, 4999) == 192);                                                                 // one launch for two
+  CHECK(keys(64, 100, 5776) == 192 && keys(64, 103, 6923) == 256 && keys(64, 130, 7182) == 192);      // 32 and 90, 270 and 210 in the last; two launches for three
+  CHECK(keys(64, 643, 781) == 256 && keys(64, 100, 7700) == 192);                                    // 3 for 1, 2 for 2 on a compute unit
+  CHECK(keys(64, 521, 484) == 64 && keys(64, 259, 1188) == 64 && keys(64, 562, 1040) == 64);          // not for 32 and 64
+  CHECK(keys(64, 100, 5147) == 96 && keys(64, 613, 1040) == 96);                                     // nor for 96
+  CHECK(keys(64, 16, 8192) == 32 && keys(64, 16, 8192, 1000, 32) == 32);
+  // the order of the units does not matter; what is refused
+  const int32_t a[] = {700, 300, 8000}, b[] = {8000, 700, 300}, bad[] = {5, 0}, large[] = {8193};
+  CHECK(hack_score_item_keys(ctx[0], 3, a) == hack_score_item_keys(ctx[0], 3, b));
+  CHECK(hack_score_item_keys(ctx[0], 2, bad) == HACK_EINVAL && hack_score_item_keys(ctx[0], 1, large) == HACK_EINVAL);
+  CHECK(hack_score_item_keys(ctx[0], 0, a) == HACK_EINVAL && hack_score_item_keys(ctx[0], 1, nullptr) == HACK_EINVAL);
+  for (hack_ctx* c : ctx) hack_destroy(c);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   int rc = 2;
@@ -654,6 +689,7 @@ int main(int argc, char** argv) {
   if (which == "attn_rule") rc = attn_rule();
   if (which == "f32_workspace") rc = f32_workspace();
   if (which == "whole_steps") rc = whole_steps();
+  if (which == "score_items") rc = score_items();
   if (rc == 0) printf("ok\n");
   return rc;
 }

@@ -160,7 +160,10 @@ hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuc
 namespace hack {
 
 int score_max_groups() { return 64; }
-int score_fused_capacity(int, int) { return 2048; }
+// as the kernels' registers and LDS have it on a device of 256 compute units
+int score_fused_capacity(int head_dim, int item_keys) {
+  return 1024 * (head_dim == 128 ? 2 : item_keys == 32 ? 5 : item_keys == 64 ? 4 : item_keys == 96 || item_keys == 192 ? 3 : 2);
+}
 int attn_stream_slots(int) { return 512; }
 int attn_split_q_tile_rows() { return 32; }
 int attn_f32_q_tile_rows(int n_units, int N_k) { return n_units * ((N_k + 15) / 16) <= kAttnF32SmallItems ? 16 : 32; }

@@ -49,6 +49,7 @@ def test_status_strings_and_null_handling():
     cap[1] = 0
     assert lib.hack_kvcache_rows_required(3, cap, ctypes.byref(rows)) == -1
     assert lib.hack_kvcache_step_form(None) == 0
+    assert lib.hack_score_item_keys(None, 1, cap) == -1
 
 
 def test_host_arrays_are_typed_pointers():

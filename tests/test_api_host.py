@@ -70,3 +70,7 @@ def test_keys_in_halves_only_where_most_work_items_are_long(check):
 
 def test_short_compressing_steps_take_one_launch(check):
     check("whole_steps")
+
+
+def test_score_item_sizes(check):
+    check("score_items")

@@ -310,10 +310,11 @@ def test_score_many_units_split_into_launch_groups_and_repeated_calls():
     hk.close()
 
 
-@pytest.mark.parametrize("d,longest", [(128, 2240), (128, 4800), (64, 4352), (64, 4800)])   # items of 96, 192, 96, 192 keys
-def test_score_items_of_three_and_six_tiles(d, longest):
-    """Item sizes between the powers of two, chosen where smaller items do not fit one launch: units that end on and around item, tile and
-    work-group boundaries, in one launch, in two passes and with fixed scratch (the same bits), against float64."""
+@pytest.mark.parametrize("d,longest,keys", [(128, 2400, 96), (128, 4800, 192), (64, 5000, 96), (64, 5500, 192), (64, 7000, 256)])
+def test_score_items_of_three_and_six_tiles(d, longest, keys):
+    """Item sizes between the powers of two, chosen where smaller items do not fit one launch (the last case: 256 keys where 192 would put a
+    third work-group on a compute unit): units that end on and around item, tile and work-group boundaries, in one launch, in two
+    passes and with fixed scratch (the same bits), against float64."""
     u = _u()
     H, Nk = 64, 40
     gen = torch.Generator(u.DEV)
@@ -329,6 +330,7 @@ def test_score_items_of_three_and_six_tiles(d, longest):
     K = torch.randn((int(off[-1]), d), generator=gen, device=u.DEV).bfloat16()
     scale = float(np.float32(d ** -0.5))
     hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=longest, max_queries=Nk)
+    assert hk.score_item_keys(t_in) == keys                    # the size that is under test
     src = Cache(K, K, off[:-1], lens)
     stride = (longest + 63) // 64 * 64
     imps = []
