@@ -501,9 +501,13 @@ void build_score_items(const std::vector<UnitDesc>& descs, int n, int item_keys,
   for (int i = 0; i < n; ++i) order[i] = i;
   auto t_in = [&](int pos) { return descs[pos].len_in + descs[pos].n_new; };
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return t_in(a) > t_in(b); });
+  auto groups = [&](int pos) { return ((t_in(pos) + item_keys - 1) / item_keys + 3) / 4; };   // 4 items per work-group, same unit
+  size_t n_items = 0;
+  for (int pos : order) n_items += 4 * groups(pos);
+  items->reserve(n_items);
   for (int pos : order) {
     const UnitDesc& d = descs[pos];
-    const int wgs = ((t_in(pos) + item_keys - 1) / item_keys + 3) / 4;  // 4 items per work-group, same unit
+    const int wgs = groups(pos);
     if ((int)items->size() - group_begin->back() + 4 * wgs > capacity) group_begin->push_back((int)items->size());
     for (int c = 0; c < 4 * wgs; ++c)
       items->push_back(ScoreItem{d.in_off, d.unit, d.len_in, t_in(pos), c, pos, wgs});
@@ -529,7 +533,14 @@ void build_score_items(const std::vector<UnitDesc>& descs, int n, int item_keys,
 // The choice does not depend on the score mode, so both modes (and the fixed-scratch entry point, which applies the same
 // rule) group the keys alike and give the same bits.
 int choose_score_item_keys(const hack_ctx* ctx, std::vector<int> t_in) {
-  std::stable_sort(t_in.begin(), t_in.end(), [](int a, int b) { return a > b; });   // the order build_score_items fills launches in
+  // lengths in the order build_score_items fills launches in, each with the number of its units (most units share a few lengths: six sizes over
+  // 609 units of two cost a call of hack_score 10 us one unit at a time)
+  std::sort(t_in.begin(), t_in.end(), [](int a, int b) { return a > b; });
+  std::vector<std::pair<int, long>> lengths;
+  for (int t : t_in) {
+    if (lengths.empty() || lengths.back().first != t) lengths.push_back({t, 0});
+    ++lengths.back().second;
+  }
   struct Size { int keys; long launches, last; };   // last: work-groups of the last launch
   auto choose = [&](bool others) {
     Size best{256, 0, 0};
@@ -538,11 +549,16 @@ int choose_score_item_keys(const hack_ctx* ctx, std::vector<int> t_in) {
       if (cap <= 0 || (others && (keys == 192 || keys == 32))) continue;
       Size x{keys, 1, 0};
       bool fits = true;
-      for (int t : t_in) {
-        const int wgs = ((t + keys - 1) / keys + 3) / 4;
-        if (wgs > score_max_groups()) { fits = false; break; }
-        if (x.last + wgs > cap) { ++x.launches; x.last = 0; }
-        x.last += wgs;
+      for (const auto& run : lengths) {
+        const long wgs = ((run.first + keys - 1) / keys + 3) / 4;
+        if (wgs > score_max_groups() || wgs > cap) { fits = false; break; }
+        long left = run.second;
+        while (left > (cap - x.last) / wgs) {
+          left -= (cap - x.last) / wgs;
+          ++x.launches;
+          x.last = 0;
+        }
+        x.last += left * wgs;
       }
       if (!fits) continue;
       if (x.launches <= 1) return x;

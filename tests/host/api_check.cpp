@@ -665,6 +665,29 @@ int score_items() {
   CHECK(keys(64, 521, 484) == 64 && keys(64, 259, 1188) == 64 && keys(64, 562, 1040) == 64);          // not for 32 and 64
   CHECK(keys(64, 100, 5147) == 96 && keys(64, 613, 1040) == 96);                                     // nor for 96
   CHECK(keys(64, 16, 8192) == 32 && keys(64, 16, 8192, 1000, 32) == 32);
+  // units of a few lengths, in any order: launches counted one unit at a time, as build_score_items fills them
+  unsigned seed = 1;
+  const auto rnd = [&](int n) { return (int)((seed = seed * 1664525u + 1013904223u) >> 8) % n; };
+  for (int rep = 0; rep < 400; ++rep) {
+    std::vector<int32_t> ts(1 + rnd(700));
+    int32_t some[5];
+    for (int32_t& t : some) t = 1 + rnd(rep % 2 ? 8192 : 900);
+    for (int32_t& t : ts) t = rep % 3 ? some[rnd(5)] : 1 + rnd(1200);
+    const int32_t got = hack_score_item_keys(ctx[1], (int)ts.size(), ts.data());
+    std::sort(ts.begin(), ts.end(), [](int a, int b) { return a > b; });
+    int want = 0, fewest = 1 << 30;
+    for (int k : {32, 64, 96, 128, 192, 256}) {
+      int launches = 1, in_launch = 0;
+      for (int t : ts) {
+        const int groups = ((t + k - 1) / k + 3) / 4;
+        if (in_launch + groups > 512) ++launches, in_launch = 0;
+        in_launch += groups;
+      }
+      if (launches < fewest) want = k, fewest = launches;
+      if (launches == 1) break;
+    }
+    CHECK(got == want);
+  }
   // the order of the units does not matter; what is refused
   const int32_t a[] = {700, 300, 8000}, b[] = {8000, 700, 300}, bad[] = {5, 0}, large[] = {8193};
   CHECK(hack_score_item_keys(ctx[0], 3, a) == hack_score_item_keys(ctx[0], 3, b));
