@@ -62,11 +62,18 @@ __device__ __forceinline__ float rows_sum(float v) {
 // GATHER (fuse == 0): keys are the rows the unit keeps, read in place through its list, whose entries are loaded a block
 // ahead; ga.n_moves further work-groups move those rows (as in the bf16 key-split kernel).  A step less one launch: the 680-token
 // schedule 130.9 -> 124.3 us; single compressing steps of 8 to 64 units, 78 to 414 keys, 0 to 2 us of 35 to 100 less.
-template <int D, int R, int NW, bool GATHER>
+// kCache: fuse == 0 is known, for hack_attn with 16 queries a work item.  Where the kernel does not know it, every key's row is looked for in two homes, and
+// rows to append are held through the loop: head_dim 128, 36 units of 3 queries over 1230 keys 34.8 -> 33.8 us, 34 of 2 over 2315 54.2 -> 53.4,
+// 200 random launches of 16 and 32 queries 0.98 of the time; with 32 queries it gains nothing (332 units of 17 over 757 keys 71.3 / 74.6).  The store
+// of one-block units without the merge, worth 10 to 20 % to those, still costs few long units 2 to 4 % (36 of 3 over 1230 without it 33.4).
+enum : int { kFuse = 0, kCache = 1, kGather = 2 };
+template <int D, int R, int NW, int MODE>
 __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
     const AttnItem* __restrict__ items, const float* __restrict__ q, const float* k_cache, const float* v_cache,
-    const float* k_new, const float* v_new, float* k_app, float* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k,
+    const float* k_new, const float* v_new, float* k_app, float* v_app, int32_t* pos_app, int pos_new, int may_fuse, int N_k,
     float scale, float* __restrict__ out, const UnitDesc* __restrict__ descs, GatherArgs ga) {
+  constexpr bool GATHER = MODE == kGather;
+  const int fuse = MODE == kFuse ? may_fuse : 0;
   constexpr int C = D / 16;          // 16-byte pieces of a K / Q row per lane
   constexpr int M = D / 64;          // 16-byte pieces of a V row per lane
   constexpr int QT = 16 * R;         // queries per work item
@@ -117,7 +124,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32(
   const int64_t cache0 = GATHER ? it.in_off : base;
   const int home = GATHER ? it.len_in : len_c;   // entries below are cached rows
   auto row_of = [&](const float* cache, const float* fresh, int x) -> const float* {
-    return x < home ? cache + (cache0 + x) * D : fresh + (new_row0 + (x - home)) * D;
+    if constexpr (MODE == kCache) return cache + (cache0 + x) * D;
+    else return x < home ? cache + (cache0 + x) * D : fresh + (new_row0 + (x - home)) * D;
   };
   floatx4 kf[C], vf[4][M];
   int xk = 0, xv[4];   // entries of the next K block, of this V block
@@ -302,7 +310,7 @@ template <int D, int R, int NW>
 void launch_gather_t(hipStream_t s, const UnitDesc* descs, const AttnItem* items, int n_items, const GatherArgs& g, const void* q,
                      const void* k_cache, const void* v_cache, int N_k, float scale, void* out) {
   typedef float T;
-  hipLaunchKernelGGL((attn_f32<D, R, NW, true>), dim3(n_items + g.n_moves), dim3(64 * NW), 0, s, items, (const T*)q,
+  hipLaunchKernelGGL((attn_f32<D, R, NW, kGather>), dim3(n_items + g.n_moves), dim3(64 * NW), 0, s, items, (const T*)q,
                      (const T*)k_cache, (const T*)v_cache, (const T*)g.k_new, (const T*)g.v_new, nullptr, nullptr, nullptr, 0, 0, N_k,
                      scale, (T*)out, descs, g);
 }
@@ -312,9 +320,18 @@ void launch_t(hipStream_t s, const AttnItem* items, int n_items, const void* q, 
               const void* k_new, const void* v_new, void* k_app, void* v_app, int32_t* pos_app, int pos_new, int fuse, int N_k,
               float scale, void* out) {
   typedef float T;
-  hipLaunchKernelGGL((attn_f32<D, R, NW, false>), dim3(n_items), dim3(64 * NW), 0, s, items, (const T*)q, (const T*)k_cache,
-                     (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app, pos_app, pos_new, fuse, N_k,
-                     scale, (T*)out, nullptr, GatherArgs{});
+#define HACK_ATTN(MODE_)                                                                                                             \
+  hipLaunchKernelGGL((attn_f32<D, R, NW, MODE_>), dim3(n_items), dim3(64 * NW), 0, s, items, (const T*)q, (const T*)k_cache,          \
+                     (const T*)v_cache, (const T*)k_new, (const T*)v_new, (T*)k_app, (T*)v_app, pos_app, pos_new, fuse, N_k,          \
+                     scale, (T*)out, nullptr, GatherArgs{})
+  if constexpr (R == 1) {
+    if (!fuse) {
+      HACK_ATTN(kCache);
+      return;
+    }
+  }
+  HACK_ATTN(kFuse);
+#undef HACK_ATTN
 }
 
 }  // namespace
