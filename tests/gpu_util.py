@@ -86,5 +86,38 @@ def make_hack(cfg_or_none=None, *, heads=None, head_dim=None, dtype=None, max_un
                 os.environ[k] = v
 
 
+def walked_keys(k, v, walkers: int, kind: str, scale: float):
+    """A unit's keys and values [n, d] for attention whose walkers (waves, key splits) take the 32-key blocks w, w + walkers, ...  Queries
+    have 4.0 in coordinate 0.  "grows" ("shrinks"): each block of a walk scores 14 nats (20 bits) above (below) the one before it, more than the 16 bits by
+    which a row's reference lies ahead, and values are scaled so that every block keeps its share of the outputs; "no start",
+    "one key", "no end": keys whose scores are -inf fill every walk's first block, everything but one key, the second half of the blocks."""
+    n = k.shape[0]
+    step = torch.arange(n, device=k.device) // 32 // walkers
+    last = int(step[-1])
+    assert last <= 4, "20 bits a block"
+    k, v = k * 0.25, v.clone()
+    if kind in ("grows", "shrinks"):
+        level = step if kind == "grows" else last - step
+        k[:, 0] = (level - 2) * 14 / (4.0 * scale)
+        v *= torch.exp2(20.0 * (last - level))[:, None]
+    elif kind == "no start":
+        k[:min(32 * walkers, n - 1), 0] = -torch.inf
+    elif kind == "one key":
+        k[torch.arange(n, device=k.device) != n // 2, 0] = -torch.inf
+    elif kind == "no end":
+        k[max(1, n // 64 * 32):, 0] = -torch.inf
+    return k.bfloat16(), v.bfloat16()
+
+
+def reference_moves(logits, walkers: int) -> int:
+    """How often a walk meets a block that scores more than 16 bits (11.1 nats) above what it has seen, for every query."""
+    n, moves = logits.shape[1], 0
+    tops = [logits[:, b:b + 32].amax(1) for b in range(0, n, 32)]
+    for w in range(walkers):
+        for x, y in zip(tops[w::walkers], tops[w + walkers::walkers]):
+            moves += bool((y - x > 11.1).all())
+    return moves
+
+
 # the verdict rules live with the oracle-side checker (pure numpy)
 from oracle.parity import kept_set_verdict, ranked_segment  # noqa: E402,F401

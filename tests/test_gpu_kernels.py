@@ -664,6 +664,49 @@ def test_key_split_attention_with_16_and_32_queries_a_work_group(d, U, Nk, lens)
     hk.close()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("waves,queries", [(4, 16), (4, 32), (8, 16), (8, 32)])
+def test_key_split_attention_moving_reference_and_minus_infinity(d, waves, queries):
+    """Scores that leave the room of a row's reference in every block of every wave, upwards and downwards, and first, last and all but one of
+    the blocks at -inf, in work-groups of four and eight waves and of 16 and 32 queries."""
+    u = _u()
+    U = {(4, 16): 12, (4, 32): 200 if d == 128 else 392, (8, 16): 12, (8, 32): 100 if d == 128 else 136}[waves, queries]
+    Nk, longest = 20, 32 * waves * 5
+    kinds = ["grows", "shrinks", "no start", "one key", "no end"]
+    some = [longest, longest - 1, longest - 31, 32 * waves * 2 + 1, 32 * waves + 33, 32 * waves]
+    lens = np.array([some[i // 5 % 6] for i in range(U)], np.int32)
+    off = np.concatenate([[0], np.cumsum((lens + 7) // 8 * 8)]).astype(np.int64)
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(d + waves + queries)
+    q = torch.randn((1, U, Nk, d), generator=gen, device=u.DEV)
+    q[..., 0] = 4.0
+    q = q.bfloat16()
+    scale = float(np.float32(d ** -0.5))
+    K, V = (torch.zeros((int(off[-1]), d), dtype=torch.bfloat16, device=u.DEV) for _ in range(2))
+    for h in range(U):
+        k, v = (torch.randn((int(lens[h]), d), generator=gen, device=u.DEV) for _ in range(2))
+        K[off[h]:off[h] + lens[h]], V[off[h]:off[h] + lens[h]] = u.walked_keys(k, v, waves, kinds[h % 5], scale)
+    hk = u.make_hack(heads=U, head_dim=d, dtype="bf16", max_units=U, max_cache_len=longest, max_queries=Nk, attention="split")
+    out = torch.full_like(q, 7.0)
+    hk.attn(q, Cache(K, V, off[:-1], lens), scale, out)
+    torch.cuda.synchronize()
+    moves = 0
+    for h in range(min(U, 60)):
+        k, v = (x[off[h]:off[h] + lens[h]].double() for x in (K, V))
+        logits = scale * (q[0, h].double() @ k.T.contiguous())
+        if h % 5 == 0:
+            got = u.reference_moves(logits, waves)
+            assert got == (int(lens[h]) + 31) // 32 - waves, (h, got)      # in every block but the first ones
+            moves += got
+        p = torch.softmax(logits, -1)
+        # every probability, their sum and the output carry 2^-9 each; float32 scores (of up to 42 nats) and sums are far below
+        bound = 3 * 2.0 ** -9 * (p @ v.abs()) * 1.02 + 1e-4
+        assert bool(((out[0, h].double() - p @ v).abs() <= bound).all()), (h, kinds[h % 5], int(lens[h]))
+    assert moves > 0
+    hk.check()
+    hk.close()
+
+
 # the forms of the 128-query kernel (halves: head_dim 128)
 TILE_FORMS = [(d, n, f) for d, n in ((64, 130), (128, 33), (128, 257)) for f in ("tile128", "stream", "halves") if d == 128 or f != "halves"]
 

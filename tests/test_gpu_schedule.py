@@ -1201,3 +1201,55 @@ def test_short_steps_in_one_launch(d, H, n, L, keep, queries, with_pos):
     # the first pass of either context saw the same inputs
     assert [a for a, _ in results] == [None, None, "split"]
     assert all(torch.equal(a, b) for a, b in zip(results[0][1], results[2][1]))
+
+
+# (head_dim, heads, new rows, rows in front of them), queries per work-group and key splits of the step
+WALKED_STEPS = [(64, 8, 40, 500, 16, 8), (64, 60, 65, 475, 32, 4), (64, 60, 146, 394, 64, 4), (64, 120, 150, 390, 128, 2), (64, 256, 256, 284, 256, 1),
+                (128, 8, 40, 210, 16, 8), (128, 32, 120, 130, 32, 4), (128, 64, 150, 100, 64, 4), (128, 120, 150, 100, 128, 2), (128, 256, 200, 50, 256, 1)]
+
+
+@pytest.mark.parametrize("d,H,n,L,queries,splits", WALKED_STEPS)
+def test_short_steps_in_one_launch_moving_reference_and_minus_infinity(d, H, n, L, queries, splits):
+    """Whole steps in one launch over scores that leave the room of a row's reference in every block of every key split, upwards and downwards
+    (units that lose a few rows), and over units that keep everything with first, last and all but one of the blocks at -inf."""
+    u = _u()
+    T = L + n
+    kinds = ["grows", "no start", "shrinks", "one key", "no end"]
+    walk = max(splits, -(-T // 160))        # blocks of one step of the data's walk, so that it has five steps at most
+    walk = (walk + splits - 1) // splits * splits
+    types, scale = (np.arange(H) % 2).astype(np.uint8), float(np.float32(d ** -0.5))
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(d + H)
+    k, v = (torch.zeros((1, H, T, d), dtype=torch.bfloat16, device=u.DEV) for _ in range(2))
+    budget = np.full(H, 10**6, np.int32)
+    for h in range(H):
+        kind = kinds[h % 5]
+        k[0, h], v[0, h] = u.walked_keys(*(torch.randn((T, d), generator=gen, device=u.DEV) for _ in range(2)), walk, kind, scale)
+        if kind in ("grows", "shrinks"):
+            budget[h] = T - 1 - h % 4
+    q0, q = (torch.randn((1, H, m, d), generator=gen, device=u.DEV) for m in (L, n))
+    q0[..., 0] = q[..., 0] = 4.0
+    q0, q = q0.bfloat16(), q.bfloat16()
+    for attention in (None, "split"):
+        hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=T, max_queries=max(L, n), attention=attention)
+        mc = hk.managed_cache(np.full(H, T, np.int32))
+        hk.step(mc, q0, k[:, :, :L].contiguous(), v[:, :, :L].contiguous(), types, np.full(H, 10**6, np.int32), 3, scale, torch.empty_like(q0))
+        out = torch.full_like(q, 7.0)
+        hk.step(mc, q, k[:, :, L:].contiguous(), v[:, :, L:].contiguous(), types, budget, 3, scale, out)
+        torch.cuda.synchronize()
+        assert mc.step_form() == (queries if attention is None else 0)
+        off, ln = mc.view()
+        assert list(ln) == list(np.minimum(budget, T))
+        moves = 0
+        for h in list(range(min(H, 20))) + [H - 1]:
+            ks, vs = (t[off[h]:off[h] + ln[h]].double() for t in (mc.k, mc.v))
+            logits = scale * (q[0, h].double() @ ks.T.contiguous())
+            if h % 5 == 0:
+                moves += u.reference_moves(logits, splits)
+            p = torch.softmax(logits, -1)
+            bound = 3 * 2.0 ** -9 * (p @ vs.abs()) * 1.02 + 1e-4   # probabilities, their sum and the output carry 2^-9 each
+            assert bool(((out[0, h].double() - p @ vs).abs() <= bound).all()), (attention, h, kinds[h % 5])
+        assert moves > 0 or T <= 32 * splits
+        hk.check()
+        mc.close()
+        hk.close()
