@@ -42,10 +42,6 @@ template <int D> __device__ __forceinline__ int swz_v(int r) { return D == 128 ?
 // swz_v16: V tiles read as operands of v_mfma_f32_16x16x32_bf16, whose transposing reads cover 8 rows x 32 bytes a phase.
 template <int D> __device__ __forceinline__ int swz_v16(int r) { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); }
 
-// The reference of a row's probabilities lies 2^15 above its running maximum, so that the exponent's top bit says that one of them
-// reached 2: float32 and bf16 keep their precision down to 2^-111 of the row's largest probability.
-constexpr float kRowHeadroom = 15.f;
-
 __device__ __forceinline__ unsigned lds_addr_of(const void* p) {
   return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
@@ -117,6 +113,16 @@ __device__ __forceinline__ float quad_max(float v) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   return pair_max(fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])));
+}
+// The larger value, NaN if either is: v_maximum3_f32 takes operands as they come, where fmaxf has results of matrix instructions and lane swaps
+// passed through a v_max of their own first (13 -> 7 instructions for the largest of a quad's 8 scores a lane).
+__device__ __forceinline__ float maximum(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ float quad_maximum(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned m = __builtin_bit_cast(unsigned, maximum(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])));
+  const auto s = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+  return maximum(__builtin_bit_cast(float, (unsigned)s[0]), __builtin_bit_cast(float, (unsigned)s[1]));
 }
 // the partner lane's value
 __device__ __forceinline__ unsigned pair_other(unsigned u) {

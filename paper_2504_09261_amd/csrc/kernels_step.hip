@@ -229,15 +229,21 @@ __global__ __launch_bounds__(64 * kNW, D == 64 && TILES <= 2 && NQ == 1 ? 4 : 2)
 #pragma unroll
           for (int j = 0; j < 8; ++j) pf[qt][j] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sc[j >> 2][qt][j & 3], c2, -mc[qt]));
       };
-      auto follow = [&](bool nothing_yet) {
+      {   // the reference is the largest score so far (see attn_split)
+        float m_new[NQ];
+        bool moved = false;
 #pragma unroll
         for (int qt = 0; qt < NQ; ++qt) {
           float mx = sc[0][qt][0];
 #pragma unroll
-          for (int j = 1; j < 8; ++j) mx = fmaxf(mx, sc[j >> 2][qt][j & 3]);
-          const float m_new = fmaxf(mc[qt], fmaf(quad_max(mx), c2, kRowHeadroom));
-          if (!nothing_yet) {
-            const float a = __builtin_amdgcn_exp2f(mc[qt] - m_new);
+          for (int j = 1; j < 8; ++j) mx = maximum(mx, sc[j >> 2][qt][j & 3]);
+          m_new[qt] = maximum(mc[qt], quad_maximum(mx) * c2);
+          moved |= m_new[qt] != mc[qt];
+        }
+        if (b != split && __any(moved)) {
+#pragma unroll
+          for (int qt = 0; qt < NQ; ++qt) {
+            const float a = __builtin_amdgcn_exp2f(mc[qt] - m_new[qt]);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               ls[qt][r] *= a;
@@ -245,25 +251,11 @@ __global__ __launch_bounds__(64 * kNW, D == 64 && TILES <= 2 && NQ == 1 ? 4 : 2)
               for (int mt = 0; mt < MT; ++mt) o[mt][qt][r] *= a;
             }
           }
-          mc[qt] = m_new;
         }
-      };
-      if (b == split) {
-        follow(true);
-        probs();
-      } else {
-        probs();
-        unsigned x = 0;
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) {
-          const uintx4 a = __builtin_bit_cast(uintx4, pf[qt]);
-          x |= a[0] | a[1] | a[2] | a[3];
-        }
-        if (__any(x & 0x40004000u)) {
-          follow(false);
-          probs();
-        }
+        for (int qt = 0; qt < NQ; ++qt) mc[qt] = m_new[qt];
       }
+      probs();
 #pragma unroll
       for (int qt = 0; qt < NQ; ++qt) ls[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qt], ls[qt], 0, 0, 0);
 #pragma unroll

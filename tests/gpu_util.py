@@ -88,8 +88,8 @@ def make_hack(cfg_or_none=None, *, heads=None, head_dim=None, dtype=None, max_un
 
 def walked_keys(k, v, walkers: int, kind: str, scale: float):
     """A unit's keys and values [n, d] for attention whose walkers (waves, key splits) take the 32-key blocks w, w + walkers, ...  Queries
-    have 4.0 in coordinate 0.  "grows" ("shrinks"): each block of a walk scores 14 nats (20 bits) above (below) the one before it, more than the 16 bits by
-    which a row's reference lies ahead, and values are scaled so that every block keeps its share of the outputs; "no start",
+    have 4.0 in coordinate 0.  "grows" ("shrinks"): each block of a walk scores 14 nats (20 bits) above (below) the one before it, and
+    values are scaled so that every block keeps its share of the outputs; "no start",
     "one key", "no end": keys whose scores are -inf fill every walk's first block, everything but one key, the second half of the blocks."""
     n = k.shape[0]
     step = torch.arange(n, device=k.device) // 32 // walkers
@@ -110,13 +110,33 @@ def walked_keys(k, v, walkers: int, kind: str, scale: float):
 
 
 def reference_moves(logits, walkers: int) -> int:
-    """How often a walk meets a block that scores more than 16 bits (11.1 nats) above what it has seen, for every query."""
+    """How often a walk meets a block that scores 16 bits (11.1 nats) and more above the one before it, for every query."""
     n, moves = logits.shape[1], 0
     tops = [logits[:, b:b + 32].amax(1) for b in range(0, n, 32)]
     for w in range(walkers):
         for x, y in zip(tops[w::walkers], tops[w + walkers::walkers]):
             moves += bool((y - x > 11.1).all())
     return moves
+
+
+def attention_with_rounded_probabilities(q, k, v, scale: float, walkers: int):
+    """softmax(scale q k^T) v in float64 but for the probabilities, which are rounded to bf16 in units of the largest score that their walk
+    (blocks w, w + walkers, ... of 32 keys) has met so far, and the output."""
+    s = scale * (q.double() @ k.double().T.contiguous())
+    parts = []
+    for w in range(min(walkers, (s.shape[1] + 31) // 32)):
+        m = torch.full_like(s[:, 0], -torch.inf)
+        l, o = torch.zeros_like(m), torch.zeros((s.shape[0], v.shape[1]), dtype=torch.float64, device=s.device)
+        for j in range(32 * w, s.shape[1], 32 * walkers):
+            x = s[:, j:j + 32]
+            new = torch.maximum(m, x.amax(1))
+            p, a = torch.exp(x - new[:, None]).bfloat16().double(), torch.exp(m - new)
+            l, o, m = l * a + p.sum(1), o * a[:, None] + p @ v[j:j + 32].double(), new
+        parts.append((m, l, o))
+    top = torch.stack([m for m, _, _ in parts]).amax(0)
+    f = [torch.exp(m - top) for m, _, _ in parts]
+    out = sum(x[:, None] * o for x, (_, _, o) in zip(f, parts)) / sum(x * l for x, (_, l, _) in zip(f, parts))[:, None]
+    return out.bfloat16()
 
 
 # the verdict rules live with the oracle-side checker (pure numpy)

@@ -667,8 +667,8 @@ def test_key_split_attention_with_16_and_32_queries_a_work_group(d, U, Nk, lens)
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("waves,queries", [(4, 16), (4, 32), (8, 16), (8, 32)])
 def test_key_split_attention_moving_reference_and_minus_infinity(d, waves, queries):
-    """Scores that leave the room of a row's reference in every block of every wave, upwards and downwards, and first, last and all but one of
-    the blocks at -inf, in work-groups of four and eight waves and of 16 and 32 queries."""
+    """Scores that rise and fall by 20 bits with every block of every wave, and first, last and all but one of the blocks at -inf, in
+    work-groups of four and eight waves and of 16 and 32 queries."""
     u = _u()
     U = {(4, 16): 12, (4, 32): 200 if d == 128 else 392, (8, 16): 12, (8, 32): 100 if d == 128 else 136}[waves, queries]
     Nk, longest = 20, 32 * waves * 5
@@ -704,6 +704,31 @@ def test_key_split_attention_moving_reference_and_minus_infinity(d, waves, queri
         assert bool(((out[0, h].double() - p @ v).abs() <= bound).all()), (h, kinds[h % 5], int(lens[h]))
     assert moves > 0
     hk.check()
+    hk.close()
+
+
+@pytest.mark.parametrize("d,T,waves", [(64, 640, 4), (128, 600, 4), (64, 1504, 8), (128, 1304, 8)])
+def test_key_split_attention_rounds_no_coarser_than_its_probabilities(d, T, waves):
+    """The error against float64 is that of probabilities rounded to bf16 in units of the largest score so far, each wave's largest one exactly.
+    (Rounded in units of the first block's scores, probabilities just below the largest lose up to a bit: 1.08 to 1.2 times the error.)"""
+    u = _u()
+    U, Nk = 8, 64
+    gen = torch.Generator(u.DEV)
+    gen.manual_seed(d + T)
+    q = (2 * torch.randn((1, U, Nk, d), generator=gen, device=u.DEV)).bfloat16()
+    K, V = (torch.randn((U * T, d), generator=gen, device=u.DEV).bfloat16() for _ in range(2))
+    scale = float(np.float32(d ** -0.5))
+    hk = u.make_hack(heads=U, head_dim=d, dtype="bf16", max_units=U, max_cache_len=T, max_queries=Nk, attention="split")
+    out = torch.full_like(q, 7.0)
+    hk.attn(q, Cache(K, V, np.arange(U, dtype=np.int64) * T, np.full(U, T, np.int32)), scale, out)
+    torch.cuda.synchronize()
+    off, as_rounded = 0.0, 0.0
+    for h in range(U):
+        k, v = K[h * T:(h + 1) * T], V[h * T:(h + 1) * T]
+        want = torch.softmax(scale * (q[0, h].double() @ k.double().T.contiguous()), -1) @ v.double()
+        off += float((out[0, h].double() - want).square().sum())
+        as_rounded += float((u.attention_with_rounded_probabilities(q[0, h], k, v, scale, waves).double() - want).square().sum())
+    assert off ** 0.5 < 1.02 * as_rounded ** 0.5       # the same roundings; float32 scores and sums are 2^-15 of them
     hk.close()
 
 

@@ -1210,8 +1210,7 @@ WALKED_STEPS = [(64, 8, 40, 500, 16, 8), (64, 60, 65, 475, 32, 4), (64, 60, 146,
 
 @pytest.mark.parametrize("d,H,n,L,queries,splits", WALKED_STEPS)
 def test_short_steps_in_one_launch_moving_reference_and_minus_infinity(d, H, n, L, queries, splits):
-    """Whole steps in one launch over scores that leave the room of a row's reference in every block of every key split, upwards and downwards
-    (units that lose a few rows), and over units that keep everything with first, last and all but one of the blocks at -inf."""
+    """Whole steps in one launch over scores that rise and fall by 20 bits with every block of every key split (units that lose a few rows), and over units that keep everything with first, last and all but one of the blocks at -inf."""
     u = _u()
     T = L + n
     kinds = ["grows", "no start", "shrinks", "one key", "no end"]
@@ -1253,3 +1252,31 @@ def test_short_steps_in_one_launch_moving_reference_and_minus_infinity(d, H, n, 
         hk.check()
         mc.close()
         hk.close()
+
+
+@pytest.mark.parametrize("d,H,n,L,queries,splits", [c for c in WALKED_STEPS if c[5] <= 4 and c[0] == 64])
+def test_short_steps_in_one_launch_round_no_coarser_than_their_probabilities(d, H, n, L, queries, splits):
+    """As of key-split attention: the error of a whole step against float64 is that of probabilities rounded to bf16 in units of the largest
+    score so far."""
+    u = _u()
+    scale, gen = float(np.float32(d ** -0.5)), torch.Generator(u.DEV)
+    gen.manual_seed(d + H)
+    hk = u.make_hack(heads=H, head_dim=d, dtype="bf16", max_units=H, max_cache_len=L + n, max_queries=max(L, n))
+    mc = hk.managed_cache(np.full(H, L + n, np.int32))
+    types = (np.arange(H) % 2).astype(np.uint8)
+    k0, v0, q, kn, vn = (torch.randn((1, H, m, d), generator=gen, device=u.DEV).bfloat16() for m in (L, L, n, n, n))
+    q = 2 * q
+    hk.step(mc, k0, k0, v0, types, np.full(H, 10**6, np.int32), 3, scale, torch.empty_like(k0))
+    out = torch.full_like(q, 7.0)
+    hk.step(mc, q, kn, vn, types, np.full(H, L + n - 10, np.int32), 3, scale, out)
+    torch.cuda.synchronize()
+    assert mc.step_form() == queries
+    view, off, as_rounded = mc.view(), 0.0, 0.0
+    for h in range(8):
+        k, v = (t[view[0][h]:view[0][h] + view[1][h]] for t in (mc.k, mc.v))
+        want = torch.softmax(scale * (q[0, h].double() @ k.double().T.contiguous()), -1) @ v.double()
+        off += float((out[0, h].double() - want).square().sum())
+        as_rounded += float((u.attention_with_rounded_probabilities(q[0, h], k, v, scale, splits).double() - want).square().sum())
+    assert off ** 0.5 < 1.02 * as_rounded ** 0.5
+    mc.close()
+    hk.close()
