@@ -1240,11 +1240,15 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   AttnStreamPlan plan;
   std::vector<AttnItem> items;
   std::vector<ScoreItem> sitems;
-  g->attn_kernel = ctx->attn_kernel == kAttnPlain ? kAttnPlain : kAttnPipe;
-  if (!n.split && !shared && use_key_halves(ctx, u.descs, n.N_k, &items)) g->attn_kernel = kAttnHalves;
-  g->streamed = !n.split && g->attn_kernel != kAttnHalves && use_stream_attention(ctx, u.descs, n.N_k, shared, &items, &plan);
-  if (g->streamed) items.clear();
-  else if (items.empty()) build_attn_items(u.descs, n.N_k, n.tile, &items);
+  // (a launch that does the whole step needs no work items, and no moves: outputs over its inputs have the rows moved by the launch that scores)
+  g->whole = shared ? 0 : use_whole_step(ctx, u, n, *g);
+  if (!g->whole) {
+    g->attn_kernel = ctx->attn_kernel == kAttnPlain ? kAttnPlain : kAttnPipe;
+    if (!n.split && !shared && use_key_halves(ctx, u.descs, n.N_k, &items)) g->attn_kernel = kAttnHalves;
+    g->streamed = !n.split && g->attn_kernel != kAttnHalves && use_stream_attention(ctx, u.descs, n.N_k, shared, &items, &plan);
+    if (g->streamed) items.clear();
+    else if (items.empty()) build_attn_items(u.descs, n.N_k, n.tile, &items);
+  }
   g->small = ctx->cfg.dtype == HACK_BF16 ? use_score_select(ctx->cfg.head_dim, u.n_comp, g->max_t)
                                          : use_score_select_f32(ctx->cfg.head_dim, u.n_comp, g->max_t);
   if (ctx->cfg.dtype == HACK_BF16 && u.n_comp > 0 && !g->small)
@@ -1252,7 +1256,7 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
   // The key-split and the float32 kernel read the rows in place unless they change on the way (merge) or a unit's cache is longer than
   // the list of a unit that keeps everything.
   std::vector<MoveItem> moves;
-  g->gathered = (n.split || ctx->cfg.dtype == HACK_F32) && !n.fuse_append && u.merging.empty();
+  g->gathered = !g->whole && (n.split || ctx->cfg.dtype == HACK_F32) && !n.fuse_append && u.merging.empty();
   for (const UnitDesc& d : u.descs) g->gathered = g->gathered && (d.mode == MOVE_GATHER || d.n_out <= kIotaRows);
   if (g->gathered)
     for (size_t i = 0; i < u.descs.size(); ++i)
@@ -1262,7 +1266,6 @@ hack_status upload_group(hack_ctx* ctx, const GroupUnits& u, const StepNode& n, 
     while (g->n_short < u.n_comp && score_select_short(u.descs[g->n_short])) ++g->n_short;
     if (!split_score_select(u.n_comp, g->n_short, g->gathered ? 0 : (int)u.descs.size() - u.n_comp)) g->n_short = 0;
   }
-  g->whole = shared ? 0 : use_whole_step(ctx, u, n, *g);
   g->n_moves = (int)moves.size();
   g->n_desc = (int)u.descs.size();
   g->n_comp = u.n_comp;
@@ -1325,11 +1328,14 @@ void launch_group_attention(hack_ctx* ctx, const StepNode& n, const StepGroup& g
   const AttnItem* items = reinterpret_cast<const AttnItem*>(g.dev + g.o_items);
   const bool append = n.fuse_append && a.in_place;
   const bool eight = n.split && attn_split_in_eight(ctx->cfg.head_dim, g.n_items, g.n_desc, g.max_keys);
-  if (g.whole || (g.gathered && a.in_place)) {
-    GatherArgs ga{a.kept, a.kstride, ctx->seam, ctx->iota, reinterpret_cast<const MoveItem*>(g.dev + g.o_moves), g.n_moves,
-                  a.pos_new, a.k_new, a.v_new, a.cp, eight, WholeStep{}};
-    if (g.whole)
-      ga.whole = WholeStep{g.n_desc, g.max_t, g.max_keys, g.whole, n.n_obs, reinterpret_cast<const int32_t*>(g.dev + g.o_rows), ctx->fault, !a.apart, 0};
+  if (g.whole) {
+    const WholeStep st{g.n_desc, g.max_t, g.max_keys, g.whole, n.n_obs, reinterpret_cast<const int32_t*>(g.dev + g.o_rows), ctx->fault, !a.apart, 0};
+    launch_step_units(s, ctx->cfg.head_dim, g.ddev(), st, a.q, a.cp, a.k_new, a.v_new, a.pos_new, n.N_k, a.scale, a.out, a.kept, a.kstride);
+    return;
+  }
+  if (g.gathered && a.in_place) {
+    const GatherArgs ga{a.kept, a.kstride, ctx->seam, ctx->iota, reinterpret_cast<const MoveItem*>(g.dev + g.o_moves), g.n_moves,
+                        a.pos_new, a.k_new, a.v_new, a.cp, eight};
     if (ctx->cfg.dtype == HACK_F32)
       launch_attn_f32_gather(s, ctx->cfg.head_dim, g.ddev(), items, g.n_items, n.tile, ga, a.q, a.cp.k, a.cp.v, n.N_k, a.scale, a.out);
     else

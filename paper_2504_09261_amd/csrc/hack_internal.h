@@ -74,7 +74,7 @@ struct alignas(8) MoveItem {
 // A whole compressing step of short units in one launch (launch_step_units): every work-group scores and selects for its unit, holds the rows
 // that the unit keeps in LDS, moves a share of them and attends for its queries.
 struct WholeStep {
-  int32_t n_units;          // 0: not such a step
+  int32_t n_units;
   int32_t max_t, max_rows;  // longest compressing unit with its new rows (at most kWholeStepKeys), most rows a unit attends over
   int32_t queries;          // per work-group: 16, 32, 64, 128 or 256
   int32_t n_obs;
@@ -154,7 +154,6 @@ struct GatherArgs {
   const void* v_new;
   CachePtrs cache;         // written by the moving work-groups
   bool eight;              // bf16: eight waves a work-group (attn_split_in_eight)
-  WholeStep whole;
 };
 
 // fp32 score: keys per work-group of a launch over n_list units of up to max_t_in keys (see kernels_score.hip for the line
@@ -356,9 +355,9 @@ void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const
                        const void* q, const void* k_cache, const void* v_cache, const void* k_new, const void* v_new,
                        void* k_app, void* v_app, int32_t* pos_app, int pos_new, bool append, bool eight, int N_k, float scale,
                        void* out);
-// A whole step (see WholeStep); reached through launch_attn_split_gather, whose arguments it takes.
-void launch_step_units(hipStream_t s, int head_dim, const UnitDesc* descs, WholeStep st, const GatherArgs& g, const void* q, const void* k_cache,
-                       const void* v_cache, int N_k, float scale, void* out);
+// A whole step (see WholeStep); kept: the lists of the compressing units are left there too, [unit id, kept_stride].
+void launch_step_units(hipStream_t s, int head_dim, const UnitDesc* descs, WholeStep st, const void* q, const CachePtrs& cache, const void* k_new,
+                       const void* v_new, int pos_new, int N_k, float scale, void* out, int32_t* kept, int64_t kept_stride);
 // Attention variance of the listed units (bf16): sigma[desc.unit] = sum over the
 // unit's n_out keys of the population variance, across its N_k queries, of the
 // softmax probabilities.  stats: workspace of 2 floats per (unit, query).

@@ -532,10 +532,6 @@ void launch_attn_split(hipStream_t s, int head_dim, const UnitDesc* descs, const
 void launch_attn_split_gather(hipStream_t s, int head_dim, const UnitDesc* descs, const AttnItem* items, int n_items,
                               const GatherArgs& g, const void* q, const void* k_cache, const void* v_cache, int N_k,
                               float scale, void* out) {
-  if (g.whole.n_units > 0) {
-    launch_step_units(s, head_dim, descs, g.whole, g, q, k_cache, v_cache, N_k, scale, out);
-    return;
-  }
   if (n_items + g.n_moves <= 0) return;
   typedef __bf16 T;
 #define HACK_ARGS s, g.eight, n_items, g.n_moves, descs, items, (const T*)q, (const T*)k_cache, (const T*)v_cache, (const T*)nullptr, (const T*)nullptr, \

@@ -337,16 +337,16 @@ __global__ __launch_bounds__(64 * kNW, D == 64 && TILES <= 2 && NQ == 1 ? 4 : 2)
 
 }  // namespace
 
-void launch_step_units(hipStream_t s, int head_dim, const UnitDesc* descs, WholeStep st, const GatherArgs& g, const void* q, const void* k_cache,
-                       const void* v_cache, int N_k, float scale, void* out) {
+void launch_step_units(hipStream_t s, int head_dim, const UnitDesc* descs, WholeStep st, const void* q, const CachePtrs& cache, const void* k_new,
+                       const void* v_new, int pos_new, int N_k, float scale, void* out, int32_t* kept, int64_t kept_stride) {
   typedef __bf16 T;
   const int rows = (st.max_rows + 31) / 32 * 32;
   st.region = (int)whole_step_region(head_dim, st.max_rows);
   const dim3 grid(8 * ((N_k + st.queries - 1) / st.queries), (st.n_units + 7) / 8);
   const size_t lds = st.region + rows * 4;
-#define HACK_STEP(D_, T_, Q_, S_)                                                                                                               \
-  hipLaunchKernelGGL((step_units<D_, T_, Q_, S_>), grid, dim3(64 * kNW), lds, s, descs, (const T*)q, st.q_rows, (const T*)k_cache, (const T*)v_cache, \
-                     (const T*)g.k_new, (const T*)g.v_new, st, g.cache, g.pos_new, N_k, scale, (T*)out, const_cast<int32_t*>(g.kept), g.kept_stride)
+#define HACK_STEP(D_, T_, Q_, S_)                                                                                                              \
+  hipLaunchKernelGGL((step_units<D_, T_, Q_, S_>), grid, dim3(64 * kNW), lds, s, descs, (const T*)q, st.q_rows, (const T*)cache.k, (const T*)cache.v, \
+                     (const T*)k_new, (const T*)v_new, st, cache, pos_new, N_k, scale, (T*)out, kept, kept_stride)
 #define HACK_STEP_Q(D_, T_)                                \
   switch (st.queries) {                                    \
     case 16: HACK_STEP(D_, T_, 1, 8); break;               \

@@ -487,7 +487,9 @@ int whole_steps() {
           stub::launches.clear();
           stub::whole_launches.clear();
           CHECK(s.step_each(30, *budget, last == 1, 5, to) == HACK_OK && as_wanted());
+          const StepGroup& group = s.cache->at->g[0];
           CHECK(hack_kvcache_step_form(s.cache) == (stub::whole_launches.empty() ? 0 : 16));
+          CHECK((group.whole == 0) == (group.n_items > 0) && (group.whole == 0 || group.n_moves == 0));   // nothing planned that no launch reads
         }
         CHECK(before() && hack_kvcache_step_form(s.cache) == 0);
         stub::Graph g;

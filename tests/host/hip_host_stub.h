@@ -233,17 +233,16 @@ void launch_attn_split(hipStream_t s, int, const UnitDesc*, const AttnItem* it, 
 }
 void launch_attn_split_gather(hipStream_t s, int, const UnitDesc* descs, const AttnItem* it, int n, const GatherArgs& g, const void*,
                               const void*, const void*, int, float, void*) {
-  if (g.whole.n_units > 0) {
-    stub::launch(g.whole.moved ? "attend_whole" : "step_whole", s, descs, nullptr, g.whole.n_units);
-    stub::Quiet q;
-    const WholeStep w = g.whole;
-    stub::submit(s, [=] { stub::whole_launches.push_back({w, std::vector<UnitDesc>(descs, descs + w.n_units)}); });
-    return;
-  }
   stub::launch_items("attn_split_gather", s, it, n);
   stub::Quiet q;
   const bool eight = g.eight;
   stub::submit(s, [=] { stub::waves.push_back(eight ? 8 : 4); });
+}
+void launch_step_units(hipStream_t s, int, const UnitDesc* descs, WholeStep w, const void*, const CachePtrs&, const void*, const void*, int, int, float,
+                       void*, int32_t*, int64_t) {
+  stub::launch(w.moved ? "attend_whole" : "step_whole", s, descs, nullptr, w.n_units);
+  stub::Quiet q;
+  stub::submit(s, [=] { stub::whole_launches.push_back({w, std::vector<UnitDesc>(descs, descs + w.n_units)}); });
 }
 void launch_attn_f32(hipStream_t s, int, const AttnItem* it, int n, int, const void*, const void*, const void*, const void*, const void*,
                      void*, void*, int32_t*, int, int fuse, int, float, void*) {
