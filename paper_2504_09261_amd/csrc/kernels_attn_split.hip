@@ -41,6 +41,7 @@
 
 #include "device_util.h"
 #include "hack_internal.h"
+#include "split_stage.h"
 
 namespace hack {
 
@@ -254,31 +255,8 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     }
   }
 
-  floatx4 o[MT][NQ];       // O^T: head-dim 16 mt + 4 g + r, query 16 qt + col
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) o[mt][qt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  floatx4 ls[NQ];          // row sums of P: all four rows hold the same
-  float mc[NQ];            // probabilities are 2^(c2 s - mc); finite from the start, so that keys whose score is -inf get 0
-#pragma unroll
-  for (int qt = 0; qt < NQ; ++qt) {
-    ls[qt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    mc[qt] = -FLT_MAX;
-  }
-  const float c2 = scale * kLog2eF;
-  bf16x8 ones;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.0f;
-
-  int k_off[KC];   // K operand: row 16 kt + col, chunk 4 c + g
-#pragma unroll
-  for (int c = 0; c < KC; ++c) k_off[c] = col * D + (((4 * c + g) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
-  const int e = col >> 2, qd = col & 3;
-  int v_off[MT];   // V^T operand: rows 4 g + e and 16 + 4 g + e, head-dim 16 mt + 4 qd
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-    v_off[mt] = (4 * g + e) * D + (((2 * mt + (qd >> 1)) ^ swz_v16<D>(4 * g + e)) & (CPR - 1)) * 8 + 4 * (qd & 1);
+  SplitStage<D, NQ> att;
+  att.init(scale, lane);
 
   // The queries and the first K block have landed; what was issued behind them, the first V block and the rows to append, may still be
   // on its way.  A wave that has issued fewer copies (a ragged block, a share of the only block, none) waits for all of them.
@@ -291,83 +269,8 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
-    for (int c = 0; c < KC; ++c) qf[qt][c] = *reinterpret_cast<const bf16x8*>(&q_sh[16 * qt * D + k_off[c]]);
+    for (int c = 0; c < KC; ++c) qf[qt][c] = *reinterpret_cast<const bf16x8*>(&q_sh[16 * qt * D + att.k_off[c]]);
 
-  // Scores of a block: sc[kt][qt], keys 16 kt + 4 g + r, query 16 qt + col.
-  auto scores = [&](const __bf16* Kt, floatx4 (&sc)[2][NQ]) {
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int qt = 0; qt < NQ; ++qt) sc[kt][qt] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < KC; ++c)
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kt[16 * kt * D + k_off[c]]);
-#pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) sc[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[qt][c], sc[kt][qt], 0, 0, 0);
-      }
-  };
-  auto mask = [&](floatx4 (&sc)[2][NQ], int b) {   // keys past the end
-    if ((b + 1) * kKB > total) {
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (b * kKB + 16 * kt + 4 * g + r >= total) {
-#pragma unroll
-            for (int qt = 0; qt < NQ; ++qt) sc[kt][qt][r] = -INFINITY;
-          }
-    }
-  };
-  // Probabilities of a block in the order of the B operand of the PV product: element j of lane group g is key 4 g + j (j < 4) or
-  // 16 + 4 g + j - 4, and the V^T operand is read in the same order.
-  auto probs = [&](const floatx4 (&sc)[2][NQ], bf16x8 (&pf)[NQ]) {
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) pf[qt][j] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sc[j >> 2][qt][j & 3], c2, -mc[qt]));
-  };
-  // The reference is the largest score so far; what has been summed against the old one is brought to the new one.  A reference ahead of the
-  // first block's scores, moved only when a probability outgrows it, spares most of this (200 random launches 0.987 of the time, 256^2 schedules the
-  // same, odd sides 0.98), but the largest probabilities then lie anywhere between two powers of two instead of just below one, where bf16 rounds
-  // them finest: 1.04 times the error against float64 over 128 to 300 keys, 1.1 (up to 1.2) over more.
-  auto follow = [&](const floatx4 (&sc)[2][NQ], bool nothing_yet) {
-    float m_new[NQ];
-    bool moved = false;
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-      float mx = sc[0][qt][0];
-#pragma unroll
-      for (int j = 1; j < 8; ++j) mx = maximum(mx, sc[j >> 2][qt][j & 3]);
-      m_new[qt] = maximum(mc[qt], quad_maximum(mx) * c2);
-      moved |= m_new[qt] != mc[qt];
-    }
-    if (!nothing_yet && __any(moved)) {
-#pragma unroll
-      for (int qt = 0; qt < NQ; ++qt) {
-        const float a = __builtin_amdgcn_exp2f(mc[qt] - m_new[qt]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          ls[qt][r] *= a;
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) o[mt][qt][r] *= a;
-        }
-      }
-    }
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) mc[qt] = m_new[qt];
-  };
-  auto pv = [&](const __bf16* Vt, const bf16x8 (&pf)[NQ], int mt) {
-    const bf16x4 v0 = lds_read_tr(&Vt[v_off[mt]]), v1 = lds_read_tr(&Vt[16 * D + v_off[mt]]);
-    const bf16x8 vf = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) o[mt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qt], o[mt][qt], 0, 0, 0);
-  };
-  auto row_sums = [&](const bf16x8 (&pf)[NQ]) {   // over the rounded probabilities, the numbers the PV product uses
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) ls[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qt], ls[qt], 0, 0, 0);
-  };
   auto append = [&] {
     if (!GATHER && fuse) {
       uintx4* kd = reinterpret_cast<uintx4*>(k_app) + (d.in_off + d.len_in + q0) * LPR;
@@ -385,24 +288,23 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
   };
   auto store = [&](int mt, int qt, const floatx4& x, float inv) {
     const int qi = q0 + 16 * qt + col;
-    const bf16x4 pk = {(__bf16)(x[0] * inv), (__bf16)(x[1] * inv), (__bf16)(x[2] * inv), (__bf16)(x[3] * inv)};
-    if (qi < N_k) *reinterpret_cast<bf16x4*>(out + (new_row0 + qi) * D + 16 * mt + 4 * g) = pk;
+    if (qi < N_k) att.store(out + (new_row0 + qi) * D, mt, x, inv);
   };
 
   if (lone) {
     floatx4 sc[2][NQ];
     bf16x8 pf[NQ];
-    scores(&ring[0][0][0], sc);
-    mask(sc, 0);
-    follow(sc, true);
-    probs(sc, pf);
-    row_sums(pf);
+    att.scores(&ring[0][0][0], qf, sc);
+    att.mask(sc, 0, total);
+    att.follow(sc, true);
+    att.probs(sc, pf);
+    att.row_sums(pf);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
       if (mt % kWaves == w) {
-        pv(&ring[0][1][0], pf, mt);
+        att.pv(&ring[0][1][0], pf, mt);
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) store(mt, qt, o[mt][qt], 1.f / ls[qt][0]);
+        for (int qt = 0; qt < NQ; ++qt) store(mt, qt, att.o[mt][qt], 1.f / att.ls[qt][0]);
       }
     append();
     return;
@@ -416,7 +318,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
     const bool more = b + kWaves < n_blocks;
     dma_wait_but<IPB>();                 // K(b) has landed (V(b) may still be in flight)
     floatx4 sc[2][NQ];
-    scores(&ring[w][0][0], sc);
+    att.scores(&ring[w][0][0], qf, sc);
     // the MFMAs above have consumed every K read, so the slot may be refilled;
     // nothing below moves above this point
     __builtin_amdgcn_sched_barrier(0);
@@ -425,15 +327,15 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
       if constexpr (GATHER) issue_x(b + 3 * kWaves);
       issue_k(b + kWaves, lds_of(w, 0));
     }
-    mask(sc, b);
+    att.mask(sc, b, total);
     bf16x8 pf[NQ];
-    follow(sc, b == w);
-    probs(sc, pf);
+    att.follow(sc, b == w);
+    att.probs(sc, pf);
     if (more) dma_wait_but<IPB + XI>();  // V(b) has landed (K(next) and list entries may still be in flight)
     else dma_wait_but<0>();
-    row_sums(pf);
+    att.row_sums(pf);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) pv(&ring[w][1][0], pf, mt);
+    for (int mt = 0; mt < MT; ++mt) att.pv(&ring[w][1][0], pf, mt);
     // every V read has been consumed by an MFMA above: the slot may be refilled
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
@@ -451,12 +353,12 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_split(
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) mine[(mt * NQ + qt) * 64] = make_float4(o[mt][qt][0], o[mt][qt][1], o[mt][qt][2], o[mt][qt][3]);
+    for (int qt = 0; qt < NQ; ++qt) mine[(mt * NQ + qt) * 64] = make_float4(att.o[mt][qt][0], att.o[mt][qt][1], att.o[mt][qt][2], att.o[mt][qt][3]);
   if (g == 0) {
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      m_sh[w][16 * qt + col] = mc[qt];
-      l_sh[w][16 * qt + col] = ls[qt][0];
+      m_sh[w][16 * qt + col] = att.mc[qt];
+      l_sh[w][16 * qt + col] = att.ls[qt][0];
     }
   }
   __syncthreads();

@@ -18,6 +18,7 @@
 #include "hack_internal.h"
 #include "score_device.h"
 #include "select_device.h"
+#include "split_stage.h"
 
 namespace hack {
 
@@ -149,27 +150,8 @@ __global__ __launch_bounds__(64 * kNW, D == 64 && TILES <= 2 && NQ == 1 ? 4 : 2)
     }
   }
 
-  int k_off[KC];   // K operand: row 16 kt + col, chunk 4 c + g
-#pragma unroll
-  for (int c = 0; c < KC; ++c) k_off[c] = col * D + (((4 * c + g) ^ swz_k<D>(col)) & (CPR - 1)) * 8;
-  const int e = col >> 2, qd = col & 3;
-  int v_off[MT];   // V^T operand: rows 4 g + e and 16 + 4 g + e, head-dim 16 mt + 4 qd
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-    v_off[mt] = (4 * g + e) * D + (((2 * mt + (qd >> 1)) ^ swz_v16<D>(4 * g + e)) & (CPR - 1)) * 8 + 4 * (qd & 1);
-  floatx4 o[MT][NQ], ls[NQ];
-  float mc[NQ];
-#pragma unroll
-  for (int qt = 0; qt < NQ; ++qt) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) o[mt][qt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    ls[qt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    mc[qt] = -FLT_MAX;
-  }
-  const float c2 = scale * kLog2eF;
-  bf16x8 ones;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.0f;
+  SplitStage<D, NQ> att;
+  att.init(scale, lane);
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
@@ -200,84 +182,26 @@ __global__ __launch_bounds__(64 * kNW, D == 64 && TILES <= 2 && NQ == 1 ? 4 : 2)
       const __bf16* const Kt = Kh + b * 32 * D;
       const __bf16* const Vt = Vh + b * 32 * D;
       floatx4 sc[2][NQ];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) sc[kt][qt] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < KC; ++c)
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-          const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kt[16 * kt * D + k_off[c]]);
-#pragma unroll
-          for (int qt = 0; qt < NQ; ++qt) sc[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[qt][c], sc[kt][qt], 0, 0, 0);
-        }
-      if ((b + 1) * 32 > n) {
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (b * 32 + 16 * kt + 4 * g + r >= n) {
-#pragma unroll
-              for (int qt = 0; qt < NQ; ++qt) sc[kt][qt][r] = -INFINITY;
-            }
-      }
       bf16x8 pf[NQ];
-      auto probs = [&] {
+      att.scores(Kt, qf, sc);
+      att.mask(sc, b, n);
+      att.follow(sc, b == split);
+      att.probs(sc, pf);
+      att.row_sums(pf);
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) pf[qt][j] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sc[j >> 2][qt][j & 3], c2, -mc[qt]));
-      };
-      {   // the reference is the largest score so far (see attn_split)
-        float m_new[NQ];
-        bool moved = false;
-#pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) {
-          float mx = sc[0][qt][0];
-#pragma unroll
-          for (int j = 1; j < 8; ++j) mx = maximum(mx, sc[j >> 2][qt][j & 3]);
-          m_new[qt] = maximum(mc[qt], quad_maximum(mx) * c2);
-          moved |= m_new[qt] != mc[qt];
-        }
-        if (b != split && __any(moved)) {
-#pragma unroll
-          for (int qt = 0; qt < NQ; ++qt) {
-            const float a = __builtin_amdgcn_exp2f(mc[qt] - m_new[qt]);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              ls[qt][r] *= a;
-#pragma unroll
-              for (int mt = 0; mt < MT; ++mt) o[mt][qt][r] *= a;
-            }
-          }
-        }
-#pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) mc[qt] = m_new[qt];
-      }
-      probs();
-#pragma unroll
-      for (int qt = 0; qt < NQ; ++qt) ls[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qt], ls[qt], 0, 0, 0);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const bf16x4 v0 = lds_read_tr(&Vt[v_off[mt]]), v1 = lds_read_tr(&Vt[16 * D + v_off[mt]]);
-        const bf16x8 vf = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-#pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) o[mt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qt], o[mt][qt], 0, 0, 0);
-      }
+      for (int mt = 0; mt < MT; ++mt) att.pv(Vt, pf, mt);
     }
   }
   auto store = [&](int mt, int qt, const floatx4& x, float inv) {
     const int qi = q0 + 16 * qt + col;
-    const bf16x4 pk = {(__bf16)(x[0] * inv), (__bf16)(x[1] * inv), (__bf16)(x[2] * inv), (__bf16)(x[3] * inv)};
-    if (qi < N_k) *reinterpret_cast<bf16x4*>(out + (new0 + qi) * D + 16 * mt + 4 * g) = pk;
+    if (qi < N_k) att.store(out + (new0 + qi) * D, mt, x, inv);
   };
   if constexpr (S == 1) {
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      const float inv = 1.f / ls[qt][0];
+      const float inv = 1.f / att.ls[qt][0];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) store(mt, qt, o[mt][qt], inv);
+      for (int mt = 0; mt < MT; ++mt) store(mt, qt, att.o[mt][qt], inv);
     }
     return;
   }
@@ -289,12 +213,12 @@ __global__ __launch_bounds__(64 * kNW, D == 64 && TILES <= 2 && NQ == 1 ? 4 : 2)
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) mine[(mt * NQ + qt) * 64] = make_float4(o[mt][qt][0], o[mt][qt][1], o[mt][qt][2], o[mt][qt][3]);
+    for (int qt = 0; qt < NQ; ++qt) mine[(mt * NQ + qt) * 64] = make_float4(att.o[mt][qt][0], att.o[mt][qt][1], att.o[mt][qt][2], att.o[mt][qt][3]);
   if (g == 0) {
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      m_sh[w * 32 + 16 * qt + col] = mc[qt];
-      l_sh[w * 32 + 16 * qt + col] = ls[qt][0];
+      m_sh[w * 32 + 16 * qt + col] = att.mc[qt];
+      l_sh[w * 32 + 16 * qt + col] = att.ls[qt][0];
     }
   }
   __syncthreads();
