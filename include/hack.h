@@ -339,8 +339,9 @@ hack_status hack_kvcache_reset(hack_kvcache* c);
 hack_status hack_kvcache_view(const hack_kvcache* c, hack_cache* view);
 /* The form of the step that led to the current state (reported, as hack_attn_variant,
  * so that measurements can be attributed to a kernel): queries per work-group (16 to
- * 256) of a compressing step that one launch serves; 0 where its stages are launches
- * of their own, for the empty cache and for a NULL cache. */
+ * 256) of a compressing step that one launch serves (where outputs share memory with
+ * inputs, scores and moves go in front of it in launches of their own); 0 where its
+ * stages are launches of their own, for the empty cache and for a NULL cache. */
 int32_t hack_kvcache_step_form(const hack_kvcache* c);
 
 /* One scale step for all units of a layer (Sec. 4.3: compression is applied

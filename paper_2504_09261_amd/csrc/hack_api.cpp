@@ -360,9 +360,11 @@ void build_attn_items(const std::vector<UnitDesc>& descs, int N_k, int tile_rows
 // 256, 1600 24.1 / 22.4, 76.6 / 78.6; 22.6 / 25.8, 45.0 / 41.5; 256, 1440 23.2 / 22.2, 73.1 / 76.9; 21.5 / 24.6, 41.4 / 40.8; 256, 1280 22.6 / 21.9,
 // 60.4 / 65.3; 20.4 / 23.6, 37.6 / 40.2.  In two rounds of them or part empty they lose: 576, 1980 31.1 / 31.5, 67.0 / 68.4; 32.0 / 34.9, 57.5 / 58.2;
 // 224, 1960 29.1 / 28.7, 94.6 / 97.9; 23.8 / 30.4, 51.9 / 51.0; 140, 2000 28.4 / 30.3, 128.5 / 142.3; 21.7 / 29.2, 49.6 / 60.0.
-// (With 32x32x16 products in the split kernel; with its present ones the line stands: head_dim 128, 32 units, 512 queries, compressing to 300 and
-// 1943 rows, appending to 2000 32.2 / 34.0, 55.6 / 56.4; 31.4 / 31.9; 576 35.6 / 33.1, 70.7 / 61.8; to 1500 32.3 / 29.5; head_dim 64, 256 queries, 1920 items,
-// compressing to 102 33.7 / 37.9, appending to 1500 48.8 / 38.4.)
+// (All with 32x32x16 products in the split kernel.  With its present ones, head_dim 128, 32 units, 512 queries, compressing to 300 and 1943 rows, appending
+// to 2000 25.4 / 26.1, 52.8 / 58.8; 30.0 / 36.5; 576 31.2 / 26.0, 72.1 / 59.6; to 1500 36.4 / 31.5: the line stands.  head_dim 64, 256 queries, compressing to 1200,
+// appending to 1500, 1920 items 75.8 / 82.8; 52.1 / 38.1; 1600 62.6 / 75.0; 50.2 / 36.0; 1440 67.8 / 70.2; 39.8 / 34.4: a compressing step would gain by the split kernel
+// what an appending one and more would lose, and one line serves both.  Compressing steps of short units, to 102 rows, mostly leave it: 24.8 / 19.9, in one
+// launch 16.2.)
 bool use_split_attention(const hack_ctx* ctx, int n_units, int N_k) {
   if (ctx->cfg.dtype != HACK_BF16) return false;
   const int tile = attn_split_q_tile_rows();

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kThreads, 2) void hv_rowstats(
   constexpr int KK = D / 16;
   __shared__ __attribute__((aligned(1024))) __bf16 ring[kRing][St::BLK];
   const UnitDesc d = descs[blockIdx.y];
-  if (blockIdx.x == 0 && threadIdx.x == 0) sigma[d.unit] = 0.0;   // pass 2 adds to it (a launch that cleared it cost 4 us)
+  if (blockIdx.x == 0 && threadIdx.x == 0) sigma[d.unit] = 0.0;   // pass 2 adds to it (a launch that cleared it took 1 to 3 us)
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int q0 = blockIdx.x * kTile1 + w * (32 * kRB1);   // may lie past N_k: the wave still copies and synchronises

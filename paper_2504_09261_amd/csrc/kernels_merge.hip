@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kThreads) void merge_apply(
     if (lane == 0) cnt[w] = n;
     __syncthreads();
     // The lists of waves 0..3 one after the other are in ascending row order: a fixed summation order per kept
-    // row.  A wave takes the entries of its 8 kept rows kFold at a time, whatever rows they go to: the loads of all of
+    // row.  A wave takes the entries of its RPW kept rows (2 or 8) kFold at a time, whatever rows they go to: the loads of all of
     // them are issued together, then each is added to its row.
     for (int q = 0; q < kWaves; ++q) {
       const int nq = cnt[q];

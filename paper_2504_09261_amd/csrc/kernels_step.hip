@@ -8,10 +8,10 @@
 // Work-groups of one unit (whole_step_queries says how many there are) repeat its scores and selection and share out queries and rows.
 //
 // These steps are chains of latencies.  As launches of their own (score and selection, then attention and moves, which start with the
-// table, the list, the rows from memory again) they took 13.9 us at 60 units of 64 queries over 166 keys and 38.5 + 32.5 us at 480 units of 562 keys and 480 of 358
-// (kernel trace); in one 8.8 and 58.  In-kernel time stamps, thousands of cycles, 60 units of 169 queries over 424 keys, 255 kept: scores 11.2, selection 4.7, row
-// copies 4.3, waiting for them 1.5, moves 0.9, attention 2.6, merge 6.3; with 32-bit row offsets where a copy's rows have one home and the number of
-// splits known to the compiler (a launch 21.4 -> 15.3 us) what is left is mostly the scores' vector work.
+// table, the list, the rows from memory again) they took 6.8 + 3.8 us at 60 units of 64 queries over 166 keys, 102 kept, and 23.0 + 39.7 us at 480 units of 256
+// over 562, 306 kept (kernel trace); in one 8.4 and 48.7.  In-kernel time stamps, thousands of cycles: 60 units of 169 queries over 424 keys, 255 kept, four
+// splits: scores 11.7, selection 5.4, row copies 2.0, waiting for them 0.4, moves 0.8, attention 2.7, merge 3.3 (a launch of 15.0 us); 480 units of 256 over 562, 306
+// kept, no splits: 16.3, 5.8, 2.8, 1.1, 2.0, 12.1, stores 1.0.  What is left is mostly the scores' vector work and the barriers of the ranking.
 #include <cfloat>
 
 #include "device_util.h"
